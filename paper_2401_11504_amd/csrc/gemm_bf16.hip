@@ -1,4 +1,4 @@
-// bf16 MFMA GEMMs for the LoRA-adapted linear layers (gfx950, v_mfma_f32_32x32x16_bf16).
+// bf16 MFMA GEMMs for the LoRA-adapted linear layers (gfx950).
 //
 //  gemm_nt : C = alpha (A B^T + A2 B2^T) (+ R)      both operand pairs are K-contiguous.
 //            Forward:  Y  = X W^T  + Hs B^T           (A2 = Hs = s X A^T, K2 = r)
@@ -155,13 +155,12 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmNT p, int tiles_m, int
 __global__ void splitk_reduce_kernel(GemmNT p, int split_k);
 
 // ======================================================================== NT, direct-to-LDS pipeline
-// Same contract as gemm_nt_kernel for K % 64 == 0 and K2 % 64 == 0.  Operand tiles go from global
-// memory straight into LDS (global_load_lds_dwordx4: each lane's 16 bytes land at M0 + 16 * lane), so a
-// ring of STAGES tiles is in flight without staging registers.  A tile row is 64 bf16 = 8 chunks of
-// 16 bytes; chunk c of row r is kept at position c ^ ((r / 2) % 8), chosen by which global chunk each
-// lane fetches.  The LDS serves 16 lanes x 16 bytes per clock from 64 banks, and two 128-byte rows span
-// the 64 banks once, so 16 consecutive rows reading the same logical chunk must land on 8 distinct
-// positions in the even rows and 8 in the odd rows: that is what the (r / 2) term gives.
+// Same contract as gemm_nt_kernel.  Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4: each
+// lane's 16 bytes land at M0 + 16 * lane), so whole rings of tiles are in flight without staging registers.  A tile row
+// is 64 bf16 = one 128-byte cache line = 8 chunks of 16 bytes; chunk c of row r is kept at position c ^ ((r / 2) % 8),
+// chosen by which global chunk each lane fetches.  The LDS serves 16 lanes x 16 bytes per clock from 64 banks, and two
+// rows span the 64 banks once, so 16 consecutive rows reading the same logical chunk must land on 8 distinct positions
+// in the even rows and 8 in the odd rows: that is what the (r / 2) term gives.
 // Rows beyond M / N are clamped to the last valid row: they only feed outputs that are never stored.
 __device__ __forceinline__ void load_lds16(unsigned voff, const void* sbase, unsigned lds_addr) {
     // M0 carries the LDS destination: bound as a physical-register operand, so the compiler sets it and knows it is used
@@ -170,6 +169,11 @@ __device__ __forceinline__ void load_lds16(unsigned voff, const void* sbase, uns
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// Accumulates in place, in accumulation registers.  As a builtin the compiler renames the accumulators of the 192- and
+// 128-column instances from one k-step to the next and moves every one of them (a quarter of the loop's issue slots).
+__device__ __forceinline__ void mfma16_acc(f32x4_t& c, bf16x8_t a, bf16x8_t b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
 // How a launch maps workgroup ids to tiles and contraction ranges, worked out on the host: the kernel's prologue is
@@ -197,34 +201,46 @@ static NtMap make_nt_map(int tiles_m, int tiles_n, int n_split, int batch, bool 
 }
 __device__ __forceinline__ unsigned div_by(unsigned n, unsigned inv) { return inv == 0 ? n : __umulhi(n, inv); }   // inv == 0 encodes d = 1
 
-template <int BM, int BN, int WM, int WN, int STAGES, int BKT = 64, bool SPLITK = false, int PIPE = 0>
-__global__ __launch_bounds__(WM* WN * 64) void gemm_nt_dl_kernel(GemmNT p, NtMap map) {
-    constexpr int NT = WM * WN * 64;
-    constexpr int ROWS = BM + BN;
-    constexpr int CPRW = BKT / 8;             // 16-byte chunks per tile row
-    constexpr int RP = 256 / (BKT * 2);       // tile rows per 256 bytes of LDS (one pass over the 64 banks)
-    constexpr int KS = BKT / 16;              // MFMA k-steps per tile
-    constexpr int L = ROWS * CPRW / NT;       // 16-byte loads per thread per stage
-    constexpr int LA = BM * CPRW / NT;        // the first LA of them fetch A rows
-    constexpr int ROWB = BKT * 2;             // bytes per tile row
-    constexpr int STAGE_BYTES = ROWS * ROWB;
-    constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 32, FN = TN / 32;
-    static_assert((ROWS * CPRW) % NT == 0 && (BM * CPRW) % NT == 0 && FM >= 1 && FN >= 1 && STAGES >= 2, "tile shape");
-    static_assert((STAGES - 2) * L <= 63, "vmcnt range");  // s_waitcnt vmcnt is a 6-bit field
-    static_assert(BKT == 64 || BKT == 32, "tile depth");
+// Four waves, each with a (BM / 2) x (BN / 2) share of the tile, one wave per SIMD for the large tiles.
+//
+// The order of the contraction: first the "edge" tiles -- the low-rank pair A2 B2^T, and the last K % 64 elements of
+// A B^T -- then the whole 64-wide tiles of A B^T.  Edge tiles may be narrower than 64 and, where the column groups of a
+// product share a tile (GemmNT::grp_cols), need part of their B rows left out: lanes with nothing to fetch store zeros to
+// LDS instead.  With the usual ranks they are all fetched by the prologue, and the loop proper fetches only whole tiles
+// through pointers that advance by a constant.
+//
+// The A operand has AST tiles of LDS, the B operand (the weights, which come from HBM) one more: a tile of B is fetched
+// AST tiles ahead of its use during the first k-step, a tile of A at the end of the tile whose place it takes.  One
+// barrier per tile ("hand-over"): before the second k-step every wave has read the whole tile (its places may be
+// refilled) and the next tile has landed.  Nothing is issued in bursts: the fragments of the next k-step and the fetches
+// are spread between the MFMAs, at most as fast as the LDS (one 16-byte read per wave and three MFMAs) and the address
+// unit take them, so that the matrix pipe is what the wave waits for.
+//
+// Measured, M = 2048, N = 32000, K = 4096, weights cold: 455 us (1180 TFLOP/s) with 256x256 tiles of eight waves,
+// v_mfma_f32_32x32x16_bf16, a barrier every 32 contraction elements; 413 us with four waves and one barrier every 64;
+// 370 us (1450 TFLOP/s) with v_mfma_f32_16x16x32_bf16, which draws less power (the chip is power-limited here: it then
+// runs at 2.0 instead of 1.8 GHz), and the reads spread over the k-step.
+template <int BM, int BN, int AST, bool SPLITK>
+__global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map) {
+    constexpr int NT = 256, BST = AST + 1;
+    constexpr int ROWB = BK * 2;                                // bytes per tile row
+    constexpr int LA = BM * 8 / NT, LB = BN * 8 / NT;           // 16-byte fetches per thread per tile
+    constexpr int A_STAGE = BM * ROWB, B_STAGE = BN * ROWB, B_RING = AST * A_STAGE;
+    constexpr int TM = BM / 2, TN = BN / 2, FM = TM / 16, FN = TN / 16;
+    static_assert(LA >= 1 && LB >= 1 && FM >= 1 && FN >= 1 && AST >= 2, "tile shape");
     extern __shared__ __align__(16) unsigned char smem[];
     const unsigned lds0 = (unsigned)(size_t)smem;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    const int l32 = lane & 31, g = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int l16 = lane & 15, g = lane >> 4;
 
     // Workgroup ids go round-robin over the 8 XCDs (x fastest, then y), each with its own L2: XCD c gets a contiguous
     // range of tiles (m fastest), so that its CUs share weight rows.  With the contraction split 2, 4 or 8 ways the
     // XCD also fixes the split: XCD c works on split c / (8 / n_split) only, so an XCD fetches just its share of the
     // contraction range of the activations instead of all of it.
-    const int tiles_m = map.tiles_m, tiles_n = map.tiles_n;
-    const int ntiles = tiles_m * tiles_n;
+    const int tiles_m = map.tiles_m;
+    const int ntiles = tiles_m * map.tiles_n;
     const int n_split = SPLITK ? (int)gridDim.y : 1;
     int pid = blockIdx.x, split = SPLITK ? (int)blockIdx.y : 0;
     if (SPLITK && map.xcd_split) {
@@ -242,362 +258,335 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_nt_dl_kernel(GemmNT p, NtMap
     const bf16_t* B = p.B + (long)z * p.bB;
     const bf16_t* A2 = p.A2 ? p.A2 + (long)z * p.bA2 : nullptr;
     const bf16_t* B2 = p.B2 ? p.B2 + (long)z * p.bB2 : nullptr;
-    const int nk1 = p.K / BKT, nk2 = p.K2 / BKT;
-    // with SPLITK, n_split workgroups share one output tile: this one takes k-tiles [kt0, kt0 + nk)
-    const int kt0 = SPLITK ? (int)div_by((unsigned)((nk1 + nk2) * split), map.inv_n_split) : 0;
-    const int nk = (SPLITK ? (int)div_by((unsigned)((nk1 + nk2) * (split + 1)), map.inv_n_split) : nk1 + nk2) - kt0;
-
-    // per-thread byte offsets of its L chunks, for the main and the low-rank operand pair
-    unsigned vo1[L], vo2[L];
-#pragma unroll
-    for (int j = 0; j < L; ++j) {
-        const int q = j * NT + tid, r = q / CPRW, c = (q % CPRW) ^ ((r / RP) % CPRW);
-        // 32-bit arithmetic: the launcher only takes this path for operands below 2^30 elements
-        if (j < LA) {
-            const unsigned row = (unsigned)min(m0 + r, p.M - 1);
-            vo1[j] = (row * (unsigned)p.lda + c * 8) * 2;
-            vo2[j] = (row * (unsigned)p.lda2 + c * 8) * 2;
-        } else {
-            const unsigned row = (unsigned)min(n0 + r - BM, p.N - 1);
-            vo1[j] = (row * (unsigned)p.ldb + c * 8) * 2;
-            vo2[j] = (row * (unsigned)p.ldb2 + c * 8) * 2;
-        }
+    // edge tiles: the low-rank pair (once per column group that this tile touches), then the ragged end of the main pair
+    const int per_grp = (p.K2 + BK - 1) / BK;
+    int grp0 = 0, n_grp = 1;
+    if (p.grp_cols > 0) {
+        grp0 = (p.col0 + n0) / p.grp_cols;
+        n_grp = (p.col0 + min(n0 + BN, p.N) - 1) / p.grp_cols - grp0 + 1;
     }
-    auto issue = [&](int ktl) {
-        const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + (ktl % STAGES) * STAGE_BYTES + wave * 1024);
-        const int kt = kt0 + ktl;
-        if (kt < nk1) {
-            const bf16_t* ba = A + (long)kt * BKT;
-            const bf16_t* bb = B + (long)kt * BKT;
+    const int n_low = per_grp * n_grp, nk1 = p.K / BK;
+    const int n_edge_all = n_low + ((p.K & (BK - 1)) ? 1 : 0), nk_all = n_edge_all + nk1;
+    // with SPLITK, n_split workgroups share one output tile: this one takes tiles [kt0, kt0 + nk) of that order
+    const int kt0 = SPLITK ? (int)div_by((unsigned)(nk_all * split), map.inv_n_split) : 0;
+    const int nk = (SPLITK ? (int)div_by((unsigned)(nk_all * (split + 1)), map.inv_n_split) : nk_all) - kt0;
+    const int n_edge = max(0, min(nk, n_edge_all - kt0));
+    const bf16_t* Am = A + (long)max(0, kt0 - n_edge_all) * BK;       // first whole tile of this workgroup
+    const bf16_t* Bm = B + (long)max(0, kt0 - n_edge_all) * BK;
+
+    // byte offsets of this thread's chunks within a tile of the main pair; its logical chunk is the same in every row
+    const int chunk = (tid & 7) ^ ((tid >> 4) & 7), trow = tid >> 3;
+    unsigned va[LA], vb[LB];
 #pragma unroll
-            for (int j = 0; j < L; ++j) load_lds16(vo1[j], j < LA ? (const void*)ba : (const void*)bb, dst + j * NT * 16);
+    for (int j = 0; j < LA; ++j)   // 32-bit arithmetic: the launcher only takes this path for operands below 2^30 elements
+        va[j] = ((unsigned)min(m0 + trow + 32 * j, p.M - 1) * (unsigned)p.lda + chunk * 8) * 2;
+#pragma unroll
+    for (int j = 0; j < LB; ++j)
+        vb[j] = ((unsigned)min(n0 + trow + 32 * j, p.N - 1) * (unsigned)p.ldb + chunk * 8) * 2;
+    const unsigned wdst = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
+
+    // fetch an edge tile's A rows or B rows (t counts from this workgroup's first tile); zeros where there is nothing
+    auto fetch_edge = [&](int t, auto side, unsigned slot) {
+        constexpr bool b_side = decltype(side)::value;
+        const int e = kt0 + t;
+        int valid, lo = 0, hi = p.N;          // valid chunks; columns that take part
+        const bf16_t* src;
+        long ld;
+        if (e < n_low) {
+            const int gi = e / per_grp, k0 = (e - gi * per_grp) * BK;
+            valid = min(BK, p.K2 - k0) >> 3;
+            if (p.grp_cols > 0) { lo = (grp0 + gi) * p.grp_cols - p.col0; hi = lo + p.grp_cols; }
+            src = b_side ? B2 + k0 : A2 + (long)(grp0 + gi) * p.bA2_grp + k0;
+            ld = b_side ? p.ldb2 : p.lda2;
         } else {
-            const bf16_t* ba = A2 + (long)(kt - nk1) * BKT;
-            const bf16_t* bb = B2 + (long)(kt - nk1) * BKT;
+            valid = (p.K & (BK - 1)) >> 3;
+            src = (b_side ? B : A) + (long)nk1 * BK;
+            ld = b_side ? p.ldb : p.lda;
+        }
+        const int r0 = (b_side ? n0 : m0) + trow, last = (b_side ? p.N : p.M) - 1;
 #pragma unroll
-            for (int j = 0; j < L; ++j) load_lds16(vo2[j], j < LA ? (const void*)ba : (const void*)bb, dst + j * NT * 16);
+        for (int j = 0; j < (b_side ? LB : LA); ++j) {
+            const int row = min(r0 + 32 * j, last);
+            const unsigned dst = slot + wave * 1024 + j * NT * 16;      // LDS offset of this wave's 64 chunks
+            if (chunk < valid && (!b_side || (row >= lo && row < hi)))
+                load_lds16(((unsigned)row * (unsigned)ld + chunk * 8) * 2, src, __builtin_amdgcn_readfirstlane(lds0 + dst));
+            else
+                *(uint4*)(smem + dst + lane * 16) = make_uint4(0, 0, 0, 0);
         }
     };
 
-    f32x16_t acc[FM][FN];
+    using T_ = std::true_type; using F_ = std::false_type;
+    f32x4_t acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = zero16();
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    // fragment read offsets: row (w*T + l32) -> swizzle (l32 / RP) % CPRW; chunk (2 ks + g) ^ swizzle
-    int coff[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) coff[ks] = (((2 * ks + g) ^ ((l32 / RP) % CPRW)) << 4);
-    const int a_row = (wm * TM + l32) * ROWB, b_row = (BM + wn * TN + l32) * ROWB;
+    // fragment reads: row (w * T + l16), chunk 4 ks + g, swizzled by the row
+    const int coff0 = (g ^ (l16 >> 1)) << 4, coff1 = ((4 + g) ^ (l16 >> 1)) << 4;
+    const unsigned char* a_ptr = smem + (wm * TM + l16) * ROWB;
+    const unsigned char* b_ptr = smem + B_RING + (wn * TN + l16) * ROWB;
+    constexpr int NMF = FM * FN, NRD = FM + FN;
+    constexpr int RSP = NMF / NRD >= 3 ? 3 : NMF >= 32 ? 2 : 1;           // MFMAs per fragment read
+    constexpr int BSP = NMF / LB >= 6 ? 6 : NMF / LB, ASP = NMF / LA;     // MFMAs per fetch
+    static_assert(BSP >= 1 && ASP >= 1 && RSP * NRD <= NMF, "every read and fetch of a k-step has a slot");
 
-    if constexpr (PIPE != 0) {
-        // One wave per SIMD: the matrix pipe only stays busy if the wave never waits, so inside the steady-state
-        // loop nothing is issued in bursts.  Tile kt+STAGES-1 is fetched during iteration kt, its 16-byte
-        // global->LDS loads spread evenly between the MFMAs (a burst of L loads would hold the wave at the address
-        // unit for hundreds of clocks), and the fragments of the k-step PD steps ahead are read one per MFMA slot
-        // while the current k-step's MFMAs run (PD = PIPE; with 64x64 wave tiles a k-step is only 128 clocks of
-        // MFMA, less than an LDS round trip under load, hence PD = 2 there).  The loop body has no branches; the
-        // last STAGES-1 tiles, which fetch nothing, run in a peeled tail.  The host only picks this path for
-        // nk >= STAGES.
-        constexpr int PD = PIPE, NSETS = PD == 1 ? 2 : 4, HS = KS - PD;   // hand-over happens before k-step HS
-        static_assert(PD == 1 || (PD == 2 && KS == 4), "prefetch distance");
-        static_assert(STAGES >= 3 && KS * FM * FN >= L && KS % NSETS == 0, "slots");
-        constexpr int NMF = FM * FN, NRD = FM + FN, NSLOT = KS * NMF, RPS = (NRD + NMF - 1) / NMF;
-        // load j of a tile goes into slot j * NSLOT / L; LBH = loads issued before the hand-over
-        constexpr int LBH = (HS * NMF * L + NSLOT - 1) / NSLOT;
-        const unsigned char* a_ptr = smem + a_row;
-        const unsigned char* b_ptr = smem + b_row;
-        bf16x8_t fa[NSETS][FM], fb[NSETS][FN];
-        // one k-step: NMF MFMAs on fragment set ks % NSETS; the slot after MFMA e carries one fragment read of the
-        // k-step PD ahead (RPS per slot until all NRD are issued); the tile's L DMA loads are spread evenly over its KS * NMF slots
-        auto kstep = [&](auto loads_c, unsigned ext, auto reads_c, int ks, size_t rd_stage, int rd_ks,
-                         const bf16_t* pa, const bf16_t* pb, unsigned dst) {
-            constexpr bool LOADS = decltype(loads_c)::value, READS = decltype(reads_c)::value;
-            const int cur = ks % NSETS, nxt = (ks + PD) % NSETS;
+    // prologue: the first AST tiles of both operands (rolled: code that a launch jumps over is an instruction-cache miss)
+#pragma unroll 1
+    for (int s = 0; s < min(AST, nk); ++s) {
+        const unsigned as = s * A_STAGE, bs = B_RING + s * B_STAGE;
+        if (s < n_edge) {
+            fetch_edge(s, F_{}, as);
+            fetch_edge(s, T_{}, bs);
+        } else {
+            const bf16_t *pa = Am + (long)(s - n_edge) * BK, *pb = Bm + (long)(s - n_edge) * BK;
 #pragma unroll
-            for (int e = 0; e < NMF; ++e) {
-                acc[e / FN][e % FN] = mfma32(fa[cur][e / FN], fb[cur][e % FN], acc[e / FN][e % FN]);
-                if constexpr (READS) {
-                    // RPS reads per slot, in the order A0, B0..B(FN-1), A1..: what that k-step's first MFMAs need first
+            for (int j = 0; j < LA; ++j) load_lds16(va[j], pa, wdst + as + j * NT * 16);
 #pragma unroll
-                    for (int r = e * RPS; r < (e + 1) * RPS && r < NRD; ++r) {
-                        if (r == 0) fa[nxt][0] = *(const bf16x8_t*)(a_ptr + rd_stage + coff[rd_ks]);
-                        else if (r <= FN) fb[nxt][r - 1] = *(const bf16x8_t*)(b_ptr + rd_stage + (r - 1) * 32 * ROWB + coff[rd_ks]);
-                        else fa[nxt][r - FN] = *(const bf16x8_t*)(a_ptr + rd_stage + (r - FN) * 32 * ROWB + coff[rd_ks]);
-                    }
+            for (int j = 0; j < LB; ++j) load_lds16(vb[j], pb, wdst + bs + j * NT * 16);
+        }
+    }
+    bf16x8_t fa[2][FM], fb[2][FN];
+    unsigned sa = 0, sb = 0, sbw = AST * B_STAGE;     // LDS offsets: the current tile's places, the place of B to fill
+    // wait until at most the fetches of the r youngest tiles are outstanding (exact: those are whole tiles, A before B)
+    auto wait_tiles = [&](int r) {
+        static_assert((AST - 1) * (LA + LB) <= 63, "s_waitcnt vmcnt is a 6-bit field");
+        if (r <= 0) wait_vmcnt<0>();
+        else if (r == 1 || AST == 2) wait_vmcnt<LA + LB>();
+        else if (r == 2 || AST == 3) wait_vmcnt<(AST > 2 ? 2 : 1) * (LA + LB)>();
+        else wait_vmcnt<(AST - 1) * (LA + LB)>();
+    };
+    // tile 0 has landed; an edge tile in the prologue may have skipped lanes, so its fetches cannot be counted
+    wait_tiles(n_edge == 0 ? min(nk, AST) - 1 : 0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (nk > 0) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i) fa[0][i] = *(const bf16x8_t*)(a_ptr + i * 16 * ROWB + coff0);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) fb[0][j] = *(const bf16x8_t*)(b_ptr + j * 16 * ROWB + coff0);
+    }
+
+    // One k-step on fragment set CUR: the slot behind MFMA e carries one fragment read of the next k-step (in the order
+    // A0, B0 .. B(FN-1), A1 ..: what its first MFMAs need first) and, if FETCH, one fetch of the operand whose place is free:
+    // B during the first k-step of a tile, A during the second.
+    auto kstep = [&](auto cur_c, auto reads_c, auto fetch_c, const unsigned char* ra, const unsigned char* rb,
+                     const bf16_t* src, unsigned dst) {
+        constexpr int CUR = decltype(cur_c)::value, NXT = CUR ^ 1;
+        constexpr bool READS = decltype(reads_c)::value, FETCH = decltype(fetch_c)::value;
+#pragma unroll
+        for (int e = 0; e < NMF; ++e) {
+            // operands swapped: lane (l16, g) then holds row l16, columns 4 g .. 4 g + 3 of the fragment
+            mfma16_acc(acc[e / FN][e % FN], fb[CUR][e % FN], fa[CUR][e / FN]);
+            if constexpr (READS) {
+                if (e % RSP == 0 && e / RSP < NRD) {
+                    const int r = e / RSP;
+                    if (r == 0) fa[NXT][0] = *(const bf16x8_t*)ra;
+                    else if (r <= FN) fb[NXT][r - 1] = *(const bf16x8_t*)(rb + (r - 1) * 16 * ROWB);
+                    else fa[NXT][r - FN] = *(const bf16x8_t*)(ra + (r - FN) * 16 * ROWB);
                 }
-                if constexpr (LOADS) {
-                    const int gs = ks * NMF + e;          // slot number within the tile
-                    const int j = (gs * L + NSLOT - 1) / NSLOT;   // first load with j * NSLOT / L >= gs
-                    if (j < L && j * NSLOT / L == gs) {
-                        // vo2 - vo1 is folded in arithmetically (ext is 0 or 1, wave-uniform): one loop body serves both pairs
-                        load_lds16(vo1[j] + ext * vo2[j], j < LA ? (const void*)pa : (const void*)pb, dst + j * NT * 16);
-                    }
+            }
+            if constexpr (FETCH) {
+                if constexpr (CUR == 0) {
+                    if (e % BSP == (BSP > 1 ? 1 : 0) && e / BSP < LB) load_lds16(vb[e / BSP], src, dst + (e / BSP) * NT * 16);
+                } else {
+                    if (e % ASP == (ASP > 1 ? 1 : 0) && e / ASP < LA) load_lds16(va[e / ASP], src, dst + (e / ASP) * NT * 16);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    using C0 = std::integral_constant<int, 0>; using C1 = std::integral_constant<int, 1>;
+    const bf16_t *pa = Am + (long)max(0, AST - n_edge) * BK, *pb = Bm + (long)max(0, AST - n_edge) * BK;   // next whole tiles to fetch
+    // fetches that may still be outstanding at the hand-over of a steady-state tile (the younger tiles')
+    constexpr int HW = (AST - 1) * LB + (AST - 2) * LA;
+    static_assert(HW <= 63, "s_waitcnt vmcnt is a 6-bit field");
+    // the last AST tiles fetch nothing, and the tiles still in flight can be counted unless they are edge tiles from the
+    // loop for those
+    const bool counted = n_edge <= AST || nk >= n_edge + AST;
+    auto next = [](unsigned s, unsigned stage, unsigned ring) { return s + stage == ring ? 0u : s + stage; };
+    // MODE 2: fetch whole tiles; 1: fetch edge tiles; 0: fetch nothing (the last AST tiles)
+    auto tile = [&](auto mode_c, auto last_c, int kt) {
+        constexpr int MODE = decltype(mode_c)::value;
+        constexpr bool LAST = decltype(last_c)::value;
+        const unsigned char *ra = a_ptr + sa, *rb = b_ptr + sb;
+        using FETCH = std::integral_constant<bool, MODE == 2>;
+        if constexpr (MODE == 1) fetch_edge(kt + AST, T_{}, B_RING + sbw);
+        kstep(C0{}, T_{}, FETCH{}, ra + coff1, rb + coff1, pb, wdst + B_RING + sbw);
+        const unsigned da = wdst + sa, sa_old = sa;
+        sa = next(sa, A_STAGE, AST * A_STAGE);
+        sb = next(sb, B_STAGE, BST * B_STAGE);
+        sbw = next(sbw, B_STAGE, BST * B_STAGE);
+        if constexpr (!LAST) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if constexpr (MODE == 2) wait_vmcnt<HW>(); else wait_tiles(MODE == 0 && counted ? nk - 2 - kt : 0);
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if constexpr (MODE == 1) fetch_edge(kt + AST, F_{}, sa_old);
+            kstep(C1{}, T_{}, FETCH{}, a_ptr + sa + coff0, b_ptr + sb + coff0, pa, da);
+        } else {
+            kstep(C1{}, F_{}, F_{}, ra, rb, pa, da);
+        }
+        if constexpr (MODE == 2) { pa += BK; pb += BK; }
+    };
+    int kt = 0;
+    // more edge tiles than the prologue fetches (ranks above 128): their hand-overs wait for everything in flight
+    for (; kt < n_edge - AST; ++kt) tile(C1{}, F_{}, kt);
+    for (; kt < nk - AST; ++kt) tile(std::integral_constant<int, 2>{}, F_{}, kt);
+    for (; kt < nk - 1; ++kt) tile(C0{}, F_{}, kt);
+    if (nk > 0) tile(C0{}, T_{}, kt);
+
+    // Ordinary instructions read the accumulators from here on.  The compiler does not see the matrix instructions inside
+    // the asm statements, so the wait for their last results is spelled out, and every accumulator passes through a
+    // statement behind it so that no read can be moved in front.
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[i][j]));
+
+    // Output.  A lane holds four neighbouring columns of one row per fragment; each wave turns its share of the tile around
+    // in LDS so that rows leave as 16-byte pieces of TN contiguous columns.  The stores run in a rolled loop: unrolled over
+    // the fragments with their bounds checks they were 50 KB of code.  (LDS operations of one wave execute in order, so the
+    // slab needs no waits of its own.)
+    __builtin_amdgcn_s_barrier();  // every wave is done reading operand tiles
+    asm volatile("" ::: "memory");
+    // (lane numbers formed anew: kept across the loop they cost the 256x256 instance a spill, and with it a scratch allocation)
+    const int elane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), el16 = elane & 15, eg = elane >> 4;
+    const int row0 = m0 + wm * TM, col0 = n0 + wn * TN;
+    const bool whole = m0 + BM <= p.M && n0 + BN <= p.N;       // workgroup-uniform: no bounds checks
+    constexpr int LDS_BYTES = AST * A_STAGE + BST * B_STAGE;
+    bool bf16_out = !p.c_f32;
+    if constexpr (SPLITK) bf16_out = p.partial_bf16 != 0;
+    if (!bf16_out) {
+        // fp32: each split stores its raw tile (splitk_reduce_kernel or the consumer adds the splits in index order
+        // afterwards: device-wide fences inside a kernel cost a full L2 write-back on this chip), or C = alpha acc (+ R)
+        constexpr int SLD = TN + 4, CPR = TN / 4;
+        constexpr int PI = 4 * TM * SLD * 4 <= LDS_BYTES ? FM : FM / 2;      // fragment rows per pass
+        static_assert(4 * PI * 16 * SLD * 4 <= LDS_BYTES && FM % PI == 0, "the output slab fits");
+        float* slab = (float*)smem + wave * PI * 16 * SLD;
+        float* C;
+        const float* R = nullptr;
+        long ldc;
+        float alpha = 1.f;
+        if constexpr (SPLITK) {
+            C = p.partial + ((long)z * n_split + split) * (long)p.M * p.N;
+            ldc = p.N;
+        } else {
+            C = (float*)p.C + (long)z * p.bC;
+            if (p.R) R = p.R + (long)z * p.bC;
+            ldc = p.ldc;
+            alpha = p.alpha;
+        }
+        const bool vec = (ldc & 3) == 0 && (((size_t)C | (size_t)R) & 15) == 0;
+#pragma unroll
+        for (int i0 = 0; i0 < FM; i0 += PI) {
+#pragma unroll
+            for (int i = 0; i < PI; ++i) {
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    const f32x4_t v = acc[i0 + i][j];
+                    *(float4*)(slab + (i * 16 + el16) * SLD + j * 16 + 4 * eg) =
+                        make_float4(alpha * v[0], alpha * v[1], alpha * v[2], alpha * v[3]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-        };
-        // one tile; HW = loads that may still be outstanding at the hand-over so that tile kt+1 has landed
-        auto tile = [&](auto loads_c, auto hw_c, auto last_c, int kt) {
-            constexpr int HW = decltype(hw_c)::value;
-            constexpr bool LAST = decltype(last_c)::value;
-            const int tn = kt + STAGES - 1;
-            const int ktn = kt0 + tn;
-            const unsigned ext_c = ktn >= nk1 ? 1u : 0u;
-            const bf16_t* pa = ext_c ? A2 + (long)(ktn - nk1) * BKT : A + (long)ktn * BKT;
-            const bf16_t* pb = ext_c ? B2 + (long)(ktn - nk1) * BKT : B + (long)ktn * BKT;
-            const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + (tn % STAGES) * STAGE_BYTES + wave * 1024);
-            const size_t st_cur = (size_t)(kt % STAGES) * STAGE_BYTES, st_nxt = (size_t)((kt + 1) % STAGES) * STAGE_BYTES;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                if (ks < HS) {
-                    kstep(loads_c, ext_c, std::true_type{}, ks, st_cur, ks + PD, pa, pb, dst);
-                } else if constexpr (!LAST) {
-                    if (ks == HS) {
-                        // hand-over: every wave's reads of this tile are complete (so its buffer may be refilled from
-                        // the next iteration on) and tile kt+1 has landed for every wave
-                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                        wait_vmcnt<HW>();
-                        __builtin_amdgcn_s_barrier();
-                        asm volatile("" ::: "memory");
+            __builtin_amdgcn_wave_barrier();
+            auto store4 = [&](int c, bool check) {
+                const int r = c / CPR, cc = (c % CPR) * 4;
+                const int row = row0 + i0 * 16 + r, col = col0 + cc;
+                if (check && (row >= p.M || col >= p.N)) return;
+                const long off = (long)row * ldc + col;
+                float4 v = *(const float4*)(slab + r * SLD + cc);
+                if (!check || (vec && col + 4 <= p.N)) {
+                    if (R) {
+                        const float4 q = *(const float4*)(R + off);
+                        v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
                     }
-                    kstep(loads_c, ext_c, std::true_type{}, ks, st_nxt, ks + PD - KS, pa, pb, dst);
+                    *(float4*)(C + off) = v;
                 } else {
-                    kstep(std::false_type{}, 0u, std::false_type{}, ks, 0, 0, pa, pb, dst);
+                    const float e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        if (col + x < p.N) C[off + x] = e[x] + (R ? R[off + x] : 0.f);
                 }
-            }
-        };
-#pragma unroll
-        for (int s = 0; s < STAGES - 1; ++s) issue(s);
-#pragma unroll
-        for (int j = 0; j < L; ++j) vo2[j] -= vo1[j];
-        wait_vmcnt<(STAGES - 2) * L>();
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-#pragma unroll
-        for (int ks = 0; ks < PD; ++ks) {
-#pragma unroll
-            for (int i = 0; i < FM; ++i) fa[ks][i] = *(const bf16x8_t*)(a_ptr + i * 32 * ROWB + coff[ks]);
-#pragma unroll
-            for (int j = 0; j < FN; ++j) fb[ks][j] = *(const bf16x8_t*)(b_ptr + j * 32 * ROWB + coff[ks]);
-        }
-        // at the hand-over of a steady-state tile, tile kt+2.. and the LBH loads of tile kt+STAGES-1 issued
-        // so far may be outstanding
-        constexpr int HW_STEADY = (STAGES - 3) * L + LBH;
-        static_assert(HW_STEADY <= 63, "vmcnt range");
-        using T_ = std::true_type; using F_ = std::false_type;
-        int kt = 0;
-        // (vo2 now holds the difference to vo1, see kstep)
-        for (; kt + STAGES - 1 < nk; ++kt) tile(T_{}, std::integral_constant<int, HW_STEADY>{}, F_{}, kt);
-        // tail: tiles nk-STAGES+1 .. nk-1 fetch nothing; with r tiles after this one, r-1 of them may be in flight
-        auto tail = [&](auto self, auto r_c) -> void {
-            constexpr int R = decltype(r_c)::value;
-            if constexpr (R > 0) {
-                tile(F_{}, std::integral_constant<int, (R - 1) * L>{}, F_{}, kt);
-                ++kt;
-                self(self, std::integral_constant<int, R - 1>{});
+            };
+            if (whole && vec) {
+#pragma unroll 4
+                for (int c = elane; c < PI * 16 * CPR; c += 64) store4(c, false);
             } else {
-                tile(F_{}, std::integral_constant<int, 0>{}, T_{}, kt);
+#pragma unroll 2
+                for (int c = elane; c < PI * 16 * CPR; c += 64) store4(c, true);
             }
-        };
-        tail(tail, std::integral_constant<int, STAGES - 2>{});
-    } else if constexpr (STAGES >= 3) {
-#pragma unroll
-        for (int s = 0; s < STAGES - 1; ++s)
-            if (s < nk) issue(s);
-        // Software pipeline: the fragments of k-step ks+1 are read while the MFMAs of ks run, and the
-        // hand-over to the next tile (wait, barrier, next global loads, first fragments) happens before
-        // the last k-step's MFMAs, so the matrix pipe never waits for LDS at a tile boundary.
-        auto read_frags = [&](int stage, int ks, bf16x8_t* fa, bf16x8_t* fb) {
-            const unsigned char* st = smem + stage * STAGE_BYTES;
-#pragma unroll
-            for (int i = 0; i < FM; ++i) fa[i] = *(const bf16x8_t*)(st + a_row + i * 32 * ROWB + coff[ks]);
-#pragma unroll
-            for (int j = 0; j < FN; ++j) fb[j] = *(const bf16x8_t*)(st + b_row + j * 32 * ROWB + coff[ks]);
-        };
-        if (STAGES - 2 < nk) wait_vmcnt<(STAGES - 2) * L>(); else wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        bf16x8_t fa[2][FM], fb[2][FN];
-        read_frags(0, 0, fa[0], fb[0]);
-        for (int kt = 0; kt < nk; ++kt) {
-            const int stg = kt % STAGES;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int cur = ks & 1, nxt = cur ^ 1;
-                if (ks < KS - 1) {
-                    read_frags(stg, ks + 1, fa[nxt], fb[nxt]);
-                } else if (kt + 1 < nk) {
-                    if (kt + STAGES - 2 < nk) wait_vmcnt<(STAGES - 3) * L>(); else wait_vmcnt<0>();
-                    __builtin_amdgcn_s_barrier();
-                    asm volatile("" ::: "memory");
-                    if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1);
-                    read_frags((kt + 1) % STAGES, 0, fa[nxt], fb[nxt]);
-                }
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j) acc[i][j] = mfma32(fa[cur][i], fb[cur][j], acc[i][j]);
-            }
+            __builtin_amdgcn_wave_barrier();
         }
     } else {
-#pragma unroll
-        for (int s = 0; s < STAGES - 1; ++s)
-            if (s < nk) issue(s);
-        for (int kt = 0; kt < nk; ++kt) {
-            // tile kt has landed once at most the loads of the STAGES-2 younger tiles are outstanding
-            if (kt + STAGES - 2 < nk) wait_vmcnt<(STAGES - 2) * L>(); else wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1);   // into the buffer every wave finished reading last iteration
-            const unsigned char* st = smem + (kt % STAGES) * STAGE_BYTES;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                bf16x8_t fa[FM], fb[FN];
-#pragma unroll
-                for (int i = 0; i < FM; ++i) fa[i] = *(const bf16x8_t*)(st + a_row + i * 32 * ROWB + coff[ks]);
-#pragma unroll
-                for (int j = 0; j < FN; ++j) fb[j] = *(const bf16x8_t*)(st + b_row + j * 32 * ROWB + coff[ks]);
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j) acc[i][j] = mfma32(fa[i], fb[j], acc[i][j]);
-            }
+        // bf16: C = alpha acc, or (a split whose consumer adds the tiles up itself and asked for bf16 ones) this split's
+        // tile, unscaled, in its [M, N] slice of the scratch
+        constexpr int SLD = TN + 8, CPR = TN / 8;
+        static_assert(4 * TM * SLD * 2 <= LDS_BYTES, "the output slab fits");
+        bf16_t* slab = (bf16_t*)smem + wave * TM * SLD;
+        bf16_t* C = (bf16_t*)p.C + (long)z * p.bC;
+        long ldc = p.ldc;
+        float alpha = p.alpha;
+        if constexpr (SPLITK) {
+            C = (bf16_t*)p.partial + ((long)z * n_split + split) * (long)p.M * p.N;
+            ldc = p.N;
+            alpha = 1.f;
         }
-    }
-
-    bool bf16_partials = false;
-    if constexpr (SPLITK) bf16_partials = p.partial_bf16 != 0;
-    if (SPLITK && !bf16_partials) {
-        // each split stores its fp32 tile; splitk_reduce_kernel adds the splits in index order afterwards
-        // (a second launch: device-wide fences inside a kernel cost a full L2 write-back on this chip)
-        float* part = p.partial + ((long)z * n_split + split) * (long)p.M * p.N;
-        if (m0 + BM <= p.M && n0 + BN <= p.N) {
-            // a whole tile (workgroup-uniform): no bounds checks, one base address per lane
-            float* base = part + (long)(m0 + wm * TM + 4 * g) * p.N + n0 + wn * TN + l32;
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        base[(long)(i * 32 + 8 * (v >> 2) + (v & 3)) * p.N + j * 32] = acc[i][j][v];
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const int col = n0 + wn * TN + j * 32 + l32;
-                if (col >= p.N) continue;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = m0 + wm * TM + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-                    if (row < p.M) part[(long)row * p.N + col] = acc[i][j][v];
-                }
-            }
-        return;
-    }
-    if (p.c_f32 && !bf16_partials) {
-        // fp32 output (+ fp32 residual): half a wave already writes 128 contiguous bytes per row
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const int col = n0 + wn * TN + j * 32 + l32;
-                if (col >= p.N) continue;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = m0 + wm * TM + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-                    if (row >= p.M) continue;
-                    const long off = (long)z * p.bC + (long)row * p.ldc + col;
-                    float val = p.alpha * acc[i][j][v];
-                    if (p.R) val += p.R[off];
-                    ((float*)p.C)[off] = val;
-                }
-            }
-    } else {
-        // bf16 output: each wave turns 32-row slabs of its tile around in LDS so that a row leaves as
-        // 16-byte pieces covering TN contiguous columns instead of 2-byte pieces
-        constexpr int SLD = TN + 8;  // slab row stride in elements
-        static_assert(WM * WN * 32 * SLD * 2 <= STAGES * STAGE_BYTES, "epilogue slab fits in the tile ring");
-        __builtin_amdgcn_s_barrier();  // every wave is done reading operand tiles
-        asm volatile("" ::: "memory");
-        bf16_t* slab = (bf16_t*)smem + wave * 32 * SLD;
-        // a split whose consumer adds the tiles up itself and asked for bf16 ones: the split's tile leaves the same
-        // way, unscaled, into its [M, N] slice of the scratch
-        bf16_t* Cb = bf16_partials ? (bf16_t*)p.partial + ((long)z * n_split + split) * (long)p.M * p.N
-                                   : (bf16_t*)p.C + (long)z * p.bC;
-        const long ldc = bf16_partials ? (long)p.N : p.ldc;
-        const float alpha = bf16_partials ? 1.f : p.alpha;
-        const bool vec_ok = bf16_partials ? ((p.N & 7) == 0 && (((size_t)p.partial & 15) == 0) && (((long)p.M * p.N) & 7) == 0)
-                                          : ((p.ldc & 7) == 0) && ((p.bC & 7) == 0) && (((size_t)p.C & 15) == 0);
+        const bool vec = (ldc & 7) == 0 && ((size_t)C & 15) == 0;
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
 #pragma unroll
-            for (int j = 0; j < FN; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    slab[(8 * (v >> 2) + 4 * g + (v & 3)) * SLD + j * 32 + l32] = f32_to_bf16(alpha * acc[i][j][v]);
-            __builtin_amdgcn_wave_barrier();
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            constexpr int CPR = TN / 8;  // 16-byte chunks per slab row
-            if (vec_ok && m0 + BM <= p.M && n0 + BN <= p.N) {
-                // a whole tile with aligned rows (workgroup-uniform): no bounds checks
-                bf16_t* tile = Cb + (long)(m0 + wm * TM + i * 32) * ldc + n0 + wn * TN;
-#pragma unroll
-                for (int c = lane; c < 32 * CPR; c += 64) {
-                    const int r = c / CPR, cc = (c % CPR) * 8;
-                    *(uint4*)(tile + (long)r * ldc + cc) = *(const uint4*)(slab + r * SLD + cc);
-                }
-                __builtin_amdgcn_wave_barrier();
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                continue;
+            for (int j = 0; j < FN; ++j) {
+                const f32x4_t v = acc[i][j];
+                uint2 w;
+                w.x = pack_bf16x2(alpha * v[0], alpha * v[1]);
+                w.y = pack_bf16x2(alpha * v[2], alpha * v[3]);
+                *(uint2*)(slab + (i * 16 + el16) * SLD + j * 16 + 4 * eg) = w;
             }
-#pragma unroll
-            for (int c = lane; c < 32 * CPR; c += 64) {
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (vec && whole) {
+#pragma unroll 4
+            for (int c = elane; c < TM * CPR; c += 64) {
                 const int r = c / CPR, cc = (c % CPR) * 8;
-                const int row = m0 + wm * TM + i * 32 + r, col = n0 + wn * TN + cc;
+                *(uint4*)(C + (long)(row0 + r) * ldc + col0 + cc) = *(const uint4*)(slab + r * SLD + cc);
+            }
+        } else {
+#pragma unroll 1
+            for (int c = elane; c < TM * CPR; c += 64) {
+                const int r = c / CPR, cc = (c % CPR) * 8;
+                const int row = row0 + r, col = col0 + cc;
                 if (row >= p.M || col >= p.N) continue;
-                const uint4 val = *(const uint4*)(slab + r * SLD + cc);
-                bf16_t* dst = Cb + (long)row * ldc + col;
-                if (vec_ok && col + 8 <= p.N) {
-                    *(uint4*)dst = val;
+                bf16_t* dst = C + (long)row * ldc + col;
+                if (vec && col + 8 <= p.N) {
+                    *(uint4*)dst = *(const uint4*)(slab + r * SLD + cc);
                 } else {
-                    // (taken apart by shifts: a pointer into `val` would put it, and a scratch allocation, into memory)
-                    const uint32_t w[4] = {val.x, val.y, val.z, val.w};
-#pragma unroll
-                    for (int x = 0; x < 8; ++x)
-                        if (col + x < p.N) dst[x] = (bf16_t)(w[x >> 1] >> (16 * (x & 1)));
+                    for (int x = 0; x < 8 && col + x < p.N; ++x) dst[x] = slab[r * SLD + cc + x];
                 }
             }
-            __builtin_amdgcn_wave_barrier();
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
     }
 }
 
-template <int BM, int BN, int WM, int WN, int STAGES, int BKT = 64, bool SPLITK = false, int PIPE = 0>
+template <int BM, int BN, int AST, bool SPLITK>
 static hipError_t run_nt_dl(const GemmNT& g, hipStream_t s, int n_split = 1) {
     const int tiles_m = cdiv(g.M, BM), tiles_n = cdiv(g.N, BN);
-    const size_t lds = (size_t)STAGES * (BM + BN) * BKT * 2;
+    const size_t lds = (size_t)(AST * BM + (AST + 1) * BN) * BK * 2;
     dim3 grid(tiles_m * tiles_n, SPLITK ? n_split : 1, g.batch);
-    auto kern = gemm_nt_dl_kernel<BM, BN, WM, WN, STAGES, BKT, SPLITK, PIPE>;
-    if constexpr (PIPE != 0) {  // the branch-free steady-state loop assumes every split has at least STAGES k-tiles
-        const int nkt = g.K / BKT + g.K2 / BKT;
-        if (nkt / n_split < STAGES) return run_nt_dl<BM, BN, WM, WN, STAGES, BKT, SPLITK, 0>(g, s, n_split);
-    }
+    auto kern = gemm_nt_dl_kernel<BM, BN, AST, SPLITK>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     GemmNT gk = g;
-    if (!(SPLITK && g.deferred && BM >= 256)) gk.partial_bf16 = 0;   // bf16 partial tiles only where the reduce is left to the consumer
-    kern<<<grid, WM * WN * 64, lds, s>>>(gk, make_nt_map(tiles_m, tiles_n, SPLITK ? n_split : 1, g.batch, SPLITK));
-    if (SPLITK) {
-        if (g.deferred && BM >= 256) {    // wide-output instance: the consumer adds the partial tiles up
-            *g.deferred = n_split;
-            return hipGetLastError();
-        }
+    const bool defer = SPLITK && g.deferred && BM >= 256;            // wide-output instance: the consumer adds the partial tiles up
+    if (!defer) gk.partial_bf16 = 0;   // bf16 partial tiles only where the reduce is left to the consumer
+    kern<<<grid, 256, lds, s>>>(gk, make_nt_map(tiles_m, tiles_n, SPLITK ? n_split : 1, g.batch, SPLITK));
+    if (defer) {
+        *g.deferred = n_split;
+    } else if (SPLITK) {
         const long n = (long)g.M * (g.N >> 2) * g.batch;
         splitk_reduce_kernel<<<cdiv(n, 256), 256, 0, s>>>(g, n_split);
     }
@@ -662,13 +651,27 @@ static hipError_t run_nt(const GemmNT& g, int split_k, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Whether the direct-to-LDS kernel takes this product.  Its offsets within an operand are 32-bit.  A contraction that is no
+// multiple of 64 (ranks below 64, ragged widths) costs it one edge tile, waited for before the loop starts: worth it from
+// 256 elements on (1024 x 1024 x 1024 with rank 16: 12 us against 34 us register-staged), below that the whole contraction
+// is one or two such waits.
+static bool nt_direct(const GemmNT& g) {
+    if (g.K <= 0) return false;
+    if (((g.K % BK) || (g.K2 % BK)) && g.K < 256) return false;
+    return (long)g.M * g.lda < (1L << 30) && (long)g.N * g.ldb < (1L << 30) && (long)g.M * g.lda2 < (1L << 30) &&
+           (long)g.N * g.ldb2 < (1L << 30);
+}
+// the same for 64x64 tiles: a narrow output over a ragged contraction (a low-rank product of a ragged width) stays with the
+// register-staged kernel, whose split it shares with every other rank
+static bool nt_direct_small(const GemmNT& g) { return nt_direct(g) && ((g.K % BK) == 0 || g.N >= 128); }
+
 // A many-tile GEMM whose tile count leaves the last round of workgroups poorly filled can be cheaper as two launches:
 // columns [0, N1) (of every batch) as whole rounds of 256x256 tiles, the rest on its own with whatever tile suits it
 // (gate|up at 1024 tokens: 688 tiles of 256x128 are 2.7 rounds and cost three; 256 tiles of 256x256 plus 176 of 256x128
 // cost 12.2 + 7.0 instead of 3 x 7.0 in the units of the tile model below).  Returns N1, or 0 for one launch.
 int gemm_nt_column_split(const GemmNT& g) {
     if (g.deferred || g.split_k > 1 || g.M <= 0 || g.N < 512 || g.batch <= 0) return 0;
-    if ((g.K % BK) || (g.K2 % BK) || g.K <= 0) return 0;
+    if (!nt_direct(g)) return 0;
     const long tm = (long)cdiv(g.M, 256) * g.batch;
     if (tm > 256 || 256 % tm) return 0;                       // a round of 256x256 tiles must be whole tile columns
     const long cols_round = 256 / tm * 256;
@@ -724,9 +727,7 @@ static NtConfig choose_nt(const GemmNT& g, int* n_split) {
     const int nk = cdiv(g.K, BK) + cdiv(g.K2, BK);
     const long t128 = (long)cdiv(g.M, 128) * cdiv(g.N, 128) * g.batch;
     const long t64n = (long)cdiv(g.M, 128) * cdiv(g.N, 64) * g.batch;
-    const bool dl_ok = (g.K % BK) == 0 && (g.K2 % BK) == 0 && g.K > 0 && g.N > 64 &&
-                       (long)g.M * g.lda < (1L << 30) && (long)g.N * g.ldb < (1L << 30) &&
-                       (long)g.M * g.lda2 < (1L << 30) && (long)g.N * g.ldb2 < (1L << 30);
+    const bool dl_ok = g.N > 64 && nt_direct(g);
     auto rounds = [](long t) { return (double)((t + 255) / 256); };
     if (dl_ok && t128 >= 128) {
         const long t256 = (long)cdiv(g.M, 256) * cdiv(g.N, 256) * g.batch;
@@ -799,9 +800,7 @@ const char* gemm_nt_plan(const GemmNT& g, int* n_split) {
         case NT_REG_128x64: return "reg-128x64";
         case NT_SKINNY: break;
     }
-    const bool dl_small = (g.K % BK) == 0 && g.K2 == 0 && g.K > 0 && (long)g.M * g.lda < (1L << 30) &&
-                          (long)g.N * g.ldb < (1L << 30);
-    return dl_small ? (sp > 1 ? "64x64-split" : "64x64") : (sp > 1 ? "reg-64x64-split" : "reg-64x64");
+    return nt_direct_small(g) ? (sp > 1 ? "64x64-split" : "64x64") : (sp > 1 ? "reg-64x64-split" : "reg-64x64");
 }
 
 hipError_t launch_gemm_nt(const GemmNT& g, hipStream_t s) {
@@ -815,21 +814,19 @@ hipError_t launch_gemm_nt(const GemmNT& g, hipStream_t s) {
     if (!g.c_f32 && g.R) return hipErrorInvalidValue;
     int split = 1;
     switch (choose_nt(g, &split)) {
-        case NT_128x128: return run_nt_dl<128, 128, 2, 2, 4, 64, false, 1>(g, s);
-        case NT_256x128: return run_nt_dl<256, 128, 4, 2, 3, 64, false, 1>(g, s);
-        case NT_256x128_SPLIT: return run_nt_dl<256, 128, 4, 2, 3, 64, true, 1>(g, s, split);
-        case NT_256x192: return run_nt_dl<256, 192, 4, 2, 2>(g, s);
-        case NT_256x256: return run_nt_dl<256, 256, 4, 2, 4, 32, false, 1>(g, s);
+        case NT_128x128: return run_nt_dl<128, 128, 4, false>(g, s);
+        case NT_256x128: return run_nt_dl<256, 128, 3, false>(g, s);
+        case NT_256x128_SPLIT: return run_nt_dl<256, 128, 3, true>(g, s, split);
+        case NT_256x192: return run_nt_dl<256, 192, 2, false>(g, s);
+        case NT_256x256: return run_nt_dl<256, 256, 2, false>(g, s);
         case NT_REG_128x128: return run_nt<128, 128, 2, 2>(g, 1, s);
         case NT_REG_128x64: return run_nt<128, 64, 2, 2>(g, 1, s);
         case NT_SKINNY: break;
     }
     if (split > 1 && (!g.partial || (size_t)split * g.M * g.N * g.batch > g.partial_elems)) return hipErrorInvalidValue;
-    const bool dl_small = (g.K % BK) == 0 && g.K2 == 0 && g.K > 0 && (long)g.M * g.lda < (1L << 30) &&
-                          (long)g.N * g.ldb < (1L << 30);
-    if (dl_small) {
-        if (split > 1) return run_nt_dl<64, 64, 2, 2, 4, 64, true>(g, s, split);
-        return run_nt_dl<64, 64, 2, 2, 4>(g, s);
+    if (nt_direct_small(g)) {
+        if (split > 1) return run_nt_dl<64, 64, 4, true>(g, s, split);
+        return run_nt_dl<64, 64, 4, false>(g, s);
     }
     return run_nt<64, 64, 2, 2>(g, split, s);
 }
