@@ -73,10 +73,33 @@ struct GemmTNGroup {
 };
 hipError_t launch_gemm_tn_grouped(GemmTNGroup& g, hipStream_t s);
 
-// fp32 reference-precision GEMM for the single-layer fp32 step: C = alpha * op(A) op(B) + beta * C
-// ta/tb: 0 = as stored [rows, cols] row-major, 1 = transposed use.  (gemm_f32.hip)
-hipError_t launch_sgemm(int ta, int tb, int M, int N, int K, float alpha, const float* A, int lda, const float* B,
-                        int ldb, float beta, float* C, int ldc, hipStream_t s);
+// fp32 products of the single-layer fp32 step (gemm_f32.hip): C = alpha A B^T (+ alpha2 A2 B2^T), fp32 throughout.
+enum F32Kind { F32_KK = 0, F32_KN = 1, F32_MN = 2 };   // A [M,K] B [N,K] / A [M,K] B [K,N] / A [K,M] B [K,N], row-major
+// the first AdamW step of a parameter (moments zero before it)
+struct AdamWFirst { float lr, b1, b2, eps, decay, inv_bc1, inv_bc2; };
+__device__ __forceinline__ float adamw_first(float p, float g, const AdamWFirst& o) {
+    const float m = (1.f - o.b1) * g, v = (1.f - o.b2) * g * g;
+    return p * o.decay - o.lr * (m * o.inv_bc1) / (sqrtf(v * o.inv_bc2) + o.eps);
+}
+struct F32Product {
+    int kind = F32_KK;
+    const float* A = nullptr;  long lda = 0;
+    const float* B = nullptr;  long ldb = 0;
+    int M = 0, N = 0, K = 0;
+    const float* A2 = nullptr; long lda2 = 0;   // second operand pair of the same layouts (the low-rank term), K2 elements
+    const float* B2 = nullptr; long ldb2 = 0;
+    int K2 = 0;
+    float alpha = 1.f, alpha2 = 1.f;
+    float* C = nullptr;        long ldc = 0;
+    const float* p_old = nullptr;               // with p_new: the product is the gradient of p_old (same shape and row
+    float* p_new = nullptr;                     // stride), and p_new receives p_old after its first AdamW step
+    AdamWFirst opt = {};
+    int tiles_m = 0, tiles_n = 0, tile0 = 0;    // filled in by the launcher
+};
+constexpr int F32_GROUP_MAX = 4;
+// n independent products in one launch.  Outputs must not overlap any operand.
+hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s);
+hipError_t launch_adamw_first(const float* g, const float* p, float* p_new, size_t n, const AdamWFirst& o, hipStream_t s);
 
 // ---------------------------------------------------------------- attention (attention.hip)
 hipError_t launch_attention_fwd(const bf16_t* q, const bf16_t* k, const bf16_t* v, long ldq, int T, int n_heads,

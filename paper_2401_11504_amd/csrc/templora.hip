@@ -1222,28 +1222,57 @@ extern "C" tl_status tl_profile_read(tl_lora* L, double* ms_total, int64_t* laun
 }
 
 // ---------------------------------------------------------------- single fp32 LoRA-adapted linear layer
-// H, dH: [T, r] scratch; mom: 2 (r d_in + d_out r) floats of optimizer moments (only with apply_adamw).
+// H, dH: [T, r] scratch.  Two dependent steps: the low-rank products H = X A^T and dH = s dY B, then everything else in one
+// launch.
 static tl_status linear_step_run(const float* X, const float* W, const float* A, const float* B, const float* dY, int T,
                                  int d_in, int d_out, int r, float s, float lr, float beta1, float beta2, float eps,
                                  float wd, int apply_adamw, float* Y, float* dX, float* dA, float* dB, float* A_new,
-                                 float* B_new, float* H, float* dH, float* mom, hipStream_t st) {
-    // H = X A^T;  Y = X W^T + s H B^T
-    HIPCHK(launch_sgemm(0, 1, T, r, d_in, 1.f, X, d_in, A, d_in, 0.f, H, r, st));
-    HIPCHK(launch_sgemm(0, 1, T, d_out, d_in, 1.f, X, d_in, W, d_in, 0.f, Y, d_out, st));
-    HIPCHK(launch_sgemm(0, 1, T, d_out, r, s, H, r, B, r, 1.f, Y, d_out, st));
-    // dH = s dY B;  dX = dY W + dH A;  dA = dH^T X;  dB = s dY^T H
-    HIPCHK(launch_sgemm(0, 0, T, r, d_out, s, dY, d_out, B, r, 0.f, dH, r, st));
-    HIPCHK(launch_sgemm(0, 0, T, d_in, d_out, 1.f, dY, d_out, W, d_in, 0.f, dX, d_in, st));
-    HIPCHK(launch_sgemm(0, 0, T, d_in, r, 1.f, dH, r, A, d_in, 1.f, dX, d_in, st));
-    HIPCHK(launch_sgemm(1, 0, r, d_in, T, 1.f, dH, r, X, d_in, 0.f, dA, d_in, st));
-    HIPCHK(launch_sgemm(1, 0, d_out, r, T, s, dY, d_out, H, r, 0.f, dB, r, st));
-    if (apply_adamw) {
-        const size_t na = (size_t)r * d_in, nb = (size_t)d_out * r;
-        HIPCHK(launch_fill_f32(mom, 2 * (na + nb), 0.f, st));     // first step: zero moments (a kernel, not a memset node)
-        HIPCHK(hipMemcpyAsync(A_new, A, na * sizeof(float), hipMemcpyDeviceToDevice, st));
-        HIPCHK(hipMemcpyAsync(B_new, B, nb * sizeof(float), hipMemcpyDeviceToDevice, st));
-        HIPCHK(launch_adamw(A_new, dA, mom, mom + na, nullptr, na, 1, lr, beta1, beta2, eps, wd, st));
-        HIPCHK(launch_adamw(B_new, dB, mom + 2 * na, mom + 2 * na + nb, nullptr, nb, 1, lr, beta1, beta2, eps, wd, st));
+                                 float* B_new, float* H, float* dH, hipStream_t st) {
+    const size_t na = (size_t)r * d_in, nb = (size_t)d_out * r;
+    AdamWFirst opt = {lr, beta1, beta2, eps, 1.f - lr * wd, (float)(1.0 / (1.0 - (double)beta1)),
+                      (float)(1.0 / (1.0 - (double)beta2))};
+    F32Product low[2];
+    low[0].kind = F32_KK; low[0].A = X; low[0].lda = d_in; low[0].B = A; low[0].ldb = d_in;
+    low[0].M = T; low[0].N = r; low[0].K = d_in; low[0].C = H; low[0].ldc = r;
+    low[1].kind = F32_KN; low[1].A = dY; low[1].lda = d_out; low[1].B = B; low[1].ldb = r;
+    low[1].M = T; low[1].N = r; low[1].K = d_out; low[1].alpha = s; low[1].C = dH; low[1].ldc = r;
+    F32Product p[4];      // Y = X W^T + s H B^T;  dX = dY W + dH A;  dA = dH^T X;  dB = s dY^T H
+    p[0].kind = F32_KK; p[0].A = X; p[0].lda = d_in; p[0].B = W; p[0].ldb = d_in; p[0].M = T; p[0].N = d_out; p[0].K = d_in;
+    p[0].A2 = H; p[0].lda2 = r; p[0].B2 = B; p[0].ldb2 = r; p[0].K2 = r; p[0].alpha2 = s; p[0].C = Y; p[0].ldc = d_out;
+    p[1].kind = F32_KN; p[1].A = dY; p[1].lda = d_out; p[1].B = W; p[1].ldb = d_in; p[1].M = T; p[1].N = d_in; p[1].K = d_out;
+    p[1].A2 = dH; p[1].lda2 = r; p[1].B2 = A; p[1].ldb2 = d_in; p[1].K2 = r; p[1].C = dX; p[1].ldc = d_in;
+    p[2].kind = F32_MN; p[2].A = dH; p[2].lda = r; p[2].B = X; p[2].ldb = d_in; p[2].M = r; p[2].N = d_in; p[2].K = T;
+    p[2].C = dA; p[2].ldc = d_in;
+    p[3].kind = F32_MN; p[3].A = dY; p[3].lda = d_out; p[3].B = H; p[3].ldb = r; p[3].M = d_out; p[3].N = r; p[3].K = T;
+    p[3].alpha = s; p[3].C = dB; p[3].ldc = r;
+    // A caller may have an output share memory with an input that is not needed any more by the time it is written in the
+    // order H, Y, dH, dX, dA, dB, A_new, B_new (an update in place: A_new = A), or with an output that it does not want.
+    // Then that order is kept, one launch after another.
+    const struct { const void* p; size_t n; } buf[] = {{Y, (size_t)T * d_out}, {dX, (size_t)T * d_in}, {dA, na}, {dB, nb},
+                                                       {apply_adamw ? A_new : nullptr, na}, {apply_adamw ? B_new : nullptr, nb},
+                                                       {X, (size_t)T * d_in}, {W, (size_t)d_out * d_in}, {A, na}, {B, nb},
+                                                       {dY, (size_t)T * d_out}};
+    bool shared = false;
+    for (int o = 0; o < 6; ++o)
+        for (int i = o + 1; i < 11; ++i)
+            shared |= buf[o].p && buf[i].p && (uintptr_t)buf[o].p < (uintptr_t)buf[i].p + buf[i].n * sizeof(float) &&
+                      (uintptr_t)buf[i].p < (uintptr_t)buf[o].p + buf[o].n * sizeof(float);
+    if (!shared) {
+        HIPCHK(launch_gemm_f32_group(low, 2, st));
+        if (apply_adamw) {
+            p[2].p_old = A; p[2].p_new = A_new; p[2].opt = opt;
+            p[3].p_old = B; p[3].p_new = B_new; p[3].opt = opt;
+        }
+        HIPCHK(launch_gemm_f32_group(p, 4, st));
+    } else {
+        HIPCHK(launch_gemm_f32_group(&low[0], 1, st));
+        HIPCHK(launch_gemm_f32_group(&p[0], 1, st));
+        HIPCHK(launch_gemm_f32_group(&low[1], 1, st));
+        for (int k = 1; k < 4; ++k) HIPCHK(launch_gemm_f32_group(&p[k], 1, st));
+        if (apply_adamw) {
+            HIPCHK(launch_adamw_first(dA, A, A_new, na, opt, st));
+            HIPCHK(launch_adamw_first(dB, B, B_new, nb, opt, st));
+        }
     }
     HIPCHK(hipStreamSynchronize(st));
     return TL_OK;
@@ -1265,13 +1294,11 @@ extern "C" tl_status tl_linear_step(const float* X, const float* W, const float*
     TLCHK(linear_step_args(X, W, A, B, dY, T, d_in, d_out, r, apply_adamw, Y, dX, dA, dB, A_new, B_new));
     hipStream_t st = (hipStream_t)hip_stream;
     Pool pool;
-    float *H = nullptr, *dH = nullptr, *mom = nullptr;
+    float* H = nullptr;     // H and dH in one allocation: each costs as much as a launch
     auto body = [&]() -> tl_status {
-        TLCHK(pool.alloc(&H, (size_t)T * r));
-        TLCHK(pool.alloc(&dH, (size_t)T * r));
-        if (apply_adamw) TLCHK(pool.alloc(&mom, 2 * ((size_t)r * d_in + (size_t)d_out * r)));
+        TLCHK(pool.alloc(&H, 2 * (size_t)T * r));
         return linear_step_run(X, W, A, B, dY, T, d_in, d_out, r, s, lr, beta1, beta2, eps, wd, apply_adamw, Y, dX, dA, dB,
-                               A_new, B_new, H, dH, mom, st);
+                               A_new, B_new, H, H + (size_t)T * r, st);
     };
     tl_status rc = body();
     if (rc != TL_OK) (void)hipStreamSynchronize(st);
@@ -1281,7 +1308,7 @@ extern "C" tl_status tl_linear_step(const float* X, const float* W, const float*
 
 // ---------------------------------------------------------------- tl_linear_step without allocation
 // For callers that cannot allocate (HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the
-// scratch tl_linear_step takes from hipMalloc (H, dH and, with AdamW, the moments) lives in one file-scope device
+// scratch tl_linear_step takes from hipMalloc (H and dH) lives in one file-scope device
 // array instead.  Every GPU the library runs on holds its own copy for the life of the process; the array's name is
 // only a host-side handle, so its device address is looked up once per device (with that device current) and kept.
 constexpr size_t kStaticScratchFloats = (size_t)1 << 20;    // 4 MiB
@@ -1311,11 +1338,10 @@ extern "C" tl_status tl_linear_step_static(const float* X, const float* W, const
                                            float* Y, float* dX, float* dA, float* dB, float* A_new, float* B_new,
                                            void* hip_stream) {
     TLCHK(linear_step_args(X, W, A, B, dY, T, d_in, d_out, r, apply_adamw, Y, dX, dA, dB, A_new, B_new));
-    // sub-buffers start on 256-byte boundaries
+    // what is refused is what the header states: H, dH and two moments per parameter, though the moments are not stored
     auto up = [](size_t n) { return (n + 63) & ~(size_t)63; };
     const size_t n_h = up((size_t)T * r);
-    const size_t n_mom = apply_adamw ? up(2 * ((size_t)r * d_in + (size_t)d_out * r)) : 0;
-    const size_t need = 2 * n_h + n_mom;
+    const size_t need = 2 * n_h + (apply_adamw ? up(2 * ((size_t)r * d_in + (size_t)d_out * r)) : 0);
     if (need > kStaticScratchFloats)
         return fail(TL_ERR_SHAPE, "tl_linear_step_static: needs %zu floats of scratch (2 T r%s), the static buffer holds %zu; "
                                   "use tl_linear_step", need, apply_adamw ? " + 2 r (d_in + d_out)" : "", kStaticScratchFloats);
@@ -1323,7 +1349,7 @@ extern "C" tl_status tl_linear_step_static(const float* X, const float* W, const
     TLCHK(static_scratch(&base));
     hipStream_t st = (hipStream_t)hip_stream;
     tl_status rc = linear_step_run(X, W, A, B, dY, T, d_in, d_out, r, s, lr, beta1, beta2, eps, wd, apply_adamw, Y, dX, dA,
-                                   dB, A_new, B_new, base, base + n_h, apply_adamw ? base + 2 * n_h : nullptr, st);
+                                   dB, A_new, B_new, base, base + n_h, st);
     if (rc != TL_OK) (void)hipStreamSynchronize(st);
     return rc;
 }

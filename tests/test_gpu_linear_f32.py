@@ -1,0 +1,72 @@
+"""The fp32 LoRA-adapted linear step at the sizes where its tiles can go wrong: every tile shape (32, 64, 128 wide), split
+contractions, row lengths that are no multiple of four floats, ragged rows, columns, ranks and contractions, and an update
+in place.  Reference: fp64."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2401_11504_amd import api  # noqa: E402
+
+LR = 5e-5
+# a sum of K <= 4224 fp32 products strays by about sqrt(K) 2^-24 = 3.9e-6 of its 2-norm; doubled for the low-rank chain
+TOL = 8e-6
+
+CASES = [
+    # T, d_in, d_out, r
+    (1, 1, 1, 1), (33, 100, 101, 4), (5, 64, 3, 32), (31, 129, 66, 33),      # 32-wide tiles
+    (300, 777, 1003, 7), (65, 1030, 259, 16),                                # split low-rank products, narrow
+    (515, 1023, 1030, 64), (700, 1200, 1111, 37),                            # 64-wide tiles
+    (1027, 4096, 2050, 64), (1400, 2049, 4101, 48), (130, 4096, 16400, 5),   # 128-wide tiles, split low-rank products
+]
+
+
+def make(T, din, dout, r):
+    g = torch.Generator().manual_seed(T * 7 + din)
+    n = lambda std, *size: torch.randn(*size, generator=g) * std
+    return [n(1.0, T, din), n(0.02, dout, din), n(0.02, r, din), n(0.01, dout, r), n(1.0, T, dout)]
+
+
+def reference(ins, s):
+    X, W, A, B, dY = (t.double() for t in ins)
+    H, dH = X @ A.T, s * dY @ B
+    return {"Y": X @ W.T + s * H @ B.T, "dX": dY @ W + dH @ A, "dA": dH.T @ X, "dB": s * dY.T @ H}
+
+
+def step(ins, s, outs, A_new, B_new):
+    api.tl_linear_step(*ins, s, LR, 0.9, 0.999, 1e-8, 0.01, True, *outs, A_new, B_new)
+
+
+@pytest.mark.parametrize("T,din,dout,r", CASES)
+def test_linear_step(T, din, dout, r):
+    ins, s = make(T, din, dout, r), 1.5
+    dev = [t.cuda() for t in ins]
+    shapes = dict(Y=(T, dout), dX=(T, din), dA=(r, din), dB=(dout, r))
+    # what lies behind an output's last element stays as it is
+    flat = {k: torch.full((a * b + 64,), 3.0, device="cuda") for k, (a, b) in shapes.items()}
+    outs = [flat[k][:a * b].view(a, b) for k, (a, b) in shapes.items()]
+    new = [torch.empty_like(dev[2]), torch.empty_like(dev[3])]
+    step(dev, s, outs, *new)
+    ref = reference(ins, s)
+    for (k, (a, b)), o in zip(shapes.items(), outs):
+        err = (o.cpu().double() - ref[k]).norm() / ref[k].norm()
+        assert err < TOL, (k, err)
+        assert bool((flat[k][a * b:] == 3.0).all()), k
+    for p, gname, p1 in ((ins[2], "dA", new[0]), (ins[3], "dB", new[1])):
+        gr = outs[2 if gname == "dA" else 3].cpu().double()
+        want = p.double() * (1 - LR * 0.01) - LR * gr / (gr.abs() + 1e-8)       # first AdamW step, from the gradient handed out
+        # p itself is rounded to fp32 (|p| < 0.1: 4e-9), the step of size LR to a few ulp
+        assert (p1.cpu().double() - want).abs().max() < 8e-9 + LR * 1e-6, gname
+
+    # the same in place: the factors are updated where they are
+    dev2 = [t.cuda() for t in ins]
+    outs2 = [torch.empty_like(o) for o in outs]
+    step(dev2, s, outs2, dev2[2], dev2[3])
+    for k, o, o2 in zip(shapes, outs, outs2):
+        err = (o2.cpu().double() - ref[k]).norm() / ref[k].norm()
+        assert err < TOL, (k, err)
+    for p, g2, p1 in ((ins[2], outs2[2], dev2[2]), (ins[3], outs2[3], dev2[3])):
+        gr = g2.cpu().double()
+        want = p.double() * (1 - LR * 0.01) - LR * gr / (gr.abs() + 1e-8)
+        assert (p1.cpu().double() - want).abs().max() < 8e-9 + LR * 1e-6
