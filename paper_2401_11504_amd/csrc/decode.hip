@@ -3,47 +3,187 @@
 // the greedy argmax.  All of them stream their operand once: at one token per step the decoder is bound by reading
 // the 13.5 GB of frozen weights, not by arithmetic.
 #include "kernels.h"
+#include <type_traits>
 
 typedef unsigned gemv_vu4 __attribute__((ext_vector_type(4)));
 // 16 bytes of a weight row.  Every byte of the matrix is read exactly once per token, so the loads are marked
-// non-temporal: measured 5 % faster per token than ordinary loads (eight loads in flight instead of four, two or four
-// rows per wave, or two waves per row were all slower or equal).
+// non-temporal: measured 5 % faster per token than ordinary loads.
 __device__ __forceinline__ uint4 load_w16(const bf16_t* p) {
     const gemv_vu4 v = __builtin_nontemporal_load((const gemv_vu4*)p);
     return make_uint4(v.x, v.y, v.z, v.w);
 }
+__device__ __forceinline__ float dot8(const uint4& w, const float (&b)[8], float acc) {
+    float a[8];
+    unpack8(w, a);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc += a[e] * b[e];
+    return acc;
+}
+
+// One piece's share of A x: part[j] = sum over the piece's C columns of a[j, c] x[c], j < r, by NT threads.  C / 8 lanes share a
+// row of A (row stride lda, a points at the piece's first column); x is in LDS, zero past the `left` columns that exist.
+// av: the first NA rows per thread, row j = thread / (C / 8) + i * (8 NT / C), fetched ahead by the caller.
+template <int C, int NT, int NA>
+__device__ __forceinline__ void lowrank_part(const bf16_t* a, long lda, int r, const float* x, int left, uint4 (&av)[NA], float* part) {
+    constexpr int LPR = C / 8, STEP = NT / LPR;
+    const int sub = threadIdx.x % LPR, jj = threadIdx.x / LPR;
+    float xv[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) xv[e] = x[sub * 8 + e];
+    for (int j0 = 0; j0 < r; j0 += NA * STEP) {
+        if (j0) {
+#pragma unroll
+            for (int i = 0; i < NA; ++i) av[i] = *(const uint4*)(a + (long)min(j0 + jj + i * STEP, r - 1) * lda + min(sub * 8, left - 8));
+        }
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            float v = dot8(av[i], xv, 0.f);
+#pragma unroll
+            for (int off = LPR >> 1; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+            const int j = j0 + jj + i * STEP;
+            if (sub == 0 && j < r) part[j] = v;
+        }
+    }
+}
 
 // ---------------------------------------------------------------- y = W x (+ s-scaled LoRA term) (+ residual)
-// One wave per output row n: the row W[n, :] is read with 16-byte loads, 64 lanes wide; x sits in LDS.
-// lora_h (fp32 [G * r], already scaled by s) and lora_b (bf16 [N, r]) add  sum_j B[n, j] h[(n / rows_per_group) r + j].
+// R output rows n per wave: a row W[n, :] is read with 16-byte loads, 64 lanes wide; x sits in LDS.  The first eight loads
+// of each row (all of it up to 4096 columns) are issued before x is formed, so that the weights stream while the workgroup
+// is busy with its prologue (lm_head of the 7B shape 51.7 -> 41.7 us, 6.3 TB/s; gate|up 30.9 us with its rows of A, 5.8 TB/s).
+// The low-rank term of a projection costs no launch of its own (four of them per layer were 26 of 122 us: a few microseconds
+// of latency each):
+//   lora.a: the rows of A ride along behind the rows of W and leave h = scale A x in lora.h_out, for whoever reads y to add
+//   B h (q|k|v: the attention launch; gate|up: decode_swiglu_kernel);
+//   lora.b (bf16 [N, r]) adds  sum_j B[n, j] h[(n / rows_per_group) r + j], where h = scale * the sum of n_parts vectors
+//   that the launch before has left, each from its own piece of x (attention: one per head; decode_swiglu_kernel: one per
+//   workgroup).
+// (One launch that computes A x in its first workgroups and hands it to the others through tagged words was no faster than
+// two: every wave waited for it at the end with its registers full.)
 // Where x comes from (pre.mode): 0 a bf16 vector; 1 RMSNorm of an fp32 row, x = bf16(h rho gain); 2 SwiGLU of a
 // gate|up row, x = bf16(silu(g) u).  Modes 1 and 2 do the work of the separate kernels in every workgroup (the
 // vector is a few KB out of L2), and workgroup 0 stores x to pre.x_out for the launches that follow.
-__global__ __launch_bounds__(256) void gemv_kernel(const bf16_t* __restrict__ W, long ldw, const bf16_t* __restrict__ x, int N,
-                                                   int K, const bf16_t* __restrict__ lora_b, const float* __restrict__ lora_h,
-                                                   int r, int rows_per_group, float alpha, const float* __restrict__ resid,
-                                                   bf16_t* __restrict__ y_bf, float* __restrict__ y_f32, GemvPre pre,
-                                                   int row_per_block) {
+constexpr int GEMV_AHEAD = 8;
+
+// a long row's product with x, w0 holding this lane's share of its first 4096 columns: eight loads ahead of the eight that
+// are being added up
+__device__ __forceinline__ float gemv_row(const bf16_t* w, const bf16_t* sx, int K, int lane, uint4 (&w0)[GEMV_AHEAD]) {
+    constexpr int NB = GEMV_AHEAD, STEP = NB * 512;
+    uint4 w1[NB];
+    float acc = 0.f;
+    auto load = [&](uint4 (&wv)[NB], int k) {
+        if (k >= K) return;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) wv[u] = load_w16(w + min(k + u * 512 + lane * 8, K - 8));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto add = [&](const uint4 (&wv)[NB], int k) {
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int kk = k + u * 512 + lane * 8;
+            float b[8];
+            unpack8(*(const uint4*)(sx + min(kk, K - 8)), b);
+            acc = kk < K ? dot8(wv[u], b, acc) : acc;
+        }
+    };
+    for (int k = 0; k < K; k += 2 * STEP) {
+        load(w1, k + STEP);
+        add(w0, k);
+        if (k + STEP >= K) break;
+        load(w0, k + 2 * STEP);
+        add(w1, k + STEP);
+    }
+    return acc;
+}
+
+template <int R, int MODE>
+__global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t* __restrict__ W, long ldw,
+                                                                   const bf16_t* __restrict__ x, int N, int K, GemvLora lora,
+                                                                   float alpha, const float* __restrict__ resid,
+                                                                   bf16_t* __restrict__ y_bf, float* __restrict__ y_f32,
+                                                                   GemvPre pre) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float red[16];
     bf16_t* sx = (bf16_t*)smem;
-    if (pre.mode == 1) {
+    float *hp = (float*)(smem + (((size_t)K * 2 + 15) & ~(size_t)15)), *hs = hp + 256;      // only with lora.n_parts
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rows = N + lora.n_a, n0 = ((int)blockIdx.x * 4 + wave) * R;
+
+    // A norm's operands are asked for first (loads return in order), if they fit.
+    constexpr int NV = 4;
+    const bool short_row = MODE == 1 && K <= 1024 * NV;
+    float4 hv[NV], gv[NV];
+    if (short_row) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const int i = threadIdx.x * 4 + 1024 * j;
+            if (1024 * j >= K) break;
+            hv[j] = *(const float4*)(pre.h + min(i, K - 4));
+            gv[j] = *(const float4*)(pre.gain + min(i, K - 4));
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const bf16_t* w[R];
+    uint4 wv[R][GEMV_AHEAD];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const long n = min(n0 + i, rows - 1);        // rows past the end repeat the last one and are not stored
+        w[i] = n < N ? W + n * ldw : lora.a + (n - N) * K;
+#pragma unroll
+        for (int u = 0; u < GEMV_AHEAD; ++u) {
+            const int k = lane * 8 + u * 512;
+            wv[i][u] = load_w16(w[i] + min(k, K - 8));      // (no branch around a load; left out of the sum below)
+        }
+    }
+    // this lane's element of the rows of B
+    bf16_t bv[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) bv[i] = lora.b ? lora.b[(long)min(n0 + i, rows - 1) * lora.r + min(lane, lora.r - 1)] : (bf16_t)0;
+    // h from its parts: 256 / r threads per entry.  (All of it, and a given x, in registers ahead of the weights or right
+    // behind them was slower, 9 -> 12 us for o and 21 -> 31 for down.)
+    const int hg = lora.n_parts > 0 ? 256 / lora.r : 0;
+    float hsum = 0.f;
+    if ((int)threadIdx.x < hg * lora.r) {
+        const int j = threadIdx.x % lora.r, g = threadIdx.x / lora.r;
+        for (int p0 = g; p0 < lora.n_parts; p0 += 8 * hg) {
+            float t[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = lora.h[(long)min(p0 + u * hg, lora.n_parts - 1) * lora.r + j];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) hsum += p0 + u * hg < lora.n_parts ? t[u] : 0.f;
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    if constexpr (MODE == 1) {
         float ss = 0.f;
-        for (int i = threadIdx.x * 4; i < K; i += blockDim.x * 4) {
-            const float4 v = *(const float4*)(pre.h + i);
-            ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-        }
-        ss = block_sum(ss, red);
-        const float rho = rsqrtf(ss / (float)K + pre.eps);
-        for (int i = threadIdx.x * 4; i < K; i += blockDim.x * 4) {
-            const float4 v = *(const float4*)(pre.h + i), w = *(const float4*)(pre.gain + i);
+        auto emit = [&](int i, const float4& v, const float4& g, float rho) {
             uint2 o;
-            o.x = pack_bf16x2(v.x * rho * w.x, v.y * rho * w.y);
-            o.y = pack_bf16x2(v.z * rho * w.z, v.w * rho * w.w);
+            o.x = pack_bf16x2(v.x * rho * g.x, v.y * rho * g.y);
+            o.y = pack_bf16x2(v.z * rho * g.z, v.w * rho * g.w);
             *(uint2*)(sx + i) = o;
+        };
+        if (short_row) {
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+                if ((int)threadIdx.x * 4 + 1024 * j < K) ss += hv[j].x * hv[j].x + hv[j].y * hv[j].y + hv[j].z * hv[j].z + hv[j].w * hv[j].w;
+            ss = block_sum(ss, red);
+            const float rho = rsqrtf(ss / (float)K + pre.eps);
+#pragma unroll
+            for (int j = 0; j < NV; ++j) {
+                const int i = threadIdx.x * 4 + 1024 * j;
+                if (i < K) emit(i, hv[j], gv[j], rho);
+            }
+        } else {
+            for (int i = threadIdx.x * 4; i < K; i += 1024) {
+                const float4 v = *(const float4*)(pre.h + i);
+                ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+            }
+            ss = block_sum(ss, red);
+            const float rho = rsqrtf(ss / (float)K + pre.eps);
+            for (int i = threadIdx.x * 4; i < K; i += 1024) emit(i, *(const float4*)(pre.h + i), *(const float4*)(pre.gain + i), rho);
         }
-    } else if (pre.mode == 2) {
-        for (int i = threadIdx.x * 8; i < K; i += blockDim.x * 8) {
+    } else if constexpr (MODE == 2) {
+        for (int i = threadIdx.x * 8; i < K; i += 2048) {
             float g[8], u[8], o[8];
             unpack8(*(const uint4*)(pre.gu + i), g);
             unpack8(*(const uint4*)(pre.gu + K + i), u);
@@ -52,91 +192,133 @@ __global__ __launch_bounds__(256) void gemv_kernel(const bf16_t* __restrict__ W,
             *(uint4*)(sx + i) = pack8(o);
         }
     } else {
-        for (int i = threadIdx.x * 8; i < K; i += blockDim.x * 8) *(uint4*)(sx + i) = *(const uint4*)(x + i);
+        for (int i = threadIdx.x * 8; i < K; i += 2048) *(uint4*)(sx + i) = *(const uint4*)(x + i);
     }
+    if (hg) hp[threadIdx.x] = hsum;
     __syncthreads();
     if (pre.x_out && blockIdx.x == 0)
-        for (int i = threadIdx.x * 8; i < K; i += blockDim.x * 8) *(uint4*)(pre.x_out + i) = *(const uint4*)(sx + i);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (row_per_block) {
-        // few rows (the LoRA A factors): the whole workgroup shares one row, so that the row's loads are all in
-        // flight at once instead of queued behind one wave
-        const int n = blockIdx.x;
-        const bf16_t* w = W + (long)n * ldw;
-        float acc = 0.f;
-        for (int k = threadIdx.x * 8; k < K; k += 2048) {
-            float a[8], b[8];
-            unpack8(*(const uint4*)(w + k), a);
-            unpack8(*(const uint4*)(sx + k), b);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc += a[e] * b[e];
+        for (int i = threadIdx.x * 8; i < K; i += 2048) *(uint4*)(pre.x_out + i) = *(const uint4*)(sx + i);
+    if (hg) {
+        if ((int)threadIdx.x < lora.r) {
+            float h = 0.f;
+            for (int g = 0; g < hg; ++g) h += hp[g * lora.r + threadIdx.x];
+            hs[threadIdx.x] = lora.scale * h;
         }
-        if (lora_b) {
-            const float* h = lora_h + (long)(n / rows_per_group) * r;
-            const bf16_t* b = lora_b + (long)n * r;
-            for (int j = threadIdx.x; j < r; j += 256) acc += bf16_to_f32(b[j]) * h[j];
-        }
-        acc = block_sum(acc, red);
-        if (threadIdx.x == 0) {
-            float v = alpha * acc;
-            if (y_f32) y_f32[n] = v + (resid ? resid[n] : 0.f);
-            else y_bf[n] = f32_to_bf16(v);
-        }
-        return;
+        __syncthreads();
     }
-    const int n = blockIdx.x * 4 + wave;
-    if (n >= N) return;
-    const bf16_t* w = W + (long)n * ldw;
-    float acc = 0.f;
-    int k = lane * 8;
-    for (; k + 3 * 512 < K; k += 4 * 512) {          // four 16-byte loads of the row in flight per lane
-        uint4 wv[4];
+    if (n0 >= rows) return;
+
+    float acc[R];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) wv[u] = load_w16(w + k + u * 512);
+    for (int i = 0; i < R; ++i) acc[i] = 0.f;
+    if (K > GEMV_AHEAD * 512) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float a[8], b[8];
-            unpack8(wv[u], a);
-            unpack8(*(const uint4*)(sx + k + u * 512), b);
+        for (int i = 0; i < R; ++i) acc[i] = gemv_row(w[i], sx, K, lane, wv[i]);
+    } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc += a[e] * b[e];
+        for (int u = 0; u < GEMV_AHEAD; ++u) {
+            const int k = lane * 8 + u * 512;
+            float b[8];
+            unpack8(*(const uint4*)(sx + min(k, K - 8)), b);
+#pragma unroll
+            for (int i = 0; i < R; ++i) acc[i] = k < K ? dot8(wv[i][u], b, acc[i]) : acc[i];
         }
     }
-    for (; k < K; k += 512) {
-        float a[8], b[8];
-        unpack8(load_w16(w + k), a);
-        unpack8(*(const uint4*)(sx + k), b);
+    if (lora.b) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc += a[e] * b[e];
+        for (int i = 0; i < R; ++i) {
+            const int n = min(n0 + i, rows - 1);
+            const float* h = hg ? hs : lora.h + (long)(n / lora.rows_per_group) * lora.r;
+            const bf16_t* b = lora.b + (long)n * lora.r;
+            if (lane < lora.r) acc[i] += bf16_to_f32(bv[i]) * h[lane];
+            for (int j = lane + 64; j < lora.r; j += 64) acc[i] += bf16_to_f32(b[j]) * h[j];
+        }
     }
-    if (lora_b) {
-        const float* h = lora_h + (long)(n / rows_per_group) * r;
-        const bf16_t* b = lora_b + (long)n * r;
-        for (int j = lane; j < r; j += 64) acc += bf16_to_f32(b[j]) * h[j];
-    }
-    acc = wave_sum(acc);
-    if (lane == 0) {
-        float v = alpha * acc;
-        if (y_f32) y_f32[n] = v + (resid ? resid[n] : 0.f);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const float sum = wave_sum(acc[i]), v = alpha * sum;
+        const int n = n0 + i;
+        if (lane != 0 || n >= rows) continue;
+        if (n >= N) lora.h_out[n - N] = lora.scale * sum;
+        else if (y_f32) y_f32[n] = v + (resid ? resid[n] : 0.f);
         else y_bf[n] = f32_to_bf16(v);
     }
 }
 
-hipError_t launch_gemv(const bf16_t* W, long ldw, const bf16_t* x, int N, int K, const bf16_t* lora_b, const float* lora_h,
-                       int r, int rows_per_group, float alpha, const float* resid, bf16_t* y_bf, float* y_f32,
-                       hipStream_t s, const GemvPre* pre) {
+hipError_t launch_gemv(const bf16_t* W, long ldw, const bf16_t* x, int N, int K, const GemvLora& lora, float alpha,
+                       const float* resid, bf16_t* y_bf, float* y_f32, hipStream_t s, const GemvPre* pre) {
     if (N <= 0) return hipSuccess;
     if ((K & 7) || (ldw & 7) || K <= 0 || (size_t)K * 2 > 160 * 1024 || (!y_bf && !y_f32)) return hipErrorInvalidValue;
     GemvPre p = pre ? *pre : GemvPre{};
     if (p.mode < 0 || p.mode > 2 || (p.mode == 0 && !x) || (p.mode == 1 && (!p.h || !p.gain)) || (p.mode == 2 && !p.gu))
         return hipErrorInvalidValue;
-    const size_t lds = (size_t)K * sizeof(bf16_t);
-    hipError_t e = hipFuncSetAttribute((const void*)gemv_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    const int row_per_block = N <= 512;
-    gemv_kernel<<<row_per_block ? N : cdiv(N, 4), 256, lds, s>>>(W, ldw, x, N, K, lora_b, lora_h, r,
-                                                                 rows_per_group > 0 ? rows_per_group : N, alpha, resid, y_bf,
-                                                                 y_f32, p, row_per_block);
+    GemvLora lo = lora;
+    if (lo.rows_per_group <= 0) lo.rows_per_group = N;
+    if (lo.n_a > 0 ? (!lo.a || !lo.h_out || lo.b) : (lo.b && (!lo.h || lo.r < 1))) return hipErrorInvalidValue;
+    if (lo.n_parts > 0 && (!lo.b || lo.r > 256 || lo.rows_per_group < N)) return hipErrorInvalidValue;   // summed for one group
+    const size_t lds = lo.n_parts > 0 ? (((size_t)K * 2 + 15) & ~(size_t)15) + 512 * sizeof(float) : (size_t)K * sizeof(bf16_t);
+    // Two rows per wave halve the number of times the input vector is formed; worth it while that leaves every CU a few
+    // workgroups.
+    const bool two = N >= 8192;
+    const int grid = cdiv((long)N + lo.n_a, two ? 8 : 4);
+    auto run = [&](auto kern) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        kern<<<grid, 256, lds, s>>>(W, ldw, x, N, K, lo, alpha, resid, y_bf, y_f32, p);
+        return hipGetLastError();
+    };
+    if (p.mode == 0) return two ? run(gemv_kernel<2, 0>) : run(gemv_kernel<1, 0>);
+    if (p.mode == 1) return two ? run(gemv_kernel<2, 1>) : run(gemv_kernel<1, 1>);
+    return two ? run(gemv_kernel<2, 2>) : run(gemv_kernel<1, 2>);
+}
+
+// ---------------------------------------------------------------- SwiGLU of one token
+// DECODE_SW columns of act per workgroup: gate and up rows get their low-rank term (raw + B h, rounded to bf16 as the chunk
+// path keeps them), act = bf16(silu(g) u), and the piece's share of the down projection's A act goes to
+// part[blockIdx.x * r + j] (summed by gemv_kernel).
+__global__ __launch_bounds__(256) void decode_swiglu_kernel(const float* __restrict__ raw, const bf16_t* __restrict__ b,
+                                                            const float* __restrict__ h, int r, int f, bf16_t* __restrict__ act,
+                                                            const bf16_t* __restrict__ a_down, float* __restrict__ part) {
+    static_assert(DECODE_SW == 128, "256 threads: gate and up of 128 columns; 16 lanes per row of A");
+    __shared__ float gu[256], sa[DECODE_SW];
+    const int c0 = blockIdx.x * DECODE_SW, c = threadIdx.x & 127, which = threadIdx.x >> 7;
+    const int sub = threadIdx.x & 15, jj = threadIdx.x >> 4, left = f - c0;
+    uint4 av[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        av[i] = *(const uint4*)(a_down + (long)min(jj + 16 * i, r - 1) * f + c0 + min(sub * 8, left - 8));
+    {
+        const long n = (long)which * f + min(c0 + c, f - 1);
+        float v = 0.f;
+        for (int j0 = 0; j0 < r; j0 += 64) {
+            uint4 bv[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) bv[i] = *(const uint4*)(b + n * r + min(j0 + 8 * i, r - 8));
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                float t[8];
+                unpack8(bv[i], t);
+                if (j0 + 8 * i < r)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v += t[e] * h[which * r + j0 + 8 * i + e];
+            }
+        }
+        gu[threadIdx.x] = bf16_to_f32(f32_to_bf16(raw[n] + v));
+    }
+    __syncthreads();
+    if (threadIdx.x < DECODE_SW) {
+        const float g = gu[c], v = g / (1.f + __expf(-g)) * gu[128 + c];
+        const bf16_t o = f32_to_bf16(v);
+        if (c0 + c < f) act[c0 + c] = o;
+        sa[c] = c0 + c < f ? bf16_to_f32(o) : 0.f;
+    }
+    __syncthreads();
+    lowrank_part<DECODE_SW, 256, 4>(a_down + c0, f, r, sa, left, av, part + (long)blockIdx.x * r);
+}
+hipError_t launch_decode_swiglu(const float* raw, const bf16_t* b, const float* h, int r, int f, bf16_t* act,
+                                const bf16_t* a_down, float* part, hipStream_t s) {
+    if (f <= 0 || (f & 7) || r < 8 || (r & 7)) return hipErrorInvalidValue;
+    decode_swiglu_kernel<<<cdiv(f, DECODE_SW), 256, 0, s>>>(raw, b, h, r, f, act, a_down, part);
     return hipGetLastError();
 }
 
@@ -145,202 +327,283 @@ hipError_t launch_gemv(const bf16_t* W, long ldw, const bf16_t* x, int N, int K,
 // the chunk path, so the cache IS the forward pass's saved projections).  Scores and the softmax are fp32; the
 // output row is written in bf16.
 //
-// attend_range: one head against nk consecutive keys, by one workgroup.  A key (or value) row of the head is
-// d_head * 2 contiguous bytes, read by d_head / 8 adjacent lanes with one 16-byte load each, so a workgroup covers
-// blockDim / (d_head / 8) keys per pass; four passes of loads are issued before the first is consumed (the loop is
-// bound by load latency, not by bytes).  Returns the score maximum and the sum of exponentials; the unnormalised
-// output sum_u exp(s_u - max) v_u is left in out_acc[0 .. d_head).
+// attend_range: one head against nk consecutive keys, by one workgroup of NW waves.  A key (or value) row of the head is
+// DH * 2 contiguous bytes, read by DH / 8 adjacent lanes with one 16-byte load each; such a group of lanes takes its keys
+// NP at a time, keys and values all in flight together (the loop is bound by load latency, not by bytes), and keeps a
+// running maximum, sum and output of its own.  The groups are merged at the end: one barrier in all.  Leaves the
+// unnormalised output in out[0 .. DH) of the first DH threads' `o`, with the maximum and the sum of exponentials.
+// (1024 keys, 32 heads of 128: 7.7 us, against 11.0 with the scores in LDS, two block reductions and the values fetched after
+// them; with the fresh token's rows formed as well 11.8.)
 //
-// rope_row != null: the query row and key row `new_key` of the range (the token being decoded; -1 if it lies in another
-// range) are still unrotated.  They are rotated here with the (cos, sin) pairs of the token's position (RoPE pairs
-// elements i and i + d_head / 2; both halves of a row are held by lanes of the same wave), rounded to bf16 as the
-// separate kernel would have stored them, and the rotated key is written back to the cache for the tokens to come.
-__device__ __forceinline__ void rope8(const float* mine, const float* other, const float2* __restrict__ rope_row,
-                                      int sub, int lpk, float* out) {
+// fresh.raw != null: the token being decoded.  Its q, k and v do not exist yet as bf16 rows: they are raw + B h (fp32 sums,
+// rounded to bf16), formed here -- q by every workgroup of the head, k and v by the one whose range ends with key `new_key`
+// (-1: another range) -- and q and k are rotated with the (cos, sin) pairs of the token's position (RoPE pairs elements i
+// and i + d_head / 2) and rounded to bf16 once more, as the chunk path's separate kernels would have stored them.  k and v
+// are written to the cache for the tokens to come.
+__device__ __forceinline__ void rope8(const float* mine, const float* other, const float2 (&row)[8], int sub, int lpk, float* out) {
     const bool first = sub < (lpk >> 1);
-    const int i0 = (sub % (lpk >> 1)) * 8;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const float2 cs = rope_row[i0 + e];
+        const float2 cs = row[e];
         const float a = first ? mine[e] : other[e], b = first ? other[e] : mine[e];   // a: first-half element of the pair
         out[e] = bf16_to_f32(f32_to_bf16(first ? a * cs.x - b * cs.y : b * cs.x + a * cs.y));
     }
 }
+template <int DH, int NW>
 __device__ __forceinline__ void attend_range(const bf16_t* __restrict__ qh, bf16_t* __restrict__ kh,
-                                             const bf16_t* __restrict__ vh, long ld, int nk, int d_head, float scale,
-                                             float* sp, float* part_buf, float* red, float& mx_out, float& sum_out,
-                                             const float2* __restrict__ rope_row, int new_key) {
-    const int tid = threadIdx.x, nthr = blockDim.x;
-    const int lpk = d_head >> 3, sub = tid % lpk, kk = tid / lpk, kpp = nthr / lpk;   // lanes per key, keys per pass
-    const int psub = sub ^ (lpk >> 1);                                                 // the lane holding the pair partners
-    float qv[8];
-    unpack8(*(const uint4*)(qh + sub * 8), qv);
-    if (rope_row) {
-        float other[8], rot[8];
-        unpack8(*(const uint4*)(qh + psub * 8), other);
-        rope8(qv, other, rope_row, sub, lpk, rot);
+                                             bf16_t* __restrict__ vh, long ld, int nk, float scale,
+                                             float& o, float& mx_out, float& sum_out, const DecodeFresh& fresh, int head,
+                                             int new_key) {
+    constexpr int LPK = DH / 8, KPW = 64 / LPK, KPP = NW * KPW;   // lanes per key, keys per wave and per pass
+    constexpr int NP = NW > 4 ? 4 : 8;                                    // passes in flight (sixteen waves: 128 registers)
+    __shared__ float part[NW][DH + 2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sub = lane % LPK, kk = wave * KPW + lane / LPK;
+    const int psub = sub ^ (LPK >> 1);                                    // the lanes holding the pair partners
+    __shared__ float row[3][DH];                                          // fresh q, k, v
+    float2 cs[8];                                                         // this lane's share of the position's (cos, sin)
+    uint4 kr[NP], vr[NP];
+    auto fetch = [&](int u0) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) qv[e] = rot[e];
-    }
-    for (int u0 = 0; u0 < nk; u0 += 4 * kpp) {
-        uint4 kr[4];
+        for (int i = 0; i < NP; ++i) kr[i] = *(const uint4*)(kh + (long)min(u0 + i * KPP + kk, nk - 1) * ld + sub * 8);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int u = u0 + b * kpp + kk;
-            kr[b] = u < nk ? *(const uint4*)(kh + (long)u * ld + sub * 8) : make_uint4(0, 0, 0, 0);
-        }
+        for (int i = 0; i < NP; ++i) vr[i] = *(const uint4*)(vh + (long)min(u0 + i * KPP + kk, nk - 1) * ld + sub * 8);
+    };
+    float qv[8], kn[8] = {}, vn[8] = {};                                  // kn, vn: the new key's and value's share
+    fetch(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (fresh.raw) {
+        // TPR threads per row of the head, each with every TPR-th eight of the row of B
+        constexpr int TPR = NW * 64 / DH;
+        const int c = tid / TPR, p = tid % TPR;
+        float v[3] = {0.f, 0.f, 0.f}, raw[3];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int u = u0 + b * kpp + kk;
-            float a[8], sdot = 0.f;
-            unpack8(kr[b], a);
-            if (rope_row && u == new_key) {      // taken by the d_head / 8 lanes of one key, all in one wave
-                float other[8], rot[8];
-                unpack8(*(const uint4*)(kh + (long)u * ld + psub * 8), other);
-                rope8(a, other, rope_row, sub, lpk, rot);
-                *(uint4*)(kh + (long)u * ld + sub * 8) = pack8(rot);
+        for (int x = 0; x < 3; ++x) raw[x] = fresh.raw[(long)x * fresh.d + head * DH + c];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) a[e] = rot[e];
+        for (int e = 0; e < 8; ++e) cs[e] = fresh.rope[sub % (LPK >> 1) * 8 + e];
+        constexpr int NC = TPR >= 8 ? 1 : 8 / TPR;                        // pieces of eight per thread and trip: 64 of a row
+        auto low = [&](auto rows) {               // every load of a trip before the first is used
+            constexpr int NR = decltype(rows)::value;
+            for (int j0 = 0; j0 < fresh.r; j0 += NC * TPR * 8) {
+                uint4 bv[NR][NC];
+                float4 ha[NR][NC], hb[NR][NC];
+#pragma unroll
+                for (int x = 0; x < NR; ++x)
+#pragma unroll
+                    for (int i = 0; i < NC; ++i) {
+                        const int j = min(j0 + (i * TPR + p) * 8, fresh.r - 8);
+                        bv[x][i] = *(const uint4*)(fresh.b + ((long)x * fresh.d + head * DH + c) * fresh.r + j);
+                        ha[x][i] = *(const float4*)(fresh.h + x * fresh.r + j);
+                        hb[x][i] = *(const float4*)(fresh.h + x * fresh.r + j + 4);
+                    }
+#pragma unroll
+                for (int x = 0; x < NR; ++x)
+#pragma unroll
+                    for (int i = 0; i < NC; ++i) {
+                        const float4 a = ha[x][i], b = hb[x][i];
+                        const float hh[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+                        v[x] = j0 + (i * TPR + p) * 8 < fresh.r ? dot8(bv[x][i], hh, v[x]) : v[x];
+                    }
             }
+        };
+        if (new_key >= 0) low(std::integral_constant<int, 3>{}); else low(std::integral_constant<int, 1>{});
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+#pragma unroll
+            for (int off = TPR >> 1; off > 0; off >>= 1) v[x] += __shfl_xor(v[x], off, 64);
+            if (p == 0) row[x][c] = bf16_to_f32(f32_to_bf16(raw[x] + v[x]));
+        }
+        __syncthreads();
+        rope8(row[0] + sub * 8, row[0] + psub * 8, cs, sub, LPK, qv);
+        if (new_key >= 0) {
+            rope8(row[1] + sub * 8, row[1] + psub * 8, cs, sub, LPK, kn);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) vn[e] = row[2][sub * 8 + e];
+            if (tid < LPK) {
+                *(uint4*)(kh + (long)new_key * ld + sub * 8) = pack8(kn);
+                *(uint4*)(vh + (long)new_key * ld + sub * 8) = pack8(vn);
+            }
+        }
+    } else {
+        unpack8(*(const uint4*)(qh + sub * 8), qv);
+    }
+    float m = -1.0e30f, l = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int u0 = 0; u0 < nk; u0 += NP * KPP) {
+        if (u0 > 0) fetch(u0);
+        __builtin_amdgcn_sched_barrier(0);
+        float sc[NP], mloc = m;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int u = u0 + i * KPP + kk;
+            float a[8], sdot = 0.f;
+            unpack8(kr[i], a);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a[e] = u == new_key ? kn[e] : a[e];
 #pragma unroll
             for (int e = 0; e < 8; ++e) sdot += a[e] * qv[e];
-            for (int off = lpk >> 1; off > 0; off >>= 1) sdot += __shfl_xor(sdot, off, 64);
-            if (u < nk && sub == 0) sp[u] = sdot * scale;
-        }
-    }
-    __syncthreads();
-    float mx = -1.0e30f;
-    for (int u = tid; u < nk; u += nthr) mx = fmaxf(mx, sp[u]);
-    mx = block_max(mx, red);
-    float sum = 0.f;
-    for (int u = tid; u < nk; u += nthr) {
-        const float pr = __expf(sp[u] - mx);
-        sp[u] = pr;
-        sum += pr;
-    }
-    sum = block_sum(sum, red);
-    __syncthreads();
-    // lane group kk accumulates its keys' share of columns sub*8 .. sub*8+7; the groups are summed through LDS
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int u0 = 0; u0 < nk; u0 += 4 * kpp) {
-        uint4 vr[4];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int u = u0 + b * kpp + kk;
-            vr[b] = u < nk ? *(const uint4*)(vh + (long)u * ld + sub * 8) : make_uint4(0, 0, 0, 0);
+            for (int off = LPK >> 1; off > 0; off >>= 1) sdot += __shfl_xor(sdot, off, 64);
+            sc[i] = u < nk ? sdot * scale : -1.0e30f;
+            mloc = fmaxf(mloc, sc[i]);
         }
+        const float alpha = __expf(m - mloc);
+        m = mloc;
+        l *= alpha;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int u = u0 + b * kpp + kk;
-            const float pr = u < nk ? sp[u] : 0.f;
+        for (int e = 0; e < 8; ++e) acc[e] *= alpha;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const float pr = u0 + i * KPP + kk < nk ? __expf(sc[i] - m) : 0.f;
             float a[8];
-            unpack8(vr[b], a);
+            unpack8(vr[i], a);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] += pr * a[e];
+            for (int e = 0; e < 8; ++e) a[e] = u0 + i * KPP + kk == new_key ? vn[e] : u0 + i * KPP + kk < nk ? a[e] : 0.f;
+            l += pr;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] = fmaf(pr, a[e], acc[e]);
         }
     }
+    // merge the lane groups of a wave, then the waves (a group that had no key has m = -1e30 and zeros)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) part_buf[kk * d_head + sub * 8 + e] = acc[e];
-    __syncthreads();
-    if (tid < d_head) {
-        float t = 0.f;
-        for (int g = 0; g < kpp; ++g) t += part_buf[g * d_head + tid];
-        part_buf[tid] = t;      // only entry [0][tid] is overwritten, by the thread that has just read column tid
+    for (int off = LPK; off < 64; off <<= 1) {
+        const float mo = __shfl_xor(m, off, 64), lo = __shfl_xor(l, off, 64), mn = fmaxf(m, mo);
+        const float a0 = __expf(m - mn), a1 = __expf(mo - mn);
+        m = mn;
+        l = l * a0 + lo * a1;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = acc[e] * a0 + __shfl_xor(acc[e], off, 64) * a1;
     }
-    mx_out = mx;
-    sum_out = sum;
+    if (lane < LPK) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) part[wave][sub * 8 + e] = acc[e];
+        if (lane == 0) { part[wave][DH] = m; part[wave][DH + 1] = l; }
+    }
+    __syncthreads();
+    float mt = part[0][DH], lt = 0.f, ot = 0.f;
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mt = fmaxf(mt, part[w][DH]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float a = __expf(part[w][DH] - mt);
+        lt += a * part[w][DH + 1];
+        ot += a * part[w][tid % DH];
+    }
+    o = ot;
+    mx_out = mt;
+    sum_out = lt;
 }
 
-// LDS floats attend_range needs for nk keys with nthr threads
-static size_t attend_lds_floats(int nk, int nthr, int d_head) {
-    return (size_t)((nk + 3) & ~3) + (size_t)(nthr / (d_head / 8)) * d_head;
+// A head's output row, rounded, to memory, and with out.a its share of the output projection's A o (see lowrank_part).
+// c: this thread's column; every thread of the workgroup (NT of them) takes part.
+template <int DH, int NT, int NA>
+__device__ __forceinline__ void head_output(float v, int c, int head, int n_heads, const DecodeOut& out, uint4 (&av)[NA]) {
+    __shared__ float so[DH];
+    const bf16_t b = f32_to_bf16(v);
+    if ((int)threadIdx.x < DH) {
+        out.o[(long)head * DH + c] = b;
+        so[c] = bf16_to_f32(b);
+    }
+    if (!out.a) return;
+    __syncthreads();
+    lowrank_part<DH, NT, NA>(out.a + (long)head * DH, (long)n_heads * DH, out.r, so, DH, av, out.part + (long)head * out.r);
+}
+template <int DH, int NT, int NA>
+__device__ __forceinline__ void head_output_fetch(int head, int n_heads, const DecodeOut& out, uint4 (&av)[NA]) {
+    constexpr int LPR = DH / 8;
+    if (!out.a) return;
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+        av[i] = *(const uint4*)(out.a + (long)min((int)threadIdx.x / LPR + i * (NT / LPR), out.r - 1) * n_heads * DH + head * DH +
+                                threadIdx.x % LPR * 8);
 }
 
 // One workgroup per head over the whole cache.
-__global__ __launch_bounds__(1024) void attn_decode_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ k,
-                                                           const bf16_t* __restrict__ v, long ld, int n_keys, int d_head,
-                                                           float scale, bf16_t* __restrict__ o,
-                                                           const float2* __restrict__ rope_row) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    float* sp = (float*)smem;
-    float* part_buf = sp + ((n_keys + 3) & ~3);
-    __shared__ float red[16];
+template <int DH, int NW>
+__global__ __launch_bounds__(NW * 64) void attn_decode_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ k,
+                                                              bf16_t* __restrict__ v, long ld, int n_keys, float scale,
+                                                              DecodeOut out, DecodeFresh fresh) {
     const int head = blockIdx.x;
-    float mx, sum;
-    attend_range(q + (long)head * d_head, k + (long)head * d_head, v + (long)head * d_head, ld, n_keys, d_head, scale, sp,
-                 part_buf, red, mx, sum, rope_row, n_keys - 1);
-    if ((int)threadIdx.x < d_head) o[(long)head * d_head + threadIdx.x] = f32_to_bf16(part_buf[threadIdx.x] / sum);
+    float mx, sum, o;
+    attend_range<DH, NW>(q + (long)head * DH, k + (long)head * DH, v + (long)head * DH, ld, n_keys, scale, o, mx, sum, fresh,
+                         head, fresh.raw ? n_keys - 1 : -1);
+    uint4 av[1];
+    head_output_fetch<DH, NW * 64>(head, gridDim.x, out, av);
+    head_output<DH, NW * 64>(o / sum, threadIdx.x % DH, head, gridDim.x, out, av);
 }
 
 // Long windows: the keys are cut into n_split ranges, one workgroup per (head, range), so that the cache is read by
 // hundreds of workgroups instead of one per head.  Each writes its unnormalised output, its score maximum and its
 // sum of exponentials to ws[(head * n_split + range) * (d_head + 2)]; attn_decode_combine_kernel merges the ranges.
+template <int DH>
 __global__ __launch_bounds__(256) void attn_decode_split_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ k,
-                                                                const bf16_t* __restrict__ v, long ld, int n_keys,
-                                                                int d_head, float scale, int chunk,
-                                                                float* __restrict__ ws,
-                                                                const float2* __restrict__ rope_row) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    float* sp = (float*)smem;
-    float* part_buf = sp + ((chunk + 3) & ~3);
-    __shared__ float red[16];
+                                                                bf16_t* __restrict__ v, long ld, int n_keys, float scale,
+                                                                int chunk, float* __restrict__ ws, DecodeFresh fresh) {
     const int head = blockIdx.x;
     const int k0 = blockIdx.y * chunk, nk = min(chunk, n_keys - k0);   // nk >= 1 by the launch geometry
-    float mx, sum;
+    float mx, sum, o;
     const int new_key = n_keys - 1 - k0;                             // inside this range only for the last one
-    attend_range(q + (long)head * d_head, k + (long)k0 * ld + (long)head * d_head, v + (long)k0 * ld + (long)head * d_head,
-                 ld, nk, d_head, scale, sp, part_buf, red, mx, sum, rope_row, new_key < nk ? new_key : -1);
-    float* out = ws + ((long)head * gridDim.y + blockIdx.y) * (d_head + 2);
-    if ((int)threadIdx.x < d_head) out[threadIdx.x] = part_buf[threadIdx.x];
-    if (threadIdx.x == 0) { out[d_head] = mx; out[d_head + 1] = sum; }
+    attend_range<DH, 4>(q + (long)head * DH, k + (long)k0 * ld + (long)head * DH, v + (long)k0 * ld + (long)head * DH, ld, nk,
+                        scale, o, mx, sum, fresh, head, fresh.raw && new_key < nk ? new_key : -1);
+    float* out = ws + ((long)head * gridDim.y + blockIdx.y) * (DH + 2);
+    if ((int)threadIdx.x < DH) out[threadIdx.x] = o;
+    if (threadIdx.x == 0) { out[DH] = mx; out[DH + 1] = sum; }
 }
 
-__global__ void attn_decode_combine_kernel(const float* __restrict__ ws, int n_split, int d_head, bf16_t* __restrict__ o) {
-    const int head = blockIdx.x, c = threadIdx.x;
-    const float* w = ws + (long)head * n_split * (d_head + 2);
-    float M = -1.0e30f;
-    for (int i = 0; i < n_split; ++i) M = fmaxf(M, w[i * (d_head + 2) + d_head]);
-    float L = 0.f, acc = 0.f;
-    for (int i = 0; i < n_split; ++i) {
-        const float e = __expf(w[i * (d_head + 2) + d_head] - M);
-        L += e * w[i * (d_head + 2) + d_head + 1];
-        acc += e * w[i * (d_head + 2) + c];
+// One workgroup per head, one thread per column.  Lane i holds range i's maximum and sum, and every load is issued before
+// the first is used (one range after another, 32 of them took 15.9 us; now 8, with the share of A o).
+template <int DH>
+__global__ __launch_bounds__(DH) void attn_decode_combine_kernel(const float* __restrict__ ws, int n_split, DecodeOut out) {
+    static_assert(ATTN_DECODE_MAX_SPLIT <= 32, "one lane per range");
+    const int head = blockIdx.x, c = threadIdx.x, lane = threadIdx.x & 63, r = lane < n_split ? lane : n_split - 1;
+    const float* w = ws + (long)head * n_split * (DH + 2);
+    const float m = w[r * (DH + 2) + DH], l = w[r * (DH + 2) + DH + 1];
+    float t[ATTN_DECODE_MAX_SPLIT];
+#pragma unroll
+    for (int i = 0; i < ATTN_DECODE_MAX_SPLIT; ++i) t[i] = w[min(i, n_split - 1) * (DH + 2) + c];
+    uint4 av[8];
+    head_output_fetch<DH, DH>(head, gridDim.x, out, av);
+    __builtin_amdgcn_sched_barrier(0);
+    const float M = wave_max(m);             // (all lanes take part in the exchange)
+    const float e = lane < n_split ? __expf(m - M) : 0.f;
+    const float L = wave_sum(e * l);
+    float acc = 0.f;
+#pragma unroll
+    for (int i = 0; i < ATTN_DECODE_MAX_SPLIT; ++i) {
+        const float ei = __shfl(e, i, 64);
+        acc += i < n_split ? ei * t[i] : 0.f;
     }
-    o[(long)head * d_head + c] = f32_to_bf16(acc / L);
+    head_output<DH, DH>(acc / L, c, head, gridDim.x, out, av);
 }
 
 // ws (may be null): scratch of ws_elems floats for the split path; n_heads * n_split * (d_head + 2) of them are used.
-// rope_row (may be null): (cos, sin) of the newest position for i = 0 .. d_head / 2 - 1.  With it q and key row
-// n_keys - 1 are taken as unrotated, and the rotated key row is written back into k (k is then written, not only read).
-hipError_t launch_attention_decode(const bf16_t* q, bf16_t* k, const bf16_t* v, long ld, int n_keys, int n_heads,
-                                   int d_head, bf16_t* o, float* ws, size_t ws_elems, hipStream_t s,
-                                   const float2* rope_row) {
+// q is not read if `fresh` describes the newest token (then row n_keys - 1 of k and v is written).
+template <int DH>
+static hipError_t run_attention_decode(const bf16_t* q, bf16_t* k, bf16_t* v, long ld, int n_keys, int n_heads, int n_split,
+                                       const DecodeOut& out, float* ws, hipStream_t s, const DecodeFresh& fresh) {
+    const float scale = 1.f / sqrtf((float)DH);
+    if (n_split >= 2) {
+        const int chunk = cdiv(n_keys, n_split);
+        n_split = cdiv(n_keys, chunk);            // no empty range
+        attn_decode_split_kernel<DH><<<dim3(n_heads, n_split), 256, 0, s>>>(q, k, v, ld, n_keys, scale, chunk, ws, fresh);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        attn_decode_combine_kernel<DH><<<n_heads, DH, 0, s>>>(ws, n_split, out);
+        return hipGetLastError();
+    }
+    if (n_keys > ATTN_DECODE_MAX_UNSPLIT) return hipErrorInvalidValue;
+    if (n_keys > 128) attn_decode_kernel<DH, 16><<<n_heads, 1024, 0, s>>>(q, k, v, ld, n_keys, scale, out, fresh);
+    else attn_decode_kernel<DH, 4><<<n_heads, 256, 0, s>>>(q, k, v, ld, n_keys, scale, out, fresh);
+    return hipGetLastError();
+}
+hipError_t launch_attention_decode(const bf16_t* q, bf16_t* k, bf16_t* v, long ld, int n_keys, int n_heads, int d_head,
+                                   const DecodeOut& out, float* ws, size_t ws_elems, hipStream_t s, const DecodeFresh& fresh) {
     if (n_keys <= 0 || n_heads <= 0) return hipErrorInvalidValue;
-    if ((d_head != 64 && d_head != 128) || (ld & 7)) return hipErrorInvalidValue;
-    const float scale = 1.f / sqrtf((float)d_head);
+    if ((d_head != 64 && d_head != 128) || (ld & 7) || (out.a && (out.r & 7))) return hipErrorInvalidValue;
     // ranges of at least 128 keys, at most ATTN_DECODE_MAX_SPLIT of them, as many as the scratch holds
     // (below about 400 keys one workgroup per head is as fast and saves the second launch)
     int n_split = ws && n_keys >= 384 ? min(cdiv(n_keys, 128), ATTN_DECODE_MAX_SPLIT) : 1;
     if (ws && (size_t)n_heads * n_split * (d_head + 2) > ws_elems) n_split = (int)(ws_elems / ((size_t)n_heads * (d_head + 2)));
-    if (n_split >= 2) {
-        const int chunk = cdiv(n_keys, n_split);
-        n_split = cdiv(n_keys, chunk);            // no empty range
-        const size_t lds = attend_lds_floats(chunk, 256, d_head) * sizeof(float);
-        if (lds > 60 * 1024) return hipErrorInvalidValue;
-        attn_decode_split_kernel<<<dim3(n_heads, n_split), 256, lds, s>>>(q, k, v, ld, n_keys, d_head, scale, chunk, ws,
-                                                                          rope_row);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        attn_decode_combine_kernel<<<n_heads, d_head, 0, s>>>(ws, n_split, d_head, o);
-        return hipGetLastError();
-    }
-    const int nthr = n_keys > 128 ? 1024 : 256;
-    const size_t lds = attend_lds_floats(n_keys, nthr, d_head) * sizeof(float);
-    if (lds > 150 * 1024) return hipErrorInvalidValue;
-    hipError_t e = hipFuncSetAttribute((const void*)attn_decode_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attn_decode_kernel<<<n_heads, nthr, lds, s>>>(q, k, v, ld, n_keys, d_head, scale, o, rope_row);
-    return hipGetLastError();
+    return d_head == 128 ? run_attention_decode<128>(q, k, v, ld, n_keys, n_heads, n_split, out, ws, s, fresh)
+                         : run_attention_decode<64>(q, k, v, ld, n_keys, n_heads, n_split, out, ws, s, fresh);
 }
 
 // ---------------------------------------------------------------- greedy choice: index of the largest logit
@@ -350,10 +613,21 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
     __shared__ int bi[16];
     float best = -INFINITY;
     int idx = 0x7fffffff;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const float v = x[i];
+    auto take = [&](float v, int i) {
         if (v > best || (v == best && i < idx)) { best = v; idx = i; }
+    };
+    const int n4 = ((size_t)x & 15) == 0 ? n & ~3 : 0;      // sixteen bytes a time, eight loads in flight: 13 -> 6 us for 32000 values
+    for (int i0 = threadIdx.x * 4; i0 < n4; i0 += 8 * 4096) {
+        float4 v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = *(const float4*)(x + min(i0 + 4096 * j, n4 - 4));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int i = min(i0 + 4096 * j, n4 - 4);
+            take(v[j].x, i); take(v[j].y, i + 1); take(v[j].z, i + 2); take(v[j].w, i + 3);
+        }
     }
+    for (int i = n4 + threadIdx.x; i < n; i += blockDim.x) take(x[i], i);
     for (int off = 32; off > 0; off >>= 1) {
         const float ov = __shfl_xor(best, off, 64);
         const int oi = __shfl_xor(idx, off, 64);

@@ -150,7 +150,6 @@ hipError_t launch_transpose_table(const bf16_t* src_base, bf16_t* dst_base, cons
 hipError_t launch_copy2d_bf16(const bf16_t* src, long lds, int rows, int cols, bf16_t* dst, long ldd, hipStream_t s);
 
 // ---------------------------------------------------------------- one-token decoding (decode.hip)
-// y[N] = alpha * (W[N, K] x[K] + sum_j lora_b[n, j] lora_h[(n / rows_per_group) r + j]) (+ resid, fp32 output only)
 // Where a matrix-vector product takes its input vector from (see gemv_kernel)
 struct GemvPre {
     int mode = 0;                 // 0: x as given; 1: RMSNorm of h with gain; 2: SwiGLU of the gate|up row gu
@@ -160,13 +159,43 @@ struct GemvPre {
     const bf16_t* gu = nullptr;
     bf16_t* x_out = nullptr;      // if set, workgroup 0 stores the input vector it formed
 };
-hipError_t launch_gemv(const bf16_t* W, long ldw, const bf16_t* x, int N, int K, const bf16_t* lora_b, const float* lora_h,
-                       int r, int rows_per_group, float alpha, const float* resid, bf16_t* y_bf, float* y_f32,
-                       hipStream_t s, const GemvPre* pre = nullptr);
+// The low-rank term of a matrix-vector product (see gemv_kernel): either b, with h given, or the rows of a beside those of W.
+struct GemvLora {
+    const bf16_t* b = nullptr;            // [N, r]: adds sum_j b[n, j] h[(n / rows_per_group) r + j]
+    int r = 0, rows_per_group = 0;        // rows_per_group 0: one group
+    const float* h = nullptr;             // n_parts 0: h as it is; else n_parts vectors of r, h = scale * their sum (one group)
+    int n_parts = 0;
+    const bf16_t* a = nullptr;            // [n_a, K]: h_out = scale * a x
+    int n_a = 0;
+    float* h_out = nullptr;
+    float scale = 1.f;
+};
+// y[N] = alpha * (W[N, K] x[K] + low-rank term) (+ resid, fp32 output only)
+hipError_t launch_gemv(const bf16_t* W, long ldw, const bf16_t* x, int N, int K, const GemvLora& lora, float alpha,
+                       const float* resid, bf16_t* y_bf, float* y_f32, hipStream_t s, const GemvPre* pre = nullptr);
+// act = SwiGLU of one token's gate|up (raw fp32 [2 f] + B h, B [2 f, r], h [2 r]), and the shares of A_down act, one vector of
+// r per DECODE_SW columns
+constexpr int DECODE_SW = 128;
+hipError_t launch_decode_swiglu(const float* raw, const bf16_t* b, const float* h, int r, int f, bf16_t* act,
+                                const bf16_t* a_down, float* part, hipStream_t s);
 // one query row against cache rows 0 .. n_keys-1 (row stride ld), per head
 constexpr int ATTN_DECODE_MAX_SPLIT = 32;   // key ranges per head in the split decode-attention path
-hipError_t launch_attention_decode(const bf16_t* q, bf16_t* k, const bf16_t* v, long ld, int n_keys, int n_heads,
-                                   int d_head, bf16_t* o, float* ws, size_t ws_elems, hipStream_t s,
-                                   const float2* rope_row = nullptr);
+constexpr int ATTN_DECODE_MAX_UNSPLIT = 30208;   // keys that one workgroup per head takes on
+struct DecodeFresh {                      // the newest token, if its q, k, v are still to be formed: raw + B h
+    const float* raw = nullptr;           // [3 d]
+    const bf16_t* b = nullptr;            // [3 d, r]
+    const float* h = nullptr;             // [3 r]
+    int r = 0, d = 0;
+    const float2* rope = nullptr;         // (cos, sin) of its position for i = 0 .. d_head / 2 - 1
+};
+struct DecodeOut {
+    bf16_t* o = nullptr;                  // [n_heads * d_head]
+    const bf16_t* a = nullptr;            // with [r, n_heads * d_head]: part[head * r + j] = that head's share of a o
+    int r = 0;
+    float* part = nullptr;
+};
+hipError_t launch_attention_decode(const bf16_t* q, bf16_t* k, bf16_t* v, long ld, int n_keys, int n_heads, int d_head,
+                                   const DecodeOut& out, float* ws, size_t ws_elems, hipStream_t s,
+                                   const DecodeFresh& fresh = DecodeFresh{});
 // index of the largest of n floats, lowest index among equals
 hipError_t launch_argmax(const float* x, int n, int* out, hipStream_t s);

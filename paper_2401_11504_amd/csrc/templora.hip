@@ -170,6 +170,8 @@ struct tl_lora {
     bool kv_keep = false;
     std::vector<bf16_t*> kvbuf;
     float* lora_h = nullptr;      // [3 r] scaled low-rank activations of the projection group in flight
+    float* dec_raw = nullptr;     // [max(3 d, 2 f)] frozen part of one token's q|k|v or gate|up
+    float* dec_part = nullptr;    // shares of A o (one per head) or A_down act (one per DECODE_SW columns), r each
     float* attn_ws = nullptr;     // partial results of the split decode attention
     size_t attn_ws_elems = 0;
     int* next_dev = nullptr;
@@ -476,6 +478,8 @@ extern "C" tl_status tl_lora_init(tl_model* m, const tl_lora_cfg* cfg, tl_lora**
         HIPCHK(hipHostMalloc((void**)&L->loss_host, 4 * sizeof(float), hipHostMallocDefault));
         HIPCHK(hipHostMalloc((void**)&L->next_host, 4 * sizeof(int), hipHostMallocDefault));
         TLCHK(L->pool.alloc(&L->lora_h, (size_t)3 * r));
+        TLCHK(L->pool.alloc(&L->dec_raw, (size_t)std::max(3 * d, 2 * f)));
+        TLCHK(L->pool.alloc(&L->dec_part, (size_t)std::max(mc.n_heads, cdiv(f, DECODE_SW)) * r));
         L->attn_ws_elems = (size_t)mc.n_heads * ATTN_DECODE_MAX_SPLIT * (mc.d_head + 2);
         TLCHK(L->pool.alloc(&L->attn_ws, L->attn_ws_elems));
         TLCHK(L->pool.alloc(&L->next_dev, (size_t)4));
@@ -908,8 +912,7 @@ static tl_status emit_next(tl_lora* L, const float* h_last, int32_t* next_token,
     GemvPre nf;    // the final norm is formed inside the lm_head product
     nf.mode = 1; nf.h = h_last; nf.gain = m->gf; nf.eps = c.rms_eps;
     prof_mark(L);
-    hipError_t e = launch_gemv(m->head, c.d_model, nullptr, c.vocab, c.d_model, nullptr, nullptr, 0, 0, 1.f, nullptr,
-                               nullptr, L->logits, s, &nf);
+    hipError_t e = launch_gemv(m->head, c.d_model, nullptr, c.vocab, c.d_model, GemvLora{}, 1.f, nullptr, nullptr, L->logits, s, &nf);
     prof_mark(L);
     if (L->prof_on) L->prof_flop += 2.0 * c.vocab * (double)c.d_model;
     HIPCHK(e);
@@ -978,21 +981,32 @@ extern "C" tl_status tl_cache_reuse(tl_lora* L, int32_t on) {
     return TL_OK;
 }
 
-// One LoRA-adapted projection group of a single token: h = s A x, then y = W x + B h (+ residual)
-// x: the group's input vector; with `pre` it is formed (norm / SwiGLU) inside the first launch, which stores it to x
-static tl_status group_decode(tl_lora* L, int l, int g, const bf16_t* x, bf16_t* y_bf, float* y_f32, const float* resid,
-                              const GemvPre* pre = nullptr) {
+// One projection group of a single token.  q|k|v and gate|up: raw = W x (fp32) with x the norm of h, and beside it
+// lora_h = s A x; whoever reads raw adds B lora_h.  o and down: y = W x + B h + resid, h = s * the sum of n_parts shares of
+// A x that the launch before left in dec_part.
+static tl_status group_decode_in(tl_lora* L, int l, int g, const float* h, const float* gain) {
     tl_model* m = L->model;
-    hipStream_t s = m->stream;
     const int G = kGroupCount[g], din = m->d_in(g), dout = m->d_out(g), r = L->cfg.rank;
-    const LayerOff& o = L->off[l];
-    HIPCHK(launch_gemv(L->S + o.A[g], din, x, G * r, din, nullptr, nullptr, 0, 0, L->s, nullptr, nullptr, L->lora_h, s,
-                       pre));
+    GemvPre pre;
+    pre.mode = 1; pre.h = h; pre.gain = gain; pre.eps = m->cfg.rms_eps;
+    GemvLora lo;
+    lo.a = L->S + L->off[l].A[g]; lo.n_a = G * r; lo.h_out = L->lora_h; lo.scale = L->s;
     prof_mark(L);   // timing (when on) brackets the launches that stream a frozen matrix
-    hipError_t e = launch_gemv(m->layers[l].w[g], din, x, G * dout, din, L->S + o.B[g], L->lora_h, r, dout, 1.f, resid,
-                               y_bf, y_f32, s);
+    hipError_t e = launch_gemv(m->layers[l].w[g], din, nullptr, G * dout, din, lo, 1.f, nullptr, nullptr, L->dec_raw, m->stream, &pre);
     prof_mark(L);
-    if (L->prof_on) L->prof_flop += 2.0 * G * dout * ((double)din + r);
+    if (L->prof_on) L->prof_flop += 2.0 * G * (dout + r) * (double)din;
+    HIPCHK(e);
+    return TL_OK;
+}
+static tl_status group_decode_out(tl_lora* L, int l, int g, const bf16_t* x, float* y, const float* resid, int n_parts) {
+    tl_model* m = L->model;
+    const int din = m->d_in(g), dout = m->d_out(g), r = L->cfg.rank;
+    GemvLora lo;
+    lo.b = L->S + L->off[l].B[g]; lo.r = r; lo.h = L->dec_part; lo.n_parts = n_parts; lo.scale = L->s;
+    prof_mark(L);
+    hipError_t e = launch_gemv(m->layers[l].w[g], din, x, dout, din, lo, 1.f, resid, nullptr, y, m->stream);
+    prof_mark(L);
+    if (L->prof_on) L->prof_flop += 2.0 * dout * ((double)din + r);
     HIPCHK(e);
     return TL_OK;
 }
@@ -1018,18 +1032,21 @@ extern "C" tl_status tl_decode_step(tl_lora* L, int32_t token, int32_t* next_tok
         const float* h_in = L->hs[l];
         float* h_out = L->hs[l + 1];
         bf16_t* cache = L->kv_keep ? L->kvbuf[l] : sv.qkv;
-        bf16_t* row = cache + (size_t)p * 3 * d;                  // the new cache row: q | k | v of position p
-        GemvPre n1, n2, sw;
-        n1.mode = 1; n1.h = h_in; n1.gain = W.g1; n1.eps = c.rms_eps; n1.x_out = sv.x1;
-        n2.mode = 1; n2.h = sv.hmid; n2.gain = W.g2; n2.eps = c.rms_eps; n2.x_out = sv.x2;
-        sw.mode = 2; sw.gu = sv.gu; sw.x_out = sv.act;
-        TLCHK(group_decode(L, l, G_QKV, sv.x1, row, nullptr, nullptr, &n1));
-        // q and k of the new row are rotated inside the attention launch (the rotated k goes back into the cache)
-        HIPCHK(launch_attention_decode(row, cache + d, cache + 2 * d, 3L * d, p + 1, c.n_heads, c.d_head, sv.o,
-                                       L->attn_ws, L->attn_ws_elems, s, m->rope + (size_t)p * (c.d_head / 2)));
-        TLCHK(group_decode(L, l, G_O, sv.o, nullptr, sv.hmid, h_in));
-        TLCHK(group_decode(L, l, G_GU, sv.x2, sv.gu, nullptr, nullptr, &n2));
-        TLCHK(group_decode(L, l, G_DOWN, sv.act, nullptr, h_out, sv.hmid, &sw));
+        const LayerOff& o = L->off[l];
+        TLCHK(group_decode_in(L, l, G_QKV, h_in, W.g1));
+        // the attention launch finishes q, k and v of the new token, rotates q and k and puts k and v into the cache
+        DecodeFresh fresh;
+        fresh.raw = L->dec_raw; fresh.b = L->S + o.B[G_QKV]; fresh.h = L->lora_h; fresh.r = L->cfg.rank; fresh.d = d;
+        fresh.rope = m->rope + (size_t)p * (c.d_head / 2);
+        DecodeOut out;
+        out.o = sv.o; out.a = L->S + o.A[G_O]; out.r = L->cfg.rank; out.part = L->dec_part;
+        HIPCHK(launch_attention_decode(nullptr, cache + d, cache + 2 * d, 3L * d, p + 1, c.n_heads, c.d_head, out, L->attn_ws,
+                                       L->attn_ws_elems, s, fresh));
+        TLCHK(group_decode_out(L, l, G_O, sv.o, sv.hmid, h_in, c.n_heads));
+        TLCHK(group_decode_in(L, l, G_GU, sv.hmid, W.g2));
+        HIPCHK(launch_decode_swiglu(L->dec_raw, L->S + o.B[G_GU], L->lora_h, L->cfg.rank, c.d_ffn, sv.act,
+                                    L->S + o.A[G_DOWN], L->dec_part, s));
+        TLCHK(group_decode_out(L, l, G_DOWN, sv.act, h_out, sv.hmid, cdiv(c.d_ffn, DECODE_SW)));
     }
     TLCHK(emit_next(L, L->hs[c.n_layers], next_token, logits_out));
     L->kv_len = p + 1;
@@ -1449,8 +1466,10 @@ extern "C" tl_status tl_k_gemv(const uint16_t* W, int32_t ldw, const uint16_t* x
                                const float* resid, void* y, int32_t y_f32, void* hip_stream) {
     KARGS_OK(W && x && y && N >= 0 && K > 0 && (K & 7) == 0 && (ldw & 7) == 0 && (!lora_b || (lora_h && r > 0)) &&
                  (y_f32 || !resid), "tl_k_gemv");
-    HIPCHK(launch_gemv(W, ldw, x, N, K, lora_b, lora_h, r, rows_per_group, alpha, resid, y_f32 ? nullptr : (bf16_t*)y,
-                       y_f32 ? (float*)y : nullptr, (hipStream_t)hip_stream));
+    GemvLora lo;
+    lo.b = lora_b; lo.h = lora_h; lo.r = r; lo.rows_per_group = rows_per_group;
+    HIPCHK(launch_gemv(W, ldw, x, N, K, lo, alpha, resid, y_f32 ? nullptr : (bf16_t*)y, y_f32 ? (float*)y : nullptr,
+                       (hipStream_t)hip_stream));
     return TL_OK;
 }
 extern "C" tl_status tl_k_gemv_pre(const uint16_t* W, int32_t ldw, int32_t N, int32_t K, int32_t mode, const float* h,
@@ -1460,8 +1479,7 @@ extern "C" tl_status tl_k_gemv_pre(const uint16_t* W, int32_t ldw, int32_t N, in
                  ((mode == 1 && h && gain) || (mode == 2 && gu)), "tl_k_gemv_pre");
     GemvPre pre;
     pre.mode = mode; pre.h = h; pre.gain = gain; pre.eps = eps; pre.gu = gu; pre.x_out = x_out;
-    HIPCHK(launch_gemv(W, ldw, nullptr, N, K, nullptr, nullptr, 0, 0, 1.f, nullptr, nullptr, y, (hipStream_t)hip_stream,
-                       &pre));
+    HIPCHK(launch_gemv(W, ldw, nullptr, N, K, GemvLora{}, 1.f, nullptr, nullptr, y, (hipStream_t)hip_stream, &pre));
     return TL_OK;
 }
 extern "C" tl_status tl_k_attention_decode(const uint16_t* q, const uint16_t* k, const uint16_t* v, int32_t ld,
@@ -1469,8 +1487,10 @@ extern "C" tl_status tl_k_attention_decode(const uint16_t* q, const uint16_t* k,
                                            float* workspace, size_t workspace_elems, void* hip_stream) {
     KARGS_OK(q && k && v && o && n_keys > 0 && n_heads > 0 && (d_head == 64 || d_head == 128) && (ld & 7) == 0,
              "tl_k_attention_decode");
-    HIPCHK(launch_attention_decode(q, (bf16_t*)k, v, ld, n_keys, n_heads, d_head, o, workspace, workspace_elems,
-                                   (hipStream_t)hip_stream));   // without a RoPE row nothing is written to k
+    DecodeOut out;
+    out.o = o;
+    HIPCHK(launch_attention_decode(q, (bf16_t*)k, (bf16_t*)v, ld, n_keys, n_heads, d_head, out, workspace, workspace_elems,
+                                   (hipStream_t)hip_stream));   // without a fresh token nothing is written to k and v
     return TL_OK;
 }
 extern "C" tl_status tl_k_argmax(const float* x, int32_t n, int32_t* out, void* hip_stream) {
