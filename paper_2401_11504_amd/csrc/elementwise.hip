@@ -366,6 +366,11 @@ hipError_t launch_labels(const int* tokens, int T, int* labels, hipStream_t s) {
 // ---------------------------------------------------------------- fused softmax cross-entropy
 // One block per position.  Pass 1: online max / sum-exp over the vocabulary; pass 2 (targets only):
 // dlogits = (softmax - onehot) / n_targets.  Non-target rows get nll = 0 and zero gradient.
+// NV > 0: the row (V <= 512 NV) is fetched once, every load issued before the first is used, and stays in registers for both
+// passes; the sums are taken in the order of the other form (NV = 0, what is left for longer rows), so the bits are the same.
+// 4096 rows of 32000: 333 -> 211 us (0.8 GB); taking the maximum first, in 16-byte pieces, would be 142 us but rounds
+// differently.
+template <int NV>
 __global__ __launch_bounds__(512) void cross_entropy_kernel(const float* __restrict__ logits,
                                                             const int* __restrict__ labels, int T, int V,
                                                             int first_target, float inv_n, float* __restrict__ nll,
@@ -380,11 +385,22 @@ __global__ __launch_bounds__(512) void cross_entropy_kernel(const float* __restr
         if (dz) for (int i = threadIdx.x; i < V; i += blockDim.x) dz[i] = 0;
         return;
     }
+    float xs[NV > 0 ? NV : 1];
+    if constexpr (NV > 0) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) xs[j] = z[min((int)threadIdx.x + 512 * j, V - 1)];
+    }
     float m = -INFINITY, ssum = 0.f;
-    for (int i = threadIdx.x; i < V; i += blockDim.x) {
-        float x = z[i];
+    auto take = [&](float x) {
         if (x > m) { ssum *= __expf(m - x); m = x; }
         ssum += __expf(x - m);
+    };
+    if constexpr (NV > 0) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            if ((int)threadIdx.x + 512 * j < V) take(xs[j]);
+    } else {
+        for (int i = threadIdx.x; i < V; i += blockDim.x) take(z[i]);
     }
     const float M = block_max(m, red);
     ssum = block_sum(ssum * __expf(m - M), red);
@@ -392,10 +408,17 @@ __global__ __launch_bounds__(512) void cross_entropy_kernel(const float* __restr
     const int lab = labels[t];
     if (threadIdx.x == 0) nll[t] = lse - z[lab];
     if (dz) {
-        for (int i = threadIdx.x; i < V; i += blockDim.x) {
-            float p = __expf(z[i] - lse);
+        auto put = [&](float x, int i) {
+            float p = __expf(x - lse);
             if (i == lab) p -= 1.f;
             dz[i] = f32_to_bf16(p * inv_n);
+        };
+        if constexpr (NV > 0) {
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+                if ((int)threadIdx.x + 512 * j < V) put(xs[j], threadIdx.x + 512 * j);
+        } else {
+            for (int i = threadIdx.x; i < V; i += blockDim.x) put(z[i], i);
         }
     }
 }
@@ -423,8 +446,8 @@ hipError_t launch_cross_entropy(const float* logits, const int* labels, int T, i
         hipError_t e = launch_fill_f32(nll, (size_t)row0, 0.f, s);
         if (e != hipSuccess) return e;
     }
-    cross_entropy_kernel<<<T - row0, 512, 0, s>>>(logits, labels, T, V, first_target, 1.f / (float)n_targets, nll, dlogits,
-                                                  row0);
+    const auto kern = V <= 512 * 16 ? cross_entropy_kernel<16> : V <= 512 * 64 ? cross_entropy_kernel<64> : cross_entropy_kernel<0>;
+    kern<<<T - row0, 512, 0, s>>>(logits, labels, T, V, first_target, 1.f / (float)n_targets, nll, dlogits, row0);
     if (loss_sum) nll_sum_kernel<<<1, 256, 0, s>>>(nll, T, loss_sum, flag);
     return hipGetLastError();
 }
