@@ -578,17 +578,19 @@ static tl_status flush_pending(tl_lora* L) {
     return TL_OK;
 }
 
-// The partial tiles a split dX GEMM leaves to the RMSNorm backward are bf16: dX was a bf16 tensor before the reduce
-// pass was folded into the norm, so the gradient loses nothing it had, and the tiles cost half the bytes on both sides.
-constexpr int kDeferBf16 = 1;
+// Partial tiles that a split dX GEMM leaves to the RMSNorm backward: how many, and whether they are bf16.  They are for
+// contractions of whole 64-element tiles (ranks whose G r is a multiple of 64): dX was a bf16 tensor before the reduce pass was
+// folded into the norm, each half is rounded as dX was, and the tiles cost half the bytes on both sides.  Every other
+// contraction was one fp32 sum when that was decided and keeps fp32 partials: halves that cancel lose nothing.
+struct DxParts { int n = 0, bf16 = 0; };
 
 // backward: dH = s dY B;  dX = dY W + D o (dH A)  (D = 1 without dropout: then one GEMM with the contraction extended
 // by dH | A);  the products dA = dH^T X and dB = dY^T Hs are appended to `tn`, which
 // the caller launches once per layer (dY, dH, X and Hs must stay untouched until then).
-// deferred (may be null): where the dX GEMM may report that it left split partial tiles in L->partial instead of
+// parts (may be null): where the dX GEMM may report that it left split partial tiles in L->partial instead of
 // writing dX (see GemmNT::deferred); the caller's next kernel then adds them up.
 static tl_status group_bwd(tl_lora* L, int l, int g, const bf16_t* dY, const bf16_t* X, int T, bf16_t* dX,
-                           GemmTNGroup& tn, int* deferred = nullptr) {
+                           GemmTNGroup& tn, DxParts* parts = nullptr) {
     tl_model* m = L->model;
     hipStream_t s = m->stream;
     const int G = kGroupCount[g], din = m->d_in(g), dout = m->d_out(g), r = L->cfg.rank;
@@ -608,9 +610,9 @@ static tl_status group_bwd(tl_lora* L, int l, int g, const bf16_t* dY, const bf1
         if (!L->drop_on) { x.A2 = dH; x.lda2 = G * r; x.B2 = L->ST + o.AT[g]; x.ldb2 = G * r; x.K2 = G * r; }
         x.C = dX; x.ldc = din;
         x.partial = L->partial; x.partial_elems = L->partial_elems;
-        if (deferred && !L->drop_on) {   // with dropout dX is needed as a whole below
-            x.deferred = deferred;
-            x.partial_bf16 = kDeferBf16;
+        if (parts && !L->drop_on) {   // with dropout dX is needed as a whole below
+            x.deferred = &parts->n;
+            x.partial_bf16 = parts->bf16 = x.K % 64 == 0 && x.K2 % 64 == 0;
         }
         HIPCHK(timed_gemm(L, x));
         if (L->drop_on) {
@@ -683,18 +685,18 @@ static tl_status layer_backward(tl_lora* L, int l, const float* h_in, const floa
     HIPCHK(launch_swiglu_bwd(L->d_act, sv.gu, T, f, L->dgu, s));
     // the two dX GEMMs that feed an RMSNorm backward have a long contraction and may be split: the norm kernel then
     // adds the partial tiles up itself (no reduce launch, no bf16 round trip of dX)
-    int nsp = 0;
-    TLCHK(group_bwd(L, l, G_GU, L->dgu, sv.x2, T, L->dx, tn, &nsp));
+    DxParts parts;
+    TLCHK(group_bwd(L, l, G_GU, L->dgu, sv.x2, T, L->dx, tn, &parts));
     HIPCHK(launch_rmsnorm_bwd(L->dx, sv.hmid, W.g2, dh_out, T, d, c.rms_eps, L->dhmid, L->dhmid_bf, s,
-                              nsp ? L->partial : nullptr, nsp, (long)T * d, kDeferBf16));
+                              parts.n ? L->partial : nullptr, parts.n, (long)T * d, parts.bf16));
     TLCHK(group_bwd(L, l, G_O, L->dhmid_bf, sv.o, T, L->d_o, tn));
     // one launch for every dQ and dK/dV part, longest first (dq, dk rotated back inside): 120 -> 84 us per layer at 1024 tokens
     HIPCHK(launch_attention_bwd(sv.qkv, sv.qkv + d, sv.qkv + 2 * d, sv.o, L->d_o, sv.lse, 3L * d, d, T, c.n_heads,
                                 c.d_head, L->dqkv, L->dqkv + d, L->dqkv + 2 * d, L->delta, m->rope, s));
-    nsp = 0;
+    parts = DxParts();
     // dh_in == null: the caller does not want the gradient of the layer's input (the bottom layer of an update: it would
     // feed only the frozen embedding), so dX of q|k|v and the first RMSNorm's backward are left out; dA / dB are not
-    TLCHK(group_bwd(L, l, G_QKV, L->dqkv, sv.x1, T, dh_in ? L->dx : nullptr, tn, &nsp));
+    TLCHK(group_bwd(L, l, G_QKV, L->dqkv, sv.x1, T, dh_in ? L->dx : nullptr, tn, &parts));
     // all eleven dA / dB products of the layer in one launch on the side stream
     if (tn.n > TN_GROUP_MAX) return fail(TL_ERR_ARG, "too many products for one grouped launch");
     HIPCHK(hipEventRecord(L->ev_ready[par], s));
@@ -715,7 +717,7 @@ static tl_status layer_backward(tl_lora* L, int l, const float* h_in, const floa
     // dh_in_bf must not be the buffer dh_out_bf (dB of the down projection is still reading it): callers alternate
     if (dh_in)
         HIPCHK(launch_rmsnorm_bwd(L->dx, h_in, W.g1, L->dhmid, T, d, c.rms_eps, dh_in, dh_in_bf, s,
-                                  nsp ? L->partial : nullptr, nsp, (long)T * d, kDeferBf16));
+                                  parts.n ? L->partial : nullptr, parts.n, (long)T * d, parts.bf16));
     return TL_OK;
 }
 

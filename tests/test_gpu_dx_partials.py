@@ -1,0 +1,56 @@
+"""The input gradient of gate|up at ranks that are no multiple of 64: its sum is kept in fp32 wherever the contraction is
+cut.  The case is built so that the gate half and the up half of the sum are large and nearly cancel: partial sums rounded to
+bf16 leave an error of the size of the halves.  Reference: fp64 from the same bf16 operands."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2401_11504_amd import synth  # noqa: E402
+from test_gpu_kernels import H, api  # noqa: E402,F401
+
+T, D, F, HEADS = 1024, 2048, 5632, 16
+G = -2.2178     # silu(g) + g silu'(g) = 0 here: with u = -g the two halves are opposite
+# dgate and dup are stored in bf16: F independent roundings of 2^-9 / sqrt(3) at most, averaged: 1.5e-5 of a half.  Halves
+# rounded to bf16 would be off by about 2^-9 / sqrt(3) x 0.7 each, 1e-3 in all.
+TOL = 1e-4
+
+
+@pytest.mark.parametrize("rank", [8, 16, 40])
+def test_gate_up_input_gradient_is_summed_in_fp32(api, H, rank):  # noqa: F811
+    assert api.tl_k_gemm_nt_plan(T, D, 2 * F, 2 * rank, 1 << 28)[:2] == ("256x128-split", 4)
+    rng = np.random.default_rng(rank)
+    z = np.repeat(rng.normal(0, 0.02, D // 2), 2) * np.tile([1.0, -1.0], D // 2)     # no component along the rows of h
+    row = synth.round_bf16((G / D + z).astype(np.float32))
+    w_down = synth.round_bf16(rng.uniform(0.5, 1.0, F).astype(np.float32) / D)
+    tau = synth.round_bf16(rng.uniform(0.5, 1.0, T).astype(np.float32))
+    zero = torch.zeros(D, D, dtype=torch.bfloat16, device="cuda")      # no attention branch: the FFN sees h_in itself
+    gate = H.to_dev_bf16(np.tile(row, (F, 1)))
+    ones = torch.ones(D, device="cuda")
+    weights = [zero, zero, zero, zero, gate, -gate, H.to_dev_bf16(np.tile(w_down, (D, 1))), ones, ones, None, None, None]
+    model = api.tl_model_create(1, D, HEADS, D // HEADS, F, 0, T, weights, 1e-5, 10000.0)
+    lora = api.tl_lora_init(model, rank, float(rank), seed=1)          # B = 0
+    h_in = torch.ones(T, D, device="cuda")
+    dh_out = H.to_dev_f32(np.tile(tau[:, None], (1, D)))
+    h_out, dh_in = torch.empty_like(h_in), torch.empty_like(h_in)
+    api.tl_layer_step(lora, 0, h_in, dh_out, h_out, dh_in)
+    torch.cuda.synchronize()
+
+    r64 = lambda x: synth.round_bf16(np.asarray(x, np.float32)).astype(np.float64)  # noqa: E731
+    a = row.astype(np.float64)
+    g = float(r64([a.sum()])[0])                                       # x = bf16(1 / sqrt(1 + 1e-5)) = 1
+    sig = 1.0 / (1.0 + np.exp(-g))
+    da = r64(np.outer(tau, w_down.astype(np.float64)) * D)
+    dgate, dup = r64(da * -g * (sig + g * sig * (1.0 - sig))), r64(da * g * sig)
+    dx = np.outer(dgate.sum(1) - dup.sum(1), a)
+    rho = 1.0 / np.sqrt(1.0 + 1e-5)
+    xn = rho * np.ones(D)
+    want = tau[:, None] + rho * (dx - xn * (dx @ xn / D)[:, None])
+    half = np.linalg.norm(np.outer(dup.sum(1), a))
+    got = dh_in.cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(dx) < 0.05 * half                            # the halves do cancel
+    err = np.linalg.norm(got - want) / half
+    assert err < TOL, err
+    api.tl_lora_free(lora)
+    api.tl_model_destroy(model)
