@@ -63,6 +63,11 @@ __device__ __forceinline__ void lowrank_part(const bf16_t* a, long lda, int r, c
 // gate|up row, x = bf16(silu(g) u).  Modes 1 and 2 do the work of the separate kernels in every workgroup (the
 // vector is a few KB out of L2), and workgroup 0 stores x to pre.x_out for the launches that follow.
 constexpr int GEMV_AHEAD = 8;
+// LDS: x, and for the sum of the parts of h 2 KB behind it; a vector so long that it leaves no room for those (K above 80896)
+// has them in its place once the product is done.
+constexpr size_t LDS_PER_CU = 160 * 1024;
+__host__ __device__ constexpr size_t gemv_x_bytes(int K) { return ((size_t)K * 2 + 15) & ~(size_t)15; }
+__host__ __device__ constexpr bool gemv_parts_fit(int K) { return gemv_x_bytes(K) + 512 * sizeof(float) <= LDS_PER_CU; }
 
 // a long row's product with x, w0 holding this lane's share of its first 4096 columns: eight loads ahead of the eight that
 // are being added up
@@ -104,7 +109,8 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float red[16];
     bf16_t* sx = (bf16_t*)smem;
-    float *hp = (float*)(smem + (((size_t)K * 2 + 15) & ~(size_t)15)), *hs = hp + 256;      // only with lora.n_parts
+    const bool parts_last = !gemv_parts_fit(K);
+    float *hp = (float*)(smem + (parts_last ? 0 : gemv_x_bytes(K))), *hs = hp + 256;        // only with lora.n_parts
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rows = N + lora.n_a, n0 = ((int)blockIdx.x * 4 + wave) * R;
 
@@ -194,19 +200,20 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
     } else {
         for (int i = threadIdx.x * 8; i < K; i += 2048) *(uint4*)(sx + i) = *(const uint4*)(x + i);
     }
-    if (hg) hp[threadIdx.x] = hsum;
+    if (hg && !parts_last) hp[threadIdx.x] = hsum;
     __syncthreads();
     if (pre.x_out && blockIdx.x == 0)
         for (int i = threadIdx.x * 8; i < K; i += 2048) *(uint4*)(pre.x_out + i) = *(const uint4*)(sx + i);
-    if (hg) {
+    auto add_parts = [&] {
         if ((int)threadIdx.x < lora.r) {
             float h = 0.f;
             for (int g = 0; g < hg; ++g) h += hp[g * lora.r + threadIdx.x];
             hs[threadIdx.x] = lora.scale * h;
         }
         __syncthreads();
-    }
-    if (n0 >= rows) return;
+    };
+    if (hg && !parts_last) add_parts();
+    if (n0 >= rows && !(hg && parts_last)) return;      // (the barriers below are for every wave)
 
     float acc[R];
 #pragma unroll
@@ -223,6 +230,12 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
 #pragma unroll
             for (int i = 0; i < R; ++i) acc[i] = k < K ? dot8(wv[i][u], b, acc[i]) : acc[i];
         }
+    }
+    if (hg && parts_last) {
+        __syncthreads();                                // x has been read
+        hp[threadIdx.x] = hsum;
+        __syncthreads();
+        add_parts();
     }
     if (lora.b) {
 #pragma unroll
@@ -248,15 +261,16 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
 hipError_t launch_gemv(const bf16_t* W, long ldw, const bf16_t* x, int N, int K, const GemvLora& lora, float alpha,
                        const float* resid, bf16_t* y_bf, float* y_f32, hipStream_t s, const GemvPre* pre) {
     if (N <= 0) return hipSuccess;
-    if ((K & 7) || (ldw & 7) || K <= 0 || (size_t)K * 2 > 160 * 1024 || (!y_bf && !y_f32)) return hipErrorInvalidValue;
+    if ((K & 7) || (ldw & 7) || K <= 0 || (!y_bf && !y_f32)) return hipErrorInvalidValue;
     GemvPre p = pre ? *pre : GemvPre{};
+    if (gemv_x_bytes(K) + (p.mode == 1 ? 16 * sizeof(float) : 0) > LDS_PER_CU) return hipErrorInvalidValue;   // (a norm has block sums beside x)
     if (p.mode < 0 || p.mode > 2 || (p.mode == 0 && !x) || (p.mode == 1 && (!p.h || !p.gain)) || (p.mode == 2 && !p.gu))
         return hipErrorInvalidValue;
     GemvLora lo = lora;
     if (lo.rows_per_group <= 0) lo.rows_per_group = N;
     if (lo.n_a > 0 ? (!lo.a || !lo.h_out || lo.b) : (lo.b && (!lo.h || lo.r < 1))) return hipErrorInvalidValue;
     if (lo.n_parts > 0 && (!lo.b || lo.r > 256 || lo.rows_per_group < N)) return hipErrorInvalidValue;   // summed for one group
-    const size_t lds = lo.n_parts > 0 ? (((size_t)K * 2 + 15) & ~(size_t)15) + 512 * sizeof(float) : (size_t)K * sizeof(bf16_t);
+    const size_t lds = gemv_x_bytes(K) + (lo.n_parts > 0 && gemv_parts_fit(K) ? 512 * sizeof(float) : 0);
     // Two rows per wave halve the number of times the input vector is formed; worth it while that leaves every CU a few
     // workgroups.
     const bool two = N >= 8192;

@@ -29,3 +29,28 @@ def test_decoded_token_is_the_chunk_path_s(api, H, heads, d_head, d_ffn, rank, n
     check(second, want, 1e-2, "second token")
     api.tl_lora_free(lora)
     model.close()
+
+
+# The down projection's input vector is kept in LDS (160 KB): up to 80896 entries the sums of the low-rank shares fit behind
+# it, beyond that they take its place after the product, and 81920 is the widest vector.
+@pytest.mark.parametrize("d_ffn,rank", [(80896, 8), (80904, 256), (80904, 8), (81888, 40), (81920, 16)])
+def test_widest_feed_forward(api, H, d_ffn, rank):  # noqa: F811
+    shape = synth.Shape(1, 128, 2, 64, d_ffn, 504, rank, float(rank))
+    model = H.Model(shape, 78, max_tokens=12)
+    lora, _ = H.new_lora(model, 78, b_std=0.02)
+    tok = synth.zipf_tokens(78, 10, shape.vocab)
+    api.tl_prefill(lora, tok[:9], shape.vocab)
+    _, got = api.tl_decode_step(lora, int(tok[9]), shape.vocab)
+    _, want = api.tl_prefill(lora, tok, shape.vocab)
+    check(got, want, 1e-2, "logits")
+    api.tl_lora_free(lora)
+    model.close()
+
+
+def test_wider_input_vectors_are_refused(api, H):  # noqa: F811
+    W, x, y = (torch.zeros(n, dtype=torch.bfloat16, device="cuda") for n in (81928, 81928, 8))
+    with pytest.raises(api.TlError):
+        api.tl_k_gemv(W.view(1, -1), x, y[:1])
+    h = torch.zeros(81896, device="cuda")               # a norm also needs its block sums there
+    with pytest.raises(api.TlError):
+        api.tl_k_gemv_pre(W[:81896].view(1, -1), h[:1], 1, h=h, gain=h, eps=1e-5)
