@@ -54,18 +54,17 @@ __device__ __forceinline__ void lowrank_part(const bf16_t* a, long lda, int r, c
 // of latency each):
 //   lora.a: the rows of A ride along behind the rows of W and leave h = scale A x in lora.h_out, for whoever reads y to add
 //   B h (q|k|v: the attention launch; gate|up: decode_swiglu_kernel);
-//   lora.b (bf16 [N, r]) adds  sum_j B[n, j] h[(n / rows_per_group) r + j], where h = scale * the sum of n_parts vectors
-//   that the launch before has left, each from its own piece of x (attention: one per head; decode_swiglu_kernel: one per
-//   workgroup).
+//   lora.b (bf16 [N, r]) adds B h, where h = scale * the sum of n_parts vectors that the launch before has left, each from its
+//   own piece of x (attention: one per head; decode_swiglu_kernel: one per workgroup).
 // (One launch that computes A x in its first workgroups and hands it to the others through tagged words was no faster than
 // two: every wave waited for it at the end with its registers full.)
-// Where x comes from (pre.mode): 0 a bf16 vector; 1 RMSNorm of an fp32 row, x = bf16(h rho gain); 2 SwiGLU of a
-// gate|up row, x = bf16(silu(g) u).  Modes 1 and 2 do the work of the separate kernels in every workgroup (the
-// vector is a few KB out of L2), and workgroup 0 stores x to pre.x_out for the launches that follow.
+// Where x comes from (MODE = pre.mode): 0 a bf16 vector; 1 RMSNorm of an fp32 row, x = bf16(h rho gain), formed in every
+// workgroup (the vector is a few KB out of L2); workgroup 0 stores it to pre.x_out if that is set.
 constexpr int GEMV_AHEAD = 8;
-// LDS: x, and for the sum of the parts of h 2 KB behind it; a vector so long that it leaves no room for those (K above 80896)
-// has them in its place once the product is done.
+// LDS (160 KB): x, and for the sum of the parts of h 2 KB behind it; a vector so long that it leaves no room for those (K above
+// 80896) has them in its place once the product is done.
 constexpr size_t LDS_PER_CU = 160 * 1024;
+constexpr int GEMV_MAX_K = (int)(LDS_PER_CU - 16 * sizeof(float)) / 2;     // x beside the block sums
 __host__ __device__ constexpr size_t gemv_x_bytes(int K) { return ((size_t)K * 2 + 15) & ~(size_t)15; }
 __host__ __device__ constexpr bool gemv_parts_fit(int K) { return gemv_x_bytes(K) + 512 * sizeof(float) <= LDS_PER_CU; }
 
@@ -188,15 +187,6 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
             const float rho = rsqrtf(ss / (float)K + pre.eps);
             for (int i = threadIdx.x * 4; i < K; i += 1024) emit(i, *(const float4*)(pre.h + i), *(const float4*)(pre.gain + i), rho);
         }
-    } else if constexpr (MODE == 2) {
-        for (int i = threadIdx.x * 8; i < K; i += 2048) {
-            float g[8], u[8], o[8];
-            unpack8(*(const uint4*)(pre.gu + i), g);
-            unpack8(*(const uint4*)(pre.gu + K + i), u);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = g[e] / (1.f + __expf(-g[e])) * u[e];
-            *(uint4*)(sx + i) = pack8(o);
-        }
     } else {
         for (int i = threadIdx.x * 8; i < K; i += 2048) *(uint4*)(sx + i) = *(const uint4*)(x + i);
     }
@@ -241,10 +231,9 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             const int n = min(n0 + i, rows - 1);
-            const float* h = hg ? hs : lora.h + (long)(n / lora.rows_per_group) * lora.r;
             const bf16_t* b = lora.b + (long)n * lora.r;
-            if (lane < lora.r) acc[i] += bf16_to_f32(bv[i]) * h[lane];
-            for (int j = lane + 64; j < lora.r; j += 64) acc[i] += bf16_to_f32(b[j]) * h[j];
+            if (lane < lora.r) acc[i] += bf16_to_f32(bv[i]) * hs[lane];
+            for (int j = lane + 64; j < lora.r; j += 64) acc[i] += bf16_to_f32(b[j]) * hs[j];
         }
     }
 #pragma unroll
@@ -258,32 +247,115 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
     }
 }
 
+// The same product for a call that stands alone (a given vector or a SwiGLU; h, if any, is read as it is, one for every
+// rows_per_group rows), and for short, or few long, rows behind a norm: x first, then one row per wave with four loads in flight, or one row per workgroup where there are at most 512 of them, so that
+// a row's loads are all in flight at once instead of queued behind one wave.  Few registers, so that the next launch's
+// workgroups are on the chip while this one's finish: back to back, cold weights, against gemv_kernel: 512 rows of 11008 5.8 and
+// 7.3 us, 64 rows of 28672 8.5 and 12.7; 12288 rows of 256 5.8 and 8.5; 32000 rows of 4096 40.6 and 43.8.  Behind a norm the
+// other kernel is the faster one above 1024 entries (lm_head 51.7 and 41.7 us), up to 4096 of them also for few rows (512: 4.7 and
+// 4.0).
+// pre.mode as for gemv_kernel, and 2: SwiGLU of a gate|up row, x = bf16(silu(g) u).
+__global__ __launch_bounds__(256) void gemv_plain_kernel(const bf16_t* __restrict__ W, long ldw, const bf16_t* __restrict__ x,
+                                                         int N, int K, GemvLora lora, float alpha, const float* __restrict__ resid,
+                                                         bf16_t* __restrict__ y_bf, float* __restrict__ y_f32, GemvPre pre,
+                                                         int row_per_block) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ float red[16];
+    bf16_t* sx = (bf16_t*)smem;
+    if (pre.mode == 1) {
+        float ss = 0.f;
+        for (int i = threadIdx.x * 4; i < K; i += 1024) {
+            const float4 v = *(const float4*)(pre.h + i);
+            ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+        }
+        ss = block_sum(ss, red);
+        const float rho = rsqrtf(ss / (float)K + pre.eps);
+        for (int i = threadIdx.x * 4; i < K; i += 1024) {
+            const float4 v = *(const float4*)(pre.h + i), w = *(const float4*)(pre.gain + i);
+            uint2 o;
+            o.x = pack_bf16x2(v.x * rho * w.x, v.y * rho * w.y);
+            o.y = pack_bf16x2(v.z * rho * w.z, v.w * rho * w.w);
+            *(uint2*)(sx + i) = o;
+        }
+    } else if (pre.mode == 2) {
+        for (int i = threadIdx.x * 8; i < K; i += 2048) {
+            float g[8], u[8], o[8];
+            unpack8(*(const uint4*)(pre.gu + i), g);
+            unpack8(*(const uint4*)(pre.gu + K + i), u);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = g[e] / (1.f + __expf(-g[e])) * u[e];
+            *(uint4*)(sx + i) = pack8(o);
+        }
+    } else {
+        for (int i = threadIdx.x * 8; i < K; i += 2048) *(uint4*)(sx + i) = *(const uint4*)(x + i);
+    }
+    __syncthreads();
+    if (pre.x_out && blockIdx.x == 0)
+        for (int i = threadIdx.x * 8; i < K; i += 2048) *(uint4*)(pre.x_out + i) = *(const uint4*)(sx + i);
+    // the lanes of a row: t of nt
+    const int nt = row_per_block ? 256 : 64, t = threadIdx.x & (nt - 1);
+    const int n = row_per_block ? blockIdx.x : blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (n >= N) return;                                  // (whole waves of the last workgroup, never of a row per workgroup)
+    const bf16_t* w = W + (long)n * ldw;
+    float acc = 0.f;
+    auto add = [&](const uint4& wv, int k) {
+        float b[8];
+        unpack8(*(const uint4*)(sx + k), b);
+        acc = dot8(wv, b, acc);
+    };
+    if (row_per_block) {
+        for (int k = t * 8; k < K; k += 2048) add(*(const uint4*)(w + k), k);
+    } else {
+        int k = t * 8;
+        for (; k + 3 * 512 < K; k += 4 * 512) {
+            uint4 wv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) wv[u] = load_w16(w + k + u * 512);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) add(wv[u], k + u * 512);
+        }
+        for (; k < K; k += 512) add(load_w16(w + k), k);
+    }
+    if (lora.b) {
+        const float* h = lora.h + (long)(n / lora.rows_per_group) * lora.r;
+        const bf16_t* b = lora.b + (long)n * lora.r;
+        for (int j = t; j < lora.r; j += nt) acc += bf16_to_f32(b[j]) * h[j];
+    }
+    acc = row_per_block ? block_sum(acc, red) : wave_sum(acc);
+    if (t == 0) {
+        const float v = alpha * acc;
+        if (y_f32) y_f32[n] = v + (resid ? resid[n] : 0.f);
+        else y_bf[n] = f32_to_bf16(v);
+    }
+}
+
 hipError_t launch_gemv(const bf16_t* W, long ldw, const bf16_t* x, int N, int K, const GemvLora& lora, float alpha,
                        const float* resid, bf16_t* y_bf, float* y_f32, hipStream_t s, const GemvPre* pre) {
     if (N <= 0) return hipSuccess;
-    if ((K & 7) || (ldw & 7) || K <= 0 || (!y_bf && !y_f32)) return hipErrorInvalidValue;
+    if ((K & 7) || (ldw & 7) || K <= 0 || K > GEMV_MAX_K || (!y_bf && !y_f32)) return hipErrorInvalidValue;
     GemvPre p = pre ? *pre : GemvPre{};
-    if (gemv_x_bytes(K) + (p.mode == 1 ? 16 * sizeof(float) : 0) > LDS_PER_CU) return hipErrorInvalidValue;   // (a norm has block sums beside x)
     if (p.mode < 0 || p.mode > 2 || (p.mode == 0 && !x) || (p.mode == 1 && (!p.h || !p.gain)) || (p.mode == 2 && !p.gu))
         return hipErrorInvalidValue;
     GemvLora lo = lora;
     if (lo.rows_per_group <= 0) lo.rows_per_group = N;
     if (lo.n_a > 0 ? (!lo.a || !lo.h_out || lo.b) : (lo.b && (!lo.h || lo.r < 1))) return hipErrorInvalidValue;
     if (lo.n_parts > 0 && (!lo.b || lo.r > 256 || lo.rows_per_group < N)) return hipErrorInvalidValue;   // summed for one group
+    const bool alone = lo.n_a == 0 && lo.n_parts == 0 && (lo.b || p.mode != 1 || K <= 1024 || (N <= 512 && K > 4096));
     const size_t lds = gemv_x_bytes(K) + (lo.n_parts > 0 && gemv_parts_fit(K) ? 512 * sizeof(float) : 0);
+    auto run = [&](auto kern, int grid, auto... more) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        kern<<<grid, 256, lds, s>>>(W, ldw, x, N, K, lo, alpha, resid, y_bf, y_f32, p, more...);
+        return hipGetLastError();
+    };
+    if (alone) return run(gemv_plain_kernel, N <= 512 ? N : cdiv(N, 4), (int)(N <= 512));
+    if (p.mode == 2) return hipErrorInvalidValue;
     // Two rows per wave halve the number of times the input vector is formed; worth it while that leaves every CU a few
     // workgroups.
     const bool two = N >= 8192;
     const int grid = cdiv((long)N + lo.n_a, two ? 8 : 4);
-    auto run = [&](auto kern) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        kern<<<grid, 256, lds, s>>>(W, ldw, x, N, K, lo, alpha, resid, y_bf, y_f32, p);
-        return hipGetLastError();
-    };
-    if (p.mode == 0) return two ? run(gemv_kernel<2, 0>) : run(gemv_kernel<1, 0>);
-    if (p.mode == 1) return two ? run(gemv_kernel<2, 1>) : run(gemv_kernel<1, 1>);
-    return two ? run(gemv_kernel<2, 2>) : run(gemv_kernel<1, 2>);
+    if (p.mode == 0) return two ? run(gemv_kernel<2, 0>, grid) : run(gemv_kernel<1, 0>, grid);
+    return two ? run(gemv_kernel<2, 1>, grid) : run(gemv_kernel<1, 1>, grid);
 }
 
 // ---------------------------------------------------------------- SwiGLU of one token

@@ -150,7 +150,7 @@ hipError_t launch_transpose_table(const bf16_t* src_base, bf16_t* dst_base, cons
 hipError_t launch_copy2d_bf16(const bf16_t* src, long lds, int rows, int cols, bf16_t* dst, long ldd, hipStream_t s);
 
 // ---------------------------------------------------------------- one-token decoding (decode.hip)
-// Where a matrix-vector product takes its input vector from (see gemv_kernel)
+// Where a matrix-vector product takes its input vector from (see gemv_kernel; mode 2 and x_out serve single calls)
 struct GemvPre {
     int mode = 0;                 // 0: x as given; 1: RMSNorm of h with gain; 2: SwiGLU of the gate|up row gu
     const float* h = nullptr;

@@ -7,8 +7,9 @@ import pytest
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
+from oracle import templora_oracle as O  # noqa: E402
 from paper_2401_11504_amd import synth  # noqa: E402
-from test_gpu_kernels import H, api, check  # noqa: E402,F401
+from test_gpu_kernels import BF16_TOL, H, api, check, rnd  # noqa: E402,F401
 
 
 @pytest.mark.parametrize("heads,d_head,d_ffn,rank,n", [
@@ -32,8 +33,8 @@ def test_decoded_token_is_the_chunk_path_s(api, H, heads, d_head, d_ffn, rank, n
 
 
 # The down projection's input vector is kept in LDS (160 KB): up to 80896 entries the sums of the low-rank shares fit behind
-# it, beyond that they take its place after the product, and 81920 is the widest vector.
-@pytest.mark.parametrize("d_ffn,rank", [(80896, 8), (80904, 256), (80904, 8), (81888, 40), (81920, 16)])
+# it, beyond that they take its place after the product, and 81888 is the widest vector (a norm's block sums stand beside it).
+@pytest.mark.parametrize("d_ffn,rank", [(80896, 8), (80904, 256), (80904, 8), (81888, 40)])
 def test_widest_feed_forward(api, H, d_ffn, rank):  # noqa: F811
     shape = synth.Shape(1, 128, 2, 64, d_ffn, 504, rank, float(rank))
     model = H.Model(shape, 78, max_tokens=12)
@@ -48,9 +49,21 @@ def test_widest_feed_forward(api, H, d_ffn, rank):  # noqa: F811
 
 
 def test_wider_input_vectors_are_refused(api, H):  # noqa: F811
-    W, x, y = (torch.zeros(n, dtype=torch.bfloat16, device="cuda") for n in (81928, 81928, 8))
+    W, x, y = (torch.zeros(n, dtype=torch.bfloat16, device="cuda") for n in (81896, 81896, 8))
     with pytest.raises(api.TlError):
         api.tl_k_gemv(W.view(1, -1), x, y[:1])
-    h = torch.zeros(81896, device="cuda")               # a norm also needs its block sums there
+    h = torch.zeros(81896, device="cuda")
     with pytest.raises(api.TlError):
-        api.tl_k_gemv_pre(W[:81896].view(1, -1), h[:1], 1, h=h, gain=h, eps=1e-5)
+        api.tl_k_gemv_pre(W.view(1, -1), h[:1], 1, h=h, gain=h, eps=1e-5)
+
+
+# on both sides of where a product behind a norm changes kernels: 1024 columns; 512 rows of more than 4096
+@pytest.mark.parametrize("N,K", [(520, 1024), (520, 1032), (512, 1032), (512, 4096), (512, 4104), (516, 4104), (3, 8)])
+def test_product_behind_a_norm(api, H, N, K):  # noqa: F811
+    W, h, gain = rnd(1, (N, K), 0.05), rnd(2, (1, K), 2.0, False), 1.0 + rnd(3, (1, K), 0.1, False)[0]
+    y, xo = torch.empty(N, device="cuda"), torch.empty(K, dtype=torch.bfloat16, device="cuda")
+    api.tl_k_gemv_pre(H.to_dev_bf16(W), y, 1, h=H.to_dev_f32(h[0]), gain=H.to_dev_f32(gain), eps=1e-5, x_out=xo)
+    x = H.bf16_to_np(xo).astype(np.float64)
+    check(x, O.rmsnorm_fwd(h, gain, 1e-5)[0], BF16_TOL, "x")
+    # K products summed in fp32: sqrt(4104) 2^-24 = 3.8e-6 of the sum's 2-norm, doubled for the reduction across lanes
+    check(y.cpu().numpy(), W.astype(np.float64) @ x, 1e-5, "y")
