@@ -67,3 +67,16 @@ def test_product_behind_a_norm(api, H, N, K):  # noqa: F811
     check(x, O.rmsnorm_fwd(h, gain, 1e-5)[0], BF16_TOL, "x")
     # K products summed in fp32: sqrt(4104) 2^-24 = 3.8e-6 of the sum's 2-norm, doubled for the reduction across lanes
     check(y.cpu().numpy(), W.astype(np.float64) @ x, 1e-5, "y")
+
+
+# values are read sixteen bytes at a time from 16384 on, if they start on such a boundary
+@pytest.mark.parametrize("n", [1, 1025, 16383, 16384, 16387, 32769])
+@pytest.mark.parametrize("off", [0, 1])
+def test_argmax_takes_the_first_of_equal_values(api, n, off):  # noqa: F811
+    x = rnd(n, (1, n + 1), 1.0, False)[0]
+    at = sorted({n - 1, n // 2, (n - 1) // 3})
+    out = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    for first in range(len(at)):
+        x[off:][at[first:]] = 9.0 + first
+        api.tl_k_argmax(torch.from_numpy(x).cuda()[off:off + n], out)
+        assert int(out[0]) == at[first], (n, off, at)
