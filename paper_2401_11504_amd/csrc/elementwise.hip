@@ -369,7 +369,8 @@ hipError_t launch_labels(const int* tokens, int T, int* labels, hipStream_t s) {
 // NV > 0: the row (V <= 512 NV) is fetched once, every load issued before the first is used, and stays in registers for both
 // passes; the sums are taken in the order of the other form (NV = 0, what is left for longer rows), so the bits are the same.
 // 4096 rows of 32000: 333 -> 211 us (0.8 GB); taking the maximum first, in 16-byte pieces, would be 142 us but rounds
-// differently.
+// differently.  The launcher takes the smallest NV that holds the row: loads past its end are not free (1024 rows of 8200: 15.8 us
+// with NV 24, 32.0 with 64, 20.8 in two passes; of 1000: 7.7, 9.1 with 16, 8.3), nor are registers that nothing needs.
 template <int NV>
 __global__ __launch_bounds__(512) void cross_entropy_kernel(const float* __restrict__ logits,
                                                             const int* __restrict__ labels, int T, int V,
@@ -446,7 +447,17 @@ hipError_t launch_cross_entropy(const float* logits, const int* labels, int T, i
         hipError_t e = launch_fill_f32(nll, (size_t)row0, 0.f, s);
         if (e != hipSuccess) return e;
     }
-    const auto kern = V <= 512 * 16 ? cross_entropy_kernel<16> : V <= 512 * 64 ? cross_entropy_kernel<64> : cross_entropy_kernel<0>;
+    auto kern = V <= 512 * 2    ? cross_entropy_kernel<2>
+                : V <= 512 * 8  ? cross_entropy_kernel<8>
+                : V <= 512 * 16 ? cross_entropy_kernel<16>
+                : V <= 512 * 24 ? cross_entropy_kernel<24>
+                : V <= 512 * 32 ? cross_entropy_kernel<32>
+                : V <= 512 * 48 && T - row0 > 256 ? cross_entropy_kernel<48>     // (a row per CU: 12.2 us, 11.1 with 64)
+                : V <= 512 * 64 ? cross_entropy_kernel<64>
+                                : cross_entropy_kernel<0>;
+    // The largest of them leaves room for two rows per CU, the two-pass form for four: without a gradient, where each reads the
+    // row once, a round of that is faster than two (1024 rows of 32000: 30.8 and 36.6 us; 333: 27.2 and 18.2; 4096: 165 and 131).
+    if (!dlogits && V > 512 * 48 && T - row0 > 512 && T - row0 <= 1024) kern = cross_entropy_kernel<0>;
     kern<<<T - row0, 512, 0, s>>>(logits, labels, T, V, first_target, 1.f / (float)n_targets, nll, dlogits, row0);
     if (loss_sum) nll_sum_kernel<<<1, 256, 0, s>>>(nll, T, loss_sum, flag);
     return hipGetLastError();
