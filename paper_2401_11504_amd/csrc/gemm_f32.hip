@@ -43,8 +43,10 @@ struct F32Tile {
 
 // One operand's share of a contraction tile, global memory -> registers -> LDS.  The loads go through a buffer resource that
 // starts at the tile and ends with the operand: what lies behind its end reads as zero, so there is no branch around a load
-// and the compiler can count exactly which of them a use has to wait for.
-template <int B, int BKF, bool KC>     // B rows (or columns); KC: the contraction is contiguous
+// and the compiler can count exactly which of them a use has to wait for.  WIDE: rows of more than 2^22 floats, whose offsets
+// within a tile do not fit the resource's 32 bits; plain loads with their own look at the operand's end (64 tokens, 4194312 x 64,
+// rank 8: 0.21 s; one output per thread 2.9 to 3.2).
+template <int B, int BKF, bool KC, bool WIDE>     // B rows (or columns); KC: the contraction is contiguous
 struct F32Stage {
     static constexpr int CPR = (KC ? BKF : B) / 4, STEP = 256 / CPR, N = B * BKF / 1024;
     u32x4_t r[N];
@@ -52,7 +54,26 @@ struct F32Stage {
     // out of the next row: they, like rows past the end, only feed outputs that are never stored.
     __device__ __forceinline__ void load(const float* src, long ld, int r0, int rows, int k0, int kmax, int tid) {
         const long at = KC ? r0 * ld + k0 : k0 * ld + r0, end = KC ? (rows - 1) * ld + kmax : (kmax - 1) * ld + rows;
-        const long left = k0 < kmax ? (end - at) * 4 : 0;
+        if constexpr (WIDE) {
+            const float* first = src + at;
+            const long left = (unsigned)k0 < (unsigned)kmax ? end - at : 0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const long off = (tid / CPR + (long)STEP * i) * ld + (tid % CPR) * 4;
+                f4u v = {0.f, 0.f, 0.f, 0.f};
+                if (off + 4 <= left) {
+                    v = *(const f4u*)(first + off);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (off + e < left) v[e] = first[off + e];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r[i][e] = __float_as_uint(v[e]);
+            }
+            return;
+        }
+        const long left = (unsigned)k0 < (unsigned)kmax ? (end - at) * 4 : 0;
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(src + (left > 0 ? at : 0)), 0,
                                                             (int)(unsigned)(left > 0xffffffffL ? 0xffffffffL : left), 0x00020000);
         const unsigned off = ((unsigned)(tid / CPR) * (unsigned)ld + (tid % CPR) * 4) * 4, step = (unsigned)ld * (STEP * 4);
@@ -62,11 +83,11 @@ struct F32Stage {
     __device__ __forceinline__ void store(float* tile, int k0, int kmax, int tid) {
         const int c = (tid % CPR) * 4, o = tid / CPR;
         constexpr int LD = KC ? BKF + 4 : B + 4;
-        if (KC && k0 + BKF > kmax) {         // elements past the contraction's end belong to the next row: they count as zero
+        if (KC && k0 > kmax - BKF) {         // elements past the contraction's end belong to the next row: they count as zero
 #pragma unroll
             for (int i = 0; i < N; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) r[i][e] = k0 + c + e < kmax ? r[i][e] : 0u;
+                for (int e = 0; e < 4; ++e) r[i][e] = c + e < kmax - k0 ? r[i][e] : 0u;
         }
 #pragma unroll
         for (int i = 0; i < N; ++i) *(u32x4_t*)(tile + (o + STEP * i) * LD + c) = r[i];
@@ -91,7 +112,7 @@ __device__ __forceinline__ void f32_fragments(const float* tile, int row0, int k
     }
 }
 
-template <int BM, int BN, int BKF, int PF, bool AKC, bool BKC>
+template <int BM, int BN, int BKF, int PF, bool WIDE, bool AKC, bool BKC>
 __device__ __forceinline__ void f32_tile(const F32Product& q, int tile, float* smem) {
     using T = F32Tile<BM, BN, BKF>;
     constexpr int FM = T::FM, FN = T::FN, KS = BKF / 16;
@@ -109,21 +130,22 @@ __device__ __forceinline__ void f32_tile(const F32Product& q, int tile, float* s
         // Tile t goes from memory to the staging registers of slot t % PF, from there to place t % 3 of the LDS ring, and its
         // fragments to set t % 2: while tile t is multiplied the fragments of t + 1 are read, t + 2 is put into LDS and t + 3
         // .. t + 2 + PF are in flight.  One barrier per tile: it makes t + 2 visible and frees the place of t + 1.
-        F32Stage<BM, BKF, AKC> ra[PF];
-        F32Stage<BN, BKF, BKC> rb[PF];
+        F32Stage<BM, BKF, AKC, WIDE> ra[PF];
+        F32Stage<BN, BKF, BKC, WIDE> rb[PF];
         // (128-wide tiles have sixteen independent chains to hide the LDS behind, and no registers for a second set: they read
         // a tile's fragments when they multiply it)
         constexpr bool AHEAD = BM < 128;
         float a[AHEAD ? 2 : 1][KS][FM][4], b[AHEAD ? 2 : 1][KS][FN][4];
         f32x4_t acc[FM][FN];
-        // (tiles behind the last one read as zeros and are never multiplied)
+        // (tiles behind the last one read as zeros and are never multiplied; their first element may lie beyond 2^31)
+        auto tile_k = [](int t) { return (int)((unsigned)t * BKF); };
         auto load = [&](auto slot, int t) {
-            ra[slot.value].load(A, lda, m0, M, t * BKF, K, tid);
-            rb[slot.value].load(B, ldb, n0, N, t * BKF, K, tid);
+            ra[slot.value].load(A, lda, m0, M, tile_k(t), K, tid);
+            rb[slot.value].load(B, ldb, n0, N, tile_k(t), K, tid);
         };
         auto park = [&](auto slot, int place, int t) {
-            ra[slot.value].store(sA + place * T::SA, t * BKF, K, tid);
-            rb[slot.value].store(sB + place * T::SB, t * BKF, K, tid);
+            ra[slot.value].store(sA + place * T::SA, tile_k(t), K, tid);
+            rb[slot.value].store(sB + place * T::SB, tile_k(t), K, tid);
         };
         auto fetch = [&](auto set, int place) {
 #pragma unroll
@@ -225,7 +247,7 @@ __device__ __forceinline__ void f32_tile(const F32Product& q, int tile, float* s
     }
 }
 
-template <int BM, int BN, int BKF, int PF>
+template <int BM, int BN, int BKF, int PF, bool WIDE>
 __global__ __launch_bounds__(256, 2) void f32_group_kernel(F32Batch grp) {
     extern __shared__ __align__(16) float smem_f32[];
     const int b = blockIdx.x;
@@ -236,9 +258,9 @@ __global__ __launch_bounds__(256, 2) void f32_group_kernel(F32Batch grp) {
     // that the CUs of one XCD share operand rows in its L2.
     const int n = q.tiles_m * q.tiles_n, id = b - q.tile0;
     const int c = id & 7, per = n >> 3, tile = c * per + min(c, n & 7) + (id >> 3);
-    if (q.kind == F32_KK) f32_tile<BM, BN, BKF, PF, true, true>(q, tile, smem_f32);
-    else if (q.kind == F32_KN) f32_tile<BM, BN, BKF, PF, true, false>(q, tile, smem_f32);
-    else f32_tile<F32_MN_TILE(BM), F32_MN_TILE(BN), BKF, PF, false, false>(q, tile, smem_f32);
+    if (q.kind == F32_KK) f32_tile<BM, BN, BKF, PF, WIDE, true, true>(q, tile, smem_f32);
+    else if (q.kind == F32_KN) f32_tile<BM, BN, BKF, PF, WIDE, true, false>(q, tile, smem_f32);
+    else f32_tile<F32_MN_TILE(BM), F32_MN_TILE(BN), BKF, PF, WIDE, false, false>(q, tile, smem_f32);
 }
 
 __global__ __launch_bounds__(256) void adamw_first_kernel(const float* __restrict__ g, const float* p, float* p_new, size_t n,
@@ -252,7 +274,7 @@ hipError_t launch_adamw_first(const float* g, const float* p, float* p_new, size
     return hipGetLastError();
 }
 
-template <int BM, int BN, int BKF, int PF>
+template <int BM, int BN, int BKF, int PF, bool WIDE = false>
 static hipError_t run_f32(F32Batch& grp, hipStream_t s) {
     long tiles = 0;
     for (int k = 0; k < grp.n; ++k) {
@@ -264,28 +286,11 @@ static hipError_t run_f32(F32Batch& grp, hipStream_t s) {
         if (tiles > 0x7fffffffL) return hipErrorInvalidValue;
     }
     const int lds = F32Tile<BM, BN, BKF>::LDS_FLOATS * (int)sizeof(float);
-    auto kern = f32_group_kernel<BM, BN, BKF, PF>;
+    auto kern = f32_group_kernel<BM, BN, BKF, PF, WIDE>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     kern<<<(unsigned)tiles, 256, lds, s>>>(grp);
     return hipGetLastError();
-}
-
-// rows of more than 2^22 floats, whose offsets within a tile do not fit 32 bits: the same chains, one output per thread
-__global__ __launch_bounds__(256) void f32_wide_kernel(F32Product q) {
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < (long)q.M * q.N; i += (long)gridDim.x * 256) {
-        const long m = i / q.N, n = i % q.N;
-        auto chain = [&](const float* A, long lda, const float* B, long ldb, int K) {
-            float s = 0.f;
-            for (long k = 0; k < K; ++k)
-                s = fmaf(q.kind == F32_MN ? A[k * lda + m] : A[m * lda + k], q.kind == F32_KK ? B[n * ldb + k] : B[k * ldb + n], s);
-            return s;
-        };
-        float v = q.alpha * chain(q.A, q.lda, q.B, q.ldb, q.K);
-        if (q.K2 > 0) v += q.alpha2 * chain(q.A2, q.lda2, q.B2, q.ldb2, q.K2);
-        q.C[m * q.ldc + n] = v;
-        if (q.p_new) q.p_new[m * q.ldc + n] = adamw_first(q.p_old[m * q.ldc + n], v, q.opt);
-    }
 }
 
 hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s) {
@@ -307,13 +312,8 @@ hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s) 
         t128 += (long)cdiv(q.M, 128) * cdiv(q.N, 128);
         t64 += (long)cdiv(q.M, 64) * cdiv(q.N, 64);
     }
-    if (wide) {
-        for (int k = 0; k < n; ++k) {
-            const long blocks = ((long)grp.p[k].M * grp.p[k].N + 255) / 256;
-            f32_wide_kernel<<<(unsigned)(blocks < 65536 ? blocks : 65536), 256, 0, s>>>(grp.p[k]);
-        }
-        return hipGetLastError();
-    }
+    // (rows that wide are long chains on few tiles, or next to no arithmetic: no 128-wide instance for them)
+    if (wide) return t64 >= 256 ? run_f32<64, 64, 32, 2, true>(grp, s) : run_f32<32, 32, 64, 2, true>(grp, s);
     // The largest tile that gives every CU one.  Below that smaller tiles, down to one chain of 16 x 16 outputs per wave: the
     // low-rank products of 1024 tokens (K 4096) take 45 us on 128 workgroups, a third of it the chain itself.
     if (t128 >= 256) return run_f32<128, 128, 16, 2>(grp, s);

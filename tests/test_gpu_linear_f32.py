@@ -70,3 +70,23 @@ def test_linear_step(T, din, dout, r):
         gr = g2.cpu().double()
         want = p.double() * (1 - LR * 0.01) - LR * gr / (gr.abs() + 1e-8)
         assert (p1.cpu().double() - want).abs().max() < 8e-9 + LR * 1e-6
+
+
+# Rows of more than 2^22 floats, whose offsets within a tile exceed 32 bits; the in-place update takes one launch per product.
+# A chain of K fp32 products strays by about sqrt(K) 2^-24 of its 2-norm (1.2e-4 here), doubled as above.
+@pytest.mark.parametrize("T,din,dout,r", [(2, (1 << 22) + 3, 3, 2), (3, 5, (1 << 22) + 1, 4), (70, (1 << 22) + 6, 2, 1)])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_wide_rows(T, din, dout, r, in_place):
+    ins, s = make(T, din, dout, r), 1.5
+    dev = [t.cuda() for t in ins]
+    outs = [torch.empty(*size, device="cuda") for size in ((T, dout), (T, din), (r, din), (dout, r))]
+    new = dev[2:4] if in_place else [torch.empty_like(dev[2]), torch.empty_like(dev[3])]
+    step(dev, s, outs, *new)
+    ref = reference(ins, s)
+    for k, o in zip(("Y", "dX", "dA", "dB"), outs):
+        err = (o.cpu().double() - ref[k]).norm() / ref[k].norm()
+        assert err < 2.5e-4, (k, err)
+    for p, gr, p1 in ((ins[2], outs[2], new[0]), (ins[3], outs[3], new[1])):
+        gr = gr.cpu().double()
+        want = p.double() * (1 - LR * 0.01) - LR * gr / (gr.abs() + 1e-8)
+        assert (p1.cpu().double() - want).abs().max() < 8e-9 + LR * 1e-6
