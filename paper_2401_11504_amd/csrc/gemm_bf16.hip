@@ -204,9 +204,8 @@ __device__ __forceinline__ unsigned div_by(unsigned n, unsigned inv) { return in
 // Four waves, each with a (BM / 2) x (BN / 2) share of the tile, one wave per SIMD for the large tiles.
 //
 // The order of the contraction: first the "edge" tiles -- the low-rank pair A2 B2^T, and the last K % 64 elements of
-// A B^T -- then the whole 64-wide tiles of A B^T.  Edge tiles may be narrower than 64 and, where the column groups of a
-// product share a tile (GemmNT::grp_cols), need part of their B rows left out: lanes with nothing to fetch store zeros to
-// LDS instead.  With the usual ranks they are all fetched by the prologue, and the loop proper fetches only whole tiles
+// A B^T -- then the whole 64-wide tiles of A B^T.  Edge tiles may be narrower than 64: lanes with nothing to fetch store zeros
+// to LDS instead.  With the usual ranks they are all fetched by the prologue, and the loop proper fetches only whole tiles
 // through pointers that advance by a constant.
 //
 // The A operand has AST tiles of LDS, the B operand (the weights, which come from HBM) one more: a tile of B is fetched
@@ -258,14 +257,8 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
     const bf16_t* B = p.B + (long)z * p.bB;
     const bf16_t* A2 = p.A2 ? p.A2 + (long)z * p.bA2 : nullptr;
     const bf16_t* B2 = p.B2 ? p.B2 + (long)z * p.bB2 : nullptr;
-    // edge tiles: the low-rank pair (once per column group that this tile touches), then the ragged end of the main pair
-    const int per_grp = (p.K2 + BK - 1) / BK;
-    int grp0 = 0, n_grp = 1;
-    if (p.grp_cols > 0) {
-        grp0 = (p.col0 + n0) / p.grp_cols;
-        n_grp = (p.col0 + min(n0 + BN, p.N) - 1) / p.grp_cols - grp0 + 1;
-    }
-    const int n_low = per_grp * n_grp, nk1 = p.K / BK;
+    // edge tiles: the low-rank pair, then the ragged end of the main pair
+    const int n_low = (p.K2 + BK - 1) / BK, nk1 = p.K / BK;
     const int n_edge_all = n_low + ((p.K & (BK - 1)) ? 1 : 0), nk_all = n_edge_all + nk1;
     // with SPLITK, n_split workgroups share one output tile: this one takes tiles [kt0, kt0 + nk) of that order
     const int kt0 = SPLITK ? (int)div_by((unsigned)(nk_all * split), map.inv_n_split) : 0;
@@ -289,14 +282,13 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
     auto fetch_edge = [&](int t, auto side, unsigned slot) {
         constexpr bool b_side = decltype(side)::value;
         const int e = kt0 + t;
-        int valid, lo = 0, hi = p.N;          // valid chunks; columns that take part
+        int valid;          // chunks
         const bf16_t* src;
         long ld;
         if (e < n_low) {
-            const int gi = e / per_grp, k0 = (e - gi * per_grp) * BK;
+            const int k0 = e * BK;
             valid = min(BK, p.K2 - k0) >> 3;
-            if (p.grp_cols > 0) { lo = (grp0 + gi) * p.grp_cols - p.col0; hi = lo + p.grp_cols; }
-            src = b_side ? B2 + k0 : A2 + (long)(grp0 + gi) * p.bA2_grp + k0;
+            src = (b_side ? B2 : A2) + k0;
             ld = b_side ? p.ldb2 : p.lda2;
         } else {
             valid = (p.K & (BK - 1)) >> 3;
@@ -308,7 +300,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
         for (int j = 0; j < (b_side ? LB : LA); ++j) {
             const int row = min(r0 + 32 * j, last);
             const unsigned dst = slot + wave * 1024 + j * NT * 16;      // LDS offset of this wave's 64 chunks
-            if (chunk < valid && (!b_side || (row >= lo && row < hi)))
+            if (chunk < valid)
                 load_lds16(((unsigned)row * (unsigned)ld + chunk * 8) * 2, src, __builtin_amdgcn_readfirstlane(lds0 + dst));
             else
                 *(uint4*)(smem + dst + lane * 16) = make_uint4(0, 0, 0, 0);

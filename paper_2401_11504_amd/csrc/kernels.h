@@ -11,11 +11,6 @@ struct GemmNT {
     const bf16_t* A2 = nullptr; long lda2 = 0;  // [M, K2]  (low-rank K-extension; may be null)
     const bf16_t* B2 = nullptr; long ldb2 = 0;  // [N, K2]
     int K2 = 0;
-    // grp_cols > 0: the output columns fall into groups of grp_cols (the projections that share an input), and group i has a
-    // low-rank input of its own, A2 + i * bA2_grp.  B2 has one row per column, whatever its group.  col0: number of this
-    // product's first column within the groups (a launch over a column range).
-    int grp_cols = 0, col0 = 0;
-    long bA2_grp = 0;
     float alpha = 1.f;
     const float* R = nullptr;                   // fp32 [M, N] residual (c_f32 only), row stride ldc
     void* C = nullptr;          long ldc = 0;   // bf16 or fp32 [M, N]
