@@ -348,9 +348,8 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
         else if (r == 2 || AST == 3) wait_vmcnt<(AST > 2 ? 2 : 1) * (LA + LB)>();
         else wait_vmcnt<(AST - 1) * (LA + LB)>();
     };
-    // tile 0 has landed; a wave may have skipped fetches of a narrow edge tile in the prologue, which can then not be counted
-    const bool narrow = ((p.K | p.K2) & (BK - 1)) != 0;
-    wait_tiles(n_edge == 0 || !narrow ? min(nk, AST) - 1 : 0);
+    // tile 0 has landed; an edge tile in the prologue may have skipped lanes, so its fetches cannot be counted
+    wait_tiles(n_edge == 0 ? min(nk, AST) - 1 : 0);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
