@@ -376,7 +376,8 @@ tl_status tl_k_swiglu_fwd(const uint16_t* gu, int32_t T, int32_t f, uint16_t* a,
  *   rows 0 .. n_keys-1 with row stride ld (elements), every key visible.  workspace: NULL, or device fp32 scratch of
  *   workspace_elems floats: with it the keys are cut into up to 32 ranges of >= 128 keys, one workgroup per (head,
  *   range) and a second launch that merges them (n_heads * ranges * (d_head + 2) floats are used); without it one
- *   workgroup per head reads the whole cache.
+ *   workgroup per head reads the whole cache.  TL_ERR_DEVICE if a workgroup would get more than 30208 keys, or 13312 as
+ *   one of several ranges.
  * tl_k_argmax: index of the largest of n fp32 values, lowest index among equals; out is a device int32. */
 tl_status tl_k_gemv(const uint16_t* W, int32_t ldw, const uint16_t* x, int32_t N, int32_t K, const uint16_t* lora_b,
                     const float* lora_h, int32_t r, int32_t rows_per_group, float alpha, const float* resid, void* y,

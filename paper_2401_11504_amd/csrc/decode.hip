@@ -668,6 +668,7 @@ static hipError_t run_attention_decode(const bf16_t* q, bf16_t* k, bf16_t* v, lo
     const float scale = 1.f / sqrtf((float)DH);
     if (n_split >= 2) {
         const int chunk = cdiv(n_keys, n_split);
+        if (chunk > ATTN_DECODE_MAX_RANGE) return hipErrorInvalidValue;
         n_split = cdiv(n_keys, chunk);            // no empty range
         attn_decode_split_kernel<DH><<<dim3(n_heads, n_split), 256, 0, s>>>(q, k, v, ld, n_keys, scale, chunk, ws, fresh);
         hipError_t e = hipGetLastError();

@@ -175,7 +175,10 @@ hipError_t launch_decode_swiglu(const float* raw, const bf16_t* b, const float* 
                                 const bf16_t* a_down, float* part, hipStream_t s);
 // one query row against cache rows 0 .. n_keys-1 (row stride ld), per head
 constexpr int ATTN_DECODE_MAX_SPLIT = 32;   // key ranges per head in the split decode-attention path
-constexpr int ATTN_DECODE_MAX_UNSPLIT = 30208;   // keys that one workgroup per head takes on
+// Keys that one workgroup takes on, a head's whole cache or one range of it.  The kernels would take any number; these are the
+// limits the entry points have always had, so that a call with too little scratch is told so instead of leaving a long cache
+// to a few workgroups.
+constexpr int ATTN_DECODE_MAX_UNSPLIT = 30208, ATTN_DECODE_MAX_RANGE = 13312;
 struct DecodeFresh {                      // the newest token, if its q, k, v are still to be formed: raw + B h
     const float* raw = nullptr;           // [3 d]
     const bf16_t* b = nullptr;            // [3 d, r]

@@ -80,3 +80,23 @@ def test_argmax_takes_the_first_of_equal_values(api, n, off):  # noqa: F811
         x[off:][at[first:]] = 9.0 + first
         api.tl_k_argmax(torch.from_numpy(x).cuda()[off:off + n], out)
         assert int(out[0]) == at[first], (n, off, at)
+
+
+# What the attention entry refuses: more than 30208 keys without scratch, and ranges of more than 13312 keys where the scratch
+# holds too few of them.
+@pytest.mark.parametrize("n_keys,ranges,ok", [(30208, 0, True), (30209, 0, False), (26624, 2, True), (26625, 2, False),
+                                              (26625, 3, True), (40001, 3, False)])
+def test_key_counts_that_attention_takes(api, n_keys, ranges, ok):  # noqa: F811
+    dh = 64
+    kv = torch.randn(n_keys, 2 * dh, device="cuda").bfloat16()
+    q, o = torch.randn(dh, device="cuda").bfloat16(), torch.zeros(dh, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(ranges * (dh + 2), device="cuda") if ranges else None
+    call = lambda: api.tl_k_attention_decode(q, kv[:, :dh], kv[:, dh:], 1, dh, o, workspace=ws)  # noqa: E731
+    if not ok:
+        with pytest.raises(api.TlError):
+            call()
+        return
+    call()
+    k, v = kv[:, :dh].double(), kv[:, dh:].double()
+    want = torch.softmax(k @ q.double() / dh ** 0.5, 0) @ v
+    check(o.double().cpu().numpy(), want.cpu().numpy(), BF16_TOL, "o")
