@@ -100,3 +100,32 @@ def test_key_counts_that_attention_takes(api, n_keys, ranges, ok):  # noqa: F811
     k, v = kv[:, :dh].double(), kv[:, dh:].double()
     want = torch.softmax(k @ q.double() / dh ** 0.5, 0) @ v
     check(o.double().cpu().numpy(), want.cpu().numpy(), BF16_TOL, "o")
+
+
+# Values that are not finite: behind the last key they are not seen (the rest of a cache holds anything), in a key they make the
+# whole head undefined, in a value the columns they stand in.
+@pytest.mark.parametrize("n_keys,ranges", [(1, 0), (5, 0), (129, 0), (400, 0), (400, 32), (4100, 32)])
+@pytest.mark.parametrize("dh", [64, 128])
+def test_attention_and_non_finite_values(api, n_keys, ranges, dh):  # noqa: F811
+    gen = torch.Generator(device="cuda").manual_seed(n_keys)
+    kv = torch.full((n_keys + 300, 4 * dh), float("nan"), device="cuda").bfloat16()     # two heads: k k v v
+    kv[:n_keys] = torch.randn(n_keys, 4 * dh, generator=gen, device="cuda").bfloat16()
+    q, o = torch.randn(2 * dh, generator=gen, device="cuda").bfloat16(), torch.zeros(2 * dh, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(2 * ranges * (dh + 2), device="cuda") if ranges else None
+
+    def run():
+        api.tl_k_attention_decode(q, kv[:n_keys, :2 * dh], kv[:n_keys, 2 * dh:], 2, dh, o, workspace=ws)
+        return o.double().cpu().view(2, dh)
+
+    k, v = kv[:n_keys, :2 * dh].double().cpu().view(-1, 2, dh), kv[:n_keys, 2 * dh:].double().cpu().view(-1, 2, dh)
+    want = torch.stack([torch.softmax(k[:, h] @ q.double().cpu().view(2, dh)[h] / dh ** 0.5, 0) @ v[:, h] for h in range(2)])
+    check(run().numpy(), want.numpy(), BF16_TOL, "o")
+    at = (n_keys - 1) // 2
+    keep = kv[at].clone()
+    kv[at, 2 * dh + 3] = float("inf")             # a value of head 0
+    got = run()
+    assert not torch.isfinite(got[0, 3]) and torch.isfinite(got).sum() == 2 * dh - 1
+    kv[at] = keep
+    kv[at, dh + 3] = float("nan")                 # a key of head 1
+    got = run()
+    assert torch.isfinite(got[0]).all() and torch.isnan(got[1]).all()

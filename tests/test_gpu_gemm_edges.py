@@ -45,3 +45,19 @@ def test_edge_tiles(api, H, M, N, K, K2, ws, plan):  # noqa: F811
     torch.cuda.synchronize()
     check(Cf.cpu().numpy() - R, ref, F32_TOL + 2.0 ** -24 * np.abs(R).max() / ref.std(), "C f32 + R")
     check(H.bf16_to_np(Cb), 0.5 * ref, BF16_TOL, "C bf16")
+
+
+@pytest.mark.parametrize("M,N,K,K2,ws,plan", [CASES[i] for i in (0, 2, 3, 5, 8)])
+def test_undefined_values_beside_the_operands(api, M, N, K, K2, ws, plan):  # noqa: F811
+    """What lies behind a row's last element may be anything: the product is bit for bit the same."""
+    gen = torch.Generator(device="cuda").manual_seed(M + K)
+    wide = [torch.randn(r, c + 64, generator=gen, device="cuda").bfloat16() for r, c in ((M, K), (N, K), (M, K2), (N, K2))]
+    scratch = torch.empty(1 << 26, dtype=torch.float32, device="cuda") if ws else None
+    out = []
+    for behind in (3.0, float("nan"), float("-inf")):
+        for w, c in zip(wide, (K, K, K2, K2)):
+            w[:, c:] = behind
+        C = torch.empty(M, N, dtype=torch.float32, device="cuda")
+        api.tl_k_gemm_nt(wide[0][:, :K], wide[1][:, :K], C, wide[2][:, :K2], wide[3][:, :K2], workspace=scratch)
+        out.append(C)
+    assert torch.isfinite(out[0]).all() and torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
