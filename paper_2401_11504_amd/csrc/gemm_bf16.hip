@@ -645,7 +645,7 @@ static hipError_t run_nt(const GemmNT& g, int split_k, hipStream_t s) {
 
 // Whether the direct-to-LDS kernel takes this product.  Its offsets within an operand are 32-bit.  A contraction that is no
 // multiple of 64 (ranks below 64, ragged widths) costs it one edge tile, waited for before the loop starts: worth it from
-// 256 elements on (1024 x 1024 x 1024 with rank 16: 12 us against 34 us register-staged), below that the whole contraction
+// 256 elements on (1024 x 1024 x 1024 with rank 16: 8 us against 14 us register-staged, back to back), below that the whole contraction
 // is one or two such waits.
 static bool nt_direct(const GemmNT& g) {
     if (g.K <= 0) return false;
@@ -660,7 +660,8 @@ static bool nt_direct_small(const GemmNT& g) { return nt_direct(g) && ((g.K % BK
 // A many-tile GEMM whose tile count leaves the last round of workgroups poorly filled can be cheaper as two launches:
 // columns [0, N1) (of every batch) as whole rounds of 256x256 tiles, the rest on its own with whatever tile suits it
 // (gate|up at 1024 tokens: 688 tiles of 256x128 are 2.7 rounds and cost three; 256 tiles of 256x256 plus 176 of 256x128
-// cost 12.2 + 7.0 instead of 3 x 7.0 in the units of the tile model below).  Returns N1, or 0 for one launch.
+// cost 12.2 + 7.0 instead of 3 x 7.0 in the units of the tile model below: 148 us, 162 in one launch of 256x128, 165 of
+// 256x256; one of 256x192, which the model takes for slower, measures 140).  Returns N1, or 0 for one launch.
 int gemm_nt_column_split(const GemmNT& g) {
     if (g.deferred || g.split_k > 1 || g.M <= 0 || g.N < 512 || g.batch <= 0) return 0;
     if (!nt_direct(g)) return 0;
@@ -702,18 +703,25 @@ bool gemm_nt_split_columns(const GemmNT& g, GemmNT* a, GemmNT* b) {
 // The tile configurations the launcher can pick (every one is reachable from launch_gemm_nt; the kernel tests name the
 // shape that lands on each).
 enum NtConfig {
-    NT_128x128,         // 128x128 tiles, BK 64, four-stage ring, interleaved loop: a few hundred tiles in all
-    NT_256x128,         // 256x128 tiles, BK 64, three stages
+    // tiles of 64 contraction elements; A / B tiles in LDS
+    NT_128x128,         // 128x128, 4 / 5: a few hundred tiles in all
+    NT_256x128,         // 256x128, 3 / 4
     NT_256x128_SPLIT,   // the same with the contraction split 2..4 ways (partials reduced afterwards or by the consumer)
-    NT_256x192,         // 256x192 tiles, BK 64, two stages: tile counts that 256x256 leaves a third of the CUs idle on
-    NT_256x256,         // 256x256 tiles, BK 32, four stages
-    NT_REG_128x128,     // register-staged fallbacks for contractions that are no multiple of 64 or operands beyond 1 Gi elements
+    NT_256x192,         // 256x192, 2 / 3: tile counts that 256x256 leaves a third of the CUs idle on
+    NT_256x256,         // 256x256, 2 / 3
+    NT_REG_128x128,     // register-staged, for what nt_direct refuses: ragged contractions below 256 elements, operands beyond 1 Gi
     NT_REG_128x64,
     NT_SKINNY           // N <= 64 per batch or few tiles: 64x64 tiles, contraction split over up to 16 workgroups
 };
 
-// Measured on MI355X at M = 1024.  Every tile shape is limited by how fast a CU can pull operand bytes out of L2, so
-// the largest tile that still gives every CU work wins.
+// A model of the time: rounds of tiles over the 256 CUs, times the operand bytes of a tile, over a rate per CU.  The rates (53 GB/s
+// below; 42 and 55 for many tiles) were fitted to the loop that the direct-to-LDS kernel had before its present one and are
+// kept as empirical constants: the present loop's time follows its matrix instructions more than its bytes, so they rank the
+// tile shapes and are no bandwidths.  Checked on the present loop over the products of a 7B layer with cold weights, every
+// instance forced on every shape: from 128 tiles of 128x128 on and up to 3072 rows the pick is the fastest or within 3 %,
+// but for q|k|v at 1357 rows (256x192 would take 11 % less) and three others (5 to 6 %).  At 5120 rows the 4096-wide products
+// would take 17 to 20 % less in 256x192 tiles (400 instead of 640 in 2.5 rounds), and below 128 tiles (256 or 334 rows, 4096
+// wide) long contractions 11 to 47 % less split in four.
 static NtConfig choose_nt(const GemmNT& g, int* n_split) {
     *n_split = 1;
     const int nk = cdiv(g.K, BK) + cdiv(g.K2, BK);
@@ -726,11 +734,11 @@ static NtConfig choose_nt(const GemmNT& g, int* n_split) {
         const long t256x128 = (long)cdiv(g.M, 256) * cdiv(g.N, 128) * g.batch;
         if (t256 < 160) {
             // Few 256x256 tiles: pick among 128x128 tiles, 256x128 tiles, and 256x128 tiles with the contraction split
-            // 2..4 ways, by the operand bytes the busiest CU has to pull in (the loop is bound by that rate, about
-            // 53 GB/s per CU, not by the matrix pipe): rounds of tiles x (BM + BN) x K x 2 bytes.  A split adds one
-            // pass over its partials (written and read back at about 5 TB/s, plus a launch).  At M = 1024 this
-            // picks the two-way split from K of about 10k on (measured: K 11008 -7 %, 12288 -13 %, 22016 -17 %,
-            // 32000 -15 % against 128x128) and 128x128 below; at M = 2048 plain 256x128 tiles fill the chip.
+            // 2..4 ways, by the operand bytes of the busiest CU: rounds of tiles x (BM + BN) x K x 2 bytes.  A split
+            // adds one pass over its partials (written and read back at about 5 TB/s, plus a launch).  At M = 1024
+            // this picks the two-way split from K of about 10k on (with the reduce pass, against 128x128: K 11008 85 and
+            // 105 us, 12288 94 and 118, 22016 155 and 203, 32000 228 and 287) and 128x128 below (K 4096 40 us, split 43);
+            // at M = 2048 plain 256x128 tiles fill the chip.
             const double ktot = (double)g.K + g.K2, per_us = 53e3;
             double best = rounds(t128) * 256.0 * ktot * 2.0 / per_us;
             NtConfig cfg = NT_128x128;
@@ -747,11 +755,9 @@ static NtConfig choose_nt(const GemmNT& g, int* n_split) {
             }
             return cfg;
         }
-        // Many tiles: the same byte count decides between 256x256 tiles (fewest bytes per flop, but only four
-        // half-depth stages fit in LDS and the loop reaches about 42 GB/s per CU) and 256x128 tiles (55 GB/s per CU);
-        // rounds of tiles x rows per tile / rate.  256x192 tiles when they land in fewer rounds (dx of the down
-        // projection at 1024 tokens: 232 tiles, one round, against 172 of 256x256 that leave a third of the CUs
-        // idle; measured -9 %).
+        // Many tiles: rounds of tiles x rows per tile / rate, 42 for 256x256 and 256x192 tiles, 55 for 256x128.  256x192
+        // tiles when they land in fewer rounds (dx of the down projection at 1024 tokens: 232 tiles, one round, 70 us,
+        // against 172 of 256x256 that leave a third of the CUs idle, 79 us).
         const double c256 = rounds(t256) * 512.0 / 42.0, c128 = rounds(t256x128) * 384.0 / 55.0;
         const long t256x192 = (long)cdiv(g.M, 256) * cdiv(g.N, 192) * g.batch;
         const double c192 = rounds(t256x192) * 448.0 / 42.0;

@@ -3,7 +3,7 @@
 #include "common.h"
 
 // ---------------------------------------------------------------- GEMM (gemm_bf16.hip)
-// C = alpha * (A B^T + A2 B2^T) (+ R), bf16 operands, fp32 accumulate (MFMA 32x32x16).
+// C = alpha * (A B^T + A2 B2^T) (+ R), bf16 operands, fp32 accumulate (MFMA).
 struct GemmNT {
     const bf16_t* A = nullptr;  long lda = 0;   // [M, K]
     const bf16_t* B = nullptr;  long ldb = 0;   // [N, K]
@@ -109,8 +109,8 @@ hipError_t launch_attention_bwd(const bf16_t* q, const bf16_t* k, const bf16_t* 
 hipError_t launch_rmsnorm_fwd(const float* h, const float* g, int T, int d, float eps, bf16_t* y, hipStream_t s,
                               const float* part = nullptr, int n_part = 0, long part_stride = 0,
                               const float* resid = nullptr, float* h_write = nullptr);
-// dy_part != null: dy is the sum of n_part fp32 arrays [T, d] that lie part_stride elements apart (the partial tiles a
-// split GEMM left behind, see GemmNT::deferred); the bf16 dy is then not read.
+// dy_part != null: dy is the sum of n_part fp32 (part_bf16: bf16) arrays [T, d] that lie part_stride elements apart (the
+// partial tiles a split GEMM left behind, see GemmNT::deferred); the bf16 dy is then not read.
 hipError_t launch_rmsnorm_bwd(const bf16_t* dy, const float* h, const float* g, const float* dres, int T, int d,
                               float eps, float* dh_out, bf16_t* dh_bf, hipStream_t s, const float* dy_part = nullptr,
                               int n_part = 0, long part_stride = 0, int part_bf16 = 0);
