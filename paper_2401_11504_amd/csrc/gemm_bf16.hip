@@ -213,7 +213,8 @@ __device__ __forceinline__ unsigned div_by(unsigned n, unsigned inv) { return in
 // barrier per tile ("hand-over"): before the second k-step every wave has read the whole tile (its places may be
 // refilled) and the next tile has landed.  Nothing is issued in bursts: the fragments of the next k-step and the fetches
 // are spread between the MFMAs, at most as fast as the LDS (one 16-byte read per wave and three MFMAs) and the address
-// unit take them, so that the matrix pipe is what the wave waits for.
+// unit take them, so that with the 256-wide tiles the matrix pipe is what the wave waits for (256x128 and 128x128 tiles
+// request more bytes per flop: 53 to 58 GB/s per CU of the 60 that the loads reach alone with cold weights).
 //
 // Measured, M = 2048, N = 32000, K = 4096, weights cold: 455 us (1180 TFLOP/s) with 256x256 tiles of eight waves,
 // v_mfma_f32_32x32x16_bf16, a barrier every 32 contraction elements; 413 us with four waves and one barrier every 64;
@@ -716,12 +717,12 @@ enum NtConfig {
 
 // A model of the time: rounds of tiles over the 256 CUs, times the operand bytes of a tile, over a rate per CU.  The rates (53 GB/s
 // below; 42 and 55 for many tiles) were fitted to the loop that the direct-to-LDS kernel had before its present one and are
-// kept as empirical constants: the present loop's time follows its matrix instructions more than its bytes, so they rank the
-// tile shapes and are no bandwidths.  Checked on the present loop over the products of a 7B layer with cold weights, every
-// instance forced on every shape: from 128 tiles of 128x128 on and up to 3072 rows the pick is the fastest or within 3 %,
-// but for q|k|v at 1357 rows (256x192 would take 11 % less) and three others (5 to 6 %).  At 5120 rows the 4096-wide products
-// would take 17 to 20 % less in 256x192 tiles (400 instead of 640 in 2.5 rounds), and below 128 tiles (256 or 334 rows, 4096
-// wide) long contractions 11 to 47 % less split in four.
+// kept as empirical constants.  With cold weights the present loop pulls 53 GB/s in 128x128 tiles, 53 to 58 in 256x128 (loads
+// without any arithmetic: 60), 50 to 53 in 256x192 and 44 to 51 in 256x256 (there the matrix pipe holds it), so the two
+// largest are rated too slow.  What that costs, every instance forced on every product of a 7B layer: from 128 tiles of 128x128
+// on and up to 3072 rows the pick is the fastest or within 3 %, but for q|k|v at 1357 rows (256x192 would take 11 % less)
+// and three others (5 to 6 %).  At 5120 rows the 4096-wide products would take 17 to 20 % less in 256x192 tiles (400 instead of
+// 640 in 2.5 rounds), and below 128 tiles (256 or 334 rows, 4096 wide) long contractions 11 to 47 % less split in four.
 static NtConfig choose_nt(const GemmNT& g, int* n_split) {
     *n_split = 1;
     const int nk = cdiv(g.K, BK) + cdiv(g.K2, BK);
