@@ -248,12 +248,12 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
 }
 
 // The same product for a call that stands alone (a given vector or a SwiGLU; h, if any, is read as it is, one for every
-// rows_per_group rows), and for short, or few long, rows behind a norm: x first, then one row per wave with four loads in flight, or one row per workgroup where there are at most 512 of them, so that
-// a row's loads are all in flight at once instead of queued behind one wave.  Few registers, so that the next launch's
-// workgroups are on the chip while this one's finish: back to back, cold weights, against gemv_kernel: 512 rows of 11008 5.8 and
-// 7.3 us, 64 rows of 28672 8.5 and 12.7; 12288 rows of 256 5.8 and 8.5; 32000 rows of 4096 40.6 and 43.8.  Behind a norm the
-// other kernel is the faster one above 1024 entries (lm_head 51.7 and 41.7 us), up to 4096 of them also for few rows (512: 4.7 and
-// 4.0).
+// rows_per_group rows), and for few long rows behind a norm: x first, then one row per wave with four loads in flight, or one row
+// per workgroup where there are at most 512 of them, so that a row's loads are all in flight at once instead of queued behind one
+// wave.  Few registers, so that the next launch's workgroups are on the chip while this one's finish: back to back, cold
+// weights, against gemv_kernel: 512 rows of 11008 5.8 and 7.3 us, 64 rows of 28672 8.5 and 12.7; 12288 rows of 256 6.1 and 8.5;
+// 32000 rows of 4096 40.6 and 43.8.  In a chain of launches that wait for each other, as lm_head behind its norm, the other
+// kernel's early loads are worth more (51.7 and 41.7 us; 1000 rows of 256: 6 us of a token's 95).
 // pre.mode as for gemv_kernel, and 2: SwiGLU of a gate|up row, x = bf16(silu(g) u).
 __global__ __launch_bounds__(256) void gemv_plain_kernel(const bf16_t* __restrict__ W, long ldw, const bf16_t* __restrict__ x,
                                                          int N, int K, GemvLora lora, float alpha, const float* __restrict__ resid,
@@ -340,7 +340,7 @@ hipError_t launch_gemv(const bf16_t* W, long ldw, const bf16_t* x, int N, int K,
     if (lo.rows_per_group <= 0) lo.rows_per_group = N;
     if (lo.n_a > 0 ? (!lo.a || !lo.h_out || lo.b) : (lo.b && (!lo.h || lo.r < 1))) return hipErrorInvalidValue;
     if (lo.n_parts > 0 && (!lo.b || lo.r > 256 || lo.rows_per_group < N)) return hipErrorInvalidValue;   // summed for one group
-    const bool alone = lo.n_a == 0 && lo.n_parts == 0 && (lo.b || p.mode != 1 || K <= 1024 || (N <= 512 && K > 4096));
+    const bool alone = lo.n_a == 0 && lo.n_parts == 0 && (lo.b || p.mode != 1 || (N <= 512 && K > 4096));
     const size_t lds = gemv_x_bytes(K) + (lo.n_parts > 0 && gemv_parts_fit(K) ? 512 * sizeof(float) : 0);
     auto run = [&](auto kern, int grid, auto... more) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -57,7 +57,7 @@ def test_wider_input_vectors_are_refused(api, H):  # noqa: F811
         api.tl_k_gemv_pre(W.view(1, -1), h[:1], 1, h=h, gain=h, eps=1e-5)
 
 
-# on both sides of where a product behind a norm changes kernels: 1024 columns; 512 rows of more than 4096
+# on both sides of where a product behind a norm changes kernels: 512 rows of more than 4096 columns
 @pytest.mark.parametrize("N,K", [(520, 1024), (520, 1032), (512, 1032), (512, 4096), (512, 4104), (516, 4104), (3, 8)])
 def test_product_behind_a_norm(api, H, N, K):  # noqa: F811
     W, h, gain = rnd(1, (N, K), 0.05), rnd(2, (1, K), 2.0, False), 1.0 + rnd(3, (1, K), 0.1, False)[0]
