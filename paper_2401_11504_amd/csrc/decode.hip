@@ -62,7 +62,7 @@ __device__ __forceinline__ void lowrank_part(const bf16_t* a, long lda, int r, c
 // workgroup (the vector is a few KB out of L2); workgroup 0 stores it to pre.x_out if that is set.
 constexpr int GEMV_AHEAD = 8;
 // LDS (160 KB): x, and for the sum of the parts of h 2 KB behind it; a vector so long that it leaves no room for those (K above
-// 80896) has them in its place once the product is done.
+// 80896) has them in its place once the product is done (PARTS_LAST).
 constexpr size_t LDS_PER_CU = 160 * 1024;
 constexpr int GEMV_MAX_K = (int)(LDS_PER_CU - 16 * sizeof(float)) / 2;     // x beside the block sums
 __host__ __device__ constexpr size_t gemv_x_bytes(int K) { return ((size_t)K * 2 + 15) & ~(size_t)15; }
@@ -99,7 +99,7 @@ __device__ __forceinline__ float gemv_row(const bf16_t* w, const bf16_t* sx, int
     return acc;
 }
 
-template <int R, int MODE>
+template <int R, int MODE, bool PARTS_LAST = false>
 __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t* __restrict__ W, long ldw,
                                                                    const bf16_t* __restrict__ x, int N, int K, GemvLora lora,
                                                                    float alpha, const float* __restrict__ resid,
@@ -108,8 +108,7 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float red[16];
     bf16_t* sx = (bf16_t*)smem;
-    const bool parts_last = !gemv_parts_fit(K);
-    float *hp = (float*)(smem + (parts_last ? 0 : gemv_x_bytes(K))), *hs = hp + 256;        // only with lora.n_parts
+    float *hp = (float*)(smem + (PARTS_LAST ? 0 : gemv_x_bytes(K))), *hs = hp + 256;        // only with lora.n_parts
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rows = N + lora.n_a, n0 = ((int)blockIdx.x * 4 + wave) * R;
 
@@ -190,7 +189,7 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
     } else {
         for (int i = threadIdx.x * 8; i < K; i += 2048) *(uint4*)(sx + i) = *(const uint4*)(x + i);
     }
-    if (hg && !parts_last) hp[threadIdx.x] = hsum;
+    if (hg && !PARTS_LAST) hp[threadIdx.x] = hsum;
     __syncthreads();
     if (pre.x_out && blockIdx.x == 0)
         for (int i = threadIdx.x * 8; i < K; i += 2048) *(uint4*)(pre.x_out + i) = *(const uint4*)(sx + i);
@@ -202,8 +201,8 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
         }
         __syncthreads();
     };
-    if (hg && !parts_last) add_parts();
-    if (n0 >= rows && !(hg && parts_last)) return;      // (the barriers below are for every wave)
+    if (hg && !PARTS_LAST) add_parts();
+    if (n0 >= rows && !PARTS_LAST) return;      // (with PARTS_LAST the barriers below are for every wave)
 
     float acc[R];
 #pragma unroll
@@ -221,7 +220,7 @@ __global__ __launch_bounds__(256, R == 1 ? 4 : 3) void gemv_kernel(const bf16_t*
             for (int i = 0; i < R; ++i) acc[i] = k < K ? dot8(wv[i][u], b, acc[i]) : acc[i];
         }
     }
-    if (hg && parts_last) {
+    if (PARTS_LAST) {
         __syncthreads();                                // x has been read
         hp[threadIdx.x] = hsum;
         __syncthreads();
@@ -354,6 +353,7 @@ hipError_t launch_gemv(const bf16_t* W, long ldw, const bf16_t* x, int N, int K,
     // workgroups.
     const bool two = N >= 8192;
     const int grid = cdiv((long)N + lo.n_a, two ? 8 : 4);
+    if (p.mode == 0 && !gemv_parts_fit(K)) return run(gemv_kernel<1, 0, true>, cdiv(N, 4));
     if (p.mode == 0) return two ? run(gemv_kernel<2, 0>, grid) : run(gemv_kernel<1, 0>, grid);
     return two ? run(gemv_kernel<2, 1>, grid) : run(gemv_kernel<1, 1>, grid);
 }
