@@ -68,33 +68,53 @@ constexpr int GEMV_MAX_K = (int)(LDS_PER_CU - 16 * sizeof(float)) / 2;     // x 
 __host__ __device__ constexpr size_t gemv_x_bytes(int K) { return ((size_t)K * 2 + 15) & ~(size_t)15; }
 __host__ __device__ constexpr bool gemv_parts_fit(int K) { return gemv_x_bytes(K) + 512 * sizeof(float) <= LDS_PER_CU; }
 
-// a long row's product with x, w0 holding this lane's share of its first 4096 columns: eight loads ahead of the eight that
-// are being added up
+// A long row's product with x, w0 holding this lane's share of its first 4096 columns: eight loads ahead of the eight that
+// are being added up.  A last trip of fewer pieces of 512 columns loads two, four, six or eight of them (one token of two 5120-wide
+// layers: 431 us with eight, 406 with two); what a lane or a piece has behind the end of the row is left out of the sum.
+template <int NB>
+__device__ __forceinline__ void gemv_load(uint4 (&wv)[GEMV_AHEAD], const bf16_t* w, int K, int lane, int k) {
+#pragma unroll
+    for (int u = 0; u < NB; ++u) wv[u] = load_w16(w + min(k + u * 512 + lane * 8, K - 8));
+    __builtin_amdgcn_sched_barrier(0);
+}
+template <int NB>
+__device__ __forceinline__ float gemv_add(const uint4 (&wv)[GEMV_AHEAD], const bf16_t* sx, int K, int lane, int k, float acc) {
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        const int kk = k + u * 512 + lane * 8;
+        float b[8];
+        unpack8(*(const uint4*)(sx + min(kk, K - 8)), b);
+        acc = kk < K ? dot8(wv[u], b, acc) : acc;
+    }
+    return acc;
+}
 __device__ __forceinline__ float gemv_row(const bf16_t* w, const bf16_t* sx, int K, int lane, uint4 (&w0)[GEMV_AHEAD]) {
     constexpr int NB = GEMV_AHEAD, STEP = NB * 512;
     uint4 w1[NB];
     float acc = 0.f;
-    auto load = [&](uint4 (&wv)[NB], int k) {
-        if (k >= K) return;
-#pragma unroll
-        for (int u = 0; u < NB; ++u) wv[u] = load_w16(w + min(k + u * 512 + lane * 8, K - 8));
-        __builtin_amdgcn_sched_barrier(0);
+    // the trip at k, held in a, and behind it the last one, to be fetched into b; false if there is more than that
+    auto last = [&](uint4 (&a)[NB], uint4 (&b)[NB], int k) {
+        const int left = K - k - STEP;
+        auto end = [&](auto n) {
+            constexpr int NT = decltype(n)::value;
+            gemv_load<NT>(b, w, K, lane, k + STEP);
+            acc = gemv_add<NT>(b, sx, K, lane, k + STEP, gemv_add<NB>(a, sx, K, lane, k, acc));
+        };
+        if (left > STEP) return false;
+        if (left <= 0) acc = gemv_add<NB>(a, sx, K, lane, k, acc);
+        else if (left <= 1024) end(std::integral_constant<int, 2>{});
+        else if (left <= 2048) end(std::integral_constant<int, 4>{});
+        else if (left <= 3072) end(std::integral_constant<int, 6>{});
+        else end(std::integral_constant<int, 8>{});
+        return true;
     };
-    auto add = [&](const uint4 (&wv)[NB], int k) {
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int kk = k + u * 512 + lane * 8;
-            float b[8];
-            unpack8(*(const uint4*)(sx + min(kk, K - 8)), b);
-            acc = kk < K ? dot8(wv[u], b, acc) : acc;
-        }
-    };
-    for (int k = 0; k < K; k += 2 * STEP) {
-        load(w1, k + STEP);
-        add(w0, k);
-        if (k + STEP >= K) break;
-        load(w0, k + 2 * STEP);
-        add(w1, k + STEP);
+    for (int k = 0;; k += 2 * STEP) {
+        if (last(w0, w1, k)) break;
+        gemv_load<NB>(w1, w, K, lane, k + STEP);
+        acc = gemv_add<NB>(w0, sx, K, lane, k, acc);
+        if (last(w1, w0, k + STEP)) break;
+        gemv_load<NB>(w0, w, K, lane, k + 2 * STEP);
+        acc = gemv_add<NB>(w1, sx, K, lane, k + STEP, acc);
     }
     return acc;
 }

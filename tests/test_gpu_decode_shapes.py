@@ -57,15 +57,18 @@ def test_wider_input_vectors_are_refused(api, H):  # noqa: F811
         api.tl_k_gemv_pre(W.view(1, -1), h[:1], 1, h=h, gain=h, eps=1e-5)
 
 
-# on both sides of where a product behind a norm changes kernels: 512 rows of more than 4096 columns
-@pytest.mark.parametrize("N,K", [(520, 1024), (520, 1032), (512, 1032), (512, 4096), (512, 4104), (516, 4104), (3, 8)])
+# on both sides of where a product behind a norm changes kernels (512 rows of more than 4096 columns), and where a long row's last
+# trip changes length (4096 columns a trip, 1024 a step of the last one); two rows per wave from 8192 rows on
+@pytest.mark.parametrize("N,K", [(520, 1024), (520, 1032), (512, 1032), (512, 4096), (512, 4104), (516, 4104), (3, 8), (514, 5120),
+                                 (514, 5128), (514, 6144), (514, 6152), (514, 7176), (514, 8192), (514, 8200), (514, 9224),
+                                 (514, 12288), (514, 13824), (514, 16392), (8195, 5120), (8193, 9216)])
 def test_product_behind_a_norm(api, H, N, K):  # noqa: F811
     W, h, gain = rnd(1, (N, K), 0.05), rnd(2, (1, K), 2.0, False), 1.0 + rnd(3, (1, K), 0.1, False)[0]
     y, xo = torch.empty(N, device="cuda"), torch.empty(K, dtype=torch.bfloat16, device="cuda")
     api.tl_k_gemv_pre(H.to_dev_bf16(W), y, 1, h=H.to_dev_f32(h[0]), gain=H.to_dev_f32(gain), eps=1e-5, x_out=xo)
     x = H.bf16_to_np(xo).astype(np.float64)
     check(x, O.rmsnorm_fwd(h, gain, 1e-5)[0], BF16_TOL, "x")
-    # K products summed in fp32: sqrt(4104) 2^-24 = 3.8e-6 of the sum's 2-norm, doubled for the reduction across lanes
+    # K products summed in fp32: sqrt(16392) 2^-24 = 7.6e-6 of the sum's 2-norm; the lanes' chains are K / 64 long
     check(y.cpu().numpy(), W.astype(np.float64) @ x, 1e-5, "y")
 
 
