@@ -349,8 +349,10 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
         else if (r == 2 || AST == 3) wait_vmcnt<(AST > 2 ? 2 : 1) * (LA + LB)>();
         else wait_vmcnt<(AST - 1) * (LA + LB)>();
     };
-    // tile 0 has landed; an edge tile in the prologue may have skipped lanes, so its fetches cannot be counted
-    wait_tiles(n_edge == 0 ? min(nk, AST) - 1 : 0);
+    // A wave may have skipped fetches of a narrow edge tile: those cannot be counted, and whoever needs a tile behind one waits
+    // for everything in flight.
+    const bool narrow = ((p.K | p.K2) & (BK - 1)) != 0;
+    wait_tiles(n_edge == 0 || !narrow ? min(nk, AST) - 1 : 0);      // tile 0 has landed
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -395,9 +397,9 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
     // fetches that may still be outstanding at the hand-over of a steady-state tile (the younger tiles')
     constexpr int HW = (AST - 1) * LB + (AST - 2) * LA;
     static_assert(HW <= 63, "s_waitcnt vmcnt is a 6-bit field");
-    // the last AST tiles fetch nothing, and the tiles still in flight can be counted unless they are edge tiles from the
+    // the last AST tiles fetch nothing, and the tiles still in flight can be counted unless they are narrow edge tiles from the
     // loop for those
-    const bool counted = n_edge <= AST || nk >= n_edge + AST;
+    const bool counted = !narrow || n_edge <= AST || nk >= n_edge + AST;
     auto next = [](unsigned s, unsigned stage, unsigned ring) { return s + stage == ring ? 0u : s + stage; };
     // MODE 2: fetch whole tiles; 1: fetch edge tiles; 0: fetch nothing (the last AST tiles)
     auto tile = [&](auto mode_c, auto last_c, int kt) {
@@ -413,7 +415,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
         sbw = next(sbw, B_STAGE, BST * B_STAGE);
         if constexpr (!LAST) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            if constexpr (MODE == 2) wait_vmcnt<HW>(); else wait_tiles(MODE == 0 && counted ? nk - 2 - kt : 0);
+            if (MODE == 2 || (MODE == 1 && !narrow)) wait_vmcnt<HW>(); else wait_tiles(MODE == 0 && counted ? nk - 2 - kt : 0);
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             if constexpr (MODE == 1) fetch_edge(kt + AST, F_{}, sa_old);
@@ -424,7 +426,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
         if constexpr (MODE == 2) { pa += BK; pb += BK; }
     };
     int kt = 0;
-    // more edge tiles than the prologue fetches (ranks above 128): their hand-overs wait for everything in flight
+    // more edge tiles than the prologue fetches (ranks above 64 or so)
     for (; kt < n_edge - AST; ++kt) tile(C1{}, F_{}, kt);
     for (; kt < nk - AST; ++kt) tile(std::integral_constant<int, 2>{}, F_{}, kt);
     for (; kt < nk - 1; ++kt) tile(C0{}, F_{}, kt);
