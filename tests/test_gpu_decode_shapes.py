@@ -132,3 +132,20 @@ def test_attention_and_non_finite_values(api, n_keys, ranges, dh):  # noqa: F811
     kv[at, dh + 3] = float("nan")                 # a key of head 1
     got = run()
     assert torch.isfinite(got[0]).all() and torch.isnan(got[1]).all()
+
+
+# o and down at every length of a long row's last trip, a norm of more than 4096 entries in front of q|k|v and gate|up, and outputs
+# of 8192 rows and more, two per wave
+@pytest.mark.parametrize("heads,d_head,d_ffn", [(2, 64, 4104), (2, 64, 5128), (2, 64, 6152), (2, 64, 7176), (2, 64, 8200), (2, 64, 13824),
+                                                (36, 128, 520), (66, 128, 1032)])
+def test_long_rows_of_one_token(api, H, heads, d_head, d_ffn):  # noqa: F811
+    shape = synth.Shape(1, heads * d_head, heads, d_head, d_ffn, 504, 24, 24.0)
+    model = H.Model(shape, 79, max_tokens=34)
+    lora, _ = H.new_lora(model, 79, b_std=0.02)
+    tok = synth.zipf_tokens(79, 33, shape.vocab)
+    api.tl_prefill(lora, tok[:32], shape.vocab)
+    _, got = api.tl_decode_step(lora, int(tok[32]), shape.vocab)
+    _, want = api.tl_prefill(lora, tok, shape.vocab)
+    check(got, want, 1e-2, "logits")
+    api.tl_lora_free(lora)
+    model.close()
