@@ -362,7 +362,7 @@ hipError_t launch_gemv(const bf16_t* W, long ldw, const bf16_t* x, int N, int K,
     GemvLora lo = lora;
     if (lo.rows_per_group <= 0) lo.rows_per_group = N;
     if (lo.n_a > 0 ? (!lo.a || !lo.h_out || lo.b) : (lo.b && (!lo.h || lo.r < 1))) return hipErrorInvalidValue;
-    if (lo.n_parts > 0 && (!lo.b || lo.r > 256 || lo.rows_per_group < N)) return hipErrorInvalidValue;   // summed for one group
+    if (lo.n_parts > 0 && (p.mode != 0 || !lo.b || lo.r > 256 || lo.rows_per_group < N)) return hipErrorInvalidValue;   // summed for one group
     const bool alone = lo.n_a == 0 && lo.n_parts == 0 && (lo.b || p.mode != 1 || (N <= 512 && K > 4096));
     const size_t lds = gemv_x_bytes(K) + (lo.n_parts > 0 && gemv_parts_fit(K) ? 512 * sizeof(float) : 0);
     auto run = [&](auto kern, int grid, auto... more) {
