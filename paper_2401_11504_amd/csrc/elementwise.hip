@@ -19,9 +19,13 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const float* h, const 
     auto fetch = [&](int i) {
         if (!part) return ((const float4*)(h + row * d))[i];
         float4 t = resid ? *(const float4*)(resid + row * d + 4 * (long)i) : make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int k = 0; k < n_part; ++k) {
-            const float4 q = *(const float4*)(part + (long)k * part_stride + row * d + 4 * (long)i);
-            t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
+        const float* p = part + row * d + 4 * (long)i;
+        for (int k = 0; k < n_part; k += 4) {      // four in flight
+            float4 q[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q[u] = k + u < n_part ? *(const float4*)(p + (long)(k + u) * part_stride) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { t.x += q[u].x; t.y += q[u].y; t.z += q[u].z; t.w += q[u].w; }
         }
         *(float4*)(h_write + row * d + 4 * (long)i) = t;
         return t;
@@ -81,14 +85,23 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const bf16_t* __restri
     auto dy4 = [&](int i) {
         if (dy_part) {
             float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int k = 0; k < n_part; ++k) {
+            const long at = row * d + 4 * (long)i;
+            for (int k = 0; k < n_part; k += 4) {      // four in flight
                 if (part_bf16) {
-                    const uint2 r = *(const uint2*)((const bf16_t*)dy_part + (long)k * part_stride + row * d + 4 * (long)i);
-                    t.x += bf16_to_f32(r.x & 0xffff); t.y += bf16_to_f32(r.x >> 16);
-                    t.z += bf16_to_f32(r.y & 0xffff); t.w += bf16_to_f32(r.y >> 16);
+                    uint2 r[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) r[u] = k + u < n_part ? *(const uint2*)((const bf16_t*)dy_part + (long)(k + u) * part_stride + at) : make_uint2(0u, 0u);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        t.x += bf16_to_f32(r[u].x & 0xffff); t.y += bf16_to_f32(r[u].x >> 16);
+                        t.z += bf16_to_f32(r[u].y & 0xffff); t.w += bf16_to_f32(r[u].y >> 16);
+                    }
                 } else {
-                    const float4 q = *(const float4*)(dy_part + (long)k * part_stride + row * d + 4 * (long)i);
-                    t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
+                    float4 q[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) q[u] = k + u < n_part ? *(const float4*)(dy_part + (long)(k + u) * part_stride + at) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) { t.x += q[u].x; t.y += q[u].y; t.z += q[u].z; t.w += q[u].w; }
                 }
             }
             return t;
@@ -551,16 +564,21 @@ __global__ void fill_f32_kernel(float* __restrict__ p, size_t n, float v) {
 }
 // n bf16 zeros (n a multiple of 2, p 4-byte aligned): a fill kernel rather than a memset node, so that the path stays
 // capturable in a HIP graph
-__global__ void zero_u32_kernel(uint32_t* __restrict__ p, size_t n) {
+// rows [0, r0) and [r1, T) of x (fp32) and y (bf16), d columns each, become zero (sixteen bytes of x per thread and step)
+__global__ __launch_bounds__(256) void zero_rows_around_kernel(float* __restrict__ x, bf16_t* __restrict__ y, size_t n0, size_t at, size_t n) {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0u;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        const size_t k = i < n0 ? i : i - n0 + at;
+        ((float4*)x)[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+        ((uint2*)y)[k] = make_uint2(0u, 0u);
+    }
 }
-hipError_t launch_fill_bf16_zero(bf16_t* p, size_t n, hipStream_t s) {
+hipError_t launch_zero_rows_around(float* x, bf16_t* y, int T, int d, int r0, int r1, hipStream_t s) {
+    if ((d & 3) || r0 < 0 || r1 < r0 || r1 > T) return hipErrorInvalidValue;
+    const size_t q = d / 4, n0 = r0 * q, n = n0 + (T - r1) * q;
     if (n == 0) return hipSuccess;
-    if ((n & 1) || ((size_t)p & 3)) return hipErrorInvalidValue;
-    size_t blocks = (n / 2 + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    zero_u32_kernel<<<(unsigned)blocks, 256, 0, s>>>((uint32_t*)p, n / 2);
+    const size_t blocks = (n + 255) / 256;
+    zero_rows_around_kernel<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, s>>>(x, y, n0, r1 * q, n);
     return hipGetLastError();
 }
 hipError_t launch_fill_f32(float* p, size_t n, float value, hipStream_t s) {

@@ -567,6 +567,12 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
     }
 }
 
+// bf16 partial tiles where the reduce is left to a consumer that takes them, and only for products that 128x128 tiles fill half the
+// chip with and 256x128 tiles do not fill three quarters of: more rows than that were one fp32 sum when such tiles were introduced,
+// fewer have more splits, and fp32 partials cost both little beside what the split gains them.
+static bool nt_bf16_parts(const GemmNT& g) {
+    return g.partial_bf16 && (long)cdiv(g.M, 128) * cdiv(g.N, 128) * g.batch >= 128 && (long)cdiv(g.M, 256) * cdiv(g.N, 128) * g.batch < 192;
+}
 template <int BM, int BN, int AST, bool SPLITK>
 static hipError_t run_nt_dl(const GemmNT& g, hipStream_t s, int n_split = 1) {
     const int tiles_m = cdiv(g.M, BM), tiles_n = cdiv(g.N, BN);
@@ -576,11 +582,12 @@ static hipError_t run_nt_dl(const GemmNT& g, hipStream_t s, int n_split = 1) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     GemmNT gk = g;
-    const bool defer = SPLITK && g.deferred && BM >= 256;            // wide-output instance: the consumer adds the partial tiles up
-    if (!defer) gk.partial_bf16 = 0;   // bf16 partial tiles only where the reduce is left to the consumer
+    const bool defer = SPLITK && g.deferred;                         // the consumer adds the partial tiles up
+    gk.partial_bf16 = defer && nt_bf16_parts(g);
     kern<<<grid, 256, lds, s>>>(gk, make_nt_map(tiles_m, tiles_n, SPLITK ? n_split : 1, g.batch, SPLITK));
     if (defer) {
         *g.deferred = n_split;
+        if (g.deferred_bf16) *g.deferred_bf16 = gk.partial_bf16;
     } else if (SPLITK) {
         const long n = (long)g.M * (g.N >> 2) * g.batch;
         splitk_reduce_kernel<<<cdiv(n, 256), 256, 0, s>>>(g, n_split);
@@ -660,116 +667,78 @@ static bool nt_direct(const GemmNT& g) {
 // register-staged kernel, whose split it shares with every other rank
 static bool nt_direct_small(const GemmNT& g) { return nt_direct(g) && ((g.K % BK) == 0 || g.N >= 128); }
 
-// A many-tile GEMM whose tile count leaves the last round of workgroups poorly filled can be cheaper as two launches:
-// columns [0, N1) (of every batch) as whole rounds of 256x256 tiles, the rest on its own with whatever tile suits it
-// (gate|up at 1024 tokens: 688 tiles of 256x128 are 2.7 rounds and cost three; 256 tiles of 256x256 plus 176 of 256x128
-// cost 12.2 + 7.0 instead of 3 x 7.0 in the units of the tile model below: 148 us, 162 in one launch of 256x128, 165 of
-// 256x256; one of 256x192, which the model takes for slower, measures 140).  Returns N1, or 0 for one launch.
-int gemm_nt_column_split(const GemmNT& g) {
-    if (g.deferred || g.split_k > 1 || g.M <= 0 || g.N < 512 || g.batch <= 0) return 0;
-    if (!nt_direct(g)) return 0;
-    const long tm = (long)cdiv(g.M, 256) * g.batch;
-    if (tm > 256 || 256 % tm) return 0;                       // a round of 256x256 tiles must be whole tile columns
-    const long cols_round = 256 / tm * 256;
-    if (tm * cdiv(g.N, 256) < 160) return 0;                  // few tiles: launch_gemm_nt has other choices there
-    auto rounds = [](long t) { return (double)((t + 255) / 256); };
-    auto one_launch = [&](long n) {                           // the many-tile model of launch_gemm_nt, per unit of K
-        const double c256 = rounds(tm * cdiv(n, 256)) * 512.0 / 42.0, c128 = rounds(tm * cdiv(n, 128)) * 384.0 / 55.0;
-        const double c192 = rounds(tm * cdiv(n, 192)) * 448.0 / 42.0;
-        return c256 < c128 ? (c256 < c192 ? c256 : c192) : (c128 < c192 ? c128 : c192);
-    };
-    const double k_us = ((double)g.K + g.K2) * 2.0 / 1e3, second_launch_us = 6.0;
-    double best = one_launch(g.N) * k_us;
-    int n1 = 0;
-    for (long c = cols_round; c + 128 <= g.N; c += cols_round) {
-        const double cost = ((double)(c / cols_round) * 512.0 / 42.0 + one_launch(g.N - c)) * k_us + second_launch_us;
-        if (cost < 0.97 * best) { best = cost; n1 = (int)c; }
-    }
-    return n1;
-}
-
-// the two launches of a column split: a = columns [0, N1), b = the rest; false (and nothing written) for one launch
-bool gemm_nt_split_columns(const GemmNT& g, GemmNT* a, GemmNT* b) {
-    const int n1 = gemm_nt_column_split(g);
-    if (n1 <= 0) return false;
-    *a = g;
-    *b = g;
-    a->N = n1;
-    b->N = g.N - n1;
-    b->B = g.B + (long)n1 * g.ldb;
-    if (g.K2 > 0) b->B2 = g.B2 + (long)n1 * g.ldb2;
-    b->C = (char*)g.C + (size_t)n1 * (g.c_f32 ? sizeof(float) : sizeof(bf16_t));
-    if (g.R) b->R = g.R + n1;
-    return true;
-}
-
 // The tile configurations the launcher can pick (every one is reachable from launch_gemm_nt; the kernel tests name the
 // shape that lands on each).
 enum NtConfig {
     // tiles of 64 contraction elements; A / B tiles in LDS
-    NT_128x128,         // 128x128, 4 / 5: a few hundred tiles in all
+    NT_128x128,         // 128x128, 4 / 5
+    NT_128x128_SPLIT,   // with the contraction split 2, 4 or 8 ways (partials reduced afterwards or by the consumer)
     NT_256x128,         // 256x128, 3 / 4
-    NT_256x128_SPLIT,   // the same with the contraction split 2..4 ways (partials reduced afterwards or by the consumer)
-    NT_256x192,         // 256x192, 2 / 3: tile counts that 256x256 leaves a third of the CUs idle on
+    NT_256x128_SPLIT,
+    NT_256x192,         // 256x192, 2 / 3
     NT_256x256,         // 256x256, 2 / 3
+    NT_256x256_SPLIT,
     NT_REG_128x128,     // register-staged, for what nt_direct refuses: ragged contractions below 256 elements, operands beyond 1 Gi
     NT_REG_128x64,
     NT_SKINNY           // N <= 64 per batch or few tiles: 64x64 tiles, contraction split over up to 16 workgroups
 };
 
-// A model of the time: rounds of tiles over the 256 CUs, times the operand bytes of a tile, over a rate per CU.  The rates (53 GB/s
-// below; 42 and 55 for many tiles) were fitted to the loop that the direct-to-LDS kernel had before its present one and are
-// kept as empirical constants.  With cold weights the present loop pulls 53 GB/s in 128x128 tiles, 53 to 58 in 256x128 (loads
-// without any arithmetic: 60), 50 to 53 in 256x192 and 44 to 51 in 256x256 (there the matrix pipe holds it), so the two
-// largest are rated too slow.  What that costs, every instance forced on every product of a 7B layer: from 128 tiles of 128x128
-// on and up to 3072 rows the pick is the fastest or within 3 %, but for q|k|v at 1357 rows (256x192 would take 11 % less)
-// and three others (5 to 6 %).  At 5120 rows the 4096-wide products would take 17 to 20 % less in 256x192 tiles (400 instead of
-// 640 in 2.5 rounds), and below 128 tiles (256 or 334 rows, 4096 wide) long contractions 11 to 47 % less split in four.
+// A model of the time of one launch of the direct-to-LDS kernel: full rounds of 256 tiles (one per CU), then what is left, which
+// takes less the fewer CUs it keeps busy (the chip clocks higher and its memory is shared by fewer): us per 1000 contraction
+// elements of a round with next to no tiles (k_min) and with 256 (k_full).  Fitted to every instance forced on the products of
+// 7B-, 2048- and 1024-wide layers at 64 to 5120 rows, weights cold, 1500 timings: it is off by 7 % (rms), and what it picks took
+// 1.1 % longer than the fastest instance on average, where the rule before it (operand bytes of the busiest CU over one rate per
+// instance, splits of 256x128 tiles only) took 10.5 % longer: 4096 x 22016 at 256 rows 106 us against 62, at 5120 rows 1000 against
+// 787; 12288 x 4096 at 768 rows 101 against 65.
+struct NtTile { NtConfig cfg, cfg_split; int bm, bn; double k_min, k_full; };
+static const NtTile kNtTiles[] = {
+    {NT_SKINNY, NT_SKINNY, 64, 64, 3.1, 3.75},
+    {NT_128x128, NT_128x128_SPLIT, 128, 128, 7.1, 9.0},
+    {NT_256x128, NT_256x128_SPLIT, 256, 128, 9.9, 12.6},
+    {NT_256x192, NT_256x192, 256, 192, 12.2, 16.9},
+    {NT_256x256, NT_256x256_SPLIT, 256, 256, 15.5, 20.2},
+};
+struct NtPick { NtConfig cfg; int split; double us; };
+// for products that the direct-to-LDS kernel takes and that are at least 65 columns wide
+static NtPick pick_nt(const GemmNT& g) {
+    const double k1000 = ((double)g.K + g.K2) * 1e-3, mn = (double)g.M * g.N * g.batch;
+    const int nk = cdiv(g.K, BK) + cdiv(g.K2, BK);
+    const bool many = (long)cdiv(g.M, 128) * cdiv(g.N, 128) * g.batch >= 128;      // (64x64 tiles: where 128x128 leave half the CUs idle)
+    // the pass over the partial tiles of a split: a reduce launch that reads them and writes C (6.3 us and 1.4 us a million values),
+    // or, when the consumer adds them up itself (g.deferred), the extra bytes written here and read there
+    const double pass0 = g.deferred ? 0.0 : 6.3, pass1 = g.deferred ? (nt_bf16_parts(g) ? 0.55e-6 : 1.1e-6) : 1.41e-6;
+    const bool may_split = g.split_k == 0 && g.partial && !(g.N & 3);
+    NtPick whole = {NT_SKINNY, 1, 1e30}, split = {NT_SKINNY, 8, 1e30};
+    for (const NtTile& t : kNtTiles) {
+        if (t.bm == 64 && many) continue;
+        const long tiles = (long)cdiv(g.M, t.bm) * cdiv(g.N, t.bn) * g.batch;
+        for (int sp = 1; sp <= 8; sp *= 2) {
+            if (sp > 1 && (!may_split || t.cfg_split == t.cfg || nk / sp < 8 || mn * sp > (double)g.partial_elems)) break;
+            if (sp > 4 && nt_bf16_parts(g)) break;
+            const long n = tiles * sp, rem = n & 255;
+            double us = (double)(n >> 8) * t.k_full;
+            if (rem) us += t.k_min + (t.k_full - t.k_min) * rem * (1.0 / 256);
+            us = 2.0 + us * k1000 / sp + (sp > 1 ? pass0 + pass1 * mn * sp : 0.0);
+            NtPick& best = sp > 1 ? split : whole;
+            if (us < (sp > best.split ? 0.96 : 1.0) * best.us) best = {sp > 1 ? t.cfg_split : t.cfg, sp, us};
+        }
+    }
+    return split.us < 0.96 * whole.us ? split : whole;       // (what promises less than the model's error is not worth more partial tiles)
+}
+
 static NtConfig choose_nt(const GemmNT& g, int* n_split) {
     *n_split = 1;
     const int nk = cdiv(g.K, BK) + cdiv(g.K2, BK);
     const long t128 = (long)cdiv(g.M, 128) * cdiv(g.N, 128) * g.batch;
     const long t64n = (long)cdiv(g.M, 128) * cdiv(g.N, 64) * g.batch;
-    const bool dl_ok = g.N > 64 && nt_direct(g);
-    auto rounds = [](long t) { return (double)((t + 255) / 256); };
-    if (dl_ok && t128 >= 128) {
-        const long t256 = (long)cdiv(g.M, 256) * cdiv(g.N, 256) * g.batch;
-        const long t256x128 = (long)cdiv(g.M, 256) * cdiv(g.N, 128) * g.batch;
-        if (t256 < 160) {
-            // Few 256x256 tiles: pick among 128x128 tiles, 256x128 tiles, and 256x128 tiles with the contraction split
-            // 2..4 ways, by the operand bytes of the busiest CU: rounds of tiles x (BM + BN) x K x 2 bytes.  A split
-            // adds one pass over its partials (written and read back at about 5 TB/s, plus a launch).  At M = 1024
-            // this picks the two-way split from K of about 10k on (with the reduce pass, against 128x128: K 11008 85 and
-            // 105 us, 12288 94 and 118, 22016 155 and 203, 32000 228 and 287) and 128x128 below (K 4096 40 us, split 43);
-            // at M = 2048 plain 256x128 tiles fill the chip.
-            const double ktot = (double)g.K + g.K2, per_us = 53e3;
-            double best = rounds(t128) * 256.0 * ktot * 2.0 / per_us;
-            NtConfig cfg = NT_128x128;
-            const double c28 = rounds(t256x128) * 384.0 * ktot * 2.0 / per_us;
-            if (c28 < best) { best = c28; cfg = NT_256x128; }
-            for (int sp = 2; sp <= 4; ++sp) {
-                const size_t need = (size_t)sp * g.M * g.N * g.batch;
-                if (!g.partial || need > g.partial_elems || (g.N & 3) || nk / sp < 8) continue;
-                // the pass over the partials: a reduce launch that reads them and writes C, or, when the consumer
-                // adds them up itself (g.deferred), only the extra bytes written here and read there
-                const double pass = g.deferred ? (double)need * (g.partial_bf16 ? 2.0 : 4.0) / 5e6 : (double)need * 8.0 / 5e6 + 5.0;
-                const double c = rounds(t256x128 * sp) * 384.0 * (ktot / sp) * 2.0 / per_us + pass;
-                if (c < 0.97 * best) { best = c; cfg = NT_256x128_SPLIT; *n_split = sp; }
-            }
-            return cfg;
-        }
-        // Many tiles: rounds of tiles x rows per tile / rate, 42 for 256x256 and 256x192 tiles, 55 for 256x128.  256x192
-        // tiles when they land in fewer rounds (dx of the down projection at 1024 tokens: 232 tiles, one round, 70 us,
-        // against 172 of 256x256 that leave a third of the CUs idle, 79 us).
-        const double c256 = rounds(t256) * 512.0 / 42.0, c128 = rounds(t256x128) * 384.0 / 55.0;
-        const long t256x192 = (long)cdiv(g.M, 256) * cdiv(g.N, 192) * g.batch;
-        const double c192 = rounds(t256x192) * 448.0 / 42.0;
-        if (c192 < c256 && c192 < c128) return NT_256x192;
-        return c128 < c256 ? NT_256x128 : NT_256x256;
+    if (g.N > 64 && nt_direct(g) && (t128 >= 128 || (g.N >= 256 && g.split_k == 0))) {
+        const NtPick p = pick_nt(g);
+        *n_split = p.split;
+        return p.cfg;
     }
     if (g.N > 64 && t128 >= 200) return NT_REG_128x128;
     if (g.N > 64 && t64n >= 200) return NT_REG_128x64;
-    // few output tiles: 64x64 tiles, and split the contraction when scratch is available
+    // a narrow output (or one the direct-to-LDS kernel refuses): 64x64 tiles, and split the contraction when scratch is available
     const long t64 = (long)cdiv(g.M, 64) * cdiv(g.N, 64) * g.batch;
     int split = g.split_k;
     if (split == 0) {
@@ -787,12 +756,67 @@ static NtConfig choose_nt(const GemmNT& g, int* n_split) {
     return NT_SKINNY;
 }
 
+// A GEMM whose tile count leaves its last round of workgroups poorly filled can be cheaper as two launches: whole rounds of tiles
+// over the first columns (of every batch) or the first rows, and the rest on its own with whatever tile and split suits it.
+// 5120 rows of 4096 x 22016: 320 tiles of 256x256, a round and a quarter that costs two, 819 us, 787 in 256x192 tiles; as 4096 rows (482 us)
+// and 1024 (141) 623.
+bool gemm_nt_two_parts(const GemmNT& g, GemmNT* a, GemmNT* b) {
+    if (g.split_k > 1 || g.M < 256 || g.N < 512 || g.batch <= 0 || !nt_direct(g)) return false;
+    const double second_launch_us = 3.0;
+    if ((long)cdiv(g.M, 256) * cdiv(g.N, 128) * g.batch <= 256) return false;      // one round as it is
+    GemmNT h = g;
+    double best = 0.96 * pick_nt(h).us;
+    h.deferred = nullptr;
+    h.partial_bf16 = 0;
+    int rows = 0, cols = 0;
+    for (const NtTile& t : kNtTiles) {
+        if (t.bm < 256) continue;
+        const long tm = cdiv(g.M, t.bm), tn = cdiv(g.N, t.bn), rounds = tm * tn * g.batch / 256;
+        for (long r = rounds; r >= 1 && r >= rounds - 1; --r) {
+            for (int by_rows = 0; by_rows < 2; ++by_rows) {
+                const long first = by_rows ? 256 * r / (tn * g.batch) * t.bm : 256 * r / (tm * g.batch) * t.bn;
+                const int whole = by_rows ? g.M : g.N;
+                if (first <= 0 || whole - first < 64) continue;
+                int& n = by_rows ? h.M : h.N;
+                n = (int)first;
+                double us = pick_nt(h).us;
+                n = whole - (int)first;
+                us += pick_nt(h).us + second_launch_us;
+                n = whole;
+                if (us < best) { best = us; rows = by_rows ? (int)first : 0; cols = by_rows ? 0 : (int)first; }
+            }
+        }
+    }
+    if (!rows && !cols) return false;
+    const size_t out = g.c_f32 ? sizeof(float) : sizeof(bf16_t);
+    if (g.deferred) *g.deferred = 0;
+    *a = *b = h;
+    if (rows) {
+        a->M = rows;
+        b->M = g.M - rows;
+        b->A = g.A + (long)rows * g.lda;
+        if (g.K2 > 0) b->A2 = g.A2 + (long)rows * g.lda2;
+        b->C = (char*)g.C + (size_t)rows * g.ldc * out;
+        if (g.R) b->R = g.R + (long)rows * g.ldc;
+    } else {
+        a->N = cols;
+        b->N = g.N - cols;
+        b->B = g.B + (long)cols * g.ldb;
+        if (g.K2 > 0) b->B2 = g.B2 + (long)cols * g.ldb2;
+        b->C = (char*)g.C + (size_t)cols * out;
+        if (g.R) b->R = g.R + cols;
+    }
+    return true;
+}
+
 const char* gemm_nt_plan(const GemmNT& g, int* n_split) {
     int sp = 1;
     const NtConfig c = choose_nt(g, &sp);
     if (n_split) *n_split = sp;
     switch (c) {
         case NT_128x128: return "128x128";
+        case NT_128x128_SPLIT: return "128x128-split";
+        case NT_256x256_SPLIT: return "256x256-split";
         case NT_256x128: return "256x128";
         case NT_256x128_SPLIT: return "256x128-split";
         case NT_256x192: return "256x192";
@@ -817,7 +841,9 @@ hipError_t launch_gemm_nt(const GemmNT& g, hipStream_t s) {
     switch (choose_nt(g, &split)) {
         case NT_128x128: return run_nt_dl<128, 128, 4, false>(g, s);
         case NT_256x128: return run_nt_dl<256, 128, 3, false>(g, s);
+        case NT_128x128_SPLIT: return run_nt_dl<128, 128, 4, true>(g, s, split);
         case NT_256x128_SPLIT: return run_nt_dl<256, 128, 3, true>(g, s, split);
+        case NT_256x256_SPLIT: return run_nt_dl<256, 256, 2, true>(g, s, split);
         case NT_256x192: return run_nt_dl<256, 192, 2, false>(g, s);
         case NT_256x256: return run_nt_dl<256, 256, 2, false>(g, s);
         case NT_REG_128x128: return run_nt<128, 128, 2, 2>(g, 1, s);

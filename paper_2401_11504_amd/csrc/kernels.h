@@ -24,16 +24,18 @@ struct GemmNT {
     // fp32 partial tiles in `partial` ([n_split][M][N]), does not write C (nor add R), and stores n_split here, so that
     // the consumer can add them up itself instead of a reduce pass; otherwise 0 is stored and C is written.
     int* deferred = nullptr;
-    // With `deferred`: the partial tiles left for the consumer are bf16 (the same [n_split][M][N] layout over the same
-    // scratch, half the bytes written here and read there; each partial is rounded once) instead of fp32.
+    // With `deferred`: the partial tiles left for the consumer may be bf16 (the same [n_split][M][N] layout over the same
+    // scratch, half the bytes written here and read there; each partial is rounded once) instead of fp32; whether they are is
+    // stored in deferred_bf16.
     int partial_bf16 = 0;
+    int* deferred_bf16 = nullptr;
 };
 hipError_t launch_gemm_nt(const GemmNT& g, hipStream_t s);
 // name of the tile configuration launch_gemm_nt picks for g (a static string) and the contraction split it uses
 const char* gemm_nt_plan(const GemmNT& g, int* n_split);
-// N1 > 0: cheaper as two launches, columns [0, N1) and [N1, N) of every batch (see gemm_bf16.hip); 0: one launch
-int gemm_nt_column_split(const GemmNT& g);
-bool gemm_nt_split_columns(const GemmNT& g, GemmNT* a, GemmNT* b);   // the two launches, if N1 > 0
+// cheaper as two launches over two ranges of the columns (of every batch) or rows (see gemm_bf16.hip): they are left in a and b, and
+// g.deferred, if set, receives 0; false: one launch
+bool gemm_nt_two_parts(const GemmNT& g, GemmNT* a, GemmNT* b);
 
 // C[Mo, No] (fp32) = alpha * P[T, Mo]^T Q[T, No]
 struct GemmTN {
@@ -128,7 +130,8 @@ hipError_t launch_embed(const bf16_t* E, const int* tokens, int T, int d, float*
 hipError_t launch_labels(const int* tokens, int T, int* labels, hipStream_t s);
 hipError_t launch_f32_to_bf16(const float* src, bf16_t* dst, size_t n, hipStream_t s);
 hipError_t launch_fill_f32(float* p, size_t n, float value, hipStream_t s);
-hipError_t launch_fill_bf16_zero(bf16_t* p, size_t n, hipStream_t s);
+// rows [0, r0) and [r1, T) of x and y, both [T, d], d a multiple of 4, become zero
+hipError_t launch_zero_rows_around(float* x, bf16_t* y, int T, int d, int r0, int r1, hipStream_t s);
 hipError_t launch_init_normal(float* p, size_t n, float std, uint64_t seed, uint64_t stream_id, hipStream_t s);
 // LoRA dropout: the mask is a function of (key, element index); key from (seed, optimizer step, layer, group)
 uint64_t dropout_key(uint64_t seed, int64_t step, int layer, int group);

@@ -162,7 +162,8 @@ struct tl_lora {
     float* pend_h = nullptr;
     const float* pend_resid = nullptr;
     int pend_T = 0;
-    int loss_row0 = 0;            // first row lm_head and the loss were computed for in the last forward pass
+    int loss_row0 = 0;            // first row lm_head and the loss were computed for in the last forward pass ..
+    int loss_rows = 0;            // .. and how many
     int kv_len = 0;
     // cache reuse (Section 2): with kv_keep the cache lives in buffers of its own ([max_tokens, 3 d] per layer, same
     // q|k|v row layout), so that a module update leaves it in place: decoding then goes on over keys and values that
@@ -216,10 +217,10 @@ static hipError_t timed_gemm_one(tl_lora* L, const GemmNT& g) {
     if (L->prof_on) L->prof_flop += 2.0 * g.M * (double)g.N * ((double)g.K + g.K2) * g.batch;
     return e;
 }
-// as two launches over two column ranges where the tile model finds that cheaper (each is timed as a launch of its own)
+// as two launches over two ranges of columns or rows where the tile model finds that cheaper (each is timed as a launch of its own)
 static hipError_t timed_gemm(tl_lora* L, const GemmNT& g) {
     GemmNT a, b;
-    if (!gemm_nt_split_columns(g, &a, &b)) return timed_gemm_one(L, g);
+    if (!gemm_nt_two_parts(g, &a, &b)) return timed_gemm_one(L, g);
     hipError_t e = timed_gemm_one(L, a);
     return e != hipSuccess ? e : timed_gemm_one(L, b);
 }
@@ -578,10 +579,11 @@ static tl_status flush_pending(tl_lora* L) {
     return TL_OK;
 }
 
-// Partial tiles that a split dX GEMM leaves to the RMSNorm backward: how many, and whether they are bf16.  They are for
-// contractions of whole 64-element tiles (ranks whose G r is a multiple of 64): dX was a bf16 tensor before the reduce pass was
-// folded into the norm, each half is rounded as dX was, and the tiles cost half the bytes on both sides.  Every other
-// contraction was one fp32 sum when that was decided and keeps fp32 partials: halves that cancel lose nothing.
+// Partial tiles that a split dX GEMM leaves to the RMSNorm backward: how many, and whether they are bf16.  They may be for
+// contractions of whole 64-element tiles (ranks whose G r is a multiple of 64) at about 512 to 1280 rows (nt_bf16_parts in
+// gemm_bf16.hip): dX was a bf16 tensor before the reduce pass was folded into the norm, each part is rounded as dX was, and the
+// tiles cost half the bytes on both sides.  Every other contraction was one fp32 sum when that was decided and keeps fp32
+// partials: halves that cancel lose nothing.
 struct DxParts { int n = 0, bf16 = 0; };
 
 // backward: dH = s dY B;  dX = dY W + D o (dH A)  (D = 1 without dropout: then one GEMM with the contraction extended
@@ -612,7 +614,8 @@ static tl_status group_bwd(tl_lora* L, int l, int g, const bf16_t* dY, const bf1
         x.partial = L->partial; x.partial_elems = L->partial_elems;
         if (parts && !L->drop_on) {   // with dropout dX is needed as a whole below
             x.deferred = &parts->n;
-            x.partial_bf16 = parts->bf16 = x.K % 64 == 0 && x.K2 % 64 == 0;
+            x.partial_bf16 = x.K % 64 == 0 && x.K2 % 64 == 0;
+            x.deferred_bf16 = &parts->bf16;
         }
         HIPCHK(timed_gemm(L, x));
         if (L->drop_on) {
@@ -765,8 +768,11 @@ static tl_status forward_loss(tl_lora* L, const int32_t* tokens, int T, int n_ct
     // target on only (with the paper's 1024 + 1024 sample that halves it; with Table 5's short pieces it is most of it)
     const int r0 = first >= 64 ? first : 0;
     L->loss_row0 = r0;
+    // The last position predicts nothing either: it is left out where it would open a row of tiles for itself (a piece of 256
+    // tokens behind a prefix: lm_head 97 -> 74 us, its dX 221 -> 62).  Cross-entropy writes its zeros without reading its logits.
+    L->loss_rows = (T - r0) % 64 == 1 && T - r0 > 1 ? T - r0 - 1 : T - r0;
     GemmNT lg;
-    lg.A = L->hf + (size_t)r0 * d; lg.lda = d; lg.B = m->head; lg.ldb = d; lg.M = T - r0; lg.N = V; lg.K = d;
+    lg.A = L->hf + (size_t)r0 * d; lg.lda = d; lg.B = m->head; lg.ldb = d; lg.M = L->loss_rows; lg.N = V; lg.K = d;
     lg.C = L->logits + (size_t)r0 * V; lg.ldc = V; lg.c_f32 = 1;
     HIPCHK(timed_gemm(L, lg));
     HIPCHK(launch_cross_entropy(L->logits, L->labels, T, V, first, N, L->nll, want_grad ? L->dlogits : nullptr,
@@ -804,14 +810,17 @@ static tl_status update_step(tl_lora* L, const int32_t* tokens, int32_t n_tokens
     // verdict in L->flag, which every AdamW launch below reads before it writes, and the host looks at it once, after
     // the backward pass.
     // backward: lm_head, final norm, layers
-    const int r0 = L->loss_row0;          // rows below it have no loss and hence a zero gradient at the lm_head input
-    if (r0 > 0) HIPCHK(launch_fill_bf16_zero(L->dhf, (size_t)r0 * d, s));
+    const int r0 = L->loss_row0, n_rows = L->loss_rows;       // the other rows have no loss and hence a zero gradient at the final norm
+    DxParts parts;            // fp32 partial tiles, if the product is split: the norm behind it adds them up
     GemmNT dh;
-    dh.A = L->dlogits + (size_t)r0 * V; dh.lda = V; dh.B = m->head_t; dh.ldb = V; dh.M = T - r0; dh.N = d; dh.K = V;
+    dh.A = L->dlogits + (size_t)r0 * V; dh.lda = V; dh.B = m->head_t; dh.ldb = V; dh.M = n_rows; dh.N = d; dh.K = V;
     dh.C = L->dhf + (size_t)r0 * d; dh.ldc = d;
-    dh.partial = L->partial; dh.partial_elems = L->partial_elems;
+    dh.partial = L->partial; dh.partial_elems = L->partial_elems; dh.deferred = &parts.n;
     HIPCHK(timed_gemm(L, dh));
-    HIPCHK(launch_rmsnorm_bwd(L->dhf, L->hs[nl], m->gf, nullptr, T, d, c.rms_eps, L->dhs[nl], L->dh_bf[nl & 1], s));
+    const size_t at = (size_t)r0 * d;
+    HIPCHK(launch_rmsnorm_bwd(L->dhf + at, L->hs[nl] + at, m->gf, nullptr, n_rows, d, c.rms_eps, L->dhs[nl] + at, L->dh_bf[nl & 1] + at, s,
+                              parts.n ? L->partial : nullptr, parts.n, (long)n_rows * d));
+    HIPCHK(launch_zero_rows_around(L->dhs[nl], L->dh_bf[nl & 1], T, d, r0, r0 + n_rows, s));
     // a layer's AdamW step follows its dA / dB launch on the side stream (see layer_backward)
     L->opt_inline = true;
     L->opt_lr = lr;
@@ -1387,8 +1396,8 @@ extern "C" tl_status tl_k_gemm_nt(const uint16_t* A, int32_t lda, const uint16_t
     g.A2 = K2 ? A2 : nullptr; g.lda2 = lda2; g.B2 = K2 ? B2 : nullptr; g.ldb2 = ldb2; g.K2 = K2;
     g.alpha = alpha; g.R = R; g.C = C; g.ldc = ldc; g.c_f32 = c_f32;
     if (workspace && workspace_elems > 0) { g.partial = workspace; g.partial_elems = workspace_elems; }
-    GemmNT ga, gb;   // the same column split as the update path makes
-    if (gemm_nt_split_columns(g, &ga, &gb)) {
+    GemmNT ga, gb;   // the same two ranges as the update path makes
+    if (gemm_nt_two_parts(g, &ga, &gb)) {
         HIPCHK(launch_gemm_nt(ga, (hipStream_t)hip_stream));
         HIPCHK(launch_gemm_nt(gb, (hipStream_t)hip_stream));
         return TL_OK;
@@ -1405,7 +1414,7 @@ extern "C" tl_status tl_k_gemm_nt_plan(int32_t M, int32_t N, int32_t K, int32_t 
     if (workspace_elems > 0) { g.partial = &dummy; g.partial_elems = workspace_elems; }
     GemmNT ga, gb;
     int sp = 1;
-    const bool two = gemm_nt_split_columns(g, &ga, &gb);
+    const bool two = gemm_nt_two_parts(g, &ga, &gb);
     const char* name = gemm_nt_plan(two ? ga : g, &sp);
     snprintf(name_out, name_cap, "%s", name);
     if (n_split_out) *n_split_out = sp;

@@ -61,3 +61,36 @@ def test_undefined_values_beside_the_operands(api, M, N, K, K2, ws, plan):  # no
         api.tl_k_gemm_nt(wide[0][:, :K], wide[1][:, :K], C, wide[2][:, :K2], wide[3][:, :K2], workspace=scratch)
         out.append(C)
     assert torch.isfinite(out[0]).all() and torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+
+
+# contractions split over several workgroups in the two tile shapes that only the model of launch times picks, and products that go
+# out as two launches: over two ranges of rows (the second split) and of columns.  F32_TOL holds up to K = 16384.
+PARTS = [
+    # M, N, K, K2, workspace, plan (of the first launch), launches
+    (300, 1096, 8200, 64, True, ("128x128-split", 8, 1)),
+    (130, 1096, 16320, 64, True, ("128x128-split", 8, 1)),
+    (1000, 2056, 16320, 64, True, ("256x256-split", 4, 1)),
+    (4300, 4104, 8200, 64, True, ("256x256", 1, 2)),
+    (1000, 17000, 4104, 40, False, ("256x256", 1, 2)),
+]
+
+
+@pytest.mark.parametrize("M,N,K,K2,ws,plan", PARTS)
+def test_split_tiles_and_two_launches(api, M, N, K, K2, ws, plan):  # noqa: F811
+    assert api.tl_k_gemm_nt_plan(M, N, K, K2, (1 << 26) if ws else 0) == plan
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    A, B, A2, B2 = (torch.randn(r, c, generator=gen, device="cuda").bfloat16() for r, c in ((M, K), (N, K), (M, K2), (N, K2)))
+    R = torch.randn(M, N, generator=gen, device="cuda")
+    scratch = torch.empty(1 << 26, dtype=torch.float32, device="cuda") if ws else None
+    Cf, Cb = torch.full((M, N), float("nan"), device="cuda"), torch.full((M, N), float("nan"), device="cuda").bfloat16()
+    api.tl_k_gemm_nt(A, B, Cf, A2, B2, alpha=1.0, R=R, workspace=scratch)
+    api.tl_k_gemm_nt(A, B, Cb, A2, B2, alpha=0.5, workspace=scratch)
+    # every row against a sample of columns, the edges of tiles and both ranges among them; and the other way round
+    rows, cols = (sorted({i for i in (0, 127, 128, 255, 256, *seam, n - 1) if i < n} | set(range(0, n, step)))
+                  for n, seam, step in ((M, (4095, 4096), 97), (N, (16383, 16384), 89)))
+    assert max(rows) < M and max(cols) < N
+    full = lambda a, b, a2, b2: (a.double().cpu() @ b.double().cpu().T + a2.double().cpu() @ b2.double().cpu().T).numpy()  # noqa: E731
+    for r, c in ((slice(None), cols), (rows, slice(None))):
+        ref, res = full(A[r], B[c], A2[r], B2[c]), R[r][:, c].cpu().numpy()
+        check(Cf[r][:, c].cpu().numpy() - res, ref, F32_TOL + 2.0 ** -24 * np.abs(res).max() / ref.std(), "C f32 + R")
+        check(Cb[r][:, c].float().cpu().numpy(), 0.5 * ref, BF16_TOL, "C bf16")
