@@ -1166,15 +1166,23 @@ static tl_status factor_span(tl_lora* L, int layer, int proj, int which, size_t 
     return TL_OK;
 }
 
+// n floats to the host, behind everything on the model's stream.  One copy on that stream and one wait: 12.3 us for 16 KB into
+// page-locked memory, where a synchronize and hipMemcpy took 14.9.
+static tl_status copy_out(tl_lora* L, float* host_out, const float* src, size_t n) {
+    hipStream_t s = L->model->stream;
+    hipError_t e = hipMemcpyAsync(host_out, src, n * sizeof(float), hipMemcpyDeviceToHost, s);
+    const hipError_t done = hipStreamSynchronize(s);       // (also after an error: nothing may still write to the caller's memory)
+    HIPCHK(e != hipSuccess ? e : done);
+    return TL_OK;
+}
+
 extern "C" tl_status tl_get_factor(tl_lora* L, int32_t layer, int32_t proj, int32_t which, float* host_out, size_t n) {
     LIVE(L, "tl_get_factor");
     if (!host_out) return fail(TL_ERR_ARG, "host_out is null");
     size_t off = 0;
     TLCHK(factor_span(L, layer, proj, which, n, &off));
     const float* base = which < 2 ? L->P : which < 4 ? L->G : which < 6 ? L->M : L->V;
-    HIPCHK(hipStreamSynchronize(L->model->stream));
-    HIPCHK(hipMemcpy(host_out, base + off, n * sizeof(float), hipMemcpyDeviceToHost));
-    return TL_OK;
+    return copy_out(L, host_out, base + off, n);
 }
 
 extern "C" tl_status tl_set_factor(tl_lora* L, int32_t layer, int32_t proj, int32_t which, const float* host_in,
@@ -1204,9 +1212,7 @@ extern "C" tl_status tl_get_nll(tl_lora* L, float* host_out, size_t n) {
     LIVE(L, "tl_get_nll");
     if (!host_out) return fail(TL_ERR_ARG, "host_out is null");
     if (L->last_tokens <= 0 || n != (size_t)L->last_tokens) return fail(TL_ERR_ARG, "n must equal the last call's n_tokens");
-    HIPCHK(hipStreamSynchronize(L->model->stream));
-    HIPCHK(hipMemcpy(host_out, L->nll, n * sizeof(float), hipMemcpyDeviceToHost));
-    return TL_OK;
+    return copy_out(L, host_out, L->nll, n);
 }
 
 extern "C" tl_status tl_keep_input_grad(tl_lora* L, int32_t on) {
@@ -1223,9 +1229,7 @@ extern "C" tl_status tl_get_dh(tl_lora* L, int32_t boundary, float* host_out, si
     if (!L->have_grads || n != (size_t)L->last_tokens * c.d_model) return fail(TL_ERR_ARG, "n must be n_tokens * d_model of the last update");
     if (boundary == 0 && !L->have_dh0)
         return fail(TL_ERR_ARG, "the gradient at the embedding output was not computed: call tl_keep_input_grad(lora, 1) before the update");
-    HIPCHK(hipStreamSynchronize(L->model->stream));
-    HIPCHK(hipMemcpy(host_out, L->dhs[boundary], n * sizeof(float), hipMemcpyDeviceToHost));
-    return TL_OK;
+    return copy_out(L, host_out, L->dhs[boundary], n);
 }
 
 extern "C" tl_status tl_profile_enable(tl_lora* L, int32_t on) {
