@@ -121,13 +121,13 @@ hipError_t launch_rope(bf16_t* x, long ld, int T, int n_heads, int d_head, float
 hipError_t launch_rope_table(float2* table, int n_pos, int d_head, float base, hipStream_t s);
 hipError_t launch_swiglu_fwd(const bf16_t* gu, int T, int f, bf16_t* a, hipStream_t s);
 hipError_t launch_swiglu_bwd(const bf16_t* da, const bf16_t* gu, int T, int f, bf16_t* dgu, hipStream_t s);
+// labels: one per position, read for target positions only
 hipError_t launch_cross_entropy(const float* logits, const int* labels, int T, int V, int first_target,
                                 int n_targets, float* nll, bf16_t* dlogits, float* loss_sum, hipStream_t s, int row0 = 0,
                                 int* flag = nullptr);
 hipError_t launch_adamw(float* p, const float* g, float* m, float* v, bf16_t* shadow, size_t n, long step, float lr,
                         float beta1, float beta2, float eps, float wd, hipStream_t s, const int* skip_flag = nullptr);
-hipError_t launch_embed(const bf16_t* E, const int* tokens, int T, int d, float* h, hipStream_t s);
-hipError_t launch_labels(const int* tokens, int T, int* labels, hipStream_t s);
+hipError_t launch_embed(const bf16_t* E, const int* tokens, int T, int d, float* h, hipStream_t s, int* tok_out = nullptr);
 hipError_t launch_f32_to_bf16(const float* src, bf16_t* dst, size_t n, hipStream_t s);
 hipError_t launch_fill_f32(float* p, size_t n, float value, hipStream_t s);
 // rows [0, r0) and [r1, T) of x and y, both [T, d], d a multiple of 4, become zero

@@ -142,14 +142,13 @@ struct tl_lora {
     float *logits = nullptr, *nll = nullptr, *loss_sum = nullptr, *dhmid = nullptr, *delta = nullptr,
           *partial = nullptr;
     size_t partial_elems = 0;
-    int *tok = nullptr, *labels = nullptr;
-    int* tok_host = nullptr;      // pinned
-    float* loss_host = nullptr;   // pinned
+    int* tok = nullptr;
+    int* tok_host = nullptr;      // pinned; the embedding kernel reads it there
     // Device-side verdict on the update in flight: bit 0 = the loss is not finite, bit 1 = a dA / dB entry is not finite.
     // The AdamW launches read it and leave the module alone when it is set, so the host can enqueue the whole backward
     // pass without waiting for the loss and still promise that a failed update changes nothing.
-    int* flag = nullptr;
-    int* flag_host = nullptr;     // pinned
+    int* flag = nullptr;          // the word behind loss_sum: both leave in one copy
+    float* verdict_host = nullptr;     // pinned: the sum of the loss, the flag
     // generation side: the key/value cache is the q|k|v buffer the forward pass keeps per layer (rows = positions);
     // kv_len rows are valid.  Any training-side forward overwrites it, which matches the method (the cache is
     // recomputed with the updated module after every chunk update).
@@ -175,8 +174,7 @@ struct tl_lora {
     float* dec_part = nullptr;    // shares of A o (one per head) or A_down act (one per DECODE_SW columns), r each
     float* attn_ws = nullptr;     // partial results of the split decode attention
     size_t attn_ws_elems = 0;
-    int* next_dev = nullptr;
-    int* next_host = nullptr;     // pinned
+    int* next_host = nullptr;     // pinned; the argmax kernel writes it there
     // dA / dB of a layer (one grouped launch) are off the critical path of the backward pass: they run on a second
     // stream (default priority) while the main stream goes on with the layer below.  Everything that launch reads and
     // the layer below would overwrite too early exists twice, indexed by layer parity: dH of each projection group and
@@ -327,12 +325,10 @@ static void lora_release(tl_lora* L) {
     L->prof_on = false;
     L->pool.release();
     if (L->tok_host) (void)hipHostFree(L->tok_host);
-    if (L->loss_host) (void)hipHostFree(L->loss_host);
-    if (L->flag_host) (void)hipHostFree(L->flag_host);
-    L->flag_host = nullptr;
+    if (L->verdict_host) (void)hipHostFree(L->verdict_host);
+    L->verdict_host = nullptr;
     if (L->next_host) (void)hipHostFree(L->next_host);
     L->tok_host = nullptr;
-    L->loss_host = nullptr;
     L->next_host = nullptr;
     L->kv_len = 0;
     L->P = L->G = L->M = L->V = nullptr;
@@ -463,12 +459,11 @@ extern "C" tl_status tl_lora_init(tl_model* m, const tl_lora_cfg* cfg, tl_lora**
         TLCHK(L->pool.alloc(&L->partial, L->partial_elems));
 
         TLCHK(L->pool.alloc(&L->tok, (size_t)Tm));
-        TLCHK(L->pool.alloc(&L->labels, (size_t)Tm));
         TLCHK(L->pool.alloc(&L->nll, (size_t)Tm));
         TLCHK(L->pool.alloc(&L->loss_sum, (size_t)4));
-        TLCHK(L->pool.alloc(&L->flag, (size_t)4));
-        HIPCHK(hipMemsetAsync(L->flag, 0, 4 * sizeof(int), s));
-        HIPCHK(hipHostMalloc((void**)&L->flag_host, 4 * sizeof(int), hipHostMallocDefault));
+        L->flag = (int*)(L->loss_sum + 1);
+        HIPCHK(hipMemsetAsync(L->loss_sum, 0, 4 * sizeof(float), s));
+        HIPCHK(hipHostMalloc((void**)&L->verdict_host, 4 * sizeof(float), hipHostMallocDefault));
         if (V > 0) {
             TLCHK(L->pool.alloc(&L->hf, Td));
             TLCHK(L->pool.alloc(&L->dhf, Td));
@@ -476,14 +471,12 @@ extern "C" tl_status tl_lora_init(tl_model* m, const tl_lora_cfg* cfg, tl_lora**
             TLCHK(L->pool.alloc(&L->dlogits, (size_t)Tm * V));
         }
         HIPCHK(hipHostMalloc((void**)&L->tok_host, (size_t)Tm * sizeof(int), hipHostMallocDefault));
-        HIPCHK(hipHostMalloc((void**)&L->loss_host, 4 * sizeof(float), hipHostMallocDefault));
         HIPCHK(hipHostMalloc((void**)&L->next_host, 4 * sizeof(int), hipHostMallocDefault));
         TLCHK(L->pool.alloc(&L->lora_h, (size_t)3 * r));
         TLCHK(L->pool.alloc(&L->dec_raw, (size_t)std::max(3 * d, 2 * f)));
         TLCHK(L->pool.alloc(&L->dec_part, (size_t)std::max(mc.n_heads, cdiv(f, DECODE_SW)) * r));
         L->attn_ws_elems = (size_t)mc.n_heads * ATTN_DECODE_MAX_SPLIT * (mc.d_head + 2);
         TLCHK(L->pool.alloc(&L->attn_ws, L->attn_ws_elems));
-        TLCHK(L->pool.alloc(&L->next_dev, (size_t)4));
         HIPCHK(hipStreamSynchronize(s));
         return TL_OK;
     };
@@ -764,9 +757,7 @@ static tl_status forward_loss(tl_lora* L, const int32_t* tokens, int T, int n_ct
     if (!L->kv_keep) L->kv_len = 0;   // the forward pass below overwrites the buffers the cache lives in by default
     L->drop_on = want_grad && L->cfg.dropout > 0.f;   // scoring (no gradient) runs the module without dropout
     memcpy(L->tok_host, tokens, (size_t)T * sizeof(int));
-    HIPCHK(hipMemcpyAsync(L->tok, L->tok_host, (size_t)T * sizeof(int), hipMemcpyHostToDevice, s));
-    HIPCHK(launch_labels(L->tok, T, L->labels, s));
-    HIPCHK(launch_embed(m->emb, L->tok, T, d, L->hs[0], s));
+    HIPCHK(launch_embed(m->emb, L->tok_host, T, d, L->hs[0], s, L->tok));
     L->pend_n = 0;
     for (int l = 0; l < c.n_layers; ++l) TLCHK(layer_forward(L, l, L->hs[l], L->hs[l + 1], T));
     TLCHK(norm_fwd(L, L->hs[c.n_layers], m->gf, T, L->hf));
@@ -781,10 +772,16 @@ static tl_status forward_loss(tl_lora* L, const int32_t* tokens, int T, int n_ct
     lg.A = L->hf + (size_t)r0 * d; lg.lda = d; lg.B = m->head; lg.ldb = d; lg.M = L->loss_rows; lg.N = V; lg.K = d;
     lg.C = L->logits + (size_t)r0 * V; lg.ldc = V; lg.c_f32 = 1;
     HIPCHK(timed_gemm(L, lg));
-    HIPCHK(launch_cross_entropy(L->logits, L->labels, T, V, first, N, L->nll, want_grad ? L->dlogits : nullptr,
+    HIPCHK(launch_cross_entropy(L->logits, L->tok + 1, T, V, first, N, L->nll, want_grad ? L->dlogits : nullptr,
                                 L->loss_sum, s, r0, L->flag));
-    HIPCHK(hipMemcpyAsync(L->loss_host, L->loss_sum, sizeof(float), hipMemcpyDeviceToHost, s));
     L->last_tokens = T;
+    return TL_OK;
+}
+
+// loss and status word to the host, behind everything on the stream
+static tl_status read_verdict(tl_lora* L) {
+    HIPCHK(hipMemcpyAsync(L->verdict_host, L->loss_sum, 2 * sizeof(float), hipMemcpyDeviceToHost, L->model->stream));
+    HIPCHK(hipStreamSynchronize(L->model->stream));
     return TL_OK;
 }
 
@@ -795,8 +792,8 @@ extern "C" tl_status tl_chunk_loss(tl_lora* L, const int32_t* tokens, int32_t n_
     TLCHK(check_tokens(L, tokens, n_tokens, n_ctx));
     int N = 0;
     TLCHK(forward_loss(L, tokens, n_tokens, n_ctx, false, &N));
-    HIPCHK(hipStreamSynchronize(L->model->stream));
-    const float loss = L->loss_host[0] / (float)N;
+    TLCHK(read_verdict(L));
+    const float loss = L->verdict_host[0] / (float)N;
     if (!std::isfinite(loss)) return fail(TL_ERR_NONFINITE, "loss is not finite");
     *loss_out = loss;
     if (n_targets_out) *n_targets_out = N;
@@ -844,12 +841,13 @@ static tl_status update_step(tl_lora* L, const int32_t* tokens, int32_t n_tokens
     L->have_grads = true;
     HIPCHK(hipEventRecord(L->ev_opt, L->side));
     HIPCHK(hipStreamWaitEvent(s, L->ev_opt, 0));
-    HIPCHK(hipMemcpyAsync(L->flag_host, L->flag, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    const float loss = L->loss_host[0] / (float)N;
-    if ((L->flag_host[0] & 1) || !std::isfinite(loss))
+    TLCHK(read_verdict(L));
+    const float loss = L->verdict_host[0] / (float)N;
+    int flag;
+    memcpy(&flag, L->verdict_host + 1, sizeof(flag));
+    if ((flag & 1) || !std::isfinite(loss))
         return fail(TL_ERR_NONFINITE, "loss is not finite; optimizer step skipped");
-    if (L->flag_host[0] & 2)
+    if (flag & 2)
         return fail(TL_ERR_NONFINITE, "a LoRA gradient is not finite; the optimizer step of the layer it appeared in and "
                                       "of every layer below was skipped");
     L->step += 1;
@@ -933,8 +931,7 @@ static tl_status emit_next(tl_lora* L, const float* h_last, int32_t* next_token,
     prof_mark(L);
     if (L->prof_on) L->prof_flop += 2.0 * c.vocab * (double)c.d_model;
     HIPCHK(e);
-    HIPCHK(launch_argmax(L->logits, c.vocab, L->next_dev, s));
-    HIPCHK(hipMemcpyAsync(L->next_host, L->next_dev, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(launch_argmax(L->logits, c.vocab, L->next_host, s));
     if (logits_out)
         HIPCHK(hipMemcpyAsync(logits_out, L->logits, (size_t)c.vocab * sizeof(float), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
@@ -960,8 +957,7 @@ extern "C" tl_status tl_prefill(tl_lora* L, const int32_t* tokens, int32_t n_tok
     L->kv_len = 0;
     L->drop_on = false;   // generation runs the module without dropout
     memcpy(L->tok_host, tokens, (size_t)T * sizeof(int));
-    HIPCHK(hipMemcpyAsync(L->tok, L->tok_host, (size_t)T * sizeof(int), hipMemcpyHostToDevice, s));
-    HIPCHK(launch_embed(m->emb, L->tok, T, d, L->hs[0], s));
+    HIPCHK(launch_embed(m->emb, L->tok_host, T, d, L->hs[0], s));
     // the chunk path's forward: it leaves q|k|v (q, k rotated) of every position in save[l].qkv, which is the cache
     L->pend_n = 0;
     for (int l = 0; l < c.n_layers; ++l) TLCHK(layer_forward(L, l, L->hs[l], L->hs[l + 1], T));
@@ -1041,8 +1037,7 @@ extern "C" tl_status tl_decode_step(tl_lora* L, int32_t token, int32_t* next_tok
     hipStream_t s = m->stream;
     const int d = c.d_model, p = L->kv_len;
     L->tok_host[0] = token;
-    HIPCHK(hipMemcpyAsync(L->tok, L->tok_host, sizeof(int), hipMemcpyHostToDevice, s));
-    HIPCHK(launch_embed(m->emb, L->tok, 1, d, L->hs[0], s));
+    HIPCHK(launch_embed(m->emb, L->tok_host, 1, d, L->hs[0], s));
     for (int l = 0; l < c.n_layers; ++l) {
         LayerSave& sv = L->save[l];
         const LayerW& W = m->layers[l];
