@@ -672,7 +672,7 @@ static bool nt_direct_small(const GemmNT& g) { return nt_direct(g) && ((g.K % BK
 enum NtConfig {
     // tiles of 64 contraction elements; A / B tiles in LDS
     NT_128x128,         // 128x128, 4 / 5
-    NT_128x128_SPLIT,   // with the contraction split 2, 4 or 8 ways (partials reduced afterwards or by the consumer)
+    NT_128x128_SPLIT,   // with the contraction split 2 to 8 ways (partials reduced afterwards or by the consumer)
     NT_256x128,         // 256x128, 3 / 4
     NT_256x128_SPLIT,
     NT_256x192,         // 256x192, 2 / 3
@@ -712,7 +712,7 @@ static NtPick pick_nt(const GemmNT& g) {
     for (const NtTile& t : kNtTiles) {
         if (t.bm == 64 && many) continue;
         const long tiles = (long)cdiv(g.M, t.bm) * cdiv(g.N, t.bn) * g.batch;
-        for (int sp = 1; sp <= 8; sp *= 2) {
+        for (int sp = 1; sp <= 8; sp = sp == 2 && t.bn == 256 ? 3 : sp == 3 ? 4 : 2 * sp) {      // (three ways: 80 tiles of 256x256)
             if (sp > 1 && (!may_split || t.cfg_split == t.cfg || nk / sp < 8 || mn * sp > (double)g.partial_elems)) break;
             if (sp > 4 && nt_bf16_parts(g)) break;
             const long n = tiles * sp, rem = n & 255;

@@ -453,7 +453,7 @@ extern "C" tl_status tl_lora_init(tl_model* m, const tl_lora_cfg* cfg, tl_lora**
         // [T, d_model] output (long-K GEMMs with few output tiles)
         {
             const size_t skinny = (size_t)Tm * 3 * r * 16;
-            const size_t wide = (size_t)Tm * d * 4;     // four-way split of a GEMM with d_model output columns
+            const size_t wide = (size_t)Tm * d * (Tm <= 1024 ? 8 : 4);     // a GEMM with d_model output columns split that many ways
             L->partial_elems = skinny > wide ? skinny : wide;
         }
         TLCHK(L->pool.alloc(&L->partial, L->partial_elems));
