@@ -129,6 +129,7 @@ struct tl_lora {
     // During tl_chunk_update the AdamW step of a layer (and the refresh of its transposed shadows) is issued on the side
     // stream right after that layer's dA / dB launch, so it runs under the backward pass of the layers below.
     bool opt_inline = false;
+    bool side_used = false;           // by the update in flight
     float opt_lr = 0.f;
     hipEvent_t ev_opt = nullptr;      // side: every optimizer launch of the update has finished
     // The gradient at the embedding output feeds nothing trainable; an update computes it only on request
@@ -667,6 +668,7 @@ static tl_status wait_tn(tl_lora* L, int par) {
     return TL_OK;
 }
 
+constexpr size_t SIDE_MIN_WORK = (size_t)1 << 20;     // tokens x width of a layer
 // dh_out (fp32) and its bf16 copy dh_out_bf -> dh_in (fp32) and, if dh_in_bf != null, its bf16 copy
 static tl_status layer_backward(tl_lora* L, int l, const float* h_in, const float* dh_out, const bf16_t* dh_out_bf,
                                 float* dh_in, bf16_t* dh_in_bf, int T) {
@@ -699,22 +701,31 @@ static tl_status layer_backward(tl_lora* L, int l, const float* h_in, const floa
     // dh_in == null: the caller does not want the gradient of the layer's input (the bottom layer of an update: it would
     // feed only the frozen embedding), so dX of q|k|v and the first RMSNorm's backward are left out; dA / dB are not
     TLCHK(group_bwd(L, l, G_QKV, L->dqkv, sv.x1, T, dh_in ? L->dx : nullptr, tn, &parts));
-    // all eleven dA / dB products of the layer in one launch on the side stream
+    // All eleven dA / dB products of the layer in one launch.  It goes to the side stream where what follows on the main one is worth
+    // running beside: the layers below, if they have more than SIDE_MIN_WORK to do.  Handing over to another stream and back costs
+    // some 15 us: a layer on its own, and an update of a small decoder, are done sooner one launch after another.
     if (tn.n > TN_GROUP_MAX) return fail(TL_ERR_ARG, "too many products for one grouped launch");
-    HIPCHK(hipEventRecord(L->ev_ready[par], s));
-    HIPCHK(hipStreamWaitEvent(L->side, L->ev_ready[par], 0));
-    HIPCHK(launch_gemm_tn_grouped(tn, L->side));
-    HIPCHK(hipEventRecord(L->ev_done[par], L->side));
-    L->tn_pending[par] = true;
+    const bool aside = L->opt_inline && (size_t)T * d >= SIDE_MIN_WORK;
+    hipStream_t ts = aside ? L->side : s;
+    if (aside) {
+        HIPCHK(hipEventRecord(L->ev_ready[par], s));
+        HIPCHK(hipStreamWaitEvent(L->side, L->ev_ready[par], 0));
+    }
+    HIPCHK(launch_gemm_tn_grouped(tn, ts));
+    if (aside) {
+        HIPCHK(hipEventRecord(L->ev_done[par], L->side));
+        L->tn_pending[par] = true;
+    }
     if (L->opt_inline) {
         // this layer's gradients are complete once that launch is: its AdamW step and the transposed shadows follow on
-        // the side stream (every main-stream kernel that reads the layer's factors was enqueued before ev_ready)
+        // its stream (every main-stream kernel that reads the layer's factors was enqueued before it)
         const size_t off = L->off[l].A[0];
         const size_t end = (l + 1 < c.n_layers) ? L->off[l + 1].A[0] : L->n_params;
         HIPCHK(launch_adamw(L->P + off, L->G + off, L->M + off, L->V + off, L->S + off, end - off, (long)(L->step + 1),
-                            L->opt_lr, L->cfg.beta1, L->cfg.beta2, L->cfg.eps, L->cfg.weight_decay, L->side, L->flag));
+                            L->opt_lr, L->cfg.beta1, L->cfg.beta2, L->cfg.eps, L->cfg.weight_decay, ts, L->flag));
         HIPCHK(launch_transpose_table(L->S, L->ST, L->ttable, L->n_desc, L->layer_tile0[l + 1] - L->layer_tile0[l],
-                                      L->side, L->layer_tile0[l]));
+                                      ts, L->layer_tile0[l]));
+        L->side_used |= aside;
     }
     // dh_in_bf must not be the buffer dh_out_bf (dB of the down projection is still reading it): callers alternate
     if (dh_in)
@@ -826,6 +837,7 @@ static tl_status update_step(tl_lora* L, const int32_t* tokens, int32_t n_tokens
     HIPCHK(launch_zero_rows_around(L->dhs[nl], L->dh_bf[nl & 1], T, d, r0, r0 + n_rows, s));
     // a layer's AdamW step follows its dA / dB launch on the side stream (see layer_backward)
     L->opt_inline = true;
+    L->side_used = false;
     L->opt_lr = lr;
     tl_status bst = TL_OK;
     for (int l = nl - 1; l >= 0 && bst == TL_OK; --l) {
@@ -839,8 +851,10 @@ static tl_status update_step(tl_lora* L, const int32_t* tokens, int32_t n_tokens
     TLCHK(wait_tn(L, 0));
     TLCHK(wait_tn(L, 1));
     L->have_grads = true;
-    HIPCHK(hipEventRecord(L->ev_opt, L->side));
-    HIPCHK(hipStreamWaitEvent(s, L->ev_opt, 0));
+    if (L->side_used) {
+        HIPCHK(hipEventRecord(L->ev_opt, L->side));
+        HIPCHK(hipStreamWaitEvent(s, L->ev_opt, 0));
+    }
     TLCHK(read_verdict(L));
     const float loss = L->verdict_host[0] / (float)N;
     int flag;
