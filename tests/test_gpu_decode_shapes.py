@@ -149,3 +149,17 @@ def test_long_rows_of_one_token(api, H, heads, d_head, d_ffn):  # noqa: F811
     check(got, want, 1e-2, "logits")
     api.tl_lora_free(lora)
     model.close()
+
+
+# more key ranges than fit on the chip at once are made fewer and longer: on both sides of the line, in one and two trips over a range
+@pytest.mark.parametrize("n_keys,heads,dh", [(2048, 32, 128), (2049, 32, 128), (4095, 32, 64), (3000, 40, 64), (1500, 70, 64)])
+def test_attention_in_one_round_of_ranges(api, n_keys, heads, dh):  # noqa: F811
+    gen = torch.Generator(device="cuda").manual_seed(n_keys + heads)
+    kv = torch.randn(n_keys, 2 * heads * dh, generator=gen, device="cuda").bfloat16()
+    q, o = torch.randn(heads * dh, generator=gen, device="cuda").bfloat16(), torch.zeros(heads * dh, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(heads * 32 * (dh + 2), device="cuda")
+    api.tl_k_attention_decode(q, kv[:, :heads * dh], kv[:, heads * dh:], heads, dh, o, workspace=ws)
+    k, v = (x.double().cpu().view(n_keys, heads, dh) for x in (kv[:, :heads * dh], kv[:, heads * dh:]))
+    w = torch.softmax(torch.einsum("khd,hd->hk", k, q.double().cpu().view(heads, dh)) / dh ** 0.5, 1)
+    want = torch.einsum("hk,khd->hd", w, v)
+    check(o.double().cpu().view(heads, dh).numpy(), want.numpy(), BF16_TOL, "o")
