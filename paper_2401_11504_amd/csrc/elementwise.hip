@@ -2,6 +2,7 @@
 // embedding gather, fused softmax cross-entropy, fused AdamW, and layout helpers.
 // Every kernel streams its operands once with 16-byte accesses where the layout allows.
 #include "kernels.h"
+#include "tiles.h"
 
 // ---------------------------------------------------------------- RMSNorm
 // One block per token row.  y = h * rsqrt(mean(h^2) + eps) * g   (Llama2 decoder norm).
@@ -636,19 +637,64 @@ __global__ __launch_bounds__(256) void dropout_fwd_kernel(const bf16_t* __restri
         *(uint4*)(y + i * 8) = pack8(v);
     }
 }
-// dx += D o z   (the low-rank branch's share of the input gradient)
-__global__ __launch_bounds__(256) void dropout_add_kernel(bf16_t* __restrict__ dx, const float* __restrict__ z, size_t n8,
-                                                          uint64_t key, uint32_t thr, float scale) {
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n8; i += stride) {
-        float v[8];
-        unpack8(*(const uint4*)(dx + i * 8), v);
-        const float4 z0 = *(const float4*)(z + i * 8), z1 = *(const float4*)(z + i * 8 + 4);
+// dx += D o (dH A): the low-rank branch's share of the input gradient, one pass over dx.  dH [T, K], AT [d_in, K] (A transposed),
+// K = G r, both with K contiguous.  A wave has 32 rows of 64 columns: its products come out of the matrix unit with a row per lane and
+// are turned around in LDS, so that dx is read (ahead of the products) and written in whole lines.  What it waits for are the
+// fragments, 32 rows of 16 bytes a load, out of L2 (the mask drawn once in the forward pass and read here as bits: 24.3 -> 22.8 us, and as
+// much lost there).  2048 rows, 4096 columns: 24 us; 11008 columns 40; as a product into an fp32 buffer and a pass that added it up 14 + 11.4
+// and 28 + 26, and a launch more.
+__global__ __launch_bounds__(256) void dropout_low_rank_add_kernel(const bf16_t* __restrict__ dH, long ldh, const bf16_t* __restrict__ AT, long lda,
+                                                                   int K, bf16_t* __restrict__ dx, int T, int d_in, uint64_t key, uint32_t thr,
+                                                                   float scale) {
+    constexpr int LDZ = 64 + 4;
+    __shared__ __align__(16) float slab[4][32 * LDZ];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, g = lane >> 5;
+    const int row0 = blockIdx.y * 64 + (wave >> 1) * 32, col0 = blockIdx.x * 128 + (wave & 1) * 64;
+    const int pr = lane >> 3, pc = col0 + (lane & 7) * 8;                // this lane's pieces of eight columns: rows pr, pr + 8, ..
+    uint4 old[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) old[i] = *(const uint4*)(dx + (long)min(row0 + pr + 8 * i, T - 1) * d_in + min(pc, d_in - 8));
+    f32x16_t acc[2] = {zero16(), zero16()};
+    const bf16_t* m = dH + (long)min(row0 + l32, T - 1) * ldh;           // (rows and columns past the end repeat the last and are not stored)
+    const bf16_t* n0 = AT + (long)min(col0 + l32, d_in - 1) * lda;
+    const bf16_t* n1 = AT + (long)min(col0 + 32 + l32, d_in - 1) * lda;
+    for (int k0 = 0; k0 < K; k0 += 64) {
+        bf16x8_t fm[4], f0[4], f1[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = k0 + 16 * u + 8 * g;
+            const uint4 z = make_uint4(0u, 0u, 0u, 0u);
+            const uint4 a = k < K ? *(const uint4*)(m + k) : z, b = k < K ? *(const uint4*)(n0 + k) : z, c = k < K ? *(const uint4*)(n1 + k) : z;
+            fm[u] = *(const bf16x8_t*)&a;
+            f0[u] = *(const bf16x8_t*)&b;
+            f1[u] = *(const bf16x8_t*)&c;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            acc[0] = mfma32(f0[u], fm[u], acc[0]);
+            acc[1] = mfma32(f1[u], fm[u], acc[1]);
+        }
+    }
+    float* z = slab[wave];
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *(float4*)(z + l32 * LDZ + f * 32 + 8 * q + 4 * g) = make_float4(acc[f][4 * q], acc[f][4 * q + 1], acc[f][4 * q + 2], acc[f][4 * q + 3]);
+    __builtin_amdgcn_wave_barrier();                                     // (one wave's LDS operations are in order)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = pr + 8 * i, row = row0 + r;
+        if (row >= T || pc >= d_in) continue;
+        const float4 z0 = *(const float4*)(z + r * LDZ + (lane & 7) * 8), z1 = *(const float4*)(z + r * LDZ + (lane & 7) * 8 + 4);
         const float zz[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
+        const uint64_t at = (uint64_t)row * d_in + pc;
+        float v[8];
+        unpack8(old[i], v);
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-            if (dropout_keep(key, i * 8 + e, thr)) v[e] += zz[e] * scale;
-        *(uint4*)(dx + i * 8) = pack8(v);
+            if (dropout_keep(key, at + e, thr)) v[e] += zz[e] * scale;
+        *(uint4*)(dx + at) = pack8(v);
     }
 }
 static unsigned dropout_blocks(size_t n8) {
@@ -661,10 +707,13 @@ hipError_t launch_dropout_fwd(const bf16_t* x, bf16_t* y, size_t n, uint64_t key
     dropout_fwd_kernel<<<dropout_blocks(n / 8), 256, 0, s>>>(x, y, n / 8, key, dropout_threshold(p), 1.f / (1.f - p));
     return hipGetLastError();
 }
-hipError_t launch_dropout_add(bf16_t* dx, const float* z, size_t n, uint64_t key, float p, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    if ((n & 7) || !(p >= 0.f && p < 1.f)) return hipErrorInvalidValue;
-    dropout_add_kernel<<<dropout_blocks(n / 8), 256, 0, s>>>(dx, z, n / 8, key, dropout_threshold(p), 1.f / (1.f - p));
+hipError_t launch_dropout_low_rank_add(const bf16_t* dH, long ldh, const bf16_t* AT, long lda, int K, bf16_t* dx, int T, int d_in, uint64_t key,
+                                       float p, hipStream_t s) {
+    if (T <= 0 || d_in <= 0) return hipSuccess;
+    if ((d_in & 7) || (K & 7) || K < 0 || (ldh & 7) || (lda & 7) || !(p >= 0.f && p < 1.f)) return hipErrorInvalidValue;
+    if (cdiv(T, 64) > 65535) return hipErrorInvalidValue;
+    dropout_low_rank_add_kernel<<<dim3(cdiv(d_in, 128), cdiv(T, 64)), 256, 0, s>>>(dH, ldh, AT, lda, K, dx, T, d_in, key, dropout_threshold(p),
+                                                                                   1.f / (1.f - p));
     return hipGetLastError();
 }
 

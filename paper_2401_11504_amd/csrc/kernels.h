@@ -136,7 +136,9 @@ hipError_t launch_init_normal(float* p, size_t n, float std, uint64_t seed, uint
 // LoRA dropout: the mask is a function of (key, element index); key from (seed, optimizer step, layer, group)
 uint64_t dropout_key(uint64_t seed, int64_t step, int layer, int group);
 hipError_t launch_dropout_fwd(const bf16_t* x, bf16_t* y, size_t n, uint64_t key, float p, hipStream_t s);
-hipError_t launch_dropout_add(bf16_t* dx, const float* z, size_t n, uint64_t key, float p, hipStream_t s);
+// dx [T, d_in] += D o (dH A), dH [T, K], AT [d_in, K]
+hipError_t launch_dropout_low_rank_add(const bf16_t* dH, long ldh, const bf16_t* AT, long lda, int K, bf16_t* dx, int T, int d_in, uint64_t key,
+                                       float p, hipStream_t s);
 // dst[c, r] = src[r, c] for a [rows, cols] bf16 matrix with row strides lds / ldd
 hipError_t launch_transpose_bf16(const bf16_t* src, long lds, int rows, int cols, bf16_t* dst, long ldd,
                                  hipStream_t s);

@@ -155,7 +155,6 @@ struct tl_lora {
     // recomputed with the updated module after every chunk update).
     // LoRA dropout (training-side forward / backward only): on for the pass in flight?
     bool drop_on = false;
-    float* zdrop = nullptr;       // [max_tokens, max(d_model, d_ffn)] fp32: dH A before the mask is applied
     // A split down-projection GEMM may leave its partial tiles in `partial` for the next RMSNorm, which then also writes
     // the residual stream row (pend_h = pend_resid + sum of pend_n tiles); until then pend_h does not hold its values.
     int pend_n = 0;
@@ -431,7 +430,6 @@ extern "C" tl_status tl_lora_init(tl_model* m, const tl_lora_cfg* cfg, tl_lora**
             if (c.dropout > 0.f)
                 for (int g = 0; g < N_GROUPS; ++g) TLCHK(L->pool.alloc(&sv.xd[g], (size_t)Tm * m->d_in(g)));
         }
-        if (c.dropout > 0.f) TLCHK(L->pool.alloc(&L->zdrop, (size_t)Tm * (d > f ? d : f)));
         TLCHK(L->pool.alloc(&L->dh_bf[0], Td));
         TLCHK(L->pool.alloc(&L->dh_bf[1], Td));
         TLCHK(L->pool.alloc(&L->d_act, (size_t)Tm * f));
@@ -619,12 +617,8 @@ static tl_status group_bwd(tl_lora* L, int l, int g, const bf16_t* dY, const bf1
         }
         HIPCHK(timed_gemm(L, x));
         if (L->drop_on) {
-            GemmNT z;
-            z.A = dH; z.lda = G * r; z.B = L->ST + o.AT[g]; z.ldb = G * r; z.M = T; z.N = din; z.K = G * r;
-            z.C = L->zdrop; z.ldc = din; z.c_f32 = 1;
-            HIPCHK(launch_gemm_nt(z, s));
-            HIPCHK(launch_dropout_add(dX, L->zdrop, (size_t)T * din, dropout_key(L->cfg.seed, L->step, l, g),
-                                      L->cfg.dropout, s));
+            HIPCHK(launch_dropout_low_rank_add(dH, G * r, L->ST + o.AT[g], G * r, G * r, dX, T, din,
+                                               dropout_key(L->cfg.seed, L->step, l, g), L->cfg.dropout, s));
         }
     }
     if (L->drop_on) X = L->save[l].xd[g];                                                  // dA = dH^T (D o X)

@@ -127,3 +127,22 @@ def test_dropout_zero_is_bit_identical_to_the_default_path_and_bad_rates_are_rej
     for h in (la, lb):
         api.tl_lora_free(h)
     model.close()
+
+
+# The low-rank branch's share of the input gradient at the edges of its kernel's tiles (64 rows, 128 columns, 64 of the G r contraction):
+# rows and columns that fill none, contractions of 8 to 600
+@pytest.mark.parametrize("T,heads,d_head,d_ffn,rank", [(33, 2, 64, 1032, 72), (65, 3, 64, 264, 8), (130, 1, 128, 136, 200)])
+def test_input_gradient_at_the_edges_of_its_tiles(api, H, T, heads, d_head, d_ffn, rank):  # noqa: F811
+    shape, seed, p = synth.Shape(1, heads * d_head, heads, d_head, d_ffn, 0, rank, float(rank)), 6200 + T, 0.3
+    model = H.Model(shape, seed, max_tokens=T)
+    lora, facs = H.new_lora(model, seed, b_std=0.05, dropout=p)
+    h, dy = synth.hidden(seed, T, shape.d_model), synth.upstream_grad(seed, T, shape.d_model)
+    h_out, dh_in = torch.zeros(T, shape.d_model, device="cuda"), torch.zeros(T, shape.d_model, device="cuda")
+    api.tl_layer_step(lora, 0, H.to_dev_f32(h), H.to_dev_f32(dy), h_out, dh_in, 0.0, False)
+    W = model.host_layers[0]
+    ref_out, cache = O.layer_fwd(h, W, facs[0], shape, 0, O.layer_dropout((p, seed, 0), shape, 0, T))
+    ref_dh, _ = O.layer_bwd(dy, cache, W, facs[0], shape)
+    check(h_out.cpu().numpy(), ref_out, BF16_TOL, "h_out")
+    check(dh_in.cpu().numpy(), ref_dh, BF16_TOL, "dh_in")
+    api.tl_lora_free(lora)
+    model.close()
