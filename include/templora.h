@@ -330,7 +330,7 @@ tl_status tl_linear_step_static(const float* X, const float* W, const float* A, 
  * A2/B2 may be NULL (K2 = 0).  c_f32 != 0: C and R are fp32, else C is bf16 and R must be NULL.
  * lda/ldb/lda2/ldb2/ldc are row strides in elements; K, K2, lda, ldb, lda2, ldb2 multiples of 8.
  * Tile shape, contraction split and (for many-tile shapes whose last round of workgroups would be poorly filled)
- * a split into two launches over two column ranges are chosen as in the update path.
+ * a split into two launches over two ranges of columns or rows are chosen as in the update path.
  * workspace: NULL, or device fp32 scratch of workspace_elems floats for the partial results of a split contraction
  * (without it no shape is split; a split of s ways uses s * M * N floats; contents are undefined afterwards). */
 tl_status tl_k_gemm_nt(const uint16_t* A, int32_t lda, const uint16_t* B, int32_t ldb, int32_t M, int32_t N,
@@ -338,10 +338,10 @@ tl_status tl_k_gemm_nt(const uint16_t* A, int32_t lda, const uint16_t* B, int32_
                        float alpha, const float* R, void* C, int32_t ldc, int32_t c_f32, float* workspace,
                        size_t workspace_elems, void* hip_stream);
 /* Which tile configuration tl_k_gemm_nt uses for dense operands of these sizes with a workspace of workspace_elems
- * floats (0 = none): its name ("128x128", "256x128", "256x128-split", "256x192", "256x256", "reg-128x128",
- * "reg-128x64", "64x64", "64x64-split", "reg-64x64", "reg-64x64-split") into name_out (host, name_cap bytes), the
- * contraction split and the number of launches (2 = two column ranges; the name is then the first range's).  Host
- * only, nothing is launched: the kernel tests use it to show that their shapes reach every configuration. */
+ * floats (0 = none): its name ("128x128", "128x128-split", "256x128", "256x128-split", "256x192", "256x256",
+ * "256x256-split", "reg-128x128", "reg-128x64", "64x64", "64x64-split", "reg-64x64", "reg-64x64-split") into name_out
+ * (host, name_cap bytes), the contraction split and the number of launches (2 = two ranges of columns or rows; the
+ * name is then the first range's).  Host only, nothing is launched: the kernel tests use it to show that their shapes reach every configuration. */
 tl_status tl_k_gemm_nt_plan(int32_t M, int32_t N, int32_t K, int32_t K2, size_t workspace_elems, char* name_out,
                             size_t name_cap, int32_t* n_split_out, int32_t* n_launches_out);
 
