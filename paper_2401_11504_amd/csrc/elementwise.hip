@@ -79,31 +79,20 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const bf16_t* __restri
                                                           const float* __restrict__ g, const float* __restrict__ dres,
                                                           int d, float eps, float* __restrict__ dh_out,
                                                           bf16_t* __restrict__ dh_bf, const float* __restrict__ dy_part,
-                                                          int n_part, long part_stride, int part_bf16) {
+                                                          int n_part, long part_stride) {
     __shared__ float red[32];
     const long row = blockIdx.x;
-    // chunk i (four elements) of this row of dy: the bf16 array, or the sum of the partial arrays (fp32 or bf16)
+    // chunk i (four elements) of this row of dy: the bf16 array, or the sum of the fp32 partial arrays
     auto dy4 = [&](int i) {
         if (dy_part) {
             float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
             const long at = row * d + 4 * (long)i;
             for (int k = 0; k < n_part; k += 4) {      // four in flight
-                if (part_bf16) {
-                    uint2 r[4];
+                float4 q[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) r[u] = k + u < n_part ? *(const uint2*)((const bf16_t*)dy_part + (long)(k + u) * part_stride + at) : make_uint2(0u, 0u);
+                for (int u = 0; u < 4; ++u) q[u] = k + u < n_part ? *(const float4*)(dy_part + (long)(k + u) * part_stride + at) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        t.x += bf16_to_f32(r[u].x & 0xffff); t.y += bf16_to_f32(r[u].x >> 16);
-                        t.z += bf16_to_f32(r[u].y & 0xffff); t.w += bf16_to_f32(r[u].y >> 16);
-                    }
-                } else {
-                    float4 q[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) q[u] = k + u < n_part ? *(const float4*)(dy_part + (long)(k + u) * part_stride + at) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) { t.x += q[u].x; t.y += q[u].y; t.z += q[u].z; t.w += q[u].w; }
-                }
+                for (int u = 0; u < 4; ++u) { t.x += q[u].x; t.y += q[u].y; t.z += q[u].z; t.w += q[u].w; }
             }
             return t;
         }
@@ -191,12 +180,12 @@ hipError_t launch_rmsnorm_fwd(const float* h, const float* g, int T, int d, floa
 }
 hipError_t launch_rmsnorm_bwd(const bf16_t* dy, const float* h, const float* g, const float* dres, int T, int d,
                               float eps, float* dh_out, bf16_t* dh_bf, hipStream_t s, const float* dy_part, int n_part,
-                              long part_stride, int part_bf16) {
+                              long part_stride) {
     if (T <= 0) return hipSuccess;
     if (dy_part ? (n_part < 1 || (part_stride & 3)) : !dy) return hipErrorInvalidValue;
-    if (d <= 4096) rmsnorm_bwd_kernel<4><<<T, 256, 0, s>>>(dy, h, g, dres, d, eps, dh_out, dh_bf, dy_part, n_part, part_stride, part_bf16);
-    else if (d <= 8192) rmsnorm_bwd_kernel<8><<<T, 256, 0, s>>>(dy, h, g, dres, d, eps, dh_out, dh_bf, dy_part, n_part, part_stride, part_bf16);
-    else rmsnorm_bwd_kernel<0><<<T, 256, 0, s>>>(dy, h, g, dres, d, eps, dh_out, dh_bf, dy_part, n_part, part_stride, part_bf16);
+    if (d <= 4096) rmsnorm_bwd_kernel<4><<<T, 256, 0, s>>>(dy, h, g, dres, d, eps, dh_out, dh_bf, dy_part, n_part, part_stride);
+    else if (d <= 8192) rmsnorm_bwd_kernel<8><<<T, 256, 0, s>>>(dy, h, g, dres, d, eps, dh_out, dh_bf, dy_part, n_part, part_stride);
+    else rmsnorm_bwd_kernel<0><<<T, 256, 0, s>>>(dy, h, g, dres, d, eps, dh_out, dh_bf, dy_part, n_part, part_stride);
     return hipGetLastError();
 }
 

@@ -452,9 +452,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
     const int row0 = m0 + wm * TM, col0 = n0 + wn * TN;
     const bool whole = m0 + BM <= p.M && n0 + BN <= p.N;       // workgroup-uniform: no bounds checks
     constexpr int LDS_BYTES = AST * A_STAGE + BST * B_STAGE;
-    bool bf16_out = !p.c_f32;
-    if constexpr (SPLITK) bf16_out = p.partial_bf16 != 0;
-    if (!bf16_out) {
+    if (SPLITK || p.c_f32) {
         // fp32: each split stores its raw tile (splitk_reduce_kernel or the consumer adds the splits in index order
         // afterwards: device-wide fences inside a kernel cost a full L2 write-back on this chip), or C = alpha acc (+ R)
         constexpr int SLD = TN + 4, CPR = TN / 4;
@@ -517,19 +515,13 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
             __builtin_amdgcn_wave_barrier();
         }
     } else {
-        // bf16: C = alpha acc, or (a split whose consumer adds the tiles up itself and asked for bf16 ones) this split's
-        // tile, unscaled, in its [M, N] slice of the scratch
+        // bf16: C = alpha acc
         constexpr int SLD = TN + 8, CPR = TN / 8;
         static_assert(4 * TM * SLD * 2 <= LDS_BYTES, "the output slab fits");
         bf16_t* slab = (bf16_t*)smem + wave * TM * SLD;
         bf16_t* C = (bf16_t*)p.C + (long)z * p.bC;
-        long ldc = p.ldc;
-        float alpha = p.alpha;
-        if constexpr (SPLITK) {
-            C = (bf16_t*)p.partial + ((long)z * n_split + split) * (long)p.M * p.N;
-            ldc = p.N;
-            alpha = 1.f;
-        }
+        const long ldc = p.ldc;
+        const float alpha = p.alpha;
         const bool vec = (ldc & 7) == 0 && ((size_t)C & 15) == 0;
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
@@ -567,12 +559,6 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_dl_kernel(GemmNT p, NtMap map)
     }
 }
 
-// bf16 partial tiles where the reduce is left to a consumer that takes them, and only for products that 128x128 tiles fill half the
-// chip with and 256x128 tiles do not fill three quarters of: more rows than that were one fp32 sum when such tiles were introduced,
-// fewer have more splits, and fp32 partials cost both little beside what the split gains them.
-static bool nt_bf16_parts(const GemmNT& g) {
-    return g.partial_bf16 && (long)cdiv(g.M, 128) * cdiv(g.N, 128) * g.batch >= 128 && (long)cdiv(g.M, 256) * cdiv(g.N, 128) * g.batch < 192;
-}
 template <int BM, int BN, int AST, bool SPLITK>
 static hipError_t run_nt_dl(const GemmNT& g, hipStream_t s, int n_split = 1) {
     const int tiles_m = cdiv(g.M, BM), tiles_n = cdiv(g.N, BN);
@@ -581,13 +567,10 @@ static hipError_t run_nt_dl(const GemmNT& g, hipStream_t s, int n_split = 1) {
     auto kern = gemm_nt_dl_kernel<BM, BN, AST, SPLITK>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    GemmNT gk = g;
     const bool defer = SPLITK && g.deferred;                         // the consumer adds the partial tiles up
-    gk.partial_bf16 = defer && nt_bf16_parts(g);
-    kern<<<grid, 256, lds, s>>>(gk, make_nt_map(tiles_m, tiles_n, SPLITK ? n_split : 1, g.batch, SPLITK));
+    kern<<<grid, 256, lds, s>>>(g, make_nt_map(tiles_m, tiles_n, SPLITK ? n_split : 1, g.batch, SPLITK));
     if (defer) {
         *g.deferred = n_split;
-        if (g.deferred_bf16) *g.deferred_bf16 = gk.partial_bf16;
     } else if (SPLITK) {
         const long n = (long)g.M * (g.N >> 2) * g.batch;
         splitk_reduce_kernel<<<cdiv(n, 256), 256, 0, s>>>(g, n_split);
@@ -706,7 +689,7 @@ static NtPick pick_nt(const GemmNT& g) {
     const bool many = (long)cdiv(g.M, 128) * cdiv(g.N, 128) * g.batch >= 128;      // (64x64 tiles: where 128x128 leave half the CUs idle)
     // the pass over the partial tiles of a split: a reduce launch that reads them and writes C (6.3 us and 1.4 us a million values),
     // or, when the consumer adds them up itself (g.deferred), the extra bytes written here and read there
-    const double pass0 = g.deferred ? 0.0 : 6.3, pass1 = g.deferred ? (nt_bf16_parts(g) ? 0.55e-6 : 1.1e-6) : 1.41e-6;
+    const double pass0 = g.deferred ? 0.0 : 6.3, pass1 = g.deferred ? 1.1e-6 : 1.41e-6;
     const bool may_split = g.split_k == 0 && g.partial && !(g.N & 3);
     NtPick whole = {NT_SKINNY, 1, 1e30}, split = {NT_SKINNY, 8, 1e30};
     for (const NtTile& t : kNtTiles) {
@@ -714,7 +697,6 @@ static NtPick pick_nt(const GemmNT& g) {
         const long tiles = (long)cdiv(g.M, t.bm) * cdiv(g.N, t.bn) * g.batch;
         for (int sp = 1; sp <= 8; sp = sp == 2 && t.bn == 256 ? 3 : sp == 3 ? 4 : 2 * sp) {      // (three ways: 80 tiles of 256x256)
             if (sp > 1 && (!may_split || t.cfg_split == t.cfg || nk / sp < 8 || mn * sp > (double)g.partial_elems)) break;
-            if (sp > 4 && nt_bf16_parts(g)) break;
             const long n = tiles * sp, rem = n & 255;
             double us = (double)(n >> 8) * t.k_full;
             if (rem) us += t.k_min + (t.k_full - t.k_min) * rem * (1.0 / 256);
@@ -767,7 +749,6 @@ bool gemm_nt_two_parts(const GemmNT& g, GemmNT* a, GemmNT* b) {
     GemmNT h = g;
     double best = 0.96 * pick_nt(h).us;
     h.deferred = nullptr;
-    h.partial_bf16 = 0;
     int rows = 0, cols = 0;
     for (const NtTile& t : kNtTiles) {
         if (t.bm < 256) continue;

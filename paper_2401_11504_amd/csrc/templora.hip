@@ -576,20 +576,13 @@ static tl_status flush_pending(tl_lora* L) {
     return TL_OK;
 }
 
-// Partial tiles that a split dX GEMM leaves to the RMSNorm backward: how many, and whether they are bf16.  They may be for
-// contractions of whole 64-element tiles (ranks whose G r is a multiple of 64) at about 512 to 1280 rows (nt_bf16_parts in
-// gemm_bf16.hip): dX was a bf16 tensor before the reduce pass was folded into the norm, each part is rounded as dX was, and the
-// tiles cost half the bytes on both sides.  Every other contraction was one fp32 sum when that was decided and keeps fp32
-// partials: halves that cancel lose nothing.
-struct DxParts { int n = 0, bf16 = 0; };
-
 // backward: dH = s dY B;  dX = dY W + D o (dH A)  (D = 1 without dropout: then one GEMM with the contraction extended
 // by dH | A);  the products dA = dH^T X and dB = dY^T Hs are appended to `tn`, which
 // the caller launches once per layer (dY, dH, X and Hs must stay untouched until then).
 // parts (may be null): where the dX GEMM may report that it left split partial tiles in L->partial instead of
-// writing dX (see GemmNT::deferred); the caller's next kernel then adds them up.
+// writing dX (see GemmNT::deferred); the caller's next kernel then adds them up.  They are fp32: parts that cancel lose nothing.
 static tl_status group_bwd(tl_lora* L, int l, int g, const bf16_t* dY, const bf16_t* X, int T, bf16_t* dX,
-                           GemmTNGroup& tn, DxParts* parts = nullptr) {
+                           GemmTNGroup& tn, int* parts = nullptr) {
     tl_model* m = L->model;
     hipStream_t s = m->stream;
     const int G = kGroupCount[g], din = m->d_in(g), dout = m->d_out(g), r = L->cfg.rank;
@@ -610,11 +603,7 @@ static tl_status group_bwd(tl_lora* L, int l, int g, const bf16_t* dY, const bf1
         if (!L->drop_on) { x.A2 = dH; x.lda2 = G * r; x.B2 = L->ST + o.AT[g]; x.ldb2 = G * r; x.K2 = G * r; }
         x.C = dX; x.ldc = din;
         x.partial = L->partial; x.partial_elems = L->partial_elems;
-        if (parts && !L->drop_on) {   // with dropout dX is needed as a whole below
-            x.deferred = &parts->n;
-            x.partial_bf16 = x.K % 64 == 0 && x.K2 % 64 == 0;
-            x.deferred_bf16 = &parts->bf16;
-        }
+        if (!L->drop_on) x.deferred = parts;   // with dropout dX is needed as a whole below
         HIPCHK(timed_gemm(L, x));
         if (L->drop_on) {
             HIPCHK(launch_dropout_low_rank_add(dH, G * r, L->ST + o.AT[g], G * r, G * r, dX, T, din,
@@ -683,15 +672,15 @@ static tl_status layer_backward(tl_lora* L, int l, const float* h_in, const floa
     HIPCHK(launch_swiglu_bwd(L->d_act, sv.gu, T, f, L->dgu, s));
     // the two dX GEMMs that feed an RMSNorm backward have a long contraction and may be split: the norm kernel then
     // adds the partial tiles up itself (no reduce launch, no bf16 round trip of dX)
-    DxParts parts;
+    int parts = 0;
     TLCHK(group_bwd(L, l, G_GU, L->dgu, sv.x2, T, L->dx, tn, &parts));
     HIPCHK(launch_rmsnorm_bwd(L->dx, sv.hmid, W.g2, dh_out, T, d, c.rms_eps, L->dhmid, L->dhmid_bf, s,
-                              parts.n ? L->partial : nullptr, parts.n, (long)T * d, parts.bf16));
+                              parts ? L->partial : nullptr, parts, (long)T * d));
     TLCHK(group_bwd(L, l, G_O, L->dhmid_bf, sv.o, T, L->d_o, tn));
     // one launch for every dQ and dK/dV part, longest first (dq, dk rotated back inside): 120 -> 84 us per layer at 1024 tokens
     HIPCHK(launch_attention_bwd(sv.qkv, sv.qkv + d, sv.qkv + 2 * d, sv.o, L->d_o, sv.lse, 3L * d, d, T, c.n_heads,
                                 c.d_head, L->dqkv, L->dqkv + d, L->dqkv + 2 * d, L->delta, m->rope, s));
-    parts = DxParts();
+    parts = 0;
     // dh_in == null: the caller does not want the gradient of the layer's input (the bottom layer of an update: it would
     // feed only the frozen embedding), so dX of q|k|v and the first RMSNorm's backward are left out; dA / dB are not
     TLCHK(group_bwd(L, l, G_QKV, L->dqkv, sv.x1, T, dh_in ? L->dx : nullptr, tn, &parts));
@@ -724,7 +713,7 @@ static tl_status layer_backward(tl_lora* L, int l, const float* h_in, const floa
     // dh_in_bf must not be the buffer dh_out_bf (dB of the down projection is still reading it): callers alternate
     if (dh_in)
         HIPCHK(launch_rmsnorm_bwd(L->dx, h_in, W.g1, L->dhmid, T, d, c.rms_eps, dh_in, dh_in_bf, s,
-                                  parts.n ? L->partial : nullptr, parts.n, (long)T * d, parts.bf16));
+                                  parts ? L->partial : nullptr, parts, (long)T * d));
     return TL_OK;
 }
 
@@ -819,15 +808,15 @@ static tl_status update_step(tl_lora* L, const int32_t* tokens, int32_t n_tokens
     // the backward pass.
     // backward: lm_head, final norm, layers
     const int r0 = L->loss_row0, n_rows = L->loss_rows;       // the other rows have no loss and hence a zero gradient at the final norm
-    DxParts parts;            // fp32 partial tiles, if the product is split: the norm behind it adds them up
+    int parts = 0;            // fp32 partial tiles, if the product is split: the norm behind it adds them up
     GemmNT dh;
     dh.A = L->dlogits + (size_t)r0 * V; dh.lda = V; dh.B = m->head_t; dh.ldb = V; dh.M = n_rows; dh.N = d; dh.K = V;
     dh.C = L->dhf + (size_t)r0 * d; dh.ldc = d;
-    dh.partial = L->partial; dh.partial_elems = L->partial_elems; dh.deferred = &parts.n;
+    dh.partial = L->partial; dh.partial_elems = L->partial_elems; dh.deferred = &parts;
     HIPCHK(timed_gemm(L, dh));
     const size_t at = (size_t)r0 * d;
     HIPCHK(launch_rmsnorm_bwd(L->dhf + at, L->hs[nl] + at, m->gf, nullptr, n_rows, d, c.rms_eps, L->dhs[nl] + at, L->dh_bf[nl & 1] + at, s,
-                              parts.n ? L->partial : nullptr, parts.n, (long)n_rows * d));
+                              parts ? L->partial : nullptr, parts, (long)n_rows * d));
     HIPCHK(launch_zero_rows_around(L->dhs[nl], L->dh_bf[nl & 1], T, d, r0, r0 + n_rows, s));
     // a layer's AdamW step follows its dA / dB launch on the side stream (see layer_backward)
     L->opt_inline = true;

@@ -1,5 +1,5 @@
-"""The input gradient of gate|up at ranks that are no multiple of 64: its sum is kept in fp32 wherever the contraction is
-cut.  The case is built so that the gate half and the up half of the sum are large and nearly cancel: partial sums rounded to
+"""The input gradient of gate|up, at ranks that are multiples of 64 with the contraction of the low-rank pair (2 r) and at others:
+its sum is kept in fp32 wherever the contraction is cut.  The case is built so that the gate half and the up half of the sum are large and nearly cancel: partial sums rounded to
 bf16 leave an error of the size of the halves.  Reference: fp64 from the same bf16 operands."""
 import numpy as np
 import pytest
@@ -17,7 +17,7 @@ G = -2.2178     # silu(g) + g silu'(g) = 0 here: with u = -g the two halves are 
 TOL = 1e-4
 
 
-@pytest.mark.parametrize("rank", [8, 16, 40])
+@pytest.mark.parametrize("rank", [8, 16, 32, 40, 64])
 def test_gate_up_input_gradient_is_summed_in_fp32(api, H, rank):  # noqa: F811
     assert api.tl_k_gemm_nt_plan(T, D, 2 * F, 2 * rank, 1 << 28)[:2] == ("256x128-split", 4)
     rng = np.random.default_rng(rank)
