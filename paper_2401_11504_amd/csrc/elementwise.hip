@@ -627,44 +627,58 @@ __global__ __launch_bounds__(256) void dropout_fwd_kernel(const bf16_t* __restri
     }
 }
 // dx += D o (dH A): the low-rank branch's share of the input gradient, one pass over dx.  dH [T, K], AT [d_in, K] (A transposed),
-// K = G r, both with K contiguous.  A wave has 32 rows of 64 columns: its products come out of the matrix unit with a row per lane and
-// are turned around in LDS, so that dx is read (ahead of the products) and written in whole lines.  What it waits for are the
-// fragments, 32 rows of 16 bytes a load, out of L2 (the mask drawn once in the forward pass and read here as bits: 24.3 -> 22.8 us, and as
-// much lost there).  2048 rows, 4096 columns: 24 us; 11008 columns 40; as a product into an fp32 buffer and a pass that added it up 14 + 11.4
-// and 28 + 26, and a launch more.
+// K = G r, both with K contiguous.  A workgroup has 64 rows of 128 columns, a wave 32 of 64: 64 contraction elements of both operands
+// at a time go through LDS in whole lines, the next ones on their way in registers meanwhile; the products are turned around in LDS as
+// well, so that dx is read (behind the first operands, ahead of the products) and written in whole lines.
+// 2048 rows, us (beside them a product into an fp32 buffer and a pass that added it up, a launch more): 4096 columns, K 64 11.9 (22.6),
+// K 192 15.5 (24.1), K 768 28.5 (31.0); 11008 columns, K 64 26.1 (50.9).  At K 64 it is bound by dx, 2.8 to 3.5 TB/s in and out, at
+// K 768 by the operands out of L2.  Fragments straight from memory, 32 rows of 16 bytes a load: 14.0, 25.0, 72.7 and 29.8.
 __global__ __launch_bounds__(256) void dropout_low_rank_add_kernel(const bf16_t* __restrict__ dH, long ldh, const bf16_t* __restrict__ AT, long lda,
                                                                    int K, bf16_t* __restrict__ dx, int T, int d_in, uint64_t key, uint32_t thr,
                                                                    float scale) {
-    constexpr int LDZ = 64 + 4;
-    __shared__ __align__(16) float slab[4][32 * LDZ];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, g = lane >> 5;
-    const int row0 = blockIdx.y * 64 + (wave >> 1) * 32, col0 = blockIdx.x * 128 + (wave & 1) * 64;
-    const int pr = lane >> 3, pc = col0 + (lane & 7) * 8;                // this lane's pieces of eight columns: rows pr, pr + 8, ..
+    constexpr int BM = 64, BN = 128, LDO = 64 + 8, LDZ = 64 + 4;         // (144-byte rows: sixteen lanes' pieces lie in sixty-four banks)
+    constexpr int NP = (BM + BN) * 8 / 256, NM = BM * 8 / 256;           // a thread's pieces of eight elements, those of dH first
+    __shared__ __align__(16) unsigned char smem[4 * 32 * LDZ * sizeof(float)];
+    static_assert((BM + BN) * LDO * sizeof(bf16_t) <= sizeof(smem), "the operands fit");
+    bf16_t* ops = (bf16_t*)smem;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, g = lane >> 5;
+    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN, wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
+    const bf16_t* src[NP];                                               // (rows and columns past the end repeat the last and are not stored)
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const int r = (tid >> 3) + 32 * j;
+        src[j] = j < NM ? dH + (long)min(m0 + r, T - 1) * ldh : AT + (long)min(n0 + r - BM, d_in - 1) * lda;
+    }
+    uint4 st[NP];
+    auto fetch = [&](int k0) {
+        const int at = min(k0 + 8 * (tid & 7), K - 8);
+#pragma unroll
+        for (int j = 0; j < NP; ++j) st[j] = *(const uint4*)(src[j] + at);
+    };
+    if (K > 0) fetch(0);
+    const int pr = m0 + wm + (lane >> 3), pc = n0 + wn + (lane & 7) * 8;  // this lane's pieces of eight columns of dx: rows pr, pr + 8, ..
     uint4 old[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) old[i] = *(const uint4*)(dx + (long)min(row0 + pr + 8 * i, T - 1) * d_in + min(pc, d_in - 8));
+    for (int i = 0; i < 4; ++i) old[i] = *(const uint4*)(dx + (long)min(pr + 8 * i, T - 1) * d_in + min(pc, d_in - 8));
     f32x16_t acc[2] = {zero16(), zero16()};
-    const bf16_t* m = dH + (long)min(row0 + l32, T - 1) * ldh;           // (rows and columns past the end repeat the last and are not stored)
-    const bf16_t* n0 = AT + (long)min(col0 + l32, d_in - 1) * lda;
-    const bf16_t* n1 = AT + (long)min(col0 + 32 + l32, d_in - 1) * lda;
     for (int k0 = 0; k0 < K; k0 += 64) {
-        bf16x8_t fm[4], f0[4], f1[4];
+        if (k0) __syncthreads();
+        const uint32_t in = k0 + 8 * (tid & 7) < K ? ~0u : 0u;           // (zeros behind the contraction's end: a choice between two
+#pragma unroll                                                           //  addresses would go through scratch memory)
+        for (int j = 0; j < NP; ++j)
+            *(uint4*)(ops + ((tid >> 3) + 32 * j) * LDO + (tid & 7) * 8) = make_uint4(st[j].x & in, st[j].y & in, st[j].z & in, st[j].w & in);
+        __syncthreads();
+        if (k0 + 64 < K) fetch(k0 + 64);
+        const bf16_t *m = ops + (wm + l32) * LDO + 8 * g, *n = ops + (BM + wn + l32) * LDO + 8 * g;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int k = k0 + 16 * u + 8 * g;
-            const uint4 z = make_uint4(0u, 0u, 0u, 0u);
-            const uint4 a = k < K ? *(const uint4*)(m + k) : z, b = k < K ? *(const uint4*)(n0 + k) : z, c = k < K ? *(const uint4*)(n1 + k) : z;
-            fm[u] = *(const bf16x8_t*)&a;
-            f0[u] = *(const bf16x8_t*)&b;
-            f1[u] = *(const bf16x8_t*)&c;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            acc[0] = mfma32(f0[u], fm[u], acc[0]);
-            acc[1] = mfma32(f1[u], fm[u], acc[1]);
+            const bf16x8_t fm = *(const bf16x8_t*)(m + 16 * u);
+            acc[0] = mfma32(*(const bf16x8_t*)(n + 16 * u), fm, acc[0]);
+            acc[1] = mfma32(*(const bf16x8_t*)(n + 32 * LDO + 16 * u), fm, acc[1]);
         }
     }
-    float* z = slab[wave];
+    __syncthreads();                                                     // every wave is done reading operands
+    float* z = (float*)smem + wave * 32 * LDZ;
 #pragma unroll
     for (int f = 0; f < 2; ++f)
 #pragma unroll
@@ -673,9 +687,10 @@ __global__ __launch_bounds__(256) void dropout_low_rank_add_kernel(const bf16_t*
     __builtin_amdgcn_wave_barrier();                                     // (one wave's LDS operations are in order)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int r = pr + 8 * i, row = row0 + r;
+        const int row = pr + 8 * i;
         if (row >= T || pc >= d_in) continue;
-        const float4 z0 = *(const float4*)(z + r * LDZ + (lane & 7) * 8), z1 = *(const float4*)(z + r * LDZ + (lane & 7) * 8 + 4);
+        const float* zr = z + ((lane >> 3) + 8 * i) * LDZ + (lane & 7) * 8;
+        const float4 z0 = *(const float4*)zr, z1 = *(const float4*)(zr + 4);
         const float zz[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
         const uint64_t at = (uint64_t)row * d_in + pc;
         float v[8];

@@ -130,8 +130,8 @@ def test_dropout_zero_is_bit_identical_to_the_default_path_and_bad_rates_are_rej
 
 
 # The low-rank branch's share of the input gradient at the edges of its kernel's tiles (64 rows, 128 columns, 64 of the G r contraction):
-# rows and columns that fill none, contractions of 8 to 600
-@pytest.mark.parametrize("T,heads,d_head,d_ffn,rank", [(33, 2, 64, 1032, 72), (65, 3, 64, 264, 8), (130, 1, 128, 136, 200)])
+# rows and columns that fill none, contractions of 8 to 768
+@pytest.mark.parametrize("T,heads,d_head,d_ffn,rank", [(33, 2, 64, 1032, 72), (65, 3, 64, 264, 8), (130, 1, 128, 136, 200), (97, 2, 64, 264, 256)])
 def test_input_gradient_at_the_edges_of_its_tiles(api, H, T, heads, d_head, d_ffn, rank):  # noqa: F811
     shape, seed, p = synth.Shape(1, heads * d_head, heads, d_head, d_ffn, 0, rank, float(rank)), 6200 + T, 0.3
     model = H.Model(shape, seed, max_tokens=T)
