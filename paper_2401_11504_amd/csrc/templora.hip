@@ -129,7 +129,7 @@ struct tl_lora {
     // During tl_chunk_update the AdamW step of a layer (and the refresh of its transposed shadows) is issued on the side
     // stream right after that layer's dA / dB launch, so it runs under the backward pass of the layers below.
     bool opt_inline = false;
-    bool side_used = false;           // by the update in flight
+    bool side_used = false;           // optimizer launches that the main stream has not waited for
     float opt_lr = 0.f;
     hipEvent_t ev_opt = nullptr;      // side: every optimizer launch of the update has finished
     // The gradient at the embedding output feeds nothing trainable; an update computes it only on request
@@ -651,6 +651,22 @@ static tl_status wait_tn(tl_lora* L, int par) {
     return TL_OK;
 }
 
+// main stream: wait until every optimizer launch on the side stream has finished
+static tl_status join_side(tl_lora* L) {
+    if (L->side_used) {
+        HIPCHK(hipEventRecord(L->ev_opt, L->side));
+        HIPCHK(hipStreamWaitEvent(L->model->stream, L->ev_opt, 0));
+        L->side_used = false;
+    }
+    return TL_OK;
+}
+
+// Where dA, dB, AdamW and the shadows of a layer run.  Beside the backward pass of the layer below they are hidden in part, but handing
+// over to another stream and back costs some 15 us.  Updates, us, on the main stream / on the side stream in all layers but the bottom
+// one / in all of them.  Four layers of width 4096 (rank 64): 64 tokens 1704, 1793, 1826; 128 tokens 1884, 1916, 1944; 255 tokens 2243,
+// 2252, 2283; 1024 tokens 4274, 4240, 4254; 2048 tokens 7858, 7775, 7775; 24 layers, 256 tokens 12886, 12858, 12896; 1024 tokens 25282,
+// 24886, 24903.  Width 2048: 500 tokens 1597, 1624, 1640; eight layers, 2048 tokens 6617, 6543, 6542.  One layer of width 4096, 1024 tokens:
+// 1161 on the main stream, 1195 beside it.
 constexpr size_t SIDE_MIN_WORK = (size_t)1 << 20;     // tokens x width of a layer
 // dh_out (fp32) and its bf16 copy dh_out_bf -> dh_in (fp32) and, if dh_in_bf != null, its bf16 copy
 static tl_status layer_backward(tl_lora* L, int l, const float* h_in, const float* dh_out, const bf16_t* dh_out_bf,
@@ -684,11 +700,12 @@ static tl_status layer_backward(tl_lora* L, int l, const float* h_in, const floa
     // dh_in == null: the caller does not want the gradient of the layer's input (the bottom layer of an update: it would
     // feed only the frozen embedding), so dX of q|k|v and the first RMSNorm's backward are left out; dA / dB are not
     TLCHK(group_bwd(L, l, G_QKV, L->dqkv, sv.x1, T, dh_in ? L->dx : nullptr, tn, &parts));
-    // All eleven dA / dB products of the layer in one launch.  It goes to the side stream where what follows on the main one is worth
-    // running beside: the layers below, if they have more than SIDE_MIN_WORK to do.  Handing over to another stream and back costs
-    // some 15 us: a layer on its own, and an update of a small decoder, are done sooner one launch after another.
+    // All eleven dA / dB products of the layer in one launch, aside where a layer below and enough work follow on the main stream.  What
+    // does not go there waits for what did: the products leave their verdict in L->flag, which the AdamW steps of the layers above must
+    // not see.
     if (tn.n > TN_GROUP_MAX) return fail(TL_ERR_ARG, "too many products for one grouped launch");
-    const bool aside = L->opt_inline && (size_t)T * d >= SIDE_MIN_WORK;
+    const bool aside = L->opt_inline && l > 0 && (size_t)T * d >= SIDE_MIN_WORK;
+    if (!aside) TLCHK(join_side(L));
     hipStream_t ts = aside ? L->side : s;
     if (aside) {
         HIPCHK(hipEventRecord(L->ev_ready[par], s));
@@ -820,7 +837,6 @@ static tl_status update_step(tl_lora* L, const int32_t* tokens, int32_t n_tokens
     HIPCHK(launch_zero_rows_around(L->dhs[nl], L->dh_bf[nl & 1], T, d, r0, r0 + n_rows, s));
     // a layer's AdamW step follows its dA / dB launch on the side stream (see layer_backward)
     L->opt_inline = true;
-    L->side_used = false;
     L->opt_lr = lr;
     tl_status bst = TL_OK;
     for (int l = nl - 1; l >= 0 && bst == TL_OK; --l) {
@@ -834,10 +850,7 @@ static tl_status update_step(tl_lora* L, const int32_t* tokens, int32_t n_tokens
     TLCHK(wait_tn(L, 0));
     TLCHK(wait_tn(L, 1));
     L->have_grads = true;
-    if (L->side_used) {
-        HIPCHK(hipEventRecord(L->ev_opt, L->side));
-        HIPCHK(hipStreamWaitEvent(s, L->ev_opt, 0));
-    }
+    TLCHK(join_side(L));
     TLCHK(read_verdict(L));
     const float loss = L->verdict_host[0] / (float)N;
     int flag;
