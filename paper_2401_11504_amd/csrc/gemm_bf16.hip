@@ -695,9 +695,13 @@ static NtPick pick_nt(const GemmNT& g) {
     for (const NtTile& t : kNtTiles) {
         if (t.bm == 64 && many) continue;
         const long tiles = (long)cdiv(g.M, t.bm) * cdiv(g.N, t.bn) * g.batch;
-        for (int sp = 1; sp <= 8; sp = sp == 2 && t.bn == 256 ? 3 : sp == 3 ? 4 : 2 * sp) {      // (three ways: 80 tiles of 256x256)
+        for (int sp = 1; sp <= 8; sp = sp == 2 ? 3 : sp == 3 ? 4 : 2 * sp) {
             if (sp > 1 && (!may_split || t.cfg_split == t.cfg || nk / sp < 8 || mn * sp > (double)g.partial_elems)) break;
             const long n = tiles * sp, rem = n & 255;
+            // Three ways: for the 72 to 85 tiles that two leave a third of the chip idle on and four need two rounds for.  us without and
+            // with them in 128x128 and 256x128 tiles: 2048 x 11264 at 1280 rows 71 and 64, 2560 x 13824 at 1024 82 and 73, 3072 x 8192 at 700 60
+            // and 50, 5120 x 13824 at 512 83 and 75; 256x256 tiles also beyond one round, 2560 x 13824 at 1700 rows 141 and 116.
+            if (sp == 3 && t.bn < 256 && (n < 213 || n > 256)) continue;
             double us = (double)(n >> 8) * t.k_full;
             if (rem) us += t.k_min + (t.k_full - t.k_min) * rem * (1.0 / 256);
             us = 2.0 + us * k1000 / sp + (sp > 1 ? pass0 + pass1 * mn * sp : 0.0);

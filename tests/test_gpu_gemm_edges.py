@@ -71,6 +71,8 @@ PARTS = [
     (130, 1096, 16320, 64, True, ("128x128-split", 8, 1)),
     (1000, 2056, 16320, 64, True, ("256x256-split", 4, 1)),
     (1250, 4072, 8200, 64, True, ("256x256-split", 3, 1)),
+    (1250, 2040, 11272, 120, True, ("256x128-split", 3, 1)),
+    (380, 3064, 8200, 56, True, ("128x128-split", 3, 1)),
     (4300, 4104, 8200, 64, True, ("256x256", 1, 2)),
     (1000, 17000, 4104, 40, False, ("256x256", 1, 2)),
 ]
