@@ -448,11 +448,11 @@ extern "C" tl_status tl_lora_init(tl_model* m, const tl_lora_cfg* cfg, tl_lora**
         HIPCHK(hipStreamCreateWithFlags(&L->side, hipStreamNonBlocking));
         HIPCHK(hipEventCreateWithFlags(&L->ev_opt, hipEventDisableTiming));   // gates the copy of loss and status word to the host: keeps its system-scope fence
         TLCHK(L->pool.alloc(&L->delta, (size_t)mc.n_heads * Tm));
-        // split-contraction scratch: up to 16 partial copies of the largest skinny output (Hs: [T, 3r]) or four of a
-        // [T, d_model] output (long-K GEMMs with few output tiles)
+        // split-contraction scratch: up to 16 partial copies of the largest skinny output (Hs: [T, 3r]), eight of a [T, d_model] output of
+        // up to 1024 rows or four of a longer one (long-K GEMMs with few output tiles); a longer window never leaves less of it
         {
             const size_t skinny = (size_t)Tm * 3 * r * 16;
-            const size_t wide = (size_t)Tm * d * (Tm <= 1024 ? 8 : 4);     // a GEMM with d_model output columns split that many ways
+            const size_t wide = (size_t)d * std::max((size_t)4 * Tm, (size_t)8 * std::min(Tm, 1024));
             L->partial_elems = skinny > wide ? skinny : wide;
         }
         TLCHK(L->pool.alloc(&L->partial, L->partial_elems));

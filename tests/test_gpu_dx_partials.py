@@ -54,3 +54,20 @@ def test_gate_up_input_gradient_is_summed_in_fp32(api, H, rank):  # noqa: F811
     assert err < TOL, err
     api.tl_lora_free(lora)
     api.tl_model_destroy(model)
+
+
+@pytest.mark.parametrize("max_tokens", [1001, 1024, 1025, 1500])
+def test_a_longer_window_splits_a_sample_no_less(api, H, max_tokens):  # noqa: F811
+    """dX of gate|up is cut in eight here; the scratch for that does not shrink where the window grows."""
+    shape, n = synth.Shape(1, 256, 4, 64, 4096, 0, 16, 16.0), 1000
+    h, dy = H.to_dev_f32(synth.hidden(6500, n, 256)), H.to_dev_f32(synth.upstream_grad(6500, n, 256))
+    out = []
+    for window in (n, max_tokens):
+        model = H.Model(shape, 6500, max_tokens=window)
+        lora, _ = H.new_lora(model, 6500, b_std=0.05)
+        h_out, dh_in = torch.empty_like(h), torch.empty_like(h)
+        api.tl_layer_step(lora, 0, h, dy, h_out, dh_in)
+        out.append((h_out, dh_in))
+        api.tl_lora_free(lora)
+        model.close()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
