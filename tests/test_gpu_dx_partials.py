@@ -1,6 +1,7 @@
 """The input gradient of gate|up, at ranks that are multiples of 64 with the contraction of the low-rank pair (2 r) and at others:
 its sum is kept in fp32 wherever the contraction is cut.  The case is built so that the gate half and the up half of the sum are large and nearly cancel: partial sums rounded to
-bf16 leave an error of the size of the halves.  Reference: fp64 from the same bf16 operands."""
+bf16 leave an error of the size of the halves.  One size for every instance that leaves partial tiles to the norm.  Reference: fp64 from
+the same bf16 operands."""
 import numpy as np
 import pytest
 
@@ -10,16 +11,23 @@ pytestmark = pytest.mark.gpu
 from paper_2401_11504_amd import synth  # noqa: E402
 from test_gpu_kernels import H, api  # noqa: E402,F401
 
-T, D, F, HEADS = 1024, 2048, 5632, 16
 G = -2.2178     # silu(g) + g silu'(g) = 0 here: with u = -g the two halves are opposite
-# dgate and dup are stored in bf16: F independent roundings of 2^-9 / sqrt(3) at most, averaged: 1.5e-5 of a half.  Halves
+# dgate and dup are stored in bf16: F independent roundings of 2^-9 / sqrt(3) at most, averaged: 1.5e-5 of a half (F 704: 4.3e-5).  Halves
 # rounded to bf16 would be off by about 2^-9 / sqrt(3) x 0.7 each, 1e-3 in all.
 TOL = 1e-4
 
 
-@pytest.mark.parametrize("rank", [8, 16, 32, 40, 64])
-def test_gate_up_input_gradient_is_summed_in_fp32(api, H, rank):  # noqa: F811
-    assert api.tl_k_gemm_nt_plan(T, D, 2 * F, 2 * rank, 1 << 28)[:2] == ("256x128-split", 4)
+CASES = [(1024, 2048, 5632, rank, ("256x128-split", 4)) for rank in (8, 16, 32, 40, 64)] + [
+    (520, 4096, 5632, 32, ("256x256-split", 4)),
+    (1250, 4096, 5632, 64, ("256x256-split", 3)),
+    (300, 1024, 5632, 64, ("128x128-split", 8)),
+    (200, 128, 704, 16, ("64x64-split", 5)),
+]
+
+
+@pytest.mark.parametrize("T,D,F,rank,plan", CASES)
+def test_gate_up_input_gradient_is_summed_in_fp32(api, H, T, D, F, rank, plan):  # noqa: F811
+    assert api.tl_k_gemm_nt_plan(T, D, 2 * F, 2 * rank, D * max(4 * T, 8 * min(T, 1024)))[:2] == plan     # (a session's scratch)
     rng = np.random.default_rng(rank)
     z = np.repeat(rng.normal(0, 0.02, D // 2), 2) * np.tile([1.0, -1.0], D // 2)     # no component along the rows of h
     row = synth.round_bf16((G / D + z).astype(np.float32))
@@ -29,7 +37,7 @@ def test_gate_up_input_gradient_is_summed_in_fp32(api, H, rank):  # noqa: F811
     gate = H.to_dev_bf16(np.tile(row, (F, 1)))
     ones = torch.ones(D, device="cuda")
     weights = [zero, zero, zero, zero, gate, -gate, H.to_dev_bf16(np.tile(w_down, (D, 1))), ones, ones, None, None, None]
-    model = api.tl_model_create(1, D, HEADS, D // HEADS, F, 0, T, weights, 1e-5, 10000.0)
+    model = api.tl_model_create(1, D, D // 128, 128, F, 0, T, weights, 1e-5, 10000.0)
     lora = api.tl_lora_init(model, rank, float(rank), seed=1)          # B = 0
     h_in = torch.ones(T, D, device="cuda")
     dh_out = H.to_dev_f32(np.tile(tau[:, None], (1, D)))

@@ -116,6 +116,8 @@ NT_CASES = [
     (2048, 4096, 512, 64, False, ("256x128", 1)),
     (1000, 8184, 128, 64, False, ("256x128", 1)),
     (1000, 4072, 11008, 64, True, ("256x128-split", 2)),
+    (300, 1096, 8200, 64, True, ("128x128-split", 8)),
+    (1000, 2056, 16320, 64, True, ("256x256-split", 4)),
     (1000, 11008, 576, 64, False, ("256x192", 1)),
     (1024, 12288, 128, 0, False, ("256x192", 1)),
     (1000, 16200, 512, 64, False, ("256x256", 1)),
@@ -131,8 +133,8 @@ NT_CASES = [
 
 def test_gemm_nt_cases_cover_every_configuration(api):
     names = {api.tl_k_gemm_nt_plan(M, N, K, K2, (1 << 26) if ws else 0)[0] for M, N, K, K2, ws, _ in NT_CASES}
-    assert names == {"128x128", "256x128", "256x128-split", "256x192", "256x256", "reg-128x128", "reg-128x64", "64x64",
-                     "64x64-split", "reg-64x64", "reg-64x64-split"}
+    assert names == {"128x128", "128x128-split", "256x128", "256x128-split", "256x192", "256x256", "256x256-split", "reg-128x128",
+                     "reg-128x64", "64x64", "64x64-split", "reg-64x64", "reg-64x64-split"}
 
 
 @pytest.mark.parametrize("M,N,K,K2,ws,plan", NT_CASES)
@@ -158,10 +160,12 @@ def test_gemm_nt_every_configuration(api, H, M, N, K, K2, ws, plan):
     check(H.bf16_to_np(Cb), 0.5 * ref, BF16_TOL, "C bf16")
 
 
-def test_gemm_nt_two_column_ranges(api, H):
-    """The gate|up shape at 1024 tokens: the launcher sends it out as two launches over two column ranges (whole rounds
-    of 256x256 tiles, then the rest).  Checked on sampled columns, among them those on both sides of the seam."""
-    M, N, K, K2 = 1024, 22016, 4096, 128
+@pytest.mark.parametrize("N,plan", [(22016, ("256x192", 1, 1)), (18048, ("256x256", 1, 2))])
+def test_gemm_nt_two_column_ranges(api, H, N, plan):
+    """The gate|up shape at 1024 tokens, one launch, and a width that goes out as two launches over two column ranges (a whole
+    round of 256x256 tiles, then the rest).  Checked on sampled columns, among them those on both sides of the seam."""
+    M, K, K2 = 1024, 4096, 128
+    assert api.tl_k_gemm_nt_plan(M, N, K, K2, 0) == plan
     A, B = rnd(1, (M, K)), rnd(2, (N, K), 0.05)
     A2, B2 = rnd(3, (M, K2)), rnd(4, (N, K2), 0.05)
     rs = np.random.default_rng(7)
