@@ -545,9 +545,8 @@ __global__ void fill_f32_kernel(float* __restrict__ p, size_t n, float v) {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
-// n bf16 zeros (n a multiple of 2, p 4-byte aligned): a fill kernel rather than a memset node, so that the path stays
-// capturable in a HIP graph
-// rows [0, r0) and [r1, T) of x (fp32) and y (bf16), d columns each, become zero (sixteen bytes of x per thread and step)
+// rows [0, r0) and [r1, T) of x (fp32) and y (bf16), d columns each, become zero (sixteen bytes of x per thread and step; a kernel
+// rather than memset nodes, so that the path stays capturable in a HIP graph)
 __global__ __launch_bounds__(256) void zero_rows_around_kernel(float* __restrict__ x, bf16_t* __restrict__ y, size_t n0, size_t at, size_t n) {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {

@@ -668,11 +668,12 @@ enum NtConfig {
 
 // A model of the time of one launch of the direct-to-LDS kernel: full rounds of 256 tiles (one per CU), then what is left, which
 // takes less the fewer CUs it keeps busy (the chip clocks higher and its memory is shared by fewer): us per 1000 contraction
-// elements of a round with next to no tiles (k_min) and with 256 (k_full).  Fitted to every instance forced on the products of
-// 7B-, 2048- and 1024-wide layers at 64 to 5120 rows, weights cold, 1500 timings: it is off by 7 % (rms), and what it picks took
-// 1.1 % longer than the fastest instance on average, where the rule before it (operand bytes of the busiest CU over one rate per
-// instance, splits of 256x128 tiles only) took 10.5 % longer: 4096 x 22016 at 256 rows 106 us against 62, at 5120 rows 1000 against
-// 787; 12288 x 4096 at 768 rows 101 against 65.
+// elements of a round with next to no tiles (k_min) and with 256 (k_full).  Fitted to instances forced on the products of 4096-,
+// 2048- and 1024-wide layers.  Against every instance forced on the products of six layers 1024 to 5120 wide at 64 to 5120 rows, weights
+// cold, 11702 timings of 1100 products: what it picks takes 1.3 % longer than the fastest instance on average (10 % at the 95th percentile;
+// at worst 37 %, some products of 256 to 384 rows and width 2560 that 64x64 tiles are taken for and 128x128 in four would be faster).  A rule
+// that rated each instance by operand bytes and split 256x128 tiles only is 6 % behind it; 4096 x 22016 at 256 rows 106 us against 62,
+// at 5120 rows 1000 against 787.
 struct NtTile { NtConfig cfg, cfg_split; int bm, bn; double k_min, k_full; };
 static const NtTile kNtTiles[] = {
     {NT_SKINNY, NT_SKINNY, 64, 64, 3.1, 3.75},
@@ -682,7 +683,7 @@ static const NtTile kNtTiles[] = {
     {NT_256x256, NT_256x256_SPLIT, 256, 256, 15.5, 20.2},
 };
 struct NtPick { NtConfig cfg; int split; double us; };
-// for products that the direct-to-LDS kernel takes and that are at least 65 columns wide
+// for products that the direct-to-LDS kernel takes (gemm_nt_two_parts also prices with it what choose_nt keeps from it)
 static NtPick pick_nt(const GemmNT& g) {
     const double k1000 = ((double)g.K + g.K2) * 1e-3, mn = (double)g.M * g.N * g.batch;
     const int nk = cdiv(g.K, BK) + cdiv(g.K2, BK);
@@ -745,7 +746,9 @@ static NtConfig choose_nt(const GemmNT& g, int* n_split) {
 // A GEMM whose tile count leaves its last round of workgroups poorly filled can be cheaper as two launches: whole rounds of tiles
 // over the first columns (of every batch) or the first rows, and the rest on its own with whatever tile and split suits it.
 // 5120 rows of 4096 x 22016: 320 tiles of 256x256, a round and a quarter that costs two, 819 us, 787 in 256x192 tiles; as 4096 rows (482 us)
-// and 1024 (141) 623.
+// and 1024 (141) 623.  A rest of 64 to 255 columns and few rows is priced by the model too, though choose_nt runs it by the rule for narrow
+// outputs; us in one launch and in two of that kind: 1024 x 16576 x 3072 106 and 88, 2048 x 8288 x 3072 104 and 86, 1024 x 16448 x 4096 131
+// and 104, 3008 x 5520 x 1024 49 and 45, 3264 x 2560 x 13824 207 and 208.
 bool gemm_nt_two_parts(const GemmNT& g, GemmNT* a, GemmNT* b) {
     if (g.split_k > 1 || g.M < 256 || g.N < 512 || g.batch <= 0 || !nt_direct(g)) return false;
     const double second_launch_us = 3.0;

@@ -514,8 +514,9 @@ extern "C" tl_status tl_lora_free(tl_lora* L) {
         if ((L)->discarded) return fail(TL_ERR_DISCARDED, name ": module was discarded"); \
     } while (0)
 
-// A low-rank product of a short contraction is not split: its reduce pass is a launch more (about 5 us with the gap) and saves less
-// (64x64 tiles of 64 contraction elements: 0.2 us each; 1024 rows of K 1024: 7.4 us against 4.9 + 4.0).
+// A low-rank product of a short contraction is not split: its reduce pass is a launch more, with a gap in front, and saves less.  us whole
+// and split + reduce, 64 to 2048 rows, 16 to 192 columns: K 512 3.8-4.9 and 3.9-5.5 + 1.8-3.3, K 1024 4.8-6.1 and 4.0-7.6 + 2.3-4.0,
+// K 1536 6.0-7.4 and 4.5-8.7 + 2.8-4.4 (1024 rows of 64 columns: 4.7 and 4.6 + 3.0, 5.8 and 4.7 + 3.7, 6.8 and 4.8 + 4.2); K 4096 is split.
 constexpr int LOW_RANK_WHOLE_K = 1536;
 
 // ---------------------------------------------------------------- one LoRA-adapted projection group
