@@ -1,8 +1,10 @@
-// fp32 products of the single fp32 LoRA-adapted linear step, on the fp32 matrix instructions (inputs, products and sums all
-// fp32).  Several independent products C = alpha (A B^T + A2 B2^T) of three operand layouts share a launch:
+// Products of the single fp32 LoRA-adapted linear step: fp32 operands and outputs, sums in fp32.  Several independent products
+// C = alpha (A B^T + A2 B2^T) of three operand layouts share a launch:
 //   F32_KK  A [M, K], B [N, K]: the contraction is contiguous in both          (X A^T;  X W^T + H B^T)
 //   F32_KN  A [M, K], B [K, N]                                                 (dY B;   dY W + dH A)
 //   F32_MN  A [K, M], B [K, N]                                                 (dH^T X; dY^T H)
+// Small ones go through the fp32 matrix instructions (f32_group_kernel), large ones through the bf16 ones with every operand cut into
+// three parts (f32_split_kernel); f32_cost holds what the line between them was timed on.
 //
 // v_mfma_f32_16x16x4_f32 adds its four products in ascending order, each as one fused multiply-add: an output is the plain
 // chain fma(a[k], b[k], ..) over k, the same value wherever its tile boundaries lie.  (So no contraction is split, and the
@@ -13,11 +15,11 @@
 // undone).  Neither is transposed on the way.
 //
 // The bound is the matrix unit: 256 flop per clock and CU, a sixteenth of the bf16 rate, so that LDS reads are cheap beside
-// it and tiles staged through registers are enough.  Measured, one step of 1024 tokens, 4096 x 4096, rank 64: 3.89 ms with
-// 4 x 4 outputs per thread on the vector unit and thirteen launches, 0.69 ms here in two (100 of 157 TFLOP/s); the same bits.
-// 128 tokens, 256 x 256, rank 8: 263 -> 36 us, of which the two kernels are 15.
+// it and tiles staged through registers are enough.  128 tokens, 256 x 256, rank 8: 36 us, of which the two kernels are 15.
 #include "kernels.h"
+#include "tiles.h"
 #include <type_traits>
+#include <utility>
 
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // rows start at any multiple of a float
@@ -46,7 +48,8 @@ struct F32Tile {
 // and the compiler can count exactly which of them a use has to wait for.  WIDE: rows of more than 2^22 floats, whose offsets
 // within a tile do not fit the resource's 32 bits; plain loads with their own look at the operand's end (64 tokens, 4194312 x 64,
 // rank 8: 0.21 s; one output per thread 2.9 to 3.2).
-template <int B, int BKF, bool KC, bool WIDE>     // B rows (or columns); KC: the contraction is contiguous
+// PAST: the first row may lie behind the operand's end (then there is nothing to load).
+template <int B, int BKF, bool KC, bool WIDE, bool PAST>     // B rows (or columns); KC: the contraction is contiguous
 struct F32Stage {
     static constexpr int CPR = (KC ? BKF : B) / 4, STEP = 256 / CPR, N = B * BKF / 1024;
     u32x4_t r[N];
@@ -73,7 +76,7 @@ struct F32Stage {
             }
             return;
         }
-        const long left = (unsigned)k0 < (unsigned)kmax ? (end - at) * 4 : 0;
+        const long left = (unsigned)k0 < (unsigned)kmax && (!PAST || end > at) ? (end - at) * 4 : 0;
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(src + (left > 0 ? at : 0)), 0,
                                                             (int)(unsigned)(left > 0xffffffffL ? 0xffffffffL : left), 0x00020000);
         const unsigned off = ((unsigned)(tid / CPR) * (unsigned)ld + (tid % CPR) * 4) * 4, step = (unsigned)ld * (STEP * 4);
@@ -112,13 +115,12 @@ __device__ __forceinline__ void f32_fragments(const float* tile, int row0, int k
     }
 }
 
-template <int BM, int BN, int BKF, int PF, bool WIDE, bool AKC, bool BKC>
-__device__ __forceinline__ void f32_tile(const F32Product& q, int tile, float* smem) {
+template <int BM, int BN, int BKF, int PF, bool WIDE, bool AKC, bool BKC, bool PAST = false>
+__device__ __forceinline__ void f32_tile(const F32Product& q, int m0, int n0, float* smem, int tid) {
     using T = F32Tile<BM, BN, BKF>;
     constexpr int FM = T::FM, FN = T::FN, KS = BKF / 16;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, g = lane >> 4;
-    const int m0 = tile % q.tiles_m * BM, n0 = tile / q.tiles_m * BN;
     float *sA = smem, *sB = smem + 3 * T::SA;
     // First the main term, stored; then, for a product that has one, the low-rank term, added to what this thread stored.
 #pragma unroll 1
@@ -130,8 +132,8 @@ __device__ __forceinline__ void f32_tile(const F32Product& q, int tile, float* s
         // Tile t goes from memory to the staging registers of slot t % PF, from there to place t % 3 of the LDS ring, and its
         // fragments to set t % 2: while tile t is multiplied the fragments of t + 1 are read, t + 2 is put into LDS and t + 3
         // .. t + 2 + PF are in flight.  One barrier per tile: it makes t + 2 visible and frees the place of t + 1.
-        F32Stage<BM, BKF, AKC, WIDE> ra[PF];
-        F32Stage<BN, BKF, BKC, WIDE> rb[PF];
+        F32Stage<BM, BKF, AKC, WIDE, PAST> ra[PF];
+        F32Stage<BN, BKF, BKC, WIDE, PAST> rb[PF];
         // (128-wide tiles have sixteen independent chains to hide the LDS behind, and no registers for a second set: they read
         // a tile's fragments when they multiply it)
         constexpr bool AHEAD = BM < 128;
@@ -258,9 +260,306 @@ __global__ __launch_bounds__(256, 2) void f32_group_kernel(F32Batch grp) {
     // that the CUs of one XCD share operand rows in its L2.
     const int n = q.tiles_m * q.tiles_n, id = b - q.tile0;
     const int c = id & 7, per = n >> 3, tile = c * per + min(c, n & 7) + (id >> 3);
-    if (q.kind == F32_KK) f32_tile<BM, BN, BKF, PF, WIDE, true, true>(q, tile, smem_f32);
-    else if (q.kind == F32_KN) f32_tile<BM, BN, BKF, PF, WIDE, true, false>(q, tile, smem_f32);
-    else f32_tile<F32_MN_TILE(BM), F32_MN_TILE(BN), BKF, PF, WIDE, false, false>(q, tile, smem_f32);
+    const int im = tile % q.tiles_m, in = tile / q.tiles_m, tid = threadIdx.x;
+    constexpr int MM = F32_MN_TILE(BM), MN = F32_MN_TILE(BN);
+    if (q.kind == F32_KK) f32_tile<BM, BN, BKF, PF, WIDE, true, true>(q, im * BM, in * BN, smem_f32, tid);
+    else if (q.kind == F32_KN) f32_tile<BM, BN, BKF, PF, WIDE, true, false>(q, im * BM, in * BN, smem_f32, tid);
+    else f32_tile<MM, MN, BKF, PF, WIDE, false, false>(q, im * MM, in * MN, smem_f32, tid);
+}
+
+// ---------------------------------------------------------------- split operands on the bf16 matrix instructions
+// The same products with every operand cut into three bf16 parts, x = x1 + x2 + x3 (eight bits of the fraction each, by
+// truncation: nothing is lost and nothing overflows), and a b taken as a1 b3 + a1 b2 + a1 b1 + a2 b2 + a2 b1 + a3 b1 in fp32
+// accumulators.  What is left out, a2 b3 + a3 b2 + a3 b3, is 2^-24 of a product on average, half an ulp, and the accumulator is
+// rounded 6 K / 32 times instead of K times.  Against fp64, 2-norm, chain of fp32 products / parts: 1024 tokens, 4096 x 4096, rank 64
+// Y 1.15e-6 / 1.05e-6, dA 1.28e-6 / 1.24e-6; 1400, 300 x 4000 Y 3.1e-7 / 2.9e-7, dX 1.13e-6 / 1.04e-6.
+//
+// The bf16 unit has sixteen times the rate, so that six products take 6/16 of the time of one in fp32.  What is cut is cut on
+// its way from the staging registers to LDS, seven vector operations an element, in slices between the matrix instructions.
+// (A matrix instruction of 16 clocks hides two vector operations, from whichever wave: twice as many waves that cut in one go and multiply in
+// another were slower, 465 against 430 us for a step of 1024 tokens, 4096 x 4096, rank 64; in fp32 tiles of 128x128 it was 690.)  What
+// is left beside 200 us of matrix instructions: 45 us of cutting, 35 of LDS writes, 25 of waiting for memory, by leaving each out in turn, the
+// two small products behind the large ones (25) and the launch of the low-rank products ahead of them (47).
+//
+// The parts say nothing about an operand that is infinite (inf * 0 for a part that is zero) or whose last part is below the
+// bf16 range (|x| < 2^-110): a workgroup that meets one starts its outputs again with f32_tile, in two halves of 256 threads.
+//
+// Order of the 32 contraction elements of a tile within the matrix instruction: lane group g takes 4 g .. 4 g + 3 and
+// 16 + 4 g .. 16 + 4 g + 3, in both operands.
+constexpr int SPLIT_BK = 32, SPLIT_NT = 512;
+// One operand: memory -> registers (`N` items of four floats a thread) -> three planes of LDS per tile.
+//   KC: [row][32], 8-byte piece p of a row (elements 4 p .. 4 p + 3) as half p / 4 of 16-byte chunk (p % 4) ^ (row / 4 % 4), so that
+//       a lane's elements are one chunk, sixteen rows' chunks lie in distinct banks, and so do the pieces that are written
+//   otherwise [k][B + 16], read by the LDS transpose read (eight consecutive k x 32 bytes lie in distinct banks)
+template <int B, bool KC>
+struct SplitOperand {
+    static constexpr int LD = KC ? SPLIT_BK : B + 16, PLANE = KC ? B * LD : SPLIT_BK * LD, ELEMS = 3 * PLANE;
+    static constexpr int CPR = (KC ? SPLIT_BK : B) / 4, STEP = SPLIT_NT / CPR, N = B * SPLIT_BK / (4 * SPLIT_NT);
+    static_assert(N >= 1 && (!KC || STEP % 16 == 0), "tile shape");
+    unsigned off;         // byte offset of item 0 within a tile in memory
+    int dst;              // and where its parts go within a plane
+    __device__ __forceinline__ void init(long ld, int tid) {
+        const int c = tid % CPR, o = tid / CPR;
+        off = ((unsigned)o * (unsigned)ld + c * 4) * 4;
+        dst = KC ? o * LD + (((c & 3) ^ ((o >> 2) & 3)) * 8) + (c >> 2) * 4 : o * LD + c * 4;
+    }
+    // (what lies behind the operand's end reads as zero; see F32Stage)
+    static __device__ __forceinline__ auto rsrc(const float* src, long ld, int r0, int rows, int k0, int kmax) {
+        const long at = KC ? r0 * ld + k0 : k0 * ld + r0, end = KC ? (rows - 1) * ld + kmax : (kmax - 1) * ld + rows;
+        const long left = (unsigned)k0 < (unsigned)kmax ? (end - at) * 4 : 0;
+        return __builtin_amdgcn_make_buffer_rsrc((void*)(src + (left > 0 ? at : 0)), 0,
+                                                 (int)(unsigned)(left > 0xffffffffL ? 0xffffffffL : left), 0x00020000);
+    }
+    template <class R>
+    __device__ __forceinline__ u32x4_t load(R rs, int i, long ld) const {
+        return __builtin_amdgcn_raw_buffer_load_b128(rs, off + (unsigned)i * ((unsigned)ld * (STEP * 4)), 0, 0);
+    }
+    // elements past the contraction's end belong to the next row: they count as zero
+    static __device__ __forceinline__ u32x4_t mask(u32x4_t r, int left, int tid) {
+        const int c = (tid % CPR) * 4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = !KC || c + e < left ? r[e] : 0u;
+        return r;
+    }
+    // fragment of 16 rows from row0 on: lane (l16, g) holds row l16
+    static __device__ __forceinline__ int lane_offset(int row0, int lane) {
+        const int l16 = lane & 15, g = lane >> 4;
+        return KC ? (row0 + l16) * LD + ((g ^ (l16 >> 2)) * 8) : (4 * g + (l16 >> 2)) * LD + row0 + 4 * (l16 & 3);
+    }
+    static __device__ __forceinline__ bf16x8_t fragment(const bf16_t* at, int i) {
+        if constexpr (KC) {
+            return *(const bf16x8_t*)(at + 16 * i * LD);
+        } else {          // (lane q + 4 e of a group of sixteen points at element e, rows 4 q .. 4 q + 3: see load_a_tr in tiles.h)
+            typedef __attribute__((address_space(3))) bf16x4v_t* lds_ptr_t;
+            const bf16x4v_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(at + 16 * i));
+            const bf16x4v_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(at + 16 * i + 16 * LD));
+            bf16x8_t v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
+            return v;
+        }
+    }
+};
+// the parts of four floats, made in seven slices: one per element, then one per plane
+struct SplitParts {
+    unsigned x[3][4];
+    unsigned low = 0;      // bits that the third parts do not hold
+    float top = 0.f;       // the largest magnitude
+    __device__ __forceinline__ void element(unsigned bits, int e) {
+        const float v = __uint_as_float(bits);
+        x[0][e] = bits & 0xffff0000u;
+        const float y = v - __uint_as_float(x[0][e]);
+        x[1][e] = __float_as_uint(y) & 0xffff0000u;
+        x[2][e] = __float_as_uint(y - __uint_as_float(x[1][e]));
+        low |= x[2][e];
+        top = fmaxf(top, fabsf(v));
+    }
+    __device__ __forceinline__ void put(bf16_t* dst, int p) const {
+        *(uint2*)dst = make_uint2(__builtin_amdgcn_perm(x[p][1], x[p][0], 0x07060302u), __builtin_amdgcn_perm(x[p][3], x[p][2], 0x07060302u));
+    }
+    __device__ __forceinline__ bool unsplit() const { return (low & 0xffffu) != 0 || top > 3.4028234663852886e38f; }
+};
+
+// f(0), f(1), .. with the index as a constant: registers that are picked by it stay registers
+template <class F, int... I>
+__device__ __forceinline__ void for_each_index(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F f) { for_each_index(f, std::make_integer_sequence<int, N>{}); }
+
+template <int BM, int BN>
+struct SplitTile {
+    static constexpr int MAX(int a, int b) { return a > b ? a : b; }
+    static constexpr int STAGE = MAX(SplitOperand<BM, true>::ELEMS + MAX(SplitOperand<BN, true>::ELEMS, SplitOperand<BN, false>::ELEMS),
+                                     2 * SplitOperand<64, false>::ELEMS);
+    // the halves that are taken in fp32 instead
+    static constexpr int F32_BYTES = 2 * (int)sizeof(float) * MAX(F32Tile<BM / 2, BN, 16>::LDS_FLOATS, F32Tile<32, 64, 32>::LDS_FLOATS);
+    static constexpr int LDS_BYTES = MAX(16 + 2 * STAGE * (int)sizeof(bf16_t), F32_BYTES);
+};
+
+// BM x BN outputs per workgroup of WM x WN waves.  Tile t + 1 of the contraction is cut and written to the other LDS stage while
+// tile t is multiplied, and the loads of t + 2 follow into the registers that this frees: one barrier per tile, behind the last
+// write, with an eighth of the matrix instructions left to cover the first fragments of t + 1.
+template <int BM, int BN, int WM, int WN, bool AKC, bool BKC>
+__device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, unsigned char* smem) {
+    constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
+    static_assert(WM * WN * 64 == SPLIT_NT && FM >= 1 && FN >= 1, "waves");
+    using OA = SplitOperand<BM, AKC>;
+    using OB = SplitOperand<BN, BKC>;
+    constexpr int STAGE = OA::ELEMS + OB::ELEMS, NG = FM * FN, NMF = 6 * NG, NI = OA::N + OB::N, NS = 8 * NI;
+    constexpr int AT_BARRIER = NMF - (NMF + 7) / 8, SLICED = NMF * 3 / 4;      // matrix instructions ahead of the barrier, and among slices
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN, l16 = lane & 15, g = lane >> 4;
+    const int M = q.M, N = q.N;
+    int* unsplit = (int*)smem;             // [t % 2]: tile t holds a value that the parts do not
+    bf16_t* planes = (bf16_t*)(smem + 16);
+    const int a_off = OA::lane_offset(wm * TM, lane), b_off = OA::ELEMS + OB::lane_offset(wn * TN, lane);
+    f32x4_t acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    bf16x8_t fa[3][FM], fb[3][FN];
+    auto read_a = [&](const bf16_t* stage, int s, int i) { fa[s][i] = OA::fragment(stage + a_off + s * OA::PLANE, i); };
+    auto read_b = [&](const bf16_t* stage, int s, int i) { fb[s][i] = OB::fragment(stage + b_off + s * OB::PLANE, i); };
+    // the low-rank term first, scaled; the main term goes on top of it
+#pragma unroll 1
+    for (int term = q.K2 > 0 ? 0 : 1; term < 2; ++term) {
+        const float *A = term ? q.A : q.A2, *B = term ? q.B : q.B2;
+        const long lda = term ? q.lda : q.lda2, ldb = term ? q.ldb : q.ldb2;
+        const int K = term ? q.K : q.K2;
+        auto tile_k = [](int t) { return (int)((unsigned)t * SPLIT_BK); };     // (beyond the end: reads as zeros, never multiplied)
+        OA oa;
+        OB ob;
+        oa.init(lda, tid);
+        ob.init(ldb, tid);
+        SplitParts parts;
+        u32x4_t r[NI];                     // the items of A, then those of B
+        auto item_dst = [&](bf16_t* stage, int i, int p) {
+            return i < OA::N ? stage + (oa.dst + p * OA::PLANE + i * OA::STEP * OA::LD)
+                             : stage + (OA::ELEMS + ob.dst + p * OB::PLANE + (i - OA::N) * OB::STEP * OB::LD);
+        };
+        auto mask = [&](int left) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) r[i] = i < OA::N ? OA::mask(r[i], left, tid) : OB::mask(r[i], left, tid);
+        };
+        {
+            const auto rsa = OA::rsrc(A, lda, m0, M, 0, K);
+            const auto rsb = OB::rsrc(B, ldb, n0, N, 0, K);
+#pragma unroll
+            for (int i = 0; i < NI; ++i) r[i] = i < OA::N ? oa.load(rsa, i, lda) : ob.load(rsb, i - OA::N, ldb);
+            __syncthreads();               // the other term's tiles have been read
+            if (tid < 2) unsplit[tid] = 0;
+            __syncthreads();
+            mask(K);
+            const auto rsa1 = OA::rsrc(A, lda, m0, M, tile_k(1), K);
+            const auto rsb1 = OB::rsrc(B, ldb, n0, N, tile_k(1), K);
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) parts.element(r[i][e], e);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) parts.put(item_dst(planes, i, p), p);
+                r[i] = i < OA::N ? oa.load(rsa1, i, lda) : ob.load(rsb1, i - OA::N, ldb);
+            }
+            if (parts.unsplit()) unsplit[0] = 1;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < FM; ++i) read_a(planes, 0, i);
+#pragma unroll
+            for (int i = 0; i < FN; ++i) read_b(planes, 2, i);
+        }
+        int slow = __builtin_amdgcn_readfirstlane(unsplit[0]);
+        bf16_t *stage = planes, *other = planes + STAGE;
+        const int nk = (K + SPLIT_BK - 1) / SPLIT_BK;
+        for (int t = 0; t < nk; ++t) {
+            if (slow) return false;        // (every wave reads the same word, behind the barrier that its writers wait at)
+            if (t + 2 >= nk) mask(K - tile_k(t + 1));
+            const auto rsa = OA::rsrc(A, lda, m0, M, tile_k(t + 2), K);
+            const auto rsb = OB::rsrc(B, ldb, n0, N, tile_k(t + 2), K);
+            parts.low = 0;
+            parts.top = 0.f;
+            int found = 0;
+            // slice x of NS: an element of an item, one of its planes, or the load that replaces it
+            auto slice = [&](auto xc) {
+                constexpr int i = xc.value / 8, y = xc.value % 8;
+                if constexpr (y < 4) parts.element(r[i][y], y);
+                else if constexpr (y < 7) parts.put(item_dst(other, i, y - 4), y - 4);
+                else if constexpr (i < OA::N) r[i] = oa.load(rsa, i, lda);
+                else r[i] = ob.load(rsb, i - OA::N, ldb);
+            };
+            auto hand_over = [&] {
+                if (parts.unsplit()) unsplit[(t + 1) & 1] = 1;
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            };
+            unrolled<NMF>([&](auto ec) {
+                constexpr int e = ec.value, gr = e / NG, x = e % NG, i = x / FN, jn = x % FN, left = NMF - AT_BARRIER;
+                constexpr int pa = gr < 3 ? 0 : gr < 5 ? 1 : 2, pb = gr == 0 ? 2 : gr == 1 || gr == 3 ? 1 : 0;
+                // B first: a lane then holds row l16 of A's fragment, columns 4 g .. 4 g + 3 of B's
+                acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[pb][jn], fa[pa][i], acc[i][jn], 0, 0, 0);
+                // the fragments that a later group needs, spread over this one
+                unrolled<FM>([&](auto f) {
+                    if constexpr (f.value * NG / FM == x && gr == 2) read_a(stage, 1, f.value);
+                    if constexpr (f.value * NG / FM == x && gr == 4) read_a(stage, 2, f.value);
+                });
+                unrolled<FN>([&](auto f) {
+                    if constexpr (f.value == x && gr == 0) read_b(stage, 1, f.value);
+                    if constexpr (f.value == x && gr == 1) read_b(stage, 0, f.value);
+                });
+                unrolled<NS>([&](auto y) {
+                    if constexpr (y.value * SLICED / NS == e) slice(y);
+                });
+                if constexpr (e + 1 == AT_BARRIER) { hand_over(); found = unsplit[(t + 1) & 1]; }
+                unrolled<FN>([&](auto f) {
+                    if constexpr (AT_BARRIER - 1 + f.value * left / (FM + FN) == e) read_b(other, 2, f.value);
+                });
+                unrolled<FM>([&](auto f) {
+                    if constexpr (AT_BARRIER - 1 + (FN + f.value) * left / (FM + FN) == e) read_a(other, 0, f.value);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            slow = __builtin_amdgcn_readfirstlane(found);
+            bf16_t* const s = stage;
+            stage = other; other = s;
+        }
+        if (term == 0) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i][j][e] *= q.alpha2;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int r = 0; r < FN; ++r) {
+            const int m = m0 + wm * TM + 16 * i + l16, n = n0 + wn * TN + 16 * r + 4 * g;
+            if (m >= M || n >= N) continue;
+            const long at = (long)m * q.ldc + n;
+            f4u v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = q.alpha * acc[i][r][e];
+            if (n + 4 <= N) {
+                *(f4u*)(q.C + at) = v;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) q.C[at + e] = v[e];
+            }
+            if (q.p_new) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) q.p_new[at + e] = adamw_first(q.p_old[at + e], v[e], q.opt);
+            }
+        }
+    return true;
+}
+
+template <int BM, int BN, int WM, int WN, int BKF, bool AKC, bool BKC>
+__device__ __forceinline__ void split_or_f32_tile(const F32Product& q, int m0, int n0, unsigned char* smem) {
+    if (split_tile<BM, BN, WM, WN, AKC, BKC>(q, m0, n0, smem)) return;
+    __syncthreads();                       // every wave has read the flag that lies in this memory
+    const int half = threadIdx.x >> 8;
+    f32_tile<BM / 2, BN, BKF, 2, false, AKC, BKC, true>(q, m0 + half * (BM / 2), n0,
+                                                  (float*)smem + half * F32Tile<BM / 2, BN, BKF>::LDS_FLOATS, threadIdx.x & 255);
+}
+
+template <int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(SPLIT_NT, 2) void f32_split_kernel(F32Batch grp) {
+    extern __shared__ __align__(16) unsigned char smem_split[];
+    const int b = blockIdx.x;
+    int k = 0;
+    while (k + 1 < grp.n && b >= grp.p[k + 1].tile0) ++k;
+    const F32Product& q = grp.p[k];
+    const int n = q.tiles_m * q.tiles_n, id = b - q.tile0;      // (the same order of tiles as in f32_group_kernel)
+    const int c = id & 7, per = n >> 3, tile = c * per + min(c, n & 7) + (id >> 3);
+    const int im = tile % q.tiles_m, in = tile / q.tiles_m;
+    if (q.kind == F32_KK) split_or_f32_tile<BM, BN, WM, WN, 16, true, true>(q, im * BM, in * BN, smem_split);
+    else if (q.kind == F32_KN) split_or_f32_tile<BM, BN, WM, WN, 16, true, false>(q, im * BM, in * BN, smem_split);
+    else split_or_f32_tile<64, 64, 2, 4, 32, false, false>(q, im * 64, in * 64, smem_split);
 }
 
 __global__ __launch_bounds__(256) void adamw_first_kernel(const float* __restrict__ g, const float* p, float* p_new, size_t n,
@@ -274,8 +573,8 @@ hipError_t launch_adamw_first(const float* g, const float* p, float* p_new, size
     return hipGetLastError();
 }
 
-template <int BM, int BN, int BKF, int PF, bool WIDE = false>
-static hipError_t run_f32(F32Batch& grp, hipStream_t s) {
+template <int BM, int BN>
+static hipError_t place_f32(F32Batch& grp, int* n_tiles) {
     long tiles = 0;
     for (int k = 0; k < grp.n; ++k) {
         F32Product& q = grp.p[k];
@@ -285,12 +584,52 @@ static hipError_t run_f32(F32Batch& grp, hipStream_t s) {
         tiles += (long)q.tiles_m * q.tiles_n;
         if (tiles > 0x7fffffffL) return hipErrorInvalidValue;
     }
+    *n_tiles = (int)tiles;
+    return hipSuccess;
+}
+template <int BM, int BN, int BKF, int PF, bool WIDE = false>
+static hipError_t run_f32(F32Batch& grp, hipStream_t s) {
+    int tiles = 0;
+    hipError_t e = place_f32<BM, BN>(grp, &tiles);
+    if (e != hipSuccess) return e;
     const int lds = F32Tile<BM, BN, BKF>::LDS_FLOATS * (int)sizeof(float);
     auto kern = f32_group_kernel<BM, BN, BKF, PF, WIDE>;
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    kern<<<(unsigned)tiles, 256, lds, s>>>(grp);
+    kern<<<tiles, 256, lds, s>>>(grp);
     return hipGetLastError();
+}
+template <int BM, int BN, int WM, int WN>
+static hipError_t run_split(F32Batch& grp, hipStream_t s) {
+    int tiles = 0;
+    hipError_t e = place_f32<BM, BN>(grp, &tiles);
+    if (e != hipSuccess) return e;
+    const int lds = SplitTile<BM, BN>::LDS_BYTES;
+    auto kern = f32_split_kernel<BM, BN, WM, WN>;
+    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    kern<<<tiles, SPLIT_NT, lds, s>>>(grp);
+    return hipGetLastError();
+}
+
+// What a launch takes: the longest chain, or all contraction tiles spread over 256 CUs, whichever is longer, per instance: us per
+// contraction element of one chain and of 256 tiles, and what it takes besides.  Fitted to steps of 57 shapes, 33 to 1400 tokens, widths
+// 100 to 5000, ranks 4 to 64, with each instance forced: what is picked takes 0.1 % longer than the fastest on average, 4 % at worst.
+// Tokens x d_in x d_out, us in 32x32, 64x64 (fp32), 128x128, 256x128 (split): 128x256x256 36, 42, 45, 54; 128x4096x4096 198, 187, 233, 338;
+// 1400x300x4000 250, 192, 227, 328; 333x4096x4096 414, 346, 237, 344; 700x2500x2500 345, 277, 183, 230; 1027x2050x2050 356, 284, 230, 194;
+// 1024x4096x4096 1066, 778, 491, 431 (690 in 128x128 tiles in fp32, which are never the fastest).
+struct F32Cost { int bm, bn; double chain, tiles, fixed; };
+static double f32_cost(const F32Batch& grp, const F32Cost& c) {
+    double longest = 0, all = 0;
+    for (int k = 0; k < grp.n; ++k) {
+        const F32Product& q = grp.p[k];
+        const double K = (double)q.K + q.K2;
+        const bool mn = q.kind == F32_MN;
+        all += (double)cdiv(q.M, mn ? F32_MN_TILE(c.bm) : c.bm) * cdiv(q.N, mn ? F32_MN_TILE(c.bn) : c.bn) * K;
+        if ((!mn || grp.n == 1) && K > longest) longest = K;
+    }
+    const double chain = c.chain * longest, tiles = c.tiles * all / 256;
+    return c.fixed + (chain > tiles ? chain : tiles);
 }
 
 hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s) {
@@ -301,7 +640,7 @@ hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s) 
     for (int k = 0; k < n; ++k) order[k] = k;
     for (int k = 1; k < n; ++k)               // longest contraction first: what is left for the end are short tiles
         for (int j = k; j > 0 && prods[order[j]].K > prods[order[j - 1]].K; --j) { int t = order[j]; order[j] = order[j - 1]; order[j - 1] = t; }
-    long t128 = 0, t64 = 0;
+    long t64 = 0;
     bool wide = false;
     for (int k = 0; k < n; ++k) {
         F32Product& q = grp.p[k];
@@ -309,14 +648,18 @@ hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s) 
         if (q.M <= 0 || q.N <= 0 || q.K <= 0) return hipErrorInvalidValue;
         wide |= q.lda > (1L << 22) || q.ldb > (1L << 22) || q.lda2 > (1L << 22) || q.ldb2 > (1L << 22);
         if (q.kind == F32_MN) continue;
-        t128 += (long)cdiv(q.M, 128) * cdiv(q.N, 128);
         t64 += (long)cdiv(q.M, 64) * cdiv(q.N, 64);
     }
     // (rows that wide are long chains on few tiles, or next to no arithmetic: no 128-wide instance for them)
     if (wide) return t64 >= 256 ? run_f32<64, 64, 32, 2, true>(grp, s) : run_f32<32, 32, 64, 2, true>(grp, s);
-    // The largest tile that gives every CU one.  Below that smaller tiles, down to one chain of 16 x 16 outputs per wave: the
-    // low-rank products of 1024 tokens (K 4096) take 45 us on 128 workgroups, a third of it the chain itself.
-    if (t128 >= 256) return run_f32<128, 128, 16, 2>(grp, s);
-    if (t64 >= 256) return run_f32<64, 64, 32, 2>(grp, s);
-    return run_f32<32, 32, 64, 4>(grp, s);
+    const F32Cost costs[] = {{32, 32, 0.0035, 0.0076, 0.4}, {64, 64, 0.0200, 0.0219, 2.3}, {128, 128, 0.0325, 0.0475, 0.0}, {256, 128, 0.0573, 0.0731, 2.7}};
+    int best = 0;
+    for (int c = 1; c < 4; ++c)
+        if (f32_cost(grp, costs[c]) < f32_cost(grp, costs[best])) best = c;
+    switch (best) {
+        case 0: return run_f32<32, 32, 64, 4>(grp, s);
+        case 1: return run_f32<64, 64, 32, 2>(grp, s);
+        case 2: return run_split<128, 128, 2, 4>(grp, s);
+        default: return run_split<256, 128, 4, 2>(grp, s);
+    }
 }

@@ -129,3 +129,54 @@ def test_subnormal_products_and_sums():
     assert 1e-43 < ref["Y"].abs().max() < 1e-38
     # every sum is rounded to a multiple of 2^-149: 64 of them and the low-rank chain's 4 (behind a product with B < 1)
     assert (outs[0].cpu().double() - ref["Y"]).abs().max() < 69 * 2.0 ** -149
+
+
+# Operands cut into bf16 parts: ragged rows, columns and contractions of both tiles (256x128: the first; 128x128: the others), and
+# what the parts do not hold -- infinities, values below 2^-110 -- in the first and the last tile of a contraction, in either half of
+# a tile's rows, and in the low-rank factors.
+SPLIT = [(1029, 2050, 2049, 64), (701, 2500, 2501, 33), (257, 4095, 4100, 7), (1400, 1030, 1100, 1)]
+
+
+@pytest.mark.parametrize("T,din,dout,r", SPLIT)
+def test_split_operands(T, din, dout, r):
+    ins, s = make(T, din, dout, r), 1.5
+    dev = [t.cuda() for t in ins]
+    outs = [torch.empty(*size, device="cuda") for size in ((T, dout), (T, din), (r, din), (dout, r))]
+    step(dev, s, outs, torch.empty_like(dev[2]), torch.empty_like(dev[3]))
+    ref = reference(ins, s)
+    for k, o in zip(("Y", "dX", "dA", "dB"), outs):
+        assert (o.cpu().double() - ref[k]).norm() < tol(T, din, dout) * ref[k].norm(), k
+
+
+@pytest.mark.parametrize("T,din,dout,r", SPLIT[:2])
+@pytest.mark.parametrize("which,at", [(0, (5, -1)), (0, (-1, 0)), (0, (200, 40)), (1, (2, -1)), (1, (-1, 0)), (2, (0, -1)), (3, (-1, -1)), (4, (7, 0))])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_split_operands_not_finite(T, din, dout, r, which, at, value):
+    ins, s = make(T, din, dout, r), 1.5
+    ins[which][at] = value
+    dev = [t.cuda() for t in ins]
+    outs = [torch.empty(*size, device="cuda") for size in ((T, dout), (T, din), (r, din), (dout, r))]
+    step(dev, s, outs, torch.empty_like(dev[2]), torch.empty_like(dev[3]))
+    ref = reference(dev, s)                      # (on the GPU, in fp64)
+    for k, o in zip(("Y", "dX", "dA", "dB"), outs):
+        fine = torch.isfinite(ref[k])
+        assert torch.equal(torch.isfinite(o), fine), k
+        assert torch.equal(torch.isnan(o), torch.isnan(ref[k])), k
+        assert torch.equal(o[~fine & ~torch.isnan(o)].double(), ref[k][~fine & ~torch.isnan(o)]), k
+        if fine.any():
+            assert (o.double() - ref[k])[fine].norm() < tol(T, din, dout) * ref[k][fine].norm(), k
+
+
+@pytest.mark.parametrize("T,din,dout,r", SPLIT[:2])
+@pytest.mark.parametrize("rows", [slice(0, None), slice(100, 101), slice(-1, None)])
+def test_split_operands_tiny(T, din, dout, r, rows):
+    """Rows of X of the order of 2^-116, which bf16 parts would hold to 17 bits: their outputs (2^-116 too) are as precise as the others."""
+    ins, s = make(T, din, dout, r), 1.5
+    ins[0][rows] *= 2.0 ** -116
+    dev = [t.cuda() for t in ins]
+    outs = [torch.empty(*size, device="cuda") for size in ((T, dout), (T, din), (r, din), (dout, r))]
+    step(dev, s, outs, torch.empty_like(dev[2]), torch.empty_like(dev[3]))
+    ref = reference(ins, s)
+    # each of the K sums of an entry may also be off by half of 2^-149, far below a row of 2^-116
+    assert (outs[0].cpu().double() - ref["Y"])[rows].norm() < tol(T, din, dout) * ref["Y"][rows].norm()
+    assert (outs[0].cpu().double() - ref["Y"]).norm() < tol(T, din, dout) * ref["Y"].norm()
