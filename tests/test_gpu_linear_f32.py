@@ -180,3 +180,34 @@ def test_split_operands_tiny(T, din, dout, r, rows):
     # each of the K sums of an entry may also be off by half of 2^-149, far below a row of 2^-116
     assert (outs[0].cpu().double() - ref["Y"])[rows].norm() < tol(T, din, dout) * ref["Y"][rows].norm()
     assert (outs[0].cpu().double() - ref["Y"]).norm() < tol(T, din, dout) * ref["Y"].norm()
+
+
+# Main terms in fp16 halves, scaled by the operand's largest magnitude: operands far from 1 and beyond the scales there are, zeros, rows and
+# columns far below the largest magnitude (an outlier puts every other element there), contractions of less than two tiles.  Every row
+# and every column of the outputs is held to the tolerance by itself (twice, for the fewer entries it has).
+def _scale(ins, what):
+    X, W, A, B, dY = ins
+    if what == "large": X *= 2.0 ** 90; W *= 2.0 ** -95; B *= 2.0 ** -90; dY *= 2.0 ** 60
+    elif what == "beyond": W *= 2.0 ** -104; B *= 2.0 ** -100; dY *= 2.0 ** 40
+    elif what == "zero rows": X[3:400] = 0; W[:, 5:90] = 0; W[7] = 0; B[7] = 0; dY[-200:] = 0
+    elif what == "rows": X[100] *= 2.0 ** -12; X[-1] *= 2.0 ** -30; dY[257] *= 2.0 ** -20
+    elif what == "columns": W[:, 9] *= 2.0 ** -16; A[:, 9] *= 2.0 ** -16; W[-1] *= 2.0 ** -25; B[-1] *= 2.0 ** -25
+    elif what == "outlier": X[300, 11] = 3.0e4; dY[2, 2] = -7.0e5
+    elif what == "all zero": X *= 0
+
+
+@pytest.mark.parametrize("T,din,dout,r", [(1029, 2050, 2049, 64), (701, 2500, 2501, 33), (1400, 31, 4100, 3), (1400, 4100, 63, 3)])
+@pytest.mark.parametrize("what", ["", "large", "beyond", "zero rows", "rows", "columns", "outlier", "all zero"])
+def test_split_operands_scales(T, din, dout, r, what):
+    ins, s = make(T, din, dout, r), 1.5
+    _scale(ins, what)
+    dev = [t.cuda() for t in ins]
+    outs = [torch.empty(*size, device="cuda") for size in ((T, dout), (T, din), (r, din), (dout, r))]
+    step(dev, s, outs, torch.empty_like(dev[2]), torch.empty_like(dev[3]))
+    X, W, A, B, dY = (t.double() for t in dev)
+    for k, o, main, low in (("Y", outs[0], X @ W.T, s * (X @ A.T) @ B.T), ("dX", outs[1], dY @ W, s * (dY @ B) @ A)):
+        err = o.double() - (main + low)
+        for dim in (0, 1):
+            # each term strays by the tolerance of its own norm; the two may cancel (beside an outlier they do, in a few entries)
+            bound = tol(T, din, dout) * (main.norm(dim=dim) + low.norm(dim=dim))
+            assert bool((err.norm(dim=dim) <= 2 * bound).all()), (k, dim)
