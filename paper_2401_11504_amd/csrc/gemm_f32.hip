@@ -3,7 +3,7 @@
 //   F32_KK  A [M, K], B [N, K]: the contraction is contiguous in both          (X A^T;  X W^T + H B^T)
 //   F32_KN  A [M, K], B [K, N]                                                 (dY B;   dY W + dH A)
 //   F32_MN  A [K, M], B [K, N]                                                 (dH^T X; dY^T H)
-// Small ones go through the fp32 matrix instructions (f32_group_kernel), large ones through the 16-bit ones with every operand cut into
+// Small ones go through the fp32 matrix instructions (f32_direct_kernel, f32_group_kernel), large ones through the 16-bit ones with every operand cut into
 // two or three parts (f32_split_kernel); f32_cost holds what the line between them was timed on.
 //
 // v_mfma_f32_16x16x4_f32 adds its four products one after another, each as one fused multiply-add: an output is a chain
@@ -16,7 +16,7 @@
 // undone).  Neither is transposed on the way.
 //
 // The bound is the matrix unit: 256 flop per clock and CU, a sixteenth of the bf16 rate, so that LDS reads are cheap beside
-// it and tiles staged through registers are enough.  128 tokens, 256 x 256, rank 8: 36 us, of which the two kernels are 15.
+// it and tiles staged through registers are enough where the chip is full.
 #include "kernels.h"
 #include "tiles.h"
 #include <type_traits>
@@ -122,10 +122,10 @@ __device__ __forceinline__ void f32_fragments(const float* tile, int row0, int k
     }
 }
 
-template <int BM, int BN, int BKF, int PF, bool WIDE, bool AKC, bool BKC, bool PAST = false>
+template <int BM, int BN, int BKF, bool WIDE, bool AKC, bool BKC, bool PAST = false>
 __device__ __forceinline__ void f32_tile(const F32Product& q, int m0, int n0, float* smem, int tid) {
     using T = F32Tile<BM, BN, BKF>;
-    constexpr int FM = T::FM, FN = T::FN, KS = BKF / 16;
+    constexpr int FM = T::FM, FN = T::FN, KS = BKF / 16, PF = 2;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, g = lane >> 4;
     float *sA = smem, *sB = smem + 3 * T::SA;
@@ -168,10 +168,8 @@ __device__ __forceinline__ void f32_tile(const F32Product& q, int m0, int n0, fl
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        using S2 = std::integral_constant<int, 2>; using S3 = std::integral_constant<int, 3>;
         load(S0{}, 0);
         load(S1{}, 1);
-        if constexpr (PF == 4) { load(S2{}, 2); load(S3{}, 3); }
         park(S0{}, 0, 0);
         load(S0{}, PF);
         park(S1{}, 1, 1);
@@ -206,16 +204,8 @@ __device__ __forceinline__ void f32_tile(const F32Product& q, int m0, int n0, fl
         for (; t + PF <= nk; t += PF) {
             step(S0{}, t);
             step(S1{}, t + 1);
-            if constexpr (PF == 4) {
-                step(S2{}, t + 2);
-                step(S3{}, t + 3);
-            }
         }
         if (t < nk) step(S0{}, t);
-        if constexpr (PF == 4) {
-            if (t + 1 < nk) step(S1{}, t + 1);
-            if (t + 2 < nk) step(S2{}, t + 2);
-        }
         __syncthreads();                          // the places of the ring are free for the next term
         const float alpha = term ? q.alpha2 : q.alpha;
 
@@ -292,7 +282,7 @@ __device__ __forceinline__ void f32_max_scan(const F32MaxScan& sc, int w, float*
     if (tid == 0) sc.out[w] = top;
 }
 
-template <int BM, int BN, int BKF, int PF, bool WIDE>
+template <int BM, int BN, int BKF, bool WIDE>
 __global__ __launch_bounds__(256, 2) void f32_group_kernel(F32Batch grp) {
     extern __shared__ __align__(16) float smem_f32[];
     const int b = blockIdx.x;
@@ -309,9 +299,171 @@ __global__ __launch_bounds__(256, 2) void f32_group_kernel(F32Batch grp) {
     const int c = id & 7, per = n >> 3, tile = c * per + min(c, n & 7) + (id >> 3);
     const int im = tile % q.tiles_m, in = tile / q.tiles_m, tid = threadIdx.x;
     constexpr int MM = F32_MN_TILE(BM), MN = F32_MN_TILE(BN);
-    if (q.kind == F32_KK) f32_tile<BM, BN, BKF, PF, WIDE, true, true>(q, im * BM, in * BN, smem_f32, tid);
-    else if (q.kind == F32_KN) f32_tile<BM, BN, BKF, PF, WIDE, true, false>(q, im * BM, in * BN, smem_f32, tid);
-    else f32_tile<MM, MN, BKF, PF, WIDE, false, false>(q, im * MM, in * MN, smem_f32, tid);
+    if (q.kind == F32_KK) f32_tile<BM, BN, BKF, WIDE, true, true>(q, im * BM, in * BN, smem_f32, tid);
+    else if (q.kind == F32_KN) f32_tile<BM, BN, BKF, WIDE, true, false>(q, im * BM, in * BN, smem_f32, tid);
+    else f32_tile<MM, MN, BKF, WIDE, false, false>(q, im * MM, in * MN, smem_f32, tid);
+}
+
+// ---------------------------------------------------------------- small steps: fragments straight from memory
+// 16 F x 16 F outputs per workgroup of eight waves; wave w takes pieces w, w + 8, .. of sixteen contraction elements, and the eight sums are
+// added in that order through LDS.  Each wave loads its own fragments, PF pieces ahead, with no LDS, no barrier and next to no address
+// arithmetic in the loop (a base that moves in scalar registers, lane offsets that stay).  A small step is two chains over the whole
+// width on few CUs.  Staged through LDS in 32x32 tiles with a barrier per 64 elements they took 11.5 ns an element, 2700 clocks of which
+// 1024 were matrix instructions; this way it is 7 in 32x32 tiles and 3.6 in 16x16 ones, which is what a CU gets of its operands (40 to 60
+// GB/s from beyond its L2), so that the smaller tile, on more CUs, is the faster one until the chip is full.  (Fragments through LDS of the
+// wave's own, for loads of whole 64-byte runs, changed nothing; two groups of four waves in the staged kernel 9 ns, and slower where the
+// chip is full.)  us: 128 tokens, 256 x 256, rank 8 36 -> 31; 37, 3349 x 142, rank 16 92 -> 46; 36, 563 x 4006, rank 4 100 -> 51.
+constexpr int DIRECT_WAVES = 8;
+
+template <int F, int PF, bool AKC, bool BKC>
+__device__ __forceinline__ void f32_direct_sum(const float* A, long lda, const float* B, long ldb, int rows_a, int rows_b, int K,
+                                               f32x4_t (&acc)[F][F], int wave, int lane) {
+    const int l16 = lane & 15, g = lane >> 4;
+    // byte offsets of fragment i within a piece; rows (columns) past the end are the last one again, and only feed what is never stored
+    unsigned oa[F], ob[F];
+#pragma unroll
+    for (int i = 0; i < F; ++i) {
+        const unsigned ra = min(16 * i + l16, rows_a - 1), rb = min(16 * i + l16, rows_b - 1);
+        oa[i] = (AKC ? ra * (unsigned)lda + 4 * g : 4 * g * (unsigned)lda + ra) * 4;
+        ob[i] = (BKC ? rb * (unsigned)ldb + 4 * g : 4 * g * (unsigned)ldb + rb) * 4;
+    }
+    float a[PF][F][4], b[PF][F][4];
+    auto fragments = [&](auto kc, const float* base, long ld, int k, const unsigned (&off)[F], float (&v)[F][4]) {
+        if constexpr (kc.value) {
+            const char* at = (const char*)(base + k);
+#pragma unroll
+            for (int i = 0; i < F; ++i) {
+                const f4u t = *(const f4u*)(at + off[i]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[i][e] = t[e];
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const char* at = (const char*)(base + (k + e) * ld);
+#pragma unroll
+                for (int i = 0; i < F; ++i) v[i][e] = *(const float*)(at + off[i]);
+            }
+        }
+    };
+    using KA = std::integral_constant<bool, AKC>;
+    using KB = std::integral_constant<bool, BKC>;
+    auto multiply = [&](int u) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < F; ++i)
+#pragma unroll
+                for (int j = 0; j < F; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u][j][e], a[u][i][e], acc[i][j], 0, 0, 0);
+    };
+    const int full = K / 16, mine = full > wave ? (full - wave + DIRECT_WAVES - 1) / DIRECT_WAVES : 0;
+    if (mine > 0) {
+        auto load = [&](int u, int t) {           // (past the wave's last piece: that one again, never multiplied)
+            const int k = 16 * (wave + DIRECT_WAVES * min(t, mine - 1));
+            fragments(KA{}, A, lda, k, oa, a[u]);
+            fragments(KB{}, B, ldb, k, ob, b[u]);
+        };
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            load(u, u);
+            __builtin_amdgcn_sched_barrier(0);    // (in this order: what a use waits for is counted)
+        }
+        int t = 0;
+        for (; t + PF <= mine; t += PF)
+#pragma unroll
+            for (int u = 0; u < PF; ++u) {
+                multiply(u);
+                load(u, t + u + PF);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+        for (int u = 0; u + 1 < PF; ++u)
+            if (t + u < mine) multiply(u);
+    }
+    const int rest = K - 16 * full;
+    if (rest > 0 && wave == full % DIRECT_WAVES) {
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                a[0][i][e] = b[0][i][e] = 0.f;
+                if (4 * g + e < rest) {
+                    a[0][i][e] = *(const float*)((const char*)(A + (AKC ? 16 * full + e : (16 * full + e) * lda)) + oa[i]);
+                    b[0][i][e] = *(const float*)((const char*)(B + (BKC ? 16 * full + e : (16 * full + e) * ldb)) + ob[i]);
+                }
+            }
+        multiply(0);
+    }
+}
+
+template <int F, int PF, bool AKC, bool BKC>
+__device__ __forceinline__ void f32_direct_tile(const F32Product& q, int m0, int n0, float* smem) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, g = lane >> 4;
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};             // of the first STORING threads: four columns of a row
+    constexpr int SIDE = 16 * F, LD = SIDE + 4, STORING = SIDE * SIDE / 4;
+    const int row = tid / (SIDE / 4), col = tid % (SIDE / 4) * 4;
+#pragma unroll 1
+    for (int term = 0; term < (q.K2 > 0 ? 2 : 1); ++term) {
+        const float *A = term ? q.A2 : q.A, *B = term ? q.B2 : q.B;
+        const long lda = term ? q.lda2 : q.lda, ldb = term ? q.ldb2 : q.ldb;
+        f32x4_t acc[F][F];
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+            for (int j = 0; j < F; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        f32_direct_sum<F, PF, AKC, BKC>(A + (AKC ? m0 * lda : m0), lda, B + (BKC ? n0 * ldb : n0), ldb, q.M - m0, q.N - n0,
+                                     term ? q.K2 : q.K, acc, wave, lane);
+        if (term) __syncthreads();                // the other term's sums have been read
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+            for (int j = 0; j < F; ++j)           // (B first in the matrix instruction: a lane has row l16 of A's fragment, columns 4 g .. of B's)
+                *(f32x4_t*)(smem + (wave * SIDE + 16 * i + l16) * LD + 16 * j + 4 * g) = acc[i][j];
+        __syncthreads();
+        if (tid < STORING) {
+            f32x4_t sum = *(const f32x4_t*)(smem + row * LD + col);
+#pragma unroll
+            for (int w = 1; w < DIRECT_WAVES; ++w) sum += *(const f32x4_t*)(smem + (w * SIDE + row) * LD + col);
+            const float alpha = term ? q.alpha2 : q.alpha;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = term ? v[e] + alpha * sum[e] : alpha * sum[e];
+        }
+    }
+    const int m = m0 + row, n = n0 + col;
+    if (tid >= STORING || m >= q.M || n >= q.N) return;
+    const long at = (long)m * q.ldc + n;
+    if (n + 4 <= q.N) {
+        *(f4u*)(q.C + at) = v;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (n + e < q.N) q.C[at + e] = v[e];
+    }
+    if (q.p_new) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (n + e < q.N) q.p_new[at + e] = adamw_first(q.p_old[at + e], v[e], q.opt);
+    }
+}
+
+template <int F>
+__global__ __launch_bounds__(DIRECT_WAVES * 64, 4) void f32_direct_kernel(F32Batch grp) {
+    __shared__ __align__(16) float sums[DIRECT_WAVES * 16 * F * (16 * F + 4)];
+    const int b = blockIdx.x;
+    if (b >= grp.scan0) {
+        f32_max_scan(grp.scan, b - grp.scan0, sums);
+        return;
+    }
+    int k = 0;
+    while (k + 1 < grp.n && b >= grp.p[k + 1].tile0) ++k;
+    const F32Product& q = grp.p[k];
+    const int n = q.tiles_m * q.tiles_n, id = b - q.tile0;      // (the same order of tiles as in f32_group_kernel)
+    const int c = id & 7, per = n >> 3, tile = c * per + min(c, n & 7) + (id >> 3);
+    const int m0 = tile % q.tiles_m * (16 * F), n0 = tile / q.tiles_m * (16 * F);
+    if (q.kind == F32_KK) f32_direct_tile<F, 4, true, true>(q, m0, n0, sums);
+    else if (q.kind == F32_KN) f32_direct_tile<F, 4, true, false>(q, m0, n0, sums);
+    else f32_direct_tile<F, 3, false, false>(q, m0, n0, sums);
 }
 
 // ---------------------------------------------------------------- split operands on the bf16 matrix instructions
@@ -805,7 +957,7 @@ __device__ __forceinline__ void split_or_f32_tile(const F32Product& q, int m0, i
 #pragma unroll 1
     for (int m = 0; m < BM / 2; m += B) {
         if (m) __syncthreads();
-        f32_tile<B, BN, BKF, 2, false, AKC, BKC, true>(q, m0 + half * (BM / 2) + m, n0,
+        f32_tile<B, BN, BKF, false, AKC, BKC, true>(q, m0 + half * (BM / 2) + m, n0,
                                                        (float*)smem + half * F32Tile<B, BN, BKF>::LDS_FLOATS, tid & 255);
     }
 }
@@ -850,17 +1002,26 @@ static hipError_t place_f32(F32Batch& grp, int* n_tiles) {
     *n_tiles = (int)tiles;
     return hipSuccess;
 }
-template <int BM, int BN, int BKF, int PF, bool WIDE = false>
+template <int BM, int BN, int BKF, bool WIDE = false>
 static hipError_t run_f32(F32Batch& grp, hipStream_t s) {
     int tiles = 0;
     hipError_t e = place_f32<BM, BN>(grp, &tiles);
     if (e != hipSuccess) return e;
     const int lds = F32Tile<BM, BN, BKF>::LDS_FLOATS * (int)sizeof(float);
-    auto kern = f32_group_kernel<BM, BN, BKF, PF, WIDE>;
+    auto kern = f32_group_kernel<BM, BN, BKF, WIDE>;
     e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     grp.scan0 = tiles;
     kern<<<tiles + grp.scan.first[F32_SCAN_MAX], 256, lds, s>>>(grp);
+    return hipGetLastError();
+}
+template <int F>
+static hipError_t run_direct(F32Batch& grp, hipStream_t s) {
+    int tiles = 0;
+    hipError_t e = place_f32<16 * F, 16 * F>(grp, &tiles);
+    if (e != hipSuccess) return e;
+    grp.scan0 = tiles;
+    f32_direct_kernel<F><<<tiles + grp.scan.first[F32_SCAN_MAX], DIRECT_WAVES * 64, 0, s>>>(grp);
     return hipGetLastError();
 }
 template <int BM, int BN, int WM, int WN>
@@ -877,11 +1038,12 @@ static hipError_t run_split(F32Batch& grp, hipStream_t s) {
 }
 
 // What a launch takes: the longest chain, or all contraction tiles spread over 256 CUs, whichever is longer, per instance: us per
-// contraction element of one chain and of 256 tiles, and what it takes besides.  Fitted to steps of 54 shapes, 33 to 1400 tokens, widths
-// 100 to 5000, ranks 4 to 64, with each instance forced: what is picked is the fastest of the four at all of them.
-// Tokens x d_in x d_out, us in 32x32, 64x64 (fp32), 128x128, 256x128 (split): 128x256x256 37, 42, 43, 48; 128x4096x4096 192, 179, 168, 219;
-// 1400x300x4000 235, 180, 162, 213; 333x4096x4096 406, 342, 175, 221; 700x2500x2500 335, 271, 143, 154; 1027x2050x2050 346, 280, 167, 141;
-// 1024x4096x4096 1038, 771, 324, 285.
+// contraction element of one chain and of 256 tiles, and what it takes besides.  Fitted to steps of 66 shapes, 33 to 8200 tokens, widths
+// 40 to 5000, ranks 4 to 64, with each instance forced (the low-rank products in 16x16 tiles): what is picked takes 0.5 % longer than the
+// fastest on average, 8 % at worst.  Tokens x d_in x d_out, us in 16x16, 32x32 (direct), 64x64 (fp32), 128x128, 256x128 (split):
+// 128x256x256 31, 33, 39, 41, 47; 36x563x4006 51, 65, 138, 131, 180; 300x1000x1000 65, 55, 61, 61, 75; 128x4096x4096 259, 158, 146, 150, 199;
+// 1400x300x4000 241, 165, 158, 135, 184; 333x4096x4096 642, 368, 300, 153, 198; 1024x4096x4096 1885, 1005, 678, 318, 276.
+constexpr int F32_FIRST_SPLIT = 3;      // of the five
 struct F32Cost { int bm, bn; double chain, tiles, fixed; };
 static double f32_cost(const F32Batch& grp, const F32Cost& c) {
     double longest = 0, all = 0;
@@ -910,16 +1072,17 @@ static int arrange_f32(const F32Product* prods, int n, F32Batch& grp) {
         wide |= q.lda > (1L << 22) || q.ldb > (1L << 22) || q.lda2 > (1L << 22) || q.ldb2 > (1L << 22);
     }
     if (wide) return -1;
-    const F32Cost costs[] = {{32, 32, 0.0035, 0.0076, 0.4}, {64, 64, 0.0200, 0.0219, 2.3}, {128, 128, 0.0162, 0.0285, 0.0}, {256, 128, 0.0344, 0.0439, 2.7}};
+    const F32Cost costs[] = {{16, 16, 0.0036, 0.0024, -1.0}, {32, 32, 0.0045, 0.0061, 0.4}, {64, 64, 0.0162, 0.0185, 2.3},
+                             {128, 128, 0.0198, 0.0285, 1.8}, {256, 128, 0.0344, 0.0439, 2.7}};
     int best = 0;
-    for (int c = 1; c < 4; ++c)
+    for (int c = 1; c < 5; ++c)
         if (f32_cost(grp, costs[c]) < f32_cost(grp, costs[best])) best = c;
     return best;
 }
 
 bool gemm_f32_wants_max(const F32Product* prods, int n) {
     F32Batch grp;
-    return n >= 1 && n <= F32_GROUP_MAX && arrange_f32(prods, n, grp) >= 2;
+    return n >= 1 && n <= F32_GROUP_MAX && arrange_f32(prods, n, grp) >= F32_FIRST_SPLIT;
 }
 
 hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s, const F32MaxScan* scan) {
@@ -935,11 +1098,12 @@ hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s, 
         t64 += (long)cdiv(q.M, 64) * cdiv(q.N, 64);
     }
     // (rows that wide are long chains on few tiles, or next to no arithmetic: no 128-wide instance for them)
-    if (best < 0) return t64 >= 256 ? run_f32<64, 64, 32, 2, true>(grp, s) : run_f32<32, 32, 64, 2, true>(grp, s);
-    switch (scan && best > 1 ? 1 : best) {    // (what scans is a launch of low-rank products: 64 columns at most, as a rule)
-        case 0: return run_f32<32, 32, 64, 4>(grp, s);
-        case 1: return run_f32<64, 64, 32, 2>(grp, s);
-        case 2: return run_split<128, 128, 2, 4>(grp, s);
+    if (best < 0) return t64 >= 256 ? run_f32<64, 64, 32, true>(grp, s) : run_f32<32, 32, 64, true>(grp, s);
+    switch (scan && best >= F32_FIRST_SPLIT ? F32_FIRST_SPLIT - 1 : best) {   // (the split kernel does not scan; low-rank products are not for it)
+        case 0: return run_direct<1>(grp, s);
+        case 1: return run_direct<2>(grp, s);
+        case 2: return run_f32<64, 64, 32>(grp, s);
+        case F32_FIRST_SPLIT: return run_split<128, 128, 2, 4>(grp, s);
         default: return run_split<256, 128, 4, 2>(grp, s);
     }
 }

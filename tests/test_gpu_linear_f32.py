@@ -211,3 +211,20 @@ def test_split_operands_scales(T, din, dout, r, what):
             # each term strays by the tolerance of its own norm; the two may cancel (beside an outlier they do, in a few entries)
             bound = tol(T, din, dout) * (main.norm(dim=dim) + low.norm(dim=dim))
             assert bool((err.norm(dim=dim) <= 2 * bound).all()), (k, dim)
+
+
+# Fragments straight from memory: both tiles (16x16 for the first five, 32x32 for the main products of the others), sides one off a multiple of
+# the tile, contractions shorter than one piece of sixteen elements, one off it, and of fewer pieces than there are waves.
+@pytest.mark.parametrize("T,din,dout,r", [(17, 15, 33, 1), (16, 128, 16, 16), (31, 129, 47, 17), (48, 127, 2000, 5), (2, 3000, 1, 2),
+                                          (1157, 377, 486, 64), (1382, 182, 120, 33), (631, 389, 961, 4), (1400, 16, 96, 15)])
+def test_direct_fragments(T, din, dout, r):
+    ins, s = make(T, din, dout, r), 1.5
+    dev = [t.cuda() for t in ins]
+    shapes = ((T, dout), (T, din), (r, din), (dout, r))
+    flat = [torch.full((a * b + 64,), 3.0, device="cuda") for a, b in shapes]
+    outs = [f[:a * b].view(a, b) for f, (a, b) in zip(flat, shapes)]
+    step(dev, s, outs, torch.empty_like(dev[2]), torch.empty_like(dev[3]))
+    ref = reference(ins, s)
+    for k, o, f in zip(("Y", "dX", "dA", "dB"), outs, flat):
+        assert (o.cpu().double() - ref[k]).norm() < tol(T, din, dout) * ref[k].norm(), k
+        assert bool((f[o.numel():] == 3.0).all()), k
