@@ -311,8 +311,8 @@ tl_status tl_linear_step(const float* X, const float* W, const float* A, const f
 /*
  * tl_linear_step for callers that cannot allocate device memory: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments, results and errors as tl_linear_step, but the scratch that call
- * takes from hipMalloc (H = X A^T and dH, fp32 [T, r] each) lives in a buffer of 2^20 floats (4 MiB, and 1 KiB beside it for
- * the call's own use) that is part of the library's image: every GPU the library runs on holds one until the process ends, and this call performs no allocation or release of any kind.
+ * takes from hipMalloc (H = X A^T and dH, fp32 [T, r] each) lives in a buffer of 2^20 floats (4 MiB) that is part of the library's image: every GPU the library runs on holds one
+ * until the process ends, and this call performs no allocation or release of any kind.
  * TL_ERR_SHAPE if 2 T r (+ 2 r (d_in + d_out) with apply_adamw), each part rounded up to 64 floats, exceeds 2^20 floats.
  * All calls on one GPU share that buffer: it holds the previous call's values on entry (the call
  * writes what it reads), and two calls that overlap in time on one GPU race -- the caller serialises them.

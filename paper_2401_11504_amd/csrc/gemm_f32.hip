@@ -3,8 +3,8 @@
 //   F32_KK  A [M, K], B [N, K]: the contraction is contiguous in both          (X A^T;  X W^T + H B^T)
 //   F32_KN  A [M, K], B [K, N]                                                 (dY B;   dY W + dH A)
 //   F32_MN  A [K, M], B [K, N]                                                 (dH^T X; dY^T H)
-// Small ones go through the fp32 matrix instructions (f32_direct_kernel, f32_group_kernel), large ones through the 16-bit ones with every operand cut into
-// two or three parts (f32_split_kernel); f32_cost holds what the line between them was timed on.
+// Small ones go through the fp32 matrix instructions (f32_direct_kernel, f32_group_kernel), large ones through the bf16 ones with every operand cut into
+// three parts (f32_split_kernel); f32_cost holds what the line between them was timed on.
 //
 // v_mfma_f32_16x16x4_f32 adds its four products one after another, each as one fused multiply-add: an output is a chain
 // fma(a[k], b[k], ..) over k, the same value wherever its tile boundaries lie.  (The low-rank term is a chain of its own, added to the
@@ -23,15 +23,11 @@
 #include <utility>
 
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // rows start at any multiple of a float
 
 struct F32Batch {
     F32Product p[F32_GROUP_MAX];
     int n;
-    F32MaxScan scan;      // workgroups behind those of the products
-    int scan0;
 };
 
 // The gradients of the factors (F32_MN) have a side of rank elements: 64 wide at most.  A few full tiles of them beside a
@@ -254,42 +250,10 @@ __device__ __forceinline__ void f32_tile(const F32Product& q, int m0, int n0, fl
     }
 }
 
-// The largest magnitude of a share of an array (NaN counts as nothing): read once, sixteen floats a thread in flight.
-__device__ __forceinline__ void f32_max_scan(const F32MaxScan& sc, int w, float* red) {
-    int k = 0;
-    while (k + 1 < F32_SCAN_MAX && w >= sc.first[k + 1]) ++k;
-    const int wgs = sc.first[k + 1] - sc.first[k], tid = threadIdx.x, nt = blockDim.x;
-    const float* p = sc.p[k];
-    const size_t quads = sc.n[k] / 4, per = (quads + wgs - 1) / wgs, q0 = per * (w - sc.first[k]), q1 = q0 + per < quads ? q0 + per : quads;
-    float top = 0.f;
-    size_t i = q0 + tid;
-    for (; i + 3 * nt < q1; i += 4 * nt) {
-        f4u v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = *(const f4u*)(p + 4 * (i + nt * j));
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) top = fmaxf(top, fabsf(v[j][e]));
-    }
-    for (; i < q1; i += nt) {
-        const f4u v = *(const f4u*)(p + 4 * i);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) top = fmaxf(top, fabsf(v[e]));
-    }
-    if (w == sc.first[k] && 4 * quads + tid < sc.n[k]) top = fmaxf(top, fabsf(p[4 * quads + tid]));
-    top = block_max(top, red);
-    if (tid == 0) sc.out[w] = top;
-}
-
 template <int BM, int BN, int BKF, bool WIDE>
 __global__ __launch_bounds__(256, 2) void f32_group_kernel(F32Batch grp) {
     extern __shared__ __align__(16) float smem_f32[];
     const int b = blockIdx.x;
-    if (b >= grp.scan0) {
-        f32_max_scan(grp.scan, b - grp.scan0, smem_f32);
-        return;
-    }
     int k = 0;
     while (k + 1 < grp.n && b >= grp.p[k + 1].tile0) ++k;
     const F32Product& q = grp.p[k];
@@ -451,10 +415,6 @@ template <int F>
 __global__ __launch_bounds__(DIRECT_WAVES * 64, 4) void f32_direct_kernel(F32Batch grp) {
     __shared__ __align__(16) float sums[DIRECT_WAVES * 16 * F * (16 * F + 4)];
     const int b = blockIdx.x;
-    if (b >= grp.scan0) {
-        f32_max_scan(grp.scan, b - grp.scan0, sums);
-        return;
-    }
     int k = 0;
     while (k + 1 < grp.n && b >= grp.p[k + 1].tile0) ++k;
     const F32Product& q = grp.p[k];
@@ -467,9 +427,6 @@ __global__ __launch_bounds__(DIRECT_WAVES * 64, 4) void f32_direct_kernel(F32Bat
 }
 
 // ---------------------------------------------------------------- split operands on the bf16 matrix instructions
-// The main terms X W^T and dY W go through fp16 halves (half_tile, below); what follows is the way of the other products, and of a
-// workgroup whose operands the halves do not hold.
-//
 // The same products with every operand cut into three bf16 parts, x = x1 + x2 + x3 (eight bits of the fraction each, by
 // truncation: nothing is lost and nothing overflows), and a b taken as a1 b3 + a1 b2 + a1 b1 + a2 b2 + a2 b1 + a3 b1 in fp32
 // accumulators.  What is left out, a2 b3 + a3 b2 + a3 b3, is 2^-24 of a product on average, half an ulp, and the accumulator is
@@ -481,12 +438,16 @@ __global__ __launch_bounds__(DIRECT_WAVES * 64, 4) void f32_direct_kernel(F32Bat
 // (A matrix instruction of 16 clocks hides two vector operations, from whichever wave: twice as many waves that cut in one go and multiply in
 // another were slower, 465 against 430 us for a step of 1024 tokens, 4096 x 4096, rank 64; in fp32 tiles of 128x128 it was 690.)
 //
+// (Two fp16 halves an operand, scaled by a power of two for the whole array, take three products instead of six and 280 us instead of 390.
+// But fp16 has five bits of exponent: an element below 2^-17 of the array's largest loses bits, and is nothing below 2^-40, where it may be all that an output is made of --
+// the other operand may be zero, or small, where this one is large.  To find that out takes a look at every element, and among normal draws some always lie that low.)
+//
 // The parts say nothing about an operand that is infinite (inf * 0 for a part that is zero) or whose last part is below the
 // bf16 range (|x| < 2^-110): a workgroup that meets one starts its outputs again with f32_tile, in two halves of 256 threads.
 //
 // Order of the 32 contraction elements of a tile within the matrix instruction: lane group g takes 4 g .. 4 g + 3 and
 // 16 + 4 g .. 16 + 4 g + 3, in both operands.
-constexpr int SPLIT_BK = 32, SPLIT_NT = 512, SPLIT_HEAD = 64;     // (bytes of LDS ahead of the planes)
+constexpr int SPLIT_BK = 32, SPLIT_NT = 512, SPLIT_HEAD = 16;     // (bytes of LDS ahead of the planes)
 // One operand: memory -> registers (`N` items of four floats a thread) -> three planes of LDS per tile.
 //   KC: [row][32], 8-byte piece p of a row (elements 4 p .. 4 p + 3) as half p / 4 of 16-byte chunk (p % 4) ^ (row / 4 % 4), so that
 //       a lane's elements are one chunk, sixteen rows' chunks lie in distinct banks, and so do the pieces that are written
@@ -576,205 +537,6 @@ struct SplitTile {
     static constexpr int LDS_BYTES = MAX(SPLIT_HEAD + 2 * STAGE * (int)sizeof(bf16_t), F32_BYTES);
 };
 
-// ---------------------------------------------------------------- main terms: two fp16 halves an operand
-// x 2^e = h + l, both fp16 (eleven bits and eleven more with the sign of l), e such that the operand's largest magnitude is 2^14 .. 2^15;
-// a b = (ha lb + ha hb + la hb) 2^-(ea + eb).  What is left out, la lb, and what l rounds away are 2^-25 of a product on average.
-// Half the matrix instructions of the three bf16 parts, and half the cutting: 1024 tokens, 4096 x 4096, rank 64, the launch 345 -> 236 us,
-// the step 411 -> 285, Y 1.15e-6 (chain of fp32 products), 1.05e-6 (bf16 parts), 7.4e-7 (halves) from fp64; 1400, 300 x 4000 dX all 1.1e-6,
-// Y 3.1e-7; 1024 x 1024 x 1024 Y 5.7e-7 (chain), 3.8e-7.  3 x 64 matrix instructions of 16 clocks a tile and SIMD are 100 us of it; the
-// operands of a 256x128 tile in fp32 come at 50 GB/s and CU, near what a CU gets while they arrive from HBM (60).
-//
-// Below 2^-2 (2^-17 of the largest magnitude) l loses bits to fp16's range: the error is 2^-25 of it then, 2^-40 of the operand's
-// largest.  That is nothing beside a row (column) that has larger elements, and everything in one that has not.  So each thread keeps the
-// largest magnitude of what it brings of each row or column: where one is neither zero nor above 2^-10 of the operand's, its row may be
-// held to less than 2^-29 of itself, and the workgroup starts again with the bf16 parts.  So it does, at once, where the largest
-// magnitude is infinite or below 2^-100.
-//
-// The largest magnitudes come from the launch of the low-rank products (F32MaxScan), which leaves half of the chip idle: 96 MB read there
-// take it from 36 to 43 us.
-//
-// Four floats times a power of two, as fp16 and what is left, fp16 too.
-struct HalfParts {
-    unsigned x[2][2];
-    __device__ __forceinline__ void pair(unsigned b0, unsigned b1, int e, float scale) {
-        const float v0 = __uint_as_float(b0), v1 = __uint_as_float(b1);
-        typedef float f2 __attribute__((ext_vector_type(2)));
-        const half2_t h = __builtin_convertvector((f2{v0 * scale, v1 * scale}), half2_t);
-        const half2_t l = __builtin_convertvector((f2{fmaf(v0, scale, -(float)h[0]), fmaf(v1, scale, -(float)h[1])}), half2_t);
-        x[0][e] = __builtin_bit_cast(unsigned, h);
-        x[1][e] = __builtin_bit_cast(unsigned, l);
-    }
-    __device__ __forceinline__ void put(bf16_t* dst, int p) const { *(uint2*)dst = make_uint2(x[p][0], x[p][1]); }
-};
-// The power of two that takes `top` to 2^14 .. 2^15, by its exponent; 0x7fffffff where there is none.
-__device__ __forceinline__ int half_exponent(float top) {
-    if (top == 0.f) return 0;
-    return top >= 0x1p-100f && top <= 3.4028234663852886e38f ? 14 + 127 - (int)(__float_as_uint(top) >> 23) : 0x7fffffff;
-}
-
-// The thread's index as a value that nothing ahead of here can be computed from: each part of a kernel works out its own offsets, rather
-// than have those of all later parts held (and spilled) through the loops of the earlier ones.
-__device__ __forceinline__ int fresh_tid() {
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    return tid & (SPLIT_NT - 1);
-}
-
-// The main term of BM x BN outputs: the loop of split_tile with two planes instead of three, and the loads two tiles further ahead
-// (a tile takes half the time that it takes there).  false: the halves do not hold an operand.
-template <int BM, int BN, int WM, int WN, bool AKC, bool BKC>
-__device__ __forceinline__ bool half_tile(const F32Product& q, int m0, int n0, unsigned char* smem, f32x4_t (&acc)[BM / WM / 16][BN / WN / 16]) {
-    constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
-    using OA = SplitOperand<BM, AKC>;
-    using OB = SplitOperand<BN, BKC>;
-    constexpr int A_ELEMS = 2 * OA::PLANE, STAGE = A_ELEMS + 2 * OB::PLANE, NG = FM * FN, NMF = 3 * NG, NI = OA::N + OB::N, NS = 4 * NI;
-    constexpr int AT_BARRIER = NMF - (NMF + 7) / 8, SLICED = NMF * 3 / 4;
-    const int tid = fresh_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN, M = q.M, N = q.N, K = q.K;
-    int* flag = (int*)smem;
-    float* red = (float*)(smem + 16);
-    bf16_t* planes = (bf16_t*)(smem + SPLIT_HEAD);
-    const float *A = q.A, *B = q.B;
-    const long lda = q.lda, ldb = q.ldb;
-    auto tile_k = [](int t) { return (int)((unsigned)t * SPLIT_BK); };
-    OA oa;
-    OB ob;
-    oa.init(lda, tid);
-    ob.init(ldb, tid);
-    u32x4_t r[2][NI];
-    auto load_all = [&](auto set, int t) {
-        const auto rsa = OA::rsrc(A, lda, m0, M, tile_k(t), K);
-        const auto rsb = OB::rsrc(B, ldb, n0, N, tile_k(t), K);
-#pragma unroll
-        for (int i = 0; i < NI; ++i) r[set.value][i] = i < OA::N ? oa.load(rsa, i, lda) : ob.load(rsb, i - OA::N, ldb);
-    };
-    using S0 = std::integral_constant<int, 0>; using S1 = std::integral_constant<int, 1>;
-    load_all(S0{}, 0);
-    load_all(S1{}, 1);
-    // the largest magnitude of each operand, from that of its shares
-    {
-        const bool b = tid >= SPLIT_NT / 2;
-        const int at = tid & (SPLIT_NT / 2 - 1);
-        static_assert(F32_SCAN_WGS <= SPLIT_NT / 2, "one share a thread");
-        const float v = wave_max(at < (b ? q.nbmax : q.namax) ? (b ? q.bmax : q.amax)[at] : 0.f);
-        if (lane == 0) red[wave] = v;
-        if (tid == 0) *flag = 0;
-    }
-    __syncthreads();
-    const float top_a = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), top_b = fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]));
-    const int ea = half_exponent(top_a), eb = half_exponent(top_b);
-    if (ea == 0x7fffffff || eb == 0x7fffffff) return false;
-    const float sa = __uint_as_float((unsigned)(127 + ea) << 23), sb = __uint_as_float((unsigned)(127 + eb) << 23);
-    // largest magnitudes of what this thread brings: of a row (one per item) or a column (one per element)
-    float seen_a[AKC ? OA::N : 4] = {}, seen_b[BKC ? OB::N : 4] = {};
-    HalfParts parts;
-    auto cut = [&](auto set, auto ic, int y) {          // elements 2 y, 2 y + 1 of item i
-        constexpr int i = ic.value;
-        const unsigned b0 = r[set.value][i][2 * y], b1 = r[set.value][i][2 * y + 1];
-        const float m0 = fabsf(__uint_as_float(b0)), m1 = fabsf(__uint_as_float(b1));
-        if constexpr (i < OA::N) {
-            if constexpr (AKC) seen_a[i] = fmaxf(fmaxf(seen_a[i], m0), m1);
-            else { seen_a[2 * y] = fmaxf(seen_a[2 * y], m0); seen_a[2 * y + 1] = fmaxf(seen_a[2 * y + 1], m1); }
-        } else {
-            if constexpr (BKC) seen_b[i - OA::N] = fmaxf(fmaxf(seen_b[i - OA::N], m0), m1);
-            else { seen_b[2 * y] = fmaxf(seen_b[2 * y], m0); seen_b[2 * y + 1] = fmaxf(seen_b[2 * y + 1], m1); }
-        }
-        parts.pair(b0, b1, y, i < OA::N ? sa : sb);
-    };
-    auto put = [&](bf16_t* stage, auto ic) {
-        constexpr int i = ic.value;
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-            parts.put(i < OA::N ? stage + (oa.dst + p * OA::PLANE + i * OA::STEP * OA::LD)
-                                : stage + (A_ELEMS + ob.dst + p * OB::PLANE + (i - OA::N) * OB::STEP * OB::LD), p);
-    };
-    auto mask = [&](auto set, int left) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i) r[set.value][i] = i < OA::N ? OA::mask(r[set.value][i], left, tid) : OB::mask(r[set.value][i], left, tid);
-    };
-    const int a_off = OA::lane_offset(wm * TM, lane), b_off = A_ELEMS + OB::lane_offset(wn * TN, lane);
-    bf16x8_t fa[2][FM], fb[2][FN];
-    auto read_a = [&](const bf16_t* stage, int s, int i) { fa[s][i] = OA::fragment(stage + a_off + s * OA::PLANE, i); };
-    auto read_b = [&](const bf16_t* stage, int s, int i) { fb[s][i] = OB::fragment(stage + b_off + s * OB::PLANE, i); };
-    if (K < SPLIT_BK) mask(S0{}, K);
-    unrolled<NI>([&](auto i) {
-        cut(S0{}, i, 0);
-        cut(S0{}, i, 1);
-        put(planes, i);
-    });
-    load_all(S0{}, 2);
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < FM; ++i) read_a(planes, 0, i);
-#pragma unroll
-    for (int i = 0; i < FN; ++i) read_b(planes, 1, i);
-    bf16_t *stage = planes, *other = planes + STAGE;
-    const int nk = (K + SPLIT_BK - 1) / SPLIT_BK;
-    auto step = [&](auto set, int t) {                  // set: where tile t + 1 is, and t + 3 goes
-        if (t + 2 >= nk) mask(set, K - tile_k(t + 1));
-        const auto rsa = OA::rsrc(A, lda, m0, M, tile_k(t + 3), K);
-        const auto rsb = OB::rsrc(B, ldb, n0, N, tile_k(t + 3), K);
-        auto slice = [&](auto xc) {
-            constexpr int i = xc.value / 4, y = xc.value % 4;
-            using I = std::integral_constant<int, i>;
-            if constexpr (y < 2) cut(set, I{}, y);
-            else if constexpr (y == 2) put(other, I{});
-            else if constexpr (i < OA::N) r[set.value][i] = oa.load(rsa, i, lda);
-            else r[set.value][i] = ob.load(rsb, i - OA::N, ldb);
-        };
-        unrolled<NMF>([&](auto ec) {
-            constexpr int e = ec.value, gr = e / NG, x = e % NG, i = x / FN, jn = x % FN, left = NMF - AT_BARRIER;
-            constexpr int pa = gr == 2 ? 1 : 0, pb = gr == 0 ? 1 : 0;
-            acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, fb[pb][jn]), __builtin_bit_cast(half8_t, fa[pa][i]),
-                                                                acc[i][jn], 0, 0, 0);
-            unrolled<FN>([&](auto f) {
-                if constexpr (f.value == x && gr == 0) read_b(stage, 0, f.value);
-            });
-            unrolled<FM>([&](auto f) {
-                if constexpr (f.value * NG / FM == x && gr == 1) read_a(stage, 1, f.value);
-            });
-            unrolled<NS>([&](auto y) {
-                if constexpr (y.value * SLICED / NS == e) slice(y);
-            });
-            if constexpr (e + 1 == AT_BARRIER) {
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-            }
-            unrolled<FN>([&](auto f) {
-                if constexpr (AT_BARRIER - 1 + f.value * left / (FM + FN) == e) read_b(other, 1, f.value);
-            });
-            unrolled<FM>([&](auto f) {
-                if constexpr (AT_BARRIER - 1 + (FN + f.value) * left / (FM + FN) == e) read_a(other, 0, f.value);
-            });
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        bf16_t* const s = stage;
-        stage = other; other = s;
-    };
-    int t = 0;
-    for (; t + 2 <= nk; t += 2) {
-        step(S1{}, t);
-        step(S0{}, t + 1);
-    }
-    if (t < nk) step(S1{}, t);
-    bool small = false;
-#pragma unroll
-    for (float v : seen_a) small |= v != 0.f && v < top_a * 0x1p-10f;
-#pragma unroll
-    for (float v : seen_b) small |= v != 0.f && v < top_b * 0x1p-10f;
-    if (small) *flag = 1;
-    __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(*flag)) return false;
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][e] = ldexpf(acc[i][j][e], -ea - eb);
-    return true;
-}
-
 // BM x BN outputs per workgroup of WM x WN waves.  Tile t + 1 of the contraction is cut and written to the other LDS stage while
 // tile t is multiplied, and the loads of t + 2 follow into the registers that this frees: one barrier per tile, behind the last
 // write, with an eighth of the matrix instructions left to cover the first fragments of t + 1.
@@ -788,34 +550,24 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
     constexpr int AT_BARRIER = NMF - (NMF + 7) / 8, SLICED = NMF * 3 / 4;      // matrix instructions ahead of the barrier, and among slices
     const int M = q.M, N = q.N;
     f32x4_t acc[FM][FN];
-    auto clear = [&] {
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    };
-    clear();
-    int first_term = 0;
-    if constexpr (AKC) {
-        if (q.namax) {
-            if (half_tile<BM, BN, WM, WN, AKC, BKC>(q, m0, n0, smem, acc)) first_term = 1;
-            else clear();
-        }
-    }
-    const int tid = fresh_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN, l16 = lane & 15, g = lane >> 4;
     int* unsplit = (int*)smem;             // [t % 2]: tile t holds a value that the parts do not
     bf16_t* planes = (bf16_t*)(smem + SPLIT_HEAD);
     const int a_off = OA::lane_offset(wm * TM, lane), b_off = OA::ELEMS + OB::lane_offset(wn * TN, lane);
     bf16x8_t fa[3][FM], fb[3][FN];
     auto read_a = [&](const bf16_t* stage, int s, int i) { fa[s][i] = OA::fragment(stage + a_off + s * OA::PLANE, i); };
     auto read_b = [&](const bf16_t* stage, int s, int i) { fb[s][i] = OB::fragment(stage + b_off + s * OB::PLANE, i); };
-    // the main term, and the low-rank one on top of it (with alpha2 in its first operand)
+    // the low-rank term first, scaled; the main term goes on top of it
 #pragma unroll 1
-    for (int term = first_term; term < (q.K2 > 0 ? 2 : 1); ++term) {
-        const float *A = term ? q.A2 : q.A, *B = term ? q.B2 : q.B;
-        const long lda = term ? q.lda2 : q.lda, ldb = term ? q.ldb2 : q.ldb;
-        const int K = term ? q.K2 : q.K;
+    for (int term = q.K2 > 0 ? 0 : 1; term < 2; ++term) {
+        const float *A = term ? q.A : q.A2, *B = term ? q.B : q.B2;
+        const long lda = term ? q.lda : q.lda2, ldb = term ? q.ldb : q.ldb2;
+        const int K = term ? q.K : q.K2;
         auto tile_k = [](int t) { return (int)((unsigned)t * SPLIT_BK); };     // (beyond the end: reads as zeros, never multiplied)
         OA oa;
         OB ob;
@@ -831,12 +583,6 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
 #pragma unroll
             for (int i = 0; i < NI; ++i) r[i] = i < OA::N ? OA::mask(r[i], left, tid) : OB::mask(r[i], left, tid);
         };
-        auto scale_a = [&] {
-#pragma unroll
-            for (int i = 0; i < OA::N; ++i)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) r[i][e] = __float_as_uint(q.alpha2 * __uint_as_float(r[i][e]));
-        };
         {
             const auto rsa = OA::rsrc(A, lda, m0, M, 0, K);
             const auto rsb = OB::rsrc(B, ldb, n0, N, 0, K);
@@ -846,7 +592,6 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
             if (tid < 2) unsplit[tid] = 0;
             __syncthreads();
             mask(K);
-            if (term) scale_a();
             const auto rsa1 = OA::rsrc(A, lda, m0, M, tile_k(1), K);
             const auto rsb1 = OB::rsrc(B, ldb, n0, N, tile_k(1), K);
 #pragma unroll
@@ -870,7 +615,6 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
         for (int t = 0; t < nk; ++t) {
             if (slow) return false;        // (every wave reads the same word, behind the barrier that its writers wait at)
             if (t + 2 >= nk) mask(K - tile_k(t + 1));
-            if (term) scale_a();
             const auto rsa = OA::rsrc(A, lda, m0, M, tile_k(t + 2), K);
             const auto rsb = OB::rsrc(B, ldb, n0, N, tile_k(t + 2), K);
             parts.low = 0;
@@ -920,8 +664,15 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
             bf16_t* const s = stage;
             stage = other; other = s;
         }
+        if (term == 0) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i][j][e] *= q.alpha2;
+        }
     }
-    const int out_lane = fresh_tid() & 63, l16 = out_lane & 15, g = out_lane >> 4;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -952,7 +703,7 @@ template <int BM, int BN, int WM, int WN, int BKF, bool AKC, bool BKC>
 __device__ __forceinline__ void split_or_f32_tile(const F32Product& q, int m0, int n0, unsigned char* smem) {
     if (split_tile<BM, BN, WM, WN, AKC, BKC>(q, m0, n0, smem)) return;
     __syncthreads();                       // every wave has read the flag that lies in this memory
-    const int tid = fresh_tid(), half = __builtin_amdgcn_readfirstlane(tid >> 8);
+    const int tid = threadIdx.x, half = __builtin_amdgcn_readfirstlane(tid >> 8);
     constexpr int B = BM / 2 < 64 ? BM / 2 : 64;      // (rows at once: 128 would take more registers than there are)
 #pragma unroll 1
     for (int m = 0; m < BM / 2; m += B) {
@@ -1011,8 +762,7 @@ static hipError_t run_f32(F32Batch& grp, hipStream_t s) {
     auto kern = f32_group_kernel<BM, BN, BKF, WIDE>;
     e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    grp.scan0 = tiles;
-    kern<<<tiles + grp.scan.first[F32_SCAN_MAX], 256, lds, s>>>(grp);
+    kern<<<tiles, 256, lds, s>>>(grp);
     return hipGetLastError();
 }
 template <int F>
@@ -1020,8 +770,7 @@ static hipError_t run_direct(F32Batch& grp, hipStream_t s) {
     int tiles = 0;
     hipError_t e = place_f32<16 * F, 16 * F>(grp, &tiles);
     if (e != hipSuccess) return e;
-    grp.scan0 = tiles;
-    f32_direct_kernel<F><<<tiles + grp.scan.first[F32_SCAN_MAX], DIRECT_WAVES * 64, 0, s>>>(grp);
+    f32_direct_kernel<F><<<tiles, DIRECT_WAVES * 64, 0, s>>>(grp);
     return hipGetLastError();
 }
 template <int BM, int BN, int WM, int WN>
@@ -1038,12 +787,12 @@ static hipError_t run_split(F32Batch& grp, hipStream_t s) {
 }
 
 // What a launch takes: the longest chain, or all contraction tiles spread over 256 CUs, whichever is longer, per instance: us per
-// contraction element of one chain and of 256 tiles, and what it takes besides.  Fitted to steps of 66 shapes, 33 to 8200 tokens, widths
-// 40 to 5000, ranks 4 to 64, with each instance forced (the low-rank products in 16x16 tiles): what is picked takes 0.5 % longer than the
-// fastest on average, 8 % at worst.  Tokens x d_in x d_out, us in 16x16, 32x32 (direct), 64x64 (fp32), 128x128, 256x128 (split):
-// 128x256x256 31, 33, 39, 41, 47; 36x563x4006 51, 65, 138, 131, 180; 300x1000x1000 65, 55, 61, 61, 75; 128x4096x4096 259, 158, 146, 150, 199;
-// 1400x300x4000 241, 165, 158, 135, 184; 333x4096x4096 642, 368, 300, 153, 198; 1024x4096x4096 1885, 1005, 678, 318, 276.
-constexpr int F32_FIRST_SPLIT = 3;      // of the five
+// contraction element of one chain and of 256 tiles, and what it takes besides.  Fitted to steps of 86 shapes, 33 to 8200 tokens, widths
+// 40 to 5000, ranks 4 to 64, with each instance forced (the low-rank products in 16x16 tiles): what is picked takes 0.3 % longer than the
+// fastest on average, 7 % at worst.  Tokens x d_in x d_out, us in 16x16, 32x32 (direct), 64x64 (fp32), 128x128, 256x128 (split):
+// 128x256x256 30, 32, 37, 43, 51; 36x563x4006 50, 65, 122, 192, 292; 300x1000x1000 63, 52, 57, 73, 101; 128x4096x4096 246, 158, 137, 202, 307;
+// 1024x1024x1024 179, 112, 99, 78, 105; 1400x300x4000 239, 163, 144, 194, 294; 333x4096x4096 634, 368, 284, 209, 307;
+// 1024x4096x4096 1874, 1001, 676, 439, 389.
 struct F32Cost { int bm, bn; double chain, tiles, fixed; };
 static double f32_cost(const F32Batch& grp, const F32Cost& c) {
     double longest = 0, all = 0;
@@ -1073,23 +822,17 @@ static int arrange_f32(const F32Product* prods, int n, F32Batch& grp) {
     }
     if (wide) return -1;
     const F32Cost costs[] = {{16, 16, 0.0036, 0.0024, -1.0}, {32, 32, 0.0045, 0.0061, 0.4}, {64, 64, 0.0162, 0.0185, 2.3},
-                             {128, 128, 0.0198, 0.0285, 1.8}, {256, 128, 0.0344, 0.0439, 2.7}};
+                             {128, 128, 0.0246, 0.0475, -0.9}, {256, 128, 0.0573, 0.0731, 2.7}};
     int best = 0;
     for (int c = 1; c < 5; ++c)
         if (f32_cost(grp, costs[c]) < f32_cost(grp, costs[best])) best = c;
     return best;
 }
 
-bool gemm_f32_wants_max(const F32Product* prods, int n) {
-    F32Batch grp;
-    return n >= 1 && n <= F32_GROUP_MAX && arrange_f32(prods, n, grp) >= F32_FIRST_SPLIT;
-}
-
-hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s, const F32MaxScan* scan) {
+hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s) {
     if (n < 1 || n > F32_GROUP_MAX) return hipErrorInvalidValue;
     F32Batch grp;
     const int best = arrange_f32(prods, n, grp);
-    if (scan) grp.scan = *scan;
     long t64 = 0;
     for (int k = 0; k < n; ++k) {
         const F32Product& q = grp.p[k];
@@ -1099,11 +842,11 @@ hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s, 
     }
     // (rows that wide are long chains on few tiles, or next to no arithmetic: no 128-wide instance for them)
     if (best < 0) return t64 >= 256 ? run_f32<64, 64, 32, true>(grp, s) : run_f32<32, 32, 64, true>(grp, s);
-    switch (scan && best >= F32_FIRST_SPLIT ? F32_FIRST_SPLIT - 1 : best) {   // (the split kernel does not scan; low-rank products are not for it)
+    switch (best) {
         case 0: return run_direct<1>(grp, s);
         case 1: return run_direct<2>(grp, s);
         case 2: return run_f32<64, 64, 32>(grp, s);
-        case F32_FIRST_SPLIT: return run_split<128, 128, 2, 4>(grp, s);
+        case 3: return run_split<128, 128, 2, 4>(grp, s);
         default: return run_split<256, 128, 4, 2>(grp, s);
     }
 }

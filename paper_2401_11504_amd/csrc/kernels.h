@@ -86,24 +86,11 @@ struct F32Product {
     const float* p_old = nullptr;               // with p_new: the product is the gradient of p_old (same shape and row
     float* p_new = nullptr;                     // stride), and p_new receives p_old after its first AdamW step
     AdamWFirst opt = {};
-    const float *amax = nullptr, *bmax = nullptr;   // the largest magnitudes of A's and of B's shares (F32MaxScan), or none
-    int namax = 0, nbmax = 0;
     int tiles_m = 0, tiles_n = 0, tile0 = 0;    // filled in by the launcher
 };
 constexpr int F32_GROUP_MAX = 4;
-// The largest magnitude of up to three arrays, found by workgroups first[k] .. first[k + 1] - 1 for array k: each leaves that of its
-// share in out[workgroup].
-constexpr int F32_SCAN_MAX = 3, F32_SCAN_WGS = 256;
-struct F32MaxScan {
-    const float* p[F32_SCAN_MAX] = {};
-    size_t n[F32_SCAN_MAX] = {};
-    int first[F32_SCAN_MAX + 1] = {};
-    float* out = nullptr;
-};
-// n independent products in one launch, and the search for largest magnitudes beside them.  Outputs must not overlap any operand.
-hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s, const F32MaxScan* scan = nullptr);
-// Would a launch of these products use the largest magnitudes of their operands?
-bool gemm_f32_wants_max(const F32Product* prods, int n);
+// n independent products in one launch.  Outputs must not overlap any operand.
+hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s);
 hipError_t launch_adamw_first(const float* g, const float* p, float* p_new, size_t n, const AdamWFirst& o, hipStream_t s);
 
 // ---------------------------------------------------------------- attention (attention.hip)

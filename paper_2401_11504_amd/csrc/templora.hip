@@ -1266,12 +1266,12 @@ extern "C" tl_status tl_profile_read(tl_lora* L, double* ms_total, int64_t* laun
 }
 
 // ---------------------------------------------------------------- single fp32 LoRA-adapted linear layer
-// H, dH: [T, r] scratch; maxima: F32_SCAN_WGS floats of it.  Two dependent steps: the low-rank products H = X A^T and dH = s dY B, then everything else in one
+// H, dH: [T, r] scratch.  Two dependent steps: the low-rank products H = X A^T and dH = s dY B, then everything else in one
 // launch.
 static tl_status linear_step_run(const float* X, const float* W, const float* A, const float* B, const float* dY, int T,
                                  int d_in, int d_out, int r, float s, float lr, float beta1, float beta2, float eps,
                                  float wd, int apply_adamw, float* Y, float* dX, float* dA, float* dB, float* A_new,
-                                 float* B_new, float* H, float* dH, float* maxima, hipStream_t st) {
+                                 float* B_new, float* H, float* dH, hipStream_t st) {
     const size_t na = (size_t)r * d_in, nb = (size_t)d_out * r;
     AdamWFirst opt = {lr, beta1, beta2, eps, 1.f - lr * wd, (float)(1.0 / (1.0 - (double)beta1)),
                       (float)(1.0 / (1.0 - (double)beta2))};
@@ -1301,35 +1301,15 @@ static tl_status linear_step_run(const float* X, const float* W, const float* A,
         for (int i = o + 1; i < 11; ++i)
             shared |= buf[o].p && buf[i].p && (uintptr_t)buf[o].p < (uintptr_t)buf[i].p + buf[i].n * sizeof(float) &&
                       (uintptr_t)buf[i].p < (uintptr_t)buf[o].p + buf[o].n * sizeof(float);
-    // Large products cut their operands with a scale that the largest magnitudes of X, W and dY give: found beside the first
-    // launch, which leaves half of the chip idle and reads two of the three anyway.
-    F32MaxScan scan, *scan_p = nullptr;
-    if (shared ? gemm_f32_wants_max(&p[0], 1) || gemm_f32_wants_max(&p[1], 1) : gemm_f32_wants_max(p, 4)) {
-        const float* arr[F32_SCAN_MAX] = {X, W, dY};
-        const size_t len[F32_SCAN_MAX] = {(size_t)T * d_in, (size_t)d_out * d_in, (size_t)T * d_out};
-        const double all = (double)len[0] + (double)len[1] + (double)len[2];
-        for (int k = 0; k < F32_SCAN_MAX; ++k) {
-            scan.p[k] = arr[k];
-            scan.n[k] = len[k];
-            scan.first[k + 1] = scan.first[k] + 1 + (int)((F32_SCAN_WGS - F32_SCAN_MAX) * ((double)len[k] / all));
-        }
-        scan.out = maxima;
-        scan_p = &scan;
-        auto maxima_of = [&](int k, const float** at, int* n) { *at = maxima + scan.first[k]; *n = scan.first[k + 1] - scan.first[k]; };
-        maxima_of(0, &p[0].amax, &p[0].namax);
-        maxima_of(1, &p[0].bmax, &p[0].nbmax);
-        maxima_of(2, &p[1].amax, &p[1].namax);
-        maxima_of(1, &p[1].bmax, &p[1].nbmax);
-    }
     if (!shared) {
-        HIPCHK(launch_gemm_f32_group(low, 2, st, scan_p));
+        HIPCHK(launch_gemm_f32_group(low, 2, st));
         if (apply_adamw) {
             p[2].p_old = A; p[2].p_new = A_new; p[2].opt = opt;
             p[3].p_old = B; p[3].p_new = B_new; p[3].opt = opt;
         }
         HIPCHK(launch_gemm_f32_group(p, 4, st));
     } else {
-        HIPCHK(launch_gemm_f32_group(&low[0], 1, st, scan_p));
+        HIPCHK(launch_gemm_f32_group(&low[0], 1, st));
         HIPCHK(launch_gemm_f32_group(&p[0], 1, st));
         HIPCHK(launch_gemm_f32_group(&low[1], 1, st));
         for (int k = 1; k < 4; ++k) HIPCHK(launch_gemm_f32_group(&p[k], 1, st));
@@ -1360,9 +1340,9 @@ extern "C" tl_status tl_linear_step(const float* X, const float* W, const float*
     Pool pool;
     float* H = nullptr;     // H and dH in one allocation: each costs as much as a launch
     auto body = [&]() -> tl_status {
-        TLCHK(pool.alloc(&H, 2 * (size_t)T * r + F32_SCAN_WGS));
+        TLCHK(pool.alloc(&H, 2 * (size_t)T * r));
         return linear_step_run(X, W, A, B, dY, T, d_in, d_out, r, s, lr, beta1, beta2, eps, wd, apply_adamw, Y, dX, dA, dB,
-                               A_new, B_new, H, H + (size_t)T * r, H + 2 * (size_t)T * r, st);
+                               A_new, B_new, H, H + (size_t)T * r, st);
     };
     tl_status rc = body();
     if (rc != TL_OK) (void)hipStreamSynchronize(st);
@@ -1376,7 +1356,7 @@ extern "C" tl_status tl_linear_step(const float* X, const float* W, const float*
 // array instead.  Every GPU the library runs on holds its own copy for the life of the process; the array's name is
 // only a host-side handle, so its device address is looked up once per device (with that device current) and kept.
 constexpr size_t kStaticScratchFloats = (size_t)1 << 20;    // 4 MiB
-static __device__ __align__(256) float tl_static_scratch[kStaticScratchFloats + F32_SCAN_WGS];
+static __device__ __align__(256) float tl_static_scratch[kStaticScratchFloats];
 constexpr int kMaxDevices = 64;
 static float* g_static_scratch_ptr[kMaxDevices] = {};
 static std::mutex g_static_scratch_mutex;
@@ -1413,7 +1393,7 @@ extern "C" tl_status tl_linear_step_static(const float* X, const float* W, const
     TLCHK(static_scratch(&base));
     hipStream_t st = (hipStream_t)hip_stream;
     tl_status rc = linear_step_run(X, W, A, B, dY, T, d_in, d_out, r, s, lr, beta1, beta2, eps, wd, apply_adamw, Y, dX, dA,
-                                   dB, A_new, B_new, base, base + n_h, base + kStaticScratchFloats, st);
+                                   dB, A_new, B_new, base, base + n_h, st);
     if (rc != TL_OK) (void)hipStreamSynchronize(st);
     return rc;
 }

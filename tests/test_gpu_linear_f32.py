@@ -182,8 +182,8 @@ def test_split_operands_tiny(T, din, dout, r, rows):
     assert (outs[0].cpu().double() - ref["Y"]).norm() < tol(T, din, dout) * ref["Y"].norm()
 
 
-# Main terms in fp16 halves, scaled by the operand's largest magnitude: operands far from 1 and beyond the scales there are, zeros, rows and
-# columns far below the largest magnitude (an outlier puts every other element there), contractions of less than two tiles.  Every row
+# Operands far from 1 and too small for the parts, zeros, rows and columns far below the largest magnitude (an outlier puts every other
+# element there), in products of two long contractions and of a long and a short one.  Every row
 # and every column of the outputs is held to the tolerance by itself (twice, for the fewer entries it has).
 def _scale(ins, what):
     X, W, A, B, dY = ins
@@ -228,3 +228,35 @@ def test_direct_fragments(T, din, dout, r):
     for k, o, f in zip(("Y", "dX", "dA", "dB"), outs, flat):
         assert (o.cpu().double() - ref[k]).norm() < tol(T, din, dout) * ref[k].norm(), k
         assert bool((f[o.numel():] == 3.0).all()), k
+
+
+# Operands whose scale varies along the contraction: what is small in X (dY) meets what is not small in W, and may be all that an output
+# is made of.  `e`: binary orders between the two scales.  "blocks": W is block-diagonal, so that half of the outputs see the small half of
+# X only; "period": the same with every fourth element large; "balanced": W is small where X is large.  The factors are zero (balanced: small)
+# where X is large, so that the low-rank term has the outputs' scale.
+@pytest.mark.parametrize("T,din,dout,r", SPLIT[:2])
+@pytest.mark.parametrize("pattern", ["blocks", "period", "balanced"])
+@pytest.mark.parametrize("e", [14, 20, 28, 36])
+def test_scale_varies_along_the_contraction(T, din, dout, r, pattern, e):
+    ins, s = make(T, din, dout, r), 1.5
+    X, W, A, B, dY = ins
+    big_in, big_out = ((torch.arange(n) % 4 == 0) if pattern == "period" else (torch.arange(n) < n // 2) for n in (din, dout))
+    X[:, big_in] *= 2.0 ** e
+    dY[:, big_out] *= 2.0 ** e
+    if pattern == "balanced":
+        for t in (W, A):
+            t[:, big_in] *= 2.0 ** -e
+        for t in (W, B):
+            t[big_out] *= 2.0 ** -e
+    else:
+        W[big_out[:, None] != big_in[None, :]] = 0
+        A[:, big_in] = 0
+        B[big_out] = 0
+    dev = [t.cuda() for t in ins]
+    outs = [torch.empty(*size, device="cuda") for size in ((T, dout), (T, din), (r, din), (dout, r))]
+    step(dev, s, outs, torch.empty_like(dev[2]), torch.empty_like(dev[3]))
+    X, W, A, B, dY = (t.double() for t in dev)
+    for k, o, main, low in (("Y", outs[0], X @ W.T, s * (X @ A.T) @ B.T), ("dX", outs[1], dY @ W, s * (dY @ B) @ A)):
+        err = (o.double() - (main + low)).norm(dim=0)          # (of each column: its outputs have one scale)
+        bound = 2 * tol(T, din, dout) * (main.norm(dim=0) + low.norm(dim=0))
+        assert bool((err <= bound).all()), (k, (err / bound).max())
