@@ -427,11 +427,13 @@ __global__ __launch_bounds__(DIRECT_WAVES * 64, 4) void f32_direct_kernel(F32Bat
 }
 
 // ---------------------------------------------------------------- split operands on the bf16 matrix instructions
-// The same products with every operand cut into three bf16 parts, x = x1 + x2 + x3 (eight bits of the fraction each, by
-// truncation: nothing is lost and nothing overflows), and a b taken as a1 b3 + a1 b2 + a1 b1 + a2 b2 + a2 b1 + a3 b1 in fp32
-// accumulators.  What is left out, a2 b3 + a3 b2 + a3 b3, is 2^-24 of a product on average, half an ulp, and the accumulator is
-// rounded 6 K / 32 times instead of K times.  Against fp64, 2-norm, chain of fp32 products / parts: 1024 tokens, 4096 x 4096, rank 64
-// Y 1.15e-6 / 1.05e-6, dA 1.28e-6 / 1.24e-6; 1400, 300 x 4000 Y 3.1e-7 / 2.9e-7, dX 1.13e-6 / 1.04e-6.
+// The same products with every operand cut into three bf16 parts, x = x1 + x2 + x3 (each the nearest bf16 to what is left, which the
+// third holds exactly), and a b taken as a1 b3 + a1 b2 + a1 b1 + a2 b2 + a2 b1 + a3 b1 in fp32 accumulators.  What is left out,
+// a2 b3 + a3 b2 + a3 b3, is below 2^-26 of a product and of either sign.  The matrix instruction rounds to nearest, some four times for its 32
+// elements: 24 K / 32 roundings instead of K.  (Parts cut off instead of rounded have all the sign of x, and what a large sum drops of their
+// products, each below half an ulp of it, adds up: with operands of one sign 2.1e-6 to 4e-5 where this way is 1.8e-7 to 8.2e-7.)
+// Distance from fp64, 2-norm, chain of fp32 products / parts: 1024 tokens, 4096 x 4096, rank 64 Y 1.15e-6 / 1.01e-6, dA 1.28e-6 / 6.5e-7;
+// 1400 tokens, 256 x 1024, rank 64 Y 2.9e-7 / 3.0e-7, of one sign 1.2e-7 / 1.3e-7.
 //
 // The bf16 unit has sixteen times the rate, so that six products take 6/16 of the time of one in fp32.  What is cut is cut on
 // its way from the staging registers to LDS, seven vector operations an element, in slices between the matrix instructions.
@@ -501,24 +503,30 @@ struct SplitOperand {
         }
     }
 };
-// the parts of four floats, made in seven slices: one per element, then one per plane
+// the parts of four floats, made in seven slices: two per pair of elements, then one per plane
 struct SplitParts {
-    unsigned x[3][4];
+    unsigned x[3][2];
+    float y[2];            // what the first two parts leave of a pair
     unsigned low = 0;      // bits that the third parts do not hold
     float top = 0.f;       // the largest magnitude
-    __device__ __forceinline__ void element(unsigned bits, int e) {
-        const float v = __uint_as_float(bits);
-        x[0][e] = bits & 0xffff0000u;
-        const float y = v - __uint_as_float(x[0][e]);
-        x[1][e] = __float_as_uint(y) & 0xffff0000u;
-        x[2][e] = __float_as_uint(y - __uint_as_float(x[1][e]));
-        low |= x[2][e];
-        top = fmaxf(top, fabsf(v));
+    static __device__ __forceinline__ float first(unsigned pair) { return __uint_as_float(pair << 16); }
+    static __device__ __forceinline__ float second(unsigned pair) { return __uint_as_float(pair & 0xffff0000u); }
+    __device__ __forceinline__ void pair(unsigned b0, unsigned b1, int j) {
+        const float v0 = __uint_as_float(b0), v1 = __uint_as_float(b1);
+        x[0][j] = pack_bf16x2(v0, v1);
+        y[0] = v0 - first(x[0][j]);
+        y[1] = v1 - second(x[0][j]);
+        x[1][j] = pack_bf16x2(y[0], y[1]);
+        top = fmaxf(fmaxf(top, fabsf(v0)), fabsf(v1));
     }
-    __device__ __forceinline__ void put(bf16_t* dst, int p) const {
-        *(uint2*)dst = make_uint2(__builtin_amdgcn_perm(x[p][1], x[p][0], 0x07060302u), __builtin_amdgcn_perm(x[p][3], x[p][2], 0x07060302u));
+    __device__ __forceinline__ void rest(int j) {
+        const unsigned z0 = __float_as_uint(y[0] - first(x[1][j])), z1 = __float_as_uint(y[1] - second(x[1][j]));
+        x[2][j] = __builtin_amdgcn_perm(z1, z0, 0x07060302u);
+        low |= z0 | z1;
     }
-    __device__ __forceinline__ bool unsplit() const { return (low & 0xffffu) != 0 || top > 3.4028234663852886e38f; }
+    __device__ __forceinline__ void put(bf16_t* dst, int p) const { *(uint2*)dst = make_uint2(x[p][0], x[p][1]); }
+    // (a larger magnitude than the largest of bf16 may round to infinity)
+    __device__ __forceinline__ bool unsplit() const { return (low & 0xffffu) != 0 || top > 0x1.fep127f; }
 };
 
 // f(0), f(1), .. with the index as a constant: registers that are picked by it stay registers
@@ -562,12 +570,13 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
     bf16x8_t fa[3][FM], fb[3][FN];
     auto read_a = [&](const bf16_t* stage, int s, int i) { fa[s][i] = OA::fragment(stage + a_off + s * OA::PLANE, i); };
     auto read_b = [&](const bf16_t* stage, int s, int i) { fb[s][i] = OB::fragment(stage + b_off + s * OB::PLANE, i); };
-    // the low-rank term first, scaled; the main term goes on top of it
+    // the main term, and the low-rank one on top of it, with alpha2 in its first operand.  (A large low-rank term below a long main one would be
+    // rounded at each of its steps: 512 tokens, 1024 x 1024, rank 64, operands of one sign, Y 4.6e-7 from fp64 that way.)
 #pragma unroll 1
-    for (int term = q.K2 > 0 ? 0 : 1; term < 2; ++term) {
-        const float *A = term ? q.A : q.A2, *B = term ? q.B : q.B2;
-        const long lda = term ? q.lda : q.lda2, ldb = term ? q.ldb : q.ldb2;
-        const int K = term ? q.K : q.K2;
+    for (int term = 0; term < (q.K2 > 0 ? 2 : 1); ++term) {
+        const float *A = term ? q.A2 : q.A, *B = term ? q.B2 : q.B;
+        const long lda = term ? q.lda2 : q.lda, ldb = term ? q.ldb2 : q.ldb;
+        const int K = term ? q.K2 : q.K;
         auto tile_k = [](int t) { return (int)((unsigned)t * SPLIT_BK); };     // (beyond the end: reads as zeros, never multiplied)
         OA oa;
         OB ob;
@@ -583,6 +592,16 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
 #pragma unroll
             for (int i = 0; i < NI; ++i) r[i] = i < OA::N ? OA::mask(r[i], left, tid) : OB::mask(r[i], left, tid);
         };
+        auto scale_a = [&] {               // (a value that this takes to where fp32 has fewer bits counts as one that the parts do not hold)
+#pragma unroll
+            for (int i = 0; i < OA::N; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float v = __uint_as_float(r[i][e]), w = q.alpha2 * v;
+                    if (v != 0.f && fabsf(w) < 0x1p-110f) parts.low |= 1;
+                    r[i][e] = __float_as_uint(w);
+                }
+        };
         {
             const auto rsa = OA::rsrc(A, lda, m0, M, 0, K);
             const auto rsb = OB::rsrc(B, ldb, n0, N, 0, K);
@@ -592,12 +611,16 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
             if (tid < 2) unsplit[tid] = 0;
             __syncthreads();
             mask(K);
+            if (term) scale_a();
             const auto rsa1 = OA::rsrc(A, lda, m0, M, tile_k(1), K);
             const auto rsb1 = OB::rsrc(B, ldb, n0, N, tile_k(1), K);
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) parts.element(r[i][e], e);
+                for (int j = 0; j < 2; ++j) {
+                    parts.pair(r[i][2 * j], r[i][2 * j + 1], j);
+                    parts.rest(j);
+                }
 #pragma unroll
                 for (int p = 0; p < 3; ++p) parts.put(item_dst(planes, i, p), p);
                 r[i] = i < OA::N ? oa.load(rsa1, i, lda) : ob.load(rsb1, i - OA::N, ldb);
@@ -614,16 +637,18 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
         const int nk = (K + SPLIT_BK - 1) / SPLIT_BK;
         for (int t = 0; t < nk; ++t) {
             if (slow) return false;        // (every wave reads the same word, behind the barrier that its writers wait at)
-            if (t + 2 >= nk) mask(K - tile_k(t + 1));
             const auto rsa = OA::rsrc(A, lda, m0, M, tile_k(t + 2), K);
             const auto rsb = OB::rsrc(B, ldb, n0, N, tile_k(t + 2), K);
             parts.low = 0;
             parts.top = 0.f;
+            if (t + 2 >= nk) mask(K - tile_k(t + 1));
+            if (term) scale_a();
             int found = 0;
-            // slice x of NS: an element of an item, one of its planes, or the load that replaces it
+            // slice x of NS: half of the work on a pair of an item, one of its planes, or the load that replaces it
             auto slice = [&](auto xc) {
                 constexpr int i = xc.value / 8, y = xc.value % 8;
-                if constexpr (y < 4) parts.element(r[i][y], y);
+                if constexpr (y < 4 && y % 2 == 0) parts.pair(r[i][y], r[i][y + 1], y / 2);
+                else if constexpr (y < 4) parts.rest(y / 2);
                 else if constexpr (y < 7) parts.put(item_dst(other, i, y - 4), y - 4);
                 else if constexpr (i < OA::N) r[i] = oa.load(rsa, i, lda);
                 else r[i] = ob.load(rsb, i - OA::N, ldb);
@@ -663,14 +688,6 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
             slow = __builtin_amdgcn_readfirstlane(found);
             bf16_t* const s = stage;
             stage = other; other = s;
-        }
-        if (term == 0) {
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[i][j][e] *= q.alpha2;
         }
     }
 #pragma unroll

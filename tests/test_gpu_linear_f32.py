@@ -260,3 +260,19 @@ def test_scale_varies_along_the_contraction(T, din, dout, r, pattern, e):
         err = (o.double() - (main + low)).norm(dim=0)          # (of each column: its outputs have one scale)
         bound = 2 * tol(T, din, dout) * (main.norm(dim=0) + low.norm(dim=0))
         assert bool((err <= bound).all()), (k, (err / bound).max())
+
+
+# Operands of one sign: what a sum leaves out does not cancel.  Random mantissas, and ones whose bits are all set; the low-rank term is
+# far larger than any one product.  Roundings stay at random: the walk of a chain without the doubling of `tol`.
+@pytest.mark.parametrize("T,din,dout,r", [(512, 1024, 1536, 16), (1029, 2050, 2049, 64), (701, 2500, 2501, 33)])
+@pytest.mark.parametrize("values", ["random", "all bits set"])
+def test_operands_of_one_sign(T, din, dout, r, values):
+    ins = [t.abs() + 0.1 if values == "random" else torch.full_like(t, 2 - 2.0 ** -23) for t in make(T, din, dout, r)]
+    s = 1.5
+    dev = [t.cuda() for t in ins]
+    outs = [torch.empty(*size, device="cuda") for size in ((T, dout), (T, din), (r, din), (dout, r))]
+    step(dev, s, outs, torch.empty_like(dev[2]), torch.empty_like(dev[3]))
+    ref = reference(dev, s)
+    for k, o in zip(("Y", "dX", "dA", "dB"), outs):
+        err = ((o.double() - ref[k]).norm() / ref[k].norm()).item()
+        assert err < tol(T, din, dout) / 2, (k, err)
