@@ -444,12 +444,16 @@ __global__ __launch_bounds__(DIRECT_WAVES * 64, 4) void f32_direct_kernel(F32Bat
 // But fp16 has five bits of exponent: an element below 2^-17 of the array's largest loses bits, and is nothing below 2^-40, where it may be all that an output is made of --
 // the other operand may be zero, or small, where this one is large.  To find that out takes a look at every element, and among normal draws some always lie that low.)
 //
-// The parts say nothing about an operand that is infinite (inf * 0 for a part that is zero) or whose last part is below the
-// bf16 range (|x| < 2^-110): a workgroup that meets one starts its outputs again with f32_tile, in two halves of 256 threads.
+// Operands are scaled by 2^24 on the way, so that the parts hold every value down to fp32's smallest (2^-149: the third part of one below 2^-110
+// would be out of bf16's range otherwise), and outputs by 2^-48 at the end.  What does not fit then -- operands that are not finite or above
+// 2^104, sums above 2^80 -- leaves an accumulator that is not finite: such a workgroup does its outputs again with f32_tile, in two halves of 256
+// threads.  us for a step of 1024 tokens, 4096 x 4096, rank 64: 370; with a softmax for dY, most of it far below 1, 370 (674 all in fp32, 716
+// where a value below 2^-110 sends a workgroup there); with one infinity in X, 957.
 //
 // Order of the 32 contraction elements of a tile within the matrix instruction: lane group g takes 4 g .. 4 g + 3 and
 // 16 + 4 g .. 16 + 4 g + 3, in both operands.
 constexpr int SPLIT_BK = 32, SPLIT_NT = 512, SPLIT_HEAD = 16;     // (bytes of LDS ahead of the planes)
+constexpr float SPLIT_SCALE = 0x1p24f;
 // One operand: memory -> registers (`N` items of four floats a thread) -> three planes of LDS per tile.
 //   KC: [row][32], 8-byte piece p of a row (elements 4 p .. 4 p + 3) as half p / 4 of 16-byte chunk (p % 4) ^ (row / 4 % 4), so that
 //       a lane's elements are one chunk, sixteen rows' chunks lie in distinct banks, and so do the pieces that are written
@@ -503,30 +507,23 @@ struct SplitOperand {
         }
     }
 };
-// the parts of four floats, made in seven slices: two per pair of elements, then one per plane
+// the parts of four floats times a scale, made in seven slices: two per pair of elements, then one per plane
 struct SplitParts {
     unsigned x[3][2];
-    float y[2];            // what the first two parts leave of a pair
-    unsigned low = 0;      // bits that the third parts do not hold
-    float top = 0.f;       // the largest magnitude
+    float y[2];            // what the first part leaves of a pair
     static __device__ __forceinline__ float first(unsigned pair) { return __uint_as_float(pair << 16); }
     static __device__ __forceinline__ float second(unsigned pair) { return __uint_as_float(pair & 0xffff0000u); }
-    __device__ __forceinline__ void pair(unsigned b0, unsigned b1, int j) {
+    __device__ __forceinline__ void pair(unsigned b0, unsigned b1, int j, float scale) {
         const float v0 = __uint_as_float(b0), v1 = __uint_as_float(b1);
-        x[0][j] = pack_bf16x2(v0, v1);
-        y[0] = v0 - first(x[0][j]);
-        y[1] = v1 - second(x[0][j]);
-        x[1][j] = pack_bf16x2(y[0], y[1]);
-        top = fmaxf(fmaxf(top, fabsf(v0)), fabsf(v1));
+        x[0][j] = pack_bf16x2(v0 * scale, v1 * scale);
+        y[0] = fmaf(v0, scale, -first(x[0][j]));
+        y[1] = fmaf(v1, scale, -second(x[0][j]));
     }
     __device__ __forceinline__ void rest(int j) {
-        const unsigned z0 = __float_as_uint(y[0] - first(x[1][j])), z1 = __float_as_uint(y[1] - second(x[1][j]));
-        x[2][j] = __builtin_amdgcn_perm(z1, z0, 0x07060302u);
-        low |= z0 | z1;
+        x[1][j] = pack_bf16x2(y[0], y[1]);
+        x[2][j] = __builtin_amdgcn_perm(__float_as_uint(y[1] - second(x[1][j])), __float_as_uint(y[0] - first(x[1][j])), 0x07060302u);
     }
     __device__ __forceinline__ void put(bf16_t* dst, int p) const { *(uint2*)dst = make_uint2(x[p][0], x[p][1]); }
-    // (a larger magnitude than the largest of bf16 may round to infinity)
-    __device__ __forceinline__ bool unsplit() const { return (low & 0xffffu) != 0 || top > 0x1.fep127f; }
 };
 
 // f(0), f(1), .. with the index as a constant: registers that are picked by it stay registers
@@ -564,7 +561,7 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
         for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN, l16 = lane & 15, g = lane >> 4;
-    int* unsplit = (int*)smem;             // [t % 2]: tile t holds a value that the parts do not
+    int* overflow = (int*)smem;            // an accumulator is not finite
     bf16_t* planes = (bf16_t*)(smem + SPLIT_HEAD);
     const int a_off = OA::lane_offset(wm * TM, lane), b_off = OA::ELEMS + OB::lane_offset(wn * TN, lane);
     bf16x8_t fa[3][FM], fb[3][FN];
@@ -592,69 +589,50 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
 #pragma unroll
             for (int i = 0; i < NI; ++i) r[i] = i < OA::N ? OA::mask(r[i], left, tid) : OB::mask(r[i], left, tid);
         };
-        auto scale_a = [&] {               // (a value that this takes to where fp32 has fewer bits counts as one that the parts do not hold)
-#pragma unroll
-            for (int i = 0; i < OA::N; ++i)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float v = __uint_as_float(r[i][e]), w = q.alpha2 * v;
-                    if (v != 0.f && fabsf(w) < 0x1p-110f) parts.low |= 1;
-                    r[i][e] = __float_as_uint(w);
-                }
-        };
+        const float scale_a = term ? q.alpha2 * SPLIT_SCALE : SPLIT_SCALE;
         {
             const auto rsa = OA::rsrc(A, lda, m0, M, 0, K);
             const auto rsb = OB::rsrc(B, ldb, n0, N, 0, K);
 #pragma unroll
             for (int i = 0; i < NI; ++i) r[i] = i < OA::N ? oa.load(rsa, i, lda) : ob.load(rsb, i - OA::N, ldb);
             __syncthreads();               // the other term's tiles have been read
-            if (tid < 2) unsplit[tid] = 0;
-            __syncthreads();
+            if (tid == 0) *overflow = 0;
             mask(K);
-            if (term) scale_a();
             const auto rsa1 = OA::rsrc(A, lda, m0, M, tile_k(1), K);
             const auto rsb1 = OB::rsrc(B, ldb, n0, N, tile_k(1), K);
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
-                    parts.pair(r[i][2 * j], r[i][2 * j + 1], j);
+                    parts.pair(r[i][2 * j], r[i][2 * j + 1], j, i < OA::N ? scale_a : SPLIT_SCALE);
                     parts.rest(j);
                 }
 #pragma unroll
                 for (int p = 0; p < 3; ++p) parts.put(item_dst(planes, i, p), p);
                 r[i] = i < OA::N ? oa.load(rsa1, i, lda) : ob.load(rsb1, i - OA::N, ldb);
             }
-            if (parts.unsplit()) unsplit[0] = 1;
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < FM; ++i) read_a(planes, 0, i);
 #pragma unroll
             for (int i = 0; i < FN; ++i) read_b(planes, 2, i);
         }
-        int slow = __builtin_amdgcn_readfirstlane(unsplit[0]);
         bf16_t *stage = planes, *other = planes + STAGE;
         const int nk = (K + SPLIT_BK - 1) / SPLIT_BK;
         for (int t = 0; t < nk; ++t) {
-            if (slow) return false;        // (every wave reads the same word, behind the barrier that its writers wait at)
             const auto rsa = OA::rsrc(A, lda, m0, M, tile_k(t + 2), K);
             const auto rsb = OB::rsrc(B, ldb, n0, N, tile_k(t + 2), K);
-            parts.low = 0;
-            parts.top = 0.f;
             if (t + 2 >= nk) mask(K - tile_k(t + 1));
-            if (term) scale_a();
-            int found = 0;
             // slice x of NS: half of the work on a pair of an item, one of its planes, or the load that replaces it
             auto slice = [&](auto xc) {
                 constexpr int i = xc.value / 8, y = xc.value % 8;
-                if constexpr (y < 4 && y % 2 == 0) parts.pair(r[i][y], r[i][y + 1], y / 2);
+                if constexpr (y < 4 && y % 2 == 0) parts.pair(r[i][y], r[i][y + 1], y / 2, i < OA::N ? scale_a : SPLIT_SCALE);
                 else if constexpr (y < 4) parts.rest(y / 2);
                 else if constexpr (y < 7) parts.put(item_dst(other, i, y - 4), y - 4);
                 else if constexpr (i < OA::N) r[i] = oa.load(rsa, i, lda);
                 else r[i] = ob.load(rsb, i - OA::N, ldb);
             };
             auto hand_over = [&] {
-                if (parts.unsplit()) unsplit[(t + 1) & 1] = 1;
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
@@ -676,7 +654,7 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
                 unrolled<NS>([&](auto y) {
                     if constexpr (y.value * SLICED / NS == e) slice(y);
                 });
-                if constexpr (e + 1 == AT_BARRIER) { hand_over(); found = unsplit[(t + 1) & 1]; }
+                if constexpr (e + 1 == AT_BARRIER) hand_over();
                 unrolled<FN>([&](auto f) {
                     if constexpr (AT_BARRIER - 1 + f.value * left / (FM + FN) == e) read_b(other, 2, f.value);
                 });
@@ -685,11 +663,21 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
                 });
                 __builtin_amdgcn_sched_barrier(0);
             });
-            slow = __builtin_amdgcn_readfirstlane(found);
             bf16_t* const s = stage;
             stage = other; other = s;
         }
     }
+    float zero = 0.f;                      // (stays that where every accumulator is finite)
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) zero = fmaf(acc[i][j][e], 0.f, zero);
+    if (!(zero == 0.f)) *overflow = 1;
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(*overflow)) return false;
+    const float alpha = q.alpha / (SPLIT_SCALE * SPLIT_SCALE);
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -699,7 +687,7 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
             const long at = (long)m * q.ldc + n;
             f4u v;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = q.alpha * acc[i][r][e];
+            for (int e = 0; e < 4; ++e) v[e] = alpha * acc[i][r][e];
             if (n + 4 <= N) {
                 *(f4u*)(q.C + at) = v;
             } else {
@@ -831,17 +819,19 @@ static int arrange_f32(const F32Product* prods, int n, F32Batch& grp) {
     for (int k = 0; k < n; ++k) order[k] = k;
     for (int k = 1; k < n; ++k)               // longest contraction first: what is left for the end are short tiles
         for (int j = k; j > 0 && prods[order[j]].K > prods[order[j - 1]].K; --j) { int t = order[j]; order[j] = order[j - 1]; order[j - 1] = t; }
-    bool wide = false;
+    bool wide = false, split = true;
     for (int k = 0; k < n; ++k) {
         F32Product& q = grp.p[k];
         q = prods[order[k]];
         wide |= q.lda > (1L << 22) || q.ldb > (1L << 22) || q.lda2 > (1L << 22) || q.ldb2 > (1L << 22);
+        // (factors that would move what the scaled parts hold)
+        for (float f : {q.alpha, q.K2 > 0 ? q.alpha2 : 1.f}) split &= f == 0.f || (fabsf(f) >= 0x1p-20f && fabsf(f) <= 0x1p20f);
     }
     if (wide) return -1;
     const F32Cost costs[] = {{16, 16, 0.0036, 0.0024, -1.0}, {32, 32, 0.0045, 0.0061, 0.4}, {64, 64, 0.0162, 0.0185, 2.3},
                              {128, 128, 0.0246, 0.0475, -0.9}, {256, 128, 0.0573, 0.0731, 2.7}};
     int best = 0;
-    for (int c = 1; c < 5; ++c)
+    for (int c = 1; c < (split ? 5 : 3); ++c)
         if (f32_cost(grp, costs[c]) < f32_cost(grp, costs[best])) best = c;
     return best;
 }

@@ -276,3 +276,40 @@ def test_operands_of_one_sign(T, din, dout, r, values):
     for k, o in zip(("Y", "dX", "dA", "dB"), outs):
         err = ((o.double() - ref[k]).norm() / ref[k].norm()).item()
         assert err < tol(T, din, dout) / 2, (k, err)
+
+
+# Values far below the others of a tile, down to fp32's smallest: they change no output but their own, and cost none its route.
+@pytest.mark.parametrize("T,din,dout,r", SPLIT[:2])
+@pytest.mark.parametrize("value", [1.2345678e-36, 1.1754944e-38, 9.2e-41, 1.4e-45])
+def test_a_tiny_value_changes_no_other_output(T, din, dout, r, value):
+    ins, s = make(T, din, dout, r), 1.5
+    got = []
+    for v in (0.0, value):
+        ins[0][5, -1] = ins[4][7, 0] = v
+        dev = [t.cuda() for t in ins]
+        outs = [torch.empty(*size, device="cuda") for size in ((T, dout), (T, din), (r, din), (dout, r))]
+        step(dev, s, outs, torch.empty_like(dev[2]), torch.empty_like(dev[3]))
+        got.append(outs)
+    assert torch.equal(torch.cat([got[0][0][:5], got[0][0][6:]]), torch.cat([got[1][0][:5], got[1][0][6:]]))
+    assert torch.equal(torch.cat([got[0][1][:7], got[0][1][8:]]), torch.cat([got[1][1][:7], got[1][1][8:]]))
+
+
+# Operands and sums beyond what the scaled parts and their accumulators hold, all of them or a few rows, and scales of the low-rank term that would move that.
+@pytest.mark.parametrize("T,din,dout,r", SPLIT[:2])
+@pytest.mark.parametrize("what", ["operands", "one operand", "sums", "one sum", "small s", "large s"])
+def test_split_operands_beyond_the_scaled_parts(T, din, dout, r, what):
+    ins, s = make(T, din, dout, r), 1.5
+    X, W, A, B, dY = ins
+    if what == "operands": X *= 2.0 ** 108; W *= 2.0 ** -100; A *= 2.0 ** -100; dY *= 2.0 ** -10
+    elif what == "one operand": X[9, 3] = 2.0 ** 106; W[:, 3] *= 2.0 ** -90; A[:, 3] *= 2.0 ** -100
+    elif what == "sums": X *= 2.0 ** 50; W *= 2.0 ** 40; B *= 2.0 ** 40
+    elif what == "one sum": X[9] *= 2.0 ** 90; dY[3] *= 2.0 ** 90
+    elif what == "small s": s = 2.0 ** -40; A *= 2.0 ** 30; B *= 2.0 ** 12
+    elif what == "large s": s = 2.0 ** 40; A *= 2.0 ** -35
+    dev = [t.cuda() for t in ins]
+    outs = [torch.empty(*size, device="cuda") for size in ((T, dout), (T, din), (r, din), (dout, r))]
+    step(dev, s, outs, torch.empty_like(dev[2]), torch.empty_like(dev[3]))
+    X, W, A, B, dY = (t.double() for t in dev)
+    for k, o, main, low in (("Y", outs[0], X @ W.T, s * (X @ A.T) @ B.T), ("dX", outs[1], dY @ W, s * (dY @ B) @ A)):
+        err = (o.double() - (main + low)).norm(dim=1)
+        assert bool((err <= 2 * tol(T, din, dout) * (main.norm(dim=1) + low.norm(dim=1))).all()), k
