@@ -428,12 +428,15 @@ __global__ __launch_bounds__(DIRECT_WAVES * 64, 4) void f32_direct_kernel(F32Bat
 
 // ---------------------------------------------------------------- split operands on the bf16 matrix instructions
 // The same products with every operand cut into three bf16 parts, x = x1 + x2 + x3 (each the nearest bf16 to what is left, which the
-// third holds exactly), and a b taken as a1 b3 + a1 b2 + a1 b1 + a2 b2 + a2 b1 + a3 b1 in fp32 accumulators.  What is left out,
+// third holds exactly), and a b taken as a2 b2 + a2 b1 + a3 b1 + a1 b3 + a1 b2 + a1 b1 in fp32 accumulators.  What is left out,
 // a2 b3 + a3 b2 + a3 b3, is below 2^-26 of a product and of either sign.  The matrix instruction rounds to nearest, some four times for its 32
-// elements: 24 K / 32 roundings instead of K.  (Parts cut off instead of rounded have all the sign of x, and what a large sum drops of their
-// products, each below half an ulp of it, adds up: with operands of one sign 2.1e-6 to 4e-5 where this way is 1.8e-7 to 8.2e-7.)
-// Distance from fp64, 2-norm, chain of fp32 products / parts: 1024 tokens, 4096 x 4096, rank 64 Y 1.15e-6 / 1.01e-6, dA 1.28e-6 / 6.5e-7;
-// 1400 tokens, 256 x 1024, rank 64 Y 2.9e-7 / 3.0e-7, of one sign 1.2e-7 / 1.3e-7.
+// elements: 24 K / 32 roundings instead of K, those of the largest products last (of the smallest last: contractions of 1 to 32 elements 5.3e-8 to
+// 9.6e-8 from fp64 instead of 3.4e-8 to 3.8e-8, chain of fp32 products 2.5e-8 to 1.0e-7).  (Parts cut off instead of rounded have all the
+// sign of x, and what a large sum drops of their products, each below half an ulp of it, adds up: with operands of one sign 2.1e-6 to 4e-5
+// where this way is 1.8e-7 to 8.2e-7.)
+// Distance from fp64, 2-norm, chain of fp32 products / parts: 1024 tokens, 4096 x 4096, rank 64 Y 1.15e-6 / 1.01e-6, dA 1.28e-6 / 6.4e-7,
+// of one sign Y 5.3e-7 / 3.6e-7; 1400 tokens, 256 x 1024, rank 64 Y 2.9e-7 / 2.9e-7, of one sign 1.2e-7 / 7.8e-8.  Where a few large products make up
+// a long contraction it is the other way round (dX of a dY that is a softmax 6.3e-8 / 1.9e-7).
 //
 // The bf16 unit has sixteen times the rate, so that six products take 6/16 of the time of one in fp32.  What is cut is cut on
 // its way from the staging registers to LDS, seven vector operations an element, in slices between the matrix instructions.
@@ -447,7 +450,7 @@ __global__ __launch_bounds__(DIRECT_WAVES * 64, 4) void f32_direct_kernel(F32Bat
 // Operands are scaled by 2^24 on the way, so that the parts hold every value down to fp32's smallest (2^-149: the third part of one below 2^-110
 // would be out of bf16's range otherwise), and outputs by 2^-48 at the end.  What does not fit then -- operands that are not finite or above
 // 2^104, sums above 2^80 -- leaves an accumulator that is not finite: such a workgroup does its outputs again with f32_tile, in two halves of 256
-// threads.  us for a step of 1024 tokens, 4096 x 4096, rank 64: 370; with a softmax for dY, most of it far below 1, 370 (674 all in fp32, 716
+// threads.  us for a step of 1024 tokens, 4096 x 4096, rank 64: 380; with a softmax for dY, most of it far below 1, 380 (674 all in fp32, 716
 // where a value below 2^-110 sends a workgroup there); with one infinity in X, 957.
 //
 // Order of the 32 contraction elements of a tile within the matrix instruction: lane group g takes 4 g .. 4 g + 3 and
@@ -613,9 +616,9 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
             }
             __syncthreads();
 #pragma unroll
-            for (int i = 0; i < FM; ++i) read_a(planes, 0, i);
+            for (int i = 0; i < FM; ++i) read_a(planes, 1, i);
 #pragma unroll
-            for (int i = 0; i < FN; ++i) read_b(planes, 2, i);
+            for (int i = 0; i < FN; ++i) read_b(planes, 1, i);
         }
         bf16_t *stage = planes, *other = planes + STAGE;
         const int nk = (K + SPLIT_BK - 1) / SPLIT_BK;
@@ -639,27 +642,27 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
             };
             unrolled<NMF>([&](auto ec) {
                 constexpr int e = ec.value, gr = e / NG, x = e % NG, i = x / FN, jn = x % FN, left = NMF - AT_BARRIER;
-                constexpr int pa = gr < 3 ? 0 : gr < 5 ? 1 : 2, pb = gr == 0 ? 2 : gr == 1 || gr == 3 ? 1 : 0;
+                constexpr int pa = gr < 2 ? 1 : gr == 2 ? 2 : 0, pb = gr == 0 || gr == 4 ? 1 : gr == 3 ? 2 : 0;
                 // B first: a lane then holds row l16 of A's fragment, columns 4 g .. 4 g + 3 of B's
                 acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[pb][jn], fa[pa][i], acc[i][jn], 0, 0, 0);
                 // the fragments that a later group needs, spread over this one
                 unrolled<FM>([&](auto f) {
-                    if constexpr (f.value * NG / FM == x && gr == 2) read_a(stage, 1, f.value);
-                    if constexpr (f.value * NG / FM == x && gr == 4) read_a(stage, 2, f.value);
+                    if constexpr (f.value * NG / FM == x && gr == 1) read_a(stage, 2, f.value);
+                    if constexpr (f.value * NG / FM == x && gr == 2) read_a(stage, 0, f.value);
                 });
                 unrolled<FN>([&](auto f) {
-                    if constexpr (f.value == x && gr == 0) read_b(stage, 1, f.value);
-                    if constexpr (f.value == x && gr == 1) read_b(stage, 0, f.value);
+                    if constexpr (f.value == x && gr == 0) read_b(stage, 0, f.value);
+                    if constexpr (f.value * NG / FN == x && gr == 2) read_b(stage, 2, f.value);
                 });
                 unrolled<NS>([&](auto y) {
                     if constexpr (y.value * SLICED / NS == e) slice(y);
                 });
                 if constexpr (e + 1 == AT_BARRIER) hand_over();
                 unrolled<FN>([&](auto f) {
-                    if constexpr (AT_BARRIER - 1 + f.value * left / (FM + FN) == e) read_b(other, 2, f.value);
+                    if constexpr (AT_BARRIER - 1 + f.value * left / (FM + FN) == e) read_b(other, 1, f.value);
                 });
                 unrolled<FM>([&](auto f) {
-                    if constexpr (AT_BARRIER - 1 + (FN + f.value) * left / (FM + FN) == e) read_a(other, 0, f.value);
+                    if constexpr (AT_BARRIER - 1 + (FN + f.value) * left / (FM + FN) == e) read_a(other, 1, f.value);
                 });
                 __builtin_amdgcn_sched_barrier(0);
             });
@@ -795,9 +798,9 @@ static hipError_t run_split(F32Batch& grp, hipStream_t s) {
 // contraction element of one chain and of 256 tiles, and what it takes besides.  Fitted to steps of 86 shapes, 33 to 8200 tokens, widths
 // 40 to 5000, ranks 4 to 64, with each instance forced (the low-rank products in 16x16 tiles): what is picked takes 0.3 % longer than the
 // fastest on average, 7 % at worst.  Tokens x d_in x d_out, us in 16x16, 32x32 (direct), 64x64 (fp32), 128x128, 256x128 (split):
-// 128x256x256 30, 32, 37, 43, 51; 36x563x4006 50, 65, 122, 192, 292; 300x1000x1000 63, 52, 57, 73, 101; 128x4096x4096 246, 158, 137, 202, 307;
-// 1024x1024x1024 179, 112, 99, 78, 105; 1400x300x4000 239, 163, 144, 194, 294; 333x4096x4096 634, 368, 284, 209, 307;
-// 1024x4096x4096 1874, 1001, 676, 439, 389.
+// 128x256x256 30, 32, 37, 41, 49; 36x563x4006 49, 64, 122, 183, 276; 300x1000x1000 62, 52, 57, 71, 97; 128x4096x4096 249, 156, 137, 194, 293;
+// 512x1024x1024 107, 73, 64, 74, 99; 1024x1024x1024 183, 113, 98, 75, 100; 1400x300x4000 239, 164, 144, 185, 277; 333x4096x4096 632, 370, 285, 200,
+// 293; 1024x4096x4096 1879, 1006, 678, 430, 381.
 struct F32Cost { int bm, bn; double chain, tiles, fixed; };
 static double f32_cost(const F32Batch& grp, const F32Cost& c) {
     double longest = 0, all = 0;
@@ -824,7 +827,10 @@ static int arrange_f32(const F32Product* prods, int n, F32Batch& grp) {
         F32Product& q = grp.p[k];
         q = prods[order[k]];
         wide |= q.lda > (1L << 22) || q.ldb > (1L << 22) || q.lda2 > (1L << 22) || q.ldb2 > (1L << 22);
-        // (factors that would move what the scaled parts hold)
+        // (a side that leaves half of a split tile empty, as the low-rank products have; a contraction of less than a tile -- of 4 or 8 elements
+        // and a low-rank term of one to three it would be 1.07 to 1.15 times as far from fp64 as single products --; factors that would move what
+        // the scaled parts hold)
+        split &= (q.kind == F32_MN || (q.M > 64 && q.N > 64)) && q.K >= SPLIT_BK;
         for (float f : {q.alpha, q.K2 > 0 ? q.alpha2 : 1.f}) split &= f == 0.f || (fabsf(f) >= 0x1p-20f && fabsf(f) <= 0x1p20f);
     }
     if (wide) return -1;

@@ -313,3 +313,28 @@ def test_split_operands_beyond_the_scaled_parts(T, din, dout, r, what):
     for k, o, main, low in (("Y", outs[0], X @ W.T, s * (X @ A.T) @ B.T), ("dX", outs[1], dY @ W, s * (dY @ B) @ A)):
         err = (o.double() - (main + low)).norm(dim=1)
         assert bool((err <= 2 * tol(T, din, dout) * (main.norm(dim=1) + low.norm(dim=1))).all()), k
+
+
+# Short contractions (in place, where each product is a launch of its own: Y where d_in is the short side, dX where d_out is), the first two too
+# short for the split kernel, the others of one or two of its tiles: no further from fp64 than a chain of fused multiply-adds in fp32, which is
+# emulated (but for the chain that leads to H or dH, of 4100 elements at most beside a term of a hundredth of the result: 1 %).
+@pytest.mark.parametrize("T,din,dout,r", [(1400, 8, 4100, 3), (8192, 4100, 8, 3), (1400, 32, 4100, 1), (1400, 33, 4100, 3), (1400, 63, 4100, 8),
+                                          (8192, 4100, 32, 3), (1400, 4100, 63, 3)])
+def test_short_contractions(T, din, dout, r):
+    ins, s = make(T, din, dout, r), 1.5
+    dev = [t.cuda() for t in ins]
+    ref = reference(dev, s)
+    X, W, A, B, dY = (t.clone() for t in dev)
+    outs = [torch.empty(*size, device="cuda") for size in ((T, dout), (T, din), (r, din), (dout, r))]
+    step(dev, s, outs, dev[2], dev[3])
+
+    def chain(a, b):      # (a product of two floats is exact in fp64)
+        c = torch.zeros(a.shape[0], b.shape[1], device="cuda")
+        for k in range(a.shape[1]):
+            c = (c.double() + a[:, k:k + 1].double() * b[k:k + 1].double()).float()
+        return c
+
+    k, o = ("Y", outs[0]) if din < dout else ("dX", outs[1])
+    want = chain(X, W.T) + s * chain((X.double() @ A.double().T).float(), B.T) if k == "Y" else chain(dY, W) + chain((s * dY.double() @ B.double()).float(), A)
+    err, err_chain = ((t.double() - ref[k]).norm().item() for t in (o, want))
+    assert err <= 1.01 * err_chain, err / err_chain
