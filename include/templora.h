@@ -296,7 +296,9 @@ tl_status tl_layer_step(tl_lora* lora, int32_t layer, const float* h_in, const f
                         float* h_out, float* dh_in, float lr, int32_t apply_adamw);
 
 /*
- * A single LoRA-adapted linear layer in fp32 (no model needed):
+ * A single LoRA-adapted linear layer in fp32 (no model needed; operands, outputs and sums are fp32; large products are formed from
+ * bf16 parts that hold each operand whole, no further from exact than a chain of fp32 products, about sqrt(K) 2^-24 of the 2-norm
+ * over K elements):
  *   Y = X W^T + s (X A^T) B^T;  dX = dY W + dH A, dH = s dY B;  dA = dH^T X;  dB = s dY^T (X A^T);
  *   then (apply_adamw != 0) the first AdamW step (zero moments, step 1) giving A_new, B_new.
  * All pointers device fp32: X [T, d_in], W [d_out, d_in], A [r, d_in], B [d_out, r], dY [T, d_out] (read);
@@ -344,6 +346,13 @@ tl_status tl_k_gemm_nt(const uint16_t* A, int32_t lda, const uint16_t* B, int32_
  * name is then the first range's).  Host only, nothing is launched: the kernel tests use it to show that their shapes reach every configuration. */
 tl_status tl_k_gemm_nt_plan(int32_t M, int32_t N, int32_t K, int32_t K2, size_t workspace_elems, char* name_out,
                             size_t name_cap, int32_t* n_split_out, int32_t* n_launches_out);
+
+/* Which kernels a tl_linear_step of these sizes takes, launch by launch, names separated by spaces into names_out (host, names_cap bytes):
+ * "direct-16x16", "direct-32x32", "64x64", "split-128x128", "split-256x128", "wide-32x32", "wide-64x64".  Two launches (H and dH; Y, dX, dA and
+ * dB), or with one_by_one, as where an output shares memory with an input, six (H, Y, dH, dX, dA, dB).  Host only, nothing is
+ * launched: the tests use it to show that their shapes reach every kernel. */
+tl_status tl_k_linear_step_plan(int32_t T, int32_t d_in, int32_t d_out, int32_t r, float s, int32_t one_by_one, char* names_out,
+                                size_t names_cap);
 
 /* C[Mo,No] (fp32) = alpha * P[T,Mo]^T Q[T,No]  (contraction over the token dimension; dA and dB). */
 tl_status tl_k_gemm_tn(const uint16_t* P, int32_t ldp, const uint16_t* Q, int32_t ldq, int32_t T, int32_t Mo,

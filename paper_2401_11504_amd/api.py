@@ -86,6 +86,7 @@ _SIGS = {
     "tl_k_gemm_nt": [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _vp, _i32, _vp, _i32, _i32, _f32, _vp, _vp, _i32, _i32, _vp,
                      _sz, _vp],
     "tl_k_gemm_nt_plan": [_i32, _i32, _i32, _i32, _sz, C.c_char_p, _sz, C.POINTER(_i32), C.POINTER(_i32)],
+    "tl_k_linear_step_plan": [_i32] * 4 + [_f32, _i32, C.c_char_p, _sz],
     "tl_k_gemm_tn": [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _f32, _vp, _i32, _vp],
     "tl_k_rmsnorm_fwd": [_vp, _vp, _i32, _i32, _f32, _vp, _vp],
     "tl_k_rmsnorm_bwd": [_vp, _vp, _vp, _vp, _i32, _i32, _f32, _vp, _vp, _vp],
@@ -339,6 +340,13 @@ def tl_k_gemm_nt_plan(M, N, K, K2=0, workspace_elems=0):
     sp, nl = _i32(0), _i32(0)
     _chk(_lib.tl_k_gemm_nt_plan(M, N, K, K2, workspace_elems, buf, 32, C.byref(sp), C.byref(nl)))
     return buf.value.decode(), sp.value, nl.value
+
+
+def tl_k_linear_step_plan(T, d_in, d_out, r, s=1.0, one_by_one=False):
+    """-> names of the kernels of H and dH and of the rest; one_by_one: of H, Y, dH, dX, dA, dB"""
+    buf = C.create_string_buffer(128)
+    _chk(_lib.tl_k_linear_step_plan(T, d_in, d_out, r, s, int(one_by_one), buf, 128))
+    return buf.value.decode().split()
 
 
 def tl_k_gemm_tn(P, Q, C_out, alpha=1.0, stream=None):

@@ -815,7 +815,9 @@ static double f32_cost(const F32Batch& grp, const F32Cost& c) {
     return c.fixed + (chain > tiles ? chain : tiles);
 }
 
-// The products in the order they go out, and the instance that takes them (-1: rows too wide for all but WIDE ones).
+static const char* const F32_INSTANCES[] = {"direct-16x16", "direct-32x32", "64x64", "split-128x128", "split-256x128", "wide-32x32", "wide-64x64"};
+
+// The products in the order they go out, and the instance that takes them.
 static int arrange_f32(const F32Product* prods, int n, F32Batch& grp) {
     grp.n = n;
     int order[F32_GROUP_MAX];
@@ -823,17 +825,20 @@ static int arrange_f32(const F32Product* prods, int n, F32Batch& grp) {
     for (int k = 1; k < n; ++k)               // longest contraction first: what is left for the end are short tiles
         for (int j = k; j > 0 && prods[order[j]].K > prods[order[j - 1]].K; --j) { int t = order[j]; order[j] = order[j - 1]; order[j - 1] = t; }
     bool wide = false, split = true;
+    long t64 = 0;
     for (int k = 0; k < n; ++k) {
         F32Product& q = grp.p[k];
         q = prods[order[k]];
         wide |= q.lda > (1L << 22) || q.ldb > (1L << 22) || q.lda2 > (1L << 22) || q.ldb2 > (1L << 22);
+        if (q.kind != F32_MN) t64 += (long)cdiv(q.M, 64) * cdiv(q.N, 64);
         // (a side that leaves half of a split tile empty, as the low-rank products have; a contraction of less than a tile -- of 4 or 8 elements
         // and a low-rank term of one to three it would be 1.07 to 1.15 times as far from fp64 as single products --; factors that would move what
         // the scaled parts hold)
         split &= (q.kind == F32_MN || (q.M > 64 && q.N > 64)) && q.K >= SPLIT_BK;
         for (float f : {q.alpha, q.K2 > 0 ? q.alpha2 : 1.f}) split &= f == 0.f || (fabsf(f) >= 0x1p-20f && fabsf(f) <= 0x1p20f);
     }
-    if (wide) return -1;
+    // (rows that wide are long chains on few tiles, or next to no arithmetic: no 128-wide instance for them)
+    if (wide) return t64 >= 256 ? 6 : 5;
     const F32Cost costs[] = {{16, 16, 0.0036, 0.0024, -1.0}, {32, 32, 0.0045, 0.0061, 0.4}, {64, 64, 0.0162, 0.0185, 2.3},
                              {128, 128, 0.0246, 0.0475, -0.9}, {256, 128, 0.0573, 0.0731, 2.7}};
     int best = 0;
@@ -842,24 +847,23 @@ static int arrange_f32(const F32Product* prods, int n, F32Batch& grp) {
     return best;
 }
 
+const char* gemm_f32_plan(const F32Product* prods, int n) {
+    F32Batch grp;
+    return n >= 1 && n <= F32_GROUP_MAX ? F32_INSTANCES[arrange_f32(prods, n, grp)] : "";
+}
+
 hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s) {
     if (n < 1 || n > F32_GROUP_MAX) return hipErrorInvalidValue;
+    for (int k = 0; k < n; ++k)
+        if (prods[k].M <= 0 || prods[k].N <= 0 || prods[k].K <= 0) return hipErrorInvalidValue;
     F32Batch grp;
-    const int best = arrange_f32(prods, n, grp);
-    long t64 = 0;
-    for (int k = 0; k < n; ++k) {
-        const F32Product& q = grp.p[k];
-        if (q.M <= 0 || q.N <= 0 || q.K <= 0) return hipErrorInvalidValue;
-        if (q.kind == F32_MN) continue;
-        t64 += (long)cdiv(q.M, 64) * cdiv(q.N, 64);
-    }
-    // (rows that wide are long chains on few tiles, or next to no arithmetic: no 128-wide instance for them)
-    if (best < 0) return t64 >= 256 ? run_f32<64, 64, 32, true>(grp, s) : run_f32<32, 32, 64, true>(grp, s);
-    switch (best) {
+    switch (arrange_f32(prods, n, grp)) {
         case 0: return run_direct<1>(grp, s);
         case 1: return run_direct<2>(grp, s);
         case 2: return run_f32<64, 64, 32>(grp, s);
         case 3: return run_split<128, 128, 2, 4>(grp, s);
-        default: return run_split<256, 128, 4, 2>(grp, s);
+        case 4: return run_split<256, 128, 4, 2>(grp, s);
+        case 5: return run_f32<32, 32, 64, true>(grp, s);
+        default: return run_f32<64, 64, 32, true>(grp, s);
     }
 }

@@ -65,7 +65,7 @@ struct GemmTNGroup {
 };
 hipError_t launch_gemm_tn_grouped(GemmTNGroup& g, hipStream_t s);
 
-// fp32 products of the single-layer fp32 step (gemm_f32.hip): C = alpha A B^T (+ alpha2 A2 B2^T), fp32 throughout.
+// fp32 products of the single-layer fp32 step (gemm_f32.hip): C = alpha A B^T (+ alpha2 A2 B2^T), operands, outputs and sums in fp32.
 enum F32Kind { F32_KK = 0, F32_KN = 1, F32_MN = 2 };   // A [M,K] B [N,K] / A [M,K] B [K,N] / A [K,M] B [K,N], row-major
 // the first AdamW step of a parameter (moments zero before it)
 struct AdamWFirst { float lr, b1, b2, eps, decay, inv_bc1, inv_bc2; };
@@ -91,6 +91,8 @@ struct F32Product {
 constexpr int F32_GROUP_MAX = 4;
 // n independent products in one launch.  Outputs must not overlap any operand.
 hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s);
+// The name of the instance that such a launch takes.
+const char* gemm_f32_plan(const F32Product* prods, int n);
 hipError_t launch_adamw_first(const float* g, const float* p, float* p_new, size_t n, const AdamWFirst& o, hipStream_t s);
 
 // ---------------------------------------------------------------- attention (attention.hip)

@@ -1266,6 +1266,24 @@ extern "C" tl_status tl_profile_read(tl_lora* L, double* ms_total, int64_t* laun
 }
 
 // ---------------------------------------------------------------- single fp32 LoRA-adapted linear layer
+// The products of a step: low, H = X A^T and dH = s dY B;  p, Y = X W^T + s H B^T, dX = dY W + dH A, dA = dH^T X, dB = s dY^T H.
+static void linear_step_products(const float* X, const float* W, const float* A, const float* B, const float* dY, int T, int d_in,
+                                 int d_out, int r, float s, float* Y, float* dX, float* dA, float* dB, float* H, float* dH,
+                                 F32Product (&low)[2], F32Product (&p)[4]) {
+    low[0].kind = F32_KK; low[0].A = X; low[0].lda = d_in; low[0].B = A; low[0].ldb = d_in;
+    low[0].M = T; low[0].N = r; low[0].K = d_in; low[0].C = H; low[0].ldc = r;
+    low[1].kind = F32_KN; low[1].A = dY; low[1].lda = d_out; low[1].B = B; low[1].ldb = r;
+    low[1].M = T; low[1].N = r; low[1].K = d_out; low[1].alpha = s; low[1].C = dH; low[1].ldc = r;
+    p[0].kind = F32_KK; p[0].A = X; p[0].lda = d_in; p[0].B = W; p[0].ldb = d_in; p[0].M = T; p[0].N = d_out; p[0].K = d_in;
+    p[0].A2 = H; p[0].lda2 = r; p[0].B2 = B; p[0].ldb2 = r; p[0].K2 = r; p[0].alpha2 = s; p[0].C = Y; p[0].ldc = d_out;
+    p[1].kind = F32_KN; p[1].A = dY; p[1].lda = d_out; p[1].B = W; p[1].ldb = d_in; p[1].M = T; p[1].N = d_in; p[1].K = d_out;
+    p[1].A2 = dH; p[1].lda2 = r; p[1].B2 = A; p[1].ldb2 = d_in; p[1].K2 = r; p[1].C = dX; p[1].ldc = d_in;
+    p[2].kind = F32_MN; p[2].A = dH; p[2].lda = r; p[2].B = X; p[2].ldb = d_in; p[2].M = r; p[2].N = d_in; p[2].K = T;
+    p[2].C = dA; p[2].ldc = d_in;
+    p[3].kind = F32_MN; p[3].A = dY; p[3].lda = d_out; p[3].B = H; p[3].ldb = r; p[3].M = d_out; p[3].N = r; p[3].K = T;
+    p[3].alpha = s; p[3].C = dB; p[3].ldc = r;
+}
+
 // H, dH: [T, r] scratch.  Two dependent steps: the low-rank products H = X A^T and dH = s dY B, then everything else in one
 // launch.
 static tl_status linear_step_run(const float* X, const float* W, const float* A, const float* B, const float* dY, int T,
@@ -1275,20 +1293,8 @@ static tl_status linear_step_run(const float* X, const float* W, const float* A,
     const size_t na = (size_t)r * d_in, nb = (size_t)d_out * r;
     AdamWFirst opt = {lr, beta1, beta2, eps, 1.f - lr * wd, (float)(1.0 / (1.0 - (double)beta1)),
                       (float)(1.0 / (1.0 - (double)beta2))};
-    F32Product low[2];
-    low[0].kind = F32_KK; low[0].A = X; low[0].lda = d_in; low[0].B = A; low[0].ldb = d_in;
-    low[0].M = T; low[0].N = r; low[0].K = d_in; low[0].C = H; low[0].ldc = r;
-    low[1].kind = F32_KN; low[1].A = dY; low[1].lda = d_out; low[1].B = B; low[1].ldb = r;
-    low[1].M = T; low[1].N = r; low[1].K = d_out; low[1].alpha = s; low[1].C = dH; low[1].ldc = r;
-    F32Product p[4];      // Y = X W^T + s H B^T;  dX = dY W + dH A;  dA = dH^T X;  dB = s dY^T H
-    p[0].kind = F32_KK; p[0].A = X; p[0].lda = d_in; p[0].B = W; p[0].ldb = d_in; p[0].M = T; p[0].N = d_out; p[0].K = d_in;
-    p[0].A2 = H; p[0].lda2 = r; p[0].B2 = B; p[0].ldb2 = r; p[0].K2 = r; p[0].alpha2 = s; p[0].C = Y; p[0].ldc = d_out;
-    p[1].kind = F32_KN; p[1].A = dY; p[1].lda = d_out; p[1].B = W; p[1].ldb = d_in; p[1].M = T; p[1].N = d_in; p[1].K = d_out;
-    p[1].A2 = dH; p[1].lda2 = r; p[1].B2 = A; p[1].ldb2 = d_in; p[1].K2 = r; p[1].C = dX; p[1].ldc = d_in;
-    p[2].kind = F32_MN; p[2].A = dH; p[2].lda = r; p[2].B = X; p[2].ldb = d_in; p[2].M = r; p[2].N = d_in; p[2].K = T;
-    p[2].C = dA; p[2].ldc = d_in;
-    p[3].kind = F32_MN; p[3].A = dY; p[3].lda = d_out; p[3].B = H; p[3].ldb = r; p[3].M = d_out; p[3].N = r; p[3].K = T;
-    p[3].alpha = s; p[3].C = dB; p[3].ldc = r;
+    F32Product low[2], p[4];
+    linear_step_products(X, W, A, B, dY, T, d_in, d_out, r, s, Y, dX, dA, dB, H, dH, low, p);
     // A caller may have an output share memory with an input that is not needed any more by the time it is written in the
     // order H, Y, dH, dX, dA, dB, A_new, B_new (an update in place: A_new = A), or with an output that it does not want.
     // Then that order is kept, one launch after another.
@@ -1435,6 +1441,19 @@ extern "C" tl_status tl_k_gemm_nt_plan(int32_t M, int32_t N, int32_t K, int32_t 
     snprintf(name_out, name_cap, "%s", name);
     if (n_split_out) *n_split_out = sp;
     if (n_launches_out) *n_launches_out = two ? 2 : 1;
+    return TL_OK;
+}
+extern "C" tl_status tl_k_linear_step_plan(int32_t T, int32_t d_in, int32_t d_out, int32_t r, float s, int32_t one_by_one, char* names_out,
+                                          size_t names_cap) {
+    KARGS_OK(names_out && names_cap > 0 && T > 0 && d_in > 0 && d_out > 0 && r > 0, "tl_k_linear_step_plan");
+    F32Product low[2], p[4];     // only sizes and scales matter to the choice
+    linear_step_products(nullptr, nullptr, nullptr, nullptr, nullptr, T, d_in, d_out, r, s, nullptr, nullptr, nullptr, nullptr, nullptr,
+                         nullptr, low, p);
+    if (one_by_one)
+        snprintf(names_out, names_cap, "%s %s %s %s %s %s", gemm_f32_plan(&low[0], 1), gemm_f32_plan(&p[0], 1), gemm_f32_plan(&low[1], 1),
+                 gemm_f32_plan(&p[1], 1), gemm_f32_plan(&p[2], 1), gemm_f32_plan(&p[3], 1));
+    else
+        snprintf(names_out, names_cap, "%s %s", gemm_f32_plan(low, 2), gemm_f32_plan(p, 4));
     return TL_OK;
 }
 extern "C" tl_status tl_k_gemm_tn(const uint16_t* P, int32_t ldp, const uint16_t* Q, int32_t ldq, int32_t T, int32_t Mo,

@@ -1,6 +1,7 @@
-"""The fp32 LoRA-adapted linear step at the sizes where its tiles can go wrong: every tile shape (32, 64, 128 wide, and the one
-for wide rows), row lengths that are no multiple of four floats, ragged rows, columns, ranks and contractions, an update in place,
-values that are not finite or not normal.  Reference: fp64."""
+"""The fp32 LoRA-adapted linear step at the sizes where its tiles can go wrong: every kernel and tile shape (fragments straight from
+memory, tiles of 64, operands in bf16 parts, wide rows; test_linear_plan.py holds which size takes which), row lengths that are no
+multiple of four floats, ragged rows, columns, ranks and contractions, an update in place, values of every scale, values that are not
+finite or not normal.  Reference: fp64."""
 import numpy as np
 import pytest
 
@@ -14,17 +15,18 @@ LR = 5e-5
 
 def tol(*dims):
     """A chain of K fp32 products strays by about sqrt(K) 2^-24 of its 2-norm, K the longest contraction (16 more for the few
-    roundings around it); doubled for the low-rank chain.  No contraction is split."""
+    roundings around it); doubled for the low-rank chain.  (Where eight waves share a contraction, or the matrix instruction rounds once per
+    eight elements, there are fewer roundings.)"""
     return 2 * (max(dims) + 16) ** 0.5 * 2.0 ** -24
 
 
 CASES = [
-    # T, d_in, d_out, r; the low-rank products have 32-wide tiles but for the last
-    (1, 1, 1, 1), (33, 100, 101, 4), (5, 64, 3, 32), (31, 129, 66, 33),      # 32-wide tiles
-    (300, 777, 1003, 7), (65, 1030, 259, 16),                                # more of them
-    (515, 1023, 1030, 64), (700, 1200, 1111, 37),                            # 64-wide tiles
-    (1027, 4096, 2050, 64), (1400, 2049, 4101, 48), (130, 4096, 16400, 5),   # 128-wide tiles
-    (8200, 65, 40, 64),                                                      # 64-wide tiles throughout
+    # T, d_in, d_out, r; the low-rank products are direct-16x16 throughout
+    (1, 1, 1, 1), (33, 100, 101, 4), (5, 64, 3, 32), (31, 129, 66, 33), (65, 1030, 259, 16), (8200, 65, 40, 64),      # direct-16x16
+    (300, 777, 1003, 7),                                                                                              # direct-32x32
+    (512, 768, 768, 8), (592, 741, 2895, 8), (621, 1264, 686, 24), (8192, 63, 4096, 3),                               # 64x64
+    (515, 1023, 1030, 64), (700, 1200, 1111, 37), (130, 4096, 16400, 5),                                              # split-128x128
+    (1027, 4096, 2050, 64), (1400, 2049, 4101, 48),                                                                   # split-256x128
 ]
 
 
@@ -132,8 +134,8 @@ def test_subnormal_products_and_sums():
 
 
 # Operands cut into bf16 parts: ragged rows, columns and contractions of both tiles (256x128: the first; 128x128: the others), and
-# what the parts do not hold -- infinities, values below 2^-110 -- in the first and the last tile of a contraction, in either half of
-# a tile's rows, and in the low-rank factors.
+# what the parts do not hold (infinities) or hold by a scale (values below 2^-110) in the first and the last tile of a contraction, in
+# either half of a tile's rows, and in the low-rank factors.
 SPLIT = [(1029, 2050, 2049, 64), (701, 2500, 2501, 33), (257, 4095, 4100, 7), (1400, 1030, 1100, 1)]
 
 
@@ -170,7 +172,7 @@ def test_split_operands_not_finite(T, din, dout, r, which, at, value):
 @pytest.mark.parametrize("T,din,dout,r", SPLIT[:2])
 @pytest.mark.parametrize("rows", [slice(0, None), slice(100, 101), slice(-1, None)])
 def test_split_operands_tiny(T, din, dout, r, rows):
-    """Rows of X of the order of 2^-116, which bf16 parts would hold to 17 bits: their outputs (2^-116 too) are as precise as the others."""
+    """Rows of X of the order of 2^-116, which bf16 parts without a scale would hold to 17 bits: their outputs (2^-116 too) are as precise as the others."""
     ins, s = make(T, din, dout, r), 1.5
     ins[0][rows] *= 2.0 ** -116
     dev = [t.cuda() for t in ins]
@@ -213,10 +215,13 @@ def test_split_operands_scales(T, din, dout, r, what):
             assert bool((err.norm(dim=dim) <= 2 * bound).all()), (k, dim)
 
 
-# Fragments straight from memory: both tiles (16x16 for the first five, 32x32 for the main products of the others), sides one off a multiple of
-# the tile, contractions shorter than one piece of sixteen elements, one off it, and of fewer pieces than there are waves.
-@pytest.mark.parametrize("T,din,dout,r", [(17, 15, 33, 1), (16, 128, 16, 16), (31, 129, 47, 17), (48, 127, 2000, 5), (2, 3000, 1, 2),
-                                          (1157, 377, 486, 64), (1382, 182, 120, 33), (631, 389, 961, 4), (1400, 16, 96, 15)])
+# Fragments straight from memory: both tiles (DIRECT32: 32x32 for the main products; the others 16x16, but for the one of 1157 tokens, which is split),
+# sides one off a multiple of the tile, contractions shorter than one piece of sixteen elements, one off it, and of fewer pieces than there are waves.
+DIRECT16 = [(17, 15, 33, 1), (16, 128, 16, 16), (31, 129, 47, 17), (48, 127, 2000, 5), (2, 3000, 1, 2), (1382, 182, 120, 33), (1400, 16, 96, 15)]
+DIRECT32 = [(631, 389, 961, 4), (301, 1001, 999, 17), (129, 2047, 2050, 15), (1001, 129, 1100, 31)]
+
+
+@pytest.mark.parametrize("T,din,dout,r", DIRECT16 + DIRECT32 + [(1157, 377, 486, 64)])
 def test_direct_fragments(T, din, dout, r):
     ins, s = make(T, din, dout, r), 1.5
     dev = [t.cuda() for t in ins]
@@ -264,7 +269,7 @@ def test_scale_varies_along_the_contraction(T, din, dout, r, pattern, e):
 
 # Operands of one sign: what a sum leaves out does not cancel.  Random mantissas, and ones whose bits are all set; the low-rank term is
 # far larger than any one product.  Roundings stay at random: the walk of a chain without the doubling of `tol`.
-@pytest.mark.parametrize("T,din,dout,r", [(512, 1024, 1536, 16), (1029, 2050, 2049, 64), (701, 2500, 2501, 33)])
+@pytest.mark.parametrize("T,din,dout,r", [(512, 1024, 1536, 16)] + SPLIT[:2])
 @pytest.mark.parametrize("values", ["random", "all bits set"])
 def test_operands_of_one_sign(T, din, dout, r, values):
     ins = [t.abs() + 0.1 if values == "random" else torch.full_like(t, 2 - 2.0 ** -23) for t in make(T, din, dout, r)]
@@ -318,8 +323,10 @@ def test_split_operands_beyond_the_scaled_parts(T, din, dout, r, what):
 # Short contractions (in place, where each product is a launch of its own: Y where d_in is the short side, dX where d_out is), the first two too
 # short for the split kernel, the others of one or two of its tiles: no further from fp64 than a chain of fused multiply-adds in fp32, which is
 # emulated (but for the chain that leads to H or dH, of 4100 elements at most beside a term of a hundredth of the result: 1 %).
-@pytest.mark.parametrize("T,din,dout,r", [(1400, 8, 4100, 3), (8192, 4100, 8, 3), (1400, 32, 4100, 1), (1400, 33, 4100, 3), (1400, 63, 4100, 8),
-                                          (8192, 4100, 32, 3), (1400, 4100, 63, 3)])
+SHORT = [(1400, 8, 4100, 3), (8192, 4100, 8, 3), (1400, 32, 4100, 1), (1400, 33, 4100, 3), (1400, 63, 4100, 8), (8192, 4100, 32, 3), (1400, 4100, 63, 3)]
+
+
+@pytest.mark.parametrize("T,din,dout,r", SHORT)
 def test_short_contractions(T, din, dout, r):
     ins, s = make(T, din, dout, r), 1.5
     dev = [t.cuda() for t in ins]

@@ -54,6 +54,25 @@ def test_static_scratch_variant_matches_the_allocating_one():
         assert torch.equal(outs[0][k], outs[1][k]), k
 
 
+@pytest.mark.parametrize("sizes,kernel", [((701, 2500, 2501, 33), "split-128x128"), ((512, 768, 768, 8), "64x64")])
+def test_static_scratch_variant_on_the_larger_kernels(sizes, kernel):
+    """Two calls in a row, the second with operands of very different scale: what the first left in the scratch does not show."""
+    from paper_2401_11504_amd import api
+    assert api.tl_k_linear_step_plan(*sizes)[1] == kernel
+    T, din, dout, r = sizes
+    g = torch.Generator(device="cuda").manual_seed(5)
+    for scale in (1.0, 2.0 ** 40):
+        X, W, A, B, dY = (torch.randn(*z, generator=g, device="cuda") * std for z, std in (
+            ((T, din), scale), ((dout, din), 0.02 / scale), ((r, din), 0.02 / scale), ((dout, r), 0.01), ((T, dout), scale)))
+        got = []
+        for fn in (api.tl_linear_step_static, api.tl_linear_step):
+            out = [torch.full(z, float("nan"), device="cuda") for z in ((T, dout), (T, din), (r, din), (dout, r), (r, din), (dout, r))]
+            fn(X, W, A, B, dY, 2.0, LR, 0.9, 0.999, 1e-8, 0.01, True, *out)
+            got.append(out)
+        for a, b in zip(*got):
+            assert torch.equal(a, b) and bool(torch.isfinite(a).all())
+
+
 def test_static_scratch_variant_refuses_what_does_not_fit():
     from paper_2401_11504_amd import api
     # 2 T r alone exceeds the 2^20-float buffer: refused on the host before anything is launched or read
