@@ -6,17 +6,17 @@
 // Small ones go through the fp32 matrix instructions (f32_direct_kernel, f32_group_kernel), large ones through the bf16 ones with every operand cut into
 // three parts (f32_split_kernel); f32_cost holds what the line between them was timed on.
 //
-// v_mfma_f32_16x16x4_f32 adds its four products one after another, each as one fused multiply-add: an output is a chain
-// fma(a[k], b[k], ..) over k, the same value wherever its tile boundaries lie.  (The low-rank term is a chain of its own, added to the
-// stored main term.)  Lane (l16, g) holds row l16, element g of the four, one float per operand: elements 4 g .. 4 g + 3 of sixteen,
+// v_mfma_f32_16x16x4_f32 adds its four products one after another, each as one fused multiply-add: in f32_group_kernel an output is a chain
+// fma(a[k], b[k], ..) over k, the same value wherever its tile boundaries lie (the low-rank term a chain of its own, added to the
+// stored main term), in f32_direct_kernel the sum of eight of them.  Lane (l16, g) holds row l16, element g of the four, one float per operand: elements 4 g .. 4 g + 3 of sixteen,
 // for four instructions, so that they are one LDS read where the contraction is contiguous (64x64 tiles, 128 tokens, 4096 x 4096:
 // 174 us for the step, 147 as four reads became one).  An operand whose contraction is contiguous is kept in LDS as it comes, [row][k], with a stride
 // that lets the 64 lanes of a read touch 64 banks; one whose rows (or columns) are contiguous as [k][row], and a lane reads
 // F neighbouring rows at once, one for each of the F fragments of its wave's share (the output is written with that order
 // undone).  Neither is transposed on the way.
 //
-// The bound is the matrix unit: 256 flop per clock and CU, a sixteenth of the bf16 rate, so that LDS reads are cheap beside
-// it and tiles staged through registers are enough where the chip is full.
+// The bound of f32_group_kernel, where the chip is full, is the matrix unit: 256 flop per clock and CU, a sixteenth of the bf16 rate, so that
+// LDS reads are cheap beside it and tiles staged through registers are enough.  The two others say theirs.
 #include "kernels.h"
 #include "tiles.h"
 #include <type_traits>
@@ -137,10 +137,7 @@ __device__ __forceinline__ void f32_tile(const F32Product& q, int m0, int n0, fl
         // .. t + 2 + PF are in flight.  One barrier per tile: it makes t + 2 visible and frees the place of t + 1.
         F32Stage<BM, BKF, AKC, WIDE, PAST> ra[PF];
         F32Stage<BN, BKF, BKC, WIDE, PAST> rb[PF];
-        // (128-wide tiles have sixteen independent chains to hide the LDS behind, and no registers for a second set: they read
-        // a tile's fragments when they multiply it)
-        constexpr bool AHEAD = BM < 128;
-        float a[AHEAD ? 2 : 1][KS][FM][4], b[AHEAD ? 2 : 1][KS][FN][4];
+        float a[2][KS][FM][4], b[2][KS][FN][4];
         f32x4_t acc[FM][FN];
         // (tiles behind the last one read as zeros and are never multiplied; their first element may lie beyond 2^31)
         auto tile_k = [](int t) { return (int)((unsigned)t * BKF); };
@@ -171,12 +168,12 @@ __device__ __forceinline__ void f32_tile(const F32Product& q, int m0, int n0, fl
         park(S1{}, 1, 1);
         load(S1{}, PF + 1);
         __syncthreads();
-        if constexpr (AHEAD) fetch(S0{}, 0);
+        fetch(S0{}, 0);
         int p0 = 0, p1 = 1, p2 = 2;               // places of tiles t, t + 1 and t + 2
         auto step = [&](auto u, int t) {          // u = t % PF
-            using cur = std::integral_constant<int, AHEAD ? u.value & 1 : 0>;
+            using cur = std::integral_constant<int, u.value & 1>;
             using slot = std::integral_constant<int, (u.value + 2) % PF>;
-            if constexpr (AHEAD) fetch(std::integral_constant<int, cur::value ^ 1>{}, p1); else fetch(cur{}, p0);
+            fetch(std::integral_constant<int, cur::value ^ 1>{}, p1);
             park(slot{}, p2, t + 2);
             load(slot{}, t + 2 + PF);
 #pragma unroll
@@ -194,8 +191,7 @@ __device__ __forceinline__ void f32_tile(const F32Product& q, int m0, int n0, fl
             p0 = p1; p1 = p2; p2 = p;
         };
         // Whole rounds of PF tiles, then the rest: with exits between the steps the compiler sees a way from each of them to the next
-        // round and has step 0 wait for the loads just issued (2 to 6 % of a
-        // small step).
+        // round and has step 0 wait for the loads just issued (2 to 6 % of a small step).
         int t = 0;
         for (; t + PF <= nk; t += PF) {
             step(S0{}, t);
@@ -433,7 +429,7 @@ __global__ __launch_bounds__(DIRECT_WAVES * 64, 4) void f32_direct_kernel(F32Bat
 // elements: 24 K / 32 roundings instead of K, those of the largest products last (of the smallest last: contractions of 1 to 32 elements 5.3e-8 to
 // 9.6e-8 from fp64 instead of 3.4e-8 to 3.8e-8, chain of fp32 products 2.5e-8 to 1.0e-7).  (Parts cut off instead of rounded have all the
 // sign of x, and what a large sum drops of their products, each below half an ulp of it, adds up: with operands of one sign 2.1e-6 to 4e-5
-// where this way is 1.8e-7 to 8.2e-7.)
+// where this way is 9e-9 to 3.3e-7.)
 // Distance from fp64, 2-norm, chain of fp32 products / parts: 1024 tokens, 4096 x 4096, rank 64 Y 1.15e-6 / 1.01e-6, dA 1.28e-6 / 6.4e-7,
 // of one sign Y 5.3e-7 / 3.6e-7; 1400 tokens, 256 x 1024, rank 64 Y 2.9e-7 / 2.9e-7, of one sign 1.2e-7 / 7.8e-8.  Where a few large products make up
 // a long contraction it is the other way round (dX of a dY that is a softmax 6.3e-8 / 1.9e-7).
