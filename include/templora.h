@@ -297,8 +297,7 @@ tl_status tl_layer_step(tl_lora* lora, int32_t layer, const float* h_in, const f
 
 /*
  * A single LoRA-adapted linear layer in fp32 (no model needed; operands, outputs and sums are fp32; large products are formed from
- * bf16 parts that hold each operand whole, no further from exact than a chain of fp32 products, about sqrt(K) 2^-24 of the 2-norm
- * over K elements):
+ * bf16 parts that hold each operand whole, within about sqrt(K) 2^-24 of the 2-norm over K elements, as a chain of fp32 products is):
  *   Y = X W^T + s (X A^T) B^T;  dX = dY W + dH A, dH = s dY B;  dA = dH^T X;  dB = s dY^T (X A^T);
  *   then (apply_adamw != 0) the first AdamW step (zero moments, step 1) giving A_new, B_new.
  * All pointers device fp32: X [T, d_in], W [d_out, d_in], A [r, d_in], B [d_out, r], dY [T, d_out] (read);
