@@ -424,15 +424,14 @@ __global__ __launch_bounds__(DIRECT_WAVES * 64, 4) void f32_direct_kernel(F32Bat
 
 // ---------------------------------------------------------------- split operands on the bf16 matrix instructions
 // The same products with every operand cut into three bf16 parts, x = x1 + x2 + x3 (each the nearest bf16 to what is left, which the
-// third holds exactly), and a b taken as a2 b2 + a2 b1 + a3 b1 + a1 b3 + a1 b2 + a1 b1 in fp32 accumulators.  What is left out,
-// a2 b3 + a3 b2 + a3 b3, is below 2^-26 of a product and of either sign.  The matrix instruction rounds to nearest, some four times for its 32
-// elements: 24 K / 32 roundings instead of K, those of the largest products last (of the smallest last: contractions of 1 to 32 elements 5.3e-8 to
-// 9.6e-8 from fp64 instead of 3.4e-8 to 3.8e-8, chain of fp32 products 2.5e-8 to 1.0e-7).  (Parts cut off instead of rounded have all the
-// sign of x, and what a large sum drops of their products, each below half an ulp of it, adds up: with operands of one sign 2.1e-6 to 4e-5
-// where this way is 9e-9 to 3.3e-7.)
-// Distance from fp64, 2-norm, chain of fp32 products / parts: 1024 tokens, 4096 x 4096, rank 64 Y 1.15e-6 / 1.01e-6, dA 1.28e-6 / 6.4e-7,
-// of one sign Y 5.3e-7 / 3.6e-7; 1400 tokens, 256 x 1024, rank 64 Y 2.9e-7 / 2.9e-7, of one sign 1.2e-7 / 7.8e-8.  Where a few large products make up
-// a long contraction it is the other way round (dX of a dY that is a softmax 6.3e-8 / 1.9e-7).
+// third holds exactly), and a b taken as (a1 b3 + a2 b2 + a1 b2 + a3 b1 + a2 b1) + a1 b1, each of the two in fp32 accumulators of its own.
+// What is left out, a2 b3 + a3 b2 + a3 b3, is below 2^-26 of a product and of either sign.  The matrix instruction rounds to nearest,
+// some four times for its 32 elements: K / 8 roundings at the size of the result instead of K.
+// Distance from fp64, 2-norm, chain of fp32 products / parts: 1024 tokens, 4096 x 4096, rank 64 Y 1.15e-6 / 4.0e-7, dA 1.28e-6 / 4.5e-7,
+// operands of one sign Y 1.8e-7 / 5.4e-8, a dY that is a softmax dX 6.3e-8 / 9.4e-8; 700, 2500 x 2500, rank 32 Y 8.9e-7 / 3.1e-7, of one sign
+// 1.7e-7 / 5.3e-8.  (With all six products in one accumulator: Y 1.01e-6, the softmax's dX 1.9e-7, the same time.  With a sum of each tile by itself and
+// added to the accumulator: 2.3e-7, 7.3e-8, 385 instead of 367 us.  Parts cut off instead of rounded have all the sign of x, and what a large
+// sum drops of their products, each below half an ulp of it, adds up: with operands of one sign 2.1e-6 to 4e-5.)
 //
 // The bf16 unit has sixteen times the rate, so that six products take 6/16 of the time of one in fp32.  What is cut is cut on
 // its way from the staging registers to LDS, seven vector operations an element, in slices between the matrix instructions.
@@ -559,13 +558,25 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
 #pragma unroll
         for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN, l16 = lane & 15, g = lane >> 4;
+    const int wm = wave / WN, wn = wave % WN;
     int* overflow = (int*)smem;            // an accumulator is not finite
     bf16_t* planes = (bf16_t*)(smem + SPLIT_HEAD);
     const int a_off = OA::lane_offset(wm * TM, lane), b_off = OA::ELEMS + OB::lane_offset(wn * TN, lane);
-    bf16x8_t fa[3][FM], fb[3][FN];
-    auto read_a = [&](const bf16_t* stage, int s, int i) { fa[s][i] = OA::fragment(stage + a_off + s * OA::PLANE, i); };
+    // The largest products (first parts) go into acc, the five others into `small`, which joins acc at the end: there each rounding is one of
+    // 2^-8 of the result.  Fragments are taken BLOCK at a time, A's of the next block read beside the matrix instructions of this one
+    // (254 registers; A's third parts are read in their own block, with them it would be scratch memory).
+    constexpr int RB = FN >= 4 ? 1 : FN == 2 ? 2 : 1, BLOCK = RB * FN, NB = FM / RB;
+    static_assert(FM % RB == 0 && NB % 2 == 0, "A's fragments of block b are in set b % 2");
+    f32x4_t small[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) small[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    bf16x8_t fa[2][2][RB], fa2[RB], fb[3][FN];
+    auto read_a = [&](const bf16_t* stage, auto set, int b, int f) { fa[set.value][f % 2][f / 2] = OA::fragment(stage + a_off + f % 2 * OA::PLANE, b * RB + f / 2); };
+    auto read_a2 = [&](const bf16_t* stage, int b, int f) { fa2[f] = OA::fragment(stage + a_off + 2 * OA::PLANE, b * RB + f); };
     auto read_b = [&](const bf16_t* stage, int s, int i) { fb[s][i] = OB::fragment(stage + b_off + s * OB::PLANE, i); };
+    using S0 = std::integral_constant<int, 0>;
     // the main term, and the low-rank one on top of it, with alpha2 in its first operand.  (A large low-rank term below a long main one would be
     // rounded at each of its steps: 512 tokens, 1024 x 1024, rank 64, operands of one sign, Y 4.6e-7 from fp64 that way.)
 #pragma unroll 1
@@ -612,9 +623,11 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
             }
             __syncthreads();
 #pragma unroll
-            for (int i = 0; i < FM; ++i) read_a(planes, 1, i);
+            for (int i = 0; i < FN; ++i) read_b(planes, 2, i);
 #pragma unroll
             for (int i = 0; i < FN; ++i) read_b(planes, 1, i);
+#pragma unroll
+            for (int f = 0; f < 2 * RB; ++f) read_a(planes, S0{}, 0, f);
         }
         bf16_t *stage = planes, *other = planes + STAGE;
         const int nk = (K + SPLIT_BK - 1) / SPLIT_BK;
@@ -637,28 +650,31 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
                 asm volatile("" ::: "memory");
             };
             unrolled<NMF>([&](auto ec) {
-                constexpr int e = ec.value, gr = e / NG, x = e % NG, i = x / FN, jn = x % FN, left = NMF - AT_BARRIER;
-                constexpr int pa = gr < 2 ? 1 : gr == 2 ? 2 : 0, pb = gr == 0 || gr == 4 ? 1 : gr == 3 ? 2 : 0;
+                constexpr int e = ec.value, b = e / (6 * BLOCK), at = e % (6 * BLOCK), gr = at / BLOCK, x = at % BLOCK, i = x / FN, jn = x % FN;
+                constexpr int left = NMF - AT_BARRIER, set = b % 2;
+                constexpr int pa = gr == 1 || gr == 4 ? 1 : gr == 3 ? 2 : 0, pb = gr == 0 ? 2 : gr == 1 || gr == 2 ? 1 : 0;
                 // B first: a lane then holds row l16 of A's fragment, columns 4 g .. 4 g + 3 of B's
-                acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[pb][jn], fa[pa][i], acc[i][jn], 0, 0, 0);
-                // the fragments that a later group needs, spread over this one
-                unrolled<FM>([&](auto f) {
-                    if constexpr (f.value * NG / FM == x && gr == 1) read_a(stage, 2, f.value);
-                    if constexpr (f.value * NG / FM == x && gr == 2) read_a(stage, 0, f.value);
-                });
+                f32x4_t& sum = gr == 5 ? acc[b * RB + i][jn] : small[b * RB + i][jn];
+                sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[pb][jn], pa == 2 ? fa2[i] : fa[set][pa % 2][i], sum, 0, 0, 0);
+                // the fragments that are needed next: B's first parts, A's third ones, the others of A's next block
                 unrolled<FN>([&](auto f) {
-                    if constexpr (f.value == x && gr == 0) read_b(stage, 0, f.value);
-                    if constexpr (f.value * NG / FN == x && gr == 2) read_b(stage, 2, f.value);
+                    if constexpr (f.value == e) read_b(stage, 0, f.value);
+                });
+                unrolled<RB>([&](auto f) {
+                    if constexpr (f.value == at) read_a2(stage, b, f.value);
+                });
+                unrolled<2 * RB>([&](auto f) {
+                    if constexpr (b + 1 < NB && 3 * BLOCK + f.value * BLOCK / RB == at) read_a(stage, std::integral_constant<int, set ^ 1>{}, b + 1, f.value);
                 });
                 unrolled<NS>([&](auto y) {
                     if constexpr (y.value * SLICED / NS == e) slice(y);
                 });
                 if constexpr (e + 1 == AT_BARRIER) hand_over();
-                unrolled<FN>([&](auto f) {
-                    if constexpr (AT_BARRIER - 1 + f.value * left / (FM + FN) == e) read_b(other, 1, f.value);
-                });
-                unrolled<FM>([&](auto f) {
-                    if constexpr (AT_BARRIER - 1 + (FN + f.value) * left / (FM + FN) == e) read_a(other, 1, f.value);
+                unrolled<2 * FN + 2 * RB>([&](auto f) {
+                    if constexpr (AT_BARRIER - 1 + f.value * left / (2 * FN + 2 * RB) == e) {
+                        if constexpr (f.value < 2 * FN) read_b(other, 2 - f.value / FN, f.value % FN);
+                        else read_a(other, S0{}, 0, f.value - 2 * FN);
+                    }
                 });
                 __builtin_amdgcn_sched_barrier(0);
             });
@@ -666,6 +682,10 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
             stage = other; other = s;
         }
     }
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] += small[i][j];
     float zero = 0.f;                      // (stays that where every accumulator is finite)
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -677,6 +697,9 @@ __device__ __forceinline__ bool split_tile(const F32Product& q, int m0, int n0, 
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(*overflow)) return false;
     const float alpha = q.alpha / (SPLIT_SCALE * SPLIT_SCALE);
+    int out = threadIdx.x;                 // (as a new value: the output's addresses are not to be held through the loops above)
+    asm volatile("" : "+v"(out));
+    const int l16 = out & 15, g = (out >> 4) & 3;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -793,10 +816,10 @@ static hipError_t run_split(F32Batch& grp, hipStream_t s) {
 // What a launch takes: the longest chain, or all contraction tiles spread over 256 CUs, whichever is longer, per instance: us per
 // contraction element of one chain and of 256 tiles, and what it takes besides.  Fitted to steps of 86 shapes, 33 to 8200 tokens, widths
 // 40 to 5000, ranks 4 to 64, with each instance forced (the low-rank products in 16x16 tiles): what is picked takes 0.3 % longer than the
-// fastest on average, 7 % at worst.  Tokens x d_in x d_out, us in 16x16, 32x32 (direct), 64x64 (fp32), 128x128, 256x128 (split):
-// 128x256x256 30, 32, 37, 41, 49; 36x563x4006 49, 64, 122, 183, 276; 300x1000x1000 62, 52, 57, 71, 97; 128x4096x4096 249, 156, 137, 194, 293;
-// 512x1024x1024 107, 73, 64, 74, 99; 1024x1024x1024 183, 113, 98, 75, 100; 1400x300x4000 239, 164, 144, 185, 277; 333x4096x4096 632, 370, 285, 200,
-// 293; 1024x4096x4096 1879, 1006, 678, 430, 381.
+// fastest on average, 8 % at worst.  Tokens x d_in x d_out, us in 16x16, 32x32 (direct), 64x64 (fp32), 128x128, 256x128 (split):
+// 128x256x256 30, 32, 38, 42, 49; 36x563x4006 50, 65, 122, 186, 270; 300x1000x1000 63, 52, 57, 72, 96; 128x4096x4096 249, 157, 137, 197, 286;
+// 512x1024x1024 107, 74, 66, 75, 98; 1024x1024x1024 182, 112, 98, 75, 99; 1400x300x4000 239, 164, 144, 188, 271; 333x4096x4096 632, 368, 285, 205,
+// 286; 1024x4096x4096 1877, 1006, 678, 427, 377.
 struct F32Cost { int bm, bn; double chain, tiles, fixed; };
 static double f32_cost(const F32Batch& grp, const F32Cost& c) {
     double longest = 0, all = 0;
@@ -827,9 +850,8 @@ static int arrange_f32(const F32Product* prods, int n, F32Batch& grp) {
         q = prods[order[k]];
         wide |= q.lda > (1L << 22) || q.ldb > (1L << 22) || q.lda2 > (1L << 22) || q.ldb2 > (1L << 22);
         if (q.kind != F32_MN) t64 += (long)cdiv(q.M, 64) * cdiv(q.N, 64);
-        // (a side that leaves half of a split tile empty, as the low-rank products have; a contraction of less than a tile -- of 4 or 8 elements
-        // and a low-rank term of one to three it would be 1.07 to 1.15 times as far from fp64 as single products --; factors that would move what
-        // the scaled parts hold)
+        // (a side that leaves half of a split tile empty, as the low-rank products have; a contraction of less than a tile, which is padding for
+        // the rest and not nearer to fp64 in parts; factors that would move what the scaled parts hold)
         split &= (q.kind == F32_MN || (q.M > 64 && q.N > 64)) && q.K >= SPLIT_BK;
         for (float f : {q.alpha, q.K2 > 0 ? q.alpha2 : 1.f}) split &= f == 0.f || (fabsf(f) >= 0x1p-20f && fabsf(f) <= 0x1p20f);
     }

@@ -345,3 +345,19 @@ def test_short_contractions(T, din, dout, r):
     want = chain(X, W.T) + s * chain((X.double() @ A.double().T).float(), B.T) if k == "Y" else chain(dY, W) + chain((s * dY.double() @ B.double()).float(), A)
     err, err_chain = ((t.double() - ref[k]).norm().item() for t in (o, want))
     assert err <= 1.01 * err_chain, err / err_chain
+
+
+# A contraction of which a few large products are almost all (a gradient that is a softmax): a chain rounds a few times at the size of the result and
+# the parts some four times each.  A few roundings of at most 2^-24 each, at random: 2 * 2^-24 (a chain 1.0 to 1.1 of them).
+@pytest.mark.parametrize("T,din,dout,r", SPLIT[:2])
+def test_a_few_large_products(T, din, dout, r):
+    ins, s = make(T, din, dout, r), 1.5
+    ins[4] = torch.softmax(ins[4] * 25, -1)
+    ins[0] = torch.softmax(ins[0] * 25, -1)
+    dev = [t.cuda() for t in ins]
+    outs = [torch.empty(*size, device="cuda") for size in ((T, dout), (T, din), (r, din), (dout, r))]
+    step(dev, s, outs, torch.empty_like(dev[2]), torch.empty_like(dev[3]))
+    ref = reference(dev, s)
+    for k, o in zip(("Y", "dX"), outs):
+        err = ((o.double() - ref[k]).norm() / ref[k].norm()).item()
+        assert err < 2 * 2.0 ** -24, (k, err)
