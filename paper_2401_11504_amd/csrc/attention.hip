@@ -14,6 +14,7 @@
 // The two backward kernels write disjoint outputs, so no atomics are needed and results are
 // bit-reproducible.
 #include <type_traits>
+#include <utility>
 
 #include "kernels.h"
 #include "tiles.h"
@@ -254,275 +255,433 @@ __global__ __launch_bounds__(NW * 64 * KG) void attn_fwd_kernel(const bf16_t* __
     }
 }
 
-// Rotate the (d, d + DH/2) pairs of a transposed fragment set X^T[d][row] (lane = row at position `pos`) by the RoPE
-// angle of that position, sign = -1 for the inverse rotation (the adjoint of the forward rotation): both members of a
-// pair sit in the same lane and register index of fragments dt and dt + ND/2, so nothing crosses lanes.
+// ======================================================================== backward
+// One part of the backward pass: either dK and dV of a block of keys (the streamed rows are the queries from it on) or dQ of a block
+// of queries (DQ; the streamed rows are the keys up to it).  A wave keeps NG groups of 32 rows of its block, their first operand
+// P1 (K; Q) in registers, and takes every second 32-row piece of the streamed matrices X1 (Q; K) and X2 (dO; V):
+//   S[x][p] = X1[x] . P1[p],  dP[x][p] = X2[x] . P2[p]       a lane owns row p of the block, registers run over x
+//   acc1^T[d][p] += X1^T[d][x] dS[x][p]  (dK; dQ),           acc2^T[d][p] += X2^T[d][x] P[x][p]  (dV)
+// with the score fragments reused as B operands (see tiles.h).  Four waves: two row groups of the block, two halves of a 64-row
+// streamed tile; what the two halves gathered is added at the end through LDS.
+//
+// What bounds it: at d_head 128 and long samples the energy of the matrix instructions (a loop of nothing else on random operands runs
+// at 1.6 to 1.85 of 2.4 GHz here, 18 to 20 ns an MFMA; a 64-row tile takes 64 of them a wave for dK and dV, 1.2 us, and 1.7 in all), at
+// 1024 tokens also the two ends of a part (3 us of loads, 1.5 us of exchange and stores).  d_head 128 has one wave per SIMD (256
+// accumulators, 64 registers of K, 64 of S and dP, 32 of P and dS), so nothing but the order of its instructions keeps the matrix unit
+// busy: a wave has 64 rows, so that a fragment of X feeds two MFMAs, and the probabilities are formed between the MFMAs of dP, dS
+// between those of dV.  V of a key block stays in LDS for want of registers.  d_head 64 has two waves of 32 rows per SIMD.  Tiles come by
+// direct-to-LDS loads two tiles ahead, one copy of each: 16-byte chunk c of row x lies at position c ^ swz(x), so that both the reads of
+// 16 rows at one chunk and the transposing reads of four rows x 64 bytes fall into distinct banks.
+// us without and with this (before: waves of 32 rows, two copies of each tile, loads and stores of 32 rows at a time), heads of 128 / 64:
+// 1024 tokens, 32 heads 62 and 46 / 16 heads 39 and 18; 2048 tokens 189 and 138 / 78 and 47; 5120 tokens, 32 heads of 128 1000 and 755.
 template <int DH>
-__device__ __forceinline__ void rope_rotate_dT(f32x16_t* acc, const float2* __restrict__ table, int pos, float sign, int g) {
-    constexpr int ND = DH / 32, HALF = DH / 2;
-    const float2* row = table + (long)pos * HALF;
-#pragma unroll
-    for (int dt = 0; dt < ND / 2; ++dt)
-#pragma unroll
-        for (int vv = 0; vv < 16; ++vv) {
-            const int i = dt * 32 + 8 * (vv >> 2) + 4 * g + (vv & 3);
-            const float2 cs = row[i];
-            const float a = acc[dt][vv], b = acc[dt + ND / 2][vv], sn = cs.y * sign;
-            acc[dt][vv] = a * cs.x - b * sn;
-            acc[dt + ND / 2][vv] = b * cs.x + a * sn;
-        }
+__device__ __forceinline__ int attn_swz(int row) {
+    return DH == 128 ? 4 * (row & 3) | ((row >> 2) & 3) : 4 * ((row >> 1) & 1) | ((row >> 2) & 3);
+}
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
+
+__device__ const float kLseBeyond = 1.0e30f;      // log-sum-exp of a row that does not exist: every probability is 0
+
+template <int DH> struct BwdCfg {
+    static constexpr int NG = DH / 64;                     // 32-row groups per wave
+    static constexpr int PB = 64 * NG;                     // rows of a block
+    static constexpr int RB = DH * 2, TB = 64 * RB;        // bytes of a row, of a tile
+    static constexpr int STAGE = 2 * TB + 512, NST = 3;    // X1, X2, lse and delta of the 64 rows
+    static constexpr int V0 = DH == 128 ? PB * RB : 0;     // V of the block, in front of them
+    static constexpr int LDS = V0 + NST * STAGE;
+    static_assert(LDS <= 160 * 1024 && LDS >= 4 * NG * (DH / 32) * 16 * 256, "the exchange of the accumulators fits");
+};
+__device__ __forceinline__ void mfma32_acc(f32x16_t& c, bf16x8_t a, bf16x8_t b) {
+    // in place, in accumulation registers; two wait states have to pass between a vector instruction that writes an operand and this
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
-// ======================================================================== backward: dQ
-// Same shape as the forward kernel: KG key groups share the causal range tile by tile and their dQ partial sums are
-// added through LDS at the end.  delta[t] = dO[t] . O[t] is read from memory (attn_delta_kernel wrote it for the dK/dV
-// parts of the same launch); with a RoPE table the gradient is rotated back before it is stored, so no separate pass
-// over dq is needed.
-template <int DH, int NW, int KG>
-__device__ __forceinline__ void attn_dq_block(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
-    const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, long ldq, long ldo, int T,
-    bf16_t* __restrict__ dq, float scale, const float2* __restrict__ rope, int qb, int head, unsigned char* smem_raw) {
-    using C = AttnCfg<DH>;
-    constexpr int NT = NW * 64, QB = NW * 32;
-    constexpr int LDT = LTR(DH);
-    constexpr int GROUP_ELEMS = 2 * 64 * C::LSK + 64 * LDT;
-    const int kg = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
-    const int tid = threadIdx.x % NT, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, g = lane >> 5;
-    bf16_t* sK = (bf16_t*)smem_raw + kg * GROUP_ELEMS;
-    bf16_t* sV = sK + 64 * C::LSK;
-    bf16_t* sK2 = sV + 64 * C::LSK;         // K once more, with the row stride of the LDS transpose read (dS K)
-    const int tr_off = tr_lane_offset(lane, LDT);
-    const int q0 = qb * QB, tq0 = q0 + 32 * wave, t_abs = tq0 + l32;
-    const float scale_log2e = scale * 1.4426950408889634f;
-    const bf16_t* qh = q + (long)head * DH;
-    const bf16_t* kh = k + (long)head * DH;
-    const bf16_t* vh = v + (long)head * DH;
-    const bf16_t* doh = d_o + (long)head * DH;
-
-    bf16x8_t qf[C::NKS], dof[C::NKS];
-#pragma unroll
-    for (int ks = 0; ks < C::NKS; ++ks) {
-        uint4 r = (t_abs < T) ? *(const uint4*)(qh + (long)t_abs * ldq + ks * 16 + g * 8) : make_uint4(0, 0, 0, 0);
-        qf[ks] = *(bf16x8_t*)&r;
-        uint4 r2 = (t_abs < T) ? *(const uint4*)(doh + (long)t_abs * ldo + ks * 16 + g * 8) : make_uint4(0, 0, 0, 0);
-        dof[ks] = *(bf16x8_t*)&r2;
-    }
-    const float dlt = (t_abs < T) ? delta[(long)head * T + t_abs] : 0.f;
-    const float lse2 = (t_abs < T) ? lse[(long)head * T + t_abs] * 1.4426950408889634f : 1.0e30f;
-    f32x16_t acc[C::ND];
-#pragma unroll
-    for (int dt = 0; dt < C::ND; ++dt) acc[dt] = zero16();
-
-    const int kend = min(q0 + QB, T);
-    const int n_tiles = (kend + 63) / 64;
-    const int n_iter = (n_tiles + KG - 1) / KG;
-    uint4 rk[8 * DH / NT], rv[8 * DH / NT];
-    unsigned toff[8 * DH / NT];
-    tile_chunk_offsets<DH, NT>(ldq, toff, tid);
-    load_tile_regs<DH, NT>(kh, ldq, kg * 64, T, toff, rk, tid);
-    load_tile_regs<DH, NT>(vh, ldq, kg * 64, T, toff, rv, tid);
-    for (int it = 0; it < n_iter; ++it) {
-        const int u0 = (it * KG + kg) * 64;
-        __syncthreads();
-        store_tile_normal<DH, NT>(sK, rk, tid);
-        store_tile_ld<DH, NT, LDT>(sK2, rk, tid);
-        store_tile_normal<DH, NT>(sV, rv, tid);
-        __syncthreads();
-        if (it + 1 < n_iter) {
-            load_tile_regs<DH, NT>(kh, ldq, u0 + 64 * KG, T, toff, rk, tid);
-            load_tile_regs<DH, NT>(vh, ldq, u0 + 64 * KG, T, toff, rv, tid);
-        }
-        if (u0 > tq0 + 31) continue;
-        f32x16_t s0 = zero16(), s1 = zero16(), dp0 = zero16(), dp1 = zero16();
-#pragma unroll
-        for (int ks = 0; ks < C::NKS; ++ks) {
-            const int o0 = l32 * C::LSK + ks * 16 + g * 8, o1 = o0 + 32 * C::LSK;
-            s0 = mfma32(*(const bf16x8_t*)(sK + o0), qf[ks], s0);
-            s1 = mfma32(*(const bf16x8_t*)(sK + o1), qf[ks], s1);
-            dp0 = mfma32(*(const bf16x8_t*)(sV + o0), dof[ks], dp0);
-            dp1 = mfma32(*(const bf16x8_t*)(sV + o1), dof[ks], dp1);
-        }
-        float ds[32];
-        // only a tile on the diagonal needs the causal mask (wave-uniform); the others skip its compares
-        auto probs = [&](auto masked) {
-#pragma unroll
-            for (int vv = 0; vv < 16; ++vv) {
-                const int u = u0 + 8 * (vv >> 2) + 4 * g + (vv & 3);
-                const float pe0 = fast_exp2(s0[vv] * scale_log2e - lse2);
-                const float pe1 = fast_exp2(s1[vv] * scale_log2e - lse2);
-                const float p0 = (decltype(masked)::value && u > t_abs) ? 0.f : pe0;
-                const float p1 = (decltype(masked)::value && u + 32 > t_abs) ? 0.f : pe1;
-                ds[vv] = p0 * (dp0[vv] - dlt);
-                ds[16 + vv] = p1 * (dp1[vv] - dlt);
-            }
-        };
-        if (u0 + 63 > tq0) probs(std::true_type{}); else probs(std::false_type{});
-#pragma unroll
-        for (int us = 0; us < 2; ++us)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const bf16x8_t b = pack_b_from_d(ds + 16 * us, h);
-#pragma unroll
-                for (int dt = 0; dt < C::ND; ++dt) {
-                    const bf16x8_t a = load_a_tr(sK2, LDT, tr_off, dt * 32, us * 32 + 16 * h);
-                    acc[dt] = mfma32(a, b, acc[dt]);
-                }
-            }
-    }
-    if constexpr (KG > 1) {
-        static_assert(KG == 2, "two key groups");
-        float* mg = (float*)smem_raw;
-        __syncthreads();
-        if (kg == 1) {
-#pragma unroll
-            for (int dt = 0; dt < C::ND; ++dt)
-#pragma unroll
-                for (int vv = 0; vv < 16; ++vv) mg[(dt * 16 + vv) * NT + tid] = acc[dt][vv];
-        }
-        __syncthreads();
-        if (kg == 1) return;
-#pragma unroll
-        for (int dt = 0; dt < C::ND; ++dt)
-#pragma unroll
-            for (int vv = 0; vv < 16; ++vv) acc[dt][vv] += mg[(dt * 16 + vv) * NT + tid];
-    }
-    if (t_abs < T) {
-        if (rope) rope_rotate_dT<DH>(acc, rope, t_abs, -1.f, g);
-        write_rows_from_dT<DH>(dq + (long)t_abs * ldq + (long)head * DH, acc, scale, g);
-    }
+// the same in vector registers, for scores: FIRST starts from zero.  Their last results may be read once two more MFMAs have been
+// issued, or behind score_ready.
+template <bool FIRST>
+__device__ __forceinline__ void mfma32_score(f32x16_t& c, bf16x8_t a, bf16x8_t b) {
+    if constexpr (FIRST) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
 
-// ======================================================================== backward: dK, dV
-template <int DH, int NW>
-__device__ __forceinline__ void attn_dkv_block(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                               const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
-                                               const float* __restrict__ lse, const float* __restrict__ delta, long ldq,
-                                               long ldo, int T, bf16_t* __restrict__ dk, bf16_t* __restrict__ dv,
-                                               float scale, const float2* __restrict__ rope, int kb, int head,
-                                               unsigned char* smem) {
-    using C = AttnCfg<DH>;
-    constexpr int NT = NW * 64, KB = NW * 32;
-    constexpr int LDT = LTR(DH);
-    bf16_t* sQ = (bf16_t*)smem;             // [64][LSK]
-    bf16_t* sdO = sQ + 64 * C::LSK;         // [64][LSK]
-    bf16_t* sQ2 = sdO + 64 * C::LSK;        // [64][LDT]: Q and dO once more, with the row stride of the LDS transpose
-    bf16_t* sdO2 = sQ2 + 64 * LDT;          // [64][LDT]  read (dS^T Q and P^T dO take them with the token index as contraction)
-    float* sLse = (float*)(sdO2 + 64 * LDT); // [64]
-    float* sDelta = sLse + 64;              // [64]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, g = lane >> 5;
-    const int tr_off = tr_lane_offset(lane, LDT);
-    const int u0 = kb * KB, uw0 = u0 + 32 * wave, u_abs = uw0 + l32;
+template <int DH, bool DQ>
+__device__ __forceinline__ void attn_bwd_part(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
+    const float* __restrict__ lse, const float* __restrict__ delta, long ldq, long ldo, int T, bf16_t* __restrict__ dq,
+    bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, float scale, const float2* __restrict__ rope, int block, int head,
+    unsigned char* smem) {
+    using C = BwdCfg<DH>;
+    constexpr int NG = C::NG, KS = DH / 16, ND = DH / 32, RB = C::RB, TB = C::TB, STAGE = C::STAGE, NST = C::NST;
+    constexpr int NI = TB / 4096, RPI = 1024 / RB, CPR = RB / 16;      // fetches per wave and tile; rows per fetch; chunks per row
+    constexpr int NF = 2 * NI + (DQ ? 0 : 1);                          // fetches per wave and stage
+    constexpr bool V_LDS = !DQ && NG == 2;
+    static_assert(KS == 2 * ND, "as many MFMAs for each product");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, g = lane >> 5, pg = wave >> 1, sg = wave & 1;
+    const unsigned lds0 = (unsigned)(size_t)smem;
+    const int p0 = block * C::PB, pw0 = p0 + 32 * NG * pg;             // first row of the block, of this wave's share
+    // first row of group j of this wave: the waves of the two halves count their groups in opposite order, so that each hands its last
+    // one to the other in the end
+    auto group_row = [&](int j) { return pw0 + 32 * (NG == 2 ? j ^ sg : 0); };
     const float scale_log2e = scale * 1.4426950408889634f;
-    const bf16_t* qh = q + (long)head * DH;
-    const bf16_t* kh = k + (long)head * DH;
-    const bf16_t* vh = v + (long)head * DH;
-    const bf16_t* doh = d_o + (long)head * DH;
+    const long hd = (long)head * DH;
+    const bf16_t* x1 = (DQ ? k : q) + hd;
+    const bf16_t* x2 = (DQ ? v : d_o) + hd;
+    const bf16_t* p1 = (DQ ? q : k) + hd;
+    const bf16_t* p2 = (DQ ? d_o : v) + hd;
+    const long ldx2 = DQ ? ldq : ldo, ldp2 = DQ ? ldo : ldq;
+    const float* lse_h = lse + (long)head * T;
+    const float* delta_h = delta + (long)head * T;
 
-    bf16x8_t kf[C::NKS], vf[C::NKS];
+    float dlt[NG], lse2[NG];
 #pragma unroll
-    for (int ks = 0; ks < C::NKS; ++ks) {
-        uint4 r = (u_abs < T) ? *(const uint4*)(kh + (long)u_abs * ldq + ks * 16 + g * 8) : make_uint4(0, 0, 0, 0);
-        kf[ks] = *(bf16x8_t*)&r;
-        uint4 r2 = (u_abs < T) ? *(const uint4*)(vh + (long)u_abs * ldq + ks * 16 + g * 8) : make_uint4(0, 0, 0, 0);
-        vf[ks] = *(bf16x8_t*)&r2;
+    for (int j = 0; j < NG; ++j) {
+        const int p = min(group_row(j) + l32, T - 1);      // rows beyond the last are never stored, and each has a lane of its own
+        dlt[j] = DQ ? delta_h[p] : 0.f;
+        lse2[j] = DQ ? lse_h[p] * 1.4426950408889634f : 0.f;
     }
-    f32x16_t dkacc[C::ND], dvacc[C::ND];
+
+    // direct-to-LDS fetches: fetch i of a tile brings rows i RPI .. + RPI - 1 (beyond the last: that one again), this lane the chunk that
+    // belongs at its place
+    const int fr = lane / CPR;
+    const unsigned fc = (unsigned)((lane % CPR) ^ attn_swz<DH>(fr)) << 4;
+    const unsigned ld1b = (unsigned)ldq * 2, ldx2b = (unsigned)ldx2 * 2;
+    auto fetch_one = [&](const bf16_t* rows, unsigned ldb, int i, int last, unsigned dst) {      // rows: row 0 of the tile; last: its last valid one
+        const unsigned c = fc ^ (unsigned)((i * (RPI / 4) & 3) << 4);                            // swz of rows i RPI + fr
+        load_lds16((unsigned)min(i * RPI + fr, last) * ldb + c, rows, __builtin_amdgcn_readfirstlane(lds0 + dst + i * 1024));
+    };
+    struct Fetch { const bf16_t *a, *b; const float* stats; int last; unsigned st; };
+    auto fetch_of = [&](int tile, unsigned st) {
+        const long r0 = (long)tile * 64;
+        return Fetch{x1 + r0 * ldq, x2 + r0 * ldx2, (sg ? delta_h : lse_h) + r0, T - 1 - tile * 64, st};
+    };
+    // piece n of the NF a wave issues per tile (two waves each bring lse and delta, so that every wave has as many in flight)
+    auto fetch_piece = [&](const Fetch& f, int n) {
+        if (n < NI) fetch_one(f.a, ld1b, wave * NI + n, f.last, f.st);
+        else if (n < 2 * NI) fetch_one(f.b, ldx2b, wave * NI + n - NI, f.last, f.st + TB);
+        else load_lds4(lane <= f.last ? f.stats + lane : sg ? f.stats : &kLseBeyond, __builtin_amdgcn_readfirstlane(lds0 + f.st + 2 * TB + sg * 256));
+    };
+    auto fetch = [&](const Fetch& f) {
 #pragma unroll
-    for (int dt = 0; dt < C::ND; ++dt) { dkacc[dt] = zero16(); dvacc[dt] = zero16(); }
+        for (int n = 0; n < NF; ++n) fetch_piece(f, n);
+    };
 
     const int n_tiles = (T + 63) / 64;
-    const int tile0 = u0 / 64;
-    uint4 rq[8 * DH / NT], rdo[8 * DH / NT];
-    unsigned qoff[8 * DH / NT], dooff[8 * DH / NT];
-    tile_chunk_offsets<DH, NT>(ldq, qoff);
-    tile_chunk_offsets<DH, NT>(ldo, dooff);
-    float lse_v = 0.f, dl_v = 0.f;
-    auto fetch = [&](int tile) {
-        const int t0 = tile * 64;
-        load_tile_regs<DH, NT>(qh, ldq, t0, T, qoff, rq);
-        load_tile_regs<DH, NT>(doh, ldo, t0, T, dooff, rdo);
-        if (tid < 64) {
-            const int t = t0 + tid;
-            lse_v = (t < T) ? lse[(long)head * T + t] * 1.4426950408889634f : 1.0e30f;
-            dl_v = (t < T) ? delta[(long)head * T + t] : 0.f;
-        }
+    const int tile0 = DQ ? 0 : p0 / 64, tile1 = DQ ? min((p0 + C::PB + 63) / 64, n_tiles) : n_tiles;
+    // The operands of the block come through LDS too, and the results leave through it: 16 bytes a lane straight from and to memory touch
+    // 32 rows with every instruction (loads and stores of one part 8.5 us; 4.5 like this).  P1 takes the place of the third tile.
+    constexpr unsigned P1_AT = C::V0 + 2 * STAGE, P2_AT = DH == 128 ? 0 : P1_AT + TB;
+    auto fetch_block = [&](const bf16_t* x, long ld, unsigned at) {
+#pragma unroll
+        for (int j = 0; j < C::PB * RB / 4096; ++j)
+            fetch_one(x + (long)p0 * ld, (unsigned)ld * 2, wave * (C::PB * RB / 4096) + j, T - 1 - p0, at);
     };
-    if (tile0 < n_tiles) fetch(tile0);
-    for (int tile = tile0; tile < n_tiles; ++tile) {
-        const int t0 = tile * 64;
-        __syncthreads();
-        store_tile_normal<DH, NT>(sQ, rq);
-        store_tile_normal<DH, NT>(sdO, rdo);
-        store_tile_ld<DH, NT, LDT>(sQ2, rq);
-        store_tile_ld<DH, NT, LDT>(sdO2, rdo);
-        if (tid < 64) { sLse[tid] = lse_v; sDelta[tid] = dl_v; }
-        __syncthreads();
-        if (tile + 1 < n_tiles) fetch(tile + 1);
+    fetch_block(p1, ldq, P1_AT);
+    fetch_block(p2, ldp2, P2_AT);
+    // Tiles are taken from the last one down: the key blocks of a head that start together then read the same ones (5120 tokens: 764 us
+    // with dK, dV and dQ upwards, 745 with dK and dV down, 755 with both)
+    const int n_steps = tile1 - tile0;
+    auto tile_of = [&](int i) { return tile1 - 1 - min(i, n_steps - 1); };
+    fetch(fetch_of(tile_of(0), C::V0));
+    fetch(fetch_of(tile_of(1), C::V0 + STAGE));
+    // this lane's place in the fragments of block rows (chunk 2 ks + g of row l32 of a group)
+    const unsigned p_at = (unsigned)((pg * 32 * NG + (NG == 2 ? 32 * sg : 0) + l32) * RB + ((g ^ attn_swz<DH>(l32)) << 4));
+    auto p_frag = [&](unsigned at, int j, int ks) { return *(const bf16x8_t*)(smem + at + (p_at ^ (unsigned)(ks << 5 | j * 32 * RB))); };
+    wait_vmcnt<2 * NF>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    bf16x8_t p1f[NG][KS], p2f[V_LDS ? 1 : NG][V_LDS ? 1 : KS];
 #pragma unroll
-        for (int ts = 0; ts < 2; ++ts) {
-            const int tsub0 = t0 + ts * 32;
-            if (tsub0 + 31 < uw0) continue;  // wave-uniform: every query of this sub-tile precedes every key
-            f32x16_t sacc = zero16(), dpacc = zero16();
+    for (int j = 0; j < NG; ++j) {
 #pragma unroll
-            for (int ks = 0; ks < C::NKS; ++ks) {
-                bf16x8_t a = *(const bf16x8_t*)(sQ + (ts * 32 + l32) * C::LSK + ks * 16 + g * 8);
-                sacc = mfma32(a, kf[ks], sacc);
-                bf16x8_t b = *(const bf16x8_t*)(sdO + (ts * 32 + l32) * C::LSK + ks * 16 + g * 8);
-                dpacc = mfma32(b, vf[ks], dpacc);
-            }
-            float p[16], ds[16];
-            // only a sub-tile on the diagonal needs the causal mask (wave-uniform); the others skip its compares
-            auto probs = [&](auto masked) {
-#pragma unroll
-                for (int vq = 0; vq < 4; ++vq) {
-                    const int tl = ts * 32 + 8 * vq + 4 * g;
-                    const float4 l4 = *(const float4*)(sLse + tl);
-                    const float4 d4 = *(const float4*)(sDelta + tl);
-                    const float ll[4] = {l4.x, l4.y, l4.z, l4.w}, dd[4] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int vv = 4 * vq + e;
-                        const int t = t0 + tl + e;
-                        const float pe = fast_exp2(sacc[vv] * scale_log2e - ll[e]);
-                        const float pv = (decltype(masked)::value && u_abs > t) ? 0.f : pe;
-                        p[vv] = pv;
-                        ds[vv] = pv * (dpacc[vv] - dd[e]);
-                    }
-                }
-            };
-            if (tsub0 < uw0 + 32) probs(std::true_type{}); else probs(std::false_type{});
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const bf16x8_t bp = pack_b_from_d(p, h);
-                const bf16x8_t bs = pack_b_from_d(ds, h);
-#pragma unroll
-                for (int dt = 0; dt < C::ND; ++dt) {
-                    const bf16x8_t a1 = load_a_tr(sdO2, LDT, tr_off, dt * 32, ts * 32 + 16 * h);
-                    dvacc[dt] = mfma32(a1, bp, dvacc[dt]);
-                    const bf16x8_t a2 = load_a_tr(sQ2, LDT, tr_off, dt * 32, ts * 32 + 16 * h);
-                    dkacc[dt] = mfma32(a2, bs, dkacc[dt]);
-                }
-            }
+        for (int ks = 0; ks < KS; ++ks) {
+            p1f[j][ks] = p_frag(P1_AT, j, ks);
+            if constexpr (!V_LDS) p2f[j][ks] = p_frag(P2_AT, j, ks);
         }
     }
-    if (u_abs < T) {
-        if (rope) rope_rotate_dT<DH>(dkacc, rope, u_abs, -1.f, g);   // linear, so it commutes with the scale below
-        write_rows_from_dT<DH>(dk + (long)u_abs * ldq + (long)head * DH, dkacc, scale, g);
-        write_rows_from_dT<DH>(dv + (long)u_abs * ldq + (long)head * DH, dvacc, 1.f, g);
+    // the compiler's own loads are waited for here and not in the loop
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            asm volatile("" : "+v"(p1f[j][ks]));
+            if constexpr (!V_LDS) asm volatile("" : "+v"(p2f[j][ks]));
+        }
+        asm volatile("" : "+v"(dlt[j]), "+v"(lse2[j]));
+    }
+
+    // zeros by MFMAs with nothing in them: sixteen instructions instead of 256 (code that runs once is paid for in instruction cache misses)
+    f32x16_t acc1[NG][ND], acc2[DQ ? 1 : NG][DQ ? 1 : ND];
+    bf16x8_t nothing = __builtin_bit_cast(bf16x8_t, make_uint4(0, 0, 0, 0));
+    asm volatile("s_nop 1" : "+v"(nothing));
+#pragma unroll
+    for (int j = 0; j < NG; ++j)
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt) {
+            asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %1, 0" : "=a"(acc1[j][dt]) : "v"(nothing));
+            if constexpr (!DQ) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %1, 0" : "=a"(acc2[j][dt]) : "v"(nothing));
+        }
+
+    // this lane's place in a fragment read of rows (chunk 2 ks + g) and in a transposing read (see load_a_tr)
+    const unsigned row_at = (unsigned)((sg * 32 + l32) * RB + ((g ^ attn_swz<DH>(l32)) << 4));
+    const int G = lane >> 4, te = (lane & 15) >> 2, tq = lane & 3;
+    const unsigned tr_at = (unsigned)((sg * 32 + 4 * (G >> 1) + te) * RB + ((DH == 128 ? te : te >> 1) << 6) +
+                                      (((2 * (G & 1) + (tq >> 1)) ^ (G >> 1)) << 4) + ((tq & 1) << 3));
+    auto row_frag = [&](unsigned tile, int ks) { return *(const bf16x8_t*)(smem + tile + (row_at ^ (unsigned)(ks << 5))); };
+    auto tr_frag = [&](unsigned tile, int i) {       // i = h ND + dt: contraction rows 16 h .., columns 32 dt ..
+        typedef __attribute__((address_space(3))) bf16x4v_t* lds_ptr_t;
+        const unsigned at = tr_at ^ (unsigned)((i % ND) << 6);
+        const bf16x4v_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(smem + tile + at + (i / ND) * 16 * RB));
+        const bf16x4v_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(smem + tile + (at ^ 32u) + ((i / ND) * 16 + 8) * RB));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+
+    auto compute = [&](auto masked, unsigned st, int xs0, const Fetch& next) {
+        constexpr bool MASK = decltype(masked)::value;
+        // One fragment of X and NG MFMAs a slot, KS slots each of S, dP, dV and dK (of S, dP and dQ).  Fragments are asked for AHEAD slots
+        // before they are used, and the vector work on the scores, in items of four values a lane, goes between the MFMAs behind them.
+        constexpr int B0 = KS, C0 = 2 * KS, NS = (DQ ? 3 : 4) * KS, D0 = NS - KS;
+        constexpr int AHEAD = 4, AHEAD_V = 3;
+        f32x16_t s[NG], dp[NG];
+        bf16x8_t pb[NG][2], dsb[NG][2], fx[NS], fv[NG][KS];
+        float4 l4[4], d4[4];
+        const unsigned t1 = st, t2 = st + TB;
+        auto read = [&](auto slot) {
+            constexpr int i = decltype(slot)::value, n = i % KS;
+            if constexpr (i < B0) fx[i] = row_frag(t1, n);
+            else if constexpr (i < C0) {
+                fx[i] = row_frag(t2, n);
+                if constexpr (V_LDS) {
+#pragma unroll
+                    for (int j = 0; j < NG; ++j) fv[j][n] = p_frag(P2_AT, j, n);
+                }
+            } else fx[i] = tr_frag(i >= D0 ? t1 : t2, n);
+        };
+        auto mfma = [&](auto slot) {
+            constexpr int i = decltype(slot)::value, n = i % KS;
+#pragma unroll
+            for (int j = 0; j < NG; ++j) {
+                if constexpr (i < B0) mfma32_score<n == 0>(s[j], fx[i], p1f[j][n]);
+                else if constexpr (i < C0) mfma32_score<n == 0>(dp[j], fx[i], V_LDS ? fv[j][n] : p2f[V_LDS ? 0 : j][V_LDS ? 0 : n]);
+                else if constexpr (i >= D0) mfma32_acc(acc1[j][n % ND], fx[i], dsb[j][n / ND]);
+                else mfma32_acc(acc2[DQ ? 0 : j][DQ ? 0 : n % ND], fx[i], pb[j][n / ND]);
+            }
+        };
+        auto read_stats = [&](int which, int vq) {       // lse (0) or delta (1) of the rows of item vq
+            if constexpr (!DQ) (which ? d4 : l4)[vq] = *(const float4*)((const float*)(smem + st + 2 * TB) + which * 64 + sg * 32 + 8 * vq + 4 * g);
+        };
+        auto probs = [&](int j, int vq) {          // four probabilities, in place of their scores
+            const float ll[4] = {l4[vq].x, l4[vq].y, l4[vq].z, l4[vq].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float sub = DQ ? lse2[j] : ll[e] * 1.4426950408889634f;
+                float pe = fast_exp2(s[j][4 * vq + e] * scale_log2e - sub);
+                if (MASK) {
+                    const int x_p = xs0 + 8 * vq + 4 * g + e - group_row(j) - l32;          // a key must not follow its query
+                    pe = (DQ ? x_p > 0 : x_p < 0) ? 0.f : pe;
+                }
+                s[j][4 * vq + e] = pe;
+                if constexpr (!DQ) pb[j][vq >> 1][4 * (vq & 1) + e] = (__bf16)pe;
+            }
+        };
+        auto dscores = [&](int j, int vq) {
+            const float dd[4] = {d4[vq].x, d4[vq].y, d4[vq].z, d4[vq].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                dsb[j][vq >> 1][4 * (vq & 1) + e] = (__bf16)(s[j][4 * vq + e] * (dp[j][4 * vq + e] - (DQ ? dlt[j] : dd[e])));
+        };
+        // The compiler does not see the matrix instructions inside the asm statements: what reads their results comes behind a statement
+        // that passes them through, two MFMAs or enough wait states later.
+        auto ready = [&](f32x16_t* x, auto wait) {
+            if constexpr (decltype(wait)::value) asm volatile("s_nop 15\n\ts_nop 3");
+#pragma unroll
+            for (int j = 0; j < NG; ++j) asm volatile("" : "+v"(x[j]));
+        };
+        using Wait = std::true_type; using SlotWait = std::bool_constant<NG == 1>;
+        // item n: group n % NG, rows 8 (n / NG) ..; dV needs the first half of the probabilities KS / 2 slots before the second
+        constexpr int NI_P = 4 * NG;
+        auto p_item = [](int i) -> int {           // the item of probabilities behind the MFMAs of slot i
+            if (NG == 1) return i >= B0 && i < B0 + 4 ? i - B0 : -1;
+            if (DQ) return i >= B0 + 1 && i < B0 + 8 ? i - B0 - 1 : -1;
+            return i >= B0 + 1 && i <= B0 + 3 ? i - B0 - 1 : i >= B0 + 5 && i <= B0 + 6 ? i - B0 - 2 : i >= C0 && i <= C0 + 2 ? i - C0 + 5 : -1;
+        };
+        auto d_item = [](int i) -> int {           // of dS
+            if (DQ) return -1;
+            if (NG == 1) return i >= C0 && i < C0 + 4 ? i - C0 : -1;
+            return i >= C0 + 3 && i < C0 + 7 ? i - C0 - 3 : i >= D0 && i < D0 + 4 ? i - D0 + 4 : -1;
+        };
+        static_for<AHEAD>([&](auto slot) { read(slot); });
+        static_for<NS>([&](auto slot) {
+            constexpr int i = decltype(slot)::value;
+            static_for<AHEAD>([&](auto more) {
+                constexpr int r = i + 1 + decltype(more)::value;
+                if constexpr (r < NS && r - (V_LDS && r >= B0 && r < C0 ? AHEAD_V : AHEAD) == i) read(std::integral_constant<int, r>{});
+            });
+            if (i < NF - NI) fetch_piece(next, NI + i);
+            if (i >= NS - NI) fetch_piece(next, i - (NS - NI));
+#pragma unroll
+            for (int x = 0; x < NI_P; ++x) {
+                if (p_item(i + 2) == x && x % NG == 0) read_stats(0, x / NG);
+                if (d_item(i + 2) == x && x % NG == 0) read_stats(1, x / NG);
+            }
+            mfma(slot);
+            if constexpr (i == B0) ready(s, SlotWait{});
+            if constexpr (i == C0 && !DQ) ready(dp, SlotWait{});
+            if (p_item(i) >= 0) probs(p_item(i) % NG, p_item(i) / NG);
+            if (d_item(i) >= 0) dscores(d_item(i) % NG, d_item(i) / NG);
+            if constexpr (DQ) {
+                if (i == D0 - 1) {
+                    if (NG == 2) probs(1, 3);
+                    ready(dp, Wait{});
+#pragma unroll
+                    for (int x = 0; x < 2 * NG; ++x) dscores(x % NG, x / NG);
+                }
+                if (i >= D0 && i < D0 + ND) {
+#pragma unroll
+                    for (int x = 0; x < 2 * NG / ND; ++x) dscores((2 * NG + (i - D0) * (2 * NG / ND) + x) % NG, (2 * NG + (i - D0) * (2 * NG / ND) + x) / NG);
+                }
+            }
+            // two wait states between a vector instruction and the MFMA that takes its result
+            if constexpr (i == C0 - 1 || i == D0 - 1 || i == D0 + ND - 1 || (!DQ && i == C0 + ND - 1)) asm volatile("s_nop 1");
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+
+    unsigned st = C::V0, st_next = C::V0 + 2 * STAGE;
+    int i_step = 0;
+    auto step = [&](auto what) {           // 0: nothing to do for this wave, 1: every score counts, 2: with the causal mask
+        constexpr int WHAT = decltype(what)::value;
+        wait_vmcnt<NF>();                                                  // this tile has landed (the next may be in flight)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                 // and every read of the one before is done
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const Fetch next = fetch_of(tile_of(i_step + 2), st_next);         // (behind the last tile: that one again, unused)
+        if constexpr (WHAT) compute(std::integral_constant<bool, WHAT == 2>{}, st, tile_of(i_step) * 64 + 32 * sg, next);
+        else fetch(next);
+        st = st == C::V0 + (NST - 1) * STAGE ? C::V0 : st + STAGE;
+        st_next = st_next == C::V0 + (NST - 1) * STAGE ? C::V0 : st_next + STAGE;
+        ++i_step;
+    };
+    using Skip = std::integral_constant<int, 0>; using Plain = std::integral_constant<int, 1>; using Masked = std::integral_constant<int, 2>;
+    // Wave-uniform ranges of tiles: those in which every query precedes every key of this wave are left out, those on the diagonal need
+    // the mask.  (Rows beyond T need none: as queries their log-sum-exp is beyond any score, as keys they follow every query.)
+    const int w = pw0 - 32 * sg;
+    if constexpr (DQ) {
+        const int skip_end = tile1 - min(tile1, (w + 32 * NG + 63) >> 6), mask_end = tile1 - min(tile1, (w + 33) >> 6);
+        while (i_step < skip_end) step(Skip{});
+        while (i_step < mask_end) step(Masked{});
+        while (i_step < n_steps) step(Plain{});
+    } else {
+        const int plain_end = tile1 - min(tile1, (w + 32 * NG + 62) >> 6), mask_end = tile1 - min(tile1, (w + 32) >> 6);
+        while (i_step < plain_end) step(Plain{});
+        while (i_step < mask_end) step(Masked{});
+        while (i_step < n_steps) step(Skip{});
+    }
+    wait_vmcnt<0>();
+    // Ordinary instructions read the accumulators from here on (see gemm_nt_dl_kernel)
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < NG; ++j)
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt) {
+            asm volatile("" : "+a"(acc1[j][dt]));
+            if constexpr (!DQ) asm volatile("" : "+a"(acc2[j][dt]));
+        }
+    // add the two halves: each wave hands over one half of what it holds (NG 2: the other's group of rows; else dK or dV, or all of dQ)
+    // and finishes the other; values of one thread are kept 64 apart
+    // (lane numbers formed anew: kept across the loop they cost a spill)
+    const int elane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), el32 = elane & 31, eg = elane >> 5;
+    __syncthreads();
+    constexpr int HALF = C::LDS / (1024 * 4) * 1024;       // bytes of LDS per wave
+    float4* mine = (float4*)(smem + wave * HALF) + elane;
+    const float4* other = (const float4*)(smem + (wave ^ 1) * HALF) + elane;
+    auto put = [&](const f32x16_t* a, int n0) {
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq)
+                mine[(n0 + dt * 4 + vq) * 64] = make_float4(a[dt][4 * vq], a[dt][4 * vq + 1], a[dt][4 * vq + 2], a[dt][4 * vq + 3]);
+    };
+    auto add = [&](f32x16_t* a, int n0) {
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) {
+                const float4 o = other[(n0 + dt * 4 + vq) * 64];
+                a[dt][4 * vq] += o.x; a[dt][4 * vq + 1] += o.y; a[dt][4 * vq + 2] += o.z; a[dt][4 * vq + 3] += o.w;
+            }
+    };
+    // one group of rows leaves through LDS, so that a row is written in 16-byte pieces (and its RoPE angles read so)
+    auto out = [&](const f32x16_t* a, bf16_t* dst, float mul, const float2* table) {
+        constexpr int LD = DH + 4, HALF_D = DH / 2, CPH = HALF_D / 8;       // floats per row, 8-column chunks per half
+        float* slab = (float*)(smem + wave * HALF);
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq)
+                *(float4*)(slab + el32 * LD + dt * 32 + 8 * vq + 4 * eg) = make_float4(a[dt][4 * vq], a[dt][4 * vq + 1], a[dt][4 * vq + 2], a[dt][4 * vq + 3]);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int i = elane; i < 32 * CPH; i += 64) {
+            const int row = i / CPH, c = i % CPH * 8, p = group_row(0) + row;
+            if (p >= T) continue;
+            float lo[8], hi[8];
+#pragma unroll
+            for (int e = 0; e < 8; e += 4) {
+                *(float4*)(lo + e) = *(const float4*)(slab + row * LD + c + e);
+                *(float4*)(hi + e) = *(const float4*)(slab + row * LD + HALF_D + c + e);
+            }
+            if (table) {       // the inverse rotation of the pairs (d, d + DH / 2), the adjoint of the forward one
+                const float2* cs = table + (long)p * HALF_D + c;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float x = lo[e], y = hi[e], sn = -cs[e].y;
+                    lo[e] = x * cs[e].x - y * sn;
+                    hi[e] = y * cs[e].x + x * sn;
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { lo[e] *= mul; hi[e] *= mul; }
+            *(uint4*)(dst + (long)p * ldq + hd + c) = pack8(lo);
+            *(uint4*)(dst + (long)p * ldq + hd + HALF_D + c) = pack8(hi);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto out1 = [&](const f32x16_t* a) { out(a, DQ ? dq : dk, scale, rope); };
+    auto out2 = [&](const f32x16_t* a) { out(a, dv, 1.f, nullptr); };
+    if constexpr (NG == 2) {
+        put(acc1[1], 0);
+        if constexpr (!DQ) put(acc2[1], 4 * ND);
+        __syncthreads();
+        add(acc1[0], 0);
+        if constexpr (!DQ) add(acc2[0], 4 * ND);
+        __syncthreads();
+        out1(acc1[0]);
+        if constexpr (!DQ) out2(acc2[0]);
+    } else if constexpr (DQ) {
+        if (sg == 1) put(acc1[0], 0);
+        __syncthreads();
+        if (sg == 0) { add(acc1[0], 0); out1(acc1[0]); }
+    } else {
+        if (sg == 0) put(acc2[0], 0); else put(acc1[0], 0);
+        __syncthreads();
+        if (sg == 0) add(acc1[0], 0); else add(acc2[0], 0);
+        __syncthreads();
+        if (sg == 0) out1(acc1[0]); else out2(acc2[0]);
     }
 }
 
-// ======================================================================== backward: both in one launch
-// Every workgroup does ONE part -- the dK/dV of a key block (all query blocks from it on) or the dQ of a query block (all
-// key blocks up to it) -- and the parts are handed out longest first: level j of the grid holds the dK/dV part of key
-// block j and the dQ part of query block n - 1 - j of every head, which cost about the same, and levels run from the
-// heaviest down.  As two launches each part list has an 8:1 causal imbalance between its workgroups and, at 1024
-// tokens x 32 heads, exactly one workgroup per CU, so the chip waits for the longest one twice; in one launch a CU that
-// finishes a light part picks up the next.  delta must already be in memory (the dK/dV parts read rows that other
+// Both kinds of part in one launch.  Every workgroup does ONE part -- the dK/dV of a key block (all queries from it on) or the dQ of a
+// query block (all keys up to it) -- and the parts are handed out longest first: level j of the grid holds the dK/dV part of key
+// block j and the dQ part of query block n - 1 - j of every head, and levels run from the heaviest down.  As two launches each part
+// list has an 8:1 causal imbalance between its workgroups at 1024 tokens, and the chip waits for the longest one twice; in one launch a
+// CU that finishes a light part picks up the next.  delta must already be in memory (the dK/dV parts read rows that other
 // workgroups' dQ parts own).  grid = (n blocks, heads, 2).
-template <int DH, int NW>
-__global__ __launch_bounds__(NW * 64) void attn_bwd_fused_kernel(
+template <int DH>
+__global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_fused_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, long ldq, long ldo,
     int T, bf16_t* __restrict__ dq, bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, float scale,
@@ -531,8 +690,8 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_fused_kernel(
     const int n = gridDim.x, heads = gridDim.y;
     const int idx = (blockIdx.z * heads + blockIdx.y) * n + blockIdx.x;   // position in dispatch order (x fastest)
     const int level = idx / (2 * heads), r = idx % (2 * heads), head = r % heads;
-    if (r < heads) attn_dkv_block<DH, NW>(q, k, v, d_o, lse, delta, ldq, ldo, T, dk, dv, scale, rope, level, head, smem);
-    else attn_dq_block<DH, NW, 1>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, scale, rope, n - 1 - level, head, smem);
+    if (r < heads) attn_bwd_part<DH, false>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope, level, head, smem);
+    else attn_bwd_part<DH, true>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope, n - 1 - level, head, smem);
 }
 
 // ======================================================================== launchers
@@ -599,21 +758,17 @@ template <int DH>
 static hipError_t run_bwd(const bf16_t* q, const bf16_t* k, const bf16_t* v, const bf16_t* o, const bf16_t* d_o,
                           const float* lse, float* delta, long ldq, long ldo, int T, int n_heads, bf16_t* dq, bf16_t* dk,
                           bf16_t* dv, const float2* rope, hipStream_t s) {
-    using C = AttnCfg<DH>;
-    constexpr int NW = ATTN_NW;
+    using C = BwdCfg<DH>;
     const float scale = 1.f / sqrtf((float)DH);
-    dim3 grid(cdiv(T, NW * 32), n_heads, 2);
-    const size_t lds_kv = (size_t)(2 * 64 * C::LSK + 2 * 64 * LTR(DH)) * sizeof(bf16_t) + 128 * sizeof(float);
+    dim3 grid(cdiv(T, C::PB), n_heads, 2);
     const dim3 dgrid(cdiv((long)n_heads * (DH / 8), 256), T < 65535 ? T : 65535);
     attn_delta_kernel<DH><<<dgrid, 256, 0, s>>>(o, d_o, ldo, T, n_heads, delta);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const size_t lds_q = (size_t)(2 * 64 * C::LSK + 64 * LTR(DH)) * sizeof(bf16_t);
-    const size_t lds = lds_q > lds_kv ? lds_q : lds_kv;
-    auto kern = attn_bwd_fused_kernel<DH, NW>;
-    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    auto kern = attn_bwd_fused_kernel<DH>;
+    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
     if (e != hipSuccess) return e;
-    kern<<<grid, NW * 64, lds, s>>>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope);
+    kern<<<grid, 256, C::LDS, s>>>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope);
     return hipGetLastError();
 }
 

@@ -162,14 +162,6 @@ __global__ void splitk_reduce_kernel(GemmNT p, int split_k);
 // rows span the 64 banks once, so 16 consecutive rows reading the same logical chunk must land on 8 distinct positions
 // in the even rows and 8 in the odd rows: that is what the (r / 2) term gives.
 // Rows beyond M / N are clamped to the last valid row: they only feed outputs that are never stored.
-__device__ __forceinline__ void load_lds16(unsigned voff, const void* sbase, unsigned lds_addr) {
-    // M0 carries the LDS destination: bound as a physical-register operand, so the compiler sets it and knows it is used
-    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "{m0}"(lds_addr) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 // Accumulates in place, in accumulation registers.  As a builtin the compiler renames the accumulators of the 192- and
 // 128-column instances from one k-step to the next and moves every one of them (a quarter of the loop's issue slots).
 __device__ __forceinline__ void mfma16_acc(f32x4_t& c, bf16x8_t a, bf16x8_t b) {

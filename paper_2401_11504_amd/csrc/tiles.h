@@ -58,3 +58,16 @@ __device__ __forceinline__ bf16x8_t pack_b_from_d(const float* d, int h) {
     for (int e = 0; e < 8; ++e) b[e] = (__bf16)d[8 * h + e];
     return b;
 }
+
+// Direct-to-LDS loads: each lane's 16 (4) bytes land at lds_addr + 16 (4) * lane.
+__device__ __forceinline__ void load_lds16(unsigned voff, const void* sbase, unsigned lds_addr) {
+    // M0 carries the LDS destination: bound as a physical-register operand, so the compiler sets it and knows it is used
+    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "{m0}"(lds_addr) : "memory");
+}
+__device__ __forceinline__ void load_lds4(const void* p, unsigned lds_addr) {
+    asm volatile("global_load_lds_dword %0, off" ::"v"(p), "{m0}"(lds_addr) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}

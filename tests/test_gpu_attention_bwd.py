@@ -1,0 +1,45 @@
+"""Backward attention at the edges of its tiles, against the fp64 oracle.
+
+A part of the launch is a block of 128 (d_head 128) or 64 (d_head 64) keys or queries against 64-row tiles, each taken in two halves of 32
+rows; a wave holds 64 or 32 rows of the block.  The lengths lie on both sides of every one of these edges.  What follows row T in memory
+is NaN: a row read beyond the last one, and used, shows in the gradients."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from oracle import templora_oracle as O  # noqa: E402
+from paper_2401_11504_amd import synth  # noqa: E402
+from test_gpu_kernels import BF16_TOL, H, api, check  # noqa: E402,F401
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("T", [2, 31, 32, 33, 63, 65, 95, 97, 127, 128, 160, 191, 193, 257, 320])
+def test_edges(api, H, T, dh):
+    nh = 3
+    d = nh * dh
+    rows = T + 70
+
+    def draw(seed, width):
+        x = synth.normal(seed, (91, T, width), (T, width), 1.0, True)
+        full = np.full((rows, width), np.nan)
+        full[:T] = x
+        return x, H.to_dev_bf16(full)[:T]
+    qkv, qkvd = draw(1, 3 * d)
+    do, dod = draw(2, d)
+    q, k, v = (qkv[:, i * d:(i + 1) * d].reshape(T, nh, dh) for i in range(3))
+    o = torch.zeros(T, d, dtype=torch.bfloat16, device="cuda")
+    lse = torch.zeros(nh, T, dtype=torch.float32, device="cuda")
+    delta = torch.zeros(nh, T, dtype=torch.float32, device="cuda")
+    grads = torch.full((rows, 3 * d), 7.0, dtype=torch.bfloat16, device="cuda")
+    args = [qkvd[:, i * d:(i + 1) * d] for i in range(3)]
+    api.tl_k_attention_fwd(*args, nh, dh, o, lse)
+    api.tl_k_attention_bwd(*args, o, dod, lse, nh, dh, *(grads[:T, i * d:(i + 1) * d] for i in range(3)), delta)
+    torch.cuda.synchronize()
+    _, P = O.attention_fwd(q, k, v)
+    refs = O.attention_bwd(do.reshape(T, nh, dh), q, k, v, P)
+    g = H.bf16_to_np(grads)
+    assert np.all(g[T:] == 7.0)                    # nothing is written behind the last row
+    for i, name in enumerate(("dq", "dk", "dv")):
+        check(g[:T, i * d:(i + 1) * d], refs[i].reshape(T, d), BF16_TOL, name, per_row=True)
