@@ -338,6 +338,13 @@ tl_status tl_k_gemm_nt(const uint16_t* A, int32_t lda, const uint16_t* B, int32_
                        int32_t K, const uint16_t* A2, int32_t lda2, const uint16_t* B2, int32_t ldb2, int32_t K2,
                        float alpha, const float* R, void* C, int32_t ldc, int32_t c_f32, float* workspace,
                        size_t workspace_elems, void* hip_stream);
+/* The narrow products of the low-rank branch: for b < batch, C[:, b N .. b N + N - 1] = alpha * A[:, b K .. b K + K - 1] B_b^T, A bf16
+ * [M, batch * K], B_b the rows b N .. of B [batch * N, K], C bf16 [M, batch * N]; lda / ldb row strides, K, lda, ldb multiples of 8.
+ * tl_k_low_rank_plan: the tile that dense operands of these sizes get ("16x16", "16x32", "32x32", "32x48", "32x64", "48x64", "64x64"), or
+ * "general" where they go through tl_k_gemm_nt's kernels; host only. */
+tl_status tl_k_low_rank(const uint16_t* A, int32_t lda, const uint16_t* B, int32_t ldb, int32_t M, int32_t N, int32_t K, int32_t batch,
+                        float alpha, uint16_t* C, float* workspace, size_t workspace_elems, void* hip_stream);
+tl_status tl_k_low_rank_plan(int32_t M, int32_t N, int32_t K, int32_t batch, size_t workspace_elems, char* name_out, size_t name_cap);
 /* Which tile configuration tl_k_gemm_nt uses for dense operands of these sizes with a workspace of workspace_elems
  * floats (0 = none): its name ("128x128", "128x128-split", "256x128", "256x128-split", "256x192", "256x256",
  * "256x256-split", "reg-128x128", "reg-128x64", "64x64", "64x64-split", "reg-64x64", "reg-64x64-split") into name_out

@@ -85,6 +85,8 @@ _SIGS = {
     "tl_linear_step_static": [_vp] * 5 + [_i32] * 4 + [_f32] * 6 + [_i32] + [_vp] * 6 + [_vp],
     "tl_k_gemm_nt": [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _vp, _i32, _vp, _i32, _i32, _f32, _vp, _vp, _i32, _i32, _vp,
                      _sz, _vp],
+    "tl_k_low_rank": [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _i32, _f32, _vp, _vp, _sz, _vp],
+    "tl_k_low_rank_plan": [_i32, _i32, _i32, _i32, _sz, C.c_char_p, _sz],
     "tl_k_gemm_nt_plan": [_i32, _i32, _i32, _i32, _sz, C.c_char_p, _sz, C.POINTER(_i32), C.POINTER(_i32)],
     "tl_k_linear_step_plan": [_i32] * 4 + [_f32, _i32, C.c_char_p, _sz],
     "tl_k_gemm_tn": [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _f32, _vp, _i32, _vp],
@@ -332,6 +334,20 @@ def tl_k_gemm_nt(A, B, C_out, A2=None, B2=None, alpha=1.0, R=None, workspace=Non
                            A2.stride(0) if A2 is not None else 0, _dp(B2), B2.stride(0) if B2 is not None else 0, K2,
                            alpha, _dp(R), _dp(C_out), C_out.stride(0), int(C_out.dtype == torch.float32),
                            _dp(workspace), workspace.numel() if workspace is not None else 0, _s(stream)))
+
+
+def tl_k_low_rank(A, B, out, batch=1, alpha=1.0, workspace=None, stream=None):
+    """A [M, batch K], B [batch N, K], out [M, batch N], all bf16"""
+    M, K, N = A.shape[0], B.shape[1], B.shape[0] // batch
+    _chk(_lib.tl_k_low_rank(_dp(A), A.stride(0), _dp(B), B.stride(0), M, N, K, batch, alpha, _dp(out), _dp(workspace),
+                            workspace.numel() if workspace is not None else 0, _s(stream)))
+
+
+def tl_k_low_rank_plan(M, N, K, batch=1, workspace_elems=0):
+    """-> name of the tile"""
+    buf = C.create_string_buffer(32)
+    _chk(_lib.tl_k_low_rank_plan(M, N, K, batch, workspace_elems, buf, 32))
+    return buf.value.decode()
 
 
 def tl_k_gemm_nt_plan(M, N, K, K2=0, workspace_elems=0):

@@ -838,6 +838,164 @@ hipError_t launch_gemm_nt(const GemmNT& g, hipStream_t s) {
     return run_nt<64, 64, 2, 2>(g, split, s);
 }
 
+// ======================================================================== NT, narrow outputs (low-rank products)
+// C = alpha A B^T, bf16, for the few columns of a low-rank product: Hs = s X A^T, dH = s dY B (N = the rank, or three of them).
+// One launch: a workgroup computes a (16 FM) x (16 FN) tile over the whole contraction, each of its eight waves an eighth of it in
+// 64-wide pieces through a ring of its own (direct-to-LDS loads of whole 128-byte rows, ST pieces in flight, no barrier), and adds
+// the eight sums up through LDS in a fixed order.  What bounds it is the operand stream of a CU (some 88 GB/s with the weights of the
+// factor in the L2s): the tile is the one that leaves the busiest CU the fewest bytes, and the rings are small enough for two workgroups
+// per CU, whose loads, sums and stores then overlap.
+// us against 64x64 tiles with the contraction split over up to 16 workgroups and a reduce launch behind (operands cold, calls back to back;
+// columns x batch of a contraction of 4096): 1024 rows, 192: 8.0 and 12.8; 64: 5.6 and 9.7; 64 x 3: 8.5 and 13.5; 2048 rows: 9.8 and 15.4,
+// 6.7 and 12.9, 12.6 and 18.1; 5120 rows: 20 and 25, 16 and 16, 22 and 28; 64 of a contraction of 11008: 512 rows 9.9 and 14.3, 1024 rows
+// 10.6 and 13.5, 2048 rows 19 and 17.  Rings of 96 to 160 KB (two to five pieces ahead): up to 1 us slower.
+template <int FM, int FN, int ST>
+__global__ __launch_bounds__(512, 2) void low_rank_kernel(GemmNT p, int tiles_m, int tiles_n) {
+    constexpr int NL = 2 * (FM + FN), STAGE = NL * 1024, RING = ST * STAGE;      // fetches per piece; bytes
+    static_assert((ST - 1) * NL <= 63 && FM * FN * 1024 <= RING && 8 * RING <= 160 * 1024, "ring");
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
+    // the column tiles of a row tile lie on one XCD: its L2 then fetches the rows of A once
+    int id = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int tile_n = id % tiles_n;
+    id /= tiles_n;
+    const int z = id / tiles_m, tile_m = id - z * tiles_m;
+    const int m0 = tile_m * 16 * FM, n0 = tile_n * 16 * FN;
+    const bf16_t* A = p.A + (long)z * p.bA;
+    const bf16_t* B = p.B + (long)z * p.bB;
+
+    // fetch i of a piece brings rows 8 i .. 8 i + 7 (first of A, then of B); chunk c of row r lies at position c ^ (r / 2 % 8)
+    const int r8 = lane >> 3;
+    unsigned off[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        const bool a = i < 2 * FM;
+        const int r = (a ? i : i - 2 * FM) * 8 + r8;
+        const unsigned chunk = (unsigned)((lane & 7) ^ ((r >> 1) & 7));
+        off[i] = (a ? (unsigned)min(m0 + r, p.M - 1) * (unsigned)p.lda : (unsigned)min(n0 + r, p.N - 1) * (unsigned)p.ldb) * 2 + chunk * 16;
+    }
+    const int nk = (p.K + BK - 1) / BK, k_first = nk * wave >> 3, mine = (nk * (wave + 1) >> 3) - k_first;       // this wave's pieces
+    const int ragged = (p.K & (BK - 1)) >> 3;                                    // chunks of a narrow last piece
+    const unsigned ring0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)smem + wave * RING);
+    auto fetch = [&](int t, unsigned st) {
+        const int kt = k_first + t;
+        const bf16_t *pa = A + (long)kt * BK, *pb = B + (long)kt * BK;
+        if (ragged && kt == nk - 1) {              // nothing beyond the end: zeros
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                const int chunk = (lane & 7) ^ ((4 * (i & 1) + (r8 >> 1)) & 7);
+                if (chunk < ragged) load_lds16(off[i], i < 2 * FM ? pa : pb, __builtin_amdgcn_readfirstlane(ring0 + st + i * 1024));
+                else *(uint4*)(smem + wave * RING + st + i * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) load_lds16(off[i], i < 2 * FM ? pa : pb, __builtin_amdgcn_readfirstlane(ring0 + st + i * 1024));
+        }
+    };
+    f32x4_t acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int t = 0; t < min(ST, mine); ++t) fetch(t, t * STAGE);
+    const unsigned char* row = smem + wave * RING + l16 * 128;
+    const int c0 = (g ^ (l16 >> 1)) << 4, c1 = ((4 + g) ^ (l16 >> 1)) << 4;
+    unsigned st = 0;
+    for (int t = 0; t < mine; ++t) {
+        // the pieces behind this one may be in flight; a narrow last one has fetches that cannot be counted
+        const int behind = min(ST, mine - t) - 1;
+        if (behind == ST - 1 && !(ragged && t + ST >= mine)) wait_vmcnt<(ST - 1) * NL>();
+        else wait_vmcnt<0>();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        bf16x8_t fa[2][FM], fb[2][FN];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i) fa[ks][i] = *(const bf16x8_t*)(row + st + i * 2048 + (ks ? c1 : c0));
+#pragma unroll
+            for (int j = 0; j < FN; ++j) fb[ks][j] = *(const bf16x8_t*)(row + st + (FM + j) * 2048 + (ks ? c1 : c0));
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // its place may be filled again
+        if (t + ST < mine) fetch(t + ST, st);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)      // operands swapped: lane (l16, g) then holds row l16, columns 4 g .. 4 g + 3
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+        st = st + STAGE == RING ? 0 : st + STAGE;
+    }
+    // the eight sums, each in its wave's own ring
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) *(f32x4_t*)(smem + wave * RING + (i * FN + j) * 1024 + lane * 16) = acc[i][j];
+    __syncthreads();
+    for (int e = tid; e < FM * FN * 64; e += 512) {
+        f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 8; ++w) s += *(const f32x4_t*)(smem + w * RING + e * 16);
+        const int f = e >> 6, el = e & 63, r = m0 + f / FN * 16 + (el & 15), c = n0 + f % FN * 16 + 4 * (el >> 4);
+        if (r >= p.M || c >= p.N) continue;       // N is a multiple of 4
+        uint2 w;
+        w.x = pack_bf16x2(p.alpha * s[0], p.alpha * s[1]);
+        w.y = pack_bf16x2(p.alpha * s[2], p.alpha * s[3]);
+        *(uint2*)((bf16_t*)p.C + (long)z * p.bC + (long)r * p.ldc + c) = w;
+    }
+}
+template <int FM, int FN, int ST>
+static hipError_t run_low_rank(const GemmNT& g, hipStream_t s) {
+    const int tiles_m = cdiv(g.M, 16 * FM), tiles_n = cdiv(g.N, 16 * FN);
+    const int lds = 8 * ST * 2 * (FM + FN) * 1024;
+    auto kern = low_rank_kernel<FM, FN, ST>;
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    kern<<<tiles_m * tiles_n * g.batch, 512, lds, s>>>(g, tiles_m, tiles_n);
+    return hipGetLastError();
+}
+// What a tile costs: launch, ends and first loads, the stream of the busiest CU, the rows of A on their way from memory (us; within 15 % of
+// the timings above but for long contractions of few rows, which are faster).
+struct LowRankTile { int fm, fn; const char* name; };
+static const LowRankTile kLowRankTiles[] = {{1, 1, "16x16"}, {1, 2, "16x32"}, {2, 2, "32x32"}, {2, 3, "32x48"}, {2, 4, "32x64"}, {3, 4, "48x64"}, {4, 4, "64x64"}};
+// index into kLowRankTiles, or -1: 64x64 tiles of the general kernel (with the contraction split and reduced: 10 us and 0.095 per
+// million operand bytes; whole, for short contractions: 2.5 us and 3.5 per 1000 elements)
+static int pick_low_rank(const GemmNT& g) {
+    if (g.A2 || g.K2 || g.R || g.c_f32 || g.deferred || g.K <= 0 || (g.N & 3) || (g.ldc & 3) || (g.bC & 3) || ((size_t)g.C & 7)) return -1;
+    if ((long)g.M * g.lda >= (1L << 30) || (long)g.N * g.ldb >= (1L << 30)) return -1;
+    const double rows_us = 0.1e-6 * 2.0 * g.M * g.K * g.batch;
+    const long t64 = (long)cdiv(g.M, 64) * cdiv(g.N, 64) * g.batch;
+    double best = g.split_k == 1 ? 2.5 + 3.5e-3 * g.K : 10.0 + 0.095e-6 * 256.0 * g.K * t64;
+    int pick = -1;
+    for (int i = 0; i < (int)(sizeof(kLowRankTiles) / sizeof(kLowRankTiles[0])); ++i) {
+        const LowRankTile& t = kLowRankTiles[i];
+        const long n = (long)cdiv(g.M, 16 * t.fm) * cdiv(g.N, 16 * t.fn) * g.batch;
+        const double us = 2.5 + 11.4e-6 * 32.0 * (t.fm + t.fn) * g.K * (double)((n + 255) / 256) + rows_us;
+        if (us < best) { best = us; pick = i; }
+    }
+    return pick;
+}
+const char* low_rank_plan(const GemmNT& g) {
+    const int i = pick_low_rank(g);
+    return i < 0 ? "general" : kLowRankTiles[i].name;
+}
+hipError_t launch_low_rank(const GemmNT& g, hipStream_t s) {
+    if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
+    if ((g.K & 7) || (g.lda & 7) || (g.ldb & 7) || (g.bA & 7) || (g.bB & 7)) return hipErrorInvalidValue;
+    switch (pick_low_rank(g)) {
+        case 0: return run_low_rank<1, 1, 2>(g, s);
+        case 1: return run_low_rank<1, 2, 1>(g, s);
+        case 2: return run_low_rank<2, 2, 1>(g, s);
+        case 3: return run_low_rank<2, 3, 1>(g, s);
+        case 4: return run_low_rank<2, 4, 1>(g, s);
+        case 5: return run_low_rank<3, 4, 1>(g, s);
+        case 6: return run_low_rank<4, 4, 1>(g, s);
+        default: return launch_gemm_nt(g, s);
+    }
+}
+
 // ======================================================================== TN
 // One 64x64 output tile of P^T Q over the 64-token tiles [it0, it1).  The operand tiles stay in LDS as they lie in
 // memory, [t][i] with the token index t as rows, and the matrix unit's operands (contraction over t) come out of the

@@ -32,6 +32,10 @@ const char* gemm_nt_plan(const GemmNT& g, int* n_split);
 // g.deferred, if set, receives 0; false: one launch
 bool gemm_nt_two_parts(const GemmNT& g, GemmNT* a, GemmNT* b);
 
+// The same for the narrow bf16 output of a low-rank product, without a second operand pair: one launch where that is faster
+hipError_t launch_low_rank(const GemmNT& g, hipStream_t s);
+const char* low_rank_plan(const GemmNT& g);      // name of its tile, "general" where it goes to launch_gemm_nt
+
 // C[Mo, No] (fp32) = alpha * P[T, Mo]^T Q[T, No]
 struct GemmTN {
     const bf16_t* P = nullptr; long ldp = 0;

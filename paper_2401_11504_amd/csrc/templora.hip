@@ -539,7 +539,7 @@ static tl_status group_fwd(tl_lora* L, int l, int g, const bf16_t* X, int T, bf1
     h.alpha = L->s; h.C = Hs; h.ldc = G * r;
     h.partial = L->partial; h.partial_elems = L->partial_elems;
     h.split_k = h.K <= LOW_RANK_WHOLE_K;
-    HIPCHK(launch_gemm_nt(h, s));
+    HIPCHK(launch_low_rank(h, s));
     GemmNT y;
     y.A = X; y.lda = din; y.B = m->layers[l].w[g]; y.ldb = din; y.M = T; y.N = dout; y.K = din;
     y.A2 = Hs; y.lda2 = G * r; y.B2 = L->S + o.B[g]; y.ldb2 = r; y.K2 = r;
@@ -596,7 +596,7 @@ static tl_status group_bwd(tl_lora* L, int l, int g, const bf16_t* dY, const bf1
     h.batch = G; h.bA = dout; h.bB = (long)r * dout; h.bC = r;
     h.partial = L->partial; h.partial_elems = L->partial_elems;
     h.split_k = h.K <= LOW_RANK_WHOLE_K;
-    HIPCHK(launch_gemm_nt(h, s));
+    HIPCHK(launch_low_rank(h, s));
     if (dX) {
         GemmNT x;
         x.A = dY; x.lda = (long)G * dout; x.B = m->layers[l].wt[g]; x.ldb = (long)G * dout; x.M = T; x.N = din;
@@ -1441,6 +1441,27 @@ extern "C" tl_status tl_k_gemm_nt_plan(int32_t M, int32_t N, int32_t K, int32_t 
     snprintf(name_out, name_cap, "%s", name);
     if (n_split_out) *n_split_out = sp;
     if (n_launches_out) *n_launches_out = two ? 2 : 1;
+    return TL_OK;
+}
+static GemmNT low_rank_product(const uint16_t* A, int32_t lda, const uint16_t* B, int32_t ldb, int32_t M, int32_t N, int32_t K, int32_t batch,
+                               float alpha, uint16_t* C, float* workspace, size_t workspace_elems) {
+    GemmNT g;
+    g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.M = M; g.N = N; g.K = K; g.alpha = alpha; g.C = C; g.ldc = (long)batch * N;
+    g.batch = batch; g.bA = K; g.bB = (long)N * ldb; g.bC = N;
+    if (workspace && workspace_elems > 0) { g.partial = workspace; g.partial_elems = workspace_elems; }
+    g.split_k = K <= LOW_RANK_WHOLE_K;
+    return g;
+}
+extern "C" tl_status tl_k_low_rank(const uint16_t* A, int32_t lda, const uint16_t* B, int32_t ldb, int32_t M, int32_t N, int32_t K,
+                                   int32_t batch, float alpha, uint16_t* C, float* workspace, size_t workspace_elems, void* hip_stream) {
+    KARGS_OK(A && B && C && M >= 0 && N >= 0 && K >= 0 && batch >= 0, "tl_k_low_rank");
+    HIPCHK(launch_low_rank(low_rank_product(A, lda, B, ldb, M, N, K, batch, alpha, C, workspace, workspace_elems), (hipStream_t)hip_stream));
+    return TL_OK;
+}
+extern "C" tl_status tl_k_low_rank_plan(int32_t M, int32_t N, int32_t K, int32_t batch, size_t workspace_elems, char* name_out, size_t name_cap) {
+    KARGS_OK(name_out && name_cap > 0 && M > 0 && N > 0 && K > 0 && batch > 0, "tl_k_low_rank_plan");
+    static float dummy;
+    snprintf(name_out, name_cap, "%s", low_rank_plan(low_rank_product(nullptr, K * batch, nullptr, K, M, N, K, batch, 1.f, nullptr, &dummy, workspace_elems)));
     return TL_OK;
 }
 extern "C" tl_status tl_k_linear_step_plan(int32_t T, int32_t d_in, int32_t d_out, int32_t r, float s, int32_t one_by_one, char* names_out,

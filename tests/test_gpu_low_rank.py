@@ -1,0 +1,52 @@
+"""The narrow products of the low-rank branch (tl_k_low_rank) against fp64 sums of the same bf16 operands.
+
+Every tile the rule can pick, with rows and columns that end inside one, contractions that end inside a 64-wide piece or leave some of the
+eight waves without one, and the products that go on to the general kernel.  Tolerance: one bf16 rounding of the result has a relative
+error of 2^-9 / sqrt(3) = 1.1e-3 in the L2 sense and at most 2^-9 of the element; 2e-3 and 2e-2 of the RMS leave room for fp32 sums and
+elements of 4.5 RMS."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2401_11504_amd import synth  # noqa: E402
+
+SCRATCH = 16 << 20
+#        M, N, K, batch, tile
+CASES = [(1024, 64, 4096, 1, "16x16"), (37, 24, 1000, 1, "16x16"), (1, 8, 8, 1, "16x16"), (200, 48, 72, 3, "16x16"), (300, 40, 4096, 2, "16x16"),
+         (1024, 96, 4096, 1, "16x32"), (1030, 128, 4104, 1, "32x32"), (1020, 120, 4104, 1, "16x32"), (1000, 32, 4096, 3, "16x32"),
+         (1024, 192, 4096, 1, "32x32"), (1020, 56, 2048, 3, "32x32"), (2048, 192, 4096, 1, "32x48"), (2048, 64, 4096, 3, "32x64"), (2044, 60, 4096, 3, "32x64"),
+         (3000, 192, 4096, 1, "48x64"), (2990, 188, 4096, 1, "48x64"), (5120, 192, 4096, 1, "64x64"), (5101, 192, 2048, 1, "64x64"),
+         (2048, 64, 11008, 2, "general")]
+
+
+def test_the_cases_reach_every_tile():
+    from paper_2401_11504_amd import api
+    for M, N, K, nb, tile in CASES:
+        assert api.tl_k_low_rank_plan(M, N, K, nb, SCRATCH) == tile, (M, N, K, nb)
+    assert {c[4] for c in CASES} == {"16x16", "16x32", "32x32", "32x48", "32x64", "48x64", "64x64", "general"}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,nb,tile", CASES)
+def test_low_rank(M, N, K, nb, tile):
+    from paper_2401_11504_amd import api, harness as H
+    # what lies behind the contraction in memory is NaN: it must not be multiplied, not even by zero
+    lda, ldb = (nb * K + 71) // 8 * 8, (K + 71) // 8 * 8
+    a, b = np.full((M, lda), np.nan), np.full((nb * N, ldb), np.nan)
+    a[:, :nb * K] = synth.normal(1, (61, M, N), (M, nb * K), 1.0, True)
+    b[:, :K] = synth.normal(2, (62, M, N), (nb * N, K), 0.05, True)
+    A, B = H.to_dev_bf16(a)[:, :nb * K], H.to_dev_bf16(b)[:, :K]
+    out = torch.full((M + 1, nb * N), 3.0, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(SCRATCH, dtype=torch.float32, device="cuda")
+    for _ in range(2):                  # twice: the same bits
+        last = out.clone()
+        api.tl_k_low_rank(A, B, out, nb, 0.5, ws)
+        torch.cuda.synchronize()
+    assert torch.equal(last, out)
+    assert torch.all(out[M] == 3.0)
+    A64, B64 = A.double(), B.double()
+    ref = torch.cat([A64[:, i * K:(i + 1) * K] @ B64[i * N:(i + 1) * N].T for i in range(nb)], 1) * 0.5
+    err = out[:M].double() - ref
+    assert err.norm() <= 2e-3 * ref.norm()
+    assert err.abs().max() <= 2e-2 * ref.norm() / ref.numel() ** 0.5
