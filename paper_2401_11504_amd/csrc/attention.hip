@@ -273,7 +273,7 @@ __global__ __launch_bounds__(NW * 64 * KG) void attn_fwd_kernel(const bf16_t* __
 // direct-to-LDS loads two tiles ahead, one copy of each: 16-byte chunk c of row x lies at position c ^ swz(x), so that both the reads of
 // 16 rows at one chunk and the transposing reads of four rows x 64 bytes fall into distinct banks.
 // us without and with this (before: waves of 32 rows, two copies of each tile, loads and stores of 32 rows at a time), heads of 128 / 64:
-// 1024 tokens, 32 heads 62 and 46 / 16 heads 39 and 18; 2048 tokens 189 and 138 / 78 and 47; 5120 tokens, 32 heads of 128 1000 and 755.
+// 1024 tokens, 32 heads 62 and 46 / 16 heads 39 and 18; 2048 tokens 189 and 138 / 78 and 47; 5120 tokens, 32 heads of 128 1000 and 745.
 template <int DH>
 __device__ __forceinline__ int attn_swz(int row) {
     return DH == 128 ? 4 * (row & 3) | ((row >> 2) & 3) : 4 * ((row >> 1) & 1) | ((row >> 2) & 3);
@@ -381,10 +381,10 @@ __device__ __forceinline__ void attn_bwd_part(
     };
     fetch_block(p1, ldq, P1_AT);
     fetch_block(p2, ldp2, P2_AT);
-    // Tiles are taken from the last one down: the key blocks of a head that start together then read the same ones (5120 tokens: 764 us
-    // with dK, dV and dQ upwards, 745 with dK and dV down, 755 with both)
+    // dK and dV take the tiles from the last one down, dQ from the first one up: the blocks of a head that start together then read the
+    // same ones (5120 tokens: 764 us with both upwards, 755 with both downwards, 745 like this)
     const int n_steps = tile1 - tile0;
-    auto tile_of = [&](int i) { return tile1 - 1 - min(i, n_steps - 1); };
+    auto tile_of = [&](int i) { return DQ ? min(i, n_steps - 1) : tile1 - 1 - min(i, n_steps - 1); };
     fetch(fetch_of(tile_of(0), C::V0));
     fetch(fetch_of(tile_of(1), C::V0 + STAGE));
     // this lane's place in the fragments of block rows (chunk 2 ks + g of row l32 of a group)
@@ -570,10 +570,10 @@ __device__ __forceinline__ void attn_bwd_part(
     // the mask.  (Rows beyond T need none: as queries their log-sum-exp is beyond any score, as keys they follow every query.)
     const int w = pw0 - 32 * sg;
     if constexpr (DQ) {
-        const int skip_end = tile1 - min(tile1, (w + 32 * NG + 63) >> 6), mask_end = tile1 - min(tile1, (w + 33) >> 6);
-        while (i_step < skip_end) step(Skip{});
+        const int plain_end = min(tile1, (w + 33) >> 6), mask_end = min(tile1, (w + 32 * NG + 63) >> 6);
+        while (i_step < plain_end) step(Plain{});
         while (i_step < mask_end) step(Masked{});
-        while (i_step < n_steps) step(Plain{});
+        while (i_step < n_steps) step(Skip{});
     } else {
         const int plain_end = tile1 - min(tile1, (w + 32 * NG + 62) >> 6), mask_end = tile1 - min(tile1, (w + 32) >> 6);
         while (i_step < plain_end) step(Plain{});
