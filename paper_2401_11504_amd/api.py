@@ -87,6 +87,8 @@ _SIGS = {
                      _sz, _vp],
     "tl_k_low_rank": [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _i32, _f32, _vp, _vp, _sz, _vp],
     "tl_k_low_rank_plan": [_i32, _i32, _i32, _i32, _sz, C.c_char_p, _sz],
+    "tl_k_frozen": [_vp, _vp, _i32, _i32, _i32, _vp, _vp, _i32, _vp, _vp, _i32, _vp],
+    "tl_k_frozen_plan": [_i32, _i32, _i32, _i32, C.c_char_p, _sz],
     "tl_k_gemm_nt_plan": [_i32, _i32, _i32, _i32, _sz, C.c_char_p, _sz, C.POINTER(_i32), C.POINTER(_i32)],
     "tl_k_linear_step_plan": [_i32] * 4 + [_f32, _i32, C.c_char_p, _sz],
     "tl_k_gemm_tn": [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _f32, _vp, _i32, _vp],
@@ -347,6 +349,19 @@ def tl_k_low_rank_plan(M, N, K, batch=1, workspace_elems=0):
     """-> name of the tile"""
     buf = C.create_string_buffer(32)
     _chk(_lib.tl_k_low_rank_plan(M, N, K, batch, workspace_elems, buf, 32))
+    return buf.value.decode()
+
+
+def tl_k_frozen(A, B, out, A2=None, B2=None, R=None, stream=None):
+    """dense operands: A [M, K], B [N, K], A2 [M, K2], B2 [N, K2], R fp32 [M, N]; out bf16 or fp32 [M, N]"""
+    _chk(_lib.tl_k_frozen(_dp(A), _dp(B), A.shape[0], B.shape[0], A.shape[1], _dp(A2), _dp(B2), A2.shape[1] if A2 is not None else 0, _dp(R),
+                          _dp(out), int(out.dtype == torch.float32), _s(stream)))
+
+
+def tl_k_frozen_plan(M, N, K, K2=0):
+    """-> name of the tile"""
+    buf = C.create_string_buffer(32)
+    _chk(_lib.tl_k_frozen_plan(M, N, K, K2, buf, 32))
     return buf.value.decode()
 
 

@@ -838,8 +838,9 @@ hipError_t launch_gemm_nt(const GemmNT& g, hipStream_t s) {
     return run_nt<64, 64, 2, 2>(g, split, s);
 }
 
-// ======================================================================== NT, narrow outputs (low-rank products)
-// C = alpha A B^T, bf16, for the few columns of a low-rank product: Hs = s X A^T, dH = s dY B (N = the rank, or three of them).
+// ======================================================================== NT, few tiles: the waves of a workgroup split the contraction
+// The same contract as gemm_nt_kernel, for outputs too small to fill the chip with tiles that pay: the few columns of a low-rank product,
+// Hs = s X A^T, dH = s dY B (N = the rank, or three of them), and every product of a small decoder or a short sample.
 // One launch: a workgroup computes a (16 FM) x (16 FN) tile over the whole contraction, each of its eight waves an eighth of it in
 // 64-wide pieces through a ring of its own (direct-to-LDS loads of whole 128-byte rows, ST pieces in flight, no barrier), and adds
 // the eight sums up through LDS in a fixed order.  What bounds it is the operand stream of a CU (some 88 GB/s with the weights of the
@@ -850,7 +851,7 @@ hipError_t launch_gemm_nt(const GemmNT& g, hipStream_t s) {
 // 6.7 and 12.9, 12.6 and 18.1; 5120 rows: 20 and 25, 16 and 16, 22 and 28; 64 of a contraction of 11008: 512 rows 9.9 and 14.3, 1024 rows
 // 10.6 and 13.5, 2048 rows 19 and 17.  Rings of 96 to 160 KB (two to five pieces ahead): up to 1 us slower.
 template <int FM, int FN, int ST>
-__global__ __launch_bounds__(512, 2) void low_rank_kernel(GemmNT p, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(512, 2) void nt_waves_kernel(GemmNT p, int tiles_m, int tiles_n) {
     constexpr int NL = 2 * (FM + FN), STAGE = NL * 1024, RING = ST * STAGE;      // fetches per piece; bytes
     static_assert((ST - 1) * NL <= 63 && FM * FN * 1024 <= RING && 8 * RING <= 160 * 1024, "ring");
     extern __shared__ __align__(16) unsigned char smem[];
@@ -875,22 +876,34 @@ __global__ __launch_bounds__(512, 2) void low_rank_kernel(GemmNT p, int tiles_m,
         const unsigned chunk = (unsigned)((lane & 7) ^ ((r >> 1) & 7));
         off[i] = (a ? (unsigned)min(m0 + r, p.M - 1) * (unsigned)p.lda : (unsigned)min(n0 + r, p.N - 1) * (unsigned)p.ldb) * 2 + chunk * 16;
     }
-    const int nk = (p.K + BK - 1) / BK, k_first = nk * wave >> 3, mine = (nk * (wave + 1) >> 3) - k_first;       // this wave's pieces
-    const int ragged = (p.K & (BK - 1)) >> 3;                                    // chunks of a narrow last piece
+    // pieces of the contraction: the low-rank pair, then the main one; the last of each may be narrow
+    const int n_low = (p.K2 + BK - 1) / BK, nk = n_low + (p.K + BK - 1) / BK;
+    const int k_first = nk * wave >> 3, mine = (nk * (wave + 1) >> 3) - k_first;        // this wave's pieces
+    const int whole = min(n_low + p.K / BK, k_first + mine);                            // n_low .. whole - 1 are fetched without a look
+    const bool narrow = (((p.K | p.K2) & (BK - 1)) != 0) && (whole < k_first + mine || k_first < n_low);
     const unsigned ring0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)smem + wave * RING);
     auto fetch = [&](int t, unsigned st) {
         const int kt = k_first + t;
-        const bf16_t *pa = A + (long)kt * BK, *pb = B + (long)kt * BK;
-        if (ragged && kt == nk - 1) {              // nothing beyond the end: zeros
-#pragma unroll
-            for (int i = 0; i < NL; ++i) {
-                const int chunk = (lane & 7) ^ ((4 * (i & 1) + (r8 >> 1)) & 7);
-                if (chunk < ragged) load_lds16(off[i], i < 2 * FM ? pa : pb, __builtin_amdgcn_readfirstlane(ring0 + st + i * 1024));
-                else *(uint4*)(smem + wave * RING + st + i * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
-            }
-        } else {
+        if (kt >= n_low && kt < whole) {
+            const bf16_t *pa = A + (long)(kt - n_low) * BK, *pb = B + (long)(kt - n_low) * BK;
 #pragma unroll
             for (int i = 0; i < NL; ++i) load_lds16(off[i], i < 2 * FM ? pa : pb, __builtin_amdgcn_readfirstlane(ring0 + st + i * 1024));
+            return;
+        }
+        const bool low = kt < n_low;                // zeros beyond the end
+        const int k0 = (low ? kt : kt - n_low) * BK, valid = min(BK, (low ? p.K2 : p.K) - k0) >> 3;
+        const bf16_t* pa = (low ? p.A2 + (long)z * p.bA2 : A) + k0;
+        const bf16_t* pb = (low ? p.B2 + (long)z * p.bB2 : B) + k0;
+        const unsigned la = (unsigned)(low ? p.lda2 : p.lda) * 2, lb = (unsigned)(low ? p.ldb2 : p.ldb) * 2;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const bool a = i < 2 * FM;
+            const int r = (a ? i : i - 2 * FM) * 8 + r8, chunk = (lane & 7) ^ ((r >> 1) & 7);
+            if (chunk < valid)
+                load_lds16((unsigned)(a ? min(m0 + r, p.M - 1) : min(n0 + r, p.N - 1)) * (a ? la : lb) + chunk * 16, a ? pa : pb,
+                           __builtin_amdgcn_readfirstlane(ring0 + st + i * 1024));
+            else
+                *(uint4*)(smem + wave * RING + st + i * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
         }
     };
     f32x4_t acc[FM][FN];
@@ -904,9 +917,8 @@ __global__ __launch_bounds__(512, 2) void low_rank_kernel(GemmNT p, int tiles_m,
     const int c0 = (g ^ (l16 >> 1)) << 4, c1 = ((4 + g) ^ (l16 >> 1)) << 4;
     unsigned st = 0;
     for (int t = 0; t < mine; ++t) {
-        // the pieces behind this one may be in flight; a narrow last one has fetches that cannot be counted
-        const int behind = min(ST, mine - t) - 1;
-        if (behind == ST - 1 && !(ragged && t + ST >= mine)) wait_vmcnt<(ST - 1) * NL>();
+        // the pieces behind this one may be in flight; narrow ones have fetches that cannot be counted
+        if (t + ST <= mine && !narrow) wait_vmcnt<(ST - 1) * NL>();
         else wait_vmcnt<0>();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         bf16x8_t fa[2][FM], fb[2][FN];
@@ -940,17 +952,27 @@ __global__ __launch_bounds__(512, 2) void low_rank_kernel(GemmNT p, int tiles_m,
         for (int w = 0; w < 8; ++w) s += *(const f32x4_t*)(smem + w * RING + e * 16);
         const int f = e >> 6, el = e & 63, r = m0 + f / FN * 16 + (el & 15), c = n0 + f % FN * 16 + 4 * (el >> 4);
         if (r >= p.M || c >= p.N) continue;       // N is a multiple of 4
-        uint2 w;
-        w.x = pack_bf16x2(p.alpha * s[0], p.alpha * s[1]);
-        w.y = pack_bf16x2(p.alpha * s[2], p.alpha * s[3]);
-        *(uint2*)((bf16_t*)p.C + (long)z * p.bC + (long)r * p.ldc + c) = w;
+        const long at = (long)z * p.bC + (long)r * p.ldc + c;
+        if (p.c_f32) {
+            float4 v = make_float4(p.alpha * s[0], p.alpha * s[1], p.alpha * s[2], p.alpha * s[3]);
+            if (p.R) {
+                const float4 q = *(const float4*)(p.R + at);
+                v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
+            }
+            *(float4*)((float*)p.C + at) = v;
+        } else {
+            uint2 w;
+            w.x = pack_bf16x2(p.alpha * s[0], p.alpha * s[1]);
+            w.y = pack_bf16x2(p.alpha * s[2], p.alpha * s[3]);
+            *(uint2*)((bf16_t*)p.C + at) = w;
+        }
     }
 }
 template <int FM, int FN, int ST>
-static hipError_t run_low_rank(const GemmNT& g, hipStream_t s) {
+static hipError_t run_waves(const GemmNT& g, hipStream_t s) {
     const int tiles_m = cdiv(g.M, 16 * FM), tiles_n = cdiv(g.N, 16 * FN);
     const int lds = 8 * ST * 2 * (FM + FN) * 1024;
-    auto kern = low_rank_kernel<FM, FN, ST>;
+    auto kern = nt_waves_kernel<FM, FN, ST>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     kern<<<tiles_m * tiles_n * g.batch, 512, lds, s>>>(g, tiles_m, tiles_n);
@@ -958,42 +980,73 @@ static hipError_t run_low_rank(const GemmNT& g, hipStream_t s) {
 }
 // What a tile costs: launch, ends and first loads, the stream of the busiest CU, the rows of A on their way from memory (us; within 15 % of
 // the timings above but for long contractions of few rows, which are faster).
-struct LowRankTile { int fm, fn; const char* name; };
-static const LowRankTile kLowRankTiles[] = {{1, 1, "16x16"}, {1, 2, "16x32"}, {2, 2, "32x32"}, {2, 3, "32x48"}, {2, 4, "32x64"}, {3, 4, "48x64"}, {4, 4, "64x64"}};
-// index into kLowRankTiles, or -1: 64x64 tiles of the general kernel (with the contraction split and reduced: 10 us and 0.095 per
-// million operand bytes; whole, for short contractions: 2.5 us and 3.5 per 1000 elements)
-static int pick_low_rank(const GemmNT& g) {
-    if (g.A2 || g.K2 || g.R || g.c_f32 || g.deferred || g.K <= 0 || (g.N & 3) || (g.ldc & 3) || (g.bC & 3) || ((size_t)g.C & 7)) return -1;
-    if ((long)g.M * g.lda >= (1L << 30) || (long)g.N * g.ldb >= (1L << 30)) return -1;
+struct WavesTile { int fm, fn; const char* name; };
+static const WavesTile kWavesTiles[] = {{1, 1, "16x16"}, {1, 2, "16x32"}, {2, 2, "32x32"}, {2, 3, "32x48"}, {2, 4, "32x64"}, {3, 4, "48x64"}, {4, 4, "64x64"}};
+// index into kWavesTiles of the fastest tile that promises less than `best` us, or -1
+static int pick_waves(const GemmNT& g, double best, int n_tiles = (int)(sizeof(kWavesTiles) / sizeof(kWavesTiles[0]))) {
+    const size_t align = g.c_f32 ? 15 : 7;
+    if (g.K <= 0 || (g.N & 3) || (g.ldc & 3) || (g.bC & 3) || ((size_t)g.C & align) || ((size_t)g.R & 15)) return -1;
+    if ((long)g.M * g.lda >= (1L << 30) || (long)g.N * g.ldb >= (1L << 30) || (long)g.M * g.lda2 >= (1L << 30) || (long)g.N * g.ldb2 >= (1L << 30))
+        return -1;
     const double rows_us = 0.1e-6 * 2.0 * g.M * g.K * g.batch;
-    const long t64 = (long)cdiv(g.M, 64) * cdiv(g.N, 64) * g.batch;
-    double best = g.split_k == 1 ? 2.5 + 3.5e-3 * g.K : 10.0 + 0.095e-6 * 256.0 * g.K * t64;
     int pick = -1;
-    for (int i = 0; i < (int)(sizeof(kLowRankTiles) / sizeof(kLowRankTiles[0])); ++i) {
-        const LowRankTile& t = kLowRankTiles[i];
+    for (int i = 0; i < n_tiles; ++i) {
+        const WavesTile& t = kWavesTiles[i];
         const long n = (long)cdiv(g.M, 16 * t.fm) * cdiv(g.N, 16 * t.fn) * g.batch;
-        const double us = 2.5 + 11.4e-6 * 32.0 * (t.fm + t.fn) * g.K * (double)((n + 255) / 256) + rows_us;
+        const double us = 2.5 + 11.4e-6 * 32.0 * (t.fm + t.fn) * (g.K + g.K2) * (double)((n + 255) / 256) + rows_us;
         if (us < best) { best = us; pick = i; }
     }
     return pick;
 }
+static bool nt_valid(const GemmNT& g) {
+    return !((g.K & 7) || (g.K2 & 7) || (g.lda & 7) || (g.ldb & 7) || (g.lda2 & 7) || (g.ldb2 & 7) || (g.bA & 7) || (g.bB & 7) || (g.bA2 & 7) ||
+             (g.bB2 & 7)) && (g.c_f32 || !g.R);
+}
+static hipError_t launch_waves(const GemmNT& g, int tile, hipStream_t s) {
+    switch (tile) {
+        case 0: return run_waves<1, 1, 2>(g, s);
+        case 1: return run_waves<1, 2, 1>(g, s);
+        case 2: return run_waves<2, 2, 1>(g, s);
+        case 3: return run_waves<2, 3, 1>(g, s);
+        case 4: return run_waves<2, 4, 1>(g, s);
+        case 5: return run_waves<3, 4, 1>(g, s);
+        default: return run_waves<4, 4, 1>(g, s);
+    }
+}
+// A low-rank product.  On the other side 64x64 tiles of the general kernel: with the contraction split and reduced 10 us and 0.095 per
+// million operand bytes; whole, for short contractions, 2.5 us and 3.5 per 1000 elements.
+static int pick_low_rank(const GemmNT& g) {
+    const long t64 = (long)cdiv(g.M, 64) * cdiv(g.N, 64) * g.batch;
+    return pick_waves(g, g.split_k == 1 ? 2.5 + 3.5e-3 * g.K : 10.0 + 0.095e-6 * 256.0 * g.K * t64);
+}
 const char* low_rank_plan(const GemmNT& g) {
     const int i = pick_low_rank(g);
-    return i < 0 ? "general" : kLowRankTiles[i].name;
+    return i < 0 ? "general" : kWavesTiles[i].name;
 }
 hipError_t launch_low_rank(const GemmNT& g, hipStream_t s) {
-    if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
-    if ((g.K & 7) || (g.lda & 7) || (g.ldb & 7) || (g.bA & 7) || (g.bB & 7)) return hipErrorInvalidValue;
-    switch (pick_low_rank(g)) {
-        case 0: return run_low_rank<1, 1, 2>(g, s);
-        case 1: return run_low_rank<1, 2, 1>(g, s);
-        case 2: return run_low_rank<2, 2, 1>(g, s);
-        case 3: return run_low_rank<2, 3, 1>(g, s);
-        case 4: return run_low_rank<2, 4, 1>(g, s);
-        case 5: return run_low_rank<3, 4, 1>(g, s);
-        case 6: return run_low_rank<4, 4, 1>(g, s);
-        default: return launch_gemm_nt(g, s);
-    }
+    if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.deferred || !nt_valid(g)) return launch_gemm_nt(g, s);
+    const int i = pick_low_rank(g);
+    return i < 0 ? launch_gemm_nt(g, s) : launch_waves(g, i, s);
+}
+// A frozen product of a small decoder or a short sample: up to half a million outputs and four million weights (us in the general kernel
+// and here: 200 x 256 x 688 7.0 and 4.9, 300 x 512 x 1408 8.3 and 5.8, 512 x 1024 x 2816 12.8 and 11.8, 100 x 2048 x 2048 9.8 and 9.0; beyond,
+// 128 x 4096 x 4096 22.8 and 22.9, 1024 x 1024 x 1024 7.8 and 9.6, 1024 x 1024 x 2816 14.3 and 15.2).  The general kernel's model is that of launches
+// that follow one another closely; behind another kernel's end its chain of barriers costs 1 us more.
+static int pick_small(const GemmNT& g) {
+    if (g.K <= 0 || g.split_k > 1 || (long)g.M * g.N * g.batch > (1L << 19) || (long)g.N * g.K > (1L << 22)) return -1;
+    const double general = nt_direct(g) ? pick_nt(g).us : 2.0 + 4.2e-3 * (g.K + g.K2);
+    return pick_waves(g, general + 1.0, 5);
+}
+const char* frozen_plan(const GemmNT& g) {
+    const int i = pick_small(g);
+    return i < 0 ? "general" : kWavesTiles[i].name;
+}
+hipError_t launch_frozen(const GemmNT& g, hipStream_t s) {
+    if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || !nt_valid(g) || (g.deferred && (g.batch != 1 || g.alpha != 1.f))) return launch_gemm_nt(g, s);
+    const int i = pick_small(g);
+    if (i < 0) return launch_gemm_nt(g, s);
+    if (g.deferred) *g.deferred = 0;
+    return launch_waves(g, i, s);
 }
 
 // ======================================================================== TN

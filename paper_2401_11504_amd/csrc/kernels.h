@@ -36,6 +36,10 @@ bool gemm_nt_two_parts(const GemmNT& g, GemmNT* a, GemmNT* b);
 hipError_t launch_low_rank(const GemmNT& g, hipStream_t s);
 const char* low_rank_plan(const GemmNT& g);      // name of its tile, "general" where it goes to launch_gemm_nt
 
+// launch_gemm_nt, or the kernel of the low-rank products where that is faster: few outputs, few weights
+hipError_t launch_frozen(const GemmNT& g, hipStream_t s);
+const char* frozen_plan(const GemmNT& g);
+
 // C[Mo, No] (fp32) = alpha * P[T, Mo]^T Q[T, No]
 struct GemmTN {
     const bf16_t* P = nullptr; long ldp = 0;

@@ -210,7 +210,7 @@ static void prof_mark(tl_lora* L) {
 // run one frozen-weight GEMM, bracketed by events when timing is on
 static hipError_t timed_gemm_one(tl_lora* L, const GemmNT& g) {
     prof_mark(L);
-    hipError_t e = launch_gemm_nt(g, L->model->stream);
+    hipError_t e = launch_frozen(g, L->model->stream);
     prof_mark(L);
     if (L->prof_on) L->prof_flop += 2.0 * g.M * (double)g.N * ((double)g.K + g.K2) * g.batch;
     return e;
@@ -1441,6 +1441,25 @@ extern "C" tl_status tl_k_gemm_nt_plan(int32_t M, int32_t N, int32_t K, int32_t 
     snprintf(name_out, name_cap, "%s", name);
     if (n_split_out) *n_split_out = sp;
     if (n_launches_out) *n_launches_out = two ? 2 : 1;
+    return TL_OK;
+}
+static GemmNT frozen_product(const uint16_t* A, const uint16_t* B, int32_t M, int32_t N, int32_t K, const uint16_t* A2, const uint16_t* B2,
+                             int32_t K2, const float* R, void* C, int32_t c_f32) {
+    GemmNT g;
+    g.A = A; g.lda = K; g.B = B; g.ldb = K; g.M = M; g.N = N; g.K = K;
+    g.A2 = K2 ? A2 : nullptr; g.lda2 = K2; g.B2 = K2 ? B2 : nullptr; g.ldb2 = K2; g.K2 = K2;
+    g.R = R; g.C = C; g.ldc = N; g.c_f32 = c_f32;
+    return g;
+}
+extern "C" tl_status tl_k_frozen(const uint16_t* A, const uint16_t* B, int32_t M, int32_t N, int32_t K, const uint16_t* A2, const uint16_t* B2,
+                                 int32_t K2, const float* R, void* C, int32_t c_f32, void* hip_stream) {
+    KARGS_OK(A && B && C && M >= 0 && N >= 0 && K >= 0 && K2 >= 0 && (K2 == 0 || (A2 && B2)), "tl_k_frozen");
+    HIPCHK(launch_frozen(frozen_product(A, B, M, N, K, A2, B2, K2, R, C, c_f32), (hipStream_t)hip_stream));
+    return TL_OK;
+}
+extern "C" tl_status tl_k_frozen_plan(int32_t M, int32_t N, int32_t K, int32_t K2, char* name_out, size_t name_cap) {
+    KARGS_OK(name_out && name_cap > 0 && M > 0 && N > 0 && K > 0 && K2 >= 0, "tl_k_frozen_plan");
+    snprintf(name_out, name_cap, "%s", frozen_plan(frozen_product(nullptr, nullptr, M, N, K, nullptr, nullptr, K2, nullptr, nullptr, 0)));
     return TL_OK;
 }
 static GemmNT low_rank_product(const uint16_t* A, int32_t lda, const uint16_t* B, int32_t ldb, int32_t M, int32_t N, int32_t K, int32_t batch,

@@ -1,4 +1,5 @@
-"""The narrow products of the low-rank branch (tl_k_low_rank) against fp64 sums of the same bf16 operands.
+"""The narrow products of the low-rank branch (tl_k_low_rank), and the small frozen ones that take the same kernel (tl_k_frozen), against
+fp64 sums of the same bf16 operands.
 
 Every tile the rule can pick, with rows and columns that end inside one, contractions that end inside a 64-wide piece or leave some of the
 eight waves without one, and the products that go on to the general kernel.  Tolerance: one bf16 rounding of the result has a relative
@@ -50,3 +51,44 @@ def test_low_rank(M, N, K, nb, tile):
     err = out[:M].double() - ref
     assert err.norm() <= 2e-3 * ref.norm()
     assert err.abs().max() <= 2e-2 * ref.norm() / ref.numel() ** 0.5
+
+
+#         M, N, K, K2, tile
+FROZEN = [(200, 256, 256, 16, "16x16"), (200, 256, 688, 16, "16x16"), (1, 8, 8, 8, "16x16"), (45, 100, 2000, 40, "16x16"), (200, 688, 256, 16, "32x32"),
+          (300, 512, 1408, 8, "32x32"), (290, 508, 1400, 72, "32x32"), (100, 500, 4096, 64, "16x16"), (300, 400, 2048, 0, "16x32"),
+          (500, 636, 1024, 192, "32x48"), (512, 1024, 2816, 16, "32x64"), (1024, 1024, 1024, 16, "general"), (128, 4096, 4096, 64, "general")]
+
+
+def test_the_frozen_cases_reach_their_tiles():
+    from paper_2401_11504_amd import api
+    for M, N, K, K2, tile in FROZEN:
+        assert api.tl_k_frozen_plan(M, N, K, K2) == tile, (M, N, K, K2)
+    assert {c[4] for c in FROZEN} == {"16x16", "16x32", "32x32", "32x48", "32x64", "general"}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("M,N,K,K2,tile", FROZEN)
+def test_frozen(M, N, K, K2, tile, f32):
+    """bf16 output as above; fp32 output with a residual: fp32 sums of bf16 products, 1e-5 in the L2 sense (2^-24 times a few roundings of up to
+    4288 terms)."""
+    from paper_2401_11504_amd import api, harness as H
+
+    def draw(i, rows, cols, std):
+        return H.to_dev_bf16(synth.normal(i, (63, M, N), (rows, cols), std, True))
+    A, B = draw(1, M, K, 1.0), draw(2, N, K, 0.05)
+    A2, B2 = (draw(3, M, K2, 1.0), draw(4, N, K2, 0.05)) if K2 else (None, None)
+    R = torch.randn(M, N, device="cuda", generator=torch.Generator(device="cuda").manual_seed(5)) if f32 else None
+    out = torch.full((M + 1, N), 3.0, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda")
+    api.tl_k_frozen(A, B, out[:M], A2, B2, R)
+    torch.cuda.synchronize()
+    assert torch.all(out[M] == 3.0)
+    ref = A.double() @ B.double().T
+    if K2:
+        ref += A2.double() @ B2.double().T
+    if f32:
+        ref += R.double()
+    err = out[:M].double() - ref
+    tol = 1e-5 if f32 else 2e-3
+    assert err.norm() <= tol * ref.norm()
+    assert err.abs().max() <= 10 * tol * ref.norm() / ref.numel() ** 0.5
