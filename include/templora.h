@@ -359,7 +359,8 @@ tl_status tl_k_gemm_nt_plan(int32_t M, int32_t N, int32_t K, int32_t K2, size_t 
                             size_t name_cap, int32_t* n_split_out, int32_t* n_launches_out);
 
 /* Which kernels a tl_linear_step of these sizes takes, launch by launch, names separated by spaces into names_out (host, names_cap bytes):
- * "direct-16x16", "direct-32x32", "64x64", "split-128x128", "split-256x128", "wide-32x32", "wide-64x64".  Two launches (H and dH; Y, dX, dA and
+ * "direct-16x16", "direct-32x32", "64x64", "split-128x128", "split-256x128", "wide-32x32", "wide-64x64", and "waves-16x16", "waves-16x32" for H and dH of
+ * operands that start at multiples of 16 bytes, row by row (addresses are taken to be such here).  Two launches (H and dH; Y, dX, dA and
  * dB), or with one_by_one, as where an output shares memory with an input, six (H, Y, dH, dX, dA, dB).  Host only, nothing is
  * launched: the tests use it to show that their shapes reach every kernel. */
 tl_status tl_k_linear_step_plan(int32_t T, int32_t d_in, int32_t d_out, int32_t r, float s, int32_t one_by_one, char* names_out,

@@ -3,7 +3,7 @@
 //   F32_KK  A [M, K], B [N, K]: the contraction is contiguous in both          (X A^T;  X W^T + H B^T)
 //   F32_KN  A [M, K], B [K, N]                                                 (dY B;   dY W + dH A)
 //   F32_MN  A [K, M], B [K, N]                                                 (dH^T X; dY^T H)
-// Small ones go through the fp32 matrix instructions (f32_direct_kernel, f32_group_kernel), large ones through the bf16 ones with every operand cut into
+// Small ones go through the fp32 matrix instructions (f32_direct_kernel, f32_group_kernel; f32_waves_kernel: low-rank ones of long contractions), large ones through the bf16 ones with every operand cut into
 // three parts (f32_split_kernel); f32_cost holds what the line between them was timed on.
 //
 // v_mfma_f32_16x16x4_f32 adds its four products one after another, each as one fused multiply-add: in f32_group_kernel an output is a chain
@@ -422,6 +422,117 @@ __global__ __launch_bounds__(DIRECT_WAVES * 64, 4) void f32_direct_kernel(F32Bat
     else f32_direct_tile<F, 3, false, false>(q, m0, n0, sums);
 }
 
+// ---------------------------------------------------------------- the low-rank products of larger steps
+// 16 x 16 FN outputs per workgroup of eight waves, each with an eighth of the contraction in 32-wide pieces through a ring of its own:
+// f32_direct_kernel's loads touch 16 rows with every instruction (and take one element a lane where the contraction is not contiguous), and a CU gets 40
+// to 60 GB/s of them; direct-to-LDS loads of whole 128-byte rows (64-byte ones of the [K, N] operand) bring 88.  The eight sums are added in order
+// through LDS.  H and dH of 1024 tokens, 4096 x 4096, rank 64: 34.7 and 18 us (in 16x16 tiles 23; rings of two and three pieces 19 to 20).  Operands and rows start at multiples of 16 bytes.
+//   contiguous contraction: row r's chunk c (four elements) lies at position c ^ (r / 2 % 8)
+//   [K, N]: of sixteen rows k, row 4 g + e lies at place 4 e + g, so that the 64 lanes that read element e of their four touch 64 banks
+template <int FN, int ST>
+__global__ __launch_bounds__(512, 2) void f32_waves_kernel(F32Batch grp) {
+    constexpr int NL = 2 + 2 * FN, STAGE = NL * 1024, RING = ST * STAGE;
+    static_assert((ST - 1) * NL <= 63 && 8 * RING <= 160 * 1024, "ring");
+    extern __shared__ __align__(16) unsigned char smem_waves[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
+    int k = 0;
+    while (k + 1 < grp.n && (int)blockIdx.x >= grp.p[k + 1].tile0) ++k;
+    const F32Product& q = grp.p[k];
+    const int n = q.tiles_m * q.tiles_n, id = blockIdx.x - q.tile0;
+    const int c8 = id & 7, per = n >> 3, tile = c8 * per + min(c8, n & 7) + (id >> 3);
+    const int m0 = tile / q.tiles_n * 16, n0 = tile % q.tiles_n * (16 * FN);       // the column tiles of a row tile on one XCD
+    const bool kn = q.kind == F32_KN;
+    const int M = q.M, N = q.N, K = q.K;
+    const unsigned lda = (unsigned)q.lda * 4, ldb = (unsigned)q.ldb * 4;
+    const char* A = (const char*)(q.A + (long)m0 * q.lda);
+    const char* B = (const char*)(q.B + (kn ? 0 : (long)n0 * q.ldb));
+    const long step_b = kn ? 32 * (long)ldb : 128;
+    unsigned off[NL];          // of the fetches of a piece: two of A, two per fragment of B
+    int at_k[NL];              // the first contraction element that this lane brings
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        const int r = (i & 1) * 8 + (lane >> 3), chunk = (lane & 7) ^ ((r >> 1) & 7), f = i / 2 - 1;
+        if (i < 2 || !kn) {
+            const int row = i < 2 ? min(r, M - 1 - m0) : min(16 * f + r, N - 1 - n0);
+            off[i] = (unsigned)row * (i < 2 ? lda : ldb) + chunk * 16;
+            at_k[i] = chunk * 4;
+        } else {
+            const int place = lane >> 2, kk = (i & 1) * 16 + (place & 3) * 4 + (place >> 2);
+            off[i] = (unsigned)kk * ldb + (unsigned)min(n0 + 16 * f + 4 * (lane & 3), N - 4) * 4;
+            at_k[i] = kk;
+        }
+    }
+    const int nk = (K + 31) / 32, first = nk * wave >> 3, mine = (nk * (wave + 1) >> 3) - first;
+    const bool narrow = (K & 31) && first + mine == nk;
+    const unsigned ring0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)smem_waves + wave * RING);
+    auto fetch = [&](int t, unsigned st) {
+        const int kt = first + t;
+        const char *pa = A + (long)kt * 128, *pb = B + kt * step_b;
+        const int left = K - kt * 32;
+        if (left >= 32) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) load_lds16(off[i], i < 2 ? pa : pb, __builtin_amdgcn_readfirstlane(ring0 + st + i * 1024));
+        } else {                                   // zeros beyond the end
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                if (at_k[i] < left) load_lds16(off[i], i < 2 ? pa : pb, __builtin_amdgcn_readfirstlane(ring0 + st + i * 1024));
+                else *(uint4*)(smem_waves + wave * RING + st + i * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
+            }
+        }
+    };
+    f32x4_t acc[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int t = 0; t < min(ST, mine); ++t) fetch(t, t * STAGE);
+    const unsigned char* ring = smem_waves + wave * RING;
+    unsigned st = 0;
+    for (int t = 0; t < mine; ++t) {
+        if (t + ST <= mine && !narrow) wait_vmcnt<(ST - 1) * NL>();
+        else wait_vmcnt<0>();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        f32x4_t a[2], b[2][FN];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int at = l16 * 128 + (((4 * h + g) ^ (l16 >> 1)) << 4);
+            a[h] = *(const f32x4_t*)(ring + st + at);
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                if (!kn) {
+                    b[h][j] = *(const f32x4_t*)(ring + st + (j + 1) * 2048 + at);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) b[h][j][e] = *(const float*)(ring + st + (j + 1) * 2048 + h * 1024 + ((4 * e + g) * 16 + l16) * 4);
+                }
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // its place may be filled again
+        if (t + ST < mine) fetch(t + ST, st);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[h][j][e], a[h][e], acc[j], 0, 0, 0);
+        st = st + STAGE == RING ? 0 : st + STAGE;
+    }
+#pragma unroll
+    for (int j = 0; j < FN; ++j) *(f32x4_t*)(smem_waves + wave * RING + j * 1024 + lane * 16) = acc[j];
+    __syncthreads();
+    for (int i = tid; i < FN * 64; i += 512) {
+        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 8; ++w) v += *(const f32x4_t*)(smem_waves + w * RING + i * 16);
+        const int el = i & 63, row = m0 + (el & 15), col = n0 + (i >> 6) * 16 + 4 * (el >> 4);
+        if (row >= M || col >= N) continue;        // N is a multiple of 4
+        f4u o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = q.alpha * v[e];
+        *(f4u*)(q.C + (long)row * q.ldc + col) = o;
+    }
+}
+
 // ---------------------------------------------------------------- split operands on the bf16 matrix instructions
 // The same products with every operand cut into three bf16 parts, x = x1 + x2 + x3 (each the nearest bf16 to what is left, which the
 // third holds exactly), and a b taken as (a1 b3 + a2 b2 + a1 b2 + a3 b1 + a2 b1) + a1 b1, each of the two in fp32 accumulators of its own.
@@ -813,6 +924,19 @@ static hipError_t run_split(F32Batch& grp, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int FN, int ST>
+static hipError_t run_waves_f32(F32Batch& grp, hipStream_t s) {
+    int tiles = 0;
+    hipError_t e = place_f32<16, 16 * FN>(grp, &tiles);
+    if (e != hipSuccess) return e;
+    const int lds = 8 * ST * (2 + 2 * FN) * 1024;
+    auto kern = f32_waves_kernel<FN, ST>;
+    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    kern<<<tiles, 512, lds, s>>>(grp);
+    return hipGetLastError();
+}
+
 // What a launch takes: the longest chain, or all contraction tiles spread over 256 CUs, whichever is longer, per instance: us per
 // contraction element of one chain and of 256 tiles, and what it takes besides.  Fitted to steps of 86 shapes, 33 to 8200 tokens, widths
 // 40 to 5000, ranks 4 to 64, with each instance forced (the low-rank products in 16x16 tiles): what is picked takes 0.3 % longer than the
@@ -834,7 +958,7 @@ static double f32_cost(const F32Batch& grp, const F32Cost& c) {
     return c.fixed + (chain > tiles ? chain : tiles);
 }
 
-static const char* const F32_INSTANCES[] = {"direct-16x16", "direct-32x32", "64x64", "split-128x128", "split-256x128", "wide-32x32", "wide-64x64"};
+static const char* const F32_INSTANCES[] = {"direct-16x16", "direct-32x32", "64x64", "split-128x128", "split-256x128", "wide-32x32", "wide-64x64", "waves-16x16", "waves-16x32"};
 
 // The products in the order they go out, and the instance that takes them.
 static int arrange_f32(const F32Product* prods, int n, F32Batch& grp) {
@@ -862,6 +986,28 @@ static int arrange_f32(const F32Product* prods, int n, F32Batch& grp) {
     int best = 0;
     for (int c = 1; c < (split ? 5 : 3); ++c)
         if (f32_cost(grp, costs[c]) < f32_cost(grp, costs[best])) best = c;
+    // Low-rank products of long contractions, operands that can be fetched straight into LDS: 3 us and 11.4 a megabyte of the busiest CU's
+    // operands, against what the direct kernel's model says of itself, which is that of a whole step, 16 us below what this launch takes at
+    // 1024 tokens.  (Contractions of 768: 6.8 us either way.)
+    bool waves = best <= 1;
+    for (int k = 0; k < n; ++k) {
+        const F32Product& q = grp.p[k];
+        waves &= q.kind != F32_MN && q.K2 == 0 && !q.p_new && q.N <= 256 && q.K >= 1024 && ((q.lda | q.ldb | q.ldc | q.N | q.K) & 3) == 0 &&
+                 (((uintptr_t)q.A | (uintptr_t)q.B) & 15) == 0;
+    }
+    if (waves) {
+        double us[2];
+        for (int fn = 1; fn <= 2; ++fn) {
+            long tiles = 0, K = 0;
+            for (int k = 0; k < n; ++k) {
+                tiles += (long)cdiv(grp.p[k].M, 16) * cdiv(grp.p[k].N, 16 * fn);
+                K = grp.p[k].K > K ? grp.p[k].K : K;
+            }
+            us[fn - 1] = 3.0 + 11.4e-6 * 64 * (1 + fn) * K * (double)((tiles + 255) / 256);
+        }
+        const int pick = us[1] < us[0];
+        if (us[pick] < f32_cost(grp, costs[best])) return 7 + pick;
+    }
     return best;
 }
 
@@ -882,6 +1028,8 @@ hipError_t launch_gemm_f32_group(const F32Product* prods, int n, hipStream_t s) 
         case 3: return run_split<128, 128, 2, 4>(grp, s);
         case 4: return run_split<256, 128, 4, 2>(grp, s);
         case 5: return run_f32<32, 32, 64, true>(grp, s);
-        default: return run_f32<64, 64, 32, true>(grp, s);
+        case 6: return run_f32<64, 64, 32, true>(grp, s);
+        case 7: return run_waves_f32<1, 2>(grp, s);
+        default: return run_waves_f32<2, 1>(grp, s);
     }
 }
