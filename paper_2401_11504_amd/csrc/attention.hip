@@ -1,18 +1,18 @@
 // Causal self-attention within one chunk, forward and backward, on bf16 MFMA (gfx950).
 //
-// All three kernels work on the TRANSPOSED score tile where that keeps the softmax row in one lane:
+// Forward and backward work on the TRANSPOSED score tile where that keeps the softmax row in one lane:
 //   forward / dQ :  S^T[u][t] = K[u] . Q[t]   -> a lane owns one query t (and its partner lane t too),
 //                   so the running max, the row sum, lse[t] and delta[t] are per-lane scalars;
 //                   O^T[d][t] += V^T[d][u] P^T[u][t]   and   dQ^T[d][t] += K^T[d][u] dS^T[u][t]
 //                   reuse the score fragment directly as the B operand (see tiles.h); their A operands V^T, K^T (and
 //                   dO^T, Q^T below) are never built: the tiles stay as they lie in memory and are read through the
-//                   LDS transpose read of gfx950 (load_a_tr in tiles.h), which costs no bank conflicts and no
+//                   LDS transpose read of gfx950 (read_tr_frag), which costs no bank conflicts and no
 //                   transposing stores.
 //   dK / dV      :  S[t][u] = Q[t] . K[u]     -> a lane owns one key u;
 //                   dV^T[d][u] += dO^T[d][t] P[t][u],  dK^T[d][u] += Q^T[d][t] dS[t][u].
-// P is never stored: the backward kernels rebuild it from the saved log-sum-exp.
-// The two backward kernels write disjoint outputs, so no atomics are needed and results are
-// bit-reproducible.
+// P is never stored: the backward pass rebuilds it from the saved log-sum-exp.
+// The two parts of the backward launch (dK and dV; dQ) write disjoint outputs, so no atomics are needed and results
+// are bit-reproducible.
 #include <type_traits>
 #include <utility>
 
@@ -23,60 +23,10 @@
 
 template <int DH>
 struct AttnCfg {
-    static constexpr int LSK = DH + 8;  // row stride of a [row][d] tile
     static constexpr int NKS = DH / 16; // MFMA steps over d
     static constexpr int ND = DH / 32;  // 32-wide d tiles
 };
 
-// Byte offsets, within a [64 rows][DH] tile of a matrix with row stride ld, of the 16-byte chunks this thread fetches
-// (NT = threads that share the tile).  Computed once per kernel: the loop then adds them to a wave-uniform tile
-// address, which costs no vector arithmetic per load.
-template <int DH, int NT>
-__device__ __forceinline__ void tile_chunk_offsets(long ld, unsigned* off, int tid = threadIdx.x) {
-    constexpr int CH = DH / 8;  // chunks per row
-#pragma unroll
-    for (int i = 0; i < 8 * DH / NT; ++i) {
-        const int c = tid + NT * i, row = c / CH, ch = c % CH;
-        off[i] = (unsigned)((row * ld + ch * 8) * 2);
-    }
-}
-// load the tile of rows r0 .. r0 + 63 (zero beyond T) into registers; r0 is wave-uniform, so only a ragged last tile
-// pays for per-row checks
-template <int DH, int NT>
-__device__ __forceinline__ void load_tile_regs(const bf16_t* __restrict__ base, long ld, int r0, int T, const unsigned* off,
-                                               uint4* regs, int tid = threadIdx.x) {
-    constexpr int CH = DH / 8;
-    const char* p = (const char*)(base + (long)r0 * ld);
-    if (r0 + 64 <= T) {
-#pragma unroll
-        for (int i = 0; i < 8 * DH / NT; ++i) regs[i] = *(const uint4*)(p + off[i]);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8 * DH / NT; ++i) {
-            const int row = (tid + NT * i) / CH;
-            regs[i] = (r0 + row < T) ? *(const uint4*)(p + off[i]) : make_uint4(0, 0, 0, 0);
-        }
-    }
-}
-template <int DH, int NT>
-__device__ __forceinline__ void store_tile_normal(bf16_t* tile, const uint4* regs, int tid = threadIdx.x) {
-    constexpr int CH = DH / 8;
-#pragma unroll
-    for (int i = 0; i < 8 * DH / NT; ++i) {
-        const int c = tid + NT * i, row = c / CH, ch = c % CH;
-        *(uint4*)(tile + row * AttnCfg<DH>::LSK + ch * 8) = regs[i];
-    }
-}
-// the same with row stride LD (tiles that are read with the LDS transpose read, see load_a_tr)
-template <int DH, int NT, int LD>
-__device__ __forceinline__ void store_tile_ld(bf16_t* tile, const uint4* regs, int tid = threadIdx.x) {
-    constexpr int CH = DH / 8;
-#pragma unroll
-    for (int i = 0; i < 8 * DH / NT; ++i) {
-        const int c = tid + NT * i, row = c / CH, ch = c % CH;
-        *(uint4*)(tile + row * LD + ch * 8) = regs[i];
-    }
-}
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // write a D fragment set holding X^T[d][row] (lane = row) as bf16 rows of X
@@ -93,29 +43,73 @@ __device__ __forceinline__ void write_rows_from_dT(bf16_t* __restrict__ dst, con
         }
 }
 
+// ======================================================================== tiles in LDS
+// A [rows][DH] tile by direct-to-LDS loads, one copy: 16-byte chunk c of row x lies at position c ^ attn_swz(x), so that both the reads of
+// 16 rows at one chunk and the transposing reads of four rows x 64 bytes (see load_a_tr) fall into distinct banks.
+template <int DH>
+__device__ __forceinline__ int attn_swz(int row) {
+    return DH == 128 ? 4 * (row & 3) | ((row >> 2) & 3) : 4 * ((row >> 1) & 1) | ((row >> 2) & 3);
+}
+// fetch i of a tile brings its rows i RPI .. (beyond `last`: that one again), each lane the chunk that belongs at its place; base: row 0
+template <int DH>
+struct TileFetch {
+    static constexpr int CPR = DH / 8, RPI = 64 / CPR;         // chunks per row, rows per fetch
+    int fr;
+    unsigned fc;
+    __device__ __forceinline__ TileFetch(int lane) : fr(lane / CPR), fc((unsigned)((lane % CPR) ^ attn_swz<DH>(lane / CPR)) << 4) {}
+    __device__ __forceinline__ void operator()(const bf16_t* base, unsigned ldb, int i, int last, unsigned lds) const {
+        const unsigned c = fc ^ (unsigned)((i * (RPI / 4) & 3) << 4);                  // swz of rows i RPI + fr
+        load_lds16((unsigned)min(i * RPI + fr, last) * ldb + c, base, __builtin_amdgcn_readfirstlane(lds + i * 1024));
+    }
+};
+// this lane's share of the address of a fragment of rows (row l32, chunk 2 ks + g: ^ ks << 5) ..
+template <int DH>
+__device__ __forceinline__ unsigned row_frag_at(int lane) {
+    const int l32 = lane & 31, g = lane >> 5;
+    return (unsigned)(l32 * DH * 2 + ((g ^ attn_swz<DH>(l32)) << 4));
+}
+// .. and of a transposing read (contraction rows 0 .. 15, columns 32 dt ..: ^ dt << 6; rows 8 further: ^ 32, + 8 rows)
+template <int DH>
+__device__ __forceinline__ unsigned tr_frag_at(int lane) {
+    const int G = lane >> 4, te = (lane & 15) >> 2, tq = lane & 3;
+    return (unsigned)((4 * (G >> 1) + te) * DH * 2 + ((DH == 128 ? te : te >> 1) << 6) + (((2 * (G & 1) + (tq >> 1)) ^ (G >> 1)) << 4) + ((tq & 1) << 3));
+}
+template <int DH>
+__device__ __forceinline__ bf16x8_t read_tr_frag(const unsigned char* rows, unsigned at, int dt) {
+    typedef __attribute__((address_space(3))) bf16x4v_t* lds_ptr_t;
+    at ^= (unsigned)(dt << 6);
+    const bf16x4v_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(rows + at));
+    const bf16x4v_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(rows + (at ^ 32u) + 8 * DH * 2));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 // ======================================================================== forward
 // KG key groups of NW waves each; a wave owns 32 queries, and the key tiles (64 keys) of the causal range are dealt
 // out to the key groups in turn (group kg takes tiles kg, kg + KG, ..).  Every group keeps its own running max, row
 // sum and output accumulator over its tiles and the groups are merged once at the end through LDS (the usual
 // two-state softmax merge).  With KG = 2 a SIMD runs two waves, so one wave's softmax arithmetic overlaps the other's
 // MFMAs; at T = 1024 with 32 heads there are otherwise only as many 32-query waves as the chip has SIMDs.
-// K and V tiles are fetched one tile ahead into registers (the loads fly during the MFMAs of the current tile) and
-// parked in the group's LDS buffers between two barriers.
+// K and V tiles come by direct-to-LDS loads, one tile ahead in the group's other buffer, with one barrier a tile; Q and O pass through LDS
+// too (straight from and to memory every instruction touches 32 rows).  us with tiles staged through registers (two barriers a tile, Q and
+// O by rows) and with this, heads of 128 / 64: 1024 tokens, 32 heads 28.8 and 25.9 / 16 heads 17.3 and 15.3; 2048 tokens 54.8 and 47.5 /
+// 30.8 and 28.9; 5120 tokens, 32 heads of 128 277 and 246 (870 TFLOP/s; the rest is the softmax between the two products of a tile, and at
+// 1024 tokens the heaviest block: 8 rounds of two tiles where the mean is 4.5).  The order of every sum is the same in both.
 template <int DH, int NW, int KG>
-__global__ __launch_bounds__(NW * 64 * KG) void attn_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+__global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                 const bf16_t* __restrict__ v, long ldq, int T,
                                                                 bf16_t* __restrict__ o, long ldo, float* __restrict__ lse,
                                                                 float scale_log2e) {
     using C = AttnCfg<DH>;
     constexpr int NT = NW * 64, QB = NW * 32;
-    constexpr int LDV = LTR(DH);
-    constexpr int GROUP_ELEMS = 64 * C::LSK + 64 * LDV;          // bf16 elements of one group's K and V tiles
+    constexpr int RB = DH * 2, TB = 64 * RB, NI = TB / 4096;      // bytes of a row, of a tile; fetches per wave and tile
+    static_assert(NW == 4 && KG == 2, "four waves fetch a tile; the block's queries fit one buffer");
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int kg = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
-    const int tid = threadIdx.x % NT, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, g = lane >> 5;
-    bf16_t* sK = (bf16_t*)smem_raw + kg * GROUP_ELEMS;
-    bf16_t* sV = sK + 64 * C::LSK;
-    const int tr_off = tr_lane_offset(lane, LDV);
+    const int tid = threadIdx.x % NT, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, g = lane >> 5;
+    const unsigned lds0 = (unsigned)(size_t)smem_raw;
+    const unsigned group_at = kg * 4 * TB;                        // two buffers of a K and a V tile each
+    const unsigned row_at = row_frag_at<DH>(lane), tr_at = tr_frag_at<DH>(lane);
+    const TileFetch<DH> fetch_rows(lane);
     // Heaviest (latest) query blocks first; the second half of the heads takes the mirrored block, so that two
     // workgroups placed on one CU by round-robin dispatch (ids i and i + n/2 in dispatch order, x fastest) carry the
     // same total number of key tiles whichever CU they land on.
@@ -134,12 +128,6 @@ __global__ __launch_bounds__(NW * 64 * KG) void attn_fwd_kernel(const bf16_t* __
     const bf16_t* kh = k + (long)head * DH;
     const bf16_t* vh = v + (long)head * DH;
 
-    bf16x8_t qf[C::NKS];
-#pragma unroll
-    for (int ks = 0; ks < C::NKS; ++ks) {
-        uint4 r = (t_abs < T) ? *(const uint4*)(qh + (long)t_abs * ldq + ks * 16 + g * 8) : make_uint4(0, 0, 0, 0);
-        qf[ks] = *(bf16x8_t*)&r;
-    }
     f32x16_t oacc[C::ND];
 #pragma unroll
     for (int dt = 0; dt < C::ND; ++dt) oacc[dt] = zero16();
@@ -148,28 +136,42 @@ __global__ __launch_bounds__(NW * 64 * KG) void attn_fwd_kernel(const bf16_t* __
     const int kend = min(q0 + QB, T);
     const int n_tiles = (kend + 63) / 64;
     const int n_iter = (n_tiles + KG - 1) / KG;   // a group's surplus tile lies wholly in the future and is skipped
-    uint4 rk[8 * DH / NT], rv[8 * DH / NT];
-    unsigned toff[8 * DH / NT];
-    tile_chunk_offsets<DH, NT>(ldq, toff, tid);
-    load_tile_regs<DH, NT>(kh, ldq, kg * 64, T, toff, rk, tid);
-    load_tile_regs<DH, NT>(vh, ldq, kg * 64, T, toff, rv, tid);
+    auto fetch = [&](int it) {
+        const int u0 = min((it * KG + kg) * 64, (T - 1) & ~63);   // (a surplus tile may begin behind the last key: any other instead)
+        const unsigned at = lds0 + group_at + (it & 1) * 2 * TB;
+#pragma unroll
+        for (int j = 0; j < NI; ++j) fetch_rows(kh + (long)u0 * ldq, (unsigned)ldq * 2, wave * NI + j, T - 1 - u0, at);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) fetch_rows(vh + (long)u0 * ldq, (unsigned)ldq * 2, wave * NI + j, T - 1 - u0, at + TB);
+    };
+    // the block's queries (128 rows) through the first group's second buffer
+#pragma unroll
+    for (int j = 0; j < NI; ++j) fetch_rows(qh + (long)q0 * ldq, (unsigned)ldq * 2, (kg * NW + wave) * NI + j, T - 1 - q0, lds0 + 2 * TB);
+    fetch(0);
+    wait_vmcnt<2 * NI>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    bf16x8_t qf[C::NKS];
+#pragma unroll
+    for (int ks = 0; ks < C::NKS; ++ks) qf[ks] = *(const bf16x8_t*)(smem_raw + 2 * TB + wave * 32 * RB + (row_at ^ (unsigned)(ks << 5)));
+#pragma unroll
+    for (int ks = 0; ks < C::NKS; ++ks) asm volatile("" : "+v"(qf[ks]));
     for (int it = 0; it < n_iter; ++it) {
         const int u0 = (it * KG + kg) * 64;
-        __syncthreads();
-        store_tile_normal<DH, NT>(sK, rk, tid);
-        store_tile_ld<DH, NT, LDV>(sV, rv, tid);                 // V as it lies in memory: P V reads it transposed
-        __syncthreads();
-        if (it + 1 < n_iter) {
-            load_tile_regs<DH, NT>(kh, ldq, u0 + 64 * KG, T, toff, rk, tid);
-            load_tile_regs<DH, NT>(vh, ldq, u0 + 64 * KG, T, toff, rv, tid);
-        }
+        wait_vmcnt<0>();                                          // the tile has landed,
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // the one before (and Q) has been read
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (it + 1 < n_iter) fetch(it + 1);
+        const unsigned char* sK = smem_raw + group_at + (it & 1) * 2 * TB;
+        const unsigned char* sV = sK + TB;
         if (u0 > tq0 + 31) continue;  // wave-uniform: every key of this tile is in the future
         // both 32-key halves of the tile at once: two independent MFMA chains, one softmax update
         f32x16_t s0 = zero16(), s1 = zero16();
 #pragma unroll
         for (int ks = 0; ks < C::NKS; ++ks) {
-            const bf16x8_t a0 = *(const bf16x8_t*)(sK + l32 * C::LSK + ks * 16 + g * 8);
-            const bf16x8_t a1 = *(const bf16x8_t*)(sK + (32 + l32) * C::LSK + ks * 16 + g * 8);
+            const bf16x8_t a0 = *(const bf16x8_t*)(sK + (row_at ^ (unsigned)(ks << 5)));
+            const bf16x8_t a1 = *(const bf16x8_t*)(sK + 32 * RB + (row_at ^ (unsigned)(ks << 5)));
             s0 = mfma32(a0, qf[ks], s0);
             s1 = mfma32(a1, qf[ks], s1);
         }
@@ -218,7 +220,7 @@ __global__ __launch_bounds__(NW * 64 * KG) void attn_fwd_kernel(const bf16_t* __
                 const bf16x8_t b = pack_b_from_d(x + 16 * us, h);
 #pragma unroll
                 for (int dt = 0; dt < C::ND; ++dt) {
-                    const bf16x8_t a = load_a_tr(sV, LDV, tr_off, dt * 32, us * 32 + 16 * h);
+                    const bf16x8_t a = read_tr_frag<DH>(sV + (us * 32 + 16 * h) * RB, tr_at, dt);
                     oacc[dt] = mfma32(a, b, oacc[dt]);
                 }
             }
@@ -248,10 +250,19 @@ __global__ __launch_bounds__(NW * 64 * KG) void attn_fwd_kernel(const bf16_t* __
         lpart = lpart * a0 + l1 * a1;
         m = mt;
     }
-    const float ltot = lpart + __shfl_xor(lpart, 32, 64);
-    if (t_abs < T) {
-        write_rows_from_dT<DH>(o + (long)t_abs * ldo + (long)head * DH, oacc, 1.f / ltot, g);
-        if (g == 0) lse[(long)head * T + t_abs] = (m * scale_log2e + log2f(ltot)) * 0.6931471805599453f;
+    const float ltot = lpart + __shfl_xor(lpart, 32, 64), inv = 1.f / ltot;
+    if (t_abs < T && g == 0) lse[(long)head * T + t_abs] = (m * scale_log2e + log2f(ltot)) * 0.6931471805599453f;
+    // the wave's 32 rows leave through LDS (behind what the merge reads), so that a row is written in 16-byte pieces
+    constexpr int LD = DH + 8;
+    bf16_t* slab = (bf16_t*)(smem_raw + NT * (C::ND * 16 + 2) * sizeof(float)) + wave * 32 * LD;
+    static_assert(NT * (C::ND * 16 + 2) * 4 + NT / 2 * LD * 2 <= 8 * TB, "the output slab fits");
+    write_rows_from_dT<DH>(slab + l32 * LD, oacc, inv, g);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = lane; i < 32 * DH / 8; i += 64) {
+        const int row = i / (DH / 8), c = i % (DH / 8) * 8;
+        if (tq0 + row < T) *(uint4*)(o + (long)(tq0 + row) * ldo + (long)head * DH + c) = *(const uint4*)(slab + row * LD + c);
     }
 }
 
@@ -274,10 +285,6 @@ __global__ __launch_bounds__(NW * 64 * KG) void attn_fwd_kernel(const bf16_t* __
 // 16 rows at one chunk and the transposing reads of four rows x 64 bytes fall into distinct banks.
 // us without and with this (before: waves of 32 rows, two copies of each tile, loads and stores of 32 rows at a time), heads of 128 / 64:
 // 1024 tokens, 32 heads 62 and 46 / 16 heads 39 and 18; 2048 tokens 189 and 138 / 78 and 47; 5120 tokens, 32 heads of 128 1000 and 745.
-template <int DH>
-__device__ __forceinline__ int attn_swz(int row) {
-    return DH == 128 ? 4 * (row & 3) | ((row >> 2) & 3) : 4 * ((row >> 1) & 1) | ((row >> 2) & 3);
-}
 template <class F, int... I>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
 template <int N, class F>
@@ -344,15 +351,8 @@ __device__ __forceinline__ void attn_bwd_part(
         lse2[j] = DQ ? lse_h[p] * 1.4426950408889634f : 0.f;
     }
 
-    // direct-to-LDS fetches: fetch i of a tile brings rows i RPI .. + RPI - 1 (beyond the last: that one again), this lane the chunk that
-    // belongs at its place
-    const int fr = lane / CPR;
-    const unsigned fc = (unsigned)((lane % CPR) ^ attn_swz<DH>(fr)) << 4;
+    const TileFetch<DH> fetch_rows(lane);
     const unsigned ld1b = (unsigned)ldq * 2, ldx2b = (unsigned)ldx2 * 2;
-    auto fetch_one = [&](const bf16_t* rows, unsigned ldb, int i, int last, unsigned dst) {      // rows: row 0 of the tile; last: its last valid one
-        const unsigned c = fc ^ (unsigned)((i * (RPI / 4) & 3) << 4);                            // swz of rows i RPI + fr
-        load_lds16((unsigned)min(i * RPI + fr, last) * ldb + c, rows, __builtin_amdgcn_readfirstlane(lds0 + dst + i * 1024));
-    };
     struct Fetch { const bf16_t *a, *b; const float* stats; int last; unsigned st; };
     auto fetch_of = [&](int tile, unsigned st) {
         const long r0 = (long)tile * 64;
@@ -360,8 +360,8 @@ __device__ __forceinline__ void attn_bwd_part(
     };
     // piece n of the NF a wave issues per tile (two waves each bring lse and delta, so that every wave has as many in flight)
     auto fetch_piece = [&](const Fetch& f, int n) {
-        if (n < NI) fetch_one(f.a, ld1b, wave * NI + n, f.last, f.st);
-        else if (n < 2 * NI) fetch_one(f.b, ldx2b, wave * NI + n - NI, f.last, f.st + TB);
+        if (n < NI) fetch_rows(f.a, ld1b, wave * NI + n, f.last, lds0 + f.st);
+        else if (n < 2 * NI) fetch_rows(f.b, ldx2b, wave * NI + n - NI, f.last, lds0 + f.st + TB);
         else load_lds4(lane <= f.last ? f.stats + lane : sg ? f.stats : &kLseBeyond, __builtin_amdgcn_readfirstlane(lds0 + f.st + 2 * TB + sg * 256));
     };
     auto fetch = [&](const Fetch& f) {
@@ -377,7 +377,7 @@ __device__ __forceinline__ void attn_bwd_part(
     auto fetch_block = [&](const bf16_t* x, long ld, unsigned at) {
 #pragma unroll
         for (int j = 0; j < C::PB * RB / 4096; ++j)
-            fetch_one(x + (long)p0 * ld, (unsigned)ld * 2, wave * (C::PB * RB / 4096) + j, T - 1 - p0, at);
+            fetch_rows(x + (long)p0 * ld, (unsigned)ld * 2, wave * (C::PB * RB / 4096) + j, T - 1 - p0, lds0 + at);
     };
     fetch_block(p1, ldq, P1_AT);
     fetch_block(p2, ldp2, P2_AT);
@@ -388,7 +388,7 @@ __device__ __forceinline__ void attn_bwd_part(
     fetch(fetch_of(tile_of(0), C::V0));
     fetch(fetch_of(tile_of(1), C::V0 + STAGE));
     // this lane's place in the fragments of block rows (chunk 2 ks + g of row l32 of a group)
-    const unsigned p_at = (unsigned)((pg * 32 * NG + (NG == 2 ? 32 * sg : 0) + l32) * RB + ((g ^ attn_swz<DH>(l32)) << 4));
+    const unsigned p_at = (unsigned)((pg * 32 * NG + (NG == 2 ? 32 * sg : 0)) * RB) + row_frag_at<DH>(lane);
     auto p_frag = [&](unsigned at, int j, int ks) { return *(const bf16x8_t*)(smem + at + (p_at ^ (unsigned)(ks << 5 | j * 32 * RB))); };
     wait_vmcnt<2 * NF>();
     __builtin_amdgcn_s_barrier();
@@ -426,17 +426,10 @@ __device__ __forceinline__ void attn_bwd_part(
         }
 
     // this lane's place in a fragment read of rows (chunk 2 ks + g) and in a transposing read (see load_a_tr)
-    const unsigned row_at = (unsigned)((sg * 32 + l32) * RB + ((g ^ attn_swz<DH>(l32)) << 4));
-    const int G = lane >> 4, te = (lane & 15) >> 2, tq = lane & 3;
-    const unsigned tr_at = (unsigned)((sg * 32 + 4 * (G >> 1) + te) * RB + ((DH == 128 ? te : te >> 1) << 6) +
-                                      (((2 * (G & 1) + (tq >> 1)) ^ (G >> 1)) << 4) + ((tq & 1) << 3));
+    const unsigned row_at = (unsigned)(sg * 32 * RB) + row_frag_at<DH>(lane), tr_at = (unsigned)(sg * 32 * RB) + tr_frag_at<DH>(lane);
     auto row_frag = [&](unsigned tile, int ks) { return *(const bf16x8_t*)(smem + tile + (row_at ^ (unsigned)(ks << 5))); };
     auto tr_frag = [&](unsigned tile, int i) {       // i = h ND + dt: contraction rows 16 h .., columns 32 dt ..
-        typedef __attribute__((address_space(3))) bf16x4v_t* lds_ptr_t;
-        const unsigned at = tr_at ^ (unsigned)((i % ND) << 6);
-        const bf16x4v_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(smem + tile + at + (i / ND) * 16 * RB));
-        const bf16x4v_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(smem + tile + (at ^ 32u) + ((i / ND) * 16 + 8) * RB));
-        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        return read_tr_frag<DH>(smem + tile + (i / ND) * 16 * RB, tr_at, i % ND);
     };
 
     auto compute = [&](auto masked, unsigned st, int xs0, const Fetch& next) {
@@ -709,10 +702,7 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_fused_kernel(
 template <int DH, int NW, int KG>
 static hipError_t run_fwd(dim3 grid, const bf16_t* q, const bf16_t* k, const bf16_t* v, long ldq, int T, bf16_t* o,
                           long ldo, float* lse, float sl2, hipStream_t s) {
-    using C = AttnCfg<DH>;
-    size_t lds = (size_t)KG * (64 * C::LSK + 64 * LTR(DH)) * sizeof(bf16_t);
-    const size_t merge = KG > 1 ? (size_t)NW * 64 * (C::ND * 16 + 2) * sizeof(float) : 0;
-    if (merge > lds) lds = merge;
+    const size_t lds = (size_t)KG * 4 * 64 * DH * sizeof(bf16_t);
     auto kern = attn_fwd_kernel<DH, NW, KG>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

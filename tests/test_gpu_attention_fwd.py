@@ -1,0 +1,38 @@
+"""Forward attention at the edges of its tiles, against the fp64 oracle.
+
+A block is 128 queries, a wave 32 of them; two groups of waves take the 64-key tiles in turn, and the queries come through the buffer
+that the second pair of tiles lands in.  The lengths lie on both sides of these edges: one tile (the second group has none), an odd and
+an even number, a ragged last one.  What follows row T in memory is NaN: a row read beyond the last one, and used, shows in the output."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from oracle import templora_oracle as O  # noqa: E402
+from paper_2401_11504_amd import synth  # noqa: E402
+from test_gpu_kernels import BF16_TOL, H, api, check  # noqa: E402,F401
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("T", [1, 31, 33, 63, 64, 65, 97, 127, 128, 129, 192, 193, 256, 321])
+def test_edges(api, H, T, dh):
+    nh = 3
+    d = nh * dh
+    x = synth.normal(1, (92, T, 3 * d), (T, 3 * d), 1.0, True)
+    full = np.full((T + 140, 3 * d), np.nan)
+    full[:T] = x
+    qkvd = H.to_dev_bf16(full)[:T]
+    out = torch.full((T + 140, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    lse = torch.zeros(nh, T, dtype=torch.float32, device="cuda")
+    api.tl_k_attention_fwd(*(qkvd[:, i * d:(i + 1) * d] for i in range(3)), nh, dh, out[:T], lse)
+    torch.cuda.synchronize()
+    q, k, v = (x[:, i * d:(i + 1) * d].reshape(T, nh, dh).astype(np.float64) for i in range(3))
+    ref, _ = O.attention_fwd(q, k, v)
+    got = H.bf16_to_np(out)
+    assert np.all(got[T:] == 7.0)                  # nothing is written behind the last row
+    check(got[:T], ref.reshape(T, d), BF16_TOL, "o", per_row=True)
+    S = np.einsum("thd,uhd->htu", q, k) / np.sqrt(dh)
+    S = np.where(np.triu(np.ones((T, T), bool), 1)[None], -np.inf, S)
+    ref_lse = np.logaddexp.reduce(S, axis=-1)
+    assert np.abs(lse.cpu().numpy() - ref_lse).max() < 2e-3
