@@ -43,46 +43,6 @@ __device__ __forceinline__ void write_rows_from_dT(bf16_t* __restrict__ dst, con
         }
 }
 
-// ======================================================================== tiles in LDS
-// A [rows][DH] tile by direct-to-LDS loads, one copy: 16-byte chunk c of row x lies at position c ^ attn_swz(x), so that both the reads of
-// 16 rows at one chunk and the transposing reads of four rows x 64 bytes (see load_a_tr) fall into distinct banks.
-template <int DH>
-__device__ __forceinline__ int attn_swz(int row) {
-    return DH == 128 ? 4 * (row & 3) | ((row >> 2) & 3) : 4 * ((row >> 1) & 1) | ((row >> 2) & 3);
-}
-// fetch i of a tile brings its rows i RPI .. (beyond `last`: that one again), each lane the chunk that belongs at its place; base: row 0
-template <int DH>
-struct TileFetch {
-    static constexpr int CPR = DH / 8, RPI = 64 / CPR;         // chunks per row, rows per fetch
-    int fr;
-    unsigned fc;
-    __device__ __forceinline__ TileFetch(int lane) : fr(lane / CPR), fc((unsigned)((lane % CPR) ^ attn_swz<DH>(lane / CPR)) << 4) {}
-    __device__ __forceinline__ void operator()(const bf16_t* base, unsigned ldb, int i, int last, unsigned lds) const {
-        const unsigned c = fc ^ (unsigned)((i * (RPI / 4) & 3) << 4);                  // swz of rows i RPI + fr
-        load_lds16((unsigned)min(i * RPI + fr, last) * ldb + c, base, __builtin_amdgcn_readfirstlane(lds + i * 1024));
-    }
-};
-// this lane's share of the address of a fragment of rows (row l32, chunk 2 ks + g: ^ ks << 5) ..
-template <int DH>
-__device__ __forceinline__ unsigned row_frag_at(int lane) {
-    const int l32 = lane & 31, g = lane >> 5;
-    return (unsigned)(l32 * DH * 2 + ((g ^ attn_swz<DH>(l32)) << 4));
-}
-// .. and of a transposing read (contraction rows 0 .. 15, columns 32 dt ..: ^ dt << 6; rows 8 further: ^ 32, + 8 rows)
-template <int DH>
-__device__ __forceinline__ unsigned tr_frag_at(int lane) {
-    const int G = lane >> 4, te = (lane & 15) >> 2, tq = lane & 3;
-    return (unsigned)((4 * (G >> 1) + te) * DH * 2 + ((DH == 128 ? te : te >> 1) << 6) + (((2 * (G & 1) + (tq >> 1)) ^ (G >> 1)) << 4) + ((tq & 1) << 3));
-}
-template <int DH>
-__device__ __forceinline__ bf16x8_t read_tr_frag(const unsigned char* rows, unsigned at, int dt) {
-    typedef __attribute__((address_space(3))) bf16x4v_t* lds_ptr_t;
-    at ^= (unsigned)(dt << 6);
-    const bf16x4v_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(rows + at));
-    const bf16x4v_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(rows + (at ^ 32u) + 8 * DH * 2));
-    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
-
 // ======================================================================== forward
 // KG key groups of NW waves each; a wave owns 32 queries, and the key tiles (64 keys) of the causal range are dealt
 // out to the key groups in turn (group kg takes tiles kg, kg + KG, ..).  Every group keeps its own running max, row
@@ -425,7 +385,7 @@ __device__ __forceinline__ void attn_bwd_part(
             if constexpr (!DQ) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %1, 0" : "=a"(acc2[j][dt]) : "v"(nothing));
         }
 
-    // this lane's place in a fragment read of rows (chunk 2 ks + g) and in a transposing read (see load_a_tr)
+    // this lane's place in a fragment read of rows (chunk 2 ks + g) and in a transposing read (read_tr_frag)
     const unsigned row_at = (unsigned)(sg * 32 * RB) + row_frag_at<DH>(lane), tr_at = (unsigned)(sg * 32 * RB) + tr_frag_at<DH>(lane);
     auto row_frag = [&](unsigned tile, int ks) { return *(const bf16x8_t*)(smem + tile + (row_at ^ (unsigned)(ks << 5))); };
     auto tr_frag = [&](unsigned tile, int i) {       // i = h ND + dt: contraction rows 16 h .., columns 32 dt ..

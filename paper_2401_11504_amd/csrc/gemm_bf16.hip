@@ -1052,70 +1052,61 @@ hipError_t launch_frozen(const GemmNT& g, hipStream_t s) {
 // ======================================================================== TN
 // One 64x64 output tile of P^T Q over the 64-token tiles [it0, it1).  The operand tiles stay in LDS as they lie in
 // memory, [t][i] with the token index t as rows, and the matrix unit's operands (contraction over t) come out of the
-// LDS transpose read of gfx950 (load_a_tr in tiles.h): no transposing stores, no bank conflicts.  Both operands use the
-// same slot order, so the permutation that load_a_tr applies to the 16 contraction slots of a step cancels.  Two LDS
-// buffers per operand (one barrier per token tile), the next tile's global loads issued a full tile ahead.  Thread
-// (tp, ic) moves rows t = 2tp, 2tp+1 and the 8 columns i = 8ic..8ic+7.  Returns this wave's 32x32 accumulator.
+// LDS transpose read (read_tr_frag in tiles.h): no transposing stores, no bank conflicts.  Both operands use the
+// same slot order, so the permutation of the 16 contraction slots of a step cancels.  Returns this wave's 32x32 accumulator.
+// What bounds it: four MFMAs a wave and tile are a tenth of the time a tile takes to arrive, so it is the bytes in flight and, with many
+// tokens, memory: a ring of TN_ST tiles of both operands by direct-to-LDS loads, TN_ST - 1 of them on their way, one barrier a tile.
+// us of a layer's launch with one tile ahead in registers and with this: 1024 tokens of width 1024 (260 tiles) 17.6 and 11.6, 200 tokens
+// (65 tiles) 8.9 and 7.0; 7B shapes (1220 tiles), 5120 tokens 235 and 211 (3.8 TB/s of operands), 1536 tokens 62 and 60.  Three tiles (and
+// three workgroups on a CU) or a contiguous range of the tiles on each XCD measure the same within 3 %.
+constexpr int TN_ST = 4, TN_TILE = 64 * 128, TN_STAGE = 2 * TN_TILE;     // bytes of a tile, of P's and Q's
 __device__ __forceinline__ f32x16_t tn_tile(const bf16_t* P, long ldp, int Mo, const bf16_t* Q, long ldq, int No, int T,
                                             int i0, int j0, int it0, int it1) {
-    constexpr int LD = LTR(64);
-    __shared__ __align__(16) bf16_t sP[2][64 * LD];
-    __shared__ __align__(16) bf16_t sQ[2][64 * LD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wi = wave >> 1, wj = wave & 1;
-    const int tp = tid >> 3, ic = tid & 7;
-    const int tr_off = tr_lane_offset(lane, LD);
-    f32x16_t acc = zero16();
-    // byte offsets of this thread's two rows within a 64-token tile, computed once; a tile's address is wave-uniform,
-    // and only a ragged last tile (or a ragged last column block) pays for per-element bounds checks
-    const unsigned po = (unsigned)((2 * tp * ldp + i0 + ic * 8) * 2), qo = (unsigned)((2 * tp * ldq + j0 + ic * 8) * 2);
-    const unsigned pstep = (unsigned)(ldp * 2), qstep = (unsigned)(ldq * 2);
-    const bool pc = i0 + ic * 8 < Mo, qc = j0 + ic * 8 < No;
-    const bool cols_full = i0 + 64 <= Mo && j0 + 64 <= No;
-    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));   // a plain vector value: stays in registers on every path
-    u32x4 p0, p1, q0, q1;
-    auto gload = [&](int it) {
-        const char* pb = (const char*)(P + (long)it * 64 * ldp);
-        const char* qb = (const char*)(Q + (long)it * 64 * ldq);
-        if (cols_full && it * 64 + 64 <= T) {
-            p0 = *(const u32x4*)(pb + po); p1 = *(const u32x4*)(pb + po + pstep);
-            q0 = *(const u32x4*)(qb + qo); q1 = *(const u32x4*)(qb + qo + qstep);
-        } else {
-            const int t = it * 64 + 2 * tp;
-            const u32x4 z = {0u, 0u, 0u, 0u};
-            p0 = z; p1 = z; q0 = z; q1 = z;
-            if (t < T && pc) p0 = *(const u32x4*)(pb + po);
-            if (t + 1 < T && pc) p1 = *(const u32x4*)(pb + po + pstep);
-            if (t < T && qc) q0 = *(const u32x4*)(qb + qo);
-            if (t + 1 < T && qc) q1 = *(const u32x4*)(qb + qo + qstep);
+    __shared__ __align__(16) unsigned char ring[TN_ST * TN_STAGE];
+    const unsigned lds0 = (unsigned)(size_t)ring;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wi = wave >> 1, wj = wave & 1;
+    const unsigned tr_at = tr_frag_at<64>(lane);
+    // a wave brings rows 8 wave .. and 32 further of both tiles (fetches wave and wave + 4), each lane the chunk that belongs at its place;
+    // a chunk behind the last column is that one again (its products are columns or rows that nobody stores), a row behind the last token
+    // that one again, cleared below
+    const int fr = 8 * wave + (lane >> 3), fc = (lane & 7) ^ tile_swz<64>(fr);
+    const unsigned pc = (unsigned)min(i0 + fc * 8, Mo - 8) * 2, qc = (unsigned)min(j0 + fc * 8, No - 8) * 2;
+    auto fetch = [&](int it) {
+        const bf16_t *pb = P + (long)it * 64 * ldp, *qb = Q + (long)it * 64 * ldq;
+        const unsigned st = lds0 + (unsigned)((it - it0) % TN_ST * TN_STAGE) + wave * 1024;
+        const int last = T - 1 - it * 64;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const unsigned row = (unsigned)min(fr + 32 * h, last);
+            load_lds16(row * (unsigned)(ldp * 2) + pc, pb, __builtin_amdgcn_readfirstlane(st + h * 4096));
+            load_lds16(row * (unsigned)(ldq * 2) + qc, qb, __builtin_amdgcn_readfirstlane(st + TN_TILE + h * 4096));
         }
     };
-    auto park = [&](int buf) {
-        *(u32x4*)(sP[buf] + (2 * tp) * LD + ic * 8) = p0;
-        *(u32x4*)(sP[buf] + (2 * tp + 1) * LD + ic * 8) = p1;
-        *(u32x4*)(sQ[buf] + (2 * tp) * LD + ic * 8) = q0;
-        *(u32x4*)(sQ[buf] + (2 * tp + 1) * LD + ic * 8) = q1;
-    };
-    if (it0 < it1) {
-        gload(it0);
-        park(0);
-        if (it0 + 1 < it1) gload(it0 + 1);
-    }
-    __syncthreads();
+    f32x16_t acc = zero16();
+#pragma unroll
+    for (int i = 0; i < TN_ST - 1; ++i)
+        if (it0 + i < it1) fetch(it0 + i);
     for (int it = it0; it < it1; ++it) {
-        const int buf = (it - it0) & 1;
-        // registers hold tile it+1: park it in the other buffer, then fetch tile it+2
-        if (it + 1 < it1) {
-            park(buf ^ 1);
-            if (it + 2 < it1) gload(it + 2);
+        if (it + TN_ST - 2 < it1) wait_vmcnt<4 * (TN_ST - 2)>();     // this tile has landed (the last ones: all have),
+        else wait_vmcnt<0>();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // the one before has been read
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (it + TN_ST - 1 < it1) fetch(it + TN_ST - 1);
+        unsigned char* st = ring + (it - it0) % TN_ST * TN_STAGE;
+        if (it * 64 + 64 > T) {                                      // a ragged last tile: rows behind the last token are zero
+            for (int c = (T - it * 64) * 8 + (int)threadIdx.x; c < 64 * 8; c += 256) {
+                *(uint4*)(st + c * 16) = make_uint4(0, 0, 0, 0);
+                *(uint4*)(st + TN_TILE + c * 16) = make_uint4(0, 0, 0, 0);
+            }
+            __syncthreads();
         }
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-            const bf16x8_t a = load_a_tr(sP[buf], LD, tr_off, wi * 32, ks * 16);
-            const bf16x8_t b = load_a_tr(sQ[buf], LD, tr_off, wj * 32, ks * 16);
+            const bf16x8_t a = read_tr_frag<64>(st + ks * 16 * 128, tr_at, wi);
+            const bf16x8_t b = read_tr_frag<64>(st + TN_TILE + ks * 16 * 128, tr_at, wj);
             acc = mfma32(a, b, acc);
         }
-        __syncthreads();
     }
     return acc;
 }

@@ -605,7 +605,7 @@ struct SplitOperand {
     static __device__ __forceinline__ bf16x8_t fragment(const bf16_t* at, int i) {
         if constexpr (KC) {
             return *(const bf16x8_t*)(at + 16 * i * LD);
-        } else {          // (lane q + 4 e of a group of sixteen points at element e, rows 4 q .. 4 q + 3: see load_a_tr in tiles.h)
+        } else {          // (lane q + 4 e of a group of sixteen points at element e, rows 4 q .. 4 q + 3: see tr_frag_at in tiles.h)
             typedef __attribute__((address_space(3))) bf16x4v_t* lds_ptr_t;
             const bf16x4v_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(at + 16 * i));
             const bf16x4v_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(at + 16 * i + 16 * LD));

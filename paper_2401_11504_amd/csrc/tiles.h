@@ -7,7 +7,7 @@
 // Because the contraction is a sum, any permutation of the 16 slots is allowed as long as A and B
 // use the same one.  A D fragment reused as a B operand (keeping j) supplies, for registers
 // v = 8h .. 8h+7, the slot order  i = 16h + {4g..4g+3, 8+4g..8+4g+3}; the A operand is then read
-// as two 4-slot pieces at i = 16h+4g and 16h+8+4g (load_a_tr below).
+// as two 4-slot pieces at i = 16h+4g and 16h+8+4g (read_tr_frag below).
 #pragma once
 #include "common.h"
 
@@ -23,32 +23,6 @@ __device__ __forceinline__ f32x16_t zero16() {
 #pragma unroll
     for (int v = 0; v < 16; ++v) z[v] = 0.f;
     return z;
-}
-
-// A operand for a D-fragment-as-B product (contraction slots 16h + {4g..4g+3, 8+4g..8+4g+3}, see the top of this
-// file) taken from the tile as it lies in memory, [k][n] row-major with n contiguous, by the LDS transpose read of
-// gfx950 (ds_read_b64_tr_b16): within each group of 16 lanes, lane 4q + c receives element c of the four 8-byte rows
-// that lanes q, q + 4, q + 8, q + 12 of the group point at.  Lane q + 4e therefore points at row k0 + e, columns
-// n0 + 4q .. 4q + 3, and lane 4q + c ends up with column n0 + 4q + c of rows k0 .. k0 + 3: four consecutive contraction
-// slots of one operand row, which is what the matrix unit wants.  Lane groups 0 / 1 cover columns n0 .. 15 /
-// n0 + 16 .. 31 (l32), groups 2 / 3 the same columns for g = 1.  Used for both operands of a product, the slot
-// permutation cancels, so the same read serves ordinary P^T Q products (gemm_tn).
-// tr_lane_offset: the lane's share of the address, (4 g + e) * ld + 16 (G & 1) + 4 q, in elements.
-#define LTR(DH) ((DH) + 32)  // row stride of a tile read this way: 4 consecutive rows x 64 bytes fall into 4 distinct bank ranges
-__device__ __forceinline__ int tr_lane_offset(int lane, int ld) {
-    const int G = lane >> 4, s = lane & 15, q = s & 3, e = s >> 2;
-    return (4 * (G >> 1) + e) * ld + 16 * (G & 1) + 4 * q;
-}
-typedef __bf16 bf16x4v_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ bf16x8_t load_a_tr(const bf16_t* tile, int ld, int lane_off, int n0, int k16) {
-    typedef __attribute__((address_space(3))) bf16x4v_t* lds_ptr_t;
-    const bf16_t* p = tile + lane_off + k16 * ld + n0;
-    const bf16x4v_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(p));
-    const bf16x4v_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(p + 8 * ld));
-    bf16x8_t a;
-    a[0] = lo[0]; a[1] = lo[1]; a[2] = lo[2]; a[3] = lo[3];
-    a[4] = hi[0]; a[5] = hi[1]; a[6] = hi[2]; a[7] = hi[3];
-    return a;
 }
 
 // registers v = 8h .. 8h+7 of a D fragment, rounded to bf16, as a B operand
@@ -70,4 +44,52 @@ __device__ __forceinline__ void load_lds4(const void* p, unsigned lds_addr) {
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// A [rows][DH] tile by direct-to-LDS loads, one copy: 16-byte chunk c of row x lies at position c ^ tile_swz(x), so that both the reads of
+// 16 rows at one chunk and the transposing reads of four rows x 64 bytes (read_tr_frag) fall into distinct banks.
+template <int DH>
+__device__ __forceinline__ int tile_swz(int row) {
+    return DH == 128 ? 4 * (row & 3) | ((row >> 2) & 3) : 4 * ((row >> 1) & 1) | ((row >> 2) & 3);
+}
+// fetch i of a tile brings its rows i RPI .. (beyond `last`: that one again), each lane the chunk that belongs at its place; base: row 0
+template <int DH>
+struct TileFetch {
+    static constexpr int CPR = DH / 8, RPI = 64 / CPR;         // chunks per row, rows per fetch
+    int fr;
+    unsigned fc;
+    __device__ __forceinline__ TileFetch(int lane) : fr(lane / CPR), fc((unsigned)((lane % CPR) ^ tile_swz<DH>(lane / CPR)) << 4) {}
+    __device__ __forceinline__ void operator()(const bf16_t* base, unsigned ldb, int i, int last, unsigned lds) const {
+        const unsigned c = fc ^ (unsigned)((i * (RPI / 4) & 3) << 4);                  // swz of rows i RPI + fr
+        load_lds16((unsigned)min(i * RPI + fr, last) * ldb + c, base, __builtin_amdgcn_readfirstlane(lds + i * 1024));
+    }
+};
+// this lane's share of the address of a fragment of rows (row l32, chunk 2 ks + g: ^ ks << 5) ..
+template <int DH>
+__device__ __forceinline__ unsigned row_frag_at(int lane) {
+    const int l32 = lane & 31, g = lane >> 5;
+    return (unsigned)(l32 * DH * 2 + ((g ^ tile_swz<DH>(l32)) << 4));
+}
+// .. and of a transposing read (contraction rows 0 .. 15, columns 32 dt ..: ^ dt << 6; rows 8 further: ^ 32, + 8 rows).
+// A operand for a D-fragment-as-B product (contraction slots 16h + {4g..4g+3, 8+4g..8+4g+3}, see the top of this
+// file) taken from the tile as it lies in memory, [k][n] row-major with n contiguous, by the LDS transpose read of
+// gfx950 (ds_read_b64_tr_b16): within each group of 16 lanes, lane 4q + c receives element c of the four 8-byte rows
+// that lanes q, q + 4, q + 8, q + 12 of the group point at.  Lane q + 4e therefore points at row k0 + e, columns
+// n0 + 4q .. 4q + 3, and lane 4q + c ends up with column n0 + 4q + c of rows k0 .. k0 + 3: four consecutive contraction
+// slots of one operand row, which is what the matrix unit wants.  Lane groups 0 / 1 cover columns n0 .. 15 /
+// n0 + 16 .. 31 (l32), groups 2 / 3 the same columns for g = 1.  Used for both operands of a product, the slot
+// permutation cancels, so the same read serves ordinary P^T Q products (tn_tile).
+template <int DH>
+__device__ __forceinline__ unsigned tr_frag_at(int lane) {
+    const int G = lane >> 4, te = (lane & 15) >> 2, tq = lane & 3;
+    return (unsigned)((4 * (G >> 1) + te) * DH * 2 + ((DH == 128 ? te : te >> 1) << 6) + (((2 * (G & 1) + (tq >> 1)) ^ (G >> 1)) << 4) + ((tq & 1) << 3));
+}
+typedef __bf16 bf16x4v_t __attribute__((ext_vector_type(4)));
+template <int DH>
+__device__ __forceinline__ bf16x8_t read_tr_frag(const unsigned char* rows, unsigned at, int dt) {
+    typedef __attribute__((address_space(3))) bf16x4v_t* lds_ptr_t;
+    at ^= (unsigned)(dt << 6);
+    const bf16x4v_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(rows + at));
+    const bf16x4v_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(rows + (at ^ 32u) + 8 * DH * 2));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
