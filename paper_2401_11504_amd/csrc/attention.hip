@@ -51,7 +51,7 @@ __device__ __forceinline__ void write_rows_from_dT(bf16_t* __restrict__ dst, con
 // MFMAs; at T = 1024 with 32 heads there are otherwise only as many 32-query waves as the chip has SIMDs.
 // K and V tiles come by direct-to-LDS loads, one tile ahead in the group's other buffer, with one barrier a tile; Q and O pass through LDS
 // too (straight from and to memory every instruction touches 32 rows).  us with tiles staged through registers (two barriers a tile, Q and
-// O by rows) and with this, heads of 128 / 64: 1024 tokens, 32 heads 28.8 and 25.9 / 16 heads 17.3 and 15.3; 2048 tokens 54.8 and 47.5 /
+// O by rows) and with this, heads of 128 / 64: 1024 tokens, 32 heads 28.8 and 25.4 / 16 heads 17.3 and 15.3; 2048 tokens 54.8 and 47.5 /
 // 30.8 and 28.9; 5120 tokens, 32 heads of 128 277 and 246 (870 TFLOP/s; the rest is the softmax between the two products of a tile, and at
 // 1024 tokens the heaviest block: 8 rounds of two tiles where the mean is 4.5).  The order of every sum is the same in both.
 template <int DH, int NW, int KG>
@@ -70,19 +70,12 @@ __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t*
     const unsigned group_at = kg * 4 * TB;                        // two buffers of a K and a V tile each
     const unsigned row_at = row_frag_at<DH>(lane), tr_at = tr_frag_at<DH>(lane);
     const TileFetch<DH> fetch_rows(lane);
-    // Heaviest (latest) query blocks first; the second half of the heads takes the mirrored block, so that two
-    // workgroups placed on one CU by round-robin dispatch (ids i and i + n/2 in dispatch order, x fastest) carry the
-    // same total number of key tiles whichever CU they land on.
-    // With more workgroups than CUs (several rounds) the order of dispatch decides the tail instead: every head's
-    // heaviest block first, then every head's second heaviest, and so on (longest job first).
-    const bool mirror = 2 * blockIdx.y >= gridDim.y + 1;
-    int qb = mirror ? (int)blockIdx.x : (int)(gridDim.x - 1 - blockIdx.x);
-    int head = blockIdx.y;
-    if (gridDim.x * gridDim.y > 256) {
-        const int idx = blockIdx.y * gridDim.x + blockIdx.x;   // position in dispatch order (x fastest)
-        qb = (int)gridDim.x - 1 - idx / (int)gridDim.y;
-        head = idx % (int)gridDim.y;
-    }
+    // Heaviest (latest) query blocks first, every head's before any head's second heaviest (longest job first).  The blocks of a head are
+    // gridDim.y workgroups apart in dispatch order (x fastest), so with a multiple of eight heads they lie on one XCD, whose L2 fetches the
+    // head's keys and values once; with a head's blocks side by side all eight XCDs fetch them (1024 tokens, 32 heads of 128:
+    // 25 MB fetched and 22.8 us, 84 MB and 25.4).
+    const int idx = blockIdx.y * gridDim.x + blockIdx.x;
+    const int qb = (int)gridDim.x - 1 - idx / (int)gridDim.y, head = idx % (int)gridDim.y;
     const int q0 = qb * QB, tq0 = q0 + 32 * wave, t_abs = tq0 + l32;
     const bf16_t* qh = q + (long)head * DH;
     const bf16_t* kh = k + (long)head * DH;
