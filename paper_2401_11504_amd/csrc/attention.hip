@@ -53,7 +53,7 @@ __device__ __forceinline__ void write_rows_from_dT(bf16_t* __restrict__ dst, con
 // too (straight from and to memory every instruction touches 32 rows).  us with tiles staged through registers (two barriers a tile, Q and
 // O by rows) and with this, heads of 128 / 64: 1024 tokens, 32 heads 28.8 and 25.4 / 16 heads 17.3 and 15.3; 2048 tokens 54.8 and 47.5 /
 // 30.8 and 28.9; 5120 tokens, 32 heads of 128 277 and 246 (870 TFLOP/s; the rest is the softmax between the two products of a tile, and at
-// 1024 tokens the heaviest block: 8 rounds of two tiles where the mean is 4.5).  The order of every sum is the same in both.
+// 1024 tokens the heaviest block: 8 passes of two tiles where the mean is 4.5).  The order of every sum is the same in both.
 template <int DH, int NW, int KG>
 __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                 const bf16_t* __restrict__ v, long ldq, int T,
