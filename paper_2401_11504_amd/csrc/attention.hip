@@ -641,16 +641,11 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_fused_kernel(
 }
 
 // ======================================================================== launchers
-// waves per workgroup (32 queries / keys each), fixed at build time.  Measured at T = 1024, 32 heads of 128:
+// waves per key group of the forward kernel (32 queries each).  Measured at T = 1024, 32 heads of 128:
 // 4 waves beat 2 (a K/V tile is shared by more queries; the extra workgroups of 2 do not overlap enough).
-#ifndef ATTN_NW
-#define ATTN_NW 4
-#endif
-
-// key groups of the forward kernel (see attn_fwd_kernel)
-#ifndef ATTN_KG
-#define ATTN_KG 2
-#endif
+constexpr int ATTN_NW = 4;
+// its key groups (see attn_fwd_kernel)
+constexpr int ATTN_KG = 2;
 
 template <int DH, int NW, int KG>
 static hipError_t run_fwd(dim3 grid, const bf16_t* q, const bf16_t* k, const bf16_t* v, long ldq, int T, bf16_t* o,

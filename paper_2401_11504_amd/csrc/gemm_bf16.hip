@@ -3,11 +3,11 @@
 //  gemm_nt : C = alpha (A B^T + A2 B2^T) (+ R)      both operand pairs are K-contiguous.
 //            Forward:  Y  = X W^T  + Hs B^T           (A2 = Hs = s X A^T, K2 = r)
 //            Backward: dX = dY Wt^T + dH At^T          (Wt, At = transposed copies, K2 = r)
-//            Low-rank: Hs = s X A^T, dH = s dY Bt^T    (N = r, split over K)
+//            Low-rank: Hs = s X A^T, dH = s dY Bt^T    (N = r: mostly nt_waves_kernel)
 //            The low-rank term rides along as extra K tiles of the same accumulator, so the
 //            frozen product and the LoRA correction are one pass over the output.
 //  gemm_tn : C = alpha P^T Q, contraction over the token dimension (dA = dH^T X, dB = dY^T Hs),
-//            fp32 output.  Operand tiles are transposed on their way into LDS.
+//            fp32 output.  Operand tiles lie in LDS as in memory and are read transposed.
 //
 // LDS tiles hold 64 contraction elements per row, padded to 72 so that the 16-byte fragment
 // reads of 8 consecutive rows fall into distinct banks.
