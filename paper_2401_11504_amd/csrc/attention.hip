@@ -112,6 +112,7 @@ __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t*
     for (int it = 0; it < n_iter; ++it) {
         const int u0 = (it * KG + kg) * 64;
         wait_vmcnt<0>();                                          // the tile has landed,
+        if (u0 + 64 > T) clear_rows<DH>(smem_raw + group_at + (it & 1) * 2 * TB + TB, max(16 * wave, T - u0), 16 * wave + 16, lane);     // (V: P is 0 there)
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // the one before (and Q) has been read
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -243,7 +244,7 @@ __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int
 template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
-__device__ const float kLseBeyond = 1.0e30f;      // log-sum-exp of a row that does not exist: every probability is 0
+__device__ const float kBeyond[2] = {1.0e30f, 0.f};       // log-sum-exp and delta of a query that does not exist: every probability is 0
 
 template <int DH> struct BwdCfg {
     static constexpr int NG = DH / 64;                     // 32-row groups per wave
@@ -315,7 +316,7 @@ __device__ __forceinline__ void attn_bwd_part(
     auto fetch_piece = [&](const Fetch& f, int n) {
         if (n < NI) fetch_rows(f.a, ld1b, wave * NI + n, f.last, lds0 + f.st);
         else if (n < 2 * NI) fetch_rows(f.b, ldx2b, wave * NI + n - NI, f.last, lds0 + f.st + TB);
-        else load_lds4(lane <= f.last ? f.stats + lane : sg ? f.stats : &kLseBeyond, __builtin_amdgcn_readfirstlane(lds0 + f.st + 2 * TB + sg * 256));
+        else load_lds4(lane <= f.last ? f.stats + lane : kBeyond + sg, __builtin_amdgcn_readfirstlane(lds0 + f.st + 2 * TB + sg * 256));
     };
     auto fetch = [&](const Fetch& f) {
 #pragma unroll
@@ -501,6 +502,9 @@ __device__ __forceinline__ void attn_bwd_part(
     auto step = [&](auto what) {           // 0: nothing to do for this wave, 1: every score counts, 2: with the causal mask
         constexpr int WHAT = decltype(what)::value;
         wait_vmcnt<NF>();                                                  // this tile has landed (the next may be in flight)
+        if constexpr (!DQ) {                                               // (the last tile is the first; dO: P is 0 there)
+            if (i_step == 0 && tile1 * 64 > T) clear_rows<DH>(smem + st + TB, max(16 * wave, T - (tile1 - 1) * 64), 16 * wave + 16, lane);
+        }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                 // and every read of the one before is done
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");

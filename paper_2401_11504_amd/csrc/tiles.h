@@ -64,6 +64,12 @@ struct TileFetch {
         load_lds16((unsigned)min(i * RPI + fr, last) * ldb + c, base, __builtin_amdgcn_readfirstlane(lds + i * 1024));
     }
 };
+// rows first .. end - 1 of such a tile made zero by one wave.  Fetches bring the last row again in the place of rows behind it; where the products
+// take those with weights of 0, an infinity in the last row would turn into 0 x inf.
+template <int DH>
+__device__ __forceinline__ void clear_rows(unsigned char* tile, int first, int end, int lane) {
+    for (int at = first * DH * 2 + lane * 16; at < end * DH * 2; at += 1024) *(uint4*)(tile + at) = make_uint4(0, 0, 0, 0);
+}
 // this lane's share of the address of a fragment of rows (row l32, chunk 2 ks + g: ^ ks << 5) ..
 template <int DH>
 __device__ __forceinline__ unsigned row_frag_at(int lane) {

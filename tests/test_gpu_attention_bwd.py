@@ -43,3 +43,37 @@ def test_edges(api, H, T, dh):
     assert np.all(g[T:] == 7.0)                    # nothing is written behind the last row
     for i, name in enumerate(("dq", "dk", "dv")):
         check(g[:T, i * d:(i + 1) * d], refs[i].reshape(T, d), BF16_TOL, name, per_row=True)
+
+
+def gradients(api, H, T, dh, do_edit):
+    q, k, v, do = (H.to_dev_bf16(synth.normal(i, (95, T, dh), (T, dh), 1.0, True)) for i in range(4))
+    o, dq, dk, dv = (torch.zeros(T, dh, dtype=torch.bfloat16, device="cuda") for _ in range(4))
+    lse, delta = (torch.zeros(1, T, dtype=torch.float32, device="cuda") for _ in range(2))
+    do_edit(do)
+    api.tl_k_attention_fwd(q, k, v, 1, dh, o, lse)
+    api.tl_k_attention_bwd(q, k, v, o, do, lse, 1, dh, dq, dk, dv, delta)
+    torch.cuda.synchronize()
+    return dq, dk, dv
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("T", [1, 33, 100, 193])
+def test_infinity_in_the_last_row(api, H, T, dh):
+    """One value of the last token's dO is infinite: so is that column of dV for every key, all of which the last token sees, and no other."""
+    def edit(do):
+        do[-1, 5] = float("inf")
+    dv0, dv1 = (gradients(api, H, T, dh, e)[2] for e in (lambda do: None, edit))
+    assert torch.all(dv1[:, 5] == float("inf"))
+    others = torch.arange(dh, device="cuda") != 5
+    assert torch.equal(dv0[:, others], dv1[:, others])
+
+
+@pytest.mark.parametrize("T,dh", [(100, 64)])
+def test_no_number_in_the_first_row_of_a_tile(api, H, T, dh):
+    """Keys from 96 on follow token 64 by more than the 32 rows of a piece: what is not a number there stays away from them, also by way of
+    the rows that fill a ragged tile up behind the last."""
+    def edit(do):
+        do[64] = float("nan")
+    plain, edited = gradients(api, H, T, dh, lambda do: None), gradients(api, H, T, dh, edit)
+    for a, b in zip(plain, edited):
+        assert torch.equal(a[96:], b[96:])

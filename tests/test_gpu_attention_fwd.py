@@ -36,3 +36,20 @@ def test_edges(api, H, T, dh):
     S = np.where(np.triu(np.ones((T, T), bool), 1)[None], -np.inf, S)
     ref_lse = np.logaddexp.reduce(S, axis=-1)
     assert np.abs(lse.cpu().numpy() - ref_lse).max() < 2e-3
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("T", [1, 33, 100, 193])
+def test_infinity_in_the_last_row(api, H, T, dh):
+    """One value of the last token is infinite: so is the output that it has a weight in, and no other output of that row changes.  (Rows that fill a
+    tile up behind the last have weights of 0, and 0 x inf is no number.)"""
+    q, k, v = (H.to_dev_bf16(synth.normal(i, (94, T, dh), (T, dh), 1.0, True)) for i in range(3))
+    lse = torch.zeros(1, T, dtype=torch.float32, device="cuda")
+    out = [torch.zeros(T, dh, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    api.tl_k_attention_fwd(q, k, v, 1, dh, out[0], lse)
+    v[-1, 5] = float("inf")
+    api.tl_k_attention_fwd(q, k, v, 1, dh, out[1], lse)
+    torch.cuda.synchronize()
+    assert out[1][-1, 5] == float("inf")
+    others = torch.arange(dh, device="cuda") != 5
+    assert torch.equal(out[0][:, others], out[1][:, others])
