@@ -276,7 +276,7 @@ __device__ __forceinline__ void attn_bwd_part(
     unsigned char* smem) {
     using C = BwdCfg<DH>;
     constexpr int NG = C::NG, KS = DH / 16, ND = DH / 32, RB = C::RB, TB = C::TB, STAGE = C::STAGE, NST = C::NST;
-    constexpr int NI = TB / 4096, RPI = 1024 / RB, CPR = RB / 16;      // fetches per wave and tile; rows per fetch; chunks per row
+    constexpr int NI = TB / 4096;                                      // fetches per wave and tile
     constexpr int NF = 2 * NI + (DQ ? 0 : 1);                          // fetches per wave and stage
     constexpr bool V_LDS = !DQ && NG == 2;
     static_assert(KS == 2 * ND, "as many MFMAs for each product");
@@ -386,12 +386,15 @@ __device__ __forceinline__ void attn_bwd_part(
         return read_tr_frag<DH>(smem + tile + (i / ND) * 16 * RB, tr_at, i % ND);
     };
 
-    auto compute = [&](auto masked, unsigned st, int xs0, const Fetch& next) {
+    // J: groups of rows that take part (the others keep what they have: not even a weight of 0 meets a row that does not belong to them)
+    auto compute = [&](auto masked, auto groups, unsigned st, int xs0, const Fetch& next) {
         constexpr bool MASK = decltype(masked)::value;
+        constexpr int J = decltype(groups)::value;
         // One fragment of X and NG MFMAs a slot, KS slots each of S, dP, dV and dK (of S, dP and dQ).  Fragments are asked for AHEAD slots
         // before they are used, and the vector work on the scores, in items of four values a lane, goes between the MFMAs behind them.
         constexpr int B0 = KS, C0 = 2 * KS, NS = (DQ ? 3 : 4) * KS, D0 = NS - KS;
         constexpr int AHEAD = 4, AHEAD_V = 3;
+        static_assert(J == NG || !DQ, "only key blocks leave a group out");
         f32x16_t s[NG], dp[NG];
         bf16x8_t pb[NG][2], dsb[NG][2], fx[NS], fv[NG][KS];
         float4 l4[4], d4[4];
@@ -403,14 +406,14 @@ __device__ __forceinline__ void attn_bwd_part(
                 fx[i] = row_frag(t2, n);
                 if constexpr (V_LDS) {
 #pragma unroll
-                    for (int j = 0; j < NG; ++j) fv[j][n] = p_frag(P2_AT, j, n);
+                    for (int j = 0; j < J; ++j) fv[j][n] = p_frag(P2_AT, j, n);
                 }
             } else fx[i] = tr_frag(i >= D0 ? t1 : t2, n);
         };
         auto mfma = [&](auto slot) {
             constexpr int i = decltype(slot)::value, n = i % KS;
 #pragma unroll
-            for (int j = 0; j < NG; ++j) {
+            for (int j = 0; j < J; ++j) {
                 if constexpr (i < B0) mfma32_score<n == 0>(s[j], fx[i], p1f[j][n]);
                 else if constexpr (i < C0) mfma32_score<n == 0>(dp[j], fx[i], V_LDS ? fv[j][n] : p2f[V_LDS ? 0 : j][V_LDS ? 0 : n]);
                 else if constexpr (i >= D0) mfma32_acc(acc1[j][n % ND], fx[i], dsb[j][n / ND]);
@@ -445,9 +448,9 @@ __device__ __forceinline__ void attn_bwd_part(
         auto ready = [&](f32x16_t* x, auto wait) {
             if constexpr (decltype(wait)::value) asm volatile("s_nop 15\n\ts_nop 3");
 #pragma unroll
-            for (int j = 0; j < NG; ++j) asm volatile("" : "+v"(x[j]));
+            for (int j = 0; j < J; ++j) asm volatile("" : "+v"(x[j]));
         };
-        using Wait = std::true_type; using SlotWait = std::bool_constant<NG == 1>;
+        using Wait = std::true_type; using SlotWait = std::bool_constant<J == 1>;
         // item n: group n % NG, rows 8 (n / NG) ..; dV needs the first half of the probabilities KS / 2 slots before the second
         constexpr int NI_P = 4 * NG;
         auto p_item = [](int i) -> int {           // the item of probabilities behind the MFMAs of slot i
@@ -477,8 +480,8 @@ __device__ __forceinline__ void attn_bwd_part(
             mfma(slot);
             if constexpr (i == B0) ready(s, SlotWait{});
             if constexpr (i == C0 && !DQ) ready(dp, SlotWait{});
-            if (p_item(i) >= 0) probs(p_item(i) % NG, p_item(i) / NG);
-            if (d_item(i) >= 0) dscores(d_item(i) % NG, d_item(i) / NG);
+            if (p_item(i) >= 0 && p_item(i) % NG < J) probs(p_item(i) % NG, p_item(i) / NG);
+            if (d_item(i) >= 0 && d_item(i) % NG < J) dscores(d_item(i) % NG, d_item(i) / NG);
             if constexpr (DQ) {
                 if (i == D0 - 1) {
                     if (NG == 2) probs(1, 3);
@@ -499,7 +502,7 @@ __device__ __forceinline__ void attn_bwd_part(
 
     unsigned st = C::V0, st_next = C::V0 + 2 * STAGE;
     int i_step = 0;
-    auto step = [&](auto what) {           // 0: nothing to do for this wave, 1: every score counts, 2: with the causal mask
+    auto step = [&](auto what) {           // 0: nothing to do for this wave, 1: every score counts, 2: with the causal mask, 3: the first group only
         constexpr int WHAT = decltype(what)::value;
         wait_vmcnt<NF>();                                                  // this tile has landed (the next may be in flight)
         if constexpr (!DQ) {                                               // (the last tile is the first; dO: P is 0 there)
@@ -509,13 +512,14 @@ __device__ __forceinline__ void attn_bwd_part(
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         const Fetch next = fetch_of(tile_of(i_step + 2), st_next);         // (behind the last tile: that one again, unused)
-        if constexpr (WHAT) compute(std::integral_constant<bool, WHAT == 2>{}, st, tile_of(i_step) * 64 + 32 * sg, next);
+        if constexpr (WHAT) compute(std::bool_constant<(WHAT >= 2)>{}, std::integral_constant<int, WHAT == 3 ? 1 : NG>{}, st, tile_of(i_step) * 64 + 32 * sg, next);
         else fetch(next);
         st = st == C::V0 + (NST - 1) * STAGE ? C::V0 : st + STAGE;
         st_next = st_next == C::V0 + (NST - 1) * STAGE ? C::V0 : st_next + STAGE;
         ++i_step;
     };
     using Skip = std::integral_constant<int, 0>; using Plain = std::integral_constant<int, 1>; using Masked = std::integral_constant<int, 2>;
+    using First = std::integral_constant<int, 3>;
     // Wave-uniform ranges of tiles: those in which every query precedes every key of this wave are left out, those on the diagonal need
     // the mask.  (Rows beyond T need none: as queries their log-sum-exp is beyond any score, as keys they follow every query.)
     const int w = pw0 - 32 * sg;
@@ -527,6 +531,8 @@ __device__ __forceinline__ void attn_bwd_part(
     } else {
         const int plain_end = tile1 - min(tile1, (w + 32 * NG + 62) >> 6), mask_end = tile1 - min(tile1, (w + 32) >> 6);
         while (i_step < plain_end) step(Plain{});
+        // (the piece of queries at the keys of the first of two groups precedes every key of the second)
+        if constexpr (NG == 2) { if (sg == 0 && i_step < mask_end) step(First{}); }
         while (i_step < mask_end) step(Masked{});
         while (i_step < n_steps) step(Skip{});
     }

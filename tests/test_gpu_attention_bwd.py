@@ -68,7 +68,7 @@ def test_infinity_in_the_last_row(api, H, T, dh):
     assert torch.equal(dv0[:, others], dv1[:, others])
 
 
-@pytest.mark.parametrize("T,dh", [(100, 64)])
+@pytest.mark.parametrize("T,dh", [(100, 64), (100, 128), (128, 128), (200, 128)])
 def test_no_number_in_the_first_row_of_a_tile(api, H, T, dh):
     """Keys from 96 on follow token 64 by more than the 32 rows of a piece: what is not a number there stays away from them, also by way of
     the rows that fill a ragged tile up behind the last."""
