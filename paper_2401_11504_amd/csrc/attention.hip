@@ -97,9 +97,10 @@ __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t*
 #pragma unroll
         for (int j = 0; j < NI; ++j) fetch_rows(vh + (long)u0 * ldq, (unsigned)ldq * 2, wave * NI + j, T - 1 - u0, at + TB);
     };
-    // the block's queries (128 rows) through the first group's second buffer
+    // the block's queries (128 rows, 16 a wave) through the first group's second buffer
+    const int w0 = 16 * (kg * NW + wave), qr = min(q0 + w0, T - 1);
 #pragma unroll
-    for (int j = 0; j < NI; ++j) fetch_rows(qh + (long)q0 * ldq, (unsigned)ldq * 2, (kg * NW + wave) * NI + j, T - 1 - q0, lds0 + 2 * TB);
+    for (int j = 0; j < NI; ++j) fetch_rows(qh + (long)qr * ldq, (unsigned)ldq * 2, j, T - 1 - qr, lds0 + 2 * TB + w0 * RB);
     fetch(0);
     wait_vmcnt<2 * NI>();
     __builtin_amdgcn_s_barrier();
@@ -328,10 +329,11 @@ __device__ __forceinline__ void attn_bwd_part(
     // The operands of the block come through LDS too, and the results leave through it: 16 bytes a lane straight from and to memory touch
     // 32 rows with every instruction (loads and stores of one part 8.5 us; 4.5 like this).  P1 takes the place of the third tile.
     constexpr unsigned P1_AT = C::V0 + 2 * STAGE, P2_AT = DH == 128 ? 0 : P1_AT + TB;
-    auto fetch_block = [&](const bf16_t* x, long ld, unsigned at) {
+    auto fetch_block = [&](const bf16_t* x, long ld, unsigned at) {    // a quarter each, from its own first row: offsets between rows are 32-bit
+        const int w0 = wave * (C::PB / 4), r0 = min(p0 + w0, T - 1);
 #pragma unroll
         for (int j = 0; j < C::PB * RB / 4096; ++j)
-            fetch_rows(x + (long)p0 * ld, (unsigned)ld * 2, wave * (C::PB * RB / 4096) + j, T - 1 - p0, lds0 + at);
+            fetch_rows(x + (long)r0 * ld, (unsigned)ld * 2, j, T - 1 - r0, lds0 + at + w0 * RB);
     };
     fetch_block(p1, ldq, P1_AT);
     fetch_block(p2, ldp2, P2_AT);

@@ -52,7 +52,8 @@ template <int DH>
 __device__ __forceinline__ int tile_swz(int row) {
     return DH == 128 ? 4 * (row & 3) | ((row >> 2) & 3) : 4 * ((row >> 1) & 1) | ((row >> 2) & 3);
 }
-// fetch i of a tile brings its rows i RPI .. (beyond `last`: that one again), each lane the chunk that belongs at its place; base: row 0
+// fetch i of a tile brings its rows i RPI .. (beyond `last`: that one again), each lane the chunk that belongs at its place; base: row 0, or a row that
+// is a multiple of 16 further (rows up to 63 from it: the offset has 32 bits)
 template <int DH>
 struct TileFetch {
     static constexpr int CPR = DH / 8, RPI = 64 / CPR;         // chunks per row, rows per fetch

@@ -77,3 +77,22 @@ def test_no_number_in_the_first_row_of_a_tile(api, H, T, dh):
     plain, edited = gradients(api, H, T, dh, lambda do: None), gradients(api, H, T, dh, edit)
     for a, b in zip(plain, edited):
         assert torch.equal(a[96:], b[96:])
+
+
+def test_rows_far_apart(api, H):
+    """Rows so far apart that 127 of them exceed 4 GiB (64 do not): the same as with the rows side by side."""
+    T, dh, ld = 150, 128, (1 << 24) + (1 << 20)
+    x = H.to_dev_bf16(synth.normal(1, (97, T), (T, 3 * dh), 1.0, True))
+    do = H.to_dev_bf16(synth.normal(2, (97, T), (T, dh), 1.0, True))
+    outs = []
+    for step in (3 * dh, ld):
+        src, grads = (torch.empty(T * step, dtype=torch.bfloat16, device="cuda").view(T, step)[:, :3 * dh] for _ in range(2))
+        src.copy_(x)
+        o, (lse, delta) = torch.zeros_like(do), (torch.zeros(1, T, dtype=torch.float32, device="cuda") for _ in range(2))
+        args, outs_ = ([t[:, i * dh:(i + 1) * dh] for i in range(3)] for t in (src, grads))
+        api.tl_k_attention_fwd(*args, 1, dh, o, lse)
+        api.tl_k_attention_bwd(*args, o, do, lse, 1, dh, *outs_, delta)
+        torch.cuda.synchronize()
+        outs.append(grads.contiguous())
+        del src, grads, args, outs_
+    assert torch.equal(outs[0], outs[1])

@@ -53,3 +53,19 @@ def test_infinity_in_the_last_row(api, H, T, dh):
     assert out[1][-1, 5] == float("inf")
     others = torch.arange(dh, device="cuda") != 5
     assert torch.equal(out[0][:, others], out[1][:, others])
+
+
+def test_rows_far_apart(api, H):
+    """Rows so far apart that 127 of them exceed 4 GiB (64 do not): the same as with the rows side by side."""
+    T, dh = 150, 64
+    x = H.to_dev_bf16(synth.normal(1, (96, T), (T, 3 * dh), 1.0, True))
+    ld = (1 << 24) + (1 << 20)
+    far = torch.empty(T * ld, dtype=torch.bfloat16, device="cuda").view(T, ld)[:, 8:8 + 3 * dh]
+    far.copy_(x)
+    outs = []
+    for src in (x, far):
+        o, lse = torch.zeros(T, dh, dtype=torch.bfloat16, device="cuda"), torch.zeros(1, T, dtype=torch.float32, device="cuda")
+        api.tl_k_attention_fwd(*(src[:, i * dh:(i + 1) * dh] for i in range(3)), 1, dh, o, lse)
+        outs.append((o, lse))
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
