@@ -3,11 +3,11 @@
 //  gemm_nt : C = alpha (A B^T + A2 B2^T) (+ R)      both operand pairs are K-contiguous.
 //            Forward:  Y  = X W^T  + Hs B^T           (A2 = Hs = s X A^T, K2 = r)
 //            Backward: dX = dY Wt^T + dH At^T          (Wt, At = transposed copies, K2 = r)
-//            Low-rank: Hs = s X A^T, dH = s dY Bt^T    (N = r: mostly nt_waves_kernel)
+//            Low-rank: Hs = s X A^T, dH = s dY Bt^T    (N = r, split over K)
 //            The low-rank term rides along as extra K tiles of the same accumulator, so the
 //            frozen product and the LoRA correction are one pass over the output.
 //  gemm_tn : C = alpha P^T Q, contraction over the token dimension (dA = dH^T X, dB = dY^T Hs),
-//            fp32 output.  Operand tiles lie in LDS as in memory and are read transposed.
+//            fp32 output.  Operand tiles are transposed on their way into LDS.
 //
 // LDS tiles hold 64 contraction elements per row, padded to 72 so that the 16-byte fragment
 // reads of 8 consecutive rows fall into distinct banks.
@@ -1054,11 +1054,9 @@ hipError_t launch_frozen(const GemmNT& g, hipStream_t s) {
 // memory, [t][i] with the token index t as rows, and the matrix unit's operands (contraction over t) come out of the
 // LDS transpose read (read_tr_frag in tiles.h): no transposing stores, no bank conflicts.  Both operands use the
 // same slot order, so the permutation of the 16 contraction slots of a step cancels.  Returns this wave's 32x32 accumulator.
-// What bounds it: four MFMAs a wave and tile are a tenth of the time a tile takes to arrive, so it is the bytes in flight and, with many
-// tokens, memory: a ring of TN_ST tiles of both operands by direct-to-LDS loads, TN_ST - 1 of them on their way, one barrier a tile.
-// us of a layer's launch with one tile ahead in registers and with this: 1024 tokens of width 1024 (260 tiles) 17.6 and 11.6, 200 tokens
-// (65 tiles) 8.9 and 7.0; 7B shapes (1220 tiles), 5120 tokens 235 and 211 (3.8 TB/s of operands), 1536 tokens 62 and 60.  Three tiles (and
-// three workgroups on a CU) or a contiguous range of the tiles on each XCD measure the same within 3 %.
+// What bounds it: four MFMAs a wave and tile are a tenth of the time a tile takes to arrive, so it is the bytes in flight: a ring of
+// TN_ST tiles of both operands by direct-to-LDS loads, TN_ST - 1 of them on their way, one barrier a tile.
+// TN_FIGURES
 constexpr int TN_ST = 4, TN_TILE = 64 * 128, TN_STAGE = 2 * TN_TILE;     // bytes of a tile, of P's and Q's
 __device__ __forceinline__ f32x16_t tn_tile(const bf16_t* P, long ldp, int Mo, const bf16_t* Q, long ldq, int No, int T,
                                             int i0, int j0, int it0, int it1) {

@@ -52,8 +52,7 @@ template <int DH>
 __device__ __forceinline__ int tile_swz(int row) {
     return DH == 128 ? 4 * (row & 3) | ((row >> 2) & 3) : 4 * ((row >> 1) & 1) | ((row >> 2) & 3);
 }
-// fetch i of a tile brings its rows i RPI .. (beyond `last`: that one again), each lane the chunk that belongs at its place; base: row 0, or a row that
-// is a multiple of 16 further (rows up to 63 from it: the offset has 32 bits)
+// fetch i of a tile brings its rows i RPI .. (beyond `last`: that one again), each lane the chunk that belongs at its place; base: row 0
 template <int DH>
 struct TileFetch {
     static constexpr int CPR = DH / 8, RPI = 64 / CPR;         // chunks per row, rows per fetch
@@ -65,12 +64,6 @@ struct TileFetch {
         load_lds16((unsigned)min(i * RPI + fr, last) * ldb + c, base, __builtin_amdgcn_readfirstlane(lds + i * 1024));
     }
 };
-// rows first .. end - 1 of such a tile made zero by one wave.  Fetches bring the last row again in the place of rows behind it; where the products
-// take those with weights of 0, an infinity in the last row would turn into 0 x inf.
-template <int DH>
-__device__ __forceinline__ void clear_rows(unsigned char* tile, int first, int end, int lane) {
-    for (int at = first * DH * 2 + lane * 16; at < end * DH * 2; at += 1024) *(uint4*)(tile + at) = make_uint4(0, 0, 0, 0);
-}
 // this lane's share of the address of a fragment of rows (row l32, chunk 2 ks + g: ^ ks << 5) ..
 template <int DH>
 __device__ __forceinline__ unsigned row_frag_at(int lane) {
