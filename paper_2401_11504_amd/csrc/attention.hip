@@ -51,10 +51,11 @@ __device__ __forceinline__ void write_rows_from_dT(bf16_t* __restrict__ dst, con
 // MFMAs; at T = 1024 with 32 heads there are otherwise only as many 32-query waves as the chip has SIMDs.
 // K and V tiles come by direct-to-LDS loads, one tile ahead in the group's other buffer, with one barrier a tile; Q and O pass through LDS
 // too (straight from and to memory every instruction touches 32 rows).  us with tiles staged through registers (two barriers a tile, Q and
-// O by rows) and with this, heads of 128 / 64: 1024 tokens, 32 heads 28.8 and 25.9 / 16 heads 17.3 and 15.3; 2048 tokens 54.8 and 47.5 /
+// O by rows) and with this, heads of 128 / 64: 1024 tokens, 32 heads 28.8 and 25.4 / 16 heads 17.3 and 15.3; 2048 tokens 54.8 and 47.5 /
 // 30.8 and 28.9; 5120 tokens, 32 heads of 128 277 and 246 (870 TFLOP/s; the rest is the softmax between the two products of a tile, and at
-// 1024 tokens the heaviest block: 8 rounds of two tiles where the mean is 4.5).  The order of every sum is the same in both.
-template <int DH, int NW, int KG>
+// 1024 tokens the heaviest block: 8 passes of two tiles where the mean is 4.5).  The order of every sum is the same in both.
+// DIRECT: q, k and v start at multiples of 4 bytes (else their tiles come through registers)
+template <int DH, int NW, int KG, bool DIRECT>
 __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                 const bf16_t* __restrict__ v, long ldq, int T,
                                                                 bf16_t* __restrict__ o, long ldo, float* __restrict__ lse,
@@ -69,20 +70,13 @@ __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t*
     const unsigned lds0 = (unsigned)(size_t)smem_raw;
     const unsigned group_at = kg * 4 * TB;                        // two buffers of a K and a V tile each
     const unsigned row_at = row_frag_at<DH>(lane), tr_at = tr_frag_at<DH>(lane);
-    const TileFetch<DH> fetch_rows(lane);
-    // Heaviest (latest) query blocks first; the second half of the heads takes the mirrored block, so that two
-    // workgroups placed on one CU by round-robin dispatch (ids i and i + n/2 in dispatch order, x fastest) carry the
-    // same total number of key tiles whichever CU they land on.
-    // With more workgroups than CUs (several rounds) the order of dispatch decides the tail instead: every head's
-    // heaviest block first, then every head's second heaviest, and so on (longest job first).
-    const bool mirror = 2 * blockIdx.y >= gridDim.y + 1;
-    int qb = mirror ? (int)blockIdx.x : (int)(gridDim.x - 1 - blockIdx.x);
-    int head = blockIdx.y;
-    if (gridDim.x * gridDim.y > 256) {
-        const int idx = blockIdx.y * gridDim.x + blockIdx.x;   // position in dispatch order (x fastest)
-        qb = (int)gridDim.x - 1 - idx / (int)gridDim.y;
-        head = idx % (int)gridDim.y;
-    }
+    const TileFetch<DH, DIRECT> fetch_rows(lane);
+    // Heaviest (latest) query blocks first, every head's before any head's second heaviest (longest job first).  The blocks of a head are
+    // gridDim.y workgroups apart in dispatch order (x fastest), so with a multiple of eight heads they lie on one XCD, whose L2 fetches the
+    // head's keys and values once; with a head's blocks side by side all eight XCDs fetch them (1024 tokens, 32 heads of 128:
+    // 25 MB fetched and 22.8 us, 84 MB and 25.4).
+    const int idx = blockIdx.y * gridDim.x + blockIdx.x;
+    const int qb = (int)gridDim.x - 1 - idx / (int)gridDim.y, head = idx % (int)gridDim.y;
     const int q0 = qb * QB, tq0 = q0 + 32 * wave, t_abs = tq0 + l32;
     const bf16_t* qh = q + (long)head * DH;
     const bf16_t* kh = k + (long)head * DH;
@@ -104,11 +98,13 @@ __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t*
 #pragma unroll
         for (int j = 0; j < NI; ++j) fetch_rows(vh + (long)u0 * ldq, (unsigned)ldq * 2, wave * NI + j, T - 1 - u0, at + TB);
     };
-    // the block's queries (128 rows) through the first group's second buffer
+    // the block's queries (128 rows, 16 a wave) through the first group's second buffer
+    const int w0 = 16 * (kg * NW + wave), qr = min(q0 + w0, T - 1);
 #pragma unroll
-    for (int j = 0; j < NI; ++j) fetch_rows(qh + (long)q0 * ldq, (unsigned)ldq * 2, (kg * NW + wave) * NI + j, T - 1 - q0, lds0 + 2 * TB);
+    for (int j = 0; j < NI; ++j) fetch_rows(qh + (long)qr * ldq, (unsigned)ldq * 2, j, T - 1 - qr, lds0 + 2 * TB + w0 * RB);
     fetch(0);
-    wait_vmcnt<2 * NI>();
+    wait_vmcnt<DIRECT ? 2 * NI : 0>();
+    if constexpr (!DIRECT) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     bf16x8_t qf[C::NKS];
@@ -119,6 +115,7 @@ __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t*
     for (int it = 0; it < n_iter; ++it) {
         const int u0 = (it * KG + kg) * 64;
         wait_vmcnt<0>();                                          // the tile has landed,
+        if (u0 + 64 > T) clear_rows<DH>(smem_raw + group_at + (it & 1) * 2 * TB + TB, max(16 * wave, T - u0), 16 * wave + 16, lane);     // (V: P is 0 there)
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // the one before (and Q) has been read
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -250,7 +247,7 @@ __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int
 template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
-__device__ const float kLseBeyond = 1.0e30f;      // log-sum-exp of a row that does not exist: every probability is 0
+__device__ const float kBeyond[2] = {1.0e30f, 0.f};       // log-sum-exp and delta of a query that does not exist: every probability is 0
 
 template <int DH> struct BwdCfg {
     static constexpr int NG = DH / 64;                     // 32-row groups per wave
@@ -274,7 +271,8 @@ __device__ __forceinline__ void mfma32_score(f32x16_t& c, bf16x8_t a, bf16x8_t b
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
 
-template <int DH, bool DQ>
+// DIRECT: q, k, v and dO start at multiples of 4 bytes (else their tiles come through registers, ahead of the products instead of between them)
+template <int DH, bool DQ, bool DIRECT>
 __device__ __forceinline__ void attn_bwd_part(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
     const float* __restrict__ lse, const float* __restrict__ delta, long ldq, long ldo, int T, bf16_t* __restrict__ dq,
@@ -282,7 +280,7 @@ __device__ __forceinline__ void attn_bwd_part(
     unsigned char* smem) {
     using C = BwdCfg<DH>;
     constexpr int NG = C::NG, KS = DH / 16, ND = DH / 32, RB = C::RB, TB = C::TB, STAGE = C::STAGE, NST = C::NST;
-    constexpr int NI = TB / 4096, RPI = 1024 / RB, CPR = RB / 16;      // fetches per wave and tile; rows per fetch; chunks per row
+    constexpr int NI = TB / 4096;                                      // fetches per wave and tile
     constexpr int NF = 2 * NI + (DQ ? 0 : 1);                          // fetches per wave and stage
     constexpr bool V_LDS = !DQ && NG == 2;
     static_assert(KS == 2 * ND, "as many MFMAs for each product");
@@ -311,7 +309,7 @@ __device__ __forceinline__ void attn_bwd_part(
         lse2[j] = DQ ? lse_h[p] * 1.4426950408889634f : 0.f;
     }
 
-    const TileFetch<DH> fetch_rows(lane);
+    const TileFetch<DH, DIRECT> fetch_rows(lane);
     const unsigned ld1b = (unsigned)ldq * 2, ldx2b = (unsigned)ldx2 * 2;
     struct Fetch { const bf16_t *a, *b; const float* stats; int last; unsigned st; };
     auto fetch_of = [&](int tile, unsigned st) {
@@ -322,7 +320,7 @@ __device__ __forceinline__ void attn_bwd_part(
     auto fetch_piece = [&](const Fetch& f, int n) {
         if (n < NI) fetch_rows(f.a, ld1b, wave * NI + n, f.last, lds0 + f.st);
         else if (n < 2 * NI) fetch_rows(f.b, ldx2b, wave * NI + n - NI, f.last, lds0 + f.st + TB);
-        else load_lds4(lane <= f.last ? f.stats + lane : sg ? f.stats : &kLseBeyond, __builtin_amdgcn_readfirstlane(lds0 + f.st + 2 * TB + sg * 256));
+        else load_lds4(lane <= f.last ? f.stats + lane : kBeyond + sg, __builtin_amdgcn_readfirstlane(lds0 + f.st + 2 * TB + sg * 256));
     };
     auto fetch = [&](const Fetch& f) {
 #pragma unroll
@@ -334,10 +332,11 @@ __device__ __forceinline__ void attn_bwd_part(
     // The operands of the block come through LDS too, and the results leave through it: 16 bytes a lane straight from and to memory touch
     // 32 rows with every instruction (loads and stores of one part 8.5 us; 4.5 like this).  P1 takes the place of the third tile.
     constexpr unsigned P1_AT = C::V0 + 2 * STAGE, P2_AT = DH == 128 ? 0 : P1_AT + TB;
-    auto fetch_block = [&](const bf16_t* x, long ld, unsigned at) {
+    auto fetch_block = [&](const bf16_t* x, long ld, unsigned at) {    // a quarter each, from its own first row: offsets between rows are 32-bit
+        const int w0 = wave * (C::PB / 4), r0 = min(p0 + w0, T - 1);
 #pragma unroll
         for (int j = 0; j < C::PB * RB / 4096; ++j)
-            fetch_rows(x + (long)p0 * ld, (unsigned)ld * 2, wave * (C::PB * RB / 4096) + j, T - 1 - p0, lds0 + at);
+            fetch_rows(x + (long)r0 * ld, (unsigned)ld * 2, j, T - 1 - r0, lds0 + at + w0 * RB);
     };
     fetch_block(p1, ldq, P1_AT);
     fetch_block(p2, ldp2, P2_AT);
@@ -350,7 +349,8 @@ __device__ __forceinline__ void attn_bwd_part(
     // this lane's place in the fragments of block rows (chunk 2 ks + g of row l32 of a group)
     const unsigned p_at = (unsigned)((pg * 32 * NG + (NG == 2 ? 32 * sg : 0)) * RB) + row_frag_at<DH>(lane);
     auto p_frag = [&](unsigned at, int j, int ks) { return *(const bf16x8_t*)(smem + at + (p_at ^ (unsigned)(ks << 5 | j * 32 * RB))); };
-    wait_vmcnt<2 * NF>();
+    wait_vmcnt<DIRECT ? 2 * NF : 0>();
+    if constexpr (!DIRECT) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     bf16x8_t p1f[NG][KS], p2f[V_LDS ? 1 : NG][V_LDS ? 1 : KS];
@@ -392,12 +392,15 @@ __device__ __forceinline__ void attn_bwd_part(
         return read_tr_frag<DH>(smem + tile + (i / ND) * 16 * RB, tr_at, i % ND);
     };
 
-    auto compute = [&](auto masked, unsigned st, int xs0, const Fetch& next) {
+    // J: groups of rows that take part (the others keep what they have: not even a weight of 0 meets a row that does not belong to them)
+    auto compute = [&](auto masked, auto groups, unsigned st, int xs0, const Fetch& next) {
         constexpr bool MASK = decltype(masked)::value;
+        constexpr int J = decltype(groups)::value;
         // One fragment of X and NG MFMAs a slot, KS slots each of S, dP, dV and dK (of S, dP and dQ).  Fragments are asked for AHEAD slots
         // before they are used, and the vector work on the scores, in items of four values a lane, goes between the MFMAs behind them.
         constexpr int B0 = KS, C0 = 2 * KS, NS = (DQ ? 3 : 4) * KS, D0 = NS - KS;
         constexpr int AHEAD = 4, AHEAD_V = 3;
+        static_assert(J == NG || !DQ, "only key blocks leave a group out");
         f32x16_t s[NG], dp[NG];
         bf16x8_t pb[NG][2], dsb[NG][2], fx[NS], fv[NG][KS];
         float4 l4[4], d4[4];
@@ -409,14 +412,14 @@ __device__ __forceinline__ void attn_bwd_part(
                 fx[i] = row_frag(t2, n);
                 if constexpr (V_LDS) {
 #pragma unroll
-                    for (int j = 0; j < NG; ++j) fv[j][n] = p_frag(P2_AT, j, n);
+                    for (int j = 0; j < J; ++j) fv[j][n] = p_frag(P2_AT, j, n);
                 }
             } else fx[i] = tr_frag(i >= D0 ? t1 : t2, n);
         };
         auto mfma = [&](auto slot) {
             constexpr int i = decltype(slot)::value, n = i % KS;
 #pragma unroll
-            for (int j = 0; j < NG; ++j) {
+            for (int j = 0; j < J; ++j) {
                 if constexpr (i < B0) mfma32_score<n == 0>(s[j], fx[i], p1f[j][n]);
                 else if constexpr (i < C0) mfma32_score<n == 0>(dp[j], fx[i], V_LDS ? fv[j][n] : p2f[V_LDS ? 0 : j][V_LDS ? 0 : n]);
                 else if constexpr (i >= D0) mfma32_acc(acc1[j][n % ND], fx[i], dsb[j][n / ND]);
@@ -451,9 +454,9 @@ __device__ __forceinline__ void attn_bwd_part(
         auto ready = [&](f32x16_t* x, auto wait) {
             if constexpr (decltype(wait)::value) asm volatile("s_nop 15\n\ts_nop 3");
 #pragma unroll
-            for (int j = 0; j < NG; ++j) asm volatile("" : "+v"(x[j]));
+            for (int j = 0; j < J; ++j) asm volatile("" : "+v"(x[j]));
         };
-        using Wait = std::true_type; using SlotWait = std::bool_constant<NG == 1>;
+        using Wait = std::true_type; using SlotWait = std::bool_constant<J == 1>;
         // item n: group n % NG, rows 8 (n / NG) ..; dV needs the first half of the probabilities KS / 2 slots before the second
         constexpr int NI_P = 4 * NG;
         auto p_item = [](int i) -> int {           // the item of probabilities behind the MFMAs of slot i
@@ -473,8 +476,8 @@ __device__ __forceinline__ void attn_bwd_part(
                 constexpr int r = i + 1 + decltype(more)::value;
                 if constexpr (r < NS && r - (V_LDS && r >= B0 && r < C0 ? AHEAD_V : AHEAD) == i) read(std::integral_constant<int, r>{});
             });
-            if (i < NF - NI) fetch_piece(next, NI + i);
-            if (i >= NS - NI) fetch_piece(next, i - (NS - NI));
+            if (DIRECT && i < NF - NI) fetch_piece(next, NI + i);
+            if (DIRECT && i >= NS - NI) fetch_piece(next, i - (NS - NI));
 #pragma unroll
             for (int x = 0; x < NI_P; ++x) {
                 if (p_item(i + 2) == x && x % NG == 0) read_stats(0, x / NG);
@@ -483,8 +486,8 @@ __device__ __forceinline__ void attn_bwd_part(
             mfma(slot);
             if constexpr (i == B0) ready(s, SlotWait{});
             if constexpr (i == C0 && !DQ) ready(dp, SlotWait{});
-            if (p_item(i) >= 0) probs(p_item(i) % NG, p_item(i) / NG);
-            if (d_item(i) >= 0) dscores(d_item(i) % NG, d_item(i) / NG);
+            if (p_item(i) >= 0 && p_item(i) % NG < J) probs(p_item(i) % NG, p_item(i) / NG);
+            if (d_item(i) >= 0 && d_item(i) % NG < J) dscores(d_item(i) % NG, d_item(i) / NG);
             if constexpr (DQ) {
                 if (i == D0 - 1) {
                     if (NG == 2) probs(1, 3);
@@ -505,20 +508,25 @@ __device__ __forceinline__ void attn_bwd_part(
 
     unsigned st = C::V0, st_next = C::V0 + 2 * STAGE;
     int i_step = 0;
-    auto step = [&](auto what) {           // 0: nothing to do for this wave, 1: every score counts, 2: with the causal mask
+    auto step = [&](auto what) {           // 0: nothing to do for this wave, 1: every score counts, 2: with the causal mask, 3: the first group only
         constexpr int WHAT = decltype(what)::value;
-        wait_vmcnt<NF>();                                                  // this tile has landed (the next may be in flight)
+        wait_vmcnt<DIRECT ? NF : 0>();                                     // this tile has landed (the next may be in flight)
+        if constexpr (!DQ) {                                               // (the last tile is the first; dO: P is 0 there)
+            if (i_step == 0 && tile1 * 64 > T) clear_rows<DH>(smem + st + TB, max(16 * wave, T - (tile1 - 1) * 64), 16 * wave + 16, lane);
+        }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                 // and every read of the one before is done
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         const Fetch next = fetch_of(tile_of(i_step + 2), st_next);         // (behind the last tile: that one again, unused)
-        if constexpr (WHAT) compute(std::integral_constant<bool, WHAT == 2>{}, st, tile_of(i_step) * 64 + 32 * sg, next);
+        if constexpr (WHAT && !DIRECT) fetch(next);
+        if constexpr (WHAT) compute(std::bool_constant<(WHAT >= 2)>{}, std::integral_constant<int, WHAT == 3 ? 1 : NG>{}, st, tile_of(i_step) * 64 + 32 * sg, next);
         else fetch(next);
         st = st == C::V0 + (NST - 1) * STAGE ? C::V0 : st + STAGE;
         st_next = st_next == C::V0 + (NST - 1) * STAGE ? C::V0 : st_next + STAGE;
         ++i_step;
     };
     using Skip = std::integral_constant<int, 0>; using Plain = std::integral_constant<int, 1>; using Masked = std::integral_constant<int, 2>;
+    using First = std::integral_constant<int, 3>;
     // Wave-uniform ranges of tiles: those in which every query precedes every key of this wave are left out, those on the diagonal need
     // the mask.  (Rows beyond T need none: as queries their log-sum-exp is beyond any score, as keys they follow every query.)
     const int w = pw0 - 32 * sg;
@@ -530,6 +538,8 @@ __device__ __forceinline__ void attn_bwd_part(
     } else {
         const int plain_end = tile1 - min(tile1, (w + 32 * NG + 62) >> 6), mask_end = tile1 - min(tile1, (w + 32) >> 6);
         while (i_step < plain_end) step(Plain{});
+        // (the piece of queries at the keys of the first of two groups precedes every key of the second)
+        if constexpr (NG == 2) { if (sg == 0 && i_step < mask_end) step(First{}); }
         while (i_step < mask_end) step(Masked{});
         while (i_step < n_steps) step(Skip{});
     }
@@ -633,7 +643,7 @@ __device__ __forceinline__ void attn_bwd_part(
 // list has an 8:1 causal imbalance between its workgroups at 1024 tokens, and the chip waits for the longest one twice; in one launch a
 // CU that finishes a light part picks up the next.  delta must already be in memory (the dK/dV parts read rows that other
 // workgroups' dQ parts own).  grid = (n blocks, heads, 2).
-template <int DH>
+template <int DH, bool DIRECT>
 __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_fused_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, long ldq, long ldo,
@@ -643,27 +653,23 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_fused_kernel(
     const int n = gridDim.x, heads = gridDim.y;
     const int idx = (blockIdx.z * heads + blockIdx.y) * n + blockIdx.x;   // position in dispatch order (x fastest)
     const int level = idx / (2 * heads), r = idx % (2 * heads), head = r % heads;
-    if (r < heads) attn_bwd_part<DH, false>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope, level, head, smem);
-    else attn_bwd_part<DH, true>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope, n - 1 - level, head, smem);
+    if (r < heads) attn_bwd_part<DH, false, DIRECT>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope, level, head, smem);
+    else attn_bwd_part<DH, true, DIRECT>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope, n - 1 - level, head, smem);
 }
 
 // ======================================================================== launchers
-// waves per workgroup (32 queries / keys each), fixed at build time.  Measured at T = 1024, 32 heads of 128:
+// waves per key group of the forward kernel (32 queries each).  Measured at T = 1024, 32 heads of 128:
 // 4 waves beat 2 (a K/V tile is shared by more queries; the extra workgroups of 2 do not overlap enough).
-#ifndef ATTN_NW
-#define ATTN_NW 4
-#endif
-
-// key groups of the forward kernel (see attn_fwd_kernel)
-#ifndef ATTN_KG
-#define ATTN_KG 2
-#endif
+constexpr int ATTN_NW = 4;
+// its key groups (see attn_fwd_kernel)
+constexpr int ATTN_KG = 2;
 
 template <int DH, int NW, int KG>
 static hipError_t run_fwd(dim3 grid, const bf16_t* q, const bf16_t* k, const bf16_t* v, long ldq, int T, bf16_t* o,
                           long ldo, float* lse, float sl2, hipStream_t s) {
     const size_t lds = (size_t)KG * 4 * 64 * DH * sizeof(bf16_t);
-    auto kern = attn_fwd_kernel<DH, NW, KG>;
+    const bool direct = loads_to_lds(q) && loads_to_lds(k) && loads_to_lds(v);
+    auto kern = direct ? attn_fwd_kernel<DH, NW, KG, true> : attn_fwd_kernel<DH, NW, KG, false>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     kern<<<grid, NW * 64 * KG, lds, s>>>(q, k, v, ldq, T, o, ldo, lse, sl2);
@@ -715,7 +721,8 @@ static hipError_t run_bwd(const bf16_t* q, const bf16_t* k, const bf16_t* v, con
     attn_delta_kernel<DH><<<dgrid, 256, 0, s>>>(o, d_o, ldo, T, n_heads, delta);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    auto kern = attn_bwd_fused_kernel<DH>;
+    const bool direct = loads_to_lds(q) && loads_to_lds(k) && loads_to_lds(v) && loads_to_lds(d_o);
+    auto kern = direct ? attn_bwd_fused_kernel<DH, true> : attn_bwd_fused_kernel<DH, false>;
     e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
     if (e != hipSuccess) return e;
     kern<<<grid, 256, C::LDS, s>>>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope);
