@@ -329,8 +329,7 @@ tl_status tl_linear_step_static(const float* X, const float* W, const float* A, 
 
 /* C[M,N] = alpha * (A[M,K] B[N,K]^T + A2[M,K2] B2[N,K2]^T) (+ R[M,N] if R != NULL), bf16 MFMA, fp32 accumulate.
  * A2/B2 may be NULL (K2 = 0).  c_f32 != 0: C and R are fp32, else C is bf16 and R must be NULL.
- * lda/ldb/lda2/ldb2/ldc are row strides in elements; K, K2, lda, ldb, lda2, ldb2 multiples of 8.  The operands start at any element (fastest
- * at multiples of 4 bytes, C and R at multiples of 16); the same holds for the two products below.
+ * lda/ldb/lda2/ldb2/ldc are row strides in elements; K, K2, lda, ldb, lda2, ldb2 multiples of 8.
  * Tile shape, contraction split and (for many-tile shapes whose last round of workgroups would be poorly filled)
  * a split into two launches over two ranges of columns or rows are chosen as in the update path.
  * workspace: NULL, or device fp32 scratch of workspace_elems floats for the partial results of a split contraction
@@ -367,8 +366,7 @@ tl_status tl_k_gemm_nt_plan(int32_t M, int32_t N, int32_t K, int32_t K2, size_t 
 tl_status tl_k_linear_step_plan(int32_t T, int32_t d_in, int32_t d_out, int32_t r, float s, int32_t one_by_one, char* names_out,
                                 size_t names_cap);
 
-/* C[Mo,No] (fp32) = alpha * P[T,Mo]^T Q[T,No]  (contraction over the token dimension; dA and dB).  P and Q start at any element (fastest at
- * multiples of 4 bytes). */
+/* C[Mo,No] (fp32) = alpha * P[T,Mo]^T Q[T,No]  (contraction over the token dimension; dA and dB). */
 tl_status tl_k_gemm_tn(const uint16_t* P, int32_t ldp, const uint16_t* Q, int32_t ldq, int32_t T, int32_t Mo,
                        int32_t No, float alpha, float* C, int32_t ldc, void* hip_stream);
 
@@ -417,7 +415,7 @@ tl_status tl_k_argmax(const float* x, int32_t n, int32_t* out, void* hip_stream)
 tl_status tl_k_swiglu_bwd(const uint16_t* da, const uint16_t* gu, int32_t T, int32_t f, uint16_t* dgu,
                           void* hip_stream);
 /* Causal attention forward: q, k, v, o bf16 [T, n_heads, d_head] with row strides ldq (shared by q, k, v)
- * and ldo (multiples of 8 elements; the first elements lie anywhere, fastest at multiples of 4 bytes); lse fp32 [n_heads, T] = log-sum-exp of the scaled scores of each row. */
+ * and ldo; lse fp32 [n_heads, T] = log-sum-exp of the scaled scores of each row. */
 tl_status tl_k_attention_fwd(const uint16_t* q, const uint16_t* k, const uint16_t* v, int32_t ldq, int32_t T,
                              int32_t n_heads, int32_t d_head, uint16_t* o, int32_t ldo, float* lse,
                              void* hip_stream);

@@ -41,17 +41,6 @@ __device__ __forceinline__ void load_lds16(unsigned voff, const void* sbase, uns
 __device__ __forceinline__ void load_lds4(const void* p, unsigned lds_addr) {
     asm volatile("global_load_lds_dword %0, off" ::"v"(p), "{m0}"(lds_addr) : "memory");
 }
-// 16 bytes a lane to lds_addr + 16 lane, by such a load (DIRECT) or, where the address may be no multiple of 4, through registers (waited for at once)
-template <bool DIRECT>
-__device__ __forceinline__ void bring_lds16(unsigned voff, const void* sbase, unsigned lds_addr, int lane) {
-    if constexpr (DIRECT) {
-        load_lds16(voff, sbase, __builtin_amdgcn_readfirstlane(lds_addr));
-    } else {
-        typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-        typedef __attribute__((address_space(3))) u32x4_t* lds_ptr_t;
-        *(lds_ptr_t)(uintptr_t)(lds_addr + 16 * lane) = *(const u32x4_t*)((const char*)sbase + voff);
-    }
-}
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
@@ -65,16 +54,15 @@ __device__ __forceinline__ int tile_swz(int row) {
 }
 // fetch i of a tile brings its rows i RPI .. (beyond `last`: that one again), each lane the chunk that belongs at its place; base: row 0, or a row that
 // is a multiple of 16 further (rows up to 63 from it: the offset has 32 bits)
-// DIRECT: the operand starts at a multiple of 4 bytes, else through registers
-template <int DH, bool DIRECT>
+template <int DH>
 struct TileFetch {
     static constexpr int CPR = DH / 8, RPI = 64 / CPR;         // chunks per row, rows per fetch
-    int lane, fr;
+    int fr;
     unsigned fc;
-    __device__ __forceinline__ TileFetch(int lane) : lane(lane), fr(lane / CPR), fc((unsigned)((lane % CPR) ^ tile_swz<DH>(lane / CPR)) << 4) {}
+    __device__ __forceinline__ TileFetch(int lane) : fr(lane / CPR), fc((unsigned)((lane % CPR) ^ tile_swz<DH>(lane / CPR)) << 4) {}
     __device__ __forceinline__ void operator()(const bf16_t* base, unsigned ldb, int i, int last, unsigned lds) const {
         const unsigned c = fc ^ (unsigned)((i * (RPI / 4) & 3) << 4);                  // swz of rows i RPI + fr
-        bring_lds16<DIRECT>((unsigned)min(i * RPI + fr, last) * ldb + c, base, lds + i * 1024, lane);
+        load_lds16((unsigned)min(i * RPI + fr, last) * ldb + c, base, __builtin_amdgcn_readfirstlane(lds + i * 1024));
     }
 };
 // rows first .. end - 1 of such a tile made zero by one wave.  Fetches bring the last row again in the place of rows behind it; where the products
