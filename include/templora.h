@@ -366,7 +366,8 @@ tl_status tl_k_gemm_nt_plan(int32_t M, int32_t N, int32_t K, int32_t K2, size_t 
 tl_status tl_k_linear_step_plan(int32_t T, int32_t d_in, int32_t d_out, int32_t r, float s, int32_t one_by_one, char* names_out,
                                 size_t names_cap);
 
-/* C[Mo,No] (fp32) = alpha * P[T,Mo]^T Q[T,No]  (contraction over the token dimension; dA and dB). */
+/* C[Mo,No] (fp32) = alpha * P[T,Mo]^T Q[T,No]  (contraction over the token dimension; dA and dB).  P and Q start at any element (fastest at
+ * multiples of 4 bytes). */
 tl_status tl_k_gemm_tn(const uint16_t* P, int32_t ldp, const uint16_t* Q, int32_t ldq, int32_t T, int32_t Mo,
                        int32_t No, float alpha, float* C, int32_t ldc, void* hip_stream);
 

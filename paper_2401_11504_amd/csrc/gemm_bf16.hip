@@ -1060,6 +1060,8 @@ hipError_t launch_frozen(const GemmNT& g, hipStream_t s) {
 // (65 tiles) 8.9 and 7.0; 7B shapes (1220 tiles), 5120 tokens 235 and 211 (3.8 TB/s of operands), 1536 tokens 62 and 60.  Three tiles (and
 // three workgroups on a CU) or a contiguous range of the tiles on each XCD measure the same within 3 %.
 constexpr int TN_ST = 4, TN_TILE = 64 * 128, TN_STAGE = 2 * TN_TILE;     // bytes of a tile, of P's and Q's
+// DIRECT: the operands start at multiples of 4 bytes; else they come through registers, a tile at a time.
+template <bool DIRECT>
 __device__ __forceinline__ f32x16_t tn_tile(const bf16_t* P, long ldp, int Mo, const bf16_t* Q, long ldq, int No, int T,
                                             int i0, int j0, int it0, int it1) {
     __shared__ __align__(16) unsigned char ring[TN_ST * TN_STAGE];
@@ -1078,8 +1080,8 @@ __device__ __forceinline__ f32x16_t tn_tile(const bf16_t* P, long ldp, int Mo, c
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const unsigned row = (unsigned)min(fr + 32 * h, last);
-            load_lds16(row * (unsigned)(ldp * 2) + pc, pb, __builtin_amdgcn_readfirstlane(st + h * 4096));
-            load_lds16(row * (unsigned)(ldq * 2) + qc, qb, __builtin_amdgcn_readfirstlane(st + TN_TILE + h * 4096));
+            bring_lds16<DIRECT>(row * (unsigned)(ldp * 2) + pc, pb, st + h * 4096, lane);
+            bring_lds16<DIRECT>(row * (unsigned)(ldq * 2) + qc, qb, st + TN_TILE + h * 4096, lane);
         }
     };
     f32x16_t acc = zero16();
@@ -1111,6 +1113,7 @@ __device__ __forceinline__ f32x16_t tn_tile(const bf16_t* P, long ldp, int Mo, c
     return acc;
 }
 
+template <bool DIRECT>
 __global__ __launch_bounds__(256) void gemm_tn_kernel(GemmTN p, int n_split) {
     // grid.y = Mo tiles x n_split: each split covers a contiguous token range; with n_split > 1 the splits are
     // stored as fp32 partials and added by tn_reduce_kernel.
@@ -1121,7 +1124,7 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(GemmTN p, int n_split) {
     const int i0 = ti * 64, j0 = blockIdx.x * 64, z = blockIdx.z;
     const int nt_all = (p.T + 63) / 64;
     const int it0 = (int)((long)nt_all * split / n_split), it1 = (int)((long)nt_all * (split + 1) / n_split);
-    const f32x16_t acc = tn_tile(p.P + (long)z * p.bP, p.ldp, p.Mo, p.Q + (long)z * p.bQ, p.ldq, p.No, p.T, i0, j0, it0, it1);
+    const f32x16_t acc = tn_tile<DIRECT>(p.P + (long)z * p.bP, p.ldp, p.Mo, p.Q + (long)z * p.bQ, p.ldq, p.No, p.T, i0, j0, it0, it1);
     const int col = j0 + wj * 32 + l32;
     if (n_split == 1) {
         if (col < p.No) {
@@ -1146,6 +1149,7 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(GemmTN p, int n_split) {
 
 // Several independent P^T Q products over the same T tokens in one launch: workgroup b takes output tile
 // b - tile0 of the problem whose tile range holds b.  Every tile runs over all tokens, so nothing is split or reduced.
+template <bool DIRECT>
 __global__ __launch_bounds__(256) void gemm_tn_grouped_kernel(GemmTNGroup grp) {
     const int b = blockIdx.x;
     int k = 0;
@@ -1153,7 +1157,7 @@ __global__ __launch_bounds__(256) void gemm_tn_grouped_kernel(GemmTNGroup grp) {
     const TnProblem& q = grp.p[k];
     const int t = b - q.tile0, tiles_j = (q.No + 63) / 64;
     const int i0 = (t / tiles_j) * 64, j0 = (t % tiles_j) * 64;
-    const f32x16_t acc = tn_tile(q.P, q.ldp, q.Mo, q.Q, q.ldq, q.No, grp.T, i0, j0, 0, (grp.T + 63) / 64);
+    const f32x16_t acc = tn_tile<DIRECT>(q.P, q.ldp, q.Mo, q.Q, q.ldq, q.No, grp.T, i0, j0, 0, (grp.T + 63) / 64);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wi = wave >> 1, wj = wave & 1, l32 = lane & 31, g = lane >> 5;
     const int col = j0 + wj * 32 + l32;
@@ -1199,7 +1203,8 @@ hipError_t launch_gemm_tn(const GemmTN& g, hipStream_t s) {
         while (split > 1 && (size_t)split * g.Mo * g.No * g.batch > g.partial_elems) --split;
     }
     dim3 grid(cdiv(g.No, 64), cdiv(g.Mo, 64) * split, g.batch);
-    gemm_tn_kernel<<<grid, 256, 0, s>>>(g, split);
+    if (loads_to_lds(g.P) && loads_to_lds(g.Q)) gemm_tn_kernel<true><<<grid, 256, 0, s>>>(g, split);
+    else gemm_tn_kernel<false><<<grid, 256, 0, s>>>(g, split);
     if (split > 1) {
         const long n = (long)g.Mo * g.No * g.batch;
         tn_reduce_kernel<<<cdiv(n, 256), 256, 0, s>>>(g, split);
@@ -1211,12 +1216,15 @@ hipError_t launch_gemm_tn_grouped(GemmTNGroup& g, hipStream_t s) {
     if (g.n <= 0 || g.T <= 0) return hipSuccess;
     if (g.n > TN_GROUP_MAX) return hipErrorInvalidValue;
     int tiles = 0;
+    bool direct = true;
     for (int k = 0; k < g.n; ++k) {
         TnProblem& q = g.p[k];
+        direct &= loads_to_lds(q.P) && loads_to_lds(q.Q);
         if (q.Mo <= 0 || q.No <= 0 || (q.ldp & 7) || (q.ldq & 7) || (q.Mo & 7) || (q.No & 7)) return hipErrorInvalidValue;
         q.tile0 = tiles;
         tiles += cdiv(q.Mo, 64) * cdiv(q.No, 64);
     }
-    gemm_tn_grouped_kernel<<<tiles, 256, 0, s>>>(g);
+    if (direct) gemm_tn_grouped_kernel<true><<<tiles, 256, 0, s>>>(g);
+    else gemm_tn_grouped_kernel<false><<<tiles, 256, 0, s>>>(g);
     return hipGetLastError();
 }

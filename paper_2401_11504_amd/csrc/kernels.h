@@ -40,6 +40,10 @@ const char* low_rank_plan(const GemmNT& g);      // name of its tile, "general" 
 hipError_t launch_frozen(const GemmNT& g, hipStream_t s);
 const char* frozen_plan(const GemmNT& g);
 
+// Direct-to-LDS loads take addresses that are multiples of 4 bytes (4 and 8 give what 16 gives); operands that start anywhere else, which only a
+// caller of a single kernel can pass, come through registers.
+inline bool loads_to_lds(const void* p) { return ((uintptr_t)p & 3) == 0; }
+
 // C[Mo, No] (fp32) = alpha * P[T, Mo]^T Q[T, No]
 struct GemmTN {
     const bf16_t* P = nullptr; long ldp = 0;

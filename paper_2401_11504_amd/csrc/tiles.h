@@ -41,6 +41,17 @@ __device__ __forceinline__ void load_lds16(unsigned voff, const void* sbase, uns
 __device__ __forceinline__ void load_lds4(const void* p, unsigned lds_addr) {
     asm volatile("global_load_lds_dword %0, off" ::"v"(p), "{m0}"(lds_addr) : "memory");
 }
+// 16 bytes a lane to lds_addr + 16 lane, by such a load (DIRECT) or, where the address may be no multiple of 4, through registers (waited for at once)
+template <bool DIRECT>
+__device__ __forceinline__ void bring_lds16(unsigned voff, const void* sbase, unsigned lds_addr, int lane) {
+    if constexpr (DIRECT) {
+        load_lds16(voff, sbase, __builtin_amdgcn_readfirstlane(lds_addr));
+    } else {
+        typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) u32x4_t* lds_ptr_t;
+        *(lds_ptr_t)(uintptr_t)(lds_addr + 16 * lane) = *(const u32x4_t*)((const char*)sbase + voff);
+    }
+}
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

@@ -1,0 +1,40 @@
+"""Operands of the single kernels that start anywhere: one, two or four elements (2, 4, 8 bytes) behind a multiple of 16 bytes.
+
+Direct-to-LDS loads take multiples of 4 bytes; an operand that starts between them comes through registers.  Attention and the products over
+the tokens add in the same order either way: the same bits as aligned.  The products of two contiguous contractions may take another tile: a
+tolerance as in test_gpu_low_rank.py (one bf16 rounding of the result)."""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2401_11504_amd import synth  # noqa: E402
+from test_gpu_kernels import H, api  # noqa: E402,F401
+
+OFFSETS = [1, 2, 4]
+
+
+def at(x, n):
+    """x in memory that starts n elements behind a multiple of 16 bytes, rows 8 elements further apart; NaN around it"""
+    rows, cols = x.shape
+    ld = (cols + 15) // 8 * 8
+    flat = torch.full((rows * ld + 64,), float("nan"), dtype=x.dtype, device="cuda")
+    view = flat[n:n + rows * ld].view(rows, ld)[:, :cols]
+    view.copy_(x)
+    assert view.data_ptr() % 16 == n * x.element_size()
+    return view
+
+
+def draw(H, seed, rows, cols, std=1.0):
+    return H.to_dev_bf16(synth.normal(seed, (98, rows, cols), (rows, cols), std, True))
+
+
+@pytest.mark.parametrize("n", OFFSETS)
+@pytest.mark.parametrize("T,Mo,No", [(1, 8, 8), (200, 72, 136), (449, 64, 8)])
+def test_products_over_the_tokens(api, H, T, Mo, No, n):
+    P, Q = draw(H, 1, T, Mo), draw(H, 2, T, No)
+    outs = [torch.zeros(Mo, No, device="cuda") for _ in range(4)]
+    for out, p, q in zip(outs, (P, at(P, n), at(P, n), P), (Q, Q, at(Q, n), at(Q, n))):
+        api.tl_k_gemm_tn(p, q, out)
+    torch.cuda.synchronize()
+    assert all(torch.equal(outs[0], o) for o in outs[1:])
