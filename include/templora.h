@@ -416,7 +416,7 @@ tl_status tl_k_argmax(const float* x, int32_t n, int32_t* out, void* hip_stream)
 tl_status tl_k_swiglu_bwd(const uint16_t* da, const uint16_t* gu, int32_t T, int32_t f, uint16_t* dgu,
                           void* hip_stream);
 /* Causal attention forward: q, k, v, o bf16 [T, n_heads, d_head] with row strides ldq (shared by q, k, v)
- * and ldo; lse fp32 [n_heads, T] = log-sum-exp of the scaled scores of each row. */
+ * and ldo (multiples of 8 elements; the first elements lie anywhere, fastest at multiples of 4 bytes); lse fp32 [n_heads, T] = log-sum-exp of the scaled scores of each row. */
 tl_status tl_k_attention_fwd(const uint16_t* q, const uint16_t* k, const uint16_t* v, int32_t ldq, int32_t T,
                              int32_t n_heads, int32_t d_head, uint16_t* o, int32_t ldo, float* lse,
                              void* hip_stream);

@@ -54,7 +54,8 @@ __device__ __forceinline__ void write_rows_from_dT(bf16_t* __restrict__ dst, con
 // O by rows) and with this, heads of 128 / 64: 1024 tokens, 32 heads 28.8 and 25.4 / 16 heads 17.3 and 15.3; 2048 tokens 54.8 and 47.5 /
 // 30.8 and 28.9; 5120 tokens, 32 heads of 128 277 and 246 (870 TFLOP/s; the rest is the softmax between the two products of a tile, and at
 // 1024 tokens the heaviest block: 8 passes of two tiles where the mean is 4.5).  The order of every sum is the same in both.
-template <int DH, int NW, int KG>
+// DIRECT: q, k and v start at multiples of 4 bytes (else their tiles come through registers)
+template <int DH, int NW, int KG, bool DIRECT>
 __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                 const bf16_t* __restrict__ v, long ldq, int T,
                                                                 bf16_t* __restrict__ o, long ldo, float* __restrict__ lse,
@@ -69,7 +70,7 @@ __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t*
     const unsigned lds0 = (unsigned)(size_t)smem_raw;
     const unsigned group_at = kg * 4 * TB;                        // two buffers of a K and a V tile each
     const unsigned row_at = row_frag_at<DH>(lane), tr_at = tr_frag_at<DH>(lane);
-    const TileFetch<DH> fetch_rows(lane);
+    const TileFetch<DH, DIRECT> fetch_rows(lane);
     // Heaviest (latest) query blocks first, every head's before any head's second heaviest (longest job first).  The blocks of a head are
     // gridDim.y workgroups apart in dispatch order (x fastest), so with a multiple of eight heads they lie on one XCD, whose L2 fetches the
     // head's keys and values once; with a head's blocks side by side all eight XCDs fetch them (1024 tokens, 32 heads of 128:
@@ -102,7 +103,8 @@ __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t*
 #pragma unroll
     for (int j = 0; j < NI; ++j) fetch_rows(qh + (long)qr * ldq, (unsigned)ldq * 2, j, T - 1 - qr, lds0 + 2 * TB + w0 * RB);
     fetch(0);
-    wait_vmcnt<2 * NI>();
+    wait_vmcnt<DIRECT ? 2 * NI : 0>();
+    if constexpr (!DIRECT) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     bf16x8_t qf[C::NKS];
@@ -269,7 +271,8 @@ __device__ __forceinline__ void mfma32_score(f32x16_t& c, bf16x8_t a, bf16x8_t b
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
 
-template <int DH, bool DQ>
+// DIRECT: q, k, v and dO start at multiples of 4 bytes (else their tiles come through registers, ahead of the products instead of between them)
+template <int DH, bool DQ, bool DIRECT>
 __device__ __forceinline__ void attn_bwd_part(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, const bf16_t* __restrict__ d_o,
     const float* __restrict__ lse, const float* __restrict__ delta, long ldq, long ldo, int T, bf16_t* __restrict__ dq,
@@ -306,7 +309,7 @@ __device__ __forceinline__ void attn_bwd_part(
         lse2[j] = DQ ? lse_h[p] * 1.4426950408889634f : 0.f;
     }
 
-    const TileFetch<DH> fetch_rows(lane);
+    const TileFetch<DH, DIRECT> fetch_rows(lane);
     const unsigned ld1b = (unsigned)ldq * 2, ldx2b = (unsigned)ldx2 * 2;
     struct Fetch { const bf16_t *a, *b; const float* stats; int last; unsigned st; };
     auto fetch_of = [&](int tile, unsigned st) {
@@ -346,7 +349,8 @@ __device__ __forceinline__ void attn_bwd_part(
     // this lane's place in the fragments of block rows (chunk 2 ks + g of row l32 of a group)
     const unsigned p_at = (unsigned)((pg * 32 * NG + (NG == 2 ? 32 * sg : 0)) * RB) + row_frag_at<DH>(lane);
     auto p_frag = [&](unsigned at, int j, int ks) { return *(const bf16x8_t*)(smem + at + (p_at ^ (unsigned)(ks << 5 | j * 32 * RB))); };
-    wait_vmcnt<2 * NF>();
+    wait_vmcnt<DIRECT ? 2 * NF : 0>();
+    if constexpr (!DIRECT) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     bf16x8_t p1f[NG][KS], p2f[V_LDS ? 1 : NG][V_LDS ? 1 : KS];
@@ -472,8 +476,8 @@ __device__ __forceinline__ void attn_bwd_part(
                 constexpr int r = i + 1 + decltype(more)::value;
                 if constexpr (r < NS && r - (V_LDS && r >= B0 && r < C0 ? AHEAD_V : AHEAD) == i) read(std::integral_constant<int, r>{});
             });
-            if (i < NF - NI) fetch_piece(next, NI + i);
-            if (i >= NS - NI) fetch_piece(next, i - (NS - NI));
+            if (DIRECT && i < NF - NI) fetch_piece(next, NI + i);
+            if (DIRECT && i >= NS - NI) fetch_piece(next, i - (NS - NI));
 #pragma unroll
             for (int x = 0; x < NI_P; ++x) {
                 if (p_item(i + 2) == x && x % NG == 0) read_stats(0, x / NG);
@@ -506,7 +510,7 @@ __device__ __forceinline__ void attn_bwd_part(
     int i_step = 0;
     auto step = [&](auto what) {           // 0: nothing to do for this wave, 1: every score counts, 2: with the causal mask, 3: the first group only
         constexpr int WHAT = decltype(what)::value;
-        wait_vmcnt<NF>();                                                  // this tile has landed (the next may be in flight)
+        wait_vmcnt<DIRECT ? NF : 0>();                                     // this tile has landed (the next may be in flight)
         if constexpr (!DQ) {                                               // (the last tile is the first; dO: P is 0 there)
             if (i_step == 0 && tile1 * 64 > T) clear_rows<DH>(smem + st + TB, max(16 * wave, T - (tile1 - 1) * 64), 16 * wave + 16, lane);
         }
@@ -514,6 +518,7 @@ __device__ __forceinline__ void attn_bwd_part(
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         const Fetch next = fetch_of(tile_of(i_step + 2), st_next);         // (behind the last tile: that one again, unused)
+        if constexpr (WHAT && !DIRECT) fetch(next);
         if constexpr (WHAT) compute(std::bool_constant<(WHAT >= 2)>{}, std::integral_constant<int, WHAT == 3 ? 1 : NG>{}, st, tile_of(i_step) * 64 + 32 * sg, next);
         else fetch(next);
         st = st == C::V0 + (NST - 1) * STAGE ? C::V0 : st + STAGE;
@@ -638,7 +643,7 @@ __device__ __forceinline__ void attn_bwd_part(
 // list has an 8:1 causal imbalance between its workgroups at 1024 tokens, and the chip waits for the longest one twice; in one launch a
 // CU that finishes a light part picks up the next.  delta must already be in memory (the dK/dV parts read rows that other
 // workgroups' dQ parts own).  grid = (n blocks, heads, 2).
-template <int DH>
+template <int DH, bool DIRECT>
 __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_fused_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, long ldq, long ldo,
@@ -648,8 +653,8 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_fused_kernel(
     const int n = gridDim.x, heads = gridDim.y;
     const int idx = (blockIdx.z * heads + blockIdx.y) * n + blockIdx.x;   // position in dispatch order (x fastest)
     const int level = idx / (2 * heads), r = idx % (2 * heads), head = r % heads;
-    if (r < heads) attn_bwd_part<DH, false>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope, level, head, smem);
-    else attn_bwd_part<DH, true>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope, n - 1 - level, head, smem);
+    if (r < heads) attn_bwd_part<DH, false, DIRECT>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope, level, head, smem);
+    else attn_bwd_part<DH, true, DIRECT>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope, n - 1 - level, head, smem);
 }
 
 // ======================================================================== launchers
@@ -663,7 +668,8 @@ template <int DH, int NW, int KG>
 static hipError_t run_fwd(dim3 grid, const bf16_t* q, const bf16_t* k, const bf16_t* v, long ldq, int T, bf16_t* o,
                           long ldo, float* lse, float sl2, hipStream_t s) {
     const size_t lds = (size_t)KG * 4 * 64 * DH * sizeof(bf16_t);
-    auto kern = attn_fwd_kernel<DH, NW, KG>;
+    const bool direct = loads_to_lds(q) && loads_to_lds(k) && loads_to_lds(v);
+    auto kern = direct ? attn_fwd_kernel<DH, NW, KG, true> : attn_fwd_kernel<DH, NW, KG, false>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     kern<<<grid, NW * 64 * KG, lds, s>>>(q, k, v, ldq, T, o, ldo, lse, sl2);
@@ -715,7 +721,8 @@ static hipError_t run_bwd(const bf16_t* q, const bf16_t* k, const bf16_t* v, con
     attn_delta_kernel<DH><<<dgrid, 256, 0, s>>>(o, d_o, ldo, T, n_heads, delta);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    auto kern = attn_bwd_fused_kernel<DH>;
+    const bool direct = loads_to_lds(q) && loads_to_lds(k) && loads_to_lds(v) && loads_to_lds(d_o);
+    auto kern = direct ? attn_bwd_fused_kernel<DH, true> : attn_bwd_fused_kernel<DH, false>;
     e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
     if (e != hipSuccess) return e;
     kern<<<grid, 256, C::LDS, s>>>(q, k, v, d_o, lse, delta, ldq, ldo, T, dq, dk, dv, scale, rope);

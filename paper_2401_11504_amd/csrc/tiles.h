@@ -65,15 +65,16 @@ __device__ __forceinline__ int tile_swz(int row) {
 }
 // fetch i of a tile brings its rows i RPI .. (beyond `last`: that one again), each lane the chunk that belongs at its place; base: row 0, or a row that
 // is a multiple of 16 further (rows up to 63 from it: the offset has 32 bits)
-template <int DH>
+// DIRECT: the operand starts at a multiple of 4 bytes, else through registers
+template <int DH, bool DIRECT>
 struct TileFetch {
     static constexpr int CPR = DH / 8, RPI = 64 / CPR;         // chunks per row, rows per fetch
-    int fr;
+    int lane, fr;
     unsigned fc;
-    __device__ __forceinline__ TileFetch(int lane) : fr(lane / CPR), fc((unsigned)((lane % CPR) ^ tile_swz<DH>(lane / CPR)) << 4) {}
+    __device__ __forceinline__ TileFetch(int lane) : lane(lane), fr(lane / CPR), fc((unsigned)((lane % CPR) ^ tile_swz<DH>(lane / CPR)) << 4) {}
     __device__ __forceinline__ void operator()(const bf16_t* base, unsigned ldb, int i, int last, unsigned lds) const {
         const unsigned c = fc ^ (unsigned)((i * (RPI / 4) & 3) << 4);                  // swz of rows i RPI + fr
-        load_lds16((unsigned)min(i * RPI + fr, last) * ldb + c, base, __builtin_amdgcn_readfirstlane(lds + i * 1024));
+        bring_lds16<DIRECT>((unsigned)min(i * RPI + fr, last) * ldb + c, base, lds + i * 1024, lane);
     }
 };
 // rows first .. end - 1 of such a tile made zero by one wave.  Fetches bring the last row again in the place of rows behind it; where the products

@@ -38,3 +38,21 @@ def test_products_over_the_tokens(api, H, T, Mo, No, n):
         api.tl_k_gemm_tn(p, q, out)
     torch.cuda.synchronize()
     assert all(torch.equal(outs[0], o) for o in outs[1:])
+
+
+@pytest.mark.parametrize("n", OFFSETS)
+@pytest.mark.parametrize("T,nh,dh", [(1, 2, 64), (100, 2, 64), (321, 2, 64), (33, 2, 128), (129, 2, 128), (333, 2, 128)])
+def test_attention(api, H, T, nh, dh, n):
+    d = nh * dh
+    x, do = [draw(H, i, T, d) for i in range(3)], draw(H, 4, T, d)
+
+    def run(place):
+        q, k, v = (place(t) for t in x)
+        o, dq, dk, dv = (place(torch.zeros_like(do)) for _ in range(4))
+        lse, delta = (torch.zeros(nh, T, device="cuda") for _ in range(2))
+        api.tl_k_attention_fwd(q, k, v, nh, dh, o, lse)
+        api.tl_k_attention_bwd(q, k, v, o, place(do), lse, nh, dh, dq, dk, dv, delta)
+        torch.cuda.synchronize()
+        return o, lse, dq, dk, dv
+    for a, b in zip(run(lambda t: at(t, 0)), run(lambda t: at(t, n))):
+        assert torch.equal(a, b)
