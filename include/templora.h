@@ -329,7 +329,8 @@ tl_status tl_linear_step_static(const float* X, const float* W, const float* A, 
 
 /* C[M,N] = alpha * (A[M,K] B[N,K]^T + A2[M,K2] B2[N,K2]^T) (+ R[M,N] if R != NULL), bf16 MFMA, fp32 accumulate.
  * A2/B2 may be NULL (K2 = 0).  c_f32 != 0: C and R are fp32, else C is bf16 and R must be NULL.
- * lda/ldb/lda2/ldb2/ldc are row strides in elements; K, K2, lda, ldb, lda2, ldb2 multiples of 8.
+ * lda/ldb/lda2/ldb2/ldc are row strides in elements; K, K2, lda, ldb, lda2, ldb2 multiples of 8.  The operands start at any element (fastest
+ * at multiples of 4 bytes, C and R at multiples of 16); the same holds for the two products below.
  * Tile shape, contraction split and (for many-tile shapes whose last round of workgroups would be poorly filled)
  * a split into two launches over two ranges of columns or rows are chosen as in the update path.
  * workspace: NULL, or device fp32 scratch of workspace_elems floats for the partial results of a split contraction

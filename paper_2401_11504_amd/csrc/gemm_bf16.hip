@@ -628,12 +628,14 @@ static hipError_t run_nt(const GemmNT& g, int split_k, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Operands that start where direct-to-LDS loads can take them
+static bool nt_loads_to_lds(const GemmNT& g) { return loads_to_lds(g.A) && loads_to_lds(g.B) && loads_to_lds(g.A2) && loads_to_lds(g.B2); }
 // Whether the direct-to-LDS kernel takes this product.  Its offsets within an operand are 32-bit.  A contraction that is no
 // multiple of 64 (ranks below 64, ragged widths) costs it one edge tile, waited for before the loop starts: worth it from
 // 256 elements on (1024 x 1024 x 1024 with rank 16: 8 us against 14 us register-staged, back to back), below that the whole contraction
 // is one or two such waits.
 static bool nt_direct(const GemmNT& g) {
-    if (g.K <= 0) return false;
+    if (g.K <= 0 || !nt_loads_to_lds(g)) return false;
     if (((g.K % BK) || (g.K2 % BK)) && g.K < 256) return false;
     return (long)g.M * g.lda < (1L << 30) && (long)g.N * g.ldb < (1L << 30) && (long)g.M * g.lda2 < (1L << 30) &&
            (long)g.N * g.ldb2 < (1L << 30);
@@ -653,7 +655,7 @@ enum NtConfig {
     NT_256x192,         // 256x192, 2 / 3
     NT_256x256,         // 256x256, 2 / 3
     NT_256x256_SPLIT,
-    NT_REG_128x128,     // register-staged, for what nt_direct refuses: ragged contractions below 256 elements, operands beyond 1 Gi
+    NT_REG_128x128,     // register-staged, for what nt_direct refuses: ragged contractions below 256 elements, operands beyond 1 Gi or off by half a word
     NT_REG_128x64,
     NT_SKINNY           // N <= 64 per batch or few tiles: 64x64 tiles, contraction split over up to 16 workgroups
 };
@@ -985,7 +987,8 @@ static const WavesTile kWavesTiles[] = {{1, 1, "16x16"}, {1, 2, "16x32"}, {2, 2,
 // index into kWavesTiles of the fastest tile that promises less than `best` us, or -1
 static int pick_waves(const GemmNT& g, double best, int n_tiles = (int)(sizeof(kWavesTiles) / sizeof(kWavesTiles[0]))) {
     const size_t align = g.c_f32 ? 15 : 7;
-    if (g.K <= 0 || (g.N & 3) || (g.ldc & 3) || (g.bC & 3) || ((size_t)g.C & align) || ((size_t)g.R & 15)) return -1;
+    if (g.K <= 0 || (g.N & 3) || (g.ldc & 3) || (g.bC & 3) || ((size_t)g.C & align) || ((size_t)g.R & 15) || !nt_loads_to_lds(g))
+        return -1;
     if ((long)g.M * g.lda >= (1L << 30) || (long)g.N * g.ldb >= (1L << 30) || (long)g.M * g.lda2 >= (1L << 30) || (long)g.N * g.ldb2 >= (1L << 30))
         return -1;
     const double rows_us = 0.1e-6 * 2.0 * g.M * g.K * g.batch;

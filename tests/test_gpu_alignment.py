@@ -56,3 +56,34 @@ def test_attention(api, H, T, nh, dh, n):
         return o, lse, dq, dk, dv
     for a, b in zip(run(lambda t: at(t, 0)), run(lambda t: at(t, n))):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n", OFFSETS)
+@pytest.mark.parametrize("M,N,K,nb", [(37, 24, 1000, 1), (200, 48, 72, 3), (300, 64, 4096, 1), (1020, 56, 2048, 3)])
+def test_low_rank(api, H, M, N, K, nb, n):
+    A, B = draw(H, 1, M, nb * K), draw(H, 2, nb * N, K, 0.05)
+    out = torch.zeros(M, nb * N, dtype=torch.bfloat16, device="cuda")
+    api.tl_k_low_rank(at(A, n), at(B, n), out, nb, 0.5, torch.empty(16 << 20, device="cuda"))
+    torch.cuda.synchronize()
+    A64, B64 = A.double(), B.double()
+    ref = torch.cat([A64[:, i * K:(i + 1) * K] @ B64[i * N:(i + 1) * N].T for i in range(nb)], 1) * 0.5
+    err = out.double() - ref
+    assert err.norm() <= 2e-3 * ref.norm()
+    assert err.abs().max() <= 2e-2 * ref.norm() / ref.numel() ** 0.5
+
+
+@pytest.mark.parametrize("n", OFFSETS)
+@pytest.mark.parametrize("M,N,K,K2", [(200, 256, 688, 16), (300, 320, 1000, 72), (1024, 1024, 1024, 64), (1200, 2560, 512, 0)])
+def test_frozen(api, H, M, N, K, K2, n):
+    """two operand pairs, as tl_k_gemm_nt takes them"""
+    A, B = draw(H, 1, M, K), draw(H, 2, N, K, 0.05)
+    A2, B2 = (draw(H, 3, M, K2), draw(H, 4, N, K2, 0.05)) if K2 else (None, None)
+    out = torch.zeros(M, N, dtype=torch.bfloat16, device="cuda")
+    api.tl_k_gemm_nt(at(A, n), at(B, n), out, *((at(A2, n), at(B2, n)) if K2 else ()))
+    torch.cuda.synchronize()
+    ref = A.double() @ B.double().T
+    if K2:
+        ref += A2.double() @ B2.double().T
+    err = out.double() - ref
+    assert err.norm() <= 2e-3 * ref.norm()
+    assert err.abs().max() <= 2e-2 * ref.norm() / ref.numel() ** 0.5
