@@ -346,11 +346,16 @@ tl_status tl_k_gemm_nt(const uint16_t* A, int32_t lda, const uint16_t* B, int32_
 tl_status tl_k_low_rank(const uint16_t* A, int32_t lda, const uint16_t* B, int32_t ldb, int32_t M, int32_t N, int32_t K, int32_t batch,
                         float alpha, uint16_t* C, float* workspace, size_t workspace_elems, void* hip_stream);
 tl_status tl_k_low_rank_plan(int32_t M, int32_t N, int32_t K, int32_t batch, size_t workspace_elems, char* name_out, size_t name_cap);
-/* C = A B^T + A2 B2^T (+ R) as tl_k_gemm_nt for dense operands, by the rule of the update path: outputs and weights that are few go to the
- * kernel of the low-rank products (tl_k_frozen_plan: the name of its tile, or "general"; host only). */
-tl_status tl_k_frozen(const uint16_t* A, const uint16_t* B, int32_t M, int32_t N, int32_t K, const uint16_t* A2, const uint16_t* B2, int32_t K2,
-                      const float* R, void* C, int32_t c_f32, void* hip_stream);
-tl_status tl_k_frozen_plan(int32_t M, int32_t N, int32_t K, int32_t K2, char* name_out, size_t name_cap);
+/* The products of one projection group by the rule of the update path: outputs and weights that are few go to the kernel of the low-rank products
+ * (tl_k_frozen_plan: the name of its tile for dense operands, or "general"; host only).  For b < batch, C[:, b N .. b N + N - 1] = A B_b^T +
+ * A2[:, b K2 ..] B2_b^T (+ R), B_b and B2_b the rows b N .. of B [batch * N, K] and B2 [batch * N, K2], C (and R) [M, batch * N] of row stride ldc.
+ * parts_out (host, may be NULL; batch 1 only): receives how many partial tiles [M, N] (fp32, dense) were left in the workspace for the caller to add up
+ * together with R, C being written only where it is 0. */
+tl_status tl_k_frozen(const uint16_t* A, int32_t lda, const uint16_t* B, int32_t ldb, int32_t M, int32_t N, int32_t K, const uint16_t* A2,
+                      int32_t lda2, const uint16_t* B2, int32_t ldb2, int32_t K2, int32_t batch, const float* R, void* C, int32_t ldc,
+                      int32_t c_f32, float* workspace, size_t workspace_elems, int32_t* parts_out, void* hip_stream);
+tl_status tl_k_frozen_plan(int32_t M, int32_t N, int32_t K, int32_t K2, int32_t batch, size_t workspace_elems, int32_t deferred, char* name_out,
+                           size_t name_cap);
 /* Which tile configuration tl_k_gemm_nt uses for dense operands of these sizes with a workspace of workspace_elems
  * floats (0 = none): its name ("128x128", "128x128-split", "256x128", "256x128-split", "256x192", "256x256",
  * "256x256-split", "reg-128x128", "reg-128x64", "64x64", "64x64-split", "reg-64x64", "reg-64x64-split") into name_out

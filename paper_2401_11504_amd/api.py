@@ -87,8 +87,8 @@ _SIGS = {
                      _sz, _vp],
     "tl_k_low_rank": [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _i32, _f32, _vp, _vp, _sz, _vp],
     "tl_k_low_rank_plan": [_i32, _i32, _i32, _i32, _sz, C.c_char_p, _sz],
-    "tl_k_frozen": [_vp, _vp, _i32, _i32, _i32, _vp, _vp, _i32, _vp, _vp, _i32, _vp],
-    "tl_k_frozen_plan": [_i32, _i32, _i32, _i32, C.c_char_p, _sz],
+    "tl_k_frozen": [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _vp, _i32, _vp, _i32, _i32, _i32, _vp, _vp, _i32, _i32, _vp, _sz, C.POINTER(_i32), _vp],
+    "tl_k_frozen_plan": [_i32] * 5 + [_sz, _i32, C.c_char_p, _sz],
     "tl_k_gemm_nt_plan": [_i32, _i32, _i32, _i32, _sz, C.c_char_p, _sz, C.POINTER(_i32), C.POINTER(_i32)],
     "tl_k_linear_step_plan": [_i32] * 4 + [_f32, _i32, C.c_char_p, _sz],
     "tl_k_gemm_tn": [_vp, _i32, _vp, _i32, _i32, _i32, _i32, _f32, _vp, _i32, _vp],
@@ -352,16 +352,22 @@ def tl_k_low_rank_plan(M, N, K, batch=1, workspace_elems=0):
     return buf.value.decode()
 
 
-def tl_k_frozen(A, B, out, A2=None, B2=None, R=None, stream=None):
-    """dense operands: A [M, K], B [N, K], A2 [M, K2], B2 [N, K2], R fp32 [M, N]; out bf16 or fp32 [M, N]"""
-    _chk(_lib.tl_k_frozen(_dp(A), _dp(B), A.shape[0], B.shape[0], A.shape[1], _dp(A2), _dp(B2), A2.shape[1] if A2 is not None else 0, _dp(R),
-                          _dp(out), int(out.dtype == torch.float32), _s(stream)))
+def tl_k_frozen(A, B, out, A2=None, B2=None, R=None, batch=1, workspace=None, deferred=False, stream=None):
+    """A [M, K], B [batch N, K], A2 [M, batch K2], B2 [batch N, K2]; out bf16 or fp32 [M, batch N], R fp32 of out's strides
+    -> partial tiles left in the workspace (deferred), None otherwise"""
+    parts = _i32(0) if deferred else None
+    two = A2 is not None
+    _chk(_lib.tl_k_frozen(_dp(A), A.stride(0), _dp(B), B.stride(0), A.shape[0], B.shape[0] // batch, A.shape[1], _dp(A2), A2.stride(0) if two else 0,
+                          _dp(B2), B2.stride(0) if two else 0, B2.shape[1] if two else 0, batch, _dp(R), _dp(out), out.stride(0),
+                          int(out.dtype == torch.float32), _dp(workspace), workspace.numel() if workspace is not None else 0,
+                          C.byref(parts) if deferred else None, _s(stream)))
+    return parts.value if deferred else None
 
 
-def tl_k_frozen_plan(M, N, K, K2=0):
+def tl_k_frozen_plan(M, N, K, K2=0, batch=1, workspace_elems=0, deferred=False):
     """-> name of the tile"""
     buf = C.create_string_buffer(32)
-    _chk(_lib.tl_k_frozen_plan(M, N, K, K2, buf, 32))
+    _chk(_lib.tl_k_frozen_plan(M, N, K, K2, batch, workspace_elems, int(deferred), buf, 32))
     return buf.value.decode()
 
 

@@ -1443,23 +1443,37 @@ extern "C" tl_status tl_k_gemm_nt_plan(int32_t M, int32_t N, int32_t K, int32_t 
     if (n_launches_out) *n_launches_out = two ? 2 : 1;
     return TL_OK;
 }
-static GemmNT frozen_product(const uint16_t* A, const uint16_t* B, int32_t M, int32_t N, int32_t K, const uint16_t* A2, const uint16_t* B2,
-                             int32_t K2, const float* R, void* C, int32_t c_f32) {
+static GemmNT frozen_product(const uint16_t* A, int32_t lda, const uint16_t* B, int32_t ldb, int32_t M, int32_t N, int32_t K, const uint16_t* A2,
+                             int32_t lda2, const uint16_t* B2, int32_t ldb2, int32_t K2, int32_t batch, const float* R, void* C, int32_t ldc,
+                             int32_t c_f32) {
     GemmNT g;
-    g.A = A; g.lda = K; g.B = B; g.ldb = K; g.M = M; g.N = N; g.K = K;
-    g.A2 = K2 ? A2 : nullptr; g.lda2 = K2; g.B2 = K2 ? B2 : nullptr; g.ldb2 = K2; g.K2 = K2;
-    g.R = R; g.C = C; g.ldc = N; g.c_f32 = c_f32;
+    g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.M = M; g.N = N; g.K = K;
+    if (K2) { g.A2 = A2; g.lda2 = lda2; g.B2 = B2; g.ldb2 = ldb2; g.K2 = K2; g.bA2 = K2; g.bB2 = (long)N * ldb2; }
+    g.batch = batch; g.bB = (long)N * ldb; g.bC = N;
+    g.R = R; g.C = C; g.ldc = ldc; g.c_f32 = c_f32;
     return g;
 }
-extern "C" tl_status tl_k_frozen(const uint16_t* A, const uint16_t* B, int32_t M, int32_t N, int32_t K, const uint16_t* A2, const uint16_t* B2,
-                                 int32_t K2, const float* R, void* C, int32_t c_f32, void* hip_stream) {
-    KARGS_OK(A && B && C && M >= 0 && N >= 0 && K >= 0 && K2 >= 0 && (K2 == 0 || (A2 && B2)), "tl_k_frozen");
-    HIPCHK(launch_frozen(frozen_product(A, B, M, N, K, A2, B2, K2, R, C, c_f32), (hipStream_t)hip_stream));
+extern "C" tl_status tl_k_frozen(const uint16_t* A, int32_t lda, const uint16_t* B, int32_t ldb, int32_t M, int32_t N, int32_t K, const uint16_t* A2,
+                                 int32_t lda2, const uint16_t* B2, int32_t ldb2, int32_t K2, int32_t batch, const float* R, void* C, int32_t ldc,
+                                 int32_t c_f32, float* workspace, size_t workspace_elems, int32_t* parts_out, void* hip_stream) {
+    KARGS_OK(A && B && C && M >= 0 && N >= 0 && K >= 0 && K2 >= 0 && batch >= 0 && (K2 == 0 || (A2 && B2)), "tl_k_frozen");
+    GemmNT g = frozen_product(A, lda, B, ldb, M, N, K, A2, lda2, B2, ldb2, K2, batch, R, C, ldc, c_f32);
+    if (workspace && workspace_elems > 0) { g.partial = workspace; g.partial_elems = workspace_elems; }
+    int parts = 0;
+    if (parts_out) g.deferred = &parts;
+    HIPCHK(launch_frozen(g, (hipStream_t)hip_stream));
+    if (parts_out) *parts_out = parts;
     return TL_OK;
 }
-extern "C" tl_status tl_k_frozen_plan(int32_t M, int32_t N, int32_t K, int32_t K2, char* name_out, size_t name_cap) {
-    KARGS_OK(name_out && name_cap > 0 && M > 0 && N > 0 && K > 0 && K2 >= 0, "tl_k_frozen_plan");
-    snprintf(name_out, name_cap, "%s", frozen_plan(frozen_product(nullptr, nullptr, M, N, K, nullptr, nullptr, K2, nullptr, nullptr, 0)));
+extern "C" tl_status tl_k_frozen_plan(int32_t M, int32_t N, int32_t K, int32_t K2, int32_t batch, size_t workspace_elems, int32_t deferred,
+                                      char* name_out, size_t name_cap) {
+    KARGS_OK(name_out && name_cap > 0 && M > 0 && N > 0 && K > 0 && K2 >= 0 && batch > 0, "tl_k_frozen_plan");
+    GemmNT g = frozen_product(nullptr, K, nullptr, K, M, N, K, nullptr, batch * K2, nullptr, K2, K2, batch, nullptr, nullptr, batch * N, 0);
+    static float dummy;      // nothing is launched: only whether there is a workspace counts
+    int parts = 0;
+    if (workspace_elems > 0) { g.partial = &dummy; g.partial_elems = workspace_elems; }
+    if (deferred) g.deferred = &parts;
+    snprintf(name_out, name_cap, "%s", frozen_plan(g));
     return TL_OK;
 }
 static GemmNT low_rank_product(const uint16_t* A, int32_t lda, const uint16_t* B, int32_t ldb, int32_t M, int32_t N, int32_t K, int32_t batch,

@@ -53,42 +53,83 @@ def test_low_rank(M, N, K, nb, tile):
     assert err.abs().max() <= 2e-2 * ref.norm() / ref.numel() ** 0.5
 
 
-#         M, N, K, K2, tile
-FROZEN = [(200, 256, 256, 16, "16x16"), (200, 256, 688, 16, "16x16"), (1, 8, 8, 8, "16x16"), (45, 100, 2000, 40, "16x16"), (200, 688, 256, 16, "32x32"),
-          (300, 512, 1408, 8, "32x32"), (290, 508, 1400, 72, "32x32"), (100, 500, 4096, 64, "16x16"), (300, 400, 2048, 0, "16x32"),
-          (500, 636, 1024, 192, "32x48"), (512, 1024, 2816, 16, "32x64"), (1024, 1024, 1024, 16, "general"), (128, 4096, 4096, 64, "general")]
+#         M, N, K, K2, batch, tile
+FROZEN = [(200, 256, 256, 16, 1, "16x16"), (200, 256, 688, 16, 1, "16x16"), (1, 8, 8, 8, 1, "16x16"), (45, 100, 2000, 40, 1, "16x16"),
+          (200, 688, 256, 16, 1, "32x32"), (300, 512, 1408, 8, 1, "32x32"), (290, 508, 1400, 72, 1, "32x32"), (100, 500, 4096, 64, 1, "16x16"),
+          (300, 400, 2048, 0, 1, "16x32"), (500, 636, 1024, 192, 1, "32x48"), (512, 1024, 2816, 16, 1, "32x64"), (1024, 1024, 1024, 16, 1, "general"),
+          (128, 4096, 4096, 64, 1, "general"),
+          # one input, three outputs side by side, each with its own share of the second input: the q|k|v product
+          (200, 256, 256, 16, 3, "32x32"), (37, 100, 704, 8, 3, "16x16"), (190, 252, 248, 24, 3, "32x32"), (300, 508, 1000, 24, 3, "32x64"),
+          (200, 512, 512, 64, 3, "32x48"), (300, 1024, 1024, 16, 3, "general")]
 
 
 def test_the_frozen_cases_reach_their_tiles():
     from paper_2401_11504_amd import api
-    for M, N, K, K2, tile in FROZEN:
-        assert api.tl_k_frozen_plan(M, N, K, K2) == tile, (M, N, K, K2)
-    assert {c[4] for c in FROZEN} == {"16x16", "16x32", "32x32", "32x48", "32x64", "general"}
+    for *sizes, tile in FROZEN:
+        for scratch in (0, SCRATCH):
+            assert api.tl_k_frozen_plan(*sizes, scratch) == tile, sizes
+    assert {c[5] for c in FROZEN} == {"16x16", "16x32", "32x32", "32x48", "32x64", "general"}
+
+
+def frozen_operands(M, N, K, K2, nb, f32):
+    """operands with NaN around them, an output with a row and 8 columns more than it needs, the fp64 product"""
+    from paper_2401_11504_amd import harness as H
+
+    def draw(i, rows, cols, std):
+        full = np.full((rows + 8, cols + 8), np.nan)
+        full[:rows, :cols] = synth.normal(i, (63, M, N), (rows, cols), std, True)
+        return H.to_dev_bf16(full)[:rows, :cols]
+    A, B = draw(1, M, K, 1.0), draw(2, nb * N, K, 0.05)
+    A2, B2 = (draw(3, M, nb * K2, 1.0), draw(4, nb * N, K2, 0.05)) if K2 else (None, None)
+    full = torch.full((M + 1, nb * N + 8), 3.0, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda")
+    R = None
+    if f32:
+        R = torch.full((M, nb * N + 8), float("nan"), device="cuda")
+        R[:, :nb * N] = torch.randn(M, nb * N, device="cuda", generator=torch.Generator(device="cuda").manual_seed(5))
+    ref = A.double() @ B.double().T
+    if K2:
+        ref += torch.cat([A2.double()[:, b * K2:(b + 1) * K2] @ B2.double()[b * N:(b + 1) * N].T for b in range(nb)], 1)
+    return A, B, A2, B2, full, R, ref + R[:, :nb * N].double() if f32 else ref
+
+
+def check_frozen(got, ref, tol):
+    err = got.double() - ref
+    assert err.norm() <= tol * ref.norm()
+    assert err.abs().max() <= 10 * tol * ref.norm() / ref.numel() ** 0.5
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("f32", [False, True])
-@pytest.mark.parametrize("M,N,K,K2,tile", FROZEN)
-def test_frozen(M, N, K, K2, tile, f32):
+@pytest.mark.parametrize("M,N,K,K2,nb,tile", FROZEN)
+def test_frozen(M, N, K, K2, nb, tile, f32):
     """bf16 output as above; fp32 output with a residual: fp32 sums of bf16 products, 1e-5 in the L2 sense (2^-24 times a few roundings of up to
     4288 terms)."""
-    from paper_2401_11504_amd import api, harness as H
-
-    def draw(i, rows, cols, std):
-        return H.to_dev_bf16(synth.normal(i, (63, M, N), (rows, cols), std, True))
-    A, B = draw(1, M, K, 1.0), draw(2, N, K, 0.05)
-    A2, B2 = (draw(3, M, K2, 1.0), draw(4, N, K2, 0.05)) if K2 else (None, None)
-    R = torch.randn(M, N, device="cuda", generator=torch.Generator(device="cuda").manual_seed(5)) if f32 else None
-    out = torch.full((M + 1, N), 3.0, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda")
-    api.tl_k_frozen(A, B, out[:M], A2, B2, R)
+    from paper_2401_11504_amd import api
+    A, B, A2, B2, full, R, ref = frozen_operands(M, N, K, K2, nb, f32)
+    api.tl_k_frozen(A, B, full[:M, :nb * N], A2, B2, R, nb)
     torch.cuda.synchronize()
-    assert torch.all(out[M] == 3.0)
-    ref = A.double() @ B.double().T
-    if K2:
-        ref += A2.double() @ B2.double().T
-    if f32:
-        ref += R.double()
-    err = out[:M].double() - ref
-    tol = 1e-5 if f32 else 2e-3
-    assert err.norm() <= tol * ref.norm()
-    assert err.abs().max() <= 10 * tol * ref.norm() / ref.numel() ** 0.5
+    assert torch.all(full[M] == 3.0) and torch.all(full[:, nb * N:] == 3.0)
+    check_frozen(full[:M, :nb * N], ref, 1e-5 if f32 else 2e-3)
+
+
+#           M, N, K, K2, tile, partial tiles
+DEFERRED = [(200, 256, 688, 16, "16x16", 0), (290, 508, 1400, 72, "32x32", 0), (512, 1024, 2816, 16, "32x64", 0), (1024, 1024, 1024, 16, "general", 0),
+            (256, 2048, 8192, 64, "general", 8)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,K2,tile,parts", DEFERRED)
+def test_frozen_deferred(M, N, K, K2, tile, parts):
+    """What is handed over: no partial tiles and an output that is complete, residual included, or the tiles and an output that is untouched."""
+    from paper_2401_11504_amd import api
+    assert api.tl_k_frozen_plan(M, N, K, K2, 1, SCRATCH, True) == tile
+    A, B, A2, B2, full, R, ref = frozen_operands(M, N, K, K2, 1, True)
+    ws = torch.full((SCRATCH,), float("nan"), device="cuda")
+    assert api.tl_k_frozen(A, B, full[:M, :N], A2, B2, R, 1, ws, deferred=True) == parts
+    torch.cuda.synchronize()
+    assert torch.all(full[M] == 3.0) and torch.all(full[:, N:] == 3.0)
+    if parts:
+        assert torch.all(full == 3.0)
+        check_frozen(ws[:parts * M * N].view(parts, M, N).double().sum(0) + R[:, :N].double(), ref, 1e-5)
+    else:
+        check_frozen(full[:M, :N], ref, 1e-5)
