@@ -13,6 +13,7 @@
 // reads of 8 consecutive rows fall into distinct banks.
 #include "kernels.h"
 #include "tiles.h"
+#include <algorithm>
 #include <type_traits>
 
 // ======================================================================== NT
@@ -628,6 +629,11 @@ static hipError_t run_nt(const GemmNT& g, int split_k, hipStream_t s) {
     return hipGetLastError();
 }
 
+// what every kernel here asks of a product
+static bool nt_valid(const GemmNT& g) {
+    return !((g.K & 7) || (g.K2 & 7) || (g.lda & 7) || (g.ldb & 7) || (g.lda2 & 7) || (g.ldb2 & 7) || (g.bA & 7) || (g.bB & 7) || (g.bA2 & 7) ||
+             (g.bB2 & 7)) && (g.c_f32 || !g.R);
+}
 // Operands that start where direct-to-LDS loads can take them
 static bool nt_loads_to_lds(const GemmNT& g) { return loads_to_lds(g.A) && loads_to_lds(g.B) && loads_to_lds(g.A2) && loads_to_lds(g.B2); }
 // Whether the direct-to-LDS kernel takes this product.  Its offsets within an operand are 32-bit.  A contraction that is no
@@ -816,9 +822,7 @@ hipError_t launch_gemm_nt(const GemmNT& g, hipStream_t s) {
         if (g.batch != 1 || g.alpha != 1.f) return hipErrorInvalidValue;
     }
     if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
-    if ((g.K & 7) || (g.K2 & 7) || (g.lda & 7) || (g.ldb & 7) || (g.lda2 & 7) || (g.ldb2 & 7)) return hipErrorInvalidValue;
-    if ((g.bA & 7) || (g.bB & 7) || (g.bA2 & 7) || (g.bB2 & 7)) return hipErrorInvalidValue;
-    if (!g.c_f32 && g.R) return hipErrorInvalidValue;
+    if (!nt_valid(g)) return hipErrorInvalidValue;
     int split = 1;
     switch (choose_nt(g, &split)) {
         case NT_128x128: return run_nt_dl<128, 128, 4, false>(g, s);
@@ -1001,10 +1005,6 @@ static int pick_waves(const GemmNT& g, double best, int n_tiles = (int)(sizeof(k
     }
     return pick;
 }
-static bool nt_valid(const GemmNT& g) {
-    return !((g.K & 7) || (g.K2 & 7) || (g.lda & 7) || (g.ldb & 7) || (g.lda2 & 7) || (g.ldb2 & 7) || (g.bA & 7) || (g.bB & 7) || (g.bA2 & 7) ||
-             (g.bB2 & 7)) && (g.c_f32 || !g.R);
-}
 static hipError_t launch_waves(const GemmNT& g, int tile, hipStream_t s) {
     switch (tile) {
         case 0: return run_waves<1, 1, 2>(g, s);
@@ -1016,18 +1016,30 @@ static hipError_t launch_waves(const GemmNT& g, int tile, hipStream_t s) {
         default: return run_waves<4, 4, 1>(g, s);
     }
 }
-// A low-rank product.  On the other side 64x64 tiles of the general kernel: with the contraction split and reduced 10 us and 0.095 per
-// million operand bytes; whole, for short contractions, 2.5 us and 3.5 per 1000 elements.
-static int pick_low_rank(const GemmNT& g) {
+// What the general kernel promises for a low-rank product, by the route choose_nt takes with the scratch there is: whole, for short contractions, 2.5 us
+// and 3.5 per 1000 elements; long ones split and reduced 10 us and 0.095 per million operand bytes (no less than a part takes), whole 2.5
+// per 1000 elements and the rows of A for every column tile, 3.5 where tiles queue; many 128-wide tiles by their own model.  us whole and here:
+// 64 columns of 11008, two at once, 2048 rows 33.6 and 20.2, 64 rows 30.6 and 10.5; 192 columns of 4096, 5120 rows 22.8 and 19.1, 12000 rows 35.2
+// and 38.3, 16384 rows 48.8 and 54.3; 64 columns, 16384 rows 24.6 and 25.7.
+static double general_low_rank_us(const GemmNT& g) {
+    if (g.split_k == 1) return 2.5 + 3.5e-3 * g.K;
+    int split = 1;
+    if (choose_nt(g, &split) != NT_SKINNY) return pick_nt(g).us;
     const long t64 = (long)cdiv(g.M, 64) * cdiv(g.N, 64) * g.batch;
-    return pick_waves(g, g.split_k == 1 ? 2.5 + 3.5e-3 * g.K : 10.0 + 0.095e-6 * 256.0 * g.K * t64);
+    if (split > 1) return std::max(10.0 + 0.095e-6 * 256.0 * g.K * t64, 5.5 + 2.5e-3 * g.K / split);
+    const double rows_us = 0.1e-6 * 2.0 * g.M * g.K * g.batch * cdiv(g.N, 64);
+    return 2.5 + rows_us + (t64 <= 256 ? 2.5e-3 * g.K : 3.5e-3 * g.K * cdiv(t64, 256));
+}
+// index into kWavesTiles, or -1 for the general kernel (what that refuses is refused there)
+static int pick_low_rank(const GemmNT& g) {
+    if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.deferred || !nt_valid(g)) return -1;
+    return pick_waves(g, general_low_rank_us(g));
 }
 const char* low_rank_plan(const GemmNT& g) {
     const int i = pick_low_rank(g);
     return i < 0 ? "general" : kWavesTiles[i].name;
 }
 hipError_t launch_low_rank(const GemmNT& g, hipStream_t s) {
-    if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.deferred || !nt_valid(g)) return launch_gemm_nt(g, s);
     const int i = pick_low_rank(g);
     return i < 0 ? launch_gemm_nt(g, s) : launch_waves(g, i, s);
 }

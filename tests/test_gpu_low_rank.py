@@ -28,9 +28,24 @@ def test_the_cases_reach_every_tile():
     assert {c[4] for c in CASES} == {"16x16", "16x32", "32x32", "32x48", "32x64", "48x64", "64x64", "general"}
 
 
+def test_the_other_side_is_what_the_general_kernel_would_do():
+    """without scratch, or with too little, it does not split; many rows of 192 columns take its 128-wide tiles; what it refuses it gets"""
+    from paper_2401_11504_amd import api
+    assert [api.tl_k_low_rank_plan(2048, 64, 11008, 2, n) for n in (SCRATCH, 2048 * 64 * 2 - 1, 1, 0)] == ["general", "32x32", "32x32", "32x32"]
+    assert [api.tl_k_low_rank_plan(64, 64, 11008, 2, n) for n in (SCRATCH, 0)] == ["general", "16x16"]
+    assert [api.tl_k_low_rank_plan(M, 192, 4096, 1, SCRATCH) for M in (5120, 12000, 16384)] == ["64x64", "general", "general"]
+    assert api.tl_k_low_rank_plan(200, 16, 1001, 1, SCRATCH) == "general"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,nb", [(2044, 60, 11000, 2), (64, 64, 11008, 2), (5120, 64, 2048, 2)])
+def test_without_scratch(M, N, K, nb):
+    test_low_rank(M, N, K, nb, None, 0)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K,nb,tile", CASES)
-def test_low_rank(M, N, K, nb, tile):
+def test_low_rank(M, N, K, nb, tile, scratch=SCRATCH):
     from paper_2401_11504_amd import api, harness as H
     # what lies behind the contraction in memory is NaN: it must not be multiplied, not even by zero
     lda, ldb = (nb * K + 71) // 8 * 8, (K + 71) // 8 * 8
@@ -39,7 +54,7 @@ def test_low_rank(M, N, K, nb, tile):
     b[:, :K] = synth.normal(2, (62, M, N), (nb * N, K), 0.05, True)
     A, B = H.to_dev_bf16(a)[:, :nb * K], H.to_dev_bf16(b)[:, :K]
     out = torch.full((M + 1, nb * N), 3.0, dtype=torch.bfloat16, device="cuda")
-    ws = torch.empty(SCRATCH, dtype=torch.float32, device="cuda")
+    ws = torch.empty(scratch, dtype=torch.float32, device="cuda") if scratch else None
     for _ in range(2):                  # twice: the same bits
         last = out.clone()
         api.tl_k_low_rank(A, B, out, nb, 0.5, ws)
