@@ -984,23 +984,24 @@ static hipError_t run_waves(const GemmNT& g, hipStream_t s) {
     kern<<<tiles_m * tiles_n * g.batch, 512, lds, s>>>(g, tiles_m, tiles_n);
     return hipGetLastError();
 }
-// What a tile costs: launch, ends and first loads, the stream of the busiest CU, the rows of A on their way from memory (us; within 15 % of
-// the timings above but for long contractions of few rows, which are faster).
+// What a tile costs: launch, ends and first loads (2.5 us), the stream of the busiest CU, and what the way from memory adds: for low-rank products the
+// rows of A (us; within 15 % of the timings above but for long contractions of few rows, which are faster), for frozen ones, whose weights are
+// cold, the operands of all tiles (see pick_small).
 struct WavesTile { int fm, fn; const char* name; };
 static const WavesTile kWavesTiles[] = {{1, 1, "16x16"}, {1, 2, "16x32"}, {2, 2, "32x32"}, {2, 3, "32x48"}, {2, 4, "32x64"}, {3, 4, "48x64"}, {4, 4, "64x64"}};
-// index into kWavesTiles of the fastest tile that promises less than `best` us, or -1
-static int pick_waves(const GemmNT& g, double best, int n_tiles = (int)(sizeof(kWavesTiles) / sizeof(kWavesTiles[0]))) {
+// index into kWavesTiles of the fastest of the first n_tiles that promises less than `best` us, or -1
+static int pick_waves(const GemmNT& g, double best, int n_tiles, double rows_us, double all_us) {
     const size_t align = g.c_f32 ? 15 : 7;
     if (g.K <= 0 || (g.N & 3) || (g.ldc & 3) || (g.bC & 3) || ((size_t)g.C & align) || ((size_t)g.R & 15) || !nt_loads_to_lds(g))
         return -1;
     if ((long)g.M * g.lda >= (1L << 30) || (long)g.N * g.ldb >= (1L << 30) || (long)g.M * g.lda2 >= (1L << 30) || (long)g.N * g.ldb2 >= (1L << 30))
         return -1;
-    const double rows_us = 0.1e-6 * 2.0 * g.M * g.K * g.batch;
     int pick = -1;
     for (int i = 0; i < n_tiles; ++i) {
         const WavesTile& t = kWavesTiles[i];
         const long n = (long)cdiv(g.M, 16 * t.fm) * cdiv(g.N, 16 * t.fn) * g.batch;
-        const double us = 2.5 + 11.4e-6 * 32.0 * (t.fm + t.fn) * (g.K + g.K2) * (double)((n + 255) / 256) + rows_us;
+        const double bytes = 32.0 * (t.fm + t.fn) * (g.K + g.K2);
+        const double us = 2.5 + 11.4e-6 * bytes * (double)((n + 255) / 256) + rows_us + all_us * bytes * n;
         if (us < best) { best = us; pick = i; }
     }
     return pick;
@@ -1033,7 +1034,7 @@ static double general_low_rank_us(const GemmNT& g) {
 // index into kWavesTiles, or -1 for the general kernel (what that refuses is refused there)
 static int pick_low_rank(const GemmNT& g) {
     if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.deferred || !nt_valid(g)) return -1;
-    return pick_waves(g, general_low_rank_us(g));
+    return pick_waves(g, general_low_rank_us(g), (int)(sizeof(kWavesTiles) / sizeof(kWavesTiles[0])), 0.1e-6 * 2.0 * g.M * g.K * g.batch, 0.0);
 }
 const char* low_rank_plan(const GemmNT& g) {
     const int i = pick_low_rank(g);
@@ -1043,21 +1044,25 @@ hipError_t launch_low_rank(const GemmNT& g, hipStream_t s) {
     const int i = pick_low_rank(g);
     return i < 0 ? launch_gemm_nt(g, s) : launch_waves(g, i, s);
 }
-// A frozen product of a small decoder or a short sample: up to half a million outputs and four million weights (us in the general kernel
-// and here: 200 x 256 x 688 7.0 and 4.9, 300 x 512 x 1408 8.3 and 5.8, 512 x 1024 x 2816 12.8 and 11.8, 100 x 2048 x 2048 9.8 and 9.0; beyond,
-// 128 x 4096 x 4096 22.8 and 22.9, 1024 x 1024 x 1024 7.8 and 9.6, 1024 x 1024 x 2816 14.3 and 15.2).  The general kernel's model is that of launches
-// that follow one another closely; behind another kernel's end its chain of barriers costs 1 us more.
+// A frozen product of a small decoder or a short sample: up to half a million outputs and, each of a batch, four million weights (us in the general kernel
+// and here: 200 x 256 x 688 7.0 and 4.9, 300 x 512 x 1408 8.3 and 5.8, 16 x 2048 x 2048 8.4 and 4.9; three at once, 33 x 1024 x 1024 6.4 and 5.5, 16 x 2048 x
+// 2048 8.6 and 6.9; beyond, 128 x 4096 x 4096 22.8 and 22.9, 1024 x 1024 x 1024 7.8 and 9.6, 1024 x 1024 x 2816 14.3 and 15.2).  Tiles whose weights are cold get
+// 67 MB a us on top of the stream of a CU, and 32x64 ones lose to the general kernel where few rows share many columns: 200 x 2048 x 2048
+// 9.0 and 12.0, three times 85 x 2048 x 2048 9.4 and 14.4.  The general kernel's model is that of launches that follow one another closely;
+// behind another kernel's end its chain of barriers costs 1 us more.  us of a layer with every product in the general kernel, with all five tiles by the
+// stream of a CU alone, and so: 512 wide, 200 tokens 165, 153, 154; 1024 wide, 512 tokens 208, 202, 203; 1792 wide, 200 tokens 234, 238, 235; 2048 wide, 256
+// tokens 281, 288, 281 (ten lengths of 64 to 900 tokens, nine widths: no layer slower than in the general kernel by more than 1.1 %, the noise).
 static int pick_small(const GemmNT& g) {
+    if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || !nt_valid(g) || (g.deferred && (g.batch != 1 || g.alpha != 1.f))) return -1;
     if (g.K <= 0 || g.split_k > 1 || (long)g.M * g.N * g.batch > (1L << 19) || (long)g.N * g.K > (1L << 22)) return -1;
     const double general = nt_direct(g) ? pick_nt(g).us : 2.0 + 4.2e-3 * (g.K + g.K2);
-    return pick_waves(g, general + 1.0, 5);
+    return pick_waves(g, general + 1.0, 2L * g.N * g.batch <= 9L * g.M ? 5 : 4, 0.0, 1.5e-8);
 }
 const char* frozen_plan(const GemmNT& g) {
     const int i = pick_small(g);
     return i < 0 ? "general" : kWavesTiles[i].name;
 }
 hipError_t launch_frozen(const GemmNT& g, hipStream_t s) {
-    if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || !nt_valid(g) || (g.deferred && (g.batch != 1 || g.alpha != 1.f))) return launch_gemm_nt(g, s);
     const int i = pick_small(g);
     if (i < 0) return launch_gemm_nt(g, s);
     if (g.deferred) *g.deferred = 0;

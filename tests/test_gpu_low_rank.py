@@ -74,8 +74,10 @@ FROZEN = [(200, 256, 256, 16, 1, "16x16"), (200, 256, 688, 16, 1, "16x16"), (1, 
           (300, 400, 2048, 0, 1, "16x32"), (500, 636, 1024, 192, 1, "32x48"), (512, 1024, 2816, 16, 1, "32x64"), (1024, 1024, 1024, 16, 1, "general"),
           (128, 4096, 4096, 64, 1, "general"),
           # one input, three outputs side by side, each with its own share of the second input: the q|k|v product
-          (200, 256, 256, 16, 3, "32x32"), (37, 100, 704, 8, 3, "16x16"), (190, 252, 248, 24, 3, "32x32"), (300, 508, 1000, 24, 3, "32x64"),
-          (200, 512, 512, 64, 3, "32x48"), (300, 1024, 1024, 16, 3, "general")]
+          (200, 256, 256, 16, 3, "32x32"), (37, 100, 704, 8, 3, "16x16"), (190, 252, 248, 24, 3, "32x32"), (300, 508, 1000, 24, 3, "32x32"),
+          (200, 512, 512, 64, 3, "32x48"), (300, 1024, 1024, 16, 3, "general"),
+          # few rows that share many columns of cold weights
+          (200, 2048, 2048, 16, 1, "general"), (256, 1792, 1792, 16, 1, "general"), (85, 2048, 2048, 16, 3, "general"), (16, 2044, 2048, 8, 3, "16x32")]
 
 
 def test_the_frozen_cases_reach_their_tiles():
