@@ -46,24 +46,26 @@ __device__ __forceinline__ void write_rows_from_dT(bf16_t* __restrict__ dst, con
 }
 
 // ======================================================================== forward
-// KG key groups of NW waves each; a wave owns 32 queries, and the key tiles (64 keys) of the causal range are dealt
-// out to the key groups in turn (group kg takes tiles kg, kg + KG, ..).  Every group keeps its own running max, row
+// Two key groups of four waves each; a wave owns 32 queries, and the key tiles (64 keys) of the causal range are dealt
+// out to the key groups in turn (group kg takes tiles kg, kg + 2, ..).  Every group keeps its own running max, row
 // sum and output accumulator over its tiles and the groups are merged once at the end through LDS (the usual
 // two-state softmax merge).  With KG = 2 a SIMD runs two waves, so one wave's softmax arithmetic overlaps the other's
-// MFMAs; at T = 1024 with 32 heads there are otherwise only as many 32-query waves as the chip has SIMDs.
+// MFMAs; at T = 1024 with 32 heads there are otherwise only as many 32-query waves as the chip has SIMDs.  Four waves a group
+// beat two there (a K/V tile is shared by more queries; the extra workgroups of two do not overlap enough).
 // K and V tiles come by direct-to-LDS loads, one tile ahead in the group's other buffer, with one barrier a tile; Q and O pass through LDS
 // too (straight from and to memory every instruction touches 32 rows).  us with tiles staged through registers (two barriers a tile, Q and
 // O by rows) and with this, heads of 128 / 64: 1024 tokens, 32 heads 28.8 and 25.4 / 16 heads 17.3 and 15.3; 2048 tokens 54.8 and 47.5 /
 // 30.8 and 28.9; 5120 tokens, 32 heads of 128 277 and 246 (870 TFLOP/s; the rest is the softmax between the two products of a tile, and at
 // 1024 tokens the heaviest block: 8 passes of two tiles where the mean is 4.5).  The order of every sum is the same in both.
 // DIRECT: q, k and v start at multiples of 4 bytes (else their tiles come through registers)
-template <int DH, int NW, int KG, bool DIRECT>
-__global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+constexpr int ATTN_NW = 4, ATTN_KG = 2;      // waves a group, groups
+template <int DH, bool DIRECT>
+__global__ __launch_bounds__(ATTN_KG * ATTN_NW * 64, 2) void attn_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                 const bf16_t* __restrict__ v, long ldq, int T,
                                                                 bf16_t* __restrict__ o, long ldo, float* __restrict__ lse,
                                                                 float scale_log2e) {
     using C = AttnCfg<DH>;
-    constexpr int NT = NW * 64, QB = NW * 32;
+    constexpr int NW = ATTN_NW, KG = ATTN_KG, NT = NW * 64, QB = NW * 32;
     constexpr int RB = DH * 2, TB = 64 * RB, NI = TB / 4096;      // bytes of a row, of a tile; fetches per wave and tile
     static_assert(NW == 4 && KG == 2, "four waves fetch a tile; the block's queries fit one buffer");
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -184,31 +186,28 @@ __global__ __launch_bounds__(NW * 64 * KG, 2) void attn_fwd_kernel(const bf16_t*
                 }
             }
     }
-    if constexpr (KG > 1) {
-        // merge the key groups into group 0: values of thread `tid` are kept NT apart (no bank conflicts)
-        static_assert(KG == 2, "two key groups");
-        float* mg = (float*)smem_raw;
-        __syncthreads();                            // every group is done with its K / V tiles
-        if (kg == 1) {
-#pragma unroll
-            for (int dt = 0; dt < C::ND; ++dt)
-#pragma unroll
-                for (int vv = 0; vv < 16; ++vv) mg[(dt * 16 + vv) * NT + tid] = oacc[dt][vv];
-            mg[(C::ND * 16) * NT + tid] = m;
-            mg[(C::ND * 16 + 1) * NT + tid] = lpart;
-        }
-        __syncthreads();
-        if (kg == 1) return;
-        const float m1 = mg[(C::ND * 16) * NT + tid], l1 = mg[(C::ND * 16 + 1) * NT + tid];
-        const float mt = fmaxf(m, m1);
-        const float a0 = fast_exp2((m - mt) * scale_log2e), a1 = fast_exp2((m1 - mt) * scale_log2e);
+    // merge the key groups into group 0: values of thread `tid` are kept NT apart (no bank conflicts)
+    float* mg = (float*)smem_raw;
+    __syncthreads();                            // every group is done with its K / V tiles
+    if (kg == 1) {
 #pragma unroll
         for (int dt = 0; dt < C::ND; ++dt)
 #pragma unroll
-            for (int vv = 0; vv < 16; ++vv) oacc[dt][vv] = oacc[dt][vv] * a0 + mg[(dt * 16 + vv) * NT + tid] * a1;
-        lpart = lpart * a0 + l1 * a1;
-        m = mt;
+            for (int vv = 0; vv < 16; ++vv) mg[(dt * 16 + vv) * NT + tid] = oacc[dt][vv];
+        mg[(C::ND * 16) * NT + tid] = m;
+        mg[(C::ND * 16 + 1) * NT + tid] = lpart;
     }
+    __syncthreads();
+    if (kg == 1) return;
+    const float m1 = mg[(C::ND * 16) * NT + tid], l1 = mg[(C::ND * 16 + 1) * NT + tid];
+    const float mt = fmaxf(m, m1);
+    const float a0 = fast_exp2((m - mt) * scale_log2e), a1 = fast_exp2((m1 - mt) * scale_log2e);
+#pragma unroll
+    for (int dt = 0; dt < C::ND; ++dt)
+#pragma unroll
+        for (int vv = 0; vv < 16; ++vv) oacc[dt][vv] = oacc[dt][vv] * a0 + mg[(dt * 16 + vv) * NT + tid] * a1;
+    lpart = lpart * a0 + l1 * a1;
+    m = mt;
     const float ltot = lpart + __shfl_xor(lpart, 32, 64), inv = 1.f / ltot;
     if (t_abs < T && g == 0) lse[(long)head * T + t_abs] = (m * scale_log2e + log2f(ltot)) * 0.6931471805599453f;
     // the wave's 32 rows leave through LDS (behind what the merge reads), so that a row is written in 16-byte pieces.  (Bank
@@ -662,21 +661,15 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_fused_kernel(
 }
 
 // ======================================================================== launchers
-// waves per key group of the forward kernel (32 queries each).  Measured at T = 1024, 32 heads of 128:
-// 4 waves beat 2 (a K/V tile is shared by more queries; the extra workgroups of 2 do not overlap enough).
-constexpr int ATTN_NW = 4;
-// its key groups (see attn_fwd_kernel)
-constexpr int ATTN_KG = 2;
-
-template <int DH, int NW, int KG>
+template <int DH>
 static hipError_t run_fwd(dim3 grid, const bf16_t* q, const bf16_t* k, const bf16_t* v, long ldq, int T, bf16_t* o,
                           long ldo, float* lse, float sl2, hipStream_t s) {
-    const size_t lds = (size_t)KG * 4 * 64 * DH * sizeof(bf16_t);
+    const size_t lds = (size_t)ATTN_KG * 4 * 64 * DH * sizeof(bf16_t);
     const bool direct = loads_to_lds(q) && loads_to_lds(k) && loads_to_lds(v);
-    auto kern = direct ? attn_fwd_kernel<DH, NW, KG, true> : attn_fwd_kernel<DH, NW, KG, false>;
+    auto kern = direct ? attn_fwd_kernel<DH, true> : attn_fwd_kernel<DH, false>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    kern<<<grid, NW * 64 * KG, lds, s>>>(q, k, v, ldq, T, o, ldo, lse, sl2);
+    kern<<<grid, ATTN_KG * ATTN_NW * 64, lds, s>>>(q, k, v, ldq, T, o, ldo, lse, sl2);
     return hipGetLastError();
 }
 
@@ -685,10 +678,9 @@ hipError_t launch_attention_fwd(const bf16_t* q, const bf16_t* k, const bf16_t* 
     if (T <= 0 || n_heads <= 0) return hipSuccess;
     if ((ldq & 7) || (ldo & 7)) return hipErrorInvalidValue;
     const float sl2 = (1.f / sqrtf((float)d_head)) * 1.4426950408889634f;
-    constexpr int NW = ATTN_NW, KG = ATTN_KG;
-    dim3 grid(cdiv(T, NW * 32), n_heads);
-    if (d_head == 128) return run_fwd<128, NW, KG>(grid, q, k, v, ldq, T, o, ldo, lse, sl2, s);
-    if (d_head == 64) return run_fwd<64, NW, KG>(grid, q, k, v, ldq, T, o, ldo, lse, sl2, s);
+    dim3 grid(cdiv(T, ATTN_NW * 32), n_heads);
+    if (d_head == 128) return run_fwd<128>(grid, q, k, v, ldq, T, o, ldo, lse, sl2, s);
+    if (d_head == 64) return run_fwd<64>(grid, q, k, v, ldq, T, o, ldo, lse, sl2, s);
     return hipErrorInvalidValue;
 }
 
