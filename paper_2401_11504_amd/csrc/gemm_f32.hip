@@ -986,28 +986,27 @@ static int arrange_f32(const F32Product* prods, int n, F32Batch& grp) {
     int best = 0;
     for (int c = 1; c < (split ? 5 : 3); ++c)
         if (f32_cost(grp, costs[c]) < f32_cost(grp, costs[best])) best = c;
-    // Low-rank products of long contractions, operands that can be fetched straight into LDS: 3 us and 11.4 a megabyte of the busiest CU's
-    // operands, against what the direct kernel's model says of itself, which is that of a whole step, 16 us below what this launch takes at
-    // 1024 tokens.  (Contractions of 768: 6.8 us either way.)
-    bool waves = best <= 1;
+    // Low-rank products of long contractions, operands that can be fetched straight into LDS.  Launches of H and dH by themselves, 672 sizes of 17 to 4096
+    // tokens, widths 1024 to 5000, ranks 4 to 256, us in f32_direct_kernel (the instance the costs above pick) and here, 16x16 | 16x32: up to one 16x16 tile a
+    // CU 0.69 and 0.84 of the direct one's time where rows are whole 128-byte lines (333 tokens, 4096 x 4096, rank 64: 18.8, 12.5 | 13.6; 64 tokens,
+    // 2048 x 2048, rank 8: 10.1, 7.0 | 8.6), 0.96 and 1.03 where they are not (64, 2500 x 2500, rank 64: 10.8, 10.4 | 12.2), and from rank 128 on there no gain
+    // (33, 1100 x 2052, rank 128: 8.2, 10.1 | 9.3; 128, 1100 x 2052, rank 256: 8.5, 10.8 | 12.2); beyond, 0.82 and 0.73 (1024, 4096 x 4096, rank 64: 30.7,
+    // 17.1 | 14.3; 1400, 2048 x 2048, rank 64: 21.1, 14.0 | 14.1; 4096, 2500 x 2500, rank 64: 40.4, 49.2 | 41.1).  Where the costs pick larger tiles
+    // (ranks of 256, 2048 tokens) 16x32 takes 0.64 to 1.12 of their time: not taken.  Half of a 16x32 tile is empty up to rank 16 (4096, 4096 x 4096, rank 8: 26.7,
+    // 22.6 | 24.2).
+    bool waves = best <= 1, lines = true;
+    long tiles = 0;
+    int rank = 0;
     for (int k = 0; k < n; ++k) {
         const F32Product& q = grp.p[k];
         waves &= q.kind != F32_MN && q.K2 == 0 && !q.p_new && q.N <= 256 && q.K >= 1024 && ((q.lda | q.ldb | q.ldc | q.N | q.K) & 3) == 0 &&
                  (((uintptr_t)q.A | (uintptr_t)q.B) & 15) == 0;
+        lines &= (q.lda & 31) == 0 && (q.kind == F32_KN || (q.ldb & 31) == 0);
+        tiles += (long)cdiv(q.M, 16) * cdiv(q.N, 16);
+        rank = q.N > rank ? q.N : rank;
     }
-    if (waves) {
-        double us[2];
-        for (int fn = 1; fn <= 2; ++fn) {
-            long tiles = 0, K = 0;
-            for (int k = 0; k < n; ++k) {
-                tiles += (long)cdiv(grp.p[k].M, 16) * cdiv(grp.p[k].N, 16 * fn);
-                K = grp.p[k].K > K ? grp.p[k].K : K;
-            }
-            us[fn - 1] = 3.0 + 11.4e-6 * 64 * (1 + fn) * K * (double)((tiles + 255) / 256);
-        }
-        const int pick = us[1] < us[0];
-        if (us[pick] < f32_cost(grp, costs[best])) return 7 + pick;
-    }
+    if (waves && tiles > 256 && rank > 16) return 8;
+    if (waves && (lines || rank <= 64)) return 7;
     return best;
 }
 

@@ -12,7 +12,10 @@ W16, W32, D16 = "waves-16x16", "waves-16x32", "direct-16x16"
 #        T, d_in, d_out, r, name of the launch of H and dH
 CASES = [(1, 2048, 2048, 4, W16), (17, 1100, 2052, 20, W16), (250, 1060, 2100, 36, W16), (64, 4096, 2036, 8, W16),
          (1024, 4096, 4096, 64, W32), (1009, 2052, 2076, 60, W32), (530, 4100, 4124, 56, W32),
-         (1024, 4097, 4096, 64, D16), (1024, 4096, 4096, 62, D16), (512, 768, 768, 8, D16)]
+         (1024, 4097, 4096, 64, D16), (1024, 4096, 4096, 62, D16), (512, 768, 768, 8, D16),
+         # one 16x16 tile a CU and one more; rows that are no whole lines, ranks of 64 and 68
+         (512, 1024, 1024, 64, W16), (513, 1024, 1024, 64, W32), (40, 1060, 1028, 64, W16), (40, 1060, 1028, 68, D16), (40, 1056, 1024, 68, W16),
+         (1400, 1028, 1036, 64, W32), (2100, 1024, 1024, 16, W16), (2100, 1024, 1024, 20, W32)]
 
 
 def test_sizes_reach_their_kernel():
