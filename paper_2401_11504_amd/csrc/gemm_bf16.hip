@@ -849,9 +849,11 @@ hipError_t launch_gemm_nt(const GemmNT& g, hipStream_t s) {
 // Hs = s X A^T, dH = s dY B (N = the rank, or three of them), and every product of a small decoder or a short sample.
 // One launch: a workgroup computes a (16 FM) x (16 FN) tile over the whole contraction, each of its eight waves an eighth of it in
 // 64-wide pieces through a ring of its own (direct-to-LDS loads of whole 128-byte rows, ST pieces in flight, no barrier), and adds
-// the eight sums up through LDS in a fixed order.  What bounds it is the operand stream of a CU (some 88 GB/s with the weights of the
-// factor in the L2s): the tile is the one that leaves the busiest CU the fewest bytes, and the rings are small enough for two workgroups
-// per CU, whose loads, sums and stores then overlap.
+// the eight sums up through LDS in a fixed order.  What bounds it, in calls back to back, is the operand stream of a CU (some 88 GB/s with the
+// weights of the factor in the L2s): the tile is the one that leaves the busiest CU the fewest bytes, and up to 32x48 the rings (48 to 80 KB) are small
+// enough for two workgroups per CU, whose loads, sums and stores then overlap; wider tiles (96 to 128 KB) have one.  Behind another kernel a launch takes
+// 1 to 3 us more: in an update of 1024 tokens, 64 columns of 4096 behind attention and a norm 7.3 and 8.0, beside the dA/dB launch of the other stream
+// 21.2, 64 of 11008 14.5, 192 of 4096 10.8, 64 x 3 12.4.
 // us against 64x64 tiles with the contraction split over up to 16 workgroups and a reduce launch behind (operands cold, calls back to back;
 // columns x batch of a contraction of 4096): 1024 rows, 192: 8.0 and 12.8; 64: 5.6 and 9.7; 64 x 3: 8.5 and 13.5; 2048 rows: 9.8 and 15.4,
 // 6.7 and 12.9, 12.6 and 18.1; 5120 rows: 20 and 25, 16 and 16, 22 and 28; 64 of a contraction of 11008: 512 rows 9.9 and 14.3, 1024 rows
