@@ -341,8 +341,9 @@ tl_status tl_k_gemm_nt(const uint16_t* A, int32_t lda, const uint16_t* B, int32_
                        size_t workspace_elems, void* hip_stream);
 /* The narrow products of the low-rank branch: for b < batch, C[:, b N .. b N + N - 1] = alpha * A[:, b K .. b K + K - 1] B_b^T, A bf16
  * [M, batch * K], B_b the rows b N .. of B [batch * N, K], C bf16 [M, batch * N]; lda / ldb row strides, K, lda, ldb multiples of 8.
- * tl_k_low_rank_plan: the tile that dense operands of these sizes get ("16x16", "16x32", "32x32", "32x48", "32x64", "48x64", "64x64"), or
- * "general" where they go through tl_k_gemm_nt's kernels; host only. */
+ * workspace as for tl_k_gemm_nt.  tl_k_low_rank_plan: the tile that dense operands of these sizes get with a workspace of workspace_elems floats
+ * ("16x16", "16x32", "32x32", "32x48", "32x64", "48x64", "64x64"), or "general" where they go through tl_k_gemm_nt's kernels (which refuse what they
+ * cannot take); host only. */
 tl_status tl_k_low_rank(const uint16_t* A, int32_t lda, const uint16_t* B, int32_t ldb, int32_t M, int32_t N, int32_t K, int32_t batch,
                         float alpha, uint16_t* C, float* workspace, size_t workspace_elems, void* hip_stream);
 tl_status tl_k_low_rank_plan(int32_t M, int32_t N, int32_t K, int32_t batch, size_t workspace_elems, char* name_out, size_t name_cap);
